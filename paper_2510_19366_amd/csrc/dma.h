@@ -1,0 +1,51 @@
+// Wave-wide copies global -> LDS and the waits that go with them, shared by the kernels whose
+// operands do not pass through registers.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+namespace mp {
+
+__device__ __forceinline__ uint32_t lds_offset(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
+}
+
+// One wave-wide copy: lane i's 16 bytes at base + voff land at LDS address lds + 16 i.  m0 carries
+// the LDS address; the compiler reserves m0 and does not accept it in a clobber list, so the value
+// it may be keeping there is saved and put back.
+__device__ __forceinline__ void copy_to_lds16(const void* base, uint32_t voff, uint32_t lds) {
+  uint32_t keep;
+  asm volatile(
+      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, %2\n\ts_mov_b32 m0, %0"
+      : "=&s"(keep)
+      : "v"(voff), "s"(base), "s"(lds)
+      : "memory");
+}
+
+// until at most N of this wave's vector memory operations are pending (they retire in issue order)
+template <int N>
+__device__ __forceinline__ void wait_vmem() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// s_barrier without the wait for outstanding copies that __syncthreads() would add; LDS accesses
+// stay on their side of it
+__device__ __forceinline__ void raw_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// f(integral_constant<I>) for I = BEGIN .. END - 1: a loop whose index can be a template argument
+template <int BEGIN, int END, class F>
+__device__ __forceinline__ void static_loop(F&& f) {
+  if constexpr (BEGIN < END) {
+    f(std::integral_constant<int, BEGIN>{});
+    static_loop<BEGIN + 1, END>(f);
+  }
+}
+
+}  // namespace mp

@@ -77,6 +77,22 @@ hipError_t launch_combine(int dtype, const void* y, const int32_t* slot_of_pair,
 
 int num_cus();  // compute units of the current device (cached)
 
+// Kernels that need more than the default 64 KiB of dynamic LDS (the CU has 160 KiB): the
+// attribute is set once per kernel and device, so the launch path makes no other runtime call
+// (which also keeps it usable while the caller's stream is being captured into a graph, after one
+// eager call).
+template <auto Kern>
+inline hipError_t raise_lds_limit(size_t bytes) {
+  static bool done[64] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
+  if (dev >= 0 && done[dev]) return hipSuccess;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(Kern),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e == hipSuccess && dev >= 0) done[dev] = true;
+  return e;
+}
+
 // bf16 helpers (bit patterns in uint16_t)
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) {
   return __uint_as_float(((uint32_t)b) << 16);

@@ -1,5 +1,6 @@
 // Route stage (Sec. 3.2.2, expanded linear gate): router logits with a fixed
 // summation order, then per-token top-k_t and softmax weights.
+#include "dma.h"
 #include "kernels.h"
 
 namespace mp {
@@ -24,290 +25,213 @@ hipError_t launch_expand_k(int R, int T, const int32_t* req_k, const int32_t* re
 // ---------------------------------------------------------------- logits on the matrix cores
 // Every logit is ONE chain of d binary32 fused multiply-adds over the hidden index in
 // ascending order, then the fp32 bias add: the fixed summation order is what makes the
-// routing reproducible bit for bit.  The rank-1 fp32 MFMA forms add ONE k term per
-// instruction, D = a * b + D with one rounding per output (checked on the device against
-// fmaf chains of 4096 terms, subnormal sums included: bit-identical), so issuing one per k in
-// ascending order computes exactly that chain, at twice the rate of unpacked v_fma_f32.  No
-// split-K, no reordering.
+// routing reproducible bit for bit.  v_mfma_f32_16x16x4_f32 adds its four k terms as four fused
+// multiply-adds in ascending k with one rounding each (checked on the device against fmaf
+// chains, subnormal sums included: bit-identical), so issuing it for k = 0, 4, 8, ... computes
+// exactly that chain.  No split-K, no reordering.
 //
-// Large problems: v_mfma_f32_32x32x1_2b_f32.
+// What bounds it: the matrix pipe.  One instruction takes 32 cycles whether or not it depends on
+// the previous one, so one chain per wave and one wave per SIMD already run at the full rate, and
+// d = 2048 is 6.8 us for every 16 x 16 sub-tile a SIMD works through.  The fp32 matrix instructions
+// do NOT overlap with vector ALU work (measured: an ALU instruction between two of them costs its
+// 4 cycles plus about 16 for the change-over, LDS reads and scalar work nothing), so the loop
+// contains no vector ALU instruction at all:
+//   * bf16 operands are widened by the LDS read: ds_read_u16_d16_hi writes the upper half of a
+//     register whose lower half stays zero;
+//   * the eight LDS addresses of a lane never change: ring slot, sub-tile and k step are immediate
+//     offsets (the stage loop is unrolled over the ring);
+//   * the copies global -> LDS advance scalar bases.
 //
-// Workgroup tile 128 tokens x 128 sub-experts, 4 waves as 2 x 2, wave tile 64 x 64: lane l
-// feeds token row l and sub-expert row l of the wave tile; with the A-block broadcast
-// (cbsz = 1) instruction `ab` multiplies token block ab (32 rows) by both 32-column blocks.
-// Operands are staged per K slab of 64 bytes per row in LDS rows of 80 bytes (the 16 bytes
-// of padding make the per-lane row reads conflict-free).
-typedef __attribute__((__vector_size__(32 * sizeof(float)))) float f32x32;
-constexpr int LM_ROWB = 80;  // LDS bytes per row: 64 of data + 16 of padding
-
-template <typename InT>
-__device__ __forceinline__ float lm_elem(const uint4 (&q)[4], int i);
-template <>
-__device__ __forceinline__ float lm_elem<float>(const uint4 (&q)[4], int i) {
-  const uint32_t w[4] = {q[i >> 2].x, q[i >> 2].y, q[i >> 2].z, q[i >> 2].w};
-  return __uint_as_float(w[i & 3]);
-}
-template <>
-__device__ __forceinline__ float lm_elem<uint16_t>(const uint4 (&q)[4], int i) {
-  const uint32_t w[4] = {q[i >> 3].x, q[i >> 3].y, q[i >> 3].z, q[i >> 3].w};
-  const uint32_t v = w[(i >> 1) & 3];
-  return __uint_as_float((i & 1) ? (v & 0xffff0000u) : (v << 16));
-}
-
-template <typename InT>
-__global__ __launch_bounds__(256) void logits_mfma_kernel(const InT* __restrict__ x,
-                                                          const InT* __restrict__ w,
-                                                          const float* __restrict__ bias,
-                                                          float* __restrict__ logits,
-                                                          int32_t* __restrict__ hdr, int T, int d,
-                                                          int E) {
-  constexpr int KB = 64 / sizeof(InT);  // K elements per slab: 32 bf16 or 16 fp32
-  __shared__ __align__(16) unsigned char sm[2][256 * LM_ROWB];  // rows 0..127 tokens, 128..255 sub-experts
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int wm = wv >> 1, wn = wv & 1;
-  if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) hdr[HDR_FLAGS] = 0;
-  const int m0 = blockIdx.y * 128, n0 = blockIdx.x * 128;
-
-  // loader: 16-byte chunk lc of rows lr + 64 i
-  const int lc = tid & 3, lr = tid >> 2;
-  auto row_src = [&](int row) {
-    const InT* base = row < 128 ? x + (size_t)min(m0 + row, T - 1) * d
-                                : w + (size_t)min(n0 + row - 128, E - 1) * d;
-    return reinterpret_cast<const unsigned char*>(base) + lc * 16;
-  };
-  const unsigned char* src0 = row_src(lr);
-  const unsigned char* src1 = row_src(lr + 64);
-  const unsigned char* src2 = row_src(lr + 128);
-  const unsigned char* src3 = row_src(lr + 192);
-  uint4 pre0, pre1, pre2, pre3;  // named registers: an indexed array here ends up in scratch memory
-#define LM_GLOAD(k0_)                                                                   \
-  do {                                                                                  \
-    const size_t o_ = (size_t)(k0_) * sizeof(InT);                                      \
-    pre0 = *reinterpret_cast<const uint4*>(src0 + o_);                                  \
-    pre1 = *reinterpret_cast<const uint4*>(src1 + o_);                                  \
-    pre2 = *reinterpret_cast<const uint4*>(src2 + o_);                                  \
-    pre3 = *reinterpret_cast<const uint4*>(src3 + o_);                                  \
-  } while (0)
-#define LM_SSTORE(buf_)                                                                 \
-  do {                                                                                  \
-    unsigned char* b_ = &sm[buf_][lr * LM_ROWB + lc * 16];                              \
-    *reinterpret_cast<uint4*>(b_) = pre0;                                               \
-    *reinterpret_cast<uint4*>(b_ + 64 * LM_ROWB) = pre1;                                \
-    *reinterpret_cast<uint4*>(b_ + 128 * LM_ROWB) = pre2;                               \
-    *reinterpret_cast<uint4*>(b_ + 192 * LM_ROWB) = pre3;                               \
-  } while (0)
-
-  f32x32 acc0, acc1;
-#pragma unroll
-  for (int v = 0; v < 32; ++v) {
-    acc0[v] = 0.0f;
-    acc1[v] = 0.0f;
-  }
-  const int a_off = (wm * 64 + lane) * LM_ROWB, b_off = (128 + wn * 64 + lane) * LM_ROWB;
-
-  LM_GLOAD(0);
-  LM_SSTORE(0);
-  __syncthreads();
-  int buf = 0;
-  for (int k0 = 0; k0 < d; k0 += KB) {  // d % 64 == 0, so d % KB == 0
-    const bool more = k0 + KB < d;
-    if (more) LM_GLOAD(k0 + KB);
-    uint4 qa[4], qb[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      qa[c] = *reinterpret_cast<const uint4*>(&sm[buf][a_off + c * 16]);
-      qb[c] = *reinterpret_cast<const uint4*>(&sm[buf][b_off + c * 16]);
-    }
-#pragma unroll
-    for (int i = 0; i < KB; ++i) {  // ascending k: one fused multiply-add per logit and step
-      const float a = lm_elem<InT>(qa, i), b = lm_elem<InT>(qb, i);
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x1f32(a, b, acc0, 1, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x1f32(a, b, acc1, 1, 1, 0);
-    }
-    if (more) LM_SSTORE(buf ^ 1);
-    __syncthreads();
-    buf ^= 1;
-  }
-
-  // accumulator v of lane l: column block j = v / 16, row 8 ((v % 16) / 4) + 4 (l / 32) + v % 4
-  // of the 32-row token block, column l % 32
-#pragma unroll
-  for (int ab = 0; ab < 2; ++ab) {
-#pragma unroll
-    for (int v = 0; v < 32; ++v) {
-      const int vv = v & 15;
-      const int row = m0 + wm * 64 + ab * 32 + 8 * (vv >> 2) + 4 * (lane >> 5) + (vv & 3);
-      const int col = n0 + wn * 64 + (v >> 4) * 32 + (lane & 31);
-      if (row < T && col < E) {
-        float r = ab == 0 ? acc0[v] : acc1[v];
-        if (bias != nullptr) r = r + bias[col];
-        logits[(size_t)row * E + col] = r;
-      }
-    }
-  }
-#undef LM_GLOAD
-#undef LM_SSTORE
-}
-
-// Small problems (few 128 x 128 tiles): the per-logit chain of d dependent FMAs is what takes
-// the time, so the tile per wave is made as small as the matrix cores allow.
-// v_mfma_f32_4x4x1_16b_f32 performs 16 independent 4 x 4 rank-1 updates in 2 passes (8 cycles):
-// block b takes its 4 A values from lanes 4b..4b+3 and its 4 B values from the same lanes, and
-// lane 4b + j holds column j of block b, rows 0..3 in its 4 accumulator registers.  Again one
-// binary32 FMA per logit and k.  With block b = (p, q) multiplying tokens 4p..4p+3 by
-// sub-experts 4q..4q+3 (lane 4b + i feeds token 4p + i and sub-expert 4q + i) one instruction
-// covers 16 tokens x 16 sub-experts.  A dependent chain of these instructions issues only
-// every 44 to 64 cycles, so where the problem has enough work a wave keeps four chains going:
-// NSUB x NSUB such sub-tiles per wave (NSUB = 2: 32 x 32 per wave, 64 x 64 per workgroup of
-// 2 x 2 waves; NSUB = 1: 16 x 16 and 32 x 32, four times as many waves for the smallest
-// problems).
-// Operands are widened to fp32 once, when a slab of 32 k is stored to LDS (rows of 128 bytes
-// + 16 of padding: conflict-free 16-byte reads), so the inner loop is LDS reads and MFMAs only.
-// Global loads run PF slabs ahead in registers; LDS holds two slabs; one barrier per slab.
+// Operands: slabs of 128 bytes per row (64 bf16 or 32 fp32 of K) go global -> LDS directly into
+// a ring of NS stages, NS - 2 of them in flight while one is multiplied and the next one is
+// already published (its first fragments are read early).  Lane l feeds row l & 15 and k = l >> 4
+// of a step.  Chunk c (16 bytes) of row r sits at position c ^ ((r >> 1) & 7): conflict-free reads.
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
-constexpr int L4_ROWB = 144, L4_KB = 32;
 
-template <typename InT, int NSUB>
-__global__ __launch_bounds__(256) void logits_mfma4_kernel(const InT* __restrict__ x,
-                                                           const InT* __restrict__ w,
-                                                           const float* __restrict__ bias,
-                                                           float* __restrict__ logits,
-                                                           int32_t* __restrict__ hdr, int T, int d,
-                                                           int E) {
-  constexpr int ROW_GB = L4_KB * sizeof(InT);      // global bytes per row and slab: 64 or 128
-  constexpr int CPR = ROW_GB / 16;                  // 16-byte chunks per row: 4 or 8
-  constexpr int BT = 32 * NSUB;                     // tokens (and sub-experts) per workgroup
-  constexpr int L4_ROWS = 2 * BT;                   // LDS rows: BT tokens, then BT sub-experts
-  constexpr int CH = L4_ROWS * CPR / 256;           // chunks per thread and slab: 1, 2 or 4
-  constexpr int PF = CH >= 4 ? 4 : 8;               // slabs in flight
-  __shared__ __align__(16) unsigned char sm[2][L4_ROWS * L4_ROWB];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int wy = wv >> 1, wx = wv & 1;
-  if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) hdr[HDR_FLAGS] = 0;
-  const int m0 = blockIdx.y * BT, n0 = blockIdx.x * BT;
+template <typename InT, int WM, int WN, int MT, int NT, int NS>
+struct LogitsCfg {  // WM x WN waves, MT x NT sub-tiles of 16 x 16 per wave
+  static constexpr int NW = WM * WN, BT = WM * MT * 16, BE = WN * NT * 16, ROWS = BT + BE;
+  static constexpr int CP = ROWS / 8 / NW;  // copy instructions (8 rows) per wave and stage
+  static constexpr int STAGE = ROWS * 128;
+  static constexpr int LDS_BYTES = NS * STAGE;
+  static constexpr int KB = 128 / (int)sizeof(InT);
+  static constexpr int STEPS = KB / 4;      // matrix steps (4 k) per stage
+  static constexpr int NF = MT + NT;        // fragments per step
+  // fragment sets and how many steps ahead they are read: lgkmcnt counts up to 15 reads
+  static constexpr int R = NF <= 2 ? 8 : 4, PD = NF <= 2 ? 7 : NF <= 5 ? 3 : NF <= 7 ? 2 : 1;
+  static_assert(CP * NW * 8 == ROWS && BT % 8 == 0, "whole copies");
+  static_assert(NS >= 3 && (NS - 1) * CP < 63 && PD * NF <= 15 && STEPS % R == 0, "counters");
+  static_assert(LDS_BYTES <= 65536, "immediate offsets of 16 bits");
+};
 
-  // loader: chunk id c = tid + 256 j -> row c / CPR, 16-byte piece c % CPR
-  const unsigned char* src[CH];
-  int dst[CH];
+// value of this lane's element: bf16 into the upper half (the lower half stays as it is: zero), fp32 whole
+template <typename InT, int OFF>
+__device__ __forceinline__ void read_elem(uint32_t& v, uint32_t addr) {
+  if constexpr (sizeof(InT) == 2)
+    asm volatile("ds_read_u16_d16_hi %0, %1 offset:%2" : "+v"(v) : "v"(addr), "n"(OFF));
+  else
+    asm volatile("ds_read_b32 %0, %1 offset:%2" : "+v"(v) : "v"(addr), "n"(OFF));
+}
+
+template <typename InT, int WM, int WN, int MT, int NT, int NS>
+__global__ __launch_bounds__(64 * WM * WN) void logits_kernel(const InT* __restrict__ x,
+                                                              const InT* __restrict__ w,
+                                                              const float* __restrict__ bias,
+                                                              float* __restrict__ logits,
+                                                              int32_t* __restrict__ hdr, int T, int d,
+                                                              int E) {
+  using C = LogitsCfg<InT, WM, WN, MT, NT, NS>;
+  constexpr int CP = C::CP, PD = C::PD, R = C::R, NF = C::NF;
+  extern __shared__ __align__(16) unsigned char lg_smem[];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wv / WN, wn = wv % WN;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) hdr[HDR_FLAGS] = 0;
+  const int m0 = blockIdx.y * C::BT, n0 = blockIdx.x * C::BE;
+
+  // producer: copy j of this wave takes rows 8 (wv CP + j) .. + 7 of the stage (tokens first)
+  const unsigned char* base[CP];
+  uint32_t voff[CP];
 #pragma unroll
-  for (int j = 0; j < CH; ++j) {
-    const int c = tid + 256 * j, row = c / CPR, pc = c % CPR;
-    const InT* base = row < BT ? x + (size_t)min(m0 + row, T - 1) * d
-                               : w + (size_t)min(n0 + row - BT, E - 1) * d;
-    src[j] = reinterpret_cast<const unsigned char*>(base) + pc * 16;
-    dst[j] = row * L4_ROWB + pc * (sizeof(InT) == 2 ? 32 : 16);
+  for (int j = 0; j < CP; ++j) {
+    const int r0 = (wv * CP + j) * 8, row = r0 + (lane >> 3);
+    const bool tok = r0 < C::BT;  // the same for the whole copy
+    base[j] = reinterpret_cast<const unsigned char*>(tok ? x + (size_t)m0 * d : w + (size_t)n0 * d);
+    const int rr = tok ? min(row, T - 1 - m0) : min(row - C::BT, E - 1 - n0);
+    voff[j] = (uint32_t)rr * (uint32_t)(d * (int)sizeof(InT)) + (uint32_t)(((lane & 7) ^ ((row >> 1) & 7)) * 16);
   }
-  auto sstore = [&](int buf, int j, uint4 v) {  // widen to fp32 (exact) and store
-    unsigned char* o = &sm[buf][dst[j]];
-    if (sizeof(InT) == 2) {
-      const uint4 lo = {v.x << 16, v.x & 0xffff0000u, v.y << 16, v.y & 0xffff0000u};
-      const uint4 hi = {v.z << 16, v.z & 0xffff0000u, v.w << 16, v.w & 0xffff0000u};
-      *reinterpret_cast<uint4*>(o) = lo;
-      *reinterpret_cast<uint4*>(o + 16) = hi;
-    } else {
-      *reinterpret_cast<uint4*>(o) = v;
+  const uint32_t lds0 = lds_offset(lg_smem);
+  const uint32_t dst0 = lds0 + (uint32_t)(wv * CP) * 1024u;
+  const int ns = d / C::KB;  // d % 64 == 0
+  auto produce = [&](int stage, int slot) {
+    if (stage < ns) {
+#pragma unroll
+      for (int j = 0; j < CP; ++j)
+        copy_to_lds16(base[j] + (size_t)stage * 128, voff[j], dst0 + (uint32_t)(slot * C::STAGE + j * 1024));
     }
   };
+#pragma unroll
+  for (int i = 0; i < NS - 1; ++i) produce(i, i);
 
-  const int blk = lane >> 2, li = lane & 3, p = blk >> 2, q = blk & 3;
-  const int a_off = (wy * 16 * NSUB + 4 * p + li) * L4_ROWB;
-  const int b_off = (BT + wx * 16 * NSUB + 4 * q + li) * L4_ROWB;
-
-  const int ns = d / L4_KB;  // d % 64 == 0
-  uint4 pre[PF][CH];
+  // consumer: addresses of this lane's element of chunk c, in token rows and in sub-expert rows
+  const int r = lane & 15, g = lane >> 4;
+  uint32_t at[8], bt[8];
 #pragma unroll
-  for (int i = 0; i < PF; ++i)
-#pragma unroll
-    for (int j = 0; j < CH; ++j)
-      pre[i][j] = *reinterpret_cast<const uint4*>(src[j] + (size_t)(i < ns ? i : 0) * ROW_GB);
-#pragma unroll
-  for (int j = 0; j < CH; ++j) {
-    sstore(0, j, pre[0][j]);
-    pre[0][j] = *reinterpret_cast<const uint4*>(src[j] + (size_t)(PF < ns ? PF : 0) * ROW_GB);
+  for (int c = 0; c < 8; ++c) {
+    const uint32_t o = lds0 + (uint32_t)(r * 128 + ((c ^ ((r >> 1) & 7)) * 16) + g * (int)sizeof(InT));
+    at[c] = o + (uint32_t)(wm * MT) * 2048u;
+    bt[c] = o + (uint32_t)(C::BT + wn * NT * 16) * 128u;
   }
-  __syncthreads();
-
-  f32x4_t acc[NSUB][NSUB];
+  uint32_t fa[R][MT], fb[R][NT];
 #pragma unroll
-  for (int ia = 0; ia < NSUB; ++ia)
+  for (int s = 0; s < R; ++s) {
 #pragma unroll
-    for (int ib = 0; ib < NSUB; ++ib) acc[ia][ib] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-
-  for (int s0 = 0; s0 < ns; s0 += PF) {
+    for (int i = 0; i < MT; ++i) fa[s][i] = 0;
 #pragma unroll
-    for (int i = 0; i < PF; ++i) {  // slab s0 + i; s0 is a multiple of PF: ring slot and parity are static
-      const int sl = s0 + i;
-      if (sl < ns) {
-        const int nx = (i + 1) % PF, par = i & 1;
-        if (sl + 1 < ns) {
-#pragma unroll
-          for (int j = 0; j < CH; ++j) {
-            sstore(par ^ 1, j, pre[nx][j]);
-            pre[nx][j] = *reinterpret_cast<const uint4*>(
-                src[j] + (size_t)(sl + 1 + PF < ns ? sl + 1 + PF : 0) * ROW_GB);
-          }
-        }
-        const unsigned char* sa = &sm[par][a_off];
-        const unsigned char* sb = &sm[par][b_off];
-#pragma unroll
-        for (int g = 0; g < L4_KB / 4; ++g) {  // 4 k per 16-byte read, ascending k
-          f32x4_t fa[NSUB], fb[NSUB];
-#pragma unroll
-          for (int h = 0; h < NSUB; ++h) {
-            fa[h] = *reinterpret_cast<const f32x4_t*>(sa + h * 16 * L4_ROWB + g * 16);
-            fb[h] = *reinterpret_cast<const f32x4_t*>(sb + h * 16 * L4_ROWB + g * 16);
-          }
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-            for (int ia = 0; ia < NSUB; ++ia)
-#pragma unroll
-              for (int ib = 0; ib < NSUB; ++ib)
-                acc[ia][ib] = __builtin_amdgcn_mfma_f32_4x4x1f32(fa[ia][kk], fb[ib][kk], acc[ia][ib], 0, 0, 0);
-        }
-        // barrier that waits for this wave's LDS traffic only: __syncthreads() would also wait
-        // for the global loads just issued and expose their latency in every slab
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-      }
-    }
+    for (int i = 0; i < NT; ++i) fb[s][i] = 0;
   }
+  auto read = [&](auto slot_c, auto step_c) {  // the fragments of step (0 .. STEPS - 1) of ring slot
+    constexpr int SLOT = decltype(slot_c)::value, STEP = decltype(step_c)::value;
+    constexpr int CH = STEP * 4 * (int)sizeof(InT) / 16;
+    constexpr int OFF = SLOT * C::STAGE + (STEP * 4 * (int)sizeof(InT)) % 16;
+    static_loop<0, MT>([&](auto i) { read_elem<InT, OFF + decltype(i)::value * 2048>(fa[STEP % R][i], at[CH]); });
+    static_loop<0, NT>([&](auto i) { read_elem<InT, OFF + decltype(i)::value * 2048>(fb[STEP % R][i], bt[CH]); });
+  };
+  f32x4_t acc[MT][NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 
+  if (ns >= NS - 1)
+    wait_vmem<(NS - 2) * CP>();  // stage 0
+  else
+    wait_vmem<0>();
+  raw_barrier();
+  static_loop<0, PD>([&](auto s) { read(std::integral_constant<int, 0>{}, s); });
+  // Stage q: its successor's copies have landed for this wave (wait) and, behind the barrier,
+  // for all.  The barrier also frees the slot of stage q - 1 (every wave had its last fragments in
+  // registers before its last multiply), which takes stage q + NS - 1.
+  for (int q0 = 0; q0 < ns; q0 += NS) {
+    static_loop<0, NS>([&](auto slot_c) {
+      constexpr int SLOT = decltype(slot_c)::value, NSLOT = (SLOT + 1) % NS;
+      const int q = q0 + SLOT;
+      if (q >= ns) return;
+      if (q + NS - 2 < ns)
+        wait_vmem<(NS - 3) * CP>();
+      else
+        wait_vmem<0>();
+      raw_barrier();
+      produce(q + NS - 1, (SLOT + NS - 1) % NS);
+      __builtin_amdgcn_sched_barrier(0);
+      static_loop<0, C::STEPS>([&](auto step_c) {
+        constexpr int S = decltype(step_c)::value, A = S + PD;
+        if constexpr (A < C::STEPS)
+          read(slot_c, std::integral_constant<int, A>{});
+        else  // after the last stage: an old slot, not used
+          read(std::integral_constant<int, NSLOT>{}, std::integral_constant<int, A - C::STEPS>{});
+        asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(PD * NF));  // the reads of this step have returned
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int ia = 0; ia < NSUB; ++ia)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
-    for (int ib = 0; ib < NSUB; ++ib) {
-      const int col = n0 + wx * 16 * NSUB + ib * 16 + 4 * q + li;
+          for (int j = 0; j < NT; ++j)  // ascending k
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(fa[S % R][i]), __uint_as_float(fb[S % R][j]),
+                                                            acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    });
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+
+  // accumulator v of lane l: token 4 (l >> 4) + v, sub-expert l & 15 of the sub-tile
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const int col = n0 + (wn * NT + j) * 16 + r;
+    const float bv = bias != nullptr && col < E ? bias[col] : 0.0f;
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int row = m0 + wy * 16 * NSUB + ia * 16 + 4 * p + v;
+        const int row = m0 + (wm * MT + i) * 16 + 4 * g + v;
         if (row < T && col < E) {
-          float r = acc[ia][ib][v];
-          if (bias != nullptr) r = r + bias[col];
-          logits[(size_t)row * E + col] = r;
+          const float s = acc[i][j][v];
+          logits[(size_t)row * E + col] = bias != nullptr ? s + bv : s;
         }
       }
-    }
+  }
 }
 
 __global__ void clear_flags_kernel(int32_t* hdr) { hdr[HDR_FLAGS] = 0; }
 
-// 128 x 128 tiles when they fill the chip; else the small-tile kernel, with four chains per
-// wave when that still gives every SIMD a wave.
+template <typename InT, int MT, int NT, int NS>
+static void launch_logits_cfg(const InT* x, const InT* w, const float* bias, float* logits,
+                              int32_t* hdr, int T, int d, int E, hipStream_t s) {
+  using C = LogitsCfg<InT, 2, 2, MT, NT, NS>;
+  logits_kernel<InT, 2, 2, MT, NT, NS><<<dim3(cdiv(E, C::BE), cdiv(T, C::BT)), 64 * C::NW, C::LDS_BYTES, s>>>(
+      x, w, bias, logits, hdr, T, d, E);
+}
+
+// Workgroups of 2 x 2 waves on tiles of 32 x 32, 32 x 64 or 64 x 64 logits: 1, 2 or 4 sub-tiles
+// per SIMD.  The time is the number of sub-tiles the busiest SIMD works through (workgroups per
+// CU, rounded up, times sub-tiles), so the tile with the smallest such number is taken; among
+// equals the wider tile re-reads less (65 536 x 512: 0.94 ms against 1.00 and 1.04), but where
+// one or two sub-tiles are all there is its single workgroup per CU has nothing to overlap its
+// start with (4096 x 128: 20.7 us on 32 x 32, 21.5 on 32 x 64).  Measured, d = 2048, against the
+// kernels this one replaced: 16 384 x 512 0.242 ms (0.308), 8192 x 128 37 us (65), 2741 x 128
+// 20 us (35), 1 x 512 11 us (25).
 template <typename InT>
 static void launch_logits_t(const InT* x, const InT* w, const float* bias, float* logits,
                             int32_t* hdr, int T, int d, int E, hipStream_t s) {
-  const long cus = num_cus();
-  if ((long)cdiv(E, 128) * cdiv(T, 128) >= cus + cus / 2)
-    logits_mfma_kernel<InT><<<dim3(cdiv(E, 128), cdiv(T, 128)), 256, 0, s>>>(x, w, bias, logits, hdr,
-                                                                             T, d, E);
-  else if ((long)cdiv(E, 64) * cdiv(T, 64) >= cus)
-    logits_mfma4_kernel<InT, 2><<<dim3(cdiv(E, 64), cdiv(T, 64)), 256, 0, s>>>(x, w, bias, logits,
-                                                                               hdr, T, d, E);
+  auto cost = [&](int bt, int be, int sub) { return (long)cdiv((long)cdiv(T, bt) * cdiv(E, be), num_cus()) * sub; };
+  const long c1 = cost(32, 32, 1), c2 = cost(32, 64, 2), c4 = cost(64, 64, 4);
+  const long best = c1 < c2 ? (c1 < c4 ? c1 : c4) : (c2 < c4 ? c2 : c4);
+  const bool few = best <= 2, some = best <= 4;
+  if (c1 == best && (few || (c2 > best && c4 > best)))
+    launch_logits_cfg<InT, 1, 1, 6>(x, w, bias, logits, hdr, T, d, E, s);
+  else if (c2 == best && (some || c4 > best))
+    launch_logits_cfg<InT, 1, 2, 5>(x, w, bias, logits, hdr, T, d, E, s);
   else
-    logits_mfma4_kernel<InT, 1><<<dim3(cdiv(E, 32), cdiv(T, 32)), 256, 0, s>>>(x, w, bias, logits,
-                                                                               hdr, T, d, E);
+    launch_logits_cfg<InT, 2, 2, 3>(x, w, bias, logits, hdr, T, d, E, s);
 }
 
 hipError_t launch_logits(int dtype, const void* x, const void* w, const float* bias, float* logits,
