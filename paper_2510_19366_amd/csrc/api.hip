@@ -8,7 +8,7 @@
 #include <mutex>
 #include <vector>
 
-#include "kernels.h"
+#include "dispatch_common.h"
 
 namespace mp {
 
@@ -132,13 +132,30 @@ struct Timed {  // brackets one kernel launch with events when timing is on
 // ------------------------------------------------------------ stages on a layout
 static int do_route(const moe_prism_shape* s, const Layout& L, const void* x, const void* w_router,
                     const float* bias, const int32_t* k_tok, int32_t* ids, float* w, float* logits,
-                    char* ws, hipStream_t st) {
+                    char* ws, hipStream_t st, const SmallDispatch* small = nullptr) {
   const int E = s->n_experts * s->n_sub;
   int32_t* hdr = reinterpret_cast<int32_t*>(ws + L.hdr);
   MP_LAUNCH(MOE_PRISM_K_LOGITS,
             launch_logits(s->dtype, x, w_router, bias, logits, hdr, s->T, s->d, E, st));
   MP_LAUNCH(MOE_PRISM_K_TOPK, launch_topk(logits, k_tok, ids, w, hdr, s->T, E, s->k_max,
-                                          s->renormalize, s->routed_scale, st));
+                                          s->renormalize, s->routed_scale, small, st));
+  return MOE_PRISM_OK;
+}
+
+// the dispatch of T tokens with up to k_max picks out of E groups
+static int do_dispatch_over(const Layout& L, const int32_t* ids, int32_t* cnt, int32_t* off,
+                            int32_t* sorted_pair, int32_t* slot_of_pair, int32_t* chunk, int32_t* hdr,
+                            MTile* tiles, int T, int E, int k_max, hipStream_t st) {
+  if (dispatch_is_small(T, E)) {
+    MP_LAUNCH(MOE_PRISM_K_DISPATCH_PLACE, launch_dispatch_small(ids, cnt, off, hdr, sorted_pair, slot_of_pair,
+                                                                tiles, L.max_mtiles, T, E, k_max, st));
+    return MOE_PRISM_OK;
+  }
+  MP_LAUNCH(MOE_PRISM_K_DISPATCH_COUNT, launch_dispatch_count(ids, chunk, T, E, k_max, st));
+  MP_LAUNCH(MOE_PRISM_K_DISPATCH_SCAN, launch_dispatch_scan(chunk, cnt, T, E, st));
+  MP_LAUNCH(MOE_PRISM_K_DISPATCH_PLACE,
+            launch_dispatch_place(ids, chunk, cnt, off, hdr, sorted_pair, slot_of_pair, tiles, L.max_mtiles, T, E,
+                                  k_max, st));
   return MOE_PRISM_OK;
 }
 
@@ -150,12 +167,8 @@ static int do_dispatch(const moe_prism_shape* s, const Layout& L, const int32_t*
   const int E = s->n_experts * s->n_sub;
   int32_t* hdr = reinterpret_cast<int32_t*>(ws + L.hdr);
   int32_t* chunk = reinterpret_cast<int32_t*>(ws + L.chunk_cnt);
-  MP_LAUNCH(MOE_PRISM_K_DISPATCH_COUNT, launch_dispatch_count(ids, chunk, s->T, E, s->k_max, st));
-  MP_LAUNCH(MOE_PRISM_K_DISPATCH_SCAN, launch_dispatch_scan(chunk, cnt, s->T, E, st));
-  MP_LAUNCH(MOE_PRISM_K_DISPATCH_PLACE,
-            launch_dispatch_place(ids, chunk, cnt, off, hdr, sorted_pair, slot_of_pair,
-                                  with_tiles ? reinterpret_cast<MTile*>(ws + L.tiles) : nullptr,
-                                  L.max_mtiles, s->T, E, s->k_max, st));
+  MTile* tiles = with_tiles ? reinterpret_cast<MTile*>(ws + L.tiles) : nullptr;
+  return do_dispatch_over(L, ids, cnt, off, sorted_pair, slot_of_pair, chunk, hdr, tiles, s->T, E, s->k_max, st);
   return MOE_PRISM_OK;
 }
 
@@ -250,14 +263,14 @@ static int do_route_proxy(const moe_prism_shape* s, const Layout& L, const void*
   const ProxyScratch q = proxy_scratch(s, L, ws, m);
   MP_LAUNCH(MOE_PRISM_K_LOGITS,
             launch_logits(s->dtype, x, w_router0, bias0, logits0, hdr, s->T, s->d, N, st));
+  const SmallDispatch small{q.cnt0, q.off0, q.sp0, q.sl0, tiles, L.max_mtiles};
+  const bool one = dispatch_is_small(s->T, N);
   MP_LAUNCH(MOE_PRISM_K_TOPK, launch_topk(logits0, nullptr, q.ids0, q.w0, hdr, s->T, N, m,
-                                          s->renormalize, s->routed_scale, st));
-  MP_LAUNCH(MOE_PRISM_K_DISPATCH_COUNT, launch_dispatch_count(q.ids0, chunk, s->T, N, m, st));
-  MP_LAUNCH(MOE_PRISM_K_DISPATCH_SCAN, launch_dispatch_scan(chunk, q.cnt0, s->T, N, st));
-  MP_LAUNCH(MOE_PRISM_K_DISPATCH_PLACE,
-            launch_dispatch_place(q.ids0, chunk, q.cnt0, q.off0, hdr, q.sp0, q.sl0, nullptr, 0, s->T, N,
-                                  m, st));
-  MP_LAUNCH(MOE_PRISM_K_FFN_TILES, launch_ffn_tiles(q.off0, tiles, hdr, N, L.max_mtiles, s->T * m, st));
+                                          s->renormalize, s->routed_scale, one ? &small : nullptr, st));
+  if (!one) {
+    const int rc = do_dispatch_over(L, q.ids0, q.cnt0, q.off0, q.sp0, q.sl0, chunk, hdr, tiles, s->T, N, m, st);
+    if (rc) return rc;
+  }
   if (s->T == 0) return MOE_PRISM_OK;
   MP_LAUNCH(MOE_PRISM_K_FFN_GATE_UP,
             launch_ffn_gate_up(s->dtype, x, w_proxy, q.sp0, tiles, hdr, act, s->T, s->d, rows_half, m,
@@ -414,11 +427,16 @@ static int layer_on(const moe_prism_shape* shape, const Layout& L, const void* x
   int32_t* sp = reinterpret_cast<int32_t*>(w8 + L.sorted_pair);
   int32_t* sl = reinterpret_cast<int32_t*>(w8 + L.slot_of_pair);
   void* y = w8 + L.y;
+  // a small batch is dispatched by the top-k kernel itself
+  const SmallDispatch small{cnt, off, sp, sl, reinterpret_cast<MTile*>(w8 + L.tiles), L.max_mtiles};
+  const bool one = dispatch_is_small(shape->T, shape->n_experts * shape->n_sub);
   int rc = do_route(shape, L, x, w_router, router_bias, k_tok, ids, w,
-                    reinterpret_cast<float*>(w8 + L.logits), w8, st);
+                    reinterpret_cast<float*>(w8 + L.logits), w8, st, one ? &small : nullptr);
   if (rc) return rc;
-  rc = do_dispatch(shape, L, ids, cnt, off, sp, sl, w8, st, true);
-  if (rc) return rc;
+  if (!one) {
+    rc = do_dispatch(shape, L, ids, cnt, off, sp, sl, w8, st, true);
+    if (rc) return rc;
+  }
   rc = do_ffn(shape, L, x, w_gate_up, w_down, off, sp, y, w8, st, false, true);
   if (rc) return rc;
   if (shape->T == 0) return MOE_PRISM_OK;

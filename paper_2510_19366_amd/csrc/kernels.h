@@ -8,8 +8,9 @@ namespace mp {
 
 // Workspace header: int32 words at the start of ws.
 // HDR_DYN_*: cursors of the FFN kernels' work pools (cleared with the m-tile table)
+// HDR_TOPK_DONE: workgroups of the top-k kernel that have written their picks (cleared by the logits kernel)
 // HDR_DYN_FUSED .. +7: the fused FFN kernel's per-XCD tile cursors
-enum { HDR_FLAGS = 0, HDR_PAIRS = 1, HDR_MTILES = 2, HDR_DYN_GATE_UP = 3, HDR_DYN_DOWN = 4, HDR_DYN_FUSED = 8, HDR_WORDS = 64 };
+enum { HDR_FLAGS = 0, HDR_PAIRS = 1, HDR_MTILES = 2, HDR_DYN_GATE_UP = 3, HDR_DYN_DOWN = 4, HDR_TOPK_DONE = 5, HDR_DYN_FUSED = 8, HDR_WORDS = 64 };
 
 constexpr int FFN_BM = 256;  // rows of one m-tile of the grouped GEMMs
 
@@ -27,9 +28,12 @@ hipError_t launch_expand_k(int R, int T, const int32_t* req_k, const int32_t* re
 
 hipError_t launch_logits(int dtype, const void* x, const void* w, const float* bias, float* logits,
                          int32_t* hdr, int T, int d, int E, hipStream_t s);
+// with `small` (only where dispatch_is_small): the kernel also dispatches its picks
+struct MTile;
+struct SmallDispatch;
 hipError_t launch_topk(const float* logits, const int32_t* k_tok, int32_t* ids, float* w,
                        int32_t* hdr, int T, int E, int k_max, int renorm, float scale,
-                       hipStream_t s);
+                       const SmallDispatch* small, hipStream_t s);
 
 // dispatch: chunk_cnt is [n_chunks, E] scratch
 int dispatch_chunk_words(int E, int T);          // 64-token words per chunk
@@ -42,9 +46,12 @@ hipError_t launch_proxy_select(int dtype, const void* act, int act_ld, const int
                                const int32_t* kappa, int32_t* ids, float* w, int32_t* hdr, int T,
                                int S, int r, int m, int k_max, hipStream_t s);
 hipError_t launch_dispatch_scan(int32_t* chunk_cnt, int32_t* cnt, int T, int E, hipStream_t s);
+bool dispatch_is_small(int T, int E);  // the whole stage in one workgroup (launch_dispatch_small)
+hipError_t launch_dispatch_small(const int32_t* ids, int32_t* cnt, int32_t* off, int32_t* hdr,
+                                 int32_t* sorted_pair, int32_t* slot_of_pair, MTile* tiles,
+                                 int max_tiles, int T, int E, int k_max, hipStream_t s);
 // also writes off[0..E] and hdr[HDR_PAIRS] (from cnt[]) and, with tiles != nullptr, the grouped
 // FFN's m-tile table and its header words (what launch_ffn_tiles builds from off[])
-struct MTile;
 hipError_t launch_dispatch_place(const int32_t* ids, const int32_t* chunk_base, const int32_t* cnt,
                                  int32_t* off, int32_t* hdr, int32_t* sorted_pair,
                                  int32_t* slot_of_pair, MTile* tiles, int max_tiles, int T, int E,

@@ -1,7 +1,7 @@
 // Route stage (Sec. 3.2.2, expanded linear gate): router logits with a fixed
 // summation order, then per-token top-k_t and softmax weights.
+#include "dispatch_common.h"
 #include "dma.h"
-#include "kernels.h"
 
 namespace mp {
 
@@ -85,7 +85,10 @@ __global__ __launch_bounds__(64 * WM * WN) void logits_kernel(const InT* __restr
   extern __shared__ __align__(16) unsigned char lg_smem[];
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wv / WN, wn = wv % WN;
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) hdr[HDR_FLAGS] = 0;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+    hdr[HDR_FLAGS] = 0;
+    hdr[HDR_TOPK_DONE] = 0;
+  }
   const int m0 = blockIdx.y * C::BT, n0 = blockIdx.x * C::BE;
 
   // producer: copy j of this wave takes rows 8 (wv CP + j) .. + 7 of the stage (tokens first)
@@ -248,9 +251,9 @@ hipError_t launch_logits(int dtype, const void* x, const void* w, const float* b
 }
 
 // ---------------------------------------------------------------- top-k_t + weights
-// One wavefront per token.  Lane l holds logits g = i*64 + l.  Pick j is the
-// wave-wide arg-max over the logits not yet taken, by (logit desc, id asc),
-// reduced with cross-lane shuffles; no sort and no global traffic besides the
+// One wavefront per token, lane l holds logits g = i*64 + l in registers.  The k_t picks are the
+// keys above a threshold that bisection finds (a ballot and a scalar bit count per element and
+// step), compacted in id order and ranked by counting; no sort and no global traffic besides the
 // logits row and the outputs.
 // Wave-wide reductions that leave the result in every lane: four DPP steps inside each row
 // of 16 lanes (lane ^ 1, lane ^ 2, mirror inside 8, mirror inside 16), then the four row
@@ -288,11 +291,18 @@ __device__ __forceinline__ float wave_sum(float x) {
 }
 
 constexpr int TOPK_WAVES = 4;
+__host__ __device__ inline int topk_pad(int k_max) { return (k_max + 3) / 4 * 4; }
+// a wave's own LDS writes are readable by all its lanes
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
 
-// The picks run on integer keys: key(f) = bits ^ ((bits >> 31) & 0x7fffffff) orders like f for
+// Keys: key(f) = bits ^ ((bits >> 31) & 0x7fffffff) orders like f for
 // every non-NaN binary32 once -0.0 has been replaced by +0.0 (the two compare equal, and equal
-// logits go to the lower id), integer max/min fuse with the cross-lane moves, and INT_MIN, which
-// is the key of no logit (-inf maps to 0x807fffff), marks "taken or absent" without a mask.
+// logits go to the lower id), and INT_MIN, which is the key of no logit (-inf maps to 0x807fffff),
+// marks absent elements.
 __device__ __forceinline__ int topk_key(float f) {
   int b = __float_as_int(f);
   b = b == (int)0x80000000 ? 0 : b;  // -0.0 -> +0.0
@@ -309,105 +319,165 @@ __device__ __forceinline__ int wave_max_i(int v) {
   return max(max(r0, r1), max(r2, r3));
 }
 
-template <int ELEMS>
+// DISPATCH: the last workgroup to finish also dispatches the picks of all T tokens (small batches).
+template <int ELEMS, bool DISPATCH>
 __global__ __launch_bounds__(64 * TOPK_WAVES) void topk_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ k_tok, int32_t* __restrict__ ids,
     float* __restrict__ wout, int32_t* __restrict__ hdr, int T, int E, int k_max, int renorm,
-    float scale) {
-  extern __shared__ float smem[];  // per wave: the k_max picked logits, then their k_max ids
+    float scale, SmallDispatch small) {
+  extern __shared__ __align__(16) unsigned char topk_smem[];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int t = blockIdx.x * TOPK_WAVES + wv;
-  if (t >= T) return;
-  float* se = smem + (size_t)wv * 2 * k_max;
-  int* sid = reinterpret_cast<int*>(se + k_max);
+  if (t < T) {
+    // per wave: keys and ids of the picks in id order, then logits and ids in pick order
+    const int kp = topk_pad(k_max);
+    int* uk = reinterpret_cast<int*>(topk_smem) + (size_t)wv * 4 * kp;
+    int* uid = uk + kp;
+    float* se = reinterpret_cast<float*>(uid + kp);
+    int* sid = reinterpret_cast<int*>(se + kp);
 
-  int kt = k_tok != nullptr ? k_tok[t] : k_max;  // null: every token takes k_max
-  if (kt < 0 || kt > k_max) {
-    if (lane == 0) atomicOr(&hdr[HDR_FLAGS], 1);
-    kt = kt < 0 ? 0 : k_max;
-  }
-
-  const float NEG_INF = -__builtin_inff();
-  constexpr int GONE = (int)0x80000000;  // key of an element that is taken or beyond E
-  float v[ELEMS];
-  const float* row = logits + (size_t)t * E;
-#pragma unroll
-  for (int i = 0; i < ELEMS; ++i) {
-    int g = i * 64 + lane;
-    v[i] = g < E ? row[g] : NEG_INF;
-  }
-  // full-softmax denominator (only needed when weights are not renormalised)
-  float lmax = NEG_INF;
-#pragma unroll
-  for (int i = 0; i < ELEMS; ++i) lmax = fmaxf(lmax, v[i]);
-  const float mx = wave_max_f(lmax);
-  float denom = 0.0f;
-  if (!renorm) {
-#pragma unroll
-    for (int i = 0; i < ELEMS; ++i)
-      if (i * 64 + lane < E) denom += expf(v[i] - mx);
-    denom = wave_sum(denom);
-  }
-
-  // Pick j: the wave-wide maximum of the lanes' best free keys, and among the lanes that hold
-  // it the smallest sub-expert id (equal logits, +0.0 == -0.0 included, go to the lower id).
-  // g = 64 i + lane, so inside a lane the lower element index is the lower id and the winner's
-  // lane is g & 63.  Only that lane retires its element and rescans.
-  int key[ELEMS];
-#pragma unroll
-  for (int i = 0; i < ELEMS; ++i) key[i] = i * 64 + lane < E ? topk_key(v[i]) : GONE;
-  const int NONE = 0x7fffffff;
-  int bk, bg;  // this lane's best free key and its id
-  auto rescan = [&]() {
-    bk = GONE;
-#pragma unroll
-    for (int i = 0; i < ELEMS; ++i) bk = max(bk, key[i]);
-    int bi = 0;
-#pragma unroll
-    for (int i = ELEMS - 1; i >= 0; --i) bi = key[i] == bk ? i : bi;  // descending: the lowest index stays
-    bg = bk == GONE ? NONE : bi * 64 + lane;
-  };
-  rescan();
-  for (int j = 0; j < kt; ++j) {
-    const int top = wave_max_i(bk);  // > GONE: k_t <= k_max <= E, a free element is left
-    const unsigned long long holders = __ballot(bk == top);
-    int g;
-    if (__popcll(holders) == 1)  // the usual case: one lane holds the maximum
-      g = __builtin_amdgcn_readlane(bg, __ffsll((long long)holders) - 1);
-    else
-      g = wave_min_i(bk == top ? bg : NONE);
-    if (lane == 0) {
-      se[j] = topk_unkey(top);  // exponentials are taken for all picks at once after the loop
-      sid[j] = g;
+    int kt = k_tok != nullptr ? k_tok[t] : k_max;  // null: every token takes k_max
+    kt = __builtin_amdgcn_readfirstlane(kt);
+    if (kt < 0 || kt > k_max) {
+      if (lane == 0) atomicOr(&hdr[HDR_FLAGS], 1);
+      kt = kt < 0 ? 0 : k_max;
     }
-    if ((g & 63) == lane) {
-      const int gi = g >> 6;
+
+    const float NEG_INF = -__builtin_inff();
+    constexpr int GONE = (int)0x80000000;  // key of an element beyond E
+    float v[ELEMS];
+    const float* row = logits + (size_t)t * E;
 #pragma unroll
-      for (int i = 0; i < ELEMS; ++i) key[i] = i == gi ? GONE : key[i];
-      rescan();
+    for (int i = 0; i < ELEMS; ++i) {
+      int g = i * 64 + lane;
+      v[i] = g < E ? row[g] : NEG_INF;
+    }
+    // full-softmax denominator (only needed when weights are not renormalised)
+    float lmax = NEG_INF;
+#pragma unroll
+    for (int i = 0; i < ELEMS; ++i) lmax = fmaxf(lmax, v[i]);
+    const float mx = wave_max_f(lmax);
+    float denom = 0.0f;
+    if (!renorm) {
+#pragma unroll
+      for (int i = 0; i < ELEMS; ++i)
+        if (i * 64 + lane < E) denom += expf(v[i] - mx);
+      denom = wave_sum(denom);
+    }
+
+    int key[ELEMS];
+    int best = GONE;
+#pragma unroll
+    for (int i = 0; i < ELEMS; ++i) {
+      key[i] = i * 64 + lane < E ? topk_key(v[i]) : GONE;
+      best = max(best, key[i]);
+    }
+    if (kt > 0) {
+      // Threshold: the invariant is (number of keys >= lo) >= k_t > (number of keys >= hi).  The
+      // 64 lanes' best keys are 64 elements, so their minimum is a lower bound for k_t <= 64.
+      // Midpoints are taken between the logits (few steps: the gaps between neighbouring order
+      // statistics are wide compared to the range), between the keys where that does not split
+      // the interval.  A midpoint with exactly k_t keys above it ends the search; with equal keys
+      // at the border there is none and lo ends as the border key.
+      int lo = kt <= 64 ? wave_min_i(best) : GONE, hi = wave_max_i(best) + 1, above = 0;
+      int thr = 0;  // picks: all keys > thr and the first (k_t - above) keys == thr in id order
+      for (;;) {
+        if ((unsigned)(hi - lo) <= 1u) {
+          thr = lo;
+          break;
+        }
+        int m = __builtin_amdgcn_readfirstlane(topk_key(0.5f * topk_unkey(lo) + 0.5f * topk_unkey(hi)));
+        if (m <= lo || m >= hi) m = lo + (int)((unsigned)(hi - lo) >> 1);
+        int c = 0;
+#pragma unroll
+        for (int i = 0; i < ELEMS; ++i) c += __popcll(__ballot(key[i] >= m));
+        if (c == kt) {
+          thr = m - 1;
+          above = kt;
+          break;
+        }
+        if (c > kt) {
+          lo = m;
+        } else {
+          hi = m;
+          above = c;
+        }
+      }
+      // compact in id order (g = 64 i + lane: element by element, lanes ascending)
+      int base = 0, rem = kt - above;
+#pragma unroll
+      for (int i = 0; i < ELEMS; ++i) {
+        u64 take = __ballot(key[i] > thr);
+        if (rem > 0) {
+          const u64 eq = __ballot(key[i] == thr);
+          const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(eq >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eq, 0));
+          take |= __ballot(key[i] == thr && before < rem);
+          rem -= min(rem, (int)__popcll(eq));
+        }
+        if ((take >> lane) & 1) {
+          const int pos = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(take >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)take, 0));
+          uk[pos] = key[i];
+          uid[pos] = i * 64 + lane;
+        }
+        base += __popcll(take);
+      }
+      if (lane < 4 && kt + lane < kp) uk[kt + lane] = GONE;  // the ranking reads whole quadruples
+      wave_lds_fence();
+      // rank = number of larger keys plus equal keys of smaller ids (= earlier positions)
+      for (int j = lane; j < kt; j += 64) {
+        const int mine = uk[j];
+        int rank = 0;
+        for (int q = 0; q < kt; q += 4) {
+          const int4 o = *reinterpret_cast<const int4*>(uk + q);
+          rank += o.x > mine - (q < j ? 1 : 0);
+          rank += o.y > mine - (q + 1 < j ? 1 : 0);
+          rank += o.z > mine - (q + 2 < j ? 1 : 0);
+          rank += o.w > mine - (q + 3 < j ? 1 : 0);
+        }
+        se[rank] = topk_unkey(mine);
+        sid[rank] = uid[j];
+      }
+      wave_lds_fence();
+    }
+    float dsel = 0.0f;
+    for (int j = lane; j < kt; j += 64) dsel += expf(se[j] - mx);
+    if (renorm) denom = wave_sum(dsel);
+    for (int j = lane; j < k_max; j += 64) {
+      bool on = j < kt;
+      ids[(size_t)t * k_max + j] = on ? sid[j] : -1;
+      wout[(size_t)t * k_max + j] = on ? scale * expf(se[j] - mx) / denom : 0.0f;
     }
   }
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): LDS writes of lane 0 are done
-  float dsel = 0.0f;
-  for (int j = lane; j < kt; j += 64) dsel += expf(se[j] - mx);
-  if (renorm) denom = wave_sum(dsel);
-  for (int j = lane; j < k_max; j += 64) {
-    bool on = j < kt;
-    ids[(size_t)t * k_max + j] = on ? sid[j] : -1;
-    wout[(size_t)t * k_max + j] = on ? scale * expf(se[j] - mx) / denom : 0.0f;
+  if constexpr (DISPATCH) {
+    __shared__ int32_t wave_tot[4][2];
+    __shared__ int is_last;
+    __threadfence();  // this workgroup's picks are visible on the device before it counts itself done
+    __syncthreads();
+    if (threadIdx.x == 0) is_last = atomicAdd(&hdr[HDR_TOPK_DONE], 1) == (int)gridDim.x - 1;
+    __syncthreads();
+    if (!is_last) return;
+    __threadfence();
+    dispatch_one_workgroup(ids, small, hdr, reinterpret_cast<u64*>(topk_smem), wave_tot, T, E, k_max);
   }
 }
 
 hipError_t launch_topk(const float* logits, const int32_t* k_tok, int32_t* ids, float* w,
                        int32_t* hdr, int T, int E, int k_max, int renorm, float scale,
-                       hipStream_t s) {
+                       const SmallDispatch* small, hipStream_t s) {
   if (T == 0) return hipSuccess;
+  static_assert(64 * TOPK_WAVES == DISPATCH_THREADS, "the same workgroup does both");
   dim3 grid(cdiv(T, TOPK_WAVES)), block(64 * TOPK_WAVES);
-  size_t sh = (size_t)TOPK_WAVES * 2 * k_max * sizeof(float);
+  size_t sh = (size_t)TOPK_WAVES * 4 * topk_pad(k_max) * sizeof(float);
   int elems = cdiv(E, 64);
-#define MP_TOPK(N)                                                                              \
-  topk_kernel<N><<<grid, block, sh, s>>>(logits, k_tok, ids, w, hdr, T, E, k_max, renorm, scale)
+  if (small != nullptr && small_dispatch_lds(T, E) > sh) sh = small_dispatch_lds(T, E);
+#define MP_TOPK(N)                                                                                             \
+  do {                                                                                                         \
+    if (small != nullptr)                                                                                      \
+      topk_kernel<N, true><<<grid, block, sh, s>>>(logits, k_tok, ids, w, hdr, T, E, k_max, renorm, scale, *small); \
+    else                                                                                                       \
+      topk_kernel<N, false><<<grid, block, sh, s>>>(logits, k_tok, ids, w, hdr, T, E, k_max, renorm, scale,     \
+                                                    SmallDispatch{});                                          \
+  } while (0)
   if (elems <= 1) MP_TOPK(1);
   else if (elems <= 2) MP_TOPK(2);
   else if (elems <= 4) MP_TOPK(4);

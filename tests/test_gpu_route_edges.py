@@ -1,0 +1,57 @@
+"""Top-k by threshold search and the one-workgroup dispatch of small batches, at the sizes where
+they change over: mask words of 64 tokens, the 256-token limit, the LDS limit, budgets around one
+wave's 64 lanes, and logits with many equal values at the border of the budget."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2510_19366_amd import binding as B
+from paper_2510_19366_amd import workloads as W
+from gpu_util import max_rel, run_layer, run_stages, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,E,k_max", [(1, 512, 32), (64, 40, 5), (65, 40, 5), (255, 64, 9), (256, 64, 9),
+                                       (255, 1500, 7), (255, 1530, 7), (130, 2100, 66)])
+def test_small_batches_match_the_oracle(T, E, k_max):
+    k = np.random.default_rng(T).integers(0, k_max + 1, size=T).astype(np.int32)
+    wl = W.make_workload("small", dtype="bf16", d=64, n_experts=E // 2, n_sub=2, inter_sub=32,
+                         req_tokens=[1] * T, req_k=k, k_max=k_max, seed=T, bias_std=1.0, w_std=0.1)
+    r = run_stages(wl)
+    ref = O.layer_of(wl, return_all=True)
+    for key in ("ids", "cnt", "off", "sorted_pair", "slot_of_pair"):
+        assert np.array_equal(r[key], ref[key]), key
+    out, dev, ws = run_layer(wl)
+    assert max_rel(to_np(out), ref["out"]) <= 2e-2
+    # the layer's own tables (picks dispatched by the top-k kernel) equal the stage calls'
+    im = B.layer_intermediates(dev["shape"], ws)
+    assert np.array_equal(to_np(im["topk_ids"]), ref["ids"])
+    for key, name in (("cnt", "group_count"), ("off", "group_offset"), ("sorted_pair", "sorted_pair"),
+                      ("slot_of_pair", "slot_of_pair")):
+        assert np.array_equal(to_np(im[name]), ref[key]), name
+
+
+@pytest.mark.parametrize("values", [2, 9])
+@pytest.mark.parametrize("E,k_max", [(64, 64), (130, 65), (512, 63), (520, 200)])
+def test_equal_logits_at_the_border_go_to_the_lower_ids(E, k_max, values):
+    # every logit is one of a few values (signed zeros and infinities among them): x = 1, one weight
+    # per sub-expert plus the bias
+    T, d = 40, 64
+    rng = np.random.default_rng(E + values)
+    x = np.zeros((T, d), np.float32)
+    x[np.arange(T), np.arange(T) % 8] = 1.0
+    pool = np.array([0.0, -0.0, 1.0, -1.0, 1e-30, -3.0, 65504.0, 0.5, -np.inf], np.float32)[:values]
+    w = np.zeros((E, d), np.float32)
+    bias = rng.choice(pool, size=E).astype(np.float32)
+    k = rng.integers(0, k_max + 1, size=T).astype(np.int32)
+    k[:2] = [k_max, 0]
+    shape = B.make_shape(T, d, E, 1, 32, k_max, "f32")
+    ws = B.alloc_workspace(shape)
+    ids, wt, lg = B.moe_prism_route(shape, torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(),
+                                    torch.from_numpy(bias).cuda(), torch.from_numpy(k).cuda(), ws, want_logits=True)
+    torch.cuda.synchronize()
+    ref = O.logits(x, w, bias)
+    assert np.array_equal(to_np(lg).view(np.uint32), ref.view(np.uint32))
+    assert np.array_equal(to_np(ids), O.select(ref, k, k_max))
