@@ -56,10 +56,24 @@ def lib():
         if not os.path.exists(LIB_PATH):
             raise ImportError(f"{LIB_PATH} is missing: run `python -c 'import __graft_entry__ as g; "
                               "g.build()'` (the HIP library is required; there is no fallback)")
-        _lib = C.CDLL(LIB_PATH)
-        _lib.moe_prism_strerror.restype = C.c_char_p
+        handle = C.CDLL(LIB_PATH)
+        handle.moe_prism_strerror.restype = C.c_char_p
         for name in EXPORTS:
-            getattr(_lib, name)
+            getattr(handle, name)
+        # declared signatures: addresses go in as plain integers (a decode step's host time counts)
+        ptr, shp, i32, size = C.c_void_p, C.POINTER(Shape), C.c_int32, C.c_size_t
+        handle.moe_prism_expand_k.argtypes = [i32, i32, ptr, ptr, ptr, ptr]
+        handle.moe_prism_route.argtypes = [shp] + [ptr] * 8 + [size, ptr]
+        handle.moe_prism_dispatch.argtypes = [shp] + [ptr] * 6 + [size, ptr]
+        handle.moe_prism_grouped_ffn.argtypes = [shp] + [ptr] * 7 + [size, ptr]
+        handle.moe_prism_ffn_traffic_probe.argtypes = [shp] + [ptr] * 7 + [size, ptr]
+        handle.moe_prism_status.argtypes = [ptr] * 4
+        handle.moe_prism_combine.argtypes = [shp] + [ptr] * 6
+        handle.moe_prism_layer.argtypes = [shp] + [ptr] * 8 + [size, ptr]
+        handle.moe_prism_layer_static.argtypes = [shp] + [ptr] * 8
+        handle.moe_prism_route_proxy.argtypes = [shp] + [ptr] * 4 + [i32] * 3 + [ptr] * 5 + [size, ptr]
+        handle.moe_prism_layer_proxy.argtypes = [shp] + [ptr] * 4 + [i32] * 3 + [ptr] * 6 + [size, ptr]
+        _lib = handle
     return _lib
 
 
@@ -70,13 +84,14 @@ def _check(rc):
 
 def _ptr(t):
     if t is None:
-        return C.c_void_p(0)
+        return None
     assert t.is_cuda and t.is_contiguous(), "device-resident contiguous tensors only"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream of the current device, as an address (without building a Stream object)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def make_shape(T, d, n_experts, n_sub, inter_sub, k_max, dtype, renormalize=1, routed_scale=None):
@@ -116,9 +131,9 @@ def moe_prism_route(shape, x, w_router, router_bias, k_tok, ws, want_logits=Fals
     ids = torch.empty((T, km), dtype=torch.int32, device=x.device)
     w = torch.empty((T, km), dtype=torch.float32, device=x.device)
     lg = torch.empty((T, shape.E), dtype=torch.float32, device=x.device) if want_logits else None
-    _check(lib().moe_prism_route(C.byref(shape), _ptr(x), _ptr(w_router), _ptr(router_bias),
+    _check(lib().moe_prism_route(shape, _ptr(x), _ptr(w_router), _ptr(router_bias),
                                  _ptr(k_tok), _ptr(ids), _ptr(w), _ptr(lg), _ptr(ws),
-                                 C.c_size_t(ws.numel()), _stream()))
+                                 ws.numel(), _stream()))
     return (ids, w, lg) if want_logits else (ids, w)
 
 
@@ -129,17 +144,17 @@ def moe_prism_dispatch(shape, topk_ids, ws):
     off = torch.empty(E + 1, dtype=torch.int32, device=dev)
     sp = torch.empty(n, dtype=torch.int32, device=dev)
     sl = torch.empty(n, dtype=torch.int32, device=dev)
-    _check(lib().moe_prism_dispatch(C.byref(shape), _ptr(topk_ids), _ptr(cnt), _ptr(off), _ptr(sp),
-                                    _ptr(sl), _ptr(ws), C.c_size_t(ws.numel()), _stream()))
+    _check(lib().moe_prism_dispatch(shape, _ptr(topk_ids), _ptr(cnt), _ptr(off), _ptr(sp),
+                                    _ptr(sl), _ptr(ws), ws.numel(), _stream()))
     return cnt, off, sp, sl
 
 
 def moe_prism_grouped_ffn(shape, x, w_gate_up, w_down, group_offset, sorted_pair, ws, y=None):
     if y is None:
         y = torch.empty((shape.T * shape.k_max, shape.d), dtype=act_dtype(shape), device=x.device)
-    _check(lib().moe_prism_grouped_ffn(C.byref(shape), _ptr(x), _ptr(w_gate_up), _ptr(w_down),
+    _check(lib().moe_prism_grouped_ffn(shape, _ptr(x), _ptr(w_gate_up), _ptr(w_down),
                                        _ptr(group_offset), _ptr(sorted_pair), _ptr(y), _ptr(ws),
-                                       C.c_size_t(ws.numel()), _stream()))
+                                       ws.numel(), _stream()))
     return y
 
 
@@ -154,7 +169,7 @@ def moe_prism_ffn_traffic_probe(shape, x, w_gate_up, w_down, group_offset, sorte
 def moe_prism_combine(shape, y, slot_of_pair, topk_w, k_tok, out=None):
     if out is None:
         out = torch.empty((shape.T, shape.d), dtype=act_dtype(shape), device=y.device)
-    _check(lib().moe_prism_combine(C.byref(shape), _ptr(y), _ptr(slot_of_pair), _ptr(topk_w),
+    _check(lib().moe_prism_combine(shape, _ptr(y), _ptr(slot_of_pair), _ptr(topk_w),
                                    _ptr(k_tok), _ptr(out), _stream()))
     return out
 
@@ -162,9 +177,9 @@ def moe_prism_combine(shape, y, slot_of_pair, topk_w, k_tok, out=None):
 def moe_prism_layer(shape, x, w_router, router_bias, k_tok, w_gate_up, w_down, ws, out=None):
     if out is None:
         out = torch.empty((shape.T, shape.d), dtype=act_dtype(shape), device=x.device)
-    _check(lib().moe_prism_layer(C.byref(shape), _ptr(x), _ptr(w_router), _ptr(router_bias),
+    _check(lib().moe_prism_layer(shape, _ptr(x), _ptr(w_router), _ptr(router_bias),
                                  _ptr(k_tok), _ptr(w_gate_up), _ptr(w_down), _ptr(out), _ptr(ws),
-                                 C.c_size_t(ws.numel()), _stream()))
+                                 ws.numel(), _stream()))
     return out
 
 
@@ -182,7 +197,7 @@ STATIC_WS_BYTES = 64 << 20  # MOE_PRISM_STATIC_WS_BYTES
 def moe_prism_layer_static(shape, x, w_router, router_bias, k_tok, w_gate_up, w_down, out):
     """moe_prism_layer on the library's own static device workspace: allocates nothing, so
     `out` is the caller's."""
-    _check(lib().moe_prism_layer_static(C.byref(shape), _ptr(x), _ptr(w_router), _ptr(router_bias),
+    _check(lib().moe_prism_layer_static(shape, _ptr(x), _ptr(w_router), _ptr(router_bias),
                                         _ptr(k_tok), _ptr(w_gate_up), _ptr(w_down), _ptr(out),
                                         _stream()))
     return out
@@ -249,24 +264,24 @@ def moe_prism_route_proxy(shape, x, pdev, k_tok, ws):
     T, km = shape.T, shape.k_max
     ids = torch.empty((T, km), dtype=torch.int32, device=x.device)
     w = torch.empty((T, km), dtype=torch.float32, device=x.device)
-    _check(lib().moe_prism_route_proxy(C.byref(shape), _ptr(x), _ptr(pdev["w_router0"]),
+    _check(lib().moe_prism_route_proxy(shape, _ptr(x), _ptr(pdev["w_router0"]),
                                        _ptr(pdev["bias0"]), _ptr(pdev["w_proxy"]),
-                                       C.c_int32(pdev["m"]), C.c_int32(pdev["r"]),
-                                       C.c_int32(pdev["rows_half"]), _ptr(pdev["kappa"]),
+                                       pdev["m"], pdev["r"],
+                                       pdev["rows_half"], _ptr(pdev["kappa"]),
                                        _ptr(k_tok), _ptr(ids), _ptr(w), _ptr(ws),
-                                       C.c_size_t(ws.numel()), _stream()))
+                                       ws.numel(), _stream()))
     return ids, w
 
 
 def moe_prism_layer_proxy(shape, x, pdev, k_tok, w_gate_up, w_down, ws, out=None):
     if out is None:
         out = torch.empty((shape.T, shape.d), dtype=act_dtype(shape), device=x.device)
-    _check(lib().moe_prism_layer_proxy(C.byref(shape), _ptr(x), _ptr(pdev["w_router0"]),
+    _check(lib().moe_prism_layer_proxy(shape, _ptr(x), _ptr(pdev["w_router0"]),
                                        _ptr(pdev["bias0"]), _ptr(pdev["w_proxy"]),
-                                       C.c_int32(pdev["m"]), C.c_int32(pdev["r"]),
-                                       C.c_int32(pdev["rows_half"]), _ptr(pdev["kappa"]),
+                                       pdev["m"], pdev["r"],
+                                       pdev["rows_half"], _ptr(pdev["kappa"]),
                                        _ptr(k_tok), _ptr(w_gate_up), _ptr(w_down), _ptr(out),
-                                       _ptr(ws), C.c_size_t(ws.numel()), _stream()))
+                                       _ptr(ws), ws.numel(), _stream()))
     return out
 
 
