@@ -199,7 +199,17 @@ static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, cons
                                             L.max_mtiles, st));
     return MOE_PRISM_OK;
   }
+  const bool few = s->dtype == MOE_PRISM_BF16 && ffn_few_pairs(s->T, s->k_max, E, s->inter_sub);
   if (use_fused_ffn(s)) {
+    if (few) {  // both GEMMs in place of the fused kernel, timed as one
+      hipError_t e[2] = {hipSuccess, hipSuccess};
+      MP_LAUNCH(MOE_PRISM_K_FFN_FUSED,
+                (e[0] = launch_ffn_gate_up(s->dtype, x, w_gu, sorted_pair, tiles, hdr, h, s->T, s->d, s->inter_sub,
+                                           s->k_max, few, L.max_mtiles, st),
+                 e[1] = launch_ffn_down(s->dtype, h, w_dn, tiles, hdr, y, s->d, s->inter_sub, few, L.max_mtiles, st),
+                 e[0] != hipSuccess ? e[0] : e[1]));
+      return MOE_PRISM_OK;
+    }
     MP_LAUNCH(MOE_PRISM_K_FFN_FUSED,
               launch_ffn_fused_bf16((const uint16_t*)x, (const uint16_t*)w_gu, (const uint16_t*)w_dn,
                                     sorted_pair, tiles, hdr, (uint16_t*)y, s->T, s->d, s->inter_sub,
@@ -208,9 +218,9 @@ static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, cons
   }
   MP_LAUNCH(MOE_PRISM_K_FFN_GATE_UP,
             launch_ffn_gate_up(s->dtype, x, w_gu, sorted_pair, tiles, hdr, h, s->T, s->d, s->inter_sub,
-                               s->k_max, L.max_mtiles, st));
+                               s->k_max, few, L.max_mtiles, st));
   MP_LAUNCH(MOE_PRISM_K_FFN_DOWN, launch_ffn_down(s->dtype, h, w_dn, tiles, hdr, y, s->d,
-                                                  s->inter_sub, L.max_mtiles, st));
+                                                  s->inter_sub, few, L.max_mtiles, st));
   return MOE_PRISM_OK;
 }
 
@@ -274,7 +284,7 @@ static int do_route_proxy(const moe_prism_shape* s, const Layout& L, const void*
   if (s->T == 0) return MOE_PRISM_OK;
   MP_LAUNCH(MOE_PRISM_K_FFN_GATE_UP,
             launch_ffn_gate_up(s->dtype, x, w_proxy, q.sp0, tiles, hdr, act, s->T, s->d, rows_half, m,
-                               L.max_mtiles, st));
+                               s->dtype == MOE_PRISM_BF16 && ffn_few_pairs(s->T, m, N, rows_half), L.max_mtiles, st));
   MP_LAUNCH(MOE_PRISM_K_PROXY_SELECT,
             launch_proxy_select(s->dtype, act, rows_half, q.ids0, q.w0, q.sl0, k_tok, kappa, ids, w,
                                 hdr, s->T, s->n_sub, r, m, s->k_max, st));

@@ -25,6 +25,17 @@ __device__ __forceinline__ void copy_to_lds16(const void* base, uint32_t voff, u
       : "memory");
 }
 
+// the same with a 64-bit address per lane
+__device__ __forceinline__ void copy_to_lds16_addr(uint64_t addr, uint32_t lds) {
+  uint32_t keep;
+  asm volatile(
+      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
+      : "=&s"(keep)
+      : "v"(addr), "s"(lds)
+      : "memory");
+}
+
 // until at most N of this wave's vector memory operations are pending (they retire in issue order)
 template <int N>
 __device__ __forceinline__ void wait_vmem() {

@@ -5,8 +5,9 @@
 // workgroups walk (m-tile, n-tile) work items round-robin.  Two GEMMs:
 //   gate-up : h[p, c] = SiLU(x[t_p,:] . Wg[g,c,:]) * (x[t_p,:] . Wu[g,c,:])
 //   down    : y[p, q] = sum_c h[p,c] * Wd[g,q,c]
-// This file: the m-tile table and the fp32 path (plain FMA tiles, reference
-// quality, small shapes).  The bf16 MFMA kernels are in ffn_bf16.hip.
+// This file: the m-tile table and the fp32 path.  The bf16 kernels are in ffn_bf16.hip and
+// ffn_fused_bf16.hip.
+#include "chain_tile.h"
 #include "ffn_common.h"
 
 namespace mp {
@@ -84,166 +85,128 @@ hipError_t launch_ffn_tiles(const int32_t* off, MTile* tiles, int32_t* hdr, int 
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- fp32 tiles (small reference-quality path)
-// 128 x 128 output tile, 256 threads, 8 x 8 outputs per thread, K slabs of 16.  An m-tile
-// of the table (FFN_BM = 256 rows) is processed as two 128-row halves.
-constexpr int FK = 16;
-constexpr int TILE = 128;
-constexpr int HALVES = FFN_BM / TILE;
-struct SmemF {
-  float a[FK][TILE + 4];
-  float b[FK][TILE + 4];
-  long long a_off[TILE];
-  long long b_off[TILE];
-};
+// ---------------------------------------------------------------- fp32
+// Both GEMMs as fp32 chains on the matrix cores (chain_tile.h).  fp32 layers are small (reference
+// runs of a few dozen to a few thousand tokens), so the tile is small too: 32 slot rows x 64 weight
+// rows, 4 waves of 16 x 32, K in slabs of 32.  An m-tile of the table (FFN_BM = 256 rows) is up to
+// eight such row blocks.  Measured on 64 tokens, d = 256, 32 sub-experts of 128: gate-up 60 -> 5 us,
+// down 30 -> 4 us against 128 x 128 tiles of v_fma_f32 (whose 32 workgroups left the chip idle).
+constexpr int F32_ROWS = 32, F32_COLS = 64, F32_BLOCKS = FFN_BM / F32_ROWS;
+typedef ChainTile<float, 2, 2, 1, 2, 5> F32Tile;
 
-__device__ __forceinline__ void f32_tile(const float* __restrict__ a_base,
-                                         const float* __restrict__ b_base, int K, SmemF& sm,
-                                         float (&acc)[8][8]) {
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int lr = tid >> 1, lk = (tid & 1) * 8;  // loader: 8 floats of row lr
-  for (int k0 = 0; k0 < K; k0 += FK) {
-    float va[8], vb[8];
+// Copies of one tile: row `row` of the stage starts at byte offset off(row) behind the base of its
+// operand (slot rows first).  WIDE: an operand of 4 GiB or more, offsets of 64 bits.
+template <bool WIDE, class Rows>
+__device__ __forceinline__ void f32_tile(const float* a_base, const float* b_base, int K, Rows&& off,
+                                         unsigned char* smem, f32x4_t (&acc)[1][2]) {
+  constexpr int CP = F32Tile::CP;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const unsigned char* base[CP];
+  uint32_t voff[CP];
+  uint64_t addr[CP];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      bool in = k0 + lk + e < K;
-      va[e] = in ? a_base[sm.a_off[lr] + k0 + lk + e] : 0.0f;
-      vb[e] = in ? b_base[sm.b_off[lr] + k0 + lk + e] : 0.0f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      sm.a[lk + e][lr] = va[e];
-      sm.b[lk + e][lr] = vb[e];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < FK; ++kk) {
-      float a[8], b[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        a[i] = sm.a[kk][(i >> 2) * 64 + ty * 4 + (i & 3)];
-        b[i] = sm.b[kk][(i >> 2) * 64 + tx * 4 + (i & 3)];
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
+  for (int j = 0; j < CP; ++j) {
+    const int r0 = (wv * CP + j) * 8, row = r0 + (lane >> 3);
+    base[j] = reinterpret_cast<const unsigned char*>(r0 < F32_ROWS ? a_base : b_base);
+    const size_t o = off(row) * (size_t)K * 4 + (size_t)(chain_chunk(row) * 16);
+    voff[j] = (uint32_t)o;
+    addr[j] = reinterpret_cast<uint64_t>(base[j]) + o;
   }
-  __syncthreads();
+  chain_tile<F32Tile>(smem, K / F32Tile::KB, [&](int j, int stage, uint32_t lds) {
+    if constexpr (WIDE)
+      copy_to_lds16_addr(addr[j] + (uint64_t)stage * 128, lds);
+    else
+      copy_to_lds16(base[j] + (size_t)stage * 128, voff[j], lds);
+  }, acc);
 }
 
-// B columns 0..63 of a tile are gate neurons n0.., columns 64..127 the matching up neurons.
+// items: (m-tile, row block, n-tile); an item whose row block is empty is skipped
+template <class Body>
+__device__ __forceinline__ void f32_items(const MTile* __restrict__ tiles, const int32_t* __restrict__ hdr,
+                                          int n_tiles_n, Body&& body) {
+  const ItemRange ir = xcd_items(hdr[HDR_MTILES] * F32_BLOCKS * n_tiles_n);
+  for (int item = ir.begin; item < ir.end; item += ir.step) {
+    const MTile t = tiles[item / (F32_BLOCKS * n_tiles_n)];
+    const int blk = item / n_tiles_n % F32_BLOCKS, rows = min(F32_ROWS, t.rows - blk * F32_ROWS);
+    if (rows <= 0) continue;  // uniform over the workgroup
+    body(t.g, t.row0 + blk * F32_ROWS, rows, item % n_tiles_n);
+    __syncthreads();  // every wave has read the last stage before the ring is filled again
+  }
+}
+
+// Weight rows of a tile: per wave column 16 neurons' gate rows, then their up rows.
+template <bool WIDE>
 __global__ __launch_bounds__(256) void ffn_gate_up_f32_kernel(
     const float* __restrict__ x, const float* __restrict__ w_gu,
     const int32_t* __restrict__ sorted_pair, const MTile* __restrict__ tiles,
     const int32_t* __restrict__ hdr, float* __restrict__ h, int d, int Is, int k_max, int T) {
-  __shared__ SmemF sm;
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int NT = (Is + 63) / 64;
-  const int total = hdr[HDR_MTILES] * NT * HALVES;
-  const ItemRange ir = xcd_items(total);
-  for (int item = ir.begin; item < ir.end; item += ir.step) {
-    MTile tl = tiles[item / (NT * HALVES)];
-    const int half = (item / NT) % HALVES;
-    tl.row0 += half * TILE;
-    tl.rows = min(TILE, tl.rows - half * TILE);
-    if (tl.rows <= 0) continue;  // uniform over the workgroup
-    const int n0 = (item % NT) * 64;
-    if (tid < TILE) {
-      int r = min(tid, tl.rows - 1);
-      sm.a_off[tid] = (long long)min(max(sorted_pair[tl.row0 + r] / k_max, 0), T - 1) * d;
-      int neuron = min(n0 + (tid & 63), Is - 1);
-      sm.b_off[tid] = ((long long)tl.g * 2 * Is + (tid >= 64 ? Is + neuron : neuron)) * d;
+  extern __shared__ __align__(16) unsigned char f_smem[];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, wm = wv >> 1, wn = wv & 1;
+  f32_items(tiles, hdr, Is / 32, [&](int g, int row0, int rows, int nt) {  // Is % 32 == 0
+    f32x4_t acc[1][2];
+    f32_tile<WIDE>(x, w_gu + (size_t)g * 2 * Is * d, d, [&](int row) -> size_t {
+      if (row < F32_ROWS) return min(max(sorted_pair[row0 + min(row, rows - 1)] / k_max, 0), T - 1);
+      const int b = row - F32_ROWS;
+      return ((b >> 4) & 1 ? Is : 0) + nt * 32 + (b >> 5) * 16 + (b & 15);
+    }, f_smem, acc);
+    const int col = nt * 32 + wn * 16 + (lane & 15);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = wm * 16 + 4 * (lane >> 4) + v;
+      const float a = acc[0][0][v], u = acc[0][1][v];
+      if (row < rows) h[(size_t)(row0 + row) * Is + col] = a / (1.0f + expf(-a)) * u;
     }
-    __syncthreads();
-    float acc[8][8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[i][j] = 0.0f;
-    f32_tile(x, w_gu, d, sm, acc);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      int row = (i >> 2) * 64 + ty * 4 + (i & 3);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        int col = n0 + tx * 4 + j;
-        if (row < tl.rows && col < Is) {
-          float a = acc[i][j], u = acc[i][j + 4];
-          h[(size_t)(tl.row0 + row) * Is + col] = a / (1.0f + expf(-a)) * u;
-        }
-      }
-    }
-  }
+  });
 }
 
+template <bool WIDE>
 __global__ __launch_bounds__(256) void ffn_down_f32_kernel(const float* __restrict__ h,
                                                            const float* __restrict__ w_dn,
                                                            const MTile* __restrict__ tiles,
                                                            const int32_t* __restrict__ hdr,
                                                            float* __restrict__ y, int d, int Is) {
-  __shared__ SmemF sm;
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int NT = (d + TILE - 1) / TILE;
-  const int total = hdr[HDR_MTILES] * NT * HALVES;
-  const ItemRange ir = xcd_items(total);
-  for (int item = ir.begin; item < ir.end; item += ir.step) {
-    MTile tl = tiles[item / (NT * HALVES)];
-    const int half = (item / NT) % HALVES;
-    tl.row0 += half * TILE;
-    tl.rows = min(TILE, tl.rows - half * TILE);
-    if (tl.rows <= 0) continue;  // uniform over the workgroup
-    const int n0 = (item % NT) * TILE;
-    if (tid < TILE) {
-      int r = min(tid, tl.rows - 1);
-      sm.a_off[tid] = (long long)(tl.row0 + r) * Is;
-      sm.b_off[tid] = ((long long)tl.g * d + min(n0 + tid, d - 1)) * Is;
-    }
-    __syncthreads();
-    float acc[8][8];
+  extern __shared__ __align__(16) unsigned char f_smem[];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, wm = wv >> 1, wn = wv & 1;
+  f32_items(tiles, hdr, d / F32_COLS, [&](int g, int row0, int rows, int nt) {  // d % 64 == 0
+    f32x4_t acc[1][2];
+    f32_tile<WIDE>(h + (size_t)row0 * Is, w_dn + (size_t)g * d * Is, Is, [&](int row) -> size_t {
+      return row < F32_ROWS ? min(row, rows - 1) : nt * F32_COLS + row - F32_ROWS;
+    }, f_smem, acc);
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) acc[i][j] = 0.0f;
-    f32_tile(h, w_dn, Is, sm, acc);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      int row = (i >> 2) * 64 + ty * 4 + (i & 3);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        int col = n0 + (j >> 2) * 64 + tx * 4 + (j & 3);
-        if (row < tl.rows && col < d) y[(size_t)(tl.row0 + row) * d + col] = acc[i][j];
+      for (int v = 0; v < 4; ++v) {
+        const int row = wm * 16 + 4 * (lane >> 4) + v, col = nt * F32_COLS + (wn * 2 + j) * 16 + (lane & 15);
+        if (row < rows) y[(size_t)(row0 + row) * d + col] = acc[0][j][v];
       }
-    }
-  }
+  });
 }
 
 // ---------------------------------------------------------------- launchers
 hipError_t launch_ffn_gate_up(int dtype, const void* x, const void* w_gu, const int32_t* sorted_pair,
                               const MTile* tiles, int32_t* hdr, void* h, int T, int d, int Is,
-                              int k_max, int max_mtiles, hipStream_t s) {
+                              int k_max, bool few, int max_mtiles, hipStream_t s) {
   if (max_mtiles <= 0) return hipSuccess;
   if (dtype != 0)
     return launch_gate_up_bf16((const uint16_t*)x, (const uint16_t*)w_gu, sorted_pair, tiles, hdr,
-                               (uint16_t*)h, T, d, Is, k_max, max_mtiles, s);
-  long items = (long)max_mtiles * HALVES * cdiv(Is, 64);
-  ffn_gate_up_f32_kernel<<<persistent_grid(items, 2), 256, 0, s>>>(
-      (const float*)x, (const float*)w_gu, sorted_pair, tiles, hdr, (float*)h, d, Is, k_max, T);
+                               (uint16_t*)h, T, d, Is, k_max, few, max_mtiles, s);
+  const int grid = persistent_grid((long)max_mtiles * F32_BLOCKS * (Is / 32), 2);
+  auto* kern = (long)T * d >= (1L << 30) || (long)Is * d >= (1L << 29) ? ffn_gate_up_f32_kernel<true> : ffn_gate_up_f32_kernel<false>;
+  kern<<<grid, 256, F32Tile::LDS_BYTES, s>>>((const float*)x, (const float*)w_gu, sorted_pair, tiles, hdr, (float*)h,
+                                             d, Is, k_max, T);
   return hipGetLastError();
 }
 
 hipError_t launch_ffn_down(int dtype, const void* h, const void* w_dn, const MTile* tiles,
-                           int32_t* hdr, void* y, int d, int Is, int max_mtiles,
+                           int32_t* hdr, void* y, int d, int Is, bool few, int max_mtiles,
                            hipStream_t s) {
   if (max_mtiles <= 0) return hipSuccess;
   if (dtype != 0)
     return launch_down_bf16((const uint16_t*)h, (const uint16_t*)w_dn, tiles, hdr, (uint16_t*)y, d,
-                            Is, max_mtiles, s);
-  long items = (long)max_mtiles * HALVES * cdiv(d, TILE);
-  ffn_down_f32_kernel<<<persistent_grid(items, 2), 256, 0, s>>>(
-      (const float*)h, (const float*)w_dn, tiles, hdr, (float*)y, d, Is);
+                            Is, few, max_mtiles, s);
+  const int grid = persistent_grid((long)max_mtiles * F32_BLOCKS * (d / F32_COLS), 2);
+  auto* kern = (long)Is * d >= (1L << 30) ? ffn_down_f32_kernel<true> : ffn_down_f32_kernel<false>;
+  kern<<<grid, 256, F32Tile::LDS_BYTES, s>>>((const float*)h, (const float*)w_dn, tiles, hdr, (float*)y, d, Is);
   return hipGetLastError();
 }
 

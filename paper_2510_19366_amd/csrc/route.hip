@@ -1,7 +1,7 @@
 // Route stage (Sec. 3.2.2, expanded linear gate): router logits with a fixed
 // summation order, then per-token top-k_t and softmax weights.
+#include "chain_tile.h"
 #include "dispatch_common.h"
-#include "dma.h"
 
 namespace mp {
 
@@ -25,54 +25,7 @@ hipError_t launch_expand_k(int R, int T, const int32_t* req_k, const int32_t* re
 // ---------------------------------------------------------------- logits on the matrix cores
 // Every logit is ONE chain of d binary32 fused multiply-adds over the hidden index in
 // ascending order, then the fp32 bias add: the fixed summation order is what makes the
-// routing reproducible bit for bit.  v_mfma_f32_16x16x4_f32 adds its four k terms as four fused
-// multiply-adds in ascending k with one rounding each (checked on the device against fmaf
-// chains, subnormal sums included: bit-identical), so issuing it for k = 0, 4, 8, ... computes
-// exactly that chain.  No split-K, no reordering.
-//
-// What bounds it: the matrix pipe.  One instruction takes 32 cycles whether or not it depends on
-// the previous one, so one chain per wave and one wave per SIMD already run at the full rate, and
-// d = 2048 is 6.8 us for every 16 x 16 sub-tile a SIMD works through.  The fp32 matrix instructions
-// do NOT overlap with vector ALU work (measured: an ALU instruction between two of them costs its
-// 4 cycles plus about 16 for the change-over, LDS reads and scalar work nothing), so the loop
-// contains no vector ALU instruction at all:
-//   * bf16 operands are widened by the LDS read: ds_read_u16_d16_hi writes the upper half of a
-//     register whose lower half stays zero;
-//   * the eight LDS addresses of a lane never change: ring slot, sub-tile and k step are immediate
-//     offsets (the stage loop is unrolled over the ring);
-//   * the copies global -> LDS advance scalar bases.
-//
-// Operands: slabs of 128 bytes per row (64 bf16 or 32 fp32 of K) go global -> LDS directly into
-// a ring of NS stages, NS - 2 of them in flight while one is multiplied and the next one is
-// already published (its first fragments are read early).  Lane l feeds row l & 15 and k = l >> 4
-// of a step.  Chunk c (16 bytes) of row r sits at position c ^ ((r >> 1) & 7): conflict-free reads.
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
-
-template <typename InT, int WM, int WN, int MT, int NT, int NS>
-struct LogitsCfg {  // WM x WN waves, MT x NT sub-tiles of 16 x 16 per wave
-  static constexpr int NW = WM * WN, BT = WM * MT * 16, BE = WN * NT * 16, ROWS = BT + BE;
-  static constexpr int CP = ROWS / 8 / NW;  // copy instructions (8 rows) per wave and stage
-  static constexpr int STAGE = ROWS * 128;
-  static constexpr int LDS_BYTES = NS * STAGE;
-  static constexpr int KB = 128 / (int)sizeof(InT);
-  static constexpr int STEPS = KB / 4;      // matrix steps (4 k) per stage
-  static constexpr int NF = MT + NT;        // fragments per step
-  // fragment sets and how many steps ahead they are read: lgkmcnt counts up to 15 reads
-  static constexpr int R = NF <= 2 ? 8 : 4, PD = NF <= 2 ? 7 : NF <= 5 ? 3 : NF <= 7 ? 2 : 1;
-  static_assert(CP * NW * 8 == ROWS && BT % 8 == 0, "whole copies");
-  static_assert(NS >= 3 && (NS - 1) * CP < 63 && PD * NF <= 15 && STEPS % R == 0, "counters");
-  static_assert(LDS_BYTES <= 65536, "immediate offsets of 16 bits");
-};
-
-// value of this lane's element: bf16 into the upper half (the lower half stays as it is: zero), fp32 whole
-template <typename InT, int OFF>
-__device__ __forceinline__ void read_elem(uint32_t& v, uint32_t addr) {
-  if constexpr (sizeof(InT) == 2)
-    asm volatile("ds_read_u16_d16_hi %0, %1 offset:%2" : "+v"(v) : "v"(addr), "n"(OFF));
-  else
-    asm volatile("ds_read_b32 %0, %1 offset:%2" : "+v"(v) : "v"(addr), "n"(OFF));
-}
-
+// routing reproducible bit for bit.  The chains run on the matrix cores, see chain_tile.h.
 template <typename InT, int WM, int WN, int MT, int NT, int NS>
 __global__ __launch_bounds__(64 * WM * WN) void logits_kernel(const InT* __restrict__ x,
                                                               const InT* __restrict__ w,
@@ -80,18 +33,15 @@ __global__ __launch_bounds__(64 * WM * WN) void logits_kernel(const InT* __restr
                                                               float* __restrict__ logits,
                                                               int32_t* __restrict__ hdr, int T, int d,
                                                               int E) {
-  using C = LogitsCfg<InT, WM, WN, MT, NT, NS>;
-  constexpr int CP = C::CP, PD = C::PD, R = C::R, NF = C::NF;
+  using C = ChainTile<InT, WM, WN, MT, NT, NS>;
+  constexpr int CP = C::CP;
   extern __shared__ __align__(16) unsigned char lg_smem[];
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = wv / WN, wn = wv % WN;
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
     hdr[HDR_FLAGS] = 0;
     hdr[HDR_TOPK_DONE] = 0;
   }
   const int m0 = blockIdx.y * C::BT, n0 = blockIdx.x * C::BE;
-
-  // producer: copy j of this wave takes rows 8 (wv CP + j) .. + 7 of the stage (tokens first)
   const unsigned char* base[CP];
   uint32_t voff[CP];
 #pragma unroll
@@ -100,93 +50,14 @@ __global__ __launch_bounds__(64 * WM * WN) void logits_kernel(const InT* __restr
     const bool tok = r0 < C::BT;  // the same for the whole copy
     base[j] = reinterpret_cast<const unsigned char*>(tok ? x + (size_t)m0 * d : w + (size_t)n0 * d);
     const int rr = tok ? min(row, T - 1 - m0) : min(row - C::BT, E - 1 - n0);
-    voff[j] = (uint32_t)rr * (uint32_t)(d * (int)sizeof(InT)) + (uint32_t)(((lane & 7) ^ ((row >> 1) & 7)) * 16);
+    voff[j] = (uint32_t)rr * (uint32_t)(d * (int)sizeof(InT)) + (uint32_t)(chain_chunk(row) * 16);
   }
-  const uint32_t lds0 = lds_offset(lg_smem);
-  const uint32_t dst0 = lds0 + (uint32_t)(wv * CP) * 1024u;
-  const int ns = d / C::KB;  // d % 64 == 0
-  auto produce = [&](int stage, int slot) {
-    if (stage < ns) {
-#pragma unroll
-      for (int j = 0; j < CP; ++j)
-        copy_to_lds16(base[j] + (size_t)stage * 128, voff[j], dst0 + (uint32_t)(slot * C::STAGE + j * 1024));
-    }
-  };
-#pragma unroll
-  for (int i = 0; i < NS - 1; ++i) produce(i, i);
-
-  // consumer: addresses of this lane's element of chunk c, in token rows and in sub-expert rows
-  const int r = lane & 15, g = lane >> 4;
-  uint32_t at[8], bt[8];
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    const uint32_t o = lds0 + (uint32_t)(r * 128 + ((c ^ ((r >> 1) & 7)) * 16) + g * (int)sizeof(InT));
-    at[c] = o + (uint32_t)(wm * MT) * 2048u;
-    bt[c] = o + (uint32_t)(C::BT + wn * NT * 16) * 128u;
-  }
-  uint32_t fa[R][MT], fb[R][NT];
-#pragma unroll
-  for (int s = 0; s < R; ++s) {
-#pragma unroll
-    for (int i = 0; i < MT; ++i) fa[s][i] = 0;
-#pragma unroll
-    for (int i = 0; i < NT; ++i) fb[s][i] = 0;
-  }
-  auto read = [&](auto slot_c, auto step_c) {  // the fragments of step (0 .. STEPS - 1) of ring slot
-    constexpr int SLOT = decltype(slot_c)::value, STEP = decltype(step_c)::value;
-    constexpr int CH = STEP * 4 * (int)sizeof(InT) / 16;
-    constexpr int OFF = SLOT * C::STAGE + (STEP * 4 * (int)sizeof(InT)) % 16;
-    static_loop<0, MT>([&](auto i) { read_elem<InT, OFF + decltype(i)::value * 2048>(fa[STEP % R][i], at[CH]); });
-    static_loop<0, NT>([&](auto i) { read_elem<InT, OFF + decltype(i)::value * 2048>(fb[STEP % R][i], bt[CH]); });
-  };
   f32x4_t acc[MT][NT];
-#pragma unroll
-  for (int i = 0; i < MT; ++i)
-#pragma unroll
-    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  chain_tile<C>(lg_smem, d / C::KB, [&](int j, int stage, uint32_t lds) {  // d % 64 == 0
+    copy_to_lds16(base[j] + (size_t)stage * 128, voff[j], lds);
+  }, acc);
 
-  if (ns >= NS - 1)
-    wait_vmem<(NS - 2) * CP>();  // stage 0
-  else
-    wait_vmem<0>();
-  raw_barrier();
-  static_loop<0, PD>([&](auto s) { read(std::integral_constant<int, 0>{}, s); });
-  // Stage q: its successor's copies have landed for this wave (wait) and, behind the barrier,
-  // for all.  The barrier also frees the slot of stage q - 1 (every wave had its last fragments in
-  // registers before its last multiply), which takes stage q + NS - 1.
-  for (int q0 = 0; q0 < ns; q0 += NS) {
-    static_loop<0, NS>([&](auto slot_c) {
-      constexpr int SLOT = decltype(slot_c)::value, NSLOT = (SLOT + 1) % NS;
-      const int q = q0 + SLOT;
-      if (q >= ns) return;
-      if (q + NS - 2 < ns)
-        wait_vmem<(NS - 3) * CP>();
-      else
-        wait_vmem<0>();
-      raw_barrier();
-      produce(q + NS - 1, (SLOT + NS - 1) % NS);
-      __builtin_amdgcn_sched_barrier(0);
-      static_loop<0, C::STEPS>([&](auto step_c) {
-        constexpr int S = decltype(step_c)::value, A = S + PD;
-        if constexpr (A < C::STEPS)
-          read(slot_c, std::integral_constant<int, A>{});
-        else  // after the last stage: an old slot, not used
-          read(std::integral_constant<int, NSLOT>{}, std::integral_constant<int, A - C::STEPS>{});
-        asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(PD * NF));  // the reads of this step have returned
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-          for (int j = 0; j < NT; ++j)  // ascending k
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(fa[S % R][i]), __uint_as_float(fb[S % R][j]),
-                                                            acc[i][j], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      });
-    });
-  }
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-
-  // accumulator v of lane l: token 4 (l >> 4) + v, sub-expert l & 15 of the sub-tile
+  const int wm = wv / WN, wn = wv % WN, r = lane & 15, g = lane >> 4;
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
     const int col = n0 + (wn * NT + j) * 16 + r;
@@ -209,7 +80,7 @@ __global__ void clear_flags_kernel(int32_t* hdr) { hdr[HDR_FLAGS] = 0; }
 template <typename InT, int MT, int NT, int NS>
 static void launch_logits_cfg(const InT* x, const InT* w, const float* bias, float* logits,
                               int32_t* hdr, int T, int d, int E, hipStream_t s) {
-  using C = LogitsCfg<InT, 2, 2, MT, NT, NS>;
+  using C = ChainTile<InT, 2, 2, MT, NT, NS>;
   logits_kernel<InT, 2, 2, MT, NT, NS><<<dim3(cdiv(E, C::BE), cdiv(T, C::BT)), 64 * C::NW, C::LDS_BYTES, s>>>(
       x, w, bias, logits, hdr, T, d, E);
 }
