@@ -12,6 +12,7 @@
 //     64 K-elements that is refilled piece by piece;
 //   run_items (shorter K): 64-wide slabs through registers into a double-buffered, XOR-swizzled
 //     LDS tile, one slab ahead of the MFMAs.
+// So few pairs that these tiles would leave CUs idle take ffn_few_kernel (tiles of 64 weight rows).
 // Narrow sub-experts (Is in {64, 128, 192}) take the fused kernel in ffn_fused_bf16.hip
 // instead; these two kernels serve every other shape.
 #include <type_traits>
@@ -23,6 +24,7 @@ namespace mp {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_few;
 
 constexpr int BM = FFN_BM;   // slot rows per tile
 constexpr int BN = 256;      // weight rows per tile
@@ -710,6 +712,106 @@ __global__ __launch_bounds__(NT_) void ffn_short_kernel(Op op, const MTile* __re
   run_items<Op>(op, tiles, hdr, n_tiles_n);
 }
 
+// ---------------------------------------------------------------- few pairs
+// A handful of tokens touches a handful of sub-experts, and tiles of 256 weight rows are then fewer
+// than the CUs: one workgroup's copies (100 KB in flight, about 80 GB/s) set the time.  Here a
+// tile is 64 weight rows x 32 slot rows, 4 waves (2 weight blocks x 2 halves of every K stage), with
+// a ring of 6 stages of 64 K-elements and two workgroups per CU; the K halves meet in LDS.
+// Bound by the latency of one chain: ring fill, K stages, reduction.  Measured, one token of the
+// 128 x 4 layer (20 sub-experts of 192, d = 2048, 47 MB of weights): gate-up and down together
+// 17 us, the fused kernel 80 us.
+constexpr int FP_N = 64, FP_M = 32, FP_NS = 6, FP_THREADS = 256;
+constexpr int FP_STAGE = (FP_M + FP_N) * BK * 2, FP_LDS_BYTES = FP_NS * FP_STAGE;
+constexpr int FP_CP = (FP_M + FP_N) / 8 / (FP_THREADS / 64);  // copies per wave and stage
+constexpr int FP_BLOCKS = FFN_BM / FP_M;                      // row blocks of an m-tile
+
+template <class Op>
+__global__ __launch_bounds__(FP_THREADS) void ffn_few_kernel(Op op, const MTile* __restrict__ tiles,
+                                                             const int32_t* __restrict__ hdr, int n_tiles_n) {
+  extern __shared__ __align__(16) unsigned char fp_smem[];
+  const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
+  const int wb = wv & 1, kh = wv >> 1;  // weight block, half of the K steps
+  const int fr = lane & 31, fh = lane >> 5, wrow = Op::wrow(fr);
+  const int K = op.K(), ns = (K + BK - 1) / BK;
+  const uint32_t lds0 = lds_offset(fp_smem), dst0 = lds0 + (uint32_t)(wv * FP_CP) * 1024u;
+  // items: (m-tile, row block, n-tile); an item whose row block is empty is skipped
+  const ItemRange ir = xcd_items(hdr[HDR_MTILES] * FP_BLOCKS * n_tiles_n);
+  for (int item = ir.begin; item < ir.end; item += ir.step) {
+    const MTile t = tiles[item / (FP_BLOCKS * n_tiles_n)];
+    const int blk = item / n_tiles_n % FP_BLOCKS;
+    Sc sc;
+    sc.g = uni(t.g);
+    sc.row0 = uni(t.row0) + blk * FP_M;
+    sc.rows = min(FP_M, uni(t.rows) - blk * FP_M);
+    sc.n0 = item % n_tiles_n * (FP_N / Op::N_PER_ROW);
+    if (sc.rows <= 0) continue;  // uniform over the workgroup
+    const uint16_t *ba, *bb;
+    op.bases(sc, ba, bb);
+    const uint16_t* base[FP_CP];
+    uint32_t voff[FP_CP], tail[FP_CP];
+#pragma unroll
+    for (int j = 0; j < FP_CP; ++j) {
+      const int r0 = (wv * FP_CP + j) * 8, row = r0 + (lane >> 3);
+      const bool slot = r0 < FP_M;  // the same for the whole copy
+      const int br = row - FP_M;
+      const int rr = slot ? op.a_row(sc, row, Op::GATHER ? *op.idx_src(sc, row) : 0) : op.b_row(sc, br);
+      const int chunk = (lane & 7) ^ (slot ? swz_f<SWZ_SEQ>(row) : swz_f<Op::WSWZ>(br & 31));
+      base[j] = slot ? ba : bb;
+      voff[j] = (uint32_t)rr * (uint32_t)K * 2u + (uint32_t)chunk * 16u;
+      tail[j] = chunk & 4 ? 64u : 0u;
+    }
+    auto produce = [&](int stage) {
+      if (stage >= ns) return;
+      const bool cut = (stage + 1) * BK > K;  // K % 64 == 32: chunks 4..7 do not exist, fetch 0..3 (not used)
+#pragma unroll
+      for (int j = 0; j < FP_CP; ++j)
+        copy_to_lds16(base[j] + (size_t)stage * BK, cut ? voff[j] - tail[j] : voff[j],
+                      dst0 + (uint32_t)(stage % FP_NS * FP_STAGE + j * 1024));
+    };
+    for (int i = 0; i < FP_NS - 1; ++i) produce(i);
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+    for (int q = 0; q < ns; ++q) {
+      if (q + FP_NS - 2 < ns)
+        wait_vmem<(FP_NS - 2) * FP_CP>();  // stage q has landed
+      else
+        wait_vmem<0>();
+      raw_barrier();         // for every wave; and the slot of stage q - 1 has been read
+      produce(q + FP_NS - 1);
+      const unsigned char* s = fp_smem + q % FP_NS * FP_STAGE;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int ks = 2 * kh + i, c = 2 * ks + fh;
+        if (q * BK + ks * 16 < K) {
+          const bf16x8 ft = *reinterpret_cast<const bf16x8*>(s + fr * 128 + ((c ^ swz_f<SWZ_SEQ>(fr)) * 16));
+          const bf16x8 fw = *reinterpret_cast<const bf16x8*>(s + (FP_M + wb * 32 + wrow) * 128 + ((c ^ swz_f<Op::WSWZ>(wrow)) * 16));
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw, ft, acc, 0, 0, 0);
+        }
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this slot has been read
+    }
+    // the second halves through LDS (64 bytes per lane, 16-byte pieces rotated over the banks)
+    __syncthreads();
+    f32x4_few* red = reinterpret_cast<f32x4_few*>(fp_smem) + (size_t)wb * 256 + lane;
+    if (kh == 1) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[v * 64] = f32x4_few{acc[4 * v], acc[4 * v + 1], acc[4 * v + 2], acc[4 * v + 3]};
+    }
+    __syncthreads();
+    if (kh == 0) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const f32x4_few o = red[v * 64];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[4 * v + e] += o[e];
+      }
+      if (fr < sc.rows) op.store_block(sc, fr, wb, fh, acc);
+    }
+    __syncthreads();  // the ring is filled again
+  }
+}
+
 // ---------------------------------------------------------------- launchers
 // The ring driver runs its producers two stages ahead, enters at most one new item per stage and
 // needs the next item's slot list one barrier before that: at least 4 stages per item.
@@ -724,8 +826,16 @@ static hipError_t launch_big(size_t lds, int grid, hipStream_t s, const Op& op, 
 }
 
 template <class Op>
-static hipError_t launch_op(const Op& op, int K, int n_cols, bool fits, int dyn_word, int max_mtiles,
+static hipError_t launch_op(const Op& op, int K, int n_cols, bool fits, bool few, int dyn_word, int max_mtiles,
                             const MTile* tiles, int32_t* hdr, hipStream_t s) {
+  if (few && fits) {
+    const int ntn = cdiv(n_cols, FP_N / Op::N_PER_ROW);
+    const int grid = persistent_grid((long)max_mtiles * FP_BLOCKS * ntn, 2);
+    hipError_t e = raise_lds_limit<ffn_few_kernel<Op>>(FP_LDS_BYTES);
+    if (e != hipSuccess) return e;
+    ffn_few_kernel<Op><<<grid, FP_THREADS, FP_LDS_BYTES, s>>>(op, tiles, hdr, ntn);
+    return hipGetLastError();
+  }
   const int ntn = cdiv(n_cols, BN / Op::N_PER_ROW);
   const int grid = persistent_grid((long)max_mtiles * ntn, 1);
   constexpr size_t ring = Ring<Op::GATHER>::LDS_BYTES;
@@ -736,17 +846,26 @@ static hipError_t launch_op(const Op& op, int K, int n_cols, bool fits, int dyn_
   return launch_big<ffn_ring_kernel<Op, false>>(ring, grid, s, op, tiles, hdr, ntn, dyn_word);
 }
 
+// At most 64 tokens (a group is then one or two row blocks; more would read the weights again for
+// each), and the ring kernel's n-tiles of all sub-experts that they can touch are fewer than 1.5 per
+// CU.  A narrow sub-expert is one workgroup of the fused kernel and costs 80 us at d = 2048 however
+// few there are, as much as this path takes for about 200 of them.
+bool ffn_few_pairs(int T, int k_max, int E, int Is) {
+  const long pairs = (long)T * k_max, groups = pairs < E ? pairs : E;
+  return T <= 64 && groups * cdiv(Is, BN / 2) * 2 <= 3L * num_cus() * (Is <= 192 ? 2 : 1);
+}
+
 hipError_t launch_gate_up_bf16(const uint16_t* x, const uint16_t* w_gu, const int32_t* sorted_pair,
                                const MTile* tiles, int32_t* hdr, uint16_t* h, int T, int d,
-                               int Is, int k_max, int max_mtiles, hipStream_t s) {
-  return launch_op(GateUpOp{x, w_gu, sorted_pair, h, T, d, Is, k_max}, d, Is, GateUpOp::offsets_fit(T, d, Is),
+                               int Is, int k_max, bool few, int max_mtiles, hipStream_t s) {
+  return launch_op(GateUpOp{x, w_gu, sorted_pair, h, T, d, Is, k_max}, d, Is, GateUpOp::offsets_fit(T, d, Is), few,
                    HDR_DYN_GATE_UP, max_mtiles, tiles, hdr, s);
 }
 
 hipError_t launch_down_bf16(const uint16_t* h, const uint16_t* w_dn, const MTile* tiles,
-                            int32_t* hdr, uint16_t* y, int d, int Is, int max_mtiles,
+                            int32_t* hdr, uint16_t* y, int d, int Is, bool few, int max_mtiles,
                             hipStream_t s) {
-  return launch_op(DownOp{h, w_dn, y, d, Is}, Is, d, DownOp::offsets_fit(0, d, Is), HDR_DYN_DOWN, max_mtiles,
+  return launch_op(DownOp{h, w_dn, y, d, Is}, Is, d, DownOp::offsets_fit(0, d, Is), few, HDR_DYN_DOWN, max_mtiles,
                    tiles, hdr, s);
 }
 
