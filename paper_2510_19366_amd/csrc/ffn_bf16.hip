@@ -60,9 +60,6 @@ __device__ __forceinline__ int swz(int r, int c) {  // in elements
 // Tile header fields are the same for every lane: keep them in scalar registers.
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-__device__ __forceinline__ float silu_mul(float a, float u) {
-  return __fdividef(a, 1.0f + __expf(-a)) * u;
-}
 __device__ __forceinline__ uint32_t pack2(float a, float b) { return pack_bf16x2(a, b); }
 
 // What every lane knows about a work item: group, first slot row, valid rows, first

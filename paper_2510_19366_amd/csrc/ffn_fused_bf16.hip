@@ -147,9 +147,6 @@ __device__ __forceinline__ void barrier() {
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }
-__device__ __forceinline__ float silu_mul(float a, float u) {
-  return __fdividef(a, 1.0f + __expf(-a)) * u;
-}
 
 // weight-row permutations (MFMA row i = 8a + 4hi + b of a 32-row block):
 // phase 1: block row 16*(a>>1) + 8hi + 4(a&1) + b, block rows 0..15 = gate rows of 16 neurons,
