@@ -14,15 +14,16 @@
 // registers, no LDS round trip, no barrier between the phases, and neither h nor a second
 // pass over the tile table touches HBM.
 //
-// Operands travel global -> LDS directly (global_load_lds_dwordx4).  Weights: a ring of 4
-// slots of Is*128 bytes shared by the waves (phase 1: 2*Is rows x 32 K-elements; phase 2:
-// 64 output columns x Is K-elements; both fill a slot exactly), published by one s_barrier
-// per stage.  Slot rows of x: a ring of 3 slots of 2 KiB PRIVATE to each wave (a wave copies
-// the rows it multiplies itself), so x needs no barrier.  Two stages are in flight while one
-// is multiplied.  vmcnt retires in issue order, so "everything but the operations this wave
-// issued in the previous iteration has landed" is one s_waitcnt with that count.
+// Operands travel global -> LDS directly (global_load_lds_dwordx4), in whole 128-byte lines.
+// Weights: a ring of 4 slots of Is*128 bytes shared by the waves (phase 1: Is rows, half of gate and
+// up, x 64 K-elements; phase 2: 64 output columns x Is K-elements; both fill a slot exactly),
+// published by one s_barrier per stage; two stages are in flight while one is multiplied.  Slot
+// rows of x: one slot of 4 KiB PRIVATE to each wave (a wave copies the rows it multiplies itself,
+// so x needs no barrier), refilled as soon as its fragments are in registers.  vmcnt retires in
+// issue order, so a wait is for the number of operations issued behind the ones needed.
 #include <type_traits>
 
+#include "dma.h"
 #include "ffn_common.h"
 
 namespace mp {
@@ -35,10 +36,8 @@ namespace fused {
 constexpr int NT = 512;   // threads: 8 waves
 constexpr int BM = FFN_BM;
 constexpr int NSW = 4;    // weight ring slots
-constexpr int NSX = 3;    // x ring slots (per wave)
-constexpr int X_WAVE = 32 * 64;        // bytes of one wave's x stage: 32 rows x 32 K-elements
-constexpr int X_SLOT = 8 * X_WAVE;
-constexpr int EPI_WAVE = 1024;         // bytes of a wave's output staging: 16 rows x 32 columns
+constexpr int X_WAVE = 32 * 128;       // bytes of one wave's x slot: 32 rows x 64 K-elements
+constexpr int EPI_WAVE = 16 * 128;     // bytes of a wave's output staging: 16 rows x 64 columns
 constexpr int RUN = 32;   // consecutive tiles an XCD takes per turn
 constexpr int PD = 4;     // fragment reads in flight ahead of the MFMAs
 
@@ -46,53 +45,42 @@ template <int IS>
 struct Cfg {
   static_assert(IS % 64 == 0 && IS >= 64 && IS <= 192, "fused path: Is in {64, 128, 192}");
   static constexpr int NBLK = IS / 16;     // 32-row weight blocks of phase 1 = K steps of phase 2
+  static constexpr int HB = NBLK / 2;      // blocks of a phase-1 stage
   static constexpr int WPW = IS / 64;      // copy instructions per wave and weight stage
   static constexpr int W_SLOT = IS * 128;  // bytes
   static constexpr int CPR = IS / 8;       // 16-byte chunks per weight row in phase 2
   static constexpr int ROW2 = IS * 2;      // bytes per weight row in phase 2
   static constexpr int OFF_X = NSW * W_SLOT;
-  static constexpr int OFF_PAIR = OFF_X + NSX * X_SLOT;
-  static constexpr int OFF_EPI = OFF_PAIR + 2 * BM * 4;  // 1 KiB per wave: output transposition
+  static constexpr int OFF_PAIR = OFF_X + 8 * X_WAVE;
+  static constexpr int OFF_EPI = OFF_PAIR + 2 * BM * 4;   // output transposition
   static constexpr int OFF_DYN = OFF_EPI + 8 * EPI_WAVE;  // two words: tile numbers drawn by wave 0
   static constexpr int LDS_BYTES = OFF_DYN + 16;
+  // steps of a stage (one MFMA each) behind which things happen
+  static constexpr int STEPS = 2 * NBLK;
+  static constexpr int BAR = 1;                        // the stage's wait and barrier
+  static constexpr int W0 = 2, W_END = W0 + WPW;       // copies of weights, one per step
+  static constexpr int PREP = STEPS - 1;               // the next stage's weight copies are prepared
+  // copy j of the four of x; in phase 1 behind the step that waits for the last read of the slot
+  static constexpr int X0 = W_END > PD ? W_END : PD;
+  static constexpr int x_copy(int j) { return X0 + (STEPS > 8 ? j : j / 2); }
+  static constexpr int XW = STEPS - 5;                 // phase 1: x of the next stage pair has to be there
+  // phase 2, output of the previous stage: half h goes into the staging buffer, quarter k (8 rows)
+  // is read back and stored
+  static constexpr int out_write(int h) { return STEPS > 8 ? W0 + 1 + h * (STEPS * 5 / 12) : 2 + 2 * h; }
+  static constexpr int out_read(int k) {
+    return out_write(k / 2) + (STEPS > 16 ? 3 + k % 2 * 2 : STEPS > 8 ? 2 + k % 2 : 1);
+  }
+  static constexpr int out_store(int k) { return out_read(k) + (STEPS > 16 ? 3 : STEPS > 8 ? 2 : 1); }
+  static_assert(STEPS % PD == 0 && 3 * HB >= PD && XW + PD < STEPS && XW + 2 >= 3 * HB - 1, "fragment registers");
+  static_assert(out_write(0) < out_read(0) && out_read(1) <= out_write(1) && out_store(0) >= W_END &&
+                    out_store(3) < STEPS && XW >= W_END && x_copy(3) < STEPS,
+                "order inside a stage");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS per CU");
 };
 
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// Wave-wide copies global -> LDS: lane i's 16 (4) bytes at base + voff land at lds + 16 i (4 i).
-// N copies of one group go to consecutive KiB of LDS.  m0 carries the LDS address; it is
-// reserved by the compiler, so its value is put back.
-template <int N>
-__device__ __forceinline__ void dma16_group(const void* base, const uint32_t (&voff)[N], uint32_t lds) {
-  static_assert(N >= 1 && N <= 3, "copies per group");
-  uint32_t keep;
-  if constexpr (N == 1) {
-    asm volatile(
-        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\t"
-        "global_load_lds_dwordx4 %1, %2\n\ts_mov_b32 m0, %0"
-        : "=&s"(keep)
-        : "v"(voff[0]), "s"(base), "s"(lds)
-        : "memory");
-  } else if constexpr (N == 2) {
-    asm volatile(
-        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %4\n\ts_nop 0\n\t"
-        "global_load_lds_dwordx4 %1, %3\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
-        "global_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
-        : "=&s"(keep)
-        : "v"(voff[0]), "v"(voff[1]), "s"(base), "s"(lds)
-        : "memory", "scc");
-  } else {
-    asm volatile(
-        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %5\n\ts_nop 0\n\t"
-        "global_load_lds_dwordx4 %1, %4\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
-        "global_load_lds_dwordx4 %2, %4\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
-        "global_load_lds_dwordx4 %3, %4\n\ts_mov_b32 m0, %0"
-        : "=&s"(keep)
-        : "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "s"(base), "s"(lds)
-        : "memory", "scc");
-  }
-}
+// wave-wide copy of 4 bytes per lane (see copy_to_lds16)
 __device__ __forceinline__ void dma4(const void* base, uint32_t voff, uint32_t lds) {
   uint32_t keep;
   asm volatile(
@@ -102,52 +90,36 @@ __device__ __forceinline__ void dma4(const void* base, uint32_t voff, uint32_t l
       : "v"(voff), "s"(base), "s"(lds)
       : "memory");
 }
-// 16-byte store at base + voff + IMM, counted by hand like the copies (the compiler neither
+// 16-byte store at base + voff, counted by hand like the copies (the compiler neither
 // merges nor splits it).  A store of more than 8 bytes reads its data registers for a few
 // cycles after issue and the compiler's hazard handling does not look inside an asm block:
 // the s_nop keeps the next VALU write away from them.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-template <int IMM>
 __device__ __forceinline__ void store16(void* base, uint32_t voff, u32x4 v) {
-  asm volatile("global_store_dwordx4 %0, %1, %2 offset:%3\n\ts_nop 1" ::"v"(voff), "v"(v), "s"(base), "n"(IMM)
-               : "memory");
+  asm volatile("global_store_dwordx4 %0, %1, %2\n\ts_nop 1" ::"v"(voff), "v"(v), "s"(base) : "memory");
 }
-// f(integral_constant<I>) for I = BEGIN .. END-1: a loop whose index can be a template argument
-template <int BEGIN, int END, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (BEGIN < END) {
-    f(std::integral_constant<int, BEGIN>{});
-    static_for<BEGIN + 1, END>(f);
-  }
+// until at most n of this wave's vector memory operations are pending, for n one of the given
+// counts, largest first (another n: the next smaller one).  The steady state falls through; a branch per
+// count would cost more than the waits.
+template <int A, int B, int C, int D>
+__device__ __forceinline__ void wait_one_of4(int n) {
+  asm volatile(
+      "s_waitcnt vmcnt(%1)\n\ts_cmp_ge_i32 %0, %1\n\ts_cbranch_scc1 1f\n\t"
+      "s_waitcnt vmcnt(%2)\n\ts_cmp_ge_i32 %0, %2\n\ts_cbranch_scc1 1f\n\t"
+      "s_waitcnt vmcnt(%3)\n\ts_cmp_ge_i32 %0, %3\n\ts_cbranch_scc1 1f\n\t"
+      "s_waitcnt vmcnt(%4)\n1:" ::"s"(n),
+      "n"(A), "n"(B), "n"(C), "n"(D)
+      : "memory", "scc");
 }
-// until at most n of this wave's vector memory operations are pending (n is wave-uniform, 0..12;
-// the count is an immediate of s_waitcnt, so n selects one of 13 instructions by bisection)
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+template <int A, int B, int... MORE>
+__device__ __forceinline__ void wait_one_of(int n) {
+  if constexpr (sizeof...(MORE) == 0)
+    asm volatile("s_waitcnt vmcnt(%1)\n\ts_cmp_ge_i32 %0, %1\n\ts_cbranch_scc1 1f\n\ts_waitcnt vmcnt(%2)\n1:" ::"s"(n),
+                 "n"(A), "n"(B)
+                 : "memory", "scc");
+  else
+    wait_one_of4<A, B, MORE...>(n);
 }
-template <int LO, int HI>
-__device__ __forceinline__ void wait_bisect(int n) {
-  if constexpr (LO == HI) {
-    wait_vm<LO>();
-  } else {
-    constexpr int MID = (LO + HI + 1) / 2;
-    if (n >= MID)
-      wait_bisect<MID, HI>(n);
-    else
-      wait_bisect<LO, MID - 1>(n);
-  }
-}
-__device__ __forceinline__ void wait_pending(int n) { wait_bisect<0, 12>(n > 12 ? 0 : n); }
-__device__ __forceinline__ void barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
-}
-
 // weight-row permutations (MFMA row i = 8a + 4hi + b of a 32-row block):
 // phase 1: block row 16*(a>>1) + 8hi + 4(a&1) + b, block rows 0..15 = gate rows of 16 neurons,
 // 16..31 = their up rows: accumulators 0..7 of a lane = gate of neurons 8hi..8hi+7, 8..15 = up
@@ -162,8 +134,9 @@ __device__ __forceinline__ int wrow_dn(int i) {
 }
 // LDS swizzles (16-byte chunk c of row r sits at chunk position c ^ f(r)); 16 lanes read 16
 // rows at one chunk index, f spreads them over all banks.
-// 64-byte rows (phase 1, both operands): rows of equal r & 3 share banks
-__device__ __forceinline__ int f1(int r) { return (r >> 2) & 3; }
+// 128-byte rows (phase 1, both operands, and the output staging), 16 consecutive rows: rows of
+// equal parity share banks
+__device__ __forceinline__ int f1(int r) { return (r >> 1) & 7; }
 // Is*2-byte rows (phase 2): 384- and 128-byte rows alternate between two bank halves (8 rows of
 // equal parity must differ), 256-byte rows all start in bank 0 (16 rows must differ); the 16
 // rows read together are {0..7, 16..23} + const
@@ -172,21 +145,30 @@ __device__ __forceinline__ int f2(int r) {
   return IS == 128 ? ((r & 7) | (((r >> 4) & 1) << 3)) : (((r >> 1) & 3) | (((r >> 4) & 1) << 2));
 }
 
+// A fragment read into the register it is given (tied), not tracked by the compiler, and the wait
+// for all but the youngest N of this wave's LDS reads; a and b may be used behind it.
+template <int OFF>
+__device__ __forceinline__ void read_frag(bf16x8& v, uint32_t addr) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "+v"(v) : "v"(addr), "n"(OFF));
+}
+template <int N>
+__device__ __forceinline__ void wait_frags(bf16x8& a, bf16x8& b) {
+  asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N));
+}
+
 struct TileHdr {  // wave-uniform
   int g, row0, rows;
 };
 
 // One matrix-core step.  MATH = false is the traffic probe: the same operand reads, copies,
-// barriers, waits and stores, with one cheap ALU operation in place of the multiply (the
-// fragments stay live, the results mean nothing).
+// barriers, waits and stores, without the multiply (the fragments count as used, the results mean
+// nothing).
 template <bool MATH>
 __device__ __forceinline__ f32x16 mma(bf16x8 a, bf16x8 b, f32x16 c) {
   if constexpr (MATH) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   } else {
-    const uint4 u = __builtin_bit_cast(uint4, a), v = __builtin_bit_cast(uint4, b);
-    c[0] += __uint_as_float((u.x ^ v.x) & 0x3fffffffu);
-    c[5] += __uint_as_float((u.w ^ v.y) & 0x3fffffffu);
+    asm volatile("" ::"v"(a), "v"(b));
     return c;
   }
 }
@@ -224,7 +206,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   if (k0 >= n_tiles) return;  // uniform over the workgroup
   __syncthreads();            // dyn_lds is written again below
 
-  const uint32_t lds0 = lds_addr(smem);
+  const uint32_t lds0 = lds_offset(smem);
   const int32_t* pair_lds = reinterpret_cast<const int32_t*>(smem + C::OFF_PAIR);
 
   auto load_hdr = [&](int k, TileHdr& t) {
@@ -234,23 +216,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     t.rows = uni(m.rows);
   };
 
-  // ---- per-lane copy offsets that never change
-  // phase 1 weights: piece pc = 16 ring rows; ring row lr holds block row lr & 31 of block lr >> 5
-  uint32_t voff_w1[WPW];
-#pragma unroll
-  for (int j = 0; j < WPW; ++j) {
-    const int pc = wv * WPW + j;
-    const int lr = pc * 16 + (lane >> 2), pos = lane & 3;
-    const int rr = lr & 31, neuron = (lr >> 5) * 16 + (rr & 15);
-    const int grow = (rr >> 4) ? IS + neuron : neuron;
-    voff_w1[j] = (uint32_t)grow * (uint32_t)d * 2u + (uint32_t)((pos ^ f1(lr)) * 16);
-  }
-  // phase 2 weights: piece = 64 consecutive 16-byte positions of a [64 x CPR] slot; computed
-  // when needed (registers are scarcest in phase 1, which does not use these)
-  auto voff_w2 = [&](int j) {
-    const int p = (wv * WPW + j) * 64 + lane, r2 = p / C::CPR, pos2 = p % C::CPR;
-    return (uint32_t)r2 * C::ROW2 + (uint32_t)((pos2 ^ f2<IS>(r2)) * 16);
-  };
   // A copy of the lane id that the optimiser cannot see through: per-lane constants of one
   // phase are derived from it at the start of that phase, so they do not occupy registers
   // during the other (phase 1 runs at the register limit).
@@ -259,23 +224,40 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     asm volatile("" : "+v"(l));
     return l;
   };
-
-  // x offsets of the rows this lane copies (2 pieces of 16 rows) from a tile's slot list in LDS
-  auto x_offsets = [&](int parity, uint32_t (&xo)[2]) {
+  // (by hand: the compiler would take a 64-bit multiply-add and keep a pair of registers)
+  const uint32_t d2 = (uint32_t)d * 2u;
+  auto row_bytes = [&](int row) {
+    uint32_t v;
+    asm("v_mul_lo_u32 %0, %1, %2" : "=v"(v) : "v"(row), "s"(d2));
+    return v;
+  };
+  // Offsets of the weight copies.  Phase 1: piece pc = 8 ring rows of 64 K-elements; ring row lr
+  // holds block row lr & 31 of block lr >> 5 of the stage's half of the blocks: the piece starts at
+  // a weight row that is the same for all lanes (piece_row, of the first half), and odd pieces have
+  // the other swizzle (f1).  Phase 2: a wave copies ring rows 8 wv .. 8 wv + 7, piece j = 64
+  // consecutive 16-byte positions of them.
+  const uint32_t voff_w1 = row_bytes(lane >> 3) + (uint32_t)(((lane & 7) ^ (lane >> 4)) * 16);
+  auto piece_row = [&](int pc) { return (pc >> 2) * 16 + (pc & 1) * 8 + ((pc & 2) ? IS : 0); };
+  auto voff_w2 = [&](int j) {
+    const uint32_t p = j * 64 + opaque_lane(), r2 = p / C::CPR;
+    return (p ^ (uint32_t)f2<IS>(r2) ^ (uint32_t)f2<IS>(wv * 8)) * 16u;
+  };
+  // x offsets of the rows this lane copies (4 pieces of 8 rows) from a tile's slot list in LDS
+  uint32_t xoff[4];
+  auto x_offsets = [&](int parity) {
     const int l = opaque_lane();
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int lr = j * 16 + (l >> 2), pos = l & 3;
+    for (int j = 0; j < 4; ++j) {
+      const int lr = j * 8 + (l >> 3), pos = l & 7;
       int tok = pair_lds[parity * BM + wv * 32 + lr] / k_max;
       tok = min(max(tok, 0), T - 1);
-      xo[j] = (uint32_t)tok * (uint32_t)d * 2u + (uint32_t)((pos ^ f1(lr)) * 16);
+      xoff[j] = row_bytes(tok) + (uint32_t)((pos ^ f1(lr)) * 16);
     }
   };
-  auto fetch_pairs = [&](const TileHdr& t, int parity) -> int {  // waves 0..3, 64 rows each
-    if (wv >= 4) return 0;
+  auto fetch_pairs = [&](const TileHdr& t, int parity) {  // waves 0..3, 64 rows each
+    if (wv >= 4) return;
     const int r = max(min(wv * 64 + opaque_lane(), t.rows - 1), 0);
     dma4(sorted_pair + t.row0, (uint32_t)r * 4u, lds0 + C::OFF_PAIR + (uint32_t)(parity * BM + wv * 64) * 4u);
-    return 1;
   };
 
   // ---- prologue: tile 0's slot list
@@ -287,195 +269,191 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   int k_after = n_tiles;  // the tile after `nxt` (>= n_tiles: none)
   int par = 0;            // which half of the slot-list buffer holds the current tile's entries
   fetch_pairs(cur, 0);
-  wait_vm<0>();
-  barrier();
+  wait_vmem<0>();
+  raw_barrier();
 
-  // ---- producers.  Each keeps a running global pointer and LDS address and counts the stages
-  // left in its phase; they run ahead of the multiplying code across phase and tile borders
-  // (the next tile's header `nxt` is known a whole tile ahead).
-  // weights: stage q + 3
-  const uint16_t* pw_ptr = w_gu + (size_t)cur.g * (2 * IS) * d;
+  // ---- producer of weights, stage q + 3.  It keeps a running global pointer and LDS address and
+  // counts the stages left in its phase; it runs ahead of the multiplying code across phase and
+  // tile borders (the next tile's header `nxt` is known a whole tile ahead).  Behind the last tile's
+  // last stage that stage is copied again (nobody reads it), so that every stage issues the same
+  // number of copies.
+  const int half_w = IS / 2 * d;  // elements from a gate row of the first half to that of the second
+  const uint16_t* pw_ptr = w_gu + (size_t)cur.g * (2 * IS) * d + half_w - 64;
   int pw_g = cur.g, pw_phase = 0, pw_cnt = S1;
-  bool pw_on = true;  // false once the last tile's last stage has been issued
   const uint32_t pw_dst0 = lds0 + (uint32_t)(wv * WPW) * 1024u;
-  uint32_t pw_dst = pw_dst0;
-  auto produce_w = [&]() -> int {
-    if (!pw_on) return 0;
-    if (pw_phase) {
-      uint32_t vo[WPW];
-#pragma unroll
-      for (int j = 0; j < WPW; ++j) vo[j] = voff_w2(j);
-      dma16_group<WPW>(pw_ptr, vo, pw_dst);
-      pw_ptr += 64 * IS;
-    } else {
-      dma16_group<WPW>(pw_ptr, voff_w1, pw_dst);
-      pw_ptr += 32;
-    }
-    pw_dst = pw_dst + C::W_SLOT == pw_dst0 + NSW * C::W_SLOT ? pw_dst0 : pw_dst + C::W_SLOT;
-    if (--pw_cnt == 0) {
+  uint32_t pw_dst = pw_dst0 + (NSW - 1) * C::W_SLOT;
+  auto prep_w = [&]() {
+    pw_dst = pw_dst == pw_dst0 + (NSW - 1) * C::W_SLOT ? pw_dst0 : pw_dst + C::W_SLOT;
+    if (pw_cnt == 0) {
       if (pw_phase == 0) {  // on to the down weights of the same group
         pw_phase = 1;
         pw_cnt = S2;
-        pw_ptr = w_dn + (size_t)pw_g * d * IS;
+        pw_ptr = w_dn + (size_t)pw_g * d * IS - 64 * IS;
       } else if (has_next) {  // on to the next tile
         pw_phase = 0;
         pw_cnt = S1;
         pw_g = nxt.g;
-        pw_ptr = w_gu + (size_t)pw_g * (2 * IS) * d;
+        pw_ptr = w_gu + (size_t)pw_g * (2 * IS) * d + half_w - 64;
       } else {
-        pw_on = false;
+        return;
       }
     }
-    return WPW;
+    pw_ptr += pw_phase ? 64 * IS : (pw_cnt & 1) ? half_w : 64 - half_w;  // S1 is even
+    --pw_cnt;
   };
-  // x: stage q + 2, phase-1 stages only, and only for a wave that has rows in the tile.  The
-  // cursor leaves a tile only while the multiplying code is in that tile's phase 2, which is
-  // where the next tile's offsets `xo_next` live.
-  uint32_t xoff[2];
-  x_offsets(0, xoff);
-  const uint16_t* px_ptr = x;
-  int px_s = 0;
-  bool px_on = true;
-  bool px_act = cur.rows > wv * 32;
-  const uint32_t px_dst0 = lds0 + C::OFF_X + (uint32_t)wv * X_WAVE;
-  uint32_t px_dst = px_dst0;
-  auto produce_x = [&](const uint32_t* xo_next) -> int {
-    if (!px_on) return 0;
-    int n = 0;
-    if (px_s < S1 && px_act) {
-      dma16_group<2>(px_ptr, xoff, px_dst);
-      n = 2;
-    }
-    px_ptr += 32;
-    px_dst = px_dst + X_SLOT == px_dst0 + NSX * X_SLOT ? px_dst0 : px_dst + X_SLOT;
-    if (++px_s == ST && xo_next != nullptr) {
-      if (has_next) {  // on to the next tile
-        px_s = 0;
-        px_ptr = x;
-        px_act = nxt.rows > wv * 32;
-        xoff[0] = xo_next[0];
-        xoff[1] = xo_next[1];
-      } else {
-        px_on = false;
-      }
-    }
-    return n;
+  auto copy_w1 = [&](int j) {
+    const int pc = wv * WPW + j;
+    copy_to_lds16(pw_ptr + (size_t)(uint32_t)(piece_row(pc) * d), voff_w1 ^ (uint32_t)((pc & 1) * 64), pw_dst + j * 1024u);
   };
+  // (phase 1 has no registers for the offsets of phase 2: it computes them for the few copies)
+  auto copy_w = [&](int j) {
+    if (pw_phase) copy_to_lds16(pw_ptr + wv * 8 * IS, voff_w2(j), pw_dst + j * 1024u);
+    else copy_w1(j);
+  };
+  // ---- x: the rows of stage pair m + 1 are copied during the first stage of pair m, once its
+  // fragments of x are in registers; the next tile's first rows during phase 2
+  const uint32_t x_dst = lds0 + C::OFF_X + (uint32_t)wv * X_WAVE;
+  auto copy_x = [&](const uint16_t* src, int j) { copy_to_lds16(src, xoff[j], x_dst + j * 1024u); };
+
   // Stage numbering: q counts the stages this workgroup walks.  Per iteration q a wave
-  //   (a) multiplies stage q (W(q) was published by the barrier of iteration q - 1, x(q) is its own),
-  //   (b) passes barrier(q): every wave has finished reading W(q-1), and W(q+1) is published,
-  //   (c) issues its copies of x(q+2) and W(q+3) (into the slots of x(q-1), W(q-1)),
-  //   (d) waits until everything it issued before (c) has landed, except the output stores of
-  //       the previous iteration: that is x(q+1) and its part of W(q+2) (issued in iteration
-  //       q - 1).  From here on the x fragments of stage q + 1 may be read.
-  // (b) and (c) sit between MFMAs of (a) so that their scalar work hides behind them; (d) closes
-  // the iteration.
-  produce_w();  // W(0)
-  produce_w();  // W(1)
-  produce_x(nullptr);  // x(0)
-  {
-    int c0 = produce_x(nullptr);  // x(1)  } what iteration -1 would have issued
-    c0 += produce_w();            // W(2)  }
-    wait_pending(c0);             // W(0), W(1), x(0) have landed
+  //   (a) multiplies stage q (W(q) was published by the barrier of iteration q - 1, x is its own),
+  //   (b) waits for its part of W(q+1) and passes barrier(q): every wave has finished reading
+  //       W(q-1), and W(q+1) is published,
+  //   (c) issues its copies of W(q+3) (into the slot of W(q-1)), then those of x, then the stores,
+  //   (d) at the end of a stage pair of phase 1 waits for the next pair's x.
+  // They are dealt out behind single MFMAs of (a) (Cfg).
+  // Vector memory operations retire in issue order, so a wait is for "at most n pending" with n the
+  // number of operations issued behind the ones waited for.  With w = WPW copies of weights per
+  // stage and s stores per stage of phase 2 (from its second on):
+  //   (d) x was issued in the pair's first stage, behind its W: behind it one stage's W
+  //   (b) second stage of a pair: W(q+1) was issued in iteration q - 2, behind it W(q+2), x
+  //       first stage of a pair: the wait (d) of iteration q - 1 was for x issued behind W(q+1)
+  //       phase 2: W(q+1) was issued in iteration q - 2, behind it s(q-2), W(q+2), s(q-1)
+  prep_w();
+#pragma unroll
+  for (int j = 0; j < WPW; ++j) copy_w(j);  // W(0)
+  x_offsets(0);
+  if (cur.rows > wv * 32) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) copy_x(x, j);
   }
-  barrier();
+  prep_w();
+#pragma unroll
+  for (int j = 0; j < WPW; ++j) copy_w(j);  // W(1)
+  prep_w();
+#pragma unroll
+  for (int j = 0; j < WPW; ++j) copy_w(j);  // W(2)
+  prep_w();
+  wait_vmem<WPW>();  // W(0), x, W(1) have landed
+  raw_barrier();
 
   // wave 0 draws the tile after `nxt` early in a tile (its wait for the returned number drains
   // that wave's copies once per tile); every wave picks the number up two barriers later
   auto sched_hook = [&](int s) {
-    if (s == 0 && has_next && threadIdx.x == 0) dyn_lds[0] = draw();
-    if (s == 2 && has_next) k_after = uni(dyn_lds[0]);
+    if (!has_next) return;
+    if (s == 0 && threadIdx.x == 0) dyn_lds[0] = draw();
+    if (s == 1) fetch_pairs(nxt, par ^ 1);
+    if (s == 2) k_after = uni(dyn_lds[0]);
   };
-  uint32_t c_w = 0, c_x = 0;  // byte offsets of the ring slots of stage q
-  int n_allow = 0;  // operations that may still be pending at (d): last iteration's output stores + (c)
-  auto step_d = [&]() {
-    wait_pending(n_allow);
-    n_allow = 0;
-  };
+  uint32_t c_w = 0;  // byte offset of the weight slot of stage q
   auto next_w = [&](uint32_t c) { return c + C::W_SLOT == NSW * C::W_SLOT ? 0u : c + C::W_SLOT; };
-  auto next_x = [&](uint32_t c) { return c + X_SLOT == NSX * X_SLOT ? 0u : c + X_SLOT; };
-  constexpr int STEPS = 2 * NBLK;          // MFMAs per wave and stage, both phases
-  constexpr int B_STEP = 1;                // (b), (c) after this step
-  // (d) after the last step: the copies get the longest possible flight (two iterations; measured
-  // 4-6 % faster than waiting earlier and reading the next stage's x fragments inside the stream);
-  // only the x fragments of stage q + 1 depend on (d), the weight fragments of stage q + 1 are
-  // already published and are read during the last PD steps
-  constexpr int WT_STEP = STEPS - 1;
-  static_assert(WT_STEP > B_STEP, "order of the in-stage hooks");
+  constexpr int STEPS = C::STEPS;          // MFMAs per wave and stage, both phases
 
   for (;;) {
     if (cur.rows <= wv * 32) {
       // a wave whose 32 rows lie beyond the tile's rows only takes part in the copies and barriers
-      uint32_t xo_next[2] = {xoff[0], xoff[1]};
+#pragma nounroll
       for (int s = 0; s < ST; ++s) {
-        barrier();
-        n_allow += produce_x(xo_next);
-        n_allow += produce_w();
+        wait_vmem<WPW>();
+        raw_barrier();
+#pragma unroll
+        for (int j = 0; j < WPW; ++j) copy_w(j);
         sched_hook(s);
-        if (s == 1 && has_next) n_allow += fetch_pairs(nxt, par ^ 1);
-        if (s == S1 && has_next) x_offsets(par ^ 1, xo_next);
-        step_d();
+        if (s == S1) x_offsets(par ^ 1);
+        if (s == ST - 4 && has_next && nxt.rows > wv * 32) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) copy_x(x, j);
+        }
+        prep_w();
         c_w = next_w(c_w);
-        c_x = next_x(c_x);
       }
+      wait_vmem<WPW>();  // x and W(1) of the next tile
     } else {
       bf16x8 hfrag[NBLK];
       {
-        // ---- phase 1: acc1[blk] += W-block(blk) x-rows^T, 32 K-elements (2 K steps) per stage.
+        // ---- phase 1: acc1[blk] += W-block(blk) x-rows^T.  A stage is 64 K-elements (4 K steps) of half
+        // of the blocks, so that a copy takes whole 128-byte lines: with 32 K-elements of all blocks
+        // the L2 serves every line twice, half a line at a time (measured on 16384 tokens, 512
+        // sub-experts of 192 x 2048: 1042 us, with whole lines, also in the stores of y, 912 us).
         // The fragment of step i + PD is read right after the MFMA of step i is issued (the
         // scheduling barriers keep that order), and the stream of reads runs on into the next
         // stage (after the last stage of the phase it reads a slot whose values are not used).
         const int l = opaque_lane(), fr = l & 31, fh = l >> 5;
-        // fragment read offsets: row wrow_gu(fr) (+ 32 per block), chunk 2 ks + fh
-        uint32_t rd_w1[2], rd_x[2];
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-          const int r = wrow_gu(fr), c = 2 * ks + fh;
-          rd_w1[ks] = (uint32_t)(r * 64 + ((c ^ f1(r)) * 16));
-          rd_x[ks] = (uint32_t)(C::OFF_X + wv * X_WAVE + fr * 64 + ((c ^ f1(fr)) * 16));
-        }
-        auto rd_w1f = [&](uint32_t slot, int step) {
-          return *reinterpret_cast<const bf16x8*>(smem + slot + rd_w1[step / NBLK] + (step % NBLK) * 2048);
+        // fragment reads: row wrow_gu(fr) (+ 32 per block), chunk 2 ks + fh; the swizzled chunks
+        // of the K steps differ in two address bits
+        const int rw = wrow_gu(fr);
+        const uint32_t rd_w1 = lds0 + (uint32_t)(rw * 128 + ((fh ^ f1(rw)) * 16));
+        const uint32_t rd_x = lds0 + (uint32_t)(C::OFF_X + wv * X_WAVE + fr * 128 + ((fh ^ f1(fr)) * 16));
+        // Reads go into fixed registers (tied operands) and are waited for by count: left to itself
+        // the compiler rotates them through twice as many and spills what the loop needs.
+        bf16x8 xa[4] = {}, wf[PD] = {};
+        auto rd_w = [&](uint32_t slot, auto step_c) {  // the weight fragment of `step` of the stage in `slot`
+          constexpr int step = decltype(step_c)::value;
+          read_frag<step % C::HB * 4096>(wf[step % PD], (slot + rd_w1) ^ (uint32_t)(step / C::HB * 32));
         };
-        auto rd_xf = [&](uint32_t slot, int ks) {
-          return *reinterpret_cast<const bf16x8*>(smem + slot + rd_x[ks]);
-        };
+        auto rd_xf = [&](int ks) { read_frag<0>(xa[ks], rd_x ^ (uint32_t)(ks * 32)); };
         f32x16 acc1[NBLK];
 #pragma unroll
         for (int b = 0; b < NBLK; ++b)
 #pragma unroll
           for (int v = 0; v < 16; ++v) acc1[b][v] = 0.0f;
-        bf16x8 xa[2], wf[PD];
-        xa[0] = rd_xf(c_x, 0);
-#pragma unroll
-        for (int i = 0; i < PD; ++i) wf[i] = rd_w1f(c_w, i);
-        xa[1] = rd_xf(c_x, 1);
-        for (int s = 0; s < S1; ++s) {
-          const uint32_t nw = next_w(c_w), nx = next_x(c_x);
+        rd_xf(0), rd_xf(1), rd_xf(2);
+        static_loop<0, PD>([&](auto I) { rd_w(c_w, I); });
+        const uint16_t* x_src = x + 64;
+        auto stage = [&](int m, auto half_c) {
+          constexpr int half = decltype(half_c)::value;
+          const uint32_t nw = next_w(c_w);
+          const int x_go = m + 1 < S1 / 2;
           __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int i = 0; i < STEPS; ++i) {
-            acc1[i % NBLK] = mma<MATH>(wf[i % PD], xa[i / NBLK], acc1[i % NBLK]);
-            wf[i % PD] = i + PD < STEPS ? rd_w1f(c_w, i + PD) : rd_w1f(nw, i + PD - STEPS);
+          static_loop<0, STEPS>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            // all but the youngest PD - 1 reads have returned: this step's weights, and x, which is
+            // read more than PD steps ahead
+            wait_frags<PD - 1>(wf[i % PD], xa[i / C::HB]);
+            acc1[half * C::HB + i % C::HB] = mma<MATH>(wf[i % PD], xa[i / C::HB], acc1[half * C::HB + i % C::HB]);
             __builtin_amdgcn_sched_barrier(0);
-            if (i == B_STEP) {
-              barrier();
-              n_allow += produce_x(nullptr);  // stays inside this tile's stages
-              n_allow += produce_w();
-              sched_hook(s);
-              if (s == 1 && has_next) n_allow += fetch_pairs(nxt, par ^ 1);
-              __builtin_amdgcn_sched_barrier(0);
+            if constexpr (i + PD < STEPS) rd_w(c_w, std::integral_constant<int, i + PD>{});
+            else rd_w(nw, std::integral_constant<int, i + PD - STEPS>{});
+            if constexpr (half == 0 && i == 0) rd_xf(3);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (i == C::BAR) {
+              if constexpr (half == 1) wait_one_of<WPW + 4, WPW>(x_go ? WPW + 4 : WPW);
+              raw_barrier();
+              if (m <= 1) sched_hook(2 * m + half);
             }
-            if (i == WT_STEP) {
-              step_d();
-              __builtin_amdgcn_sched_barrier(0);
+            if constexpr (i >= C::W0 && i < C::W_END) copy_w(i - C::W0);
+            static_loop<0, 4>([&](auto J) {
+              constexpr int j = decltype(J)::value;
+              if constexpr (half == 0 && i == C::x_copy(j)) {
+                if (x_go) copy_x(x_src, j);
+              }
+            });
+            if constexpr (half == 1 && i >= C::XW && i < C::XW + 3) {
+              if constexpr (i == C::XW) wait_vmem<WPW>();
+              rd_xf(i - C::XW);
             }
-          }
-          xa[0] = rd_xf(nx, 0);
-          xa[1] = rd_xf(nx, 1);
+            if constexpr (i == C::PREP) prep_w();
+            __builtin_amdgcn_sched_barrier(0);
+          });
           c_w = nw;
-          c_x = nx;
+        };
+#pragma nounroll
+        for (int m = 0; m < S1 / 2; ++m) {
+          stage(m, std::integral_constant<int, 0>{});
+          stage(m, std::integral_constant<int, 1>{});
+          x_src += 64;
         }
+        static_loop<0, PD>([&](auto I) { wait_frags<0>(wf[decltype(I)::value], xa[decltype(I)::value]); });  // unused, but on their way
         // ---- SwiGLU: gate/up accumulators -> the bf16 K-step fragments of phase 2, block by
         // block (16 accumulator registers become 4), before anything of phase 2 is read
         __builtin_amdgcn_sched_barrier(0);
@@ -499,78 +477,116 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         const uint32_t co = (uint32_t)(((2 * (step >> 1) + fh) ^ f2rd) * 16);
         return *reinterpret_cast<const bf16x8*>(smem + slot + rd_w2_row + (step & 1) * 32 * C::ROW2 + co);
       };
-      // Output staging: a lane ends a stage with 16 consecutive columns of ONE slot row per
-      // block, and neighbouring lanes hold different rows, 2*d bytes apart; stored like that
-      // every lane's 16 bytes are a memory access of their own (measured: 64 accesses per
-      // instruction, and the stores alone keep the address unit busy for a quarter of the
-      // kernel).  So 16 rows x 32 columns at a time go through 1 KiB of wave-private LDS and are
-      // stored with 4 adjacent lanes covering 64 contiguous bytes of a row.
-      // Staging rows are 64 bytes (4 chunks of 16); chunk c of row r sits at position
-      // c ^ ((r >> 2) & 3), which makes both the 16-lane writes (16 rows, one chunk index) and the
-      // linear reads (4 rows x 4 positions) hit all 64 banks once.
+      // Output staging: a lane ends a stage with 2 x 16 consecutive columns of ONE slot row, and
+      // neighbouring lanes hold different rows, 2*d bytes apart; stored like that every lane's 16
+      // bytes are a memory access of their own (measured: 64 accesses per instruction, and the
+      // stores alone keep the address unit busy for a quarter of the kernel).  So 16 rows x 64
+      // columns at a time go through 2 KiB of wave-private LDS and are stored with 8 adjacent lanes
+      // covering a 128-byte line of a row.
+      // A stage ends by packing its 64 columns to bf16 (16 registers); they are stored during the
+      // next stage.
       unsigned char* epi = smem + C::OFF_EPI + wv * EPI_WAVE;
-      const int er = fr & 15, es = (er >> 2) & 3;
-      const uint32_t epi_wr0 = (uint32_t)(er * 64 + ((2 * fh) ^ es) * 16);
-      const uint32_t epi_wr1 = (uint32_t)(er * 64 + ((2 * fh + 1) ^ es) * 16);
-      const uint32_t epi_rd = (uint32_t)l * 16u;  // row l >> 2 of the 16, position l & 3
-      const int srow = wv * 32 + (l >> 2);        // + 16 for the second half of the wave's rows
-      const int echunk = (l & 3) ^ ((l >> 4) & 3);  // the chunk that sits at this lane's position
-      const uint32_t vo = (uint32_t)srow * (uint32_t)d * 2u + (uint32_t)echunk * 16u;
-      const uint32_t vo16 = vo + 16u * (uint32_t)d * 2u;
-      uint16_t* ybase = y + (size_t)cur.row0 * d;
-      uint32_t xo_next[2] = {xoff[0], xoff[1]};
+      const int er = fr & 15;
+      const uint32_t epi_wr = (uint32_t)(er * 128 + ((2 * fh) ^ f1(er)) * 16);  // chunk 2 fh; 1, 4, 5 further: xor
+      const uint32_t epi_rd = (uint32_t)l * 16u;  // row l >> 3 of the 8, position l & 7
+      const int srow = wv * 32 + (l >> 3);        // + 8 per quarter
+      const int echunk = (l & 7) ^ (l >> 4);      // the chunk that sits there (odd quarters: ^ 4)
+      uint32_t vo[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) vo[k] = row_bytes(srow + 8 * k) + (uint32_t)(echunk ^ (k & 1) * 4) * 16u;
+      uint16_t* ybase = y + (size_t)cur.row0 * d - 64;  // columns of the stage before
+      // (set here: as an undefined value `out` would hold its registers through phase 1 as well)
+      uint4 out[4] = {}, oq[2] = {};  // packed columns 0..7, 8..15 of either block; two quarters read back
+      auto out_write = [&](auto H) {  // lane (row fr, half fh): columns 32 b + 16 fh + 0..15 of slot row 32 wv + fr
+        if ((fr >> 4) == decltype(H)::value) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            *reinterpret_cast<uint4*>(epi + (epi_wr ^ (uint32_t)((c >> 1) * 64 + (c & 1) * 16))) = out[c];
+        }
+      };
+      auto out_read = [&](auto Q) {
+        constexpr int k = decltype(Q)::value;
+        oq[k & 1] = *reinterpret_cast<const uint4*>(epi + epi_rd + (k & 1) * 1024);
+      };
+      auto out_store = [&](auto Q) {
+        constexpr int k = decltype(Q)::value;
+        const uint4 v = oq[k & 1];
+        if (srow + 8 * k < cur.rows) store16(ybase, vo[k], u32x4{v.x, v.y, v.z, v.w});
+      };
+      // stores issued per stage: the quarters that have a row of the tile
+      const int n_st = min((cur.rows - wv * 32 + 7) / 8, 4);
+      uint32_t vo_w2[WPW];
+#pragma unroll
+      for (int j = 0; j < WPW; ++j) vo_w2[j] = voff_w2(j);
+      x_offsets(par ^ 1);  // of the next tile, if there is one
       bf16x8 wd[PD];
 #pragma unroll
       for (int i = 0; i < PD; ++i) wd[i] = rd_w2f(c_w, i);
+#pragma nounroll
       for (int s2 = 0; s2 < S2; ++s2) {
         const uint32_t nw = next_w(c_w);
+        const int x_go = s2 == S2 - 4 && has_next && nxt.rows > wv * 32;
         f32x16 acc2[2];
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
           for (int v = 0; v < 16; ++v) acc2[b][v] = 0.0f;
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < STEPS; ++i) {
+        static_loop<0, STEPS>([&](auto I) {
+          constexpr int i = decltype(I)::value;
           acc2[i & 1] = mma<MATH>(wd[i % PD], hfrag[i >> 1], acc2[i & 1]);
           wd[i % PD] = i + PD < STEPS ? rd_w2f(c_w, i + PD) : rd_w2f(nw, i + PD - STEPS);
           __builtin_amdgcn_sched_barrier(0);
-          if (i == B_STEP) {
-            barrier();
-            n_allow += produce_x(xo_next);
-            n_allow += produce_w();
-            if (s2 == 0 && has_next) x_offsets(par ^ 1, xo_next);
-            __builtin_amdgcn_sched_barrier(0);
+          if constexpr (i == C::BAR) {
+            wait_one_of<WPW + 8, WPW + 4, WPW + 2, WPW>(s2 >= 3 ? WPW + 2 * n_st : s2 == 2 ? WPW + n_st : WPW);
+            raw_barrier();
           }
-          if (i == WT_STEP) {
-            step_d();
-            __builtin_amdgcn_sched_barrier(0);
+          if constexpr (i >= C::W0 && i < C::W_END) {
+            constexpr int j = i - C::W0;
+            if (pw_phase) copy_to_lds16(pw_ptr + wv * 8 * IS, vo_w2[j], pw_dst + j * 1024u);
+            else copy_w1(j);
           }
-        }
-        // lane (row fr, half fh) holds columns 64 s2 + 32 b + 16 fh + 0..15 of slot row 32 wv + fr
-        static_for<0, 4>([&](auto Q) {
-          constexpr int b = decltype(Q)::value >> 1, hf = decltype(Q)::value & 1;
-          const f32x16 a = acc2[b];
-          if ((fr >> 4) == hf) {
-            *reinterpret_cast<uint4*>(epi + epi_wr0) = make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]),
-                                                                 pack_bf16x2(a[4], a[5]), pack_bf16x2(a[6], a[7]));
-            *reinterpret_cast<uint4*>(epi + epi_wr1) = make_uint4(pack_bf16x2(a[8], a[9]), pack_bf16x2(a[10], a[11]),
-                                                                 pack_bf16x2(a[12], a[13]), pack_bf16x2(a[14], a[15]));
-          }
-          const uint4 q = *reinterpret_cast<const uint4*>(epi + epi_rd);
-          if (srow + 16 * hf < cur.rows) store16<b * 64>(ybase, hf ? vo16 : vo, u32x4{q.x, q.y, q.z, q.w});
+          static_loop<0, 4>([&](auto Q) {
+            constexpr int k = decltype(Q)::value;
+            if constexpr (i == C::x_copy(k)) {
+              if (x_go) copy_x(x, k);
+            }
+            if constexpr (k < 2 && i == C::out_write(k)) out_write(Q);  // s2 = 0: nothing meaningful, not stored
+            if constexpr (i == C::out_read(k)) out_read(Q);
+            if constexpr (i == C::out_store(k)) {
+              if (s2 > 0) out_store(Q);
+            }
+          });
+          if constexpr (i == C::PREP) prep_w();
+          __builtin_amdgcn_sched_barrier(0);
         });
-        // Stores that were certainly issued (a lower bound keeps the wait at (d) safe): row 32 wv
-        // of this wave is valid, rows 32 wv + 16.. only if the tile has that many.  They may
-        // stay pending through the next iteration's (d).
-        n_allow = cur.rows > wv * 32 + 16 ? 4 : 2;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const f32x16 a = acc2[b];
+          out[2 * b] = make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]),
+                                  pack_bf16x2(a[6], a[7]));
+          out[2 * b + 1] = make_uint4(pack_bf16x2(a[8], a[9]), pack_bf16x2(a[10], a[11]), pack_bf16x2(a[12], a[13]),
+                                      pack_bf16x2(a[14], a[15]));
+        }
         ybase += 64;
         c_w = nw;
-        c_x = next_x(c_x);  // the x ring turns with every stage
       }
+      // W(1) of the next tile (and x, issued before it): behind it s, W, s
+      wait_one_of<WPW + 8, WPW + 4, WPW + 2, WPW>(WPW + 2 * n_st);
+      static_loop<0, 2>([&](auto H) {  // the last stage's columns
+        constexpr int k = 2 * decltype(H)::value;
+        out_write(H);
+        out_read(std::integral_constant<int, k>{});
+        out_read(std::integral_constant<int, k + 1>{});
+        out_store(std::integral_constant<int, k>{});
+        out_store(std::integral_constant<int, k + 1>{});
+      });
     }
     // ---- next tile
-    if (!has_next) break;
+    if (!has_next) {
+      wait_vmem<0>();  // no copy may land in LDS that is no longer this workgroup's
+      break;
+    }
     cur = nxt;
     par ^= 1;
     has_next = k_after < n_tiles;
@@ -583,15 +599,8 @@ template <int IS, bool MATH>
 static hipError_t launch_is(const uint16_t* x, const uint16_t* w_gu, const uint16_t* w_dn,
                             const int32_t* sorted_pair, const MTile* tiles, int32_t* hdr,
                             uint16_t* y, int T, int d, int k_max, int max_mtiles, hipStream_t s) {
-  static bool done[64] = {};  // per instantiation (IS, MATH)
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
-  if (dev < 0 || !done[dev]) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_fused_kernel<IS, MATH>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, Cfg<IS>::LDS_BYTES);
-    if (e != hipSuccess) return e;
-    if (dev >= 0) done[dev] = true;
-  }
+  hipError_t e = raise_lds_limit<ffn_fused_kernel<IS, MATH>>(Cfg<IS>::LDS_BYTES);
+  if (e != hipSuccess) return e;
   const int grid = persistent_grid(max_mtiles, 1);
   ffn_fused_kernel<IS, MATH><<<grid, NT, Cfg<IS>::LDS_BYTES, s>>>(x, w_gu, w_dn, sorted_pair, tiles, hdr, y,
                                                             T, d, k_max);
