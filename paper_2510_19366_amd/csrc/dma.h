@@ -42,6 +42,23 @@ __device__ __forceinline__ void wait_vmem() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// A 16-byte LDS read into the register it is given (tied), not tracked by the compiler, and the
+// wait for all but the youngest N of this wave's LDS reads, behind which the given values may be used.
+// (Kernels at the register limit: the compiler rotates reads through twice the registers.)
+template <int OFF, class V>
+__device__ __forceinline__ void read_lds16(V& v, uint32_t addr) {
+  static_assert(sizeof(V) == 16);
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "+v"(v) : "v"(addr), "n"(OFF));
+}
+template <int N, class V>
+__device__ __forceinline__ void wait_lds(V& a, V& b) {
+  asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N));
+}
+template <int N, class V>
+__device__ __forceinline__ void wait_lds(V& a, V& b, V& c, V& d) {
+  asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "n"(N));
+}
+
 // s_barrier without the wait for outstanding copies that __syncthreads() would add; LDS accesses
 // stay on their side of it
 __device__ __forceinline__ void raw_barrier() {

@@ -4,14 +4,13 @@
 // over ragged groups, as persistent workgroups that walk (m-tile, n-tile) items.
 //
 // Tile: 256 slot rows x 256 weight rows, 8 wavefronts (4 along the slot rows x 2 along the weight
-// rows), one workgroup per CU, v_mfma_f32_32x32x16_bf16.  The weight block is the MFMA's first
-// operand and its rows are fed in a permuted order, so that a lane ends up with 8 or 16
-// consecutive output columns of one slot row and stores them as 16-byte words.
-// Drivers:
+// rows), one workgroup per CU, v_mfma_f32_32x32x16_bf16.  Drivers:
 //   run_items_ring (K >= 256): operands go global -> LDS directly through a ring of two stages of
 //     64 K-elements that is refilled piece by piece;
 //   run_items (shorter K): 64-wide slabs through registers into a double-buffered, XOR-swizzled
-//     LDS tile, one slab ahead of the MFMAs.
+//     LDS tile, one slab ahead of the MFMAs.  The weight block is the MFMA's first operand and its
+//     rows are fed in a permuted order, so that a lane ends up with 8 or 16 consecutive output
+//     columns of one slot row and stores them as 16-byte words (ffn_few_kernel likewise).
 // So few pairs that these tiles would leave CUs idle take ffn_few_kernel (tiles of 64 weight rows).
 // Narrow sub-experts (Is in {64, 128, 192}) take the fused kernel in ffn_fused_bf16.hip
 // instead; these two kernels serve every other shape.
@@ -113,10 +112,26 @@ struct GateUpOp {
   static bool offsets_fit(long T, long d, long Is) {  // 32-bit byte offsets (ring driver)
     return T * d * 2 < (1L << 32) && 2 * Is * d * 2 < (1L << 32);
   }
-  // (stores certainly issued by a wave: one per slot block and weight block inside the n-range)
-  __device__ __forceinline__ int stores_issued(const Sc& sc, int wm, int wn) const {
-    const bool all = sc.n0 + (weight_block(wn, NB - 1) + 1) * 16 <= Is;
-    return all ? blocks_on(sc, wm) * NB : 0;
+  // ---- ring driver (weight rows as second operand: lane n of a block holds ITS row's products with 16
+  // slot rows).  The two blocks of a phase are the gate and the up rows of the same 32 neurons.
+  static constexpr int CHUNK = 32;  // output columns of a wave and phase
+  static constexpr int PUTS = 8;    // stores per phase and slot block
+  __device__ __forceinline__ int ring_row(const Sc& it, int br) const {
+    const int neuron = min(it.n0 + (br >> 7) * 64 + ((br >> 6) & 1) * 32 + (br & 31), Is - 1);
+    return (br & 32) ? Is + neuron : neuron;
+  }
+  __device__ __forceinline__ uint16_t* out() const { return h; }
+  // offset of what a lane stores: even lanes row v, odd lanes row v + 1 of two neighbouring neurons
+  __device__ __forceinline__ uint32_t put_off(int lane) const {
+    return ((uint32_t)(4 * (lane >> 5) + (lane & 1)) * (uint32_t)Is + (uint32_t)(lane & 30)) * 2u;
+  }
+  // slot rows v, v + 1 (v even) of a slot block: one store of 4 rows x 64 bytes
+  template <class Store>
+  __device__ __forceinline__ void put(const f32x16& a0, const f32x16& a1, int v, Store&& store) const {
+    const uint32_t mine = pack2(silu_mul(a0[v], a1[v]), silu_mul(a0[v + 1], a1[v + 1]));
+    const uint32_t other = __builtin_amdgcn_mov_dpp(mine, 0xB1, 0xF, 0xF, true);  // of the lane's neighbour
+    // even lanes: low halves (row v), odd lanes: high halves (row v + 1)
+    store(v, __builtin_amdgcn_perm(other, mine, (threadIdx.x & 1) ? 0x03020706u : 0x05040100u));
   }
   // one lane's share of a 32-row weight block: 8 neurons of one slot row
   __device__ __forceinline__ void store_block(const Sc& it, int row, int block, int hi, const f32x16& v) const {
@@ -126,7 +141,7 @@ struct GateUpOp {
           pack2(silu_mul(v[0], v[8]), silu_mul(v[1], v[9])), pack2(silu_mul(v[2], v[10]), silu_mul(v[3], v[11])),
           pack2(silu_mul(v[4], v[12]), silu_mul(v[5], v[13])), pack2(silu_mul(v[6], v[14]), silu_mul(v[7], v[15])));
   }
-  __device__ __forceinline__ void epilogue(const Sc& it, f32x16 (&acc)[NB][MB], uint16_t*) const {
+  __device__ __forceinline__ void epilogue(const Sc& it, f32x16 (&acc)[NB][MB], uint16_t*) const {  // short K
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int wm = wv >> 1, wn = wv & 1;
 #pragma unroll
@@ -167,12 +182,22 @@ struct DownOp {
   __device__ __forceinline__ int a_row(const Sc& sc, int r, int) const { return min(r, sc.rows - 1); }
   __device__ __forceinline__ int b_row(const Sc& it, int br) const { return min(it.n0 + br, d - 1); }
   static bool offsets_fit(long, long d, long Is) { return d * Is * 2 < (1L << 32); }
-  // the coalescing epilogue stores 8 rows per instruction: only full 32-row blocks count
-  __device__ __forceinline__ int stores_issued(const Sc& sc, int wm, int wn) const {
-    const bool all = sc.n0 + (weight_block(wn, NB - 1) + 1) * 32 <= d;
-    if (!all) return 0;
-    const int full = sc.rows >> 5;
-    return ((full > slot_block(wm, 0) ? 1 : 0) + (full > slot_block(wm, 1) ? 1 : 0)) * 8;
+  // ---- ring driver: the two blocks of a phase are the even and the odd ones of 64 columns, so that
+  // a lane holds two neighbouring columns
+  static constexpr int CHUNK = 64;
+  static constexpr int PUTS = 16;
+  __device__ __forceinline__ int ring_row(const Sc& it, int br) const {
+    return min(it.n0 + (br & ~63) + (br & 31) * 2 + ((br >> 5) & 1), d - 1);
+  }
+  __device__ __forceinline__ uint16_t* out() const { return y; }
+  __device__ __forceinline__ uint32_t put_off(int lane) const {
+    return ((uint32_t)(4 * (lane >> 5)) * (uint32_t)d + (uint32_t)(lane & 31) * 2u) * 2u;
+  }
+  // slot rows v, v + 1: two stores of 2 rows x 128 bytes
+  template <class Store>
+  __device__ __forceinline__ void put(const f32x16& a0, const f32x16& a1, int v, Store&& store) const {
+    store(v, pack2(a0[v], a1[v]));
+    store(v + 1, pack2(a0[v + 1], a1[v + 1]));
   }
   // one lane's share of a 32-row weight block: 16 columns of one slot row
   __device__ __forceinline__ void store_block(const Sc& it, int row, int block, int hi, const f32x16& v) const {
@@ -182,7 +207,7 @@ struct DownOp {
     o[0] = make_uint4(pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4], v[5]), pack2(v[6], v[7]));
     o[1] = make_uint4(pack2(v[8], v[9]), pack2(v[10], v[11]), pack2(v[12], v[13]), pack2(v[14], v[15]));
   }
-  // 16 rows x 64 columns at a time go through wave-private LDS and are read back row-major, so
+  // (short K)  16 rows x 64 columns at a time go through wave-private LDS and are read back row-major, so
   // that every store instruction writes 8 rows x 128 contiguous bytes (whole cache lines) instead
   // of 64 scattered 16-byte pieces: y is the layer's largest HBM stream.  LDS rows are 128 bytes,
   // 16-byte chunk c of row r sits at position c ^ ((r >> 1) & 7): conflict-free both ways.
@@ -337,12 +362,12 @@ __device__ __forceinline__ void run_items(const Op& op, const MTile* __restrict_
 // K % 64 == 32: the last stage has two K steps; its copies fetch the row's valid half twice.
 constexpr int SLOT_BYTES = (BM + BN) * BK * 2;   // A rows, then B rows
 constexpr int B_OFF = BM * BK * 2;
+constexpr int FIRST = 0, MIDDLE = 1, LAST = 2;  // stages of an item
 constexpr int DYN_DIV = 8;  // 1/DYN_DIV of the work items go to the shared pool
 template <bool GATHER>
 struct Ring {
   static constexpr int OFF_PAIR = 2 * SLOT_BYTES;
-  static constexpr int OFF_EPI = OFF_PAIR + (GATHER ? 2 * BM * 4 : 0);
-  static constexpr int OFF_DYN = OFF_EPI + (GATHER ? 0 : (NT_ / 64) * EPI_WAVE_BYTES);
+  static constexpr int OFF_DYN = OFF_PAIR + (GATHER ? 2 * BM * 4 : 0);
   static constexpr int LDS_BYTES = OFF_DYN + 16;
   static_assert(LDS_BYTES <= 160 * 1024, "LDS per CU");
 };
@@ -365,9 +390,7 @@ __device__ __forceinline__ void run_items_ring(const Op& op, const MTile* __rest
   int32_t* pair_lds = reinterpret_cast<int32_t*>(sm8 + RG::OFF_PAIR);  // [2][BM]
   int32_t* dyn_next = reinterpret_cast<int32_t*>(sm8 + RG::OFF_DYN);
   const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
-  uint16_t* epi_lds = Op::GATHER ? nullptr : reinterpret_cast<uint16_t*>(sm8 + RG::OFF_EPI + wv * EPI_WAVE_BYTES);
   const int wm = wv >> 1, wn = wv & 1;
-  const int wrow = Op::wrow(lane & 31);
   // Work split: about 1 - 1/DYN_DIV of the item list is dealt out statically (XCD-aware, see
   // xcd_items), the rest is a pool that workgroups draw from in batches once their own share is
   // done, which evens out the finishing times (m-tiles differ in their row counts).  The static
@@ -406,10 +429,8 @@ __device__ __forceinline__ void run_items_ring(const Op& op, const MTile* __rest
     sc.rows = uni(t.rows);
     sc.n0 = uni(c * C + r % Cc) * (BN / Op::N_PER_ROW);
   };
-  auto fetch_pairs = [&](const Sc& sc, int parity) -> int {  // returns the operations issued
-    if (!Op::GATHER || wv >= 4) return 0;
-    dma4(op.idx_src(sc, wv * 64 + lane), pair_base + (uint32_t)(parity * BM + wv * 64) * 4);
-    return 1;
+  auto fetch_pairs = [&](const Sc& sc, int parity) {
+    if (Op::GATHER && wv < 4) dma4(op.idx_src(sc, wv * 64 + lane), pair_base + (uint32_t)(parity * BM + wv * 64) * 4);
   };
   // Producers of the two pieces: uniform bases that advance 64 elements per stage, byte offsets of
   // this lane's rows.  A copy covers 8 rows; chunk position pos holds chunk pos ^ f(row).
@@ -432,7 +453,7 @@ __device__ __forceinline__ void run_items_ring(const Op& op, const MTile* __rest
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int r = (wv * 2 + j) * 8 + sub;
-      vb0[j] = row_bytes(op.b_row(sc, r)) + (uint32_t)(pos ^ swz_f<Op::WSWZ>(r)) * 16u;
+      vb0[j] = row_bytes(op.ring_row(sc, r)) + (uint32_t)(pos ^ swz_f<SWZ_SEQ>(r)) * 16u;
     }
   };
   auto rows_y = [&](const Sc& sc) {
@@ -442,7 +463,7 @@ __device__ __forceinline__ void run_items_ring(const Op& op, const MTile* __rest
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int r = 128 + (wv * 2 + j) * 8 + sub;
-      vb1[j] = row_bytes(op.b_row(sc, r)) + (uint32_t)(pos ^ swz_f<Op::WSWZ>(r)) * 16u;
+      vb1[j] = row_bytes(op.ring_row(sc, r)) + (uint32_t)(pos ^ swz_f<SWZ_SEQ>(r)) * 16u;
     }
   };
   // K % 64 == 32, last stage: chunks 4..7 of a row do not exist, their lanes fetch chunks 0..3 (not used)
@@ -471,7 +492,7 @@ __device__ __forceinline__ void run_items_ring(const Op& op, const MTile* __rest
 #pragma unroll
       for (int j = 0; j < 4; ++j) xa[j] = va[j] - (cut ? tail_off(swz_f<SWZ_SEQ>(j * 8)) : 0u);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) xb[j] = vb0[j] - (cut ? tail_off(swz_f<Op::WSWZ>((wv * 2 + j) * 8)) : 0u);
+      for (int j = 0; j < 2; ++j) xb[j] = vb0[j] - (cut ? tail_off(swz_f<SWZ_SEQ>((wv * 2 + j) * 8)) : 0u);
     }
   };
   auto copy_x = [&](int j) {  // copies 0..5
@@ -495,7 +516,7 @@ __device__ __forceinline__ void run_items_ring(const Op& op, const MTile* __rest
     if (HALF) {
       const bool cut = py.stage == nst;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) yb[j] = vb1[j] - (cut ? tail_off(swz_f<Op::WSWZ>((wv * 2 + j) * 8)) : 0u);
+      for (int j = 0; j < 2; ++j) yb[j] = vb1[j] - (cut ? tail_off(swz_f<SWZ_SEQ>((wv * 2 + j) * 8)) : 0u);
     }
   };
   auto copy_y = [&](int j) { copy_to_lds16(pb1, HALF ? yb[j] : vb1[j], y_lds + j * 1024u); };
@@ -511,19 +532,16 @@ __device__ __forceinline__ void run_items_ring(const Op& op, const MTile* __rest
   };
 
   // fragment addresses: slot-row block mb at + 4 * 32 rows, weight block nb at + (nb & 1) * 32 and
-  // (nb >> 1) * 128 rows; K step ks toggles bits of the chunk position
+  // (nb >> 1) * 128 rows; K step ks toggles two bits of the address
   const int fr = lane & 31, fh = lane >> 5;
-  uint32_t ra[4], rb[4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    ra[ks] = (uint32_t)((wm * 32 + fr) * 128 + (((2 * ks + fh) ^ swz_f<SWZ_SEQ>(fr)) * 16));
-    rb[ks] = (uint32_t)(B_OFF + (2 * wn * 32 + wrow) * 128 + (((2 * ks + fh) ^ swz_f<Op::WSWZ>(wrow)) * 16));
-  }
-  auto read_a = [&](const unsigned char* slot, int ks, int mb) {
-    return *reinterpret_cast<const bf16x8*>(slot + ra[ks] + mb * 128 * 128);
+  const uint32_t frag = (uint32_t)(fr * 128 + ((fh ^ swz_f<SWZ_SEQ>(fr)) * 16));
+  const uint32_t ra = smem_base + (uint32_t)(wm * 32 * 128) + frag, rb = smem_base + (uint32_t)(2 * wn * 32 * 128) + frag;
+  auto read_a = [&](bf16x8& v, uint32_t slot, auto ks, auto mb) {
+    read_lds16<decltype(mb)::value * 128 * 128>(v, (ra + slot) ^ (uint32_t)(decltype(ks)::value * 32));
   };
-  auto read_b = [&](const unsigned char* slot, int ks, int nb) {
-    return *reinterpret_cast<const bf16x8*>(slot + rb[ks] + (nb & 1) * 32 * 128 + (nb >> 1) * 128 * 128);
+  auto read_b = [&](bf16x8& v, uint32_t slot, auto ks, auto nb_c) {
+    constexpr int nb = decltype(nb_c)::value;
+    read_lds16<B_OFF + (nb & 1) * 32 * 128 + (nb >> 1) * 128 * 128>(v, (rb + slot) ^ (uint32_t)(decltype(ks)::value * 32));
   };
 
   for (;;) {
@@ -556,131 +574,190 @@ __device__ __forceinline__ void run_items_ring(const Op& op, const MTile* __rest
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[nb][mb][v] = 0.0f;
 
-    bf16x8 fa[4][MB], fb[4][2];
-    int c_stage = 0, c_item = 0;
+    bf16x8 fa[4][MB] = {}, fb[4][2] = {};
     int mb_on = blocks_on(cur, wm);
     auto p1_of = [&](const Sc& sc) { return uni(sc.n0 + BN / 2 / Op::N_PER_ROW < op.n_cols() ? 1 : 0); };
     int p1_on = p1_of(cur);  // the second half of weight rows exists
+    // ---- output.  The first half's products are complete one phase before the item's end, and the
+    // second half's registers are free until the next item's phase 1: the results of phase 0 are
+    // stored during phase 1 of the last stage, those of phase 1 during phase 0 of the next stage, a
+    // pair of slot rows behind each MFMA.  The weight rows are the MFMA's second operand, so that
+    // lanes are output columns and a store covers whole lines of a few rows as it stands.  (With the
+    // columns in registers, through LDS and as a run of code behind the last stage, the down
+    // projection of 6007 tokens, 64 x 4 sub-experts of 352, took 241 us instead of 223; what is left
+    // of its 56 us is the stores themselves, 128 KiB per CU in one stage's time.)
+    // Rows beyond the tile are dropped by the buffer's bound.
+    const uint32_t ld2 = (uint32_t)op.n_cols() * 2u;
+    const uint32_t put_off = op.put_off(lane) + (uint32_t)(slot_block(wm, 0) * 32) * ld2 + (uint32_t)wn * (Op::CHUNK * 2);
+    uint16_t* out_ptr = nullptr;
+    uint32_t out_bytes = 0;
+    int out_a = 0, out_b = 0;  // slot blocks to store of phase 0 (in the last stage), of phase 1 (behind it)
+    auto chunk_on = [&](int ph) { return cur.n0 + (2 * ph + wn) * Op::CHUNK < op.n_cols() ? mb_on : 0; };
+    auto put = [&](auto ph_c, auto slot_c, int blocks) {  // piece 0..15 of a phase's results
+      constexpr int ph = decltype(ph_c)::value, mb = decltype(slot_c)::value >> 3, v = (decltype(slot_c)::value & 7) * 2;
+      if (mb < blocks) {
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(out_ptr, 0, (int)out_bytes, 0x00020000);
+        uint32_t off = put_off;
+        asm volatile("" : "+v"(off));  // or the offsets of all pieces are kept in registers
+        op.put(acc[2 * ph][mb], acc[2 * ph + 1][mb], v, [&](int vv, uint32_t w) {
+          const uint32_t row = (uint32_t)(mb * 128 + 8 * (vv >> 2) + (vv & 3));
+          __builtin_amdgcn_raw_buffer_store_b32(w, rsrc, (int)(off + row * ld2 + ph * (4 * Op::CHUNK)), 0, 0);
+        });
+      }
+    };
     // X(q) and Y(q): this wave has its fragments of the piece in registers (lgkmcnt), its copies of
     // the piece that is read next have landed, barrier.  Issued after those copies: the 8 of a stage
-    // and, for two X and one Y behind an item's end, its epilogue's `extra` operations.
-    int extra = 0, credit = 0;
-    auto sync = [&](int n) {
+    // and `more` stores.
+    int more_x = 0, more_y = 0;
+    auto sync = [&](int more) {
       asm volatile(
-          "s_waitcnt vmcnt(24) lgkmcnt(0)\n\t"
+          "s_waitcnt vmcnt(40) lgkmcnt(0)\n\t"
+          "s_cmp_gt_u32 %0, 31\n\ts_cbranch_scc1 1f\n\t"
+          "s_waitcnt vmcnt(24)\n\t"
           "s_cmp_gt_u32 %0, 15\n\ts_cbranch_scc1 1f\n\t"
           "s_waitcnt vmcnt(16)\n\t"
           "s_cmp_gt_u32 %0, 7\n\ts_cbranch_scc1 1f\n\t"
-          "s_waitcnt vmcnt(8)\n1:" ::"s"(n)
+          "s_waitcnt vmcnt(8)\n1:" ::"s"(more)
           : "memory", "scc");
       raw_barrier();
     };
-    auto sync_x = [&]() { sync(credit > 0 ? extra : 0); };
-    auto sync_y = [&]() { sync(credit > 1 ? extra : 0); };
     // The eight steps of a stage: step t is K step t & 3 of phase t >> 2, four MFMAs.  Everything else
     // is dealt out behind single MFMAs, so that the matrix pipe never waits for a run of scalar work:
     //   fragments of step t + 2         behind MFMAs 0, 1 (steps 2, 6: behind 2, 3)
     //   X, Y                            behind MFMA 1 of steps 2, 6
     //   the copies that X, Y allow      behind MFMAs 2, 3 of steps 3, 4, 5 and of step 7
     //   preparing them                  behind MFMA 3 of steps 1 and 6
+    //   a finished item's output        behind every MFMA of one phase
     // Waves with one slot block skip MFMAs 2 and 3.
-    auto step = [&](int q, auto t_c) {
+    // Three copies of a stage (`kind`), run one behind the other for an item: what its first and last
+    // stage have besides would be 40 branches in every one (measured: 15 % of the kernel), and three
+    // alternatives in one loop spill the accumulators.
+    auto step = [&](uint32_t q, auto kind_c, auto t_c) {
+      constexpr int kind = decltype(kind_c)::value;
       constexpr int t = decltype(t_c)::value, ph = t >> 2, ks = t & 3, u = t + 2;
-      const unsigned char* slot = sm8 + (q & 1) * SLOT_BYTES;
-      const unsigned char* nslot = sm8 + ((q & 1) ^ 1) * SLOT_BYTES;
-      const bool on = (ph == 0 || p1_on != 0) && (!HALF || ks < 2 || c_stage != nst - 1);
+      const uint32_t slot = q * SLOT_BYTES, nslot = slot ^ SLOT_BYTES;
+      const bool on = (ph == 0 || p1_on != 0) && (!HALF || ks < 2 || kind != LAST);
       auto mm = [&](int mb, int n) {
-        acc[2 * ph + n][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[t & 3][n], fa[ks][mb], acc[2 * ph + n][mb], 0, 0, 0);
+        f32x16& c = acc[2 * ph + n][mb];
+        if constexpr (kind == FIRST && ks == 0)
+          c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks][mb], fb[t & 3][n], f32x16{}, 0, 0, 0);
+        else
+          c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks][mb], fb[t & 3][n], c, 0, 0, 0);
       };
-      auto rd = [&](int e) {
-        if (e < 2)
-          fb[u & 3][e] = u < 8 ? read_b(slot, u & 3, 2 * (u >> 2) + e) : read_b(nslot, u & 3, e);
-        else if (u < 4)
-          fa[u & 3][e - 2] = read_a(slot, u & 3, e - 2);
-        else if (u >= 8)
-          fa[u & 3][e - 2] = read_a(nslot, u & 3, e - 2);
+      auto piece = [&](auto e) {  // output behind MFMA e of the step
+        constexpr std::integral_constant<int, 4 * ks + decltype(e)::value> slot_c{};
+        if constexpr (kind == LAST && ph == 1) put(std::integral_constant<int, 0>{}, slot_c, out_a);
+        if constexpr (kind == FIRST && ph == 0) put(std::integral_constant<int, 1>{}, slot_c, out_b);
+      };
+      auto rd = [&](auto e_c) {
+        constexpr int e = decltype(e_c)::value;
+        constexpr std::integral_constant<int, (u & 3)> k{};
+        if constexpr (e < 2)
+          read_b(fb[u & 3][e], u < 8 ? slot : nslot, k, std::integral_constant<int, 2 * (u >> 2 & 1) + e>{});
+        else if constexpr (u < 4 || u >= 8)
+          read_a(fa[u & 3][e - 2], u < 8 ? slot : nslot, k, std::integral_constant<int, e - 2>{});
       };
       constexpr bool LATE = t == 2 || t == 6;
       __builtin_amdgcn_sched_barrier(0);
+      // all but the reads of the step before have returned
+      wait_lds<(t >= 3 && t <= 6) ? 2 : 4>(fb[t & 3][0], fb[t & 3][1], fa[ks][0], fa[ks][1]);
       if (on) mm(0, 0);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (!LATE) {
-        rd(0);
-        rd(2);
+        rd(std::integral_constant<int, 0>{});
+        rd(std::integral_constant<int, 2>{});
       }
+      piece(std::integral_constant<int, 0>{});
       __builtin_amdgcn_sched_barrier(0);
       if (on) mm(0, 1);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (!LATE) {
-        rd(1);
-        rd(3);
+        rd(std::integral_constant<int, 1>{});
+        rd(std::integral_constant<int, 3>{});
       }
-      if constexpr (t == 2) sync_x();
-      if constexpr (t == 6) sync_y();
+      if constexpr (t == 2) sync(more_x);
+      if constexpr (t == 6) sync(more_y);
+      piece(std::integral_constant<int, 1>{});
       __builtin_amdgcn_sched_barrier(0);
       if (on && mb_on == 2) mm(1, 0);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (LATE) {
-        rd(0);
-        rd(2);
+        rd(std::integral_constant<int, 0>{});
+        rd(std::integral_constant<int, 2>{});
       }
       if constexpr (t >= 3 && t <= 5) copy_x(2 * (t - 3));
       if constexpr (t == 7) copy_y(0);
+      piece(std::integral_constant<int, 2>{});
       __builtin_amdgcn_sched_barrier(0);
       if (on && mb_on == 2) mm(1, 1);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (LATE) {
-        rd(1);
-        rd(3);
+        rd(std::integral_constant<int, 1>{});
+        rd(std::integral_constant<int, 3>{});
       }
       if constexpr (t >= 3 && t <= 5) copy_x(2 * (t - 3) + 1);
       if constexpr (t == 7) copy_y(1);
       if constexpr (t == 1) prep_x();
       if constexpr (t == 6) prep_y();
+      piece(std::integral_constant<int, 3>{});
       __builtin_amdgcn_sched_barrier(0);
     };
-    auto stage = [&](int q) { static_loop<0, 8>([&](auto t_c) { step(q, t_c); }); };
-    auto first_frags = [&](const unsigned char* slot) {  // of steps 0 and 1
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          fb[u][e] = read_b(slot, u, e);
-          fa[u][e] = read_a(slot, u, e);
-        }
+    auto stage = [&](uint32_t q, auto kind_c) { static_loop<0, 8>([&](auto t_c) { step(q, kind_c, t_c); }); };
+    auto first_frags = [&](uint32_t slot) {  // of steps 0 and 1
+      static_loop<0, 2>([&](auto k) {
+        static_loop<0, 2>([&](auto e) {
+          read_b(fb[decltype(k)::value][decltype(e)::value], slot, k, e);
+          read_a(fa[decltype(k)::value][decltype(e)::value], slot, k, e);
+        });
+      });
     };
-    first_frags(sm8);
-    for (int q = 0; q < total; ++q) {
+    first_frags(0u);
+    uint32_t q = 0;  // parity of the stage's slot
+    for (int c_item = 0; c_item < n_my; ++c_item) {
       if (mb_on > 0) {
-        stage(q);
-      } else {  // no slot rows: only the copies, waits and barriers
-        sync_x();
-        all_x();
-        sync_y();
-        all_y();
-      }
-      --credit;
-      if (++c_stage == nst) {  // the item is complete
-        op.epilogue(cur, acc, epi_lds);
-        extra = uni(op.stores_issued(cur, wm, wn));
-        credit = 2;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-          for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[nb][mb][v] = 0.0f;
-        c_stage = 0;
-        ++c_item;
-        const bool idle = mb_on == 0;
-        cur = nxt;
-        mb_on = blocks_on(cur, wm);
-        p1_on = p1_of(cur);
-        if (idle && mb_on > 0) first_frags(sm8 + ((q & 1) ^ 1) * SLOT_BYTES);
-        if (c_item + 1 < n_my) {
-          load_sc(c_item + 1, nxt);
-          extra += fetch_pairs(nxt, (c_item + 1) & 1);
+        stage(q, std::integral_constant<int, FIRST>{});
+        q ^= 1;
+        more_x = more_y;  // phase-1 stores of the item before
+        more_y = 0;
+#pragma nounroll
+        for (int s = 2; s < nst; ++s) {
+          stage(q, std::integral_constant<int, MIDDLE>{});
+          q ^= 1;
+          more_x = 0;
         }
+        out_ptr = op.out() + (size_t)cur.row0 * op.n_cols() + cur.n0;
+        out_bytes = (uint32_t)cur.rows * ld2 - (uint32_t)cur.n0 * 2u;
+        out_a = chunk_on(0);
+        out_b = chunk_on(1);
+        more_y = out_a * Op::PUTS / 2;
+        stage(q, std::integral_constant<int, LAST>{});
+        q ^= 1;
+      } else {  // no slot rows: only the copies, waits and barriers
+        out_a = out_b = 0;
+#pragma nounroll
+        for (int s = 0; s < nst; ++s) {
+          sync(0);
+          all_x();
+          sync(0);
+          all_y();
+          q ^= 1;
+        }
+      }
+      // what the waits of the next stage may leave pending: the stores of phase 0 (X), of phase 1 (Y)
+      more_x = out_a * Op::PUTS;
+      more_y = out_b * Op::PUTS;
+      const bool idle = mb_on == 0;
+      cur = nxt;
+      mb_on = blocks_on(cur, wm);
+      p1_on = p1_of(cur);
+      if (mb_on == 0 || c_item + 1 == n_my) {  // no stage follows that could
+        static_loop<0, 16>([&](auto e) { put(std::integral_constant<int, 1>{}, e, out_b); });
+        out_b = 0;
+      }
+      if (idle && mb_on > 0) first_frags(q * SLOT_BYTES);
+      if (c_item + 2 < n_my) {
+        load_sc(c_item + 2, nxt);
+        fetch_pairs(nxt, c_item & 1);
       }
     }
   }

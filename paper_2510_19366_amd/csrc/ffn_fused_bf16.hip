@@ -145,17 +145,6 @@ __device__ __forceinline__ int f2(int r) {
   return IS == 128 ? ((r & 7) | (((r >> 4) & 1) << 3)) : (((r >> 1) & 3) | (((r >> 4) & 1) << 2));
 }
 
-// A fragment read into the register it is given (tied), not tracked by the compiler, and the wait
-// for all but the youngest N of this wave's LDS reads; a and b may be used behind it.
-template <int OFF>
-__device__ __forceinline__ void read_frag(bf16x8& v, uint32_t addr) {
-  asm volatile("ds_read_b128 %0, %1 offset:%2" : "+v"(v) : "v"(addr), "n"(OFF));
-}
-template <int N>
-__device__ __forceinline__ void wait_frags(bf16x8& a, bf16x8& b) {
-  asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N));
-}
-
 struct TileHdr {  // wave-uniform
   int g, row0, rows;
 };
@@ -399,9 +388,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         bf16x8 xa[4] = {}, wf[PD] = {};
         auto rd_w = [&](uint32_t slot, auto step_c) {  // the weight fragment of `step` of the stage in `slot`
           constexpr int step = decltype(step_c)::value;
-          read_frag<step % C::HB * 4096>(wf[step % PD], (slot + rd_w1) ^ (uint32_t)(step / C::HB * 32));
+          read_lds16<step % C::HB * 4096>(wf[step % PD], (slot + rd_w1) ^ (uint32_t)(step / C::HB * 32));
         };
-        auto rd_xf = [&](int ks) { read_frag<0>(xa[ks], rd_x ^ (uint32_t)(ks * 32)); };
+        auto rd_xf = [&](int ks) { read_lds16<0>(xa[ks], rd_x ^ (uint32_t)(ks * 32)); };
         f32x16 acc1[NBLK];
 #pragma unroll
         for (int b = 0; b < NBLK; ++b)
@@ -419,7 +408,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             constexpr int i = decltype(I)::value;
             // all but the youngest PD - 1 reads have returned: this step's weights, and x, which is
             // read more than PD steps ahead
-            wait_frags<PD - 1>(wf[i % PD], xa[i / C::HB]);
+            wait_lds<PD - 1>(wf[i % PD], xa[i / C::HB]);
             acc1[half * C::HB + i % C::HB] = mma<MATH>(wf[i % PD], xa[i / C::HB], acc1[half * C::HB + i % C::HB]);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (i + PD < STEPS) rd_w(c_w, std::integral_constant<int, i + PD>{});
@@ -453,7 +442,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
           stage(m, std::integral_constant<int, 1>{});
           x_src += 64;
         }
-        static_loop<0, PD>([&](auto I) { wait_frags<0>(wf[decltype(I)::value], xa[decltype(I)::value]); });  // unused, but on their way
+        static_loop<0, PD>([&](auto I) { wait_lds<0>(wf[decltype(I)::value], xa[decltype(I)::value]); });  // unused, but on their way
         // ---- SwiGLU: gate/up accumulators -> the bf16 K-step fragments of phase 2, block by
         // block (16 accumulator registers become 4), before anything of phase 2 is read
         __builtin_amdgcn_sched_barrier(0);
