@@ -26,12 +26,13 @@ __device__ __forceinline__ ItemRange xcd_items(int total) {
 
 // SiLU(a) * u = a / (1 + e^-a) * u.  v_rcp_f32 and one correction of the quotient by its remainder:
 // correctly rounded but for rare last bits, in a third of the instructions of the IEEE division the
-// compiler emits (which also scales its operands for quotients this one cannot have).  The bound on
-// the denominator keeps the remainder finite where e^-a overflows; it changes results below 2e-36.
+// compiler emits (which also scales its operands for quotients this one cannot have; a quotient
+// below 2e-36, a < -87.3, may come out as zero).  Where a or the denominator is infinite the remainder
+// is not a number and the uncorrected quotient is the result.
 __device__ __forceinline__ float silu_mul(float a, float u) {
-  const float den = fminf(1.0f + __expf(-a), 0x1p126f), r = __builtin_amdgcn_rcpf(den);
-  const float q = a * r;
-  return fmaf(fmaf(-den, q, a), r, q) * u;
+  const float den = 1.0f + __expf(-a), r = __builtin_amdgcn_rcpf(den);
+  const float q = a * r, c = fmaf(fmaf(-den, q, a), r, q);
+  return (c == c ? c : q) * u;
 }
 
 inline int persistent_grid(long max_items, int per_cu) {  // a multiple of N_XCD

@@ -1,0 +1,90 @@
+"""The grouped FFN's kernels on groups whose sizes are the edges of their tiles (slot blocks of 32
+rows, m-tiles of 256, empty groups), at widths with partial weight tiles and a half K stage, and
+SwiGLU where its gate is huge or infinite."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2510_19366_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [257, 1, 0, 31, 32, 33, 63, 64, 65, 0, 0, 127, 129, 191, 255, 256, 300, 2]
+FEW = [1, 0, 33, 0, 0, 30]
+
+
+def ffn(dtype, x, w_gu, w_dn, group):
+    """moe_prism_grouped_ffn of one pick per token, rows back in token order."""
+    T, d = x.shape
+    E, Is = w_dn.shape[0], w_dn.shape[2]
+    shape = B.make_shape(T, d, E, 1, Is, 1, dtype)
+    ws = B.alloc_workspace(shape)
+    ids = group.to(torch.int32).view(T, 1).cuda()
+    _, off, sp, sl = B.moe_prism_dispatch(shape, ids, ws)
+    y = B.moe_prism_grouped_ffn(shape, x.cuda(), w_gu.cuda(), w_dn.cuda(), off, sp, ws)
+    return y[sl.view(-1).long()].float().cpu()
+
+
+@pytest.mark.parametrize("dtype,path,sizes,d,Is", [
+    ("bf16", "auto", SIZES, 256, 256),    # two-kernel, shortest K of the ring driver
+    ("bf16", "auto", SIZES, 448, 288),    # half K stage in the down GEMM; 32 neurons in the last gate-up tile
+    ("bf16", "auto", SIZES, 576, 704),    # 64 columns in the last down tile, 64 neurons in the last gate-up tile
+    ("bf16", "auto", SIZES, 192, 320),    # gate-up K too short for the ring
+    ("bf16", "auto", SIZES, 256, 64),     # fused, each width
+    ("bf16", "auto", SIZES, 576, 128),
+    ("bf16", "auto", SIZES, 320, 192),
+    ("bf16", "split", SIZES, 512, 192),   # weight tiles with and without a second half
+    ("bf16", "auto", FEW, 64, 32),        # small tiles: one K stage; half a stage
+    ("bf16", "auto", FEW, 448, 352),
+    ("bf16", "auto", FEW, 2048, 192),
+    ("f32", "auto", SIZES, 64, 32),
+    ("f32", "auto", SIZES, 320, 96),
+    ("f32", "auto", FEW, 256, 128),
+])
+def test_group_sizes_at_the_edges_of_the_tiles(dtype, path, sizes, d, Is, monkeypatch):
+    monkeypatch.setenv("MOE_PRISM_FFN", path)
+    g = torch.Generator().manual_seed(d + Is)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    E, T = len(sizes), sum(sizes)
+    group = torch.repeat_interleave(torch.arange(E), torch.tensor(sizes))[torch.randperm(T, generator=g)]
+    x = torch.randn(T, d, generator=g).to(dt)
+    w_gu = (torch.randn(E, 2 * Is, d, generator=g) * 0.05).to(dt)
+    w_dn = (torch.randn(E, d, Is, generator=g) * 0.05).to(dt)
+    got = ffn(dtype, x, w_gu, w_dn, group)
+    ref = torch.empty(T, d, dtype=torch.float64)
+    for e in range(E):
+        rows = (group == e).nonzero().view(-1)
+        v = x[rows].double() @ w_gu[e].double().T
+        a, u = v[:, :Is], v[:, Is:]
+        ref[rows] = (a / (1 + torch.exp(-a)) * u) @ w_dn[e].double().T
+    err = (got.double() - ref).norm(dim=1) / ref.norm(dim=1)
+    # bf16: h and y are rounded once each, 2^-9 at most; fp32: chains of up to d roundings of 2^-24,
+    # twice (and expf)
+    assert err.max() <= (2 * 2.0 ** -9 if dtype == "bf16" else 2 * d * 2.0 ** -24), int(err.argmax())
+
+
+@pytest.mark.parametrize("path,T,d,Is", [("auto", 12, 256, 192),    # small tiles
+                                         ("auto", 300, 256, 192),   # fused
+                                         ("split", 300, 256, 192),  # two-kernel, ring
+                                         ("split", 300, 128, 192)])  # two-kernel, short K
+def test_swiglu_of_huge_and_infinite_gates(path, T, d, Is, monkeypatch):
+    # gate = x[0] 2^64, up = x[1] = 1, output = mean of the (equal) activations
+    monkeypatch.setenv("MOE_PRISM_FFN", path)
+    gates = torch.tensor([float("inf"), 3e38, 1e20, 100.0, 5.0, 0.0, -5.0, -80.0, -89.0, -100.0, -1e30, -3e38])
+    x = torch.zeros(T, d)
+    a = gates.repeat(-(-T // len(gates)))[:T]
+    x[:, 0] = torch.where(a.isinf(), torch.full_like(a, 2.0 ** 100), a * 2.0 ** -64)  # overflows to infinity
+    x[:, 1] = 1.0
+    x = x.bfloat16()
+    E = 2
+    w_gu = torch.zeros(E, 2 * Is, d)
+    w_gu[:, :Is, 0] = 2.0 ** 64
+    w_gu[:, Is:, 1] = 1.0
+    w_dn = torch.full((E, d, Is), 2.0 ** -8)
+    got = ffn("bf16", x, w_gu.bfloat16(), w_dn.bfloat16(), torch.arange(T) % E)
+    a = x[:, 0].float() * 2.0 ** 64
+    h = (a / (1 + torch.exp(-a))).bfloat16().double() * (2.0 ** -8 * Is)
+    for t in range(T):
+        # one bf16 rounding each of h and y, and the gate's exponential: 2^-20 at a = -80
+        torch.testing.assert_close(got[t].double(), h[t].expand(d), rtol=2.0 ** -7, atol=1e-35,
+                                   msg=lambda m: f"gate {a[t]}: {m}")
