@@ -147,8 +147,15 @@ __device__ __forceinline__ void chain_tile(unsigned char* smem, int ns, Copy&& c
       });
     });
   }
+  // fragments read ahead: not used, but on their way into registers
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-
+#pragma unroll
+  for (int s = 0; s < R; ++s) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i) asm volatile("" ::"v"(fa[s][i]));
+#pragma unroll
+    for (int i = 0; i < NT; ++i) asm volatile("" ::"v"(fb[s][i]));
+  }
 }
 
 }  // namespace mp

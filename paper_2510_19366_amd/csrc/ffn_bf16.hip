@@ -760,6 +760,11 @@ __device__ __forceinline__ void run_items_ring(const Op& op, const MTile* __rest
         fetch_pairs(nxt, c_item & 1);
       }
     }
+    // fragments read ahead of a stage that does not come: not used, but on their way into registers
+    static_loop<0, 4>([&](auto k) {
+      constexpr int s = decltype(k)::value;
+      wait_lds<0>(fb[s][0], fb[s][1], fa[s][0], fa[s][1]);
+    });
   }
     // ---- next batch from the pool (every copy of this run has landed, every wave is here)
     wait_vmem<0>();
