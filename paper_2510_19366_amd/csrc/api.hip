@@ -169,7 +169,6 @@ static int do_dispatch(const moe_prism_shape* s, const Layout& L, const int32_t*
   int32_t* chunk = reinterpret_cast<int32_t*>(ws + L.chunk_cnt);
   MTile* tiles = with_tiles ? reinterpret_cast<MTile*>(ws + L.tiles) : nullptr;
   return do_dispatch_over(L, ids, cnt, off, sorted_pair, slot_of_pair, chunk, hdr, tiles, s->T, E, s->k_max, st);
-  return MOE_PRISM_OK;
 }
 
 // The fused gate-up/SwiGLU/down kernel serves bf16 layers with narrow sub-experts; the
