@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void mfma_reg_kernel(const uint4* __restrict__
   if (blockIdx.x == 0 && threadIdx.x == 0) *clk = Clk{c1 - c0, r1 - r0};
 }
 
-// The rank-1 fp32 form the router-logits kernel issues (one binary32 FMA per output and
+// The rank-1 form of the fp32 matrix instructions (one binary32 FMA per output and
 // instruction): NACC independent chains of 32 x 64 outputs per wave.
 typedef __attribute__((__vector_size__(32 * sizeof(float)))) float f32x32;
 template <int NACC>
@@ -82,8 +82,8 @@ __global__ __launch_bounds__(256) void mfma_f32_rank1_kernel(const uint4* __rest
   if (blockIdx.x == 0 && threadIdx.x == 0) *clk = Clk{c1 - c0, r1 - r0};
 }
 
-// The same with a different pair of operand registers for every k step (32 pairs, as the
-// logits kernel has them after reading a slab from LDS).
+// The same with a different pair of operand registers for every k step (32 pairs, as a
+// kernel has them after reading a slab from LDS).
 __global__ __launch_bounds__(256) void mfma_f32_rank1_many_operands_kernel(const uint4* __restrict__ data,
                                                                           float* out, int iters, Clk* clk) {
   float fa[32], fb[32];
@@ -537,7 +537,7 @@ extern "C" int moe_prism_microbench(int32_t max_results, moe_prism_microbench_re
     __builtin_snprintf(nm, sizeof(nm), "mfma_32x32x16_bf16_registers_%s_2waves_per_simd", dname[var]);
     put(nm, v, "TFLOP/s", mhz);
   }
-  // 1b. the rank-1 fp32 form of the logits kernel: two chains per wave, two waves per SIMD
+  // 1b. the rank-1 fp32 form: two chains per wave, two waves per SIMD
   for (int var = 0; var < 2 && ok; ++var) {
     const int iters = 20000, grid = 2 * ncu;
     ok = timed(b, 3, [&] { mfma_f32_rank1_kernel<2><<<grid, 256>>>(b.data[var], b.out, iters, b.clk); }, &ms, &mhz);
