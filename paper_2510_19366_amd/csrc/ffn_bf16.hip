@@ -23,7 +23,6 @@ namespace mp {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_few;
 
 constexpr int BM = FFN_BM;   // slot rows per tile
 constexpr int BN = 256;      // weight rows per tile
@@ -794,11 +793,14 @@ __global__ __launch_bounds__(NT_) void ffn_short_kernel(Op op, const MTile* __re
 // ---------------------------------------------------------------- few pairs
 // A handful of tokens touches a handful of sub-experts, and tiles of 256 weight rows are then fewer
 // than the CUs: one workgroup's copies (100 KB in flight, about 80 GB/s) set the time.  Here a
-// tile is 64 weight rows x 32 slot rows, 4 waves (2 weight blocks x 2 halves of every K stage), with
-// a ring of 6 stages of 64 K-elements and two workgroups per CU; the K halves meet in LDS.
-// Bound by the latency of one chain: ring fill, K stages, reduction.  Measured, one token of the
-// 128 x 4 layer (20 sub-experts of 192, d = 2048, 47 MB of weights): gate-up and down together
-// 17 us, the fused kernel 80 us.
+// tile is 64 weight rows x 32 slot rows, with a ring of 6 stages of 64 K-elements and two workgroups
+// per CU.  Four waves copy, the first two multiply a block of 32 weight rows each: a sum over K is one
+// chain of MFMAs in ascending k, as in every other driver, so that which of them a batch takes does not
+// show in its results.
+// Bound by the latency of one chain: ring fill, K stages; a stage's fragments are read while the stage
+// before is multiplied.  Measured between HIP events, one token of the 128 x 4 layer (20 sub-experts of
+// 192, d = 2048, 47 MB of weights): gate-up and down together 28.5 us, the fused kernel 86 (with the two
+// halves of every stage on two waves and added up at the end, which is another order of the sum: 31.5).
 constexpr int FP_N = 64, FP_M = 32, FP_NS = 6, FP_THREADS = 256;
 constexpr int FP_STAGE = (FP_M + FP_N) * BK * 2, FP_LDS_BYTES = FP_NS * FP_STAGE;
 constexpr int FP_CP = (FP_M + FP_N) / 8 / (FP_THREADS / 64);  // copies per wave and stage
@@ -809,7 +811,7 @@ __global__ __launch_bounds__(FP_THREADS) void ffn_few_kernel(Op op, const MTile*
                                                              const int32_t* __restrict__ hdr, int n_tiles_n) {
   extern __shared__ __align__(16) unsigned char fp_smem[];
   const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
-  const int wb = wv & 1, kh = wv >> 1;  // weight block, half of the K steps
+  const int wb = wv;  // weight block (waves 0 and 1)
   const int fr = lane & 31, fh = lane >> 5, wrow = Op::wrow(fr);
   const int K = op.K(), ns = (K + BK - 1) / BK;
   const uint32_t lds0 = lds_offset(fp_smem), dst0 = lds0 + (uint32_t)(wv * FP_CP) * 1024u;
@@ -851,42 +853,42 @@ __global__ __launch_bounds__(FP_THREADS) void ffn_few_kernel(Op op, const MTile*
     f32x16 acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-    for (int q = 0; q < ns; ++q) {
+    bf16x8 f0[2][BK / 16], f1[2][BK / 16];
+    auto multiply = [&](const bf16x8 (&f)[2][BK / 16], int steps) {
+#pragma unroll
+      for (int ks = 0; ks < BK / 16; ++ks)
+        if (ks < steps) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[0][ks], f[1][ks], acc, 0, 0, 0);
+    };
+    auto stage = [&](int q, bf16x8 (&f)[2][BK / 16], const bf16x8 (&before)[2][BK / 16]) {
       if (q + FP_NS - 2 < ns)
         wait_vmem<(FP_NS - 2) * FP_CP>();  // stage q has landed
       else
         wait_vmem<0>();
       raw_barrier();         // for every wave; and the slot of stage q - 1 has been read
       produce(q + FP_NS - 1);
+      if (wb >= FP_N / 32) return;
       const unsigned char* s = fp_smem + q % FP_NS * FP_STAGE;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int ks = 2 * kh + i, c = 2 * ks + fh;
-        if (q * BK + ks * 16 < K) {
-          const bf16x8 ft = *reinterpret_cast<const bf16x8*>(s + fr * 128 + ((c ^ swz_f<SWZ_SEQ>(fr)) * 16));
-          const bf16x8 fw = *reinterpret_cast<const bf16x8*>(s + (FP_M + wb * 32 + wrow) * 128 + ((c ^ swz_f<Op::WSWZ>(wrow)) * 16));
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw, ft, acc, 0, 0, 0);
-        }
+      for (int ks = 0; ks < BK / 16; ++ks) {
+        const int c = 2 * ks + fh;
+        f[0][ks] = *reinterpret_cast<const bf16x8*>(s + (FP_M + wb * 32 + wrow) * 128 + ((c ^ swz_f<Op::WSWZ>(wrow)) * 16));
+        f[1][ks] = *reinterpret_cast<const bf16x8*>(s + fr * 128 + ((c ^ swz_f<SWZ_SEQ>(fr)) * 16));
       }
+      __builtin_amdgcn_sched_barrier(0);
+      if (q > 0) multiply(before, BK / 16);
+      __builtin_amdgcn_sched_barrier(0);
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this slot has been read
+    };
+    for (int q = 0; q < ns; q += 2) {
+      stage(q, f0, f1);
+      if (q + 1 < ns) stage(q + 1, f1, f0);
     }
-    // the second halves through LDS (64 bytes per lane, 16-byte pieces rotated over the banks)
-    __syncthreads();
-    f32x4_few* red = reinterpret_cast<f32x4_few*>(fp_smem) + (size_t)wb * 256 + lane;
-    if (kh == 1) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) red[v * 64] = f32x4_few{acc[4 * v], acc[4 * v + 1], acc[4 * v + 2], acc[4 * v + 3]};
+    if (wb < FP_N / 32) {
+      const int steps = (K - (ns - 1) * BK) / 16;
+      if (ns & 1) multiply(f0, steps);
+      else multiply(f1, steps);
     }
-    __syncthreads();
-    if (kh == 0) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const f32x4_few o = red[v * 64];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[4 * v + e] += o[e];
-      }
-      if (fr < sc.rows) op.store_block(sc, fr, wb, fh, acc);
-    }
+    if (wb < FP_N / 32 && fr < sc.rows) op.store_block(sc, fr, wb, fh, acc);
     __syncthreads();  // the ring is filled again
   }
 }

@@ -88,3 +88,16 @@ def test_swiglu_of_huge_and_infinite_gates(path, T, d, Is, monkeypatch):
         # one bf16 rounding each of h and y, and the gate's exponential: 2^-20 at a = -80
         torch.testing.assert_close(got[t].double(), h[t].expand(d), rtol=2.0 ** -7, atol=1e-35,
                                    msg=lambda m: f"gate {a[t]}: {m}")
+
+
+@pytest.mark.parametrize("d,Is", [(64, 32), (448, 192), (2048, 192), (320, 352), (1024, 704)])
+def test_a_rows_bits_do_not_depend_on_the_batch_it_is_in(d, Is):
+    # a handful of tokens takes the small tiles, hundreds of them the other drivers; every sum over K
+    # is one chain in ascending k in all of them
+    g = torch.Generator().manual_seed(d + Is)
+    E, T, few = 6, 400, 24
+    x = torch.randn(T, d, generator=g).bfloat16()
+    w_gu = (torch.randn(E, 2 * Is, d, generator=g) * 0.05).bfloat16()
+    w_dn = (torch.randn(E, d, Is, generator=g) * 0.05).bfloat16()
+    group = torch.randint(0, E, (T,), generator=g)
+    assert torch.equal(ffn("bf16", x[:few], w_gu, w_dn, group[:few]), ffn("bf16", x, w_gu, w_dn, group)[:few])
