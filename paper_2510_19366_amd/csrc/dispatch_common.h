@@ -147,7 +147,7 @@ struct SmallDispatch {
   MTile* tiles;  // nullptr: no m-tile table
   int max_tiles;
 };
-inline size_t small_dispatch_lds(int T, int E) { return (size_t)E * ((T + 63) / 64) * 8 + 2 * ((size_t)E + 1) * 4; }
+__host__ __device__ inline size_t small_dispatch_lds(int T, int E) { return (size_t)E * ((T + 63) / 64) * 8 + 2 * ((size_t)E + 1) * 4; }
 inline bool small_dispatch(int T, int E) { return T > 0 && T < 256 && small_dispatch_lds(T, E) <= 60 * 1024; }
 
 __device__ __forceinline__ void dispatch_one_workgroup(const int32_t* __restrict__ ids, const SmallDispatch& a,

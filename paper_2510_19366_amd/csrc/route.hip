@@ -320,13 +320,15 @@ __global__ __launch_bounds__(64 * TOPK_WAVES) void topk_kernel(
     }
   }
   if constexpr (DISPATCH) {
-    __shared__ int32_t wave_tot[4][2];
-    __shared__ int is_last;
+    // behind the dispatch's tables in the same dynamic LDS: the picks of the largest budget take all of
+    // the default 64 KiB, so there is no room for static LDS beside them
+    int32_t* is_last = reinterpret_cast<int32_t*>(topk_smem + small_dispatch_lds(T, E));
+    int32_t(*wave_tot)[2] = reinterpret_cast<int32_t(*)[2]>(is_last + 2);
     __threadfence();  // this workgroup's picks are visible on the device before it counts itself done
     __syncthreads();
-    if (threadIdx.x == 0) is_last = atomicAdd(&hdr[HDR_TOPK_DONE], 1) == (int)gridDim.x - 1;
+    if (threadIdx.x == 0) *is_last = atomicAdd(&hdr[HDR_TOPK_DONE], 1) == (int)gridDim.x - 1;
     __syncthreads();
-    if (!is_last) return;
+    if (!*is_last) return;
     __threadfence();
     dispatch_one_workgroup(ids, small, hdr, reinterpret_cast<u64*>(topk_smem), wave_tot, T, E, k_max);
   }
@@ -340,7 +342,8 @@ hipError_t launch_topk(const float* logits, const int32_t* k_tok, int32_t* ids, 
   dim3 grid(cdiv(T, TOPK_WAVES)), block(64 * TOPK_WAVES);
   size_t sh = (size_t)TOPK_WAVES * 4 * topk_pad(k_max) * sizeof(float);
   int elems = cdiv(E, 64);
-  if (small != nullptr && small_dispatch_lds(T, E) > sh) sh = small_dispatch_lds(T, E);
+  const size_t sh_small = small_dispatch_lds(T, E) + 10 * sizeof(int32_t);  // the last flag and wave_tot
+  if (small != nullptr && sh_small > sh) sh = sh_small;
 #define MP_TOPK(N)                                                                                             \
   do {                                                                                                         \
     if (small != nullptr)                                                                                      \
