@@ -55,3 +55,26 @@ def test_equal_logits_at_the_border_go_to_the_lower_ids(E, k_max, values):
     ref = O.logits(x, w, bias)
     assert np.array_equal(to_np(lg).view(np.uint32), ref.view(np.uint32))
     assert np.array_equal(to_np(ids), O.select(ref, k, k_max))
+
+
+@pytest.mark.parametrize("low", [float(np.finfo(np.float32).min), -np.inf, 1e30])
+@pytest.mark.parametrize("E,k_max", [(64, 2), (64, 8), (130, 16), (512, 32), (4000, 65)])
+def test_masked_logits(E, k_max, low):
+    # a router bias of the lowest finite value (or infinity; or huge outliers) on half of the
+    # sub-experts, and on all but a few in some calls: fewer unmasked ones than picks included
+    T, d = 70, 64
+    rng = np.random.default_rng(E)
+    x = rng.standard_normal((T, d)).astype(np.float32)
+    w = (rng.standard_normal((E, d)) * 0.2).astype(np.float32)
+    k = rng.integers(0, k_max + 1, size=T).astype(np.int32)
+    shape = B.make_shape(T, d, E, 1, 32, k_max, "f32")
+    ws = B.alloc_workspace(shape)
+    for masked in (1, E // 2, E - k_max // 2, E):
+        bias = np.zeros(E, np.float32)
+        bias[rng.permutation(E)[:masked]] = low
+        ids, _, lg = B.moe_prism_route(shape, torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(),
+                                       torch.from_numpy(bias).cuda(), torch.from_numpy(k).cuda(), ws, want_logits=True)
+        torch.cuda.synchronize()
+        ref = O.logits(x, w, bias)
+        assert np.array_equal(to_np(lg).view(np.uint32), ref.view(np.uint32))
+        assert np.array_equal(to_np(ids), O.select(ref, k, k_max)), masked
