@@ -163,6 +163,10 @@ __device__ __forceinline__ float wave_sum(float x) {
 }
 
 constexpr int TOPK_WAVES = 4;
+// Budgets up to this take a maximum per pick, larger ones the search, whose time is mostly the
+// compaction and ranking behind it.  16 384 x 512 between HIP events, picks | search: 2 picks 14.8 | 19 us,
+// 6 picks 21.1 | 22.3, 8 picks 24.1 | 22.4; 16 384 x 2048: 32 | 45, 47 | 51, 55 | 54.
+constexpr int TOPK_FEW = 6;
 __host__ __device__ inline int topk_pad(int k_max) { return (k_max + 3) / 4 * 4; }
 // a wave's own LDS writes are readable by all its lanes
 __device__ __forceinline__ void wave_lds_fence() {
@@ -234,7 +238,33 @@ __global__ __launch_bounds__(64 * TOPK_WAVES) void topk_kernel(
       key[i] = i * 64 + lane < E ? topk_key(v[i]) : GONE;
       best = max(best, key[i]);
     }
-    if (kt > 0) {
+    if (kt > 0 && kt <= TOPK_FEW) {
+      // One wave-wide maximum per pick: g = 64 i + lane, so inside a lane the lower element index is
+      // the lower id, and the winner's lane is g & 63.  Only that lane retires its element.
+      constexpr int NONE = 0x7fffffff;
+      for (int j = 0; j < kt; ++j) {
+        const int top = wave_max_i(best);
+        int mine = NONE;  // this lane's first element with that key
+        if (best == top) {
+#pragma unroll
+          for (int i = ELEMS - 1; i >= 0; --i) mine = key[i] == top ? i * 64 + lane : mine;
+        }
+        const int g = wave_min_i(mine);
+        if (lane == 0) {
+          se[j] = topk_unkey(top);
+          sid[j] = g;
+        }
+        if (g == mine) {
+          best = GONE;
+#pragma unroll
+          for (int i = 0; i < ELEMS; ++i) {
+            key[i] = i * 64 + lane == g ? GONE : key[i];
+            best = max(best, key[i]);
+          }
+        }
+      }
+      wave_lds_fence();
+    } else if (kt > 0) {
       // Lower bound of the border: the best keys of 64 lanes are 64 elements, so for k_t <= 64 the k_t-th
       // largest is at least their minimum.  Fewer picks need fewer such sets of elements: with the best
       // of 2, 4, 8 or 16 neighbouring lanes the bound is tighter (at 2 picks 2.6 steps instead of 4.5).

@@ -16,13 +16,13 @@ MP_HD float bits_float(int b) { return __builtin_bit_cast(float, b); }
 
 // Keys: key(f) = bits ^ ((bits >> 31) & 0x7fffffff) orders like f for
 // every non-NaN binary32 once -0.0 has been replaced by +0.0 (the two compare equal, and equal
-// logits go to the lower id), and INT_MIN, which is the key of no logit (-inf maps to 0x807fffff),
-// marks absent elements.  No key is INT_MAX (a NaN could be), so one behind the largest is a key too.
+// logits go to the lower id).  INT_MIN and INT_MAX are the keys of no logit (two NaNs could be): the one
+// marks absent elements, the other is behind every key.
 MP_HD int topk_key(float f) {
   int b = float_bits(f);
   b = b == INT32_MIN ? 0 : b;  // -0.0 -> +0.0
   const int k = b ^ ((b >> 31) & 0x7fffffff);
-  return k < INT32_MAX ? k : INT32_MAX - 1;
+  return k <= INT32_MIN ? INT32_MIN + 1 : k >= INT32_MAX ? INT32_MAX - 1 : k;
 }
 MP_HD float topk_unkey(int k) { return bits_float(k ^ ((k >> 31) & 0x7fffffff)); }
 

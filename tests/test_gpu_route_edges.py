@@ -78,3 +78,23 @@ def test_masked_logits(E, k_max, low):
         ref = O.logits(x, w, bias)
         assert np.array_equal(to_np(lg).view(np.uint32), ref.view(np.uint32))
         assert np.array_equal(to_np(ids), O.select(ref, k, k_max)), masked
+
+
+@pytest.mark.parametrize("E", [5, 64, 100, 512, 2100])
+def test_few_picks_of_equal_and_distinct_logits(E):
+    # budgets on both sides of the border between a maximum per pick and the search; few distinct values,
+    # so that several lanes, and several elements of a lane, hold the maximum
+    T, d, k_max = 90, 64, min(E, 9)
+    rng = np.random.default_rng(E)
+    for x, w in ((rng.standard_normal((T, d)), rng.standard_normal((E, d))),
+                 (np.ones((T, d)), rng.integers(-2, 3, (E, 1)) * np.ones((1, d)))):
+        x, w = x.astype(np.float32), w.astype(np.float32)
+        k = rng.integers(0, k_max + 1, size=T).astype(np.int32)
+        shape = B.make_shape(T, d, E, 1, 32, k_max, "f32")
+        ws = B.alloc_workspace(shape)
+        ids, _, lg = B.moe_prism_route(shape, torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), None,
+                                       torch.from_numpy(k).cuda(), ws, want_logits=True)
+        torch.cuda.synchronize()
+        ref = O.logits(x, w, None)
+        assert np.array_equal(to_np(lg).view(np.uint32), ref.view(np.uint32))
+        assert np.array_equal(to_np(ids), O.select(ref, k, k_max))
