@@ -205,7 +205,7 @@ static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, cons
       MP_LAUNCH(MOE_PRISM_K_FFN_FUSED,
                 (e[0] = launch_ffn_gate_up(s->dtype, x, w_gu, sorted_pair, tiles, hdr, h, s->T, s->d, s->inter_sub,
                                            s->k_max, few, L.max_mtiles, st),
-                 e[1] = launch_ffn_down(s->dtype, h, w_dn, tiles, hdr, y, s->d, s->inter_sub, few, L.max_mtiles, st),
+                 e[1] = launch_ffn_down(s->dtype, h, w_dn, tiles, hdr, y, s->T, s->d, s->inter_sub, few, L.max_mtiles, st),
                  e[0] != hipSuccess ? e[0] : e[1]));
       return MOE_PRISM_OK;
     }
@@ -218,7 +218,7 @@ static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, cons
   MP_LAUNCH(MOE_PRISM_K_FFN_GATE_UP,
             launch_ffn_gate_up(s->dtype, x, w_gu, sorted_pair, tiles, hdr, h, s->T, s->d, s->inter_sub,
                                s->k_max, few, L.max_mtiles, st));
-  MP_LAUNCH(MOE_PRISM_K_FFN_DOWN, launch_ffn_down(s->dtype, h, w_dn, tiles, hdr, y, s->d,
+  MP_LAUNCH(MOE_PRISM_K_FFN_DOWN, launch_ffn_down(s->dtype, h, w_dn, tiles, hdr, y, s->T, s->d,
                                                   s->inter_sub, few, L.max_mtiles, st));
   return MOE_PRISM_OK;
 }

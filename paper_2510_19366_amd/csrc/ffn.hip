@@ -120,29 +120,30 @@ __device__ __forceinline__ void f32_tile(const float* a_base, const float* b_bas
   }, acc);
 }
 
-// items: (m-tile, row block, n-tile); an item whose row block is empty is skipped
-template <class Body>
+// SHORT: see row_blocks.h
+template <bool SHORT, class Body>
 __device__ __forceinline__ void f32_items(const MTile* __restrict__ tiles, const int32_t* __restrict__ hdr,
                                           int n_tiles_n, Body&& body) {
-  const ItemRange ir = xcd_items(hdr[HDR_MTILES] * F32_BLOCKS * n_tiles_n);
-  for (int item = ir.begin; item < ir.end; item += ir.step) {
-    const MTile t = tiles[item / (F32_BLOCKS * n_tiles_n)];
-    const int blk = item / n_tiles_n % F32_BLOCKS, rows = min(F32_ROWS, t.rows - blk * F32_ROWS);
-    if (rows <= 0) continue;  // uniform over the workgroup
-    body(t.g, t.row0 + blk * F32_ROWS, rows, item % n_tiles_n);
+  auto tile = [&](int m) { return tiles[m]; };
+  auto each = [&](const MTile& t, int blk, int nt) {
+    body(t.g, t.row0 + blk * F32_ROWS, min(F32_ROWS, t.rows - blk * F32_ROWS), nt);
     __syncthreads();  // every wave has read the last stage before the ring is filled again
-  }
+  };
+  if constexpr (SHORT)
+    short_row_blocks<F32_ROWS>(blockIdx.x, gridDim.x, N_XCD, hdr[HDR_MTILES], n_tiles_n, tile, each);
+  else
+    all_row_blocks<F32_ROWS, F32_BLOCKS>(blockIdx.x, gridDim.x, N_XCD, hdr[HDR_MTILES], n_tiles_n, tile, each);
 }
 
 // Weight rows of a tile: per wave column 16 neurons' gate rows, then their up rows.
-template <bool WIDE>
+template <bool WIDE, bool SHORT>
 __global__ __launch_bounds__(256) void ffn_gate_up_f32_kernel(
     const float* __restrict__ x, const float* __restrict__ w_gu,
     const int32_t* __restrict__ sorted_pair, const MTile* __restrict__ tiles,
     const int32_t* __restrict__ hdr, float* __restrict__ h, int d, int Is, int k_max, int T) {
   extern __shared__ __align__(16) unsigned char f_smem[];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, wm = wv >> 1, wn = wv & 1;
-  f32_items(tiles, hdr, Is / 32, [&](int g, int row0, int rows, int nt) {  // Is % 32 == 0
+  f32_items<SHORT>(tiles, hdr, Is / 32, [&](int g, int row0, int rows, int nt) {  // Is % 32 == 0
     f32x4_t acc[1][2];
     f32_tile<WIDE>(x, w_gu + (size_t)g * 2 * Is * d, d, [&](int row) -> size_t {
       if (row < F32_ROWS) return min(max(sorted_pair[row0 + min(row, rows - 1)] / k_max, 0), T - 1);
@@ -159,7 +160,7 @@ __global__ __launch_bounds__(256) void ffn_gate_up_f32_kernel(
   });
 }
 
-template <bool WIDE>
+template <bool WIDE, bool SHORT>
 __global__ __launch_bounds__(256) void ffn_down_f32_kernel(const float* __restrict__ h,
                                                            const float* __restrict__ w_dn,
                                                            const MTile* __restrict__ tiles,
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(256) void ffn_down_f32_kernel(const float* __restri
                                                            float* __restrict__ y, int d, int Is) {
   extern __shared__ __align__(16) unsigned char f_smem[];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, wm = wv >> 1, wn = wv & 1;
-  f32_items(tiles, hdr, d / F32_COLS, [&](int g, int row0, int rows, int nt) {  // d % 64 == 0
+  f32_items<SHORT>(tiles, hdr, d / F32_COLS, [&](int g, int row0, int rows, int nt) {  // d % 64 == 0
     f32x4_t acc[1][2];
     f32_tile<WIDE>(h + (size_t)row0 * Is, w_dn + (size_t)g * d * Is, Is, [&](int row) -> size_t {
       return row < F32_ROWS ? min(row, rows - 1) : nt * F32_COLS + row - F32_ROWS;
@@ -183,6 +184,12 @@ __global__ __launch_bounds__(256) void ffn_down_f32_kernel(const float* __restri
 }
 
 // ---------------------------------------------------------------- launchers
+// A token picks a sub-expert at most once, so a group of a dispatched batch has at most T rows: two row blocks (a
+// caller's own tables may hold more, which then take longer).  Both GEMMs between HIP events, 16 | 64 tokens, 32
+// sub-experts of 256, 8 picks, d = 1024: 30.5 | 30.6 us, with the list of all row blocks 77 | 77; 64 tokens of the
+// tiny layer 15.5 | 27.8.
+static bool f32_short(int T) { return T <= 2 * F32_ROWS; }
+
 hipError_t launch_ffn_gate_up(int dtype, const void* x, const void* w_gu, const int32_t* sorted_pair,
                               const MTile* tiles, int32_t* hdr, void* h, int T, int d, int Is,
                               int k_max, bool few, int max_mtiles, hipStream_t s) {
@@ -191,21 +198,25 @@ hipError_t launch_ffn_gate_up(int dtype, const void* x, const void* w_gu, const 
     return launch_gate_up_bf16((const uint16_t*)x, (const uint16_t*)w_gu, sorted_pair, tiles, hdr,
                                (uint16_t*)h, T, d, Is, k_max, few, max_mtiles, s);
   const int grid = persistent_grid((long)max_mtiles * F32_BLOCKS * (Is / 32), 2);
-  auto* kern = (long)T * d >= (1L << 30) || (long)Is * d >= (1L << 29) ? ffn_gate_up_f32_kernel<true> : ffn_gate_up_f32_kernel<false>;
+  const bool wide = (long)T * d >= (1L << 30) || (long)Is * d >= (1L << 29);
+  auto* kern = f32_short(T) ? (wide ? ffn_gate_up_f32_kernel<true, true> : ffn_gate_up_f32_kernel<false, true>)
+                            : (wide ? ffn_gate_up_f32_kernel<true, false> : ffn_gate_up_f32_kernel<false, false>);
   kern<<<grid, 256, F32Tile::LDS_BYTES, s>>>((const float*)x, (const float*)w_gu, sorted_pair, tiles, hdr, (float*)h,
                                              d, Is, k_max, T);
   return hipGetLastError();
 }
 
 hipError_t launch_ffn_down(int dtype, const void* h, const void* w_dn, const MTile* tiles,
-                           int32_t* hdr, void* y, int d, int Is, bool few, int max_mtiles,
+                           int32_t* hdr, void* y, int T, int d, int Is, bool few, int max_mtiles,
                            hipStream_t s) {
   if (max_mtiles <= 0) return hipSuccess;
   if (dtype != 0)
     return launch_down_bf16((const uint16_t*)h, (const uint16_t*)w_dn, tiles, hdr, (uint16_t*)y, d,
                             Is, few, max_mtiles, s);
   const int grid = persistent_grid((long)max_mtiles * F32_BLOCKS * (d / F32_COLS), 2);
-  auto* kern = (long)Is * d >= (1L << 30) ? ffn_down_f32_kernel<true> : ffn_down_f32_kernel<false>;
+  const bool wide = (long)Is * d >= (1L << 30);
+  auto* kern = f32_short(T) ? (wide ? ffn_down_f32_kernel<true, true> : ffn_down_f32_kernel<false, true>)
+                            : (wide ? ffn_down_f32_kernel<true, false> : ffn_down_f32_kernel<false, false>);
   kern<<<grid, 256, F32Tile::LDS_BYTES, s>>>((const float*)h, (const float*)w_dn, tiles, hdr, (float*)y, d, Is);
   return hipGetLastError();
 }

@@ -798,13 +798,13 @@ __global__ __launch_bounds__(NT_) void ffn_short_kernel(Op op, const MTile* __re
 // chain of MFMAs in ascending k, as in every other driver, so that which of them a batch takes does not
 // show in its results.
 // Bound by the latency of one chain: ring fill, K stages; a stage's fragments are read while the stage
-// before is multiplied.  Measured between HIP events, one token of the 128 x 4 layer (20 sub-experts of
-// 192, d = 2048, 47 MB of weights): gate-up and down together 28.5 us, the fused kernel 86 (with the two
-// halves of every stage on two waves and added up at the end, which is another order of the sum: 31.5).
+// before is multiplied.  Measured between HIP events, one token of the 128 x 4 layer (20 to 32 sub-experts of
+// 192, d = 2048): gate-up and down together 22.6 us, the fused kernel 80 (with the list of all row blocks, see
+// row_blocks.h, 28.9; with the two halves of every stage on two waves and added up at the end, which is another order
+// of the sum, 31.5).
 constexpr int FP_N = 64, FP_M = 32, FP_NS = 6, FP_THREADS = 256;
 constexpr int FP_STAGE = (FP_M + FP_N) * BK * 2, FP_LDS_BYTES = FP_NS * FP_STAGE;
 constexpr int FP_CP = (FP_M + FP_N) / 8 / (FP_THREADS / 64);  // copies per wave and stage
-constexpr int FP_BLOCKS = FFN_BM / FP_M;                      // row blocks of an m-tile
 
 template <class Op>
 __global__ __launch_bounds__(FP_THREADS) void ffn_few_kernel(Op op, const MTile* __restrict__ tiles,
@@ -815,17 +815,13 @@ __global__ __launch_bounds__(FP_THREADS) void ffn_few_kernel(Op op, const MTile*
   const int fr = lane & 31, fh = lane >> 5, wrow = Op::wrow(fr);
   const int K = op.K(), ns = (K + BK - 1) / BK;
   const uint32_t lds0 = lds_offset(fp_smem), dst0 = lds0 + (uint32_t)(wv * FP_CP) * 1024u;
-  // items: (m-tile, row block, n-tile); an item whose row block is empty is skipped
-  const ItemRange ir = xcd_items(hdr[HDR_MTILES] * FP_BLOCKS * n_tiles_n);
-  for (int item = ir.begin; item < ir.end; item += ir.step) {
-    const MTile t = tiles[item / (FP_BLOCKS * n_tiles_n)];
-    const int blk = item / n_tiles_n % FP_BLOCKS;
+  short_row_blocks<FP_M>(blockIdx.x, gridDim.x, N_XCD, hdr[HDR_MTILES], n_tiles_n, [&](int m) { return tiles[m]; },
+                         [&](const MTile& t, int blk, int nt) {
     Sc sc;
     sc.g = uni(t.g);
     sc.row0 = uni(t.row0) + blk * FP_M;
     sc.rows = min(FP_M, uni(t.rows) - blk * FP_M);
-    sc.n0 = item % n_tiles_n * (FP_N / Op::N_PER_ROW);
-    if (sc.rows <= 0) continue;  // uniform over the workgroup
+    sc.n0 = nt * (FP_N / Op::N_PER_ROW);
     const uint16_t *ba, *bb;
     op.bases(sc, ba, bb);
     const uint16_t* base[FP_CP];
@@ -890,7 +886,7 @@ __global__ __launch_bounds__(FP_THREADS) void ffn_few_kernel(Op op, const MTile*
     }
     if (wb < FP_N / 32 && fr < sc.rows) op.store_block(sc, fr, wb, fh, acc);
     __syncthreads();  // the ring is filled again
-  }
+  });
 }
 
 // ---------------------------------------------------------------- launchers
@@ -911,7 +907,7 @@ static hipError_t launch_op(const Op& op, int K, int n_cols, bool fits, bool few
                             const MTile* tiles, int32_t* hdr, hipStream_t s) {
   if (few && fits) {
     const int ntn = cdiv(n_cols, FP_N / Op::N_PER_ROW);
-    const int grid = persistent_grid((long)max_mtiles * FP_BLOCKS * ntn, 2);
+    const int grid = persistent_grid((long)max_mtiles * ntn, 2);
     hipError_t e = raise_lds_limit<ffn_few_kernel<Op>>(FP_LDS_BYTES);
     if (e != hipSuccess) return e;
     ffn_few_kernel<Op><<<grid, FP_THREADS, FP_LDS_BYTES, s>>>(op, tiles, hdr, ntn);

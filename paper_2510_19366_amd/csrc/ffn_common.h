@@ -1,6 +1,7 @@
 // Shared by the grouped-FFN kernel files: persistent work distribution.
 #pragma once
 #include "kernels.h"
+#include "row_blocks.h"
 
 namespace mp {
 

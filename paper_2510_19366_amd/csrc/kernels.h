@@ -64,7 +64,7 @@ hipError_t launch_ffn_gate_up(int dtype, const void* x, const void* w_gu, const 
                               const MTile* tiles, int32_t* hdr, void* h, int T, int d, int Is,
                               int k_max, bool few, int max_mtiles, hipStream_t s);
 hipError_t launch_ffn_down(int dtype, const void* h, const void* w_dn, const MTile* tiles,
-                           int32_t* hdr, void* y, int d, int Is, bool few, int max_mtiles,
+                           int32_t* hdr, void* y, int T, int d, int Is, bool few, int max_mtiles,
                            hipStream_t s);
 // bf16: so few pairs that the small tiles of ffn_few_kernel are the faster ones (also than the
 // fused kernel)

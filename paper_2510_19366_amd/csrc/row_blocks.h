@@ -1,0 +1,38 @@
+// How workgroups share small tiles: plain C++, so that it can be run on the host as well.
+#pragma once
+#include "host_device.h"
+
+namespace mp {
+
+// An m-tile of `rows` slot rows is cut into row blocks of ROWS, and each of those into n_tiles_n n-tiles.
+// f(m-tile, row block, n-tile) for the share of workgroup b out of `grid` (a multiple of n_xcd; b serves XCD
+// b % n_xcd, and an XCD a contiguous part of the list, in which a sub-expert's weights meet).
+
+// For m-tiles of which hardly any has a second row block: the list holds (m-tile, n-tile) pairs, all of which exist,
+// and a workgroup walks through the row blocks of its pairs.  A list of every possible row block is
+// mostly empty there, and brings those that exist to the same few workgroups whenever the stride grid / n_xcd has a
+// factor in common with row blocks x n-tiles: one row in each of 32 groups, 4 n-tiles, 8 row blocks, 512
+// workgroups: 128 tiles on 64 of them; 20 groups, 32 n-tiles: 640 tiles on 256.
+template <int ROWS, class Tile, class F>
+MP_HD void short_row_blocks(int b, int grid, int n_xcd, int n_mtiles, int n_tiles_n, Tile&& tile, F&& f) {
+  const int xcd = b % n_xcd, total = n_mtiles * n_tiles_n, chunk = (total + n_xcd - 1) / n_xcd;
+  const int end = total < (xcd + 1) * chunk ? total : (xcd + 1) * chunk;
+  for (int item = xcd * chunk + b / n_xcd; item < end; item += grid / n_xcd) {
+    const auto t = tile(item / n_tiles_n);
+    for (int blk = 0; blk * ROWS < t.rows; ++blk) f(t, blk, item % n_tiles_n);
+  }
+}
+
+// For m-tiles of any length: the list (m-tile, row block of BLOCKS, n-tile).  What runs at the same time shares weights.
+template <int ROWS, int BLOCKS, class Tile, class F>
+MP_HD void all_row_blocks(int b, int grid, int n_xcd, int n_mtiles, int n_tiles_n, Tile&& tile, F&& f) {
+  const int xcd = b % n_xcd, total = n_mtiles * BLOCKS * n_tiles_n, chunk = (total + n_xcd - 1) / n_xcd;
+  const int end = total < (xcd + 1) * chunk ? total : (xcd + 1) * chunk;
+  for (int item = xcd * chunk + b / n_xcd; item < end; item += grid / n_xcd) {
+    const auto t = tile(item / (BLOCKS * n_tiles_n));
+    const int blk = item / n_tiles_n % BLOCKS;
+    if (blk * ROWS < t.rows) f(t, blk, item % n_tiles_n);
+  }
+}
+
+}  // namespace mp

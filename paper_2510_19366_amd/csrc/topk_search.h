@@ -3,11 +3,7 @@
 #pragma once
 #include <stdint.h>
 
-#ifdef __HIPCC__
-#define MP_HD __host__ __device__ __forceinline__
-#else
-#define MP_HD inline
-#endif
+#include "host_device.h"
 
 namespace mp {
 

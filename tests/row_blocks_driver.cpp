@@ -1,0 +1,60 @@
+// The deal of small tiles on the host: every tile that exists once, none that does not, and no workgroup
+// with much more than its share.
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+#include <vector>
+
+#include "../paper_2510_19366_amd/csrc/row_blocks.h"
+
+struct Tile {
+  int rows, m;
+};
+
+template <class Deal>
+int check(Deal&& deal, int grid, int n_tiles_n, const std::vector<Tile>& tiles, bool even) {
+  const int n = (int)tiles.size();
+  std::vector<int> seen((size_t)n * 8 * n_tiles_n, 0);
+  int exist = 0, most = 0;
+  for (const Tile& t : tiles) exist += (t.rows + 31) / 32 * n_tiles_n;
+  for (int b = 0; b < grid; ++b) {
+    int mine = 0;
+    deal(b, [&](int m) { return tiles.at(m); }, [&](const Tile& t, int blk, int nt) {
+      if (blk * 32 >= t.rows || nt < 0 || nt >= n_tiles_n) exit(2);
+      ++seen.at(((size_t)t.m * 8 + blk) * n_tiles_n + nt);
+      ++mine;
+    });
+    most = std::max(most, mine);
+  }
+  int done = 0;
+  for (int c : seen) {
+    if (c > 1) return 3;
+    done += c;
+  }
+  if (done != exist) return 4;
+  // an even share of what an XCD gets, which is an eighth
+  const int share = (exist + 7) / 8, per = grid / 8;
+  return even && most > (share + per - 1) / per ? 5 : 0;
+}
+
+int main() {
+  std::mt19937 gen(3);
+  for (int grid : {8, 64, 512})
+    for (int n_tiles_n : {1, 2, 4, 6, 11, 22, 32})
+      for (int n : {0, 1, 5, 20, 32, 250, 500})
+        for (int kind = 0; kind < 3; ++kind) {  // one row block, all full, any length
+          std::vector<Tile> tiles(n);
+          for (int m = 0; m < n; ++m) tiles[m] = {kind == 0 ? 1 + (int)(gen() % 32) : kind == 1 ? 256 : 1 + (int)(gen() % 256), m};
+          int e = check([&](int b, auto tile, auto f) { mp::short_row_blocks<32>(b, grid, 8, n, n_tiles_n, tile, f); }, grid,
+                        n_tiles_n, tiles, kind == 0);
+          if (!e)
+            e = check([&](int b, auto tile, auto f) { mp::all_row_blocks<32, 8>(b, grid, 8, n, n_tiles_n, tile, f); }, grid,
+                      n_tiles_n, tiles, kind == 1);
+          if (e) {
+            printf("grid %d n-tiles %d m-tiles %d kind %d: %d\n", grid, n_tiles_n, n, kind, e);
+            return e;
+          }
+        }
+  return 0;
+}

@@ -101,3 +101,24 @@ def test_a_rows_bits_do_not_depend_on_the_batch_it_is_in(d, Is):
     w_dn = (torch.randn(E, d, Is, generator=g) * 0.05).bfloat16()
     group = torch.randint(0, E, (T,), generator=g)
     assert torch.equal(ffn("bf16", x[:few], w_gu, w_dn, group[:few]), ffn("bf16", x, w_gu, w_dn, group)[:few])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_a_callers_own_tables_with_groups_of_more_rows_than_tokens(dtype):
+    # all pairs of a few tokens in one group of 320 rows: a full m-tile and a second one, in the kernels whose
+    # m-tiles otherwise have one or two row blocks
+    T, k_max, d, Is, E = 40, 8, 256, 96, 8
+    g = torch.Generator().manual_seed(5)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x = torch.randn(T, d, generator=g).to(dt)
+    w_gu = (torch.randn(E, 2 * Is, d, generator=g) * 0.05).to(dt)
+    w_dn = (torch.randn(E, d, Is, generator=g) * 0.05).to(dt)
+    pair = torch.randperm(T * k_max, generator=g).to(torch.int32)
+    off = torch.tensor([0, 0, 0, 320, 320, 320, 320, 320, 320], dtype=torch.int32)
+    shape = B.make_shape(T, d, E, 1, Is, k_max, dtype)
+    y = B.moe_prism_grouped_ffn(shape, x.cuda(), w_gu.cuda(), w_dn.cuda(), off.cuda(), pair.cuda(), B.alloc_workspace(shape))
+    v = x[(pair // k_max).long()].double() @ w_gu[2].double().T
+    a, u = v[:, :Is], v[:, Is:]
+    ref = (a / (1 + torch.exp(-a)) * u) @ w_dn[2].double().T
+    err = (y.cpu().double() - ref).norm(dim=1) / ref.norm(dim=1)
+    assert err.max() <= (2 * 2.0 ** -9 if dtype == "bf16" else 2 * d * 2.0 ** -24), int(err.argmax())
