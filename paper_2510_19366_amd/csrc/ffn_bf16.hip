@@ -23,6 +23,7 @@ namespace mp {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
 constexpr int BM = FFN_BM;   // slot rows per tile
 constexpr int BN = 256;      // weight rows per tile
@@ -210,20 +211,25 @@ struct DownOp {
   // that every store instruction writes 8 rows x 128 contiguous bytes (whole cache lines) instead
   // of 64 scattered 16-byte pieces: y is the layer's largest HBM stream.  LDS rows are 128 bytes,
   // 16-byte chunk c of row r sits at position c ^ ((r >> 1) & 7): conflict-free both ways.
+  // Rows beyond the tile are dropped by the buffer's bound, and blocks of 16 without a row skipped.
   __device__ __forceinline__ void epilogue(const Sc& it, f32x16 (&acc)[NB][MB], uint16_t* scratch) const {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
     const int wm = wv >> 1, wn = wv & 1;
     const int r = lane & 15, hi = lane >> 5, sw = (r >> 1) & 7;
+    const uint32_t ld2 = (uint32_t)d * 2u;
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(y + (size_t)it.row0 * d + it.n0, 0,
+                                                        (int)((uint32_t)it.rows * ld2 - (uint32_t)it.n0 * 2u), 0x00020000);
+    uint32_t at = (uint32_t)(lane >> 3) * ld2 + (uint32_t)(lane & 7) * 16u;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       const int row0 = slot_block(wm, mb) * 32;
-      if (row0 >= it.rows) continue;
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
-        const int col0 = it.n0 + weight_block(wn, 2 * half) * 32;
-        if (col0 >= d) continue;  // d % 64 == 0: a half is inside or outside as a whole
+        const int col0 = weight_block(wn, 2 * half) * 32;
+        if (it.n0 + col0 >= d) continue;  // d % 64 == 0: a half is inside or outside as a whole
 #pragma unroll
         for (int q = 0; q < 2; ++q) {  // rows 16 q .. 16 q + 15 of the block
+          if (row0 + 16 * q >= it.rows) continue;
           if (((lane >> 4) & 1) == q) {
 #pragma unroll
             for (int nbl = 0; nbl < 2; ++nbl) {
@@ -238,9 +244,10 @@ struct DownOp {
 #pragma unroll
           for (int j = 0; j < 2; ++j) {
             const int row = j * 8 + (lane >> 3), c = lane & 7;
-            const uint4 o = *reinterpret_cast<const uint4*>(scratch + row * 64 + ((c ^ ((row >> 1) & 7)) << 3));
-            if (row0 + q * 16 + row < it.rows)
-              *reinterpret_cast<uint4*>(y + (size_t)(it.row0 + row0 + q * 16 + row) * d + col0 + c * 8) = o;
+            const u32x4 o = *reinterpret_cast<const u32x4*>(scratch + row * 64 + ((c ^ ((row >> 1) & 7)) << 3));
+            asm volatile("" : "+v"(at));  // or the offsets of all pieces are kept in registers
+            __builtin_amdgcn_raw_buffer_store_b128(
+                o, rsrc, (int)(at + (uint32_t)(row0 + 16 * q + 8 * j) * ld2 + (uint32_t)col0 * 2u), 0, 0);
           }
         }
       }
@@ -249,7 +256,14 @@ struct DownOp {
 };
 
 // ---------------------------------------------------------------- short K
-// Slabs of 64 K-elements through registers into a double-buffered LDS tile.
+// Slabs of 64 K-elements through registers into a double-buffered LDS tile, one barrier per slab.
+// Items are one to three slabs here, so what bounds it is the way to an item's first slab: tile header,
+// slot list, rows.  Each of the three is fetched while earlier items are multiplied: the header three
+// items ahead, the slot list two, the first slab during the last slab of the item before.  Measured between
+// HIP events, 256 sub-experts of 32 | 96 x 2048, 4 to 16 picks, down: 8192 tokens 94 | 169 -> 84 | 131 us, 1024 tokens
+// 31 | 47 -> 24 | 38, against starting each item with its own loads (and 64-bit offsets and every block of 16 rows
+// in the epilogue).  The addresses of the loads and stores are recomputed throughout: with them in
+// registers the accumulators spill, and a reload waits for the loads in flight.
 constexpr int LD = BM * 8 / NT_;  // 16-byte loads per thread and slab, slot rows and weight rows alike
 constexpr size_t SLAB_LDS_BYTES = 2 * (size_t)(BM + BN) * BK * 2;
 constexpr size_t SHORT_LDS_BYTES = SLAB_LDS_BYTES + (NT_ / 64) * EPI_WAVE_BYTES;
@@ -265,40 +279,57 @@ __device__ __forceinline__ void run_items(const Op& op, const MTile* __restrict_
   const int K = op.K(), nslab = (K + BK - 1) / BK;
   const int total = hdr[HDR_MTILES] * n_tiles_n;
   const ItemRange ir = xcd_items(total);
-  uint4 ra[LD], rb[LD];
-  for (int item = ir.begin; item < ir.end; item += ir.step) {
+  if (ir.begin >= ir.end) return;  // the whole workgroup
+  auto load_sc = [&](int item) {  // an item past the end: the first one, in bounds and not used
+    if (item >= ir.end) item = ir.begin;
     const MTile t = tiles[item / n_tiles_n];
     Sc sc;
     sc.g = uni(t.g);
     sc.row0 = uni(t.row0);
     sc.rows = uni(t.rows);
     sc.n0 = uni(item % n_tiles_n) * (BN / Op::N_PER_ROW);
+    return sc;
+  };
+  int pair[LD] = {}, row[LD] = {};  // slot-list entries of the next item, operand rows of the one being loaded
+  auto load_pairs = [&](const Sc& sc) {
+    if constexpr (Op::GATHER)
+#pragma unroll
+      for (int i = 0; i < LD; ++i) pair[i] = *op.idx_src(sc, lr + 64 * i);
+  };
+  auto enter = [&](const Sc& sc) {
+    if constexpr (Op::GATHER)
+#pragma unroll
+      for (int i = 0; i < LD; ++i) row[i] = op.a_row(sc, lr + 64 * i, pair[i]);
+  };
+  // (everything else about the addresses is recomputed: the accumulators need the registers)
+  u32x4 ra[LD], rb[LD];
+  auto gload = [&](const Sc& sc, int k0) {
+    const int k = min(k0 + lc * 8, K - 8);  // K % 64 == 32: chunks 4..7 do not exist (not used)
     const uint16_t *ba, *bb;
     op.bases(sc, ba, bb);
-    int ao[LD], bo[LD];
 #pragma unroll
     for (int i = 0; i < LD; ++i) {
-      const int r = lr + 64 * i;
-      ao[i] = op.a_row(sc, r, Op::GATHER ? *op.idx_src(sc, r) : 0);
-      bo[i] = op.b_row(sc, r);
+      const int r = lr + 64 * i, ao = Op::GATHER ? row[i] : op.a_row(sc, r, 0);
+      ra[i] = *reinterpret_cast<const u32x4*>(ba + (size_t)ao * K + k);
+      rb[i] = *reinterpret_cast<const u32x4*>(bb + (size_t)op.b_row(sc, r) * K + k);
     }
-    auto gload = [&](int k0) {
-      const bool in = k0 + lc * 8 < K;  // K tail (K % 64 != 0) is zero-filled
-      const int k = k0 + lc * 8;
+  };
+  auto sstore = [&](int buf) {
+    uint16_t* sa = smem + buf * (BM + BN) * BK;
 #pragma unroll
-      for (int i = 0; i < LD; ++i) {
-        ra[i] = in ? *reinterpret_cast<const uint4*>(ba + (size_t)ao[i] * K + k) : make_uint4(0, 0, 0, 0);
-        rb[i] = in ? *reinterpret_cast<const uint4*>(bb + (size_t)bo[i] * K + k) : make_uint4(0, 0, 0, 0);
-      }
-    };
-    auto sstore = [&](int buf) {
-      uint16_t* sa = smem + buf * (BM + BN) * BK;
-#pragma unroll
-      for (int i = 0; i < LD; ++i) {
-        *reinterpret_cast<uint4*>(sa + swz<SWZ_SEQ>(lr + 64 * i, lc)) = ra[i];
-        *reinterpret_cast<uint4*>(sa + BM * BK + swz<Op::WSWZ>(lr + 64 * i, lc)) = rb[i];
-      }
-    };
+    for (int i = 0; i < LD; ++i) {
+      *reinterpret_cast<u32x4*>(sa + swz<SWZ_SEQ>(lr + 64 * i, lc)) = ra[i];
+      *reinterpret_cast<u32x4*>(sa + BM * BK + swz<Op::WSWZ>(lr + 64 * i, lc)) = rb[i];
+    }
+  };
+
+  Sc cur = load_sc(ir.begin), nxt = load_sc(ir.begin + ir.step), aft = load_sc(ir.begin + 2 * ir.step);
+  load_pairs(cur);
+  enter(cur);
+  gload(cur, 0);
+  load_pairs(nxt);
+  int buf = 0;
+  for (int item = ir.begin; item < ir.end; item += ir.step) {
     f32x16 acc[NB][MB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
@@ -306,16 +337,22 @@ __device__ __forceinline__ void run_items(const Op& op, const MTile* __restrict_
       for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[nb][mb][v] = 0.0f;
-    const int mb_on = blocks_on(sc, wm);
-    __syncthreads();  // the previous item's last slab has been read
-    gload(0);
-    sstore(0);
-    __syncthreads();
+    const int mb_on = blocks_on(cur, wm);
     for (int s = 0; s < nslab; ++s) {
-      if (s + 1 < nslab) gload((s + 1) * BK);
-      const uint16_t* sa = smem + (s & 1) * (BM + BN) * BK;
+      // the buffer was read two slabs ago, and every wave has passed the barrier of the slab between
+      sstore(buf);
+      __syncthreads();
+      if (s + 1 < nslab) {
+        gload(cur, (s + 1) * BK);
+      } else if (item + ir.step < ir.end) {
+        enter(nxt);
+        gload(nxt, 0);
+        load_pairs(aft);
+      }
+      const uint16_t* sa = smem + buf * (BM + BN) * BK;
 #pragma unroll
       for (int ks = 0; ks < BK / 16; ++ks) {
+        if (ks == 2 && s * BK + 32 == K) break;  // K % 64 == 32
         const int c = ks * 2 + (lane >> 5);
         bf16x8 fw[NB];
 #pragma unroll
@@ -330,10 +367,13 @@ __device__ __forceinline__ void run_items(const Op& op, const MTile* __restrict_
               acc[nb][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[nb], ft, acc[nb][mb], 0, 0, 0);
           }
       }
-      if (s + 1 < nslab) sstore((s + 1) & 1);
-      __syncthreads();
+      buf ^= 1;
     }
-    op.epilogue(sc, acc, epi_lds);
+    const Sc done = cur;
+    cur = nxt;
+    nxt = aft;
+    aft = load_sc(item + 3 * ir.step);
+    op.epilogue(done, acc, epi_lds);
   }
 }
 

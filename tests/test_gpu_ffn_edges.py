@@ -30,6 +30,10 @@ def ffn(dtype, x, w_gu, w_dn, group):
     ("bf16", "auto", SIZES, 448, 288),    # half K stage in the down GEMM; 32 neurons in the last gate-up tile
     ("bf16", "auto", SIZES, 576, 704),    # 64 columns in the last down tile, 64 neurons in the last gate-up tile
     ("bf16", "auto", SIZES, 192, 320),    # gate-up K too short for the ring
+    ("bf16", "auto", SIZES, 64, 8192),    # five short items per workgroup: gate-up, one and two slabs of K
+    ("bf16", "auto", SIZES, 128, 8192),
+    ("bf16", "auto", SIZES, 16384, 32),   # down, half a slab and one and a half
+    ("bf16", "auto", SIZES, 16384, 96),
     ("bf16", "auto", SIZES, 256, 64),     # fused, each width
     ("bf16", "auto", SIZES, 576, 128),
     ("bf16", "auto", SIZES, 320, 192),
