@@ -5,10 +5,10 @@
 //
 // Tile: 256 slot rows x 256 weight rows, 8 wavefronts (4 along the slot rows x 2 along the weight
 // rows), one workgroup per CU, v_mfma_f32_32x32x16_bf16.  Drivers:
-//   run_items_ring (K >= 256): operands go global -> LDS directly through a ring of two stages of
+//   run_items_ring (K > 192): operands go global -> LDS directly through a ring of two stages of
 //     64 K-elements that is refilled piece by piece;
-//   run_items (shorter K): 64-wide slabs through registers into a double-buffered, XOR-swizzled
-//     LDS tile, one slab ahead of the MFMAs.  The weight block is the MFMA's first operand and its
+//   run_items (shorter K, and tiles whose outputs are 4 GiB and more): 64-wide slabs through registers
+//     into a double-buffered, XOR-swizzled LDS tile, one slab ahead of the MFMAs.  The weight block is the MFMA's first operand and its
 //     rows are fed in a permuted order, so that a lane ends up with 8 or 16 consecutive output
 //     columns of one slot row and stores them as 16-byte words (ffn_few_kernel likewise).
 // So few pairs that these tiles would leave CUs idle take ffn_few_kernel (tiles of 64 weight rows).
@@ -55,6 +55,9 @@ template <int MODE>
 __device__ __forceinline__ int swz(int r, int c) {  // in elements
   return r * BK + ((c ^ swz_f<MODE>(r)) << 3);
 }
+
+// 32-bit byte offsets into a tile's output rows
+__host__ __device__ constexpr bool out_fits(int n_cols) { return (long)BM * n_cols * 2 < (1L << 32); }
 
 // Tile header fields are the same for every lane: keep them in scalar registers.
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -109,8 +112,8 @@ struct GateUpOp {
     const int neuron = min(it.n0 + blk * 16 + (rr & 15), Is - 1);
     return (rr >> 4) ? Is + neuron : neuron;
   }
-  static bool offsets_fit(long T, long d, long Is) {  // 32-bit byte offsets (ring driver)
-    return T * d * 2 < (1L << 32) && 2 * Is * d * 2 < (1L << 32);
+  bool offsets_fit() const {  // 32-bit byte offsets into the operands
+    return (long)T * d * 2 < (1L << 32) && 2L * Is * d * 2 < (1L << 32);
   }
   // ---- ring driver (weight rows as second operand: lane n of a block holds ITS row's products with 16
   // slot rows).  The two blocks of a phase are the gate and the up rows of the same 32 neurons.
@@ -181,7 +184,7 @@ struct DownOp {
   }
   __device__ __forceinline__ int a_row(const Sc& sc, int r, int) const { return min(r, sc.rows - 1); }
   __device__ __forceinline__ int b_row(const Sc& it, int br) const { return min(it.n0 + br, d - 1); }
-  static bool offsets_fit(long, long d, long Is) { return d * Is * 2 < (1L << 32); }
+  bool offsets_fit() const { return (long)(d < BM ? BM : d) * Is * 2 < (1L << 32); }
   // ---- ring driver: the two blocks of a phase are the even and the odd ones of 64 columns, so that
   // a lane holds two neighbouring columns
   static constexpr int CHUNK = 64;
@@ -212,9 +215,20 @@ struct DownOp {
   // of 64 scattered 16-byte pieces: y is the layer's largest HBM stream.  LDS rows are 128 bytes,
   // 16-byte chunk c of row r sits at position c ^ ((r >> 1) & 7): conflict-free both ways.
   // Rows beyond the tile are dropped by the buffer's bound, and blocks of 16 without a row skipped.
+  // (Tiles of 4 GiB and more, which a buffer cannot bound, are stored as they stand.)
   __device__ __forceinline__ void epilogue(const Sc& it, f32x16 (&acc)[NB][MB], uint16_t* scratch) const {
     const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
     const int wm = wv >> 1, wn = wv & 1;
+    if (!out_fits(d)) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        const int row = slot_block(wm, mb) * 32 + (lane & 31);
+        if (row >= it.rows) continue;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) store_block(it, row, weight_block(wn, nb), lane >> 5, acc[nb][mb]);
+      }
+      return;
+    }
     const int r = lane & 15, hi = lane >> 5, sw = (r >> 1) & 7;
     const uint32_t ld2 = (uint32_t)d * 2u;
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(y + (size_t)it.row0 * d + it.n0, 0,
@@ -420,7 +434,9 @@ __device__ __forceinline__ void dma4(const void* g, uint32_t lds) {
                : "v"(g), "s"(lds)
                : "memory");
 }
-template <class Op, bool HALF>
+// FAR: an operand of 4 GiB or more.  Byte offsets are 64 bits and added to the base by the vector ALU,
+// an addition per copy.
+template <class Op, bool HALF, bool FAR>
 __device__ __forceinline__ void run_items_ring(const Op& op, const MTile* __restrict__ tiles,
                                                int32_t* __restrict__ hdr, int n_tiles_n, int dyn_word) {
   using RG = Ring<Op::GATHER>;
@@ -476,10 +492,17 @@ __device__ __forceinline__ void run_items_ring(const Op& op, const MTile* __rest
   struct Piece {
     int left, stage, par;  // stages to go in this run; stages issued of the item; slot and slot-list parity
   };
+  typedef std::conditional_t<FAR, uint64_t, uint32_t> Off;
   const uint16_t *pa, *pb0, *pb1;
-  uint32_t va[4], vb0[2], vb1[2];
+  Off va[4], vb0[2], vb1[2];
   Piece px, py;
-  auto row_bytes = [&](int row) { return (uint32_t)row * (uint32_t)K * 2u; };
+  auto row_bytes = [&](int row) { return (Off)row * (Off)K * 2u; };
+  auto copy = [&](const uint16_t* base, Off off, uint32_t lds) {
+    if constexpr (FAR)
+      copy_to_lds16_addr((uint64_t)base + off, lds);
+    else
+      copy_to_lds16(base, off, lds);
+  };
   auto rows_x = [&](const Sc& sc, int parity) {
     op.bases(sc, pa, pb0);
     pa -= BK;  // advanced before every stage
@@ -511,7 +534,7 @@ __device__ __forceinline__ void run_items_ring(const Op& op, const MTile* __rest
   // the last stage of a run the last stage is copied again (nobody reads it), so that the number of
   // operations in flight is always the same.
   uint32_t x_lds, y_lds;
-  uint32_t xa[4], xb[2], yb[2];
+  Off xa[4], xb[2], yb[2];
   auto prep_x = [&]() {  // A, B0 of the next stage
     if (px.left > 0) {
       --px.left;
@@ -536,9 +559,9 @@ __device__ __forceinline__ void run_items_ring(const Op& op, const MTile* __rest
   };
   auto copy_x = [&](int j) {  // copies 0..5
     if (j < 4)
-      copy_to_lds16(pa, HALF ? xa[j] : va[j], x_lds + j * 1024u);
+      copy(pa, HALF ? xa[j] : va[j], x_lds + j * 1024u);
     else
-      copy_to_lds16(pb0, HALF ? xb[j - 4] : vb0[j - 4], x_lds + (B_OFF - (uint32_t)wv * 2048u) + (j - 4) * 1024u);
+      copy(pb0, HALF ? xb[j - 4] : vb0[j - 4], x_lds + (B_OFF - (uint32_t)wv * 2048u) + (j - 4) * 1024u);
   };
   auto prep_y = [&]() {  // B1 of the next stage
     if (py.left > 0) {
@@ -558,7 +581,7 @@ __device__ __forceinline__ void run_items_ring(const Op& op, const MTile* __rest
       for (int j = 0; j < 2; ++j) yb[j] = vb1[j] - (cut ? tail_off(swz_f<SWZ_SEQ>((wv * 2 + j) * 8)) : 0u);
     }
   };
-  auto copy_y = [&](int j) { copy_to_lds16(pb1, HALF ? yb[j] : vb1[j], y_lds + j * 1024u); };
+  auto copy_y = [&](int j) { copy(pb1, HALF ? yb[j] : vb1[j], y_lds + j * 1024u); };
   auto all_x = [&] {
     prep_x();
 #pragma unroll
@@ -819,10 +842,10 @@ __device__ __forceinline__ void run_items_ring(const Op& op, const MTile* __rest
 }
 
 // HALF: K % 64 == 32, the last stage of an item has two K steps
-template <class Op, bool HALF>
+template <class Op, bool HALF, bool FAR>
 __global__ __launch_bounds__(NT_) void ffn_ring_kernel(Op op, const MTile* __restrict__ tiles,
                                                        int32_t* __restrict__ hdr, int n_tiles_n, int dyn_word) {
-  run_items_ring<Op, HALF>(op, tiles, hdr, n_tiles_n, dyn_word);
+  run_items_ring<Op, HALF, FAR>(op, tiles, hdr, n_tiles_n, dyn_word);
 }
 template <class Op>
 __global__ __launch_bounds__(NT_) void ffn_short_kernel(Op op, const MTile* __restrict__ tiles,
@@ -942,10 +965,20 @@ static hipError_t launch_big(size_t lds, int grid, hipStream_t s, const Op& op, 
   return hipGetLastError();
 }
 
+// Operands of 4 GiB and more: 1.1 million tokens of d = 2048, 8 sub-experts of 704 | 192, gate-up between HIP
+// events: 5.78 | 1.79 ms; through the short-K driver, whose offsets can be of any size, 7.79 | 2.63.
+template <class Op, bool HALF>
+static hipError_t launch_ring(const Op& op, int ntn, int grid, int dyn_word, const MTile* tiles, int32_t* hdr,
+                              hipStream_t s) {
+  constexpr size_t lds = Ring<Op::GATHER>::LDS_BYTES;
+  if (op.offsets_fit()) return launch_big<ffn_ring_kernel<Op, HALF, false>>(lds, grid, s, op, tiles, hdr, ntn, dyn_word);
+  return launch_big<ffn_ring_kernel<Op, HALF, true>>(lds, grid, s, op, tiles, hdr, ntn, dyn_word);
+}
+
 template <class Op>
-static hipError_t launch_op(const Op& op, int K, int n_cols, bool fits, bool few, int dyn_word, int max_mtiles,
+static hipError_t launch_op(const Op& op, int K, int n_cols, bool few, int dyn_word, int max_mtiles,
                             const MTile* tiles, int32_t* hdr, hipStream_t s) {
-  if (few && fits) {
+  if (few && op.offsets_fit()) {
     const int ntn = cdiv(n_cols, FP_N / Op::N_PER_ROW);
     const int grid = persistent_grid((long)max_mtiles * ntn, 2);
     hipError_t e = raise_lds_limit<ffn_few_kernel<Op>>(FP_LDS_BYTES);
@@ -955,12 +988,11 @@ static hipError_t launch_op(const Op& op, int K, int n_cols, bool fits, bool few
   }
   const int ntn = cdiv(n_cols, BN / Op::N_PER_ROW);
   const int grid = persistent_grid((long)max_mtiles * ntn, 1);
-  constexpr size_t ring = Ring<Op::GATHER>::LDS_BYTES;
-  if (!fits || cdiv(K, BK) < RING_MIN_STAGES)
+  if (cdiv(K, BK) < RING_MIN_STAGES || !out_fits(n_cols))
     return launch_big<ffn_short_kernel<Op>>(SHORT_LDS_BYTES, grid, s, op, tiles, hdr, ntn);
   if constexpr (!Op::GATHER)  // Is % 32 == 0, d % 64 == 0
-    if (K % BK != 0) return launch_big<ffn_ring_kernel<Op, true>>(ring, grid, s, op, tiles, hdr, ntn, dyn_word);
-  return launch_big<ffn_ring_kernel<Op, false>>(ring, grid, s, op, tiles, hdr, ntn, dyn_word);
+    if (K % BK != 0) return launch_ring<Op, true>(op, ntn, grid, dyn_word, tiles, hdr, s);
+  return launch_ring<Op, false>(op, ntn, grid, dyn_word, tiles, hdr, s);
 }
 
 // At most 64 tokens (a group is then one or two row blocks; more would read the weights again for
@@ -975,15 +1007,14 @@ bool ffn_few_pairs(int T, int k_max, int E, int Is) {
 hipError_t launch_gate_up_bf16(const uint16_t* x, const uint16_t* w_gu, const int32_t* sorted_pair,
                                const MTile* tiles, int32_t* hdr, uint16_t* h, int T, int d,
                                int Is, int k_max, bool few, int max_mtiles, hipStream_t s) {
-  return launch_op(GateUpOp{x, w_gu, sorted_pair, h, T, d, Is, k_max}, d, Is, GateUpOp::offsets_fit(T, d, Is), few,
-                   HDR_DYN_GATE_UP, max_mtiles, tiles, hdr, s);
+  return launch_op(GateUpOp{x, w_gu, sorted_pair, h, T, d, Is, k_max}, d, Is, few, HDR_DYN_GATE_UP,
+                   max_mtiles, tiles, hdr, s);
 }
 
 hipError_t launch_down_bf16(const uint16_t* h, const uint16_t* w_dn, const MTile* tiles,
                             int32_t* hdr, uint16_t* y, int d, int Is, bool few, int max_mtiles,
                             hipStream_t s) {
-  return launch_op(DownOp{h, w_dn, y, d, Is}, Is, d, DownOp::offsets_fit(0, d, Is), few, HDR_DYN_DOWN, max_mtiles,
-                   tiles, hdr, s);
+  return launch_op(DownOp{h, w_dn, y, d, Is}, Is, d, few, HDR_DYN_DOWN, max_mtiles, tiles, hdr, s);
 }
 
 }  // namespace mp
