@@ -82,8 +82,12 @@ template <typename InT, int MT, int NT, int NS>
 static void launch_logits_cfg(const InT* x, const InT* w, const float* bias, float* logits,
                               int32_t* hdr, int T, int d, int E, hipStream_t s) {
   using C = ChainTile<InT, 2, 2, MT, NT, NS>;
-  logits_kernel<InT, 2, 2, MT, NT, NS><<<dim3(cdiv(E, C::BE), cdiv(T, C::BT)), 64 * C::NW, C::LDS_BYTES, s>>>(
-      x, w, bias, logits, hdr, T, d, E);
+  constexpr int MOST = 65535 * C::BT;  // tokens that the second dimension of a grid holds: 2.1 or 4.2 million
+  for (long t0 = 0; t0 < T; t0 += MOST) {
+    const int n = (int)(T - t0 < MOST ? T - t0 : MOST);
+    logits_kernel<InT, 2, 2, MT, NT, NS><<<dim3(cdiv(E, C::BE), cdiv(n, C::BT)), 64 * C::NW, C::LDS_BYTES, s>>>(
+        x + t0 * d, w, bias, logits + t0 * E, hdr, n, d, E);
+  }
 }
 
 // Workgroups of 2 x 2 waves on tiles of 32 x 32, 32 x 64 or 64 x 64 logits: 1, 2 or 4 sub-tiles

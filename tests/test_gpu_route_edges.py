@@ -98,3 +98,23 @@ def test_few_picks_of_equal_and_distinct_logits(E):
         ref = O.logits(x, w, None)
         assert np.array_equal(to_np(lg).view(np.uint32), ref.view(np.uint32))
         assert np.array_equal(to_np(ids), O.select(ref, k, k_max))
+
+
+def test_logits_of_more_tokens_than_a_grid_has_rows():
+    T, d, E = 4300000, 64, 33  # 32-token tiles: 134 375 rows
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randn(T, d, generator=g, device="cuda", dtype=torch.bfloat16)
+    w = torch.randn(E, d, generator=g, device="cuda", dtype=torch.bfloat16)
+
+    def route(x):
+        shape = B.make_shape(len(x), d, E, 1, 32, 1, "bf16")
+        k = torch.ones(len(x), dtype=torch.int32, device="cuda")
+        return B.moe_prism_route(shape, x, w, None, k, B.alloc_workspace(shape), want_logits=True)
+
+    ids, wt, lg = route(x)
+    ref = torch.cat([x[i:i + 500000].float() @ w.float().T for i in range(0, T, 500000)])
+    # a chain of 64 roundings of 2^-24 on sums of 64 terms, |term| <= 30 here, against another order of the same sum
+    assert (lg - ref).abs().max() <= 64 * 2.0 ** -24 * 64 * 30
+    assert torch.equal(ids[:, 0].long(), lg.argmax(dim=1))
+    for t in (0, 2097100, 4194200, T - 300):
+        assert all(torch.equal(a, b[t:t + 300]) for a, b in zip(route(x[t:t + 300].contiguous()), (ids, wt, lg)))
