@@ -93,24 +93,22 @@ static void launch_logits_cfg(const InT* x, const InT* w, const float* bias, flo
 // Workgroups of 2 x 2 waves on tiles of 32 x 32, 32 x 64 or 64 x 64 logits: 1, 2 or 4 sub-tiles
 // per SIMD.  The time is the number of sub-tiles the busiest SIMD works through (workgroups per
 // CU, rounded up, times sub-tiles), so the tile with the smallest such number is taken; among
-// equals the wider tile re-reads less (65 536 x 512: 0.94 ms against 1.00 and 1.04), but where
-// one or two sub-tiles are all there is its single workgroup per CU has nothing to overlap its
-// start with (4096 x 128: 20.7 us on 32 x 32, 21.5 on 32 x 64).  Measured, d = 2048, against the
-// kernels this one replaced: 16 384 x 512 0.242 ms (0.308), 8192 x 128 37 us (65), 2741 x 128
-// 20 us (35), 1 x 512 11 us (25).
+// equals, and up to 5 % more, the widest, which re-reads less (65 536 x 512: 0.94 ms against 1.07 and 0.98;
+// 50 000 x 512, counts 100, 98 and 98: 0.735 against 0.82 and 0.76), but where one or two sub-tiles are all there
+// is its single workgroup per CU has nothing to overlap its start with (4096 x 128: 22.2 us on 32 x 32, 24.4 on
+// 32 x 64).  Measured, d = 2048, against the kernels this one replaced: 16 384 x 512 0.242 ms (0.308), 8192 x 128
+// 37 us (65), 2741 x 128 20 us (35), 1 x 512 11 us (25).
 template <typename InT>
 static void launch_logits_t(const InT* x, const InT* w, const float* bias, float* logits,
                             int32_t* hdr, int T, int d, int E, hipStream_t s) {
   auto cost = [&](int bt, int be, int sub) { return (long)cdiv((long)cdiv(T, bt) * cdiv(E, be), num_cus()) * sub; };
-  const long c1 = cost(32, 32, 1), c2 = cost(32, 64, 2), c4 = cost(64, 64, 4);
-  const long best = c1 < c2 ? (c1 < c4 ? c1 : c4) : (c2 < c4 ? c2 : c4);
-  const bool few = best <= 2, some = best <= 4;
-  if (c1 == best && (few || (c2 > best && c4 > best)))
-    launch_logits_cfg<InT, 1, 1, 6>(x, w, bias, logits, hdr, T, d, E, s);
-  else if (c2 == best && (some || c4 > best))
+  const long c1 = cost(32, 32, 1), c2 = cost(32, 64, 2), c4 = cost(64, 64, 4);  // c1 <= c2 <= c4
+  if (c4 > 4 && c4 * 20 <= c1 * 21)
+    launch_logits_cfg<InT, 2, 2, 3>(x, w, bias, logits, hdr, T, d, E, s);
+  else if (c2 == c1 && c1 > 2)
     launch_logits_cfg<InT, 1, 2, 5>(x, w, bias, logits, hdr, T, d, E, s);
   else
-    launch_logits_cfg<InT, 2, 2, 3>(x, w, bias, logits, hdr, T, d, E, s);
+    launch_logits_cfg<InT, 1, 1, 6>(x, w, bias, logits, hdr, T, d, E, s);
 }
 
 hipError_t launch_logits(int dtype, const void* x, const void* w, const float* bias, float* logits,

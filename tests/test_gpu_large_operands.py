@@ -1,5 +1,4 @@
-"""Operands and tiles of 4 GiB and more, where byte offsets need 64 bits, and more token tiles than a grid's second
-dimension holds."""
+"""Operands and tiles of 4 GiB and more, where byte offsets need 64 bits."""
 import pytest
 import torch
 
