@@ -135,13 +135,20 @@ __device__ __forceinline__ void chain_tile(unsigned char* smem, int ns, Copy&& c
           read(slot_c, std::integral_constant<int, A>{});
         else  // after the last stage: an old slot, not used
           read(std::integral_constant<int, NSLOT>{}, std::integral_constant<int, A - C::STEPS>{});
-        asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(PD * NF));  // the reads of this step have returned
+        // the reads of this step have returned
+        uint32_t(&ua)[MT] = fa[S % R], (&ub)[NT] = fb[S % R];
+        if constexpr (MT == 2)
+          wait_lds<PD * NF>(ua[0], ua[1], ub[0], ub[1]);
+        else if constexpr (NT == 2)
+          wait_lds<PD * NF>(ua[0], ub[0], ub[1]);
+        else
+          wait_lds<PD * NF>(ua[0], ub[0]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
           for (int j = 0; j < NT; ++j)  // ascending k
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(fa[S % R][i]), __uint_as_float(fb[S % R][j]),
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(ua[i]), __uint_as_float(ub[j]),
                                                             acc[i][j], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
       });

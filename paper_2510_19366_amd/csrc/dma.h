@@ -55,6 +55,10 @@ __device__ __forceinline__ void wait_lds(V& a, V& b) {
   asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N));
 }
 template <int N, class V>
+__device__ __forceinline__ void wait_lds(V& a, V& b, V& c) {
+  asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(a), "+v"(b), "+v"(c) : "n"(N));
+}
+template <int N, class V>
 __device__ __forceinline__ void wait_lds(V& a, V& b, V& c, V& d) {
   asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "n"(N));
 }
