@@ -184,8 +184,14 @@ def moe_prism_layer(shape, x, w_router, router_bias, k_tok, w_gate_up, w_down, w
 
 
 def ffn_path(shape):
-    """Which grouped-FFN kernels moe_prism_grouped_ffn / _layer launch for this shape: "fused"
-    (bf16, inter_sub in {64, 128, 192}, d >= 256, unless MOE_PRISM_FFN=split) or "split"."""
+    """Which grouped-FFN kernels moe_prism_grouped_ffn / _layer launch for this shape: "fused" (bf16,
+    inter_sub in {64, 128, 192}, d >= 256, unless MOE_PRISM_FFN=split), "few" (bf16, at most 64 tokens and
+    few sub-experts to touch: gate-up and down on small tiles) or "split" (gate-up and down)."""
+    pairs, groups = shape.T * shape.k_max, shape.E
+    cus = torch.cuda.get_device_properties(0).multi_processor_count if torch.cuda.is_available() else 256
+    tiles = min(pairs, groups) * -(-shape.inter_sub // 128)
+    if shape.dtype == 1 and shape.T <= 64 and 2 * tiles <= 3 * cus * (2 if shape.inter_sub <= 192 else 1):
+        return "few"
     ok = (shape.dtype == 1 and shape.inter_sub in (64, 128, 192) and shape.d % 64 == 0
           and shape.d >= 256 and shape.T * shape.d * 2 < 2 ** 32)
     return "fused" if ok and os.environ.get("MOE_PRISM_FFN") != "split" else "split"

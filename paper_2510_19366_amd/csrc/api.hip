@@ -171,7 +171,8 @@ static int do_dispatch(const moe_prism_shape* s, const Layout& L, const int32_t*
   return do_dispatch_over(L, ids, cnt, off, sorted_pair, slot_of_pair, chunk, hdr, tiles, s->T, E, s->k_max, st);
 }
 
-// The fused gate-up/SwiGLU/down kernel serves bf16 layers with narrow sub-experts; the
+// The fused gate-up/SwiGLU/down kernel serves bf16 layers with narrow sub-experts (but for a handful of
+// pairs, see ffn_few_pairs); the
 // environment variable MOE_PRISM_FFN=split forces the two-kernel path (for A/B measurements
 // and so that tests reach both paths on the same shapes).
 static bool use_fused_ffn(const moe_prism_shape* s) {
@@ -199,16 +200,7 @@ static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, cons
     return MOE_PRISM_OK;
   }
   const bool few = s->dtype == MOE_PRISM_BF16 && ffn_few_pairs(s->T, s->k_max, E, s->inter_sub);
-  if (use_fused_ffn(s)) {
-    if (few) {  // both GEMMs in place of the fused kernel, timed as one
-      hipError_t e[2] = {hipSuccess, hipSuccess};
-      MP_LAUNCH(MOE_PRISM_K_FFN_FUSED,
-                (e[0] = launch_ffn_gate_up(s->dtype, x, w_gu, sorted_pair, tiles, hdr, h, s->T, s->d, s->inter_sub,
-                                           s->k_max, few, L.max_mtiles, st),
-                 e[1] = launch_ffn_down(s->dtype, h, w_dn, tiles, hdr, y, s->T, s->d, s->inter_sub, few, L.max_mtiles, st),
-                 e[0] != hipSuccess ? e[0] : e[1]));
-      return MOE_PRISM_OK;
-    }
+  if (use_fused_ffn(s) && !few) {
     MP_LAUNCH(MOE_PRISM_K_FFN_FUSED,
               launch_ffn_fused_bf16((const uint16_t*)x, (const uint16_t*)w_gu, (const uint16_t*)w_dn,
                                     sorted_pair, tiles, hdr, (uint16_t*)y, s->T, s->d, s->inter_sub,

@@ -996,9 +996,12 @@ static hipError_t launch_op(const Op& op, int K, int n_cols, bool few, int dyn_w
 }
 
 // At most 64 tokens (a group is then one or two row blocks; more would read the weights again for
-// each), and the ring kernel's n-tiles of all sub-experts that they can touch are fewer than 1.5 per
-// CU.  A narrow sub-expert is one workgroup of the fused kernel and costs 80 us at d = 2048 however
-// few there are, as much as this path takes for about 200 of them.
+// each), and the ring kernel's n-tiles of all sub-experts that they can touch are at most 1.5 per CU, or 3 where
+// Is <= 192.  Both GEMMs between HIP events, d = 2048, one pair per touched sub-expert, small tiles | what takes 65
+// tokens.  Is = 192 (fused): 20 sub-experts 20 | 78 us, 100 49 | 82, 200 97 | 113, 384 169 | 216.  Is = 32: 100 26 | 44,
+// 768 108 | 137; 96: 768 205 | 215; 160: 384 160 | 185; 352: 32 32 | 49, 128 111 | 145; 704: 16 32 | 49, 64 111 | 145.
+// All pairs of 64 tokens on 8 sub-experts of 704, 32 rows each: 36 | 50; on 4 of 3584: 69 | 83.  So they are ahead as
+// far as the rule goes; beyond it the work is that of the weights' bytes, whichever tiles read them.
 bool ffn_few_pairs(int T, int k_max, int E, int Is) {
   const long pairs = (long)T * k_max, groups = pairs < E ? pairs : E;
   return T <= 64 && groups * cdiv(Is, BN / 2) * 2 <= 3L * num_cus() * (Is <= 192 ? 2 : 1);

@@ -79,7 +79,8 @@ def test_small_cases_full_oracle(dtype, case):
     dict(T=900, d=256, N=5, S=4, Is=64, k_max=6),
     dict(T=1200, d=512, N=3, S=4, Is=128, k_max=5),
     dict(T=2000, d=320, N=6, S=4, Is=192, k_max=8),
-    dict(T=3, d=256, N=2, S=2, Is=192, k_max=4),
+    dict(T=3, d=256, N=2, S=2, Is=192, k_max=4),     # a handful of tokens: neither of the two, small tiles
+    dict(T=65, d=256, N=64, S=4, Is=192, k_max=4),   # a row or two per group: most waves multiply nothing
     dict(T=700, d=704, N=40, S=4, Is=192, k_max=20),
     dict(T=9000, d=256, N=64, S=4, Is=64, k_max=16),
 ])
@@ -102,28 +103,30 @@ def test_narrow_sub_experts_both_ffn_paths(case, path, monkeypatch):
     B.moe_prism_timing_enable(False)
     assert np.array_equal(to_np(out), r["out"])
     # the intended kernels ran
+    few = case["T"] <= 64
     assert (calls["ffn_fused"], calls["ffn_gate_up"], calls["ffn_down"]) == \
-        ((1, 0, 0) if path == "fused" else (0, 1, 1))
+        ((1, 0, 0) if path == "fused" and not few else (0, 1, 1))
+    assert B.ffn_path(r["shape"]) == ("few" if few else path)
 
 
-@pytest.mark.parametrize("stage_k", ["64", "32"])
 @pytest.mark.parametrize("case", [
-    dict(T=900, d=512, N=3, S=2, Is=256, k_max=4),      # both GEMMs in 64-element stages, 256-wide tiles
-    dict(T=1500, d=256, N=5, S=2, Is=320, k_max=6),     # shortest K the 64-element driver takes (4 stages)
-    dict(T=700, d=1024, N=4, S=2, Is=704, k_max=5),     # 192-wide gate-up tiles (1408 rows), 11 down stages
-    dict(T=1100, d=448, N=3, S=4, Is=352, k_max=7),     # Is % 64 != 0: the down GEMM keeps 32-element stages
-    dict(T=5, d=320, N=2, S=1, Is=512, k_max=2),        # a handful of rows: most waves multiply nothing
+    dict(T=900, d=512, N=3, S=2, Is=256, k_max=4),      # both GEMMs in the ring driver; four stages of K in the down one
+    dict(T=1500, d=256, N=5, S=2, Is=320, k_max=6),     # the same in the gate-up one; last weight tile half full
+    dict(T=700, d=1024, N=4, S=2, Is=704, k_max=5),     # 11 down stages
+    dict(T=1100, d=448, N=3, S=4, Is=352, k_max=7),     # Is % 64 != 0: half a stage at the end of the down GEMM's K
+    dict(T=1100, d=192, N=3, S=4, Is=160, k_max=7),     # K too short for the ring in both GEMMs
+    dict(T=65, d=320, N=16, S=4, Is=512, k_max=2),      # a row or two per group: most waves multiply nothing
+    dict(T=5, d=320, N=2, S=1, Is=512, k_max=2),        # a handful of tokens: small tiles
     dict(T=2600, d=384, N=2, S=1, Is=1024, k_max=2),    # groups of many m-tiles, several items per workgroup
 ])
-def test_wide_sub_experts_both_stage_widths(case, stage_k, monkeypatch):
-    # MOE_PRISM_FFN_K=32 sends the same shapes through the drivers with 32-element K stages
-    monkeypatch.setenv("MOE_PRISM_FFN_K", stage_k)
+def test_wide_sub_experts(case):
     rng = np.random.default_rng(case["T"] + 1)
     k = rng.integers(0, case["k_max"] + 1, size=case["T"]).astype(np.int32)
     wl = W.make_workload("wide", dtype="bf16", d=case["d"], n_experts=case["N"], n_sub=case["S"],
                          inter_sub=case["Is"], req_tokens=[1] * case["T"], req_k=k,
                          k_max=case["k_max"], seed=case["T"], bias_std=1.0, w_std=0.05)
     r = run_stages(wl)
+    assert B.ffn_path(r["shape"]) == ("few" if case["T"] <= 64 else "split")
     ref = O.layer_of(wl, return_all=True)
     check_against_oracle(wl, r, ref)
     assert row_rel(r["y"], ref["y"]) <= 4e-2 and row_rel(r["out"], ref["out"]) <= 4e-2
@@ -213,8 +216,8 @@ def test_wide_router_and_large_k():
 @pytest.mark.parametrize("seed", range(16))
 def test_random_shapes_full_oracle(seed):
     # seeded random layer shapes: K lengths on both sides of every kernel-selection threshold
-    # (register-staged, in-step ring, two-group ring; 192- and 256-wide tiles; all three logits
-    # kernels' neighbours), ragged groups, empty groups, budgets from 0 to k_max
+    # (small tiles, short-K, ring and fused drivers; the logits tiles), ragged groups, empty groups,
+    # budgets from 0 to k_max
     rng = np.random.default_rng(1000 + seed)
     d = 64 * int(rng.integers(1, 11))
     Is = 32 * int(rng.integers(1, 14))
