@@ -237,7 +237,8 @@ __global__ __launch_bounds__(64 * TOPK_WAVES) void topk_kernel(
     int best = GONE;
 #pragma unroll
     for (int i = 0; i < ELEMS; ++i) {
-      key[i] = i * 64 + lane < E ? topk_key(v[i]) : GONE;
+      const int k = topk_key(v[i]);  // outside the choice, or it becomes a branch per element
+      key[i] = i * 64 + lane < E ? k : GONE;
       best = max(best, key[i]);
     }
     if (kt > 0 && kt <= TOPK_FEW) {

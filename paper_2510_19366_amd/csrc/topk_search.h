@@ -14,13 +14,15 @@ MP_HD float bits_float(int b) { return __builtin_bit_cast(float, b); }
 // every non-NaN binary32 once -0.0 has been replaced by +0.0 (the two compare equal, and equal
 // logits go to the lower id).  INT_MIN and INT_MAX are the keys of no logit (two NaNs could be): the one
 // marks absent elements, the other is behind every key.
+MP_HD int ordered_bits(int b) { return b ^ ((b >> 31) & 0x7fffffff); }
 MP_HD int topk_key(float f) {
   int b = float_bits(f);
   b = b == INT32_MIN ? 0 : b;  // -0.0 -> +0.0
-  const int k = b ^ ((b >> 31) & 0x7fffffff);
-  return k <= INT32_MIN ? INT32_MIN + 1 : k >= INT32_MAX ? INT32_MAX - 1 : k;
+  b = ordered_bits(b);
+  b = b < INT32_MIN + 1 ? INT32_MIN + 1 : b;
+  return b > INT32_MAX - 1 ? INT32_MAX - 1 : b;
 }
-MP_HD float topk_unkey(int k) { return bits_float(k ^ ((k >> 31) & 0x7fffffff)); }
+MP_HD float topk_unkey(int k) { return bits_float(ordered_bits(k)); }
 
 // picks: all keys > thr and the first `rem` keys == thr in id order
 struct TopkCut {
@@ -30,7 +32,7 @@ constexpr int TOPK_VALUE_STEPS = 16;
 
 // at_least(key): number of keys >= key.  at_least(lo) >= k > at_least(hi).  A threshold with exactly k
 // keys above it ends the search; with equal keys at the border there is none and lo ends as the border key.
-// uniform(m): m, into a scalar register.
+// uniform(m): m, into a scalar register.  Any m with lo < m < hi will do, also one that is no logit's key.
 // Thresholds are taken midway between the logits: few steps, because the gaps between neighbouring order
 // statistics are wide compared to the range.  First, though, an end more than 2^8 times the other (a
 // mask of the lowest finite value, an infinity, an absent element), which midpoints would only halve, 128
@@ -56,13 +58,13 @@ MP_HD TopkCut topk_cut(int lo, int hi, int k, Uniform&& uniform, Count&& at_leas
     const int a = float_bits(topk_unkey(lo)), b = float_bits(topk_unkey(hi));
     const uint32_t ma = (uint32_t)a & 0x7fffffffu, mb = (uint32_t)b & 0x7fffffffu;
     if ((ma > mb ? ma - mb : mb - ma) <= (8u << 23)) break;
-    const int m = uniform((lo ^ hi) < 0 ? topk_key(-0.5f * bits_float(ma > mb ? b : a))
-                                        : topk_key(bits_float((a & INT32_MIN) | (int)((ma + mb) >> 1))));
+    const int m = uniform(ordered_bits((lo ^ hi) < 0 ? float_bits(-0.5f * bits_float(ma > mb ? b : a))
+                                                     : (a & INT32_MIN) | (int)((ma + mb) >> 1)));
     if (m <= lo || m >= hi) break;
     if (found(m)) return TopkCut{hi - 1, 0};
   }
   for (int step = 0; (uint32_t)hi - (uint32_t)lo > 1u; ++step) {
-    int m = uniform(topk_key(0.5f * topk_unkey(lo) + 0.5f * topk_unkey(hi)));
+    int m = uniform(ordered_bits(float_bits(0.5f * topk_unkey(lo) + 0.5f * topk_unkey(hi))));
     if (m <= lo || m >= hi || step >= TOPK_VALUE_STEPS) m = (int)((uint32_t)lo + (((uint32_t)hi - (uint32_t)lo) >> 1));
     if (found(m)) return TopkCut{hi - 1, 0};
   }
