@@ -135,7 +135,8 @@ __device__ __forceinline__ void chain_tile(unsigned char* smem, int ns, Copy&& c
           read(slot_c, std::integral_constant<int, A>{});
         else  // after the last stage: an old slot, not used
           read(std::integral_constant<int, NSLOT>{}, std::integral_constant<int, A - C::STEPS>{});
-        // the reads of this step have returned
+        // the reads of this step have returned (the tie brings a wait state in front of the multiply: 2741 x 128
+        // logits 22.0 -> 22.3 us, 16 384 x 512 240 either way)
         uint32_t(&ua)[MT] = fa[S % R], (&ub)[NT] = fb[S % R];
         if constexpr (MT == 2)
           wait_lds<PD * NF>(ua[0], ua[1], ub[0], ub[1]);
