@@ -862,7 +862,7 @@ __global__ __launch_bounds__(NT_) void ffn_short_kernel(Op op, const MTile* __re
 // show in its results.
 // Bound by the latency of one chain: ring fill, K stages; a stage's fragments are read while the stage
 // before is multiplied.  Measured between HIP events, one token of the 128 x 4 layer (20 to 32 sub-experts of
-// 192, d = 2048): gate-up and down together 22.6 us, the fused kernel 80 (with the list of all row blocks, see
+// 192, d = 2048): gate-up and down together 22.7 us, the fused kernel 85 (with the list of all row blocks, see
 // row_blocks.h, 28.9; with the two halves of every stage on two waves and added up at the end, which is another order
 // of the sum, 31.5).
 constexpr int FP_N = 64, FP_M = 32, FP_NS = 6, FP_THREADS = 256;

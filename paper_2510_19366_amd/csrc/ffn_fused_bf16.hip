@@ -372,8 +372,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
       {
         // ---- phase 1: acc1[blk] += W-block(blk) x-rows^T.  A stage is 64 K-elements (4 K steps) of half
         // of the blocks, so that a copy takes whole 128-byte lines: with 32 K-elements of all blocks
-        // the L2 serves every line twice, half a line at a time (measured on 16384 tokens, 512
-        // sub-experts of 192 x 2048: 1042 us, with whole lines, also in the stores of y, 912 us).
+        // the L2 serves every line twice, half a line at a time (between HIP events, 16384
+        // tokens of 20 picks, 512 sub-experts of 192 x 2048: 1016 us, with whole lines, also in the stores of y, 947).
         // The fragment of step i + PD is read right after the MFMA of step i is issued (the
         // scheduling barriers keep that order), and the stream of reads runs on into the next
         // stage (after the last stage of the phase it reads a slot whose values are not used).

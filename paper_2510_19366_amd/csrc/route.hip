@@ -166,8 +166,8 @@ __device__ __forceinline__ float wave_sum(float x) {
 
 constexpr int TOPK_WAVES = 4;
 // Budgets up to this take a maximum per pick, larger ones the search, whose time is mostly the
-// compaction and ranking behind it.  16 384 x 512 between HIP events, picks | search: 2 picks 14.8 | 19 us,
-// 6 picks 21.1 | 22.3, 8 picks 24.1 | 22.4; 16 384 x 2048: 32 | 45, 47 | 51, 55 | 54.
+// compaction and ranking behind it.  16 384 x 512 between HIP events, picks | search: 2 picks 14.7 | 18.2 us,
+// 6 picks 20.5 | 20.4, 8 picks 23.7 | 21.3; 16 384 x 2048: 30.5 | 41.6, 44.6 | 47.2, 52.8 | 47.4.
 constexpr int TOPK_FEW = 6;
 __host__ __device__ inline int topk_pad(int k_max) { return (k_max + 3) / 4 * 4; }
 // a wave's own LDS writes are readable by all its lanes
