@@ -167,8 +167,9 @@ __device__ __forceinline__ float wave_sum(float x) {
 constexpr int TOPK_WAVES = 4;
 // Budgets up to this take a maximum per pick, larger ones the search, whose time is mostly the
 // compaction and ranking behind it.  16 384 x 512 between HIP events, picks | search: 2 picks 14.7 | 18.2 us,
-// 6 picks 20.5 | 20.4, 8 picks 23.7 | 21.3; 16 384 x 2048: 30.5 | 41.6, 44.6 | 47.2, 52.8 | 47.4.
-constexpr int TOPK_FEW = 6;
+// 6 picks 20.5 | 20.4, 8 picks 23.7 | 21.3; 16 384 x 2048: 30.5 | 41.6, 44.6 | 47.2, 52.8 | 47.4.  With one element
+// per lane a maximum is cheaper: 4096 x 64, 8 picks 7.9 | 8.6, 12 picks 9.1 | 8.6 (16 384 x 64: 15.6 | 14.9).
+constexpr int topk_few(int elems) { return elems == 1 ? 8 : 6; }
 __host__ __device__ inline int topk_pad(int k_max) { return (k_max + 3) / 4 * 4; }
 // a wave's own LDS writes are readable by all its lanes
 __device__ __forceinline__ void wave_lds_fence() {
@@ -241,7 +242,7 @@ __global__ __launch_bounds__(64 * TOPK_WAVES) void topk_kernel(
       key[i] = i * 64 + lane < E ? k : GONE;
       best = max(best, key[i]);
     }
-    if (kt > 0 && kt <= TOPK_FEW) {
+    if (kt > 0 && kt <= topk_few(ELEMS)) {
       // One wave-wide maximum per pick: g = 64 i + lane, so inside a lane the lower element index is
       // the lower id, and the winner's lane is g & 63.  Only that lane retires its element.
       constexpr int NONE = 0x7fffffff;
