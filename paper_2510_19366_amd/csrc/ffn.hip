@@ -124,14 +124,15 @@ __device__ __forceinline__ void f32_tile(const float* a_base, const float* b_bas
 // SHORT: see row_blocks.h
 template <bool SHORT, class Body>
 __device__ __forceinline__ void f32_items(const MTile* __restrict__ tiles, const int32_t* __restrict__ hdr,
-                                          int n_tiles_n, Body&& body) {
+                                          int n_tiles_n, int T, Body&& body) {
   auto tile = [&](int m) { return tiles[m]; };
   auto each = [&](const MTile& t, int blk, int nt) {
     body(t.g, t.row0 + blk * F32_ROWS, min(F32_ROWS, t.rows - blk * F32_ROWS), nt);
     __syncthreads();  // every wave has read the last stage before the ring is filled again
   };
   if constexpr (SHORT)
-    short_row_blocks<F32_ROWS>(blockIdx.x, gridDim.x, N_XCD, hdr[HDR_MTILES], n_tiles_n, tile, each);
+    short_row_blocks<F32_ROWS>(blockIdx.x, gridDim.x, N_XCD, hdr[HDR_MTILES], n_tiles_n,
+                               (T + F32_ROWS - 1) / F32_ROWS, tile, each);
   else
     all_row_blocks<F32_ROWS, F32_BLOCKS>(blockIdx.x, gridDim.x, N_XCD, hdr[HDR_MTILES], n_tiles_n, tile, each);
 }
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(256) void ffn_gate_up_f32_kernel(
     const int32_t* __restrict__ hdr, float* __restrict__ h, int d, int Is, int k_max, int T) {
   extern __shared__ __align__(16) unsigned char f_smem[];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, wm = wv >> 1, wn = wv & 1;
-  f32_items<SHORT>(tiles, hdr, Is / 32, [&](int g, int row0, int rows, int nt) {  // Is % 32 == 0
+  f32_items<SHORT>(tiles, hdr, Is / 32, T, [&](int g, int row0, int rows, int nt) {  // Is % 32 == 0
     f32x4_t acc[1][2];
     f32_tile<WIDE>(x, w_gu + (size_t)g * 2 * Is * d, d, [&](int row) -> size_t {
       if (row < F32_ROWS) return min(max(sorted_pair[row0 + min(row, rows - 1)] / k_max, 0), T - 1);
@@ -166,10 +167,10 @@ __global__ __launch_bounds__(256) void ffn_down_f32_kernel(const float* __restri
                                                            const float* __restrict__ w_dn,
                                                            const MTile* __restrict__ tiles,
                                                            const int32_t* __restrict__ hdr,
-                                                           float* __restrict__ y, int d, int Is) {
+                                                           float* __restrict__ y, int T, int d, int Is) {
   extern __shared__ __align__(16) unsigned char f_smem[];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, wm = wv >> 1, wn = wv & 1;
-  f32_items<SHORT>(tiles, hdr, d / F32_COLS, [&](int g, int row0, int rows, int nt) {  // d % 64 == 0
+  f32_items<SHORT>(tiles, hdr, d / F32_COLS, T, [&](int g, int row0, int rows, int nt) {  // d % 64 == 0
     f32x4_t acc[1][2];
     f32_tile<WIDE>(h + (size_t)row0 * Is, w_dn + (size_t)g * d * Is, Is, [&](int row) -> size_t {
       return row < F32_ROWS ? min(row, rows - 1) : nt * F32_COLS + row - F32_ROWS;
@@ -212,13 +213,13 @@ hipError_t launch_ffn_down(int dtype, const void* h, const void* w_dn, const MTi
                            hipStream_t s) {
   if (max_mtiles <= 0) return hipSuccess;
   if (dtype != 0)
-    return launch_down_bf16((const uint16_t*)h, (const uint16_t*)w_dn, tiles, hdr, (uint16_t*)y, d,
+    return launch_down_bf16((const uint16_t*)h, (const uint16_t*)w_dn, tiles, hdr, (uint16_t*)y, T, d,
                             Is, few, max_mtiles, s);
   const int grid = persistent_grid((long)max_mtiles * F32_BLOCKS * (d / F32_COLS), 2);
   const bool wide = (long)Is * d >= (1L << 30);
   auto* kern = f32_short(T) ? (wide ? ffn_down_f32_kernel<true, true> : ffn_down_f32_kernel<false, true>)
                             : (wide ? ffn_down_f32_kernel<true, false> : ffn_down_f32_kernel<false, false>);
-  kern<<<grid, 256, F32Tile::LDS_BYTES, s>>>((const float*)h, (const float*)w_dn, tiles, hdr, (float*)y, d, Is);
+  kern<<<grid, 256, F32Tile::LDS_BYTES, s>>>((const float*)h, (const float*)w_dn, tiles, hdr, (float*)y, T, d, Is);
   return hipGetLastError();
 }
 

@@ -871,15 +871,16 @@ constexpr int FP_CP = (FP_M + FP_N) / 8 / (FP_THREADS / 64);  // copies per wave
 
 template <class Op>
 __global__ __launch_bounds__(FP_THREADS) void ffn_few_kernel(Op op, const MTile* __restrict__ tiles,
-                                                             const int32_t* __restrict__ hdr, int n_tiles_n) {
+                                                             const int32_t* __restrict__ hdr, int n_tiles_n,
+                                                             int blocks) {
   extern __shared__ __align__(16) unsigned char fp_smem[];
   const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
   const int wb = wv;  // weight block (waves 0 and 1)
   const int fr = lane & 31, fh = lane >> 5, wrow = Op::wrow(fr);
   const int K = op.K(), ns = (K + BK - 1) / BK;
   const uint32_t lds0 = lds_offset(fp_smem), dst0 = lds0 + (uint32_t)(wv * FP_CP) * 1024u;
-  short_row_blocks<FP_M>(blockIdx.x, gridDim.x, N_XCD, hdr[HDR_MTILES], n_tiles_n, [&](int m) { return tiles[m]; },
-                         [&](const MTile& t, int blk, int nt) {
+  short_row_blocks<FP_M>(blockIdx.x, gridDim.x, N_XCD, hdr[HDR_MTILES], n_tiles_n, blocks,
+                         [&](int m) { return tiles[m]; }, [&](const MTile& t, int blk, int nt) {
     Sc sc;
     sc.g = uni(t.g);
     sc.row0 = uni(t.row0) + blk * FP_M;
@@ -976,14 +977,14 @@ static hipError_t launch_ring(const Op& op, int ntn, int grid, int dyn_word, con
 }
 
 template <class Op>
-static hipError_t launch_op(const Op& op, int K, int n_cols, bool few, int dyn_word, int max_mtiles,
+static hipError_t launch_op(const Op& op, int T, int K, int n_cols, bool few, int dyn_word, int max_mtiles,
                             const MTile* tiles, int32_t* hdr, hipStream_t s) {
   if (few && op.offsets_fit()) {
     const int ntn = cdiv(n_cols, FP_N / Op::N_PER_ROW);
-    const int grid = persistent_grid((long)max_mtiles * ntn, 2);
+    const int blocks = cdiv(T, FP_M), grid = persistent_grid((long)max_mtiles * ntn * blocks, 2);
     hipError_t e = raise_lds_limit<ffn_few_kernel<Op>>(FP_LDS_BYTES);
     if (e != hipSuccess) return e;
-    ffn_few_kernel<Op><<<grid, FP_THREADS, FP_LDS_BYTES, s>>>(op, tiles, hdr, ntn);
+    ffn_few_kernel<Op><<<grid, FP_THREADS, FP_LDS_BYTES, s>>>(op, tiles, hdr, ntn, blocks);
     return hipGetLastError();
   }
   const int ntn = cdiv(n_cols, BN / Op::N_PER_ROW);
@@ -1010,14 +1011,14 @@ bool ffn_few_pairs(int T, int k_max, int E, int Is) {
 hipError_t launch_gate_up_bf16(const uint16_t* x, const uint16_t* w_gu, const int32_t* sorted_pair,
                                const MTile* tiles, int32_t* hdr, uint16_t* h, int T, int d,
                                int Is, int k_max, bool few, int max_mtiles, hipStream_t s) {
-  return launch_op(GateUpOp{x, w_gu, sorted_pair, h, T, d, Is, k_max}, d, Is, few, HDR_DYN_GATE_UP,
+  return launch_op(GateUpOp{x, w_gu, sorted_pair, h, T, d, Is, k_max}, T, d, Is, few, HDR_DYN_GATE_UP,
                    max_mtiles, tiles, hdr, s);
 }
 
 hipError_t launch_down_bf16(const uint16_t* h, const uint16_t* w_dn, const MTile* tiles,
-                            int32_t* hdr, uint16_t* y, int d, int Is, bool few, int max_mtiles,
+                            int32_t* hdr, uint16_t* y, int T, int d, int Is, bool few, int max_mtiles,
                             hipStream_t s) {
-  return launch_op(DownOp{h, w_dn, y, d, Is}, Is, d, few, HDR_DYN_DOWN, max_mtiles, tiles, hdr, s);
+  return launch_op(DownOp{h, w_dn, y, d, Is}, T, Is, d, few, HDR_DYN_DOWN, max_mtiles, tiles, hdr, s);
 }
 
 }  // namespace mp

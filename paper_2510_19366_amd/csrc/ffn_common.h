@@ -48,7 +48,7 @@ hipError_t launch_gate_up_bf16(const uint16_t* x, const uint16_t* w_gu, const in
                                const MTile* tiles, int32_t* hdr, uint16_t* h, int T, int d,
                                int Is, int k_max, bool few, int max_mtiles, hipStream_t s);
 hipError_t launch_down_bf16(const uint16_t* h, const uint16_t* w_dn, const MTile* tiles,
-                            int32_t* hdr, uint16_t* y, int d, int Is, bool few, int max_mtiles,
+                            int32_t* hdr, uint16_t* y, int T, int d, int Is, bool few, int max_mtiles,
                             hipStream_t s);
 
 }  // namespace mp

@@ -1,5 +1,7 @@
 // How workgroups share small tiles: plain C++, so that it can be run on the host as well.
 #pragma once
+#include <stdint.h>
+
 #include "host_device.h"
 
 namespace mp {
@@ -8,18 +10,20 @@ namespace mp {
 // f(m-tile, row block, n-tile) for the share of workgroup b out of `grid` (a multiple of n_xcd; b serves XCD
 // b % n_xcd, and an XCD a contiguous part of the list, in which a sub-expert's weights meet).
 
-// For m-tiles of which hardly any has a second row block: the list holds (m-tile, n-tile) pairs, all of which exist,
-// and a workgroup walks through the row blocks of its pairs.  A list of every possible row block is
+// For m-tiles of at most `blocks` row blocks (longer ones take longer): the list holds the first row block of every
+// (m-tile, n-tile) pair, all of which exist, then the second ones, of which few do or all.  A list of every possible row block is
 // mostly empty there, and brings those that exist to the same few workgroups whenever the stride grid / n_xcd has a
 // factor in common with row blocks x n-tiles: one row in each of 32 groups, 4 n-tiles, 8 row blocks, 512
 // workgroups: 128 tiles on 64 of them; 20 groups, 32 n-tiles: 640 tiles on 256.
 template <int ROWS, class Tile, class F>
-MP_HD void short_row_blocks(int b, int grid, int n_xcd, int n_mtiles, int n_tiles_n, Tile&& tile, F&& f) {
+MP_HD void short_row_blocks(int b, int grid, int n_xcd, int n_mtiles, int n_tiles_n, int blocks, Tile&& tile, F&& f) {
   const int xcd = b % n_xcd, total = n_mtiles * n_tiles_n, chunk = (total + n_xcd - 1) / n_xcd;
   const int end = total < (xcd + 1) * chunk ? total : (xcd + 1) * chunk;
-  for (int item = xcd * chunk + b / n_xcd; item < end; item += grid / n_xcd) {
+  const int n = end - xcd * chunk;  // the XCD's pairs
+  for (int i = b / n_xcd; i < n * blocks; i += grid / n_xcd) {
+    const int item = xcd * chunk + i % n, first = i / n, last = first == blocks - 1 ? INT32_MAX / ROWS : first;
     const auto t = tile(item / n_tiles_n);
-    for (int blk = 0; blk * ROWS < t.rows; ++blk) f(t, blk, item % n_tiles_n);
+    for (int blk = first; blk <= last && blk * ROWS < t.rows; ++blk) f(t, blk, item % n_tiles_n);
   }
 }
 

@@ -13,7 +13,8 @@ struct Tile {
 };
 
 template <class Deal>
-int check(Deal&& deal, int grid, int n_tiles_n, const std::vector<Tile>& tiles, bool even) {
+int check(Deal&& deal, int grid, int n_tiles_n, const std::vector<Tile>& tiles, bool even,
+          int blocks = 1) {
   const int n = (int)tiles.size();
   std::vector<int> seen((size_t)n * 8 * n_tiles_n, 0);
   int exist = 0, most = 0;
@@ -33,8 +34,8 @@ int check(Deal&& deal, int grid, int n_tiles_n, const std::vector<Tile>& tiles, 
     done += c;
   }
   if (done != exist) return 4;
-  // an even share of what an XCD gets, which is an eighth
-  const int share = (exist + 7) / 8, per = grid / 8;
+  // an even share of what an XCD gets, which is an eighth of the pairs
+  const int share = (exist / blocks + 7) / 8 * blocks, per = grid / 8;
   return even && most > (share + per - 1) / per ? 5 : 0;
 }
 
@@ -43,11 +44,15 @@ int main() {
   for (int grid : {8, 64, 512})
     for (int n_tiles_n : {1, 2, 4, 6, 11, 22, 32})
       for (int n : {0, 1, 5, 20, 32, 250, 500})
-        for (int kind = 0; kind < 3; ++kind) {  // one row block, all full, any length
+        for (int kind = 0; kind < 5; ++kind) {  // one row block, all full, any length, two row blocks, one or two
           std::vector<Tile> tiles(n);
-          for (int m = 0; m < n; ++m) tiles[m] = {kind == 0 ? 1 + (int)(gen() % 32) : kind == 1 ? 256 : 1 + (int)(gen() % 256), m};
-          int e = check([&](int b, auto tile, auto f) { mp::short_row_blocks<32>(b, grid, 8, n, n_tiles_n, tile, f); }, grid,
-                        n_tiles_n, tiles, kind == 0);
+          const int blocks = kind < 3 ? 1 : 2;
+          for (int m = 0; m < n; ++m) tiles[m] = {kind == 0 ? 1 + (int)(gen() % 32) : kind == 1 ? 256 : kind == 2 ? 1 + (int)(gen() % 256) : kind == 3 ? 33 + (int)(gen() % 32) : 1 + (int)(gen() % 64), m};
+          int e = check([&](int b, auto tile, auto f) { mp::short_row_blocks<32>(b, grid, 8, n, n_tiles_n, blocks, tile, f); }, grid,
+                        n_tiles_n, tiles, kind == 0 || kind == 3, blocks);
+          if (!e && kind == 2)
+            e = check([&](int b, auto tile, auto f) { mp::short_row_blocks<32>(b, grid, 8, n, n_tiles_n, 2, tile, f); }, grid,
+                      n_tiles_n, tiles, false);
           if (!e)
             e = check([&](int b, auto tile, auto f) { mp::all_row_blocks<32, 8>(b, grid, 8, n, n_tiles_n, tile, f); }, grid,
                       n_tiles_n, tiles, kind == 1);
