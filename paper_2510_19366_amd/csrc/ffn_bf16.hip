@@ -456,7 +456,10 @@ __device__ __forceinline__ void run_items_ring(const Op& op, const MTile* __rest
   const int rounds = max(1, (total_items - total_items / DYN_DIV) / grid);
   const int n_static = min(total_items, rounds * grid);
   const int K = op.K(), nst = (K + BK - 1) / BK;
-  const int batch = nst >= 12 ? 1 : (12 + nst - 1) / nst;
+  // A batch from the pool: 12 stages, since a run's start costs a few, but no more than an even share (with 264 items of
+  // 5 stages on 256 workgroups, one took the last three: 3000 tokens, 66 sub-experts of 256 x 320, 8 picks, both GEMMs
+  // 73 us instead of 48).
+  const int batch = max(1, min((12 + nst - 1) / nst, (total_items - n_static + grid - 1) / grid));
   ItemRange ir = xcd_items(n_static);
   int n_my = ir.begin < ir.end ? (ir.end - ir.begin + ir.step - 1) / ir.step : 0;
   const uint32_t smem_base = lds_offset(smem);
