@@ -132,7 +132,8 @@ __device__ __forceinline__ void f32_items(const MTile* __restrict__ tiles, const
   };
   if constexpr (SHORT)
     short_row_blocks<F32_ROWS>(blockIdx.x, gridDim.x, N_XCD, hdr[HDR_MTILES], n_tiles_n,
-                               (T + F32_ROWS - 1) / F32_ROWS, tile, each);
+                               (T + F32_ROWS - 1) / F32_ROWS, tile, [](auto&& pred) { return lane_mask(pred); },
+                               each);
   else
     all_row_blocks<F32_ROWS, F32_BLOCKS>(blockIdx.x, gridDim.x, N_XCD, hdr[HDR_MTILES], n_tiles_n, tile, each);
 }

@@ -883,7 +883,8 @@ __global__ __launch_bounds__(FP_THREADS) void ffn_few_kernel(Op op, const MTile*
   const int K = op.K(), ns = (K + BK - 1) / BK;
   const uint32_t lds0 = lds_offset(fp_smem), dst0 = lds0 + (uint32_t)(wv * FP_CP) * 1024u;
   short_row_blocks<FP_M>(blockIdx.x, gridDim.x, N_XCD, hdr[HDR_MTILES], n_tiles_n, blocks,
-                         [&](int m) { return tiles[m]; }, [&](const MTile& t, int blk, int nt) {
+                         [&](int m) { return tiles[m]; }, [](auto&& pred) { return lane_mask(pred); },
+                         [&](const MTile& t, int blk, int nt) {
     Sc sc;
     sc.g = uni(t.g);
     sc.row0 = uni(t.row0) + blk * FP_M;
@@ -1001,11 +1002,11 @@ static hipError_t launch_op(const Op& op, int T, int K, int n_cols, bool few, in
 
 // At most 64 tokens (a group is then one or two row blocks; more would read the weights again for
 // each), and the ring kernel's n-tiles of all sub-experts that they can touch are at most 1.5 per CU, or 3 where
-// Is <= 192.  Both GEMMs between HIP events, d = 2048, one pair per touched sub-expert, small tiles | what takes 65
-// tokens.  Is = 192 (fused): 20 sub-experts 20 | 78 us, 100 49 | 82, 200 97 | 113, 384 169 | 216.  Is = 32: 100 26 | 44,
-// 768 108 | 137; 96: 768 205 | 215; 160: 384 160 | 185; 352: 32 32 | 49, 128 111 | 145; 704: 16 32 | 49, 64 111 | 145.
-// All pairs of 64 tokens on 8 sub-experts of 704, 32 rows each: 36 | 50; on 4 of 3584: 69 | 83.  So they are ahead as
-// far as the rule goes; beyond it the work is that of the weights' bytes, whichever tiles read them.
+// Is <= 192.  Both GEMMs between HIP events, d = 2048, 64 tokens, one pair per touched sub-expert, small tiles | what
+// takes 65 tokens.  Is = 192 (fused): 20 sub-experts 25 | 79 us, 100 54 | 82, 200 100 | 113, 384 172 | 215.  Is = 32: 100
+// 28 | 45, 768 114 | 135; 96: 768 200 | 215; 160: 384 161 | 184; 352: 32 34 | 49, 128 112 | 140; 704: 16 33 | 50, 64 113 | 137.
+// All pairs on 8 sub-experts of 704, 32 rows each: 29 | 50; on 4 of 3584: 57 | 83.  So they are ahead as far as the
+// rule goes; beyond it the work is that of the weights' bytes, whichever tiles read them.
 bool ffn_few_pairs(int T, int k_max, int E, int Is) {
   const long pairs = (long)T * k_max, groups = pairs < E ? pairs : E;
   return T <= 64 && groups * cdiv(Is, BN / 2) * 2 <= 3L * num_cus() * (Is <= 192 ? 2 : 1);

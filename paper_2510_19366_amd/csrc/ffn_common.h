@@ -36,6 +36,12 @@ __device__ __forceinline__ float silu_mul(float a, float u) {
   return (c == c ? c : q) * u;
 }
 
+// bit l: pred(l), in every lane
+template <class P>
+__device__ __forceinline__ uint64_t lane_mask(P&& pred) {
+  return __ballot(pred((int)(threadIdx.x & 63)));
+}
+
 inline int persistent_grid(long max_items, int per_cu) {  // a multiple of N_XCD
   long g = (long)num_cus() * per_cu;
   if (g > max_items) g = max_items;

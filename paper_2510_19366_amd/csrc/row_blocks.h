@@ -11,20 +11,35 @@ namespace mp {
 // b % n_xcd, and an XCD a contiguous part of the list, in which a sub-expert's weights meet).
 
 // For m-tiles of at most `blocks` row blocks (longer ones take longer): the list holds the first row block of every
-// (m-tile, n-tile) pair, all of which exist, then the second ones, of which few do or all.  A list of every possible row block is
-// mostly empty there, and brings those that exist to the same few workgroups whenever the stride grid / n_xcd has a
-// factor in common with row blocks x n-tiles: one row in each of 32 groups, 4 n-tiles, 8 row blocks, 512
-// workgroups: 128 tiles on 64 of them; 20 groups, 32 n-tiles: 640 tiles on 256.
-template <int ROWS, class Tile, class F>
-MP_HD void short_row_blocks(int b, int grid, int n_xcd, int n_mtiles, int n_tiles_n, int blocks, Tile&& tile, F&& f) {
+// (m-tile, n-tile) pair, all of which exist, then the second ones, of which few do or all.  A list of every possible
+// row block is mostly empty there, and brings those that exist to the same few workgroups whenever the stride
+// grid / n_xcd has a factor in common with row blocks x n-tiles: one row in each of 32 groups, 4 n-tiles, 8 row
+// blocks, 512 workgroups: 128 tiles on 64 of them; 20 groups, 32 n-tiles: 640 tiles on 256.
+// mask(pred): bit l is pred(l), l = 0 .. 63 (a ballot), so that 64 pairs without a second row block cost one look at
+// their headers (768 sub-experts of 96 with a row each, both GEMMs 200 us, with a look at every pair 225).
+template <int ROWS, class Tile, class Mask, class F>
+MP_HD void short_row_blocks(int b, int grid, int n_xcd, int n_mtiles, int n_tiles_n, int blocks, Tile&& tile,
+                            Mask&& mask, F&& f) {
   const int xcd = b % n_xcd, total = n_mtiles * n_tiles_n, chunk = (total + n_xcd - 1) / n_xcd;
-  const int end = total < (xcd + 1) * chunk ? total : (xcd + 1) * chunk;
-  const int n = end - xcd * chunk;  // the XCD's pairs
-  for (int i = b / n_xcd; i < n * blocks; i += grid / n_xcd) {
-    const int item = xcd * chunk + i % n, first = i / n, last = first == blocks - 1 ? INT32_MAX / ROWS : first;
-    const auto t = tile(item / n_tiles_n);
-    for (int blk = first; blk <= last && blk * ROWS < t.rows; ++blk) f(t, blk, item % n_tiles_n);
+  const int begin = xcd * chunk, n = (total < begin + chunk ? total : begin + chunk) - begin;  // the XCD's pairs
+  const int slot = b / n_xcd, step = grid / n_xcd;
+  for (int i = slot; i < n; i += step) {
+    const auto t = tile((begin + i) / n_tiles_n);
+    for (int blk = 0; blk * ROWS < (blocks > 1 ? 1 : t.rows); ++blk) f(t, blk, (begin + i) % n_tiles_n);
   }
+  for (int first = 1; first < blocks; ++first)  // the list goes on: start where the workgroups before this one stopped
+    for (int i0 = ((slot - first * n) % step + step) % step; i0 < n; i0 += 64 * step) {
+      uint64_t on = mask([&](int l) {
+        const int i = i0 + l * step;
+        return i < n && tile((begin + i) / n_tiles_n).rows > first * ROWS;
+      });
+      for (; on != 0; on &= on - 1) {
+        const int i = i0 + __builtin_ctzll(on) * step;
+        const auto t = tile((begin + i) / n_tiles_n);
+        for (int blk = first; blk * ROWS < (first < blocks - 1 ? first * ROWS + 1 : t.rows); ++blk)
+          f(t, blk, (begin + i) % n_tiles_n);
+      }
+    }
 }
 
 // For m-tiles of any length: the list (m-tile, row block of BLOCKS, n-tile).  What runs at the same time shares weights.

@@ -12,6 +12,12 @@ struct Tile {
   int rows, m;
 };
 
+auto mask = [](auto&& pred) {
+  uint64_t m = 0;
+  for (int l = 0; l < 64; ++l) m |= (uint64_t)(pred(l) ? 1 : 0) << l;
+  return m;
+};
+
 template <class Deal>
 int check(Deal&& deal, int grid, int n_tiles_n, const std::vector<Tile>& tiles, bool even,
           int blocks = 1) {
@@ -48,10 +54,10 @@ int main() {
           std::vector<Tile> tiles(n);
           const int blocks = kind < 3 ? 1 : 2;
           for (int m = 0; m < n; ++m) tiles[m] = {kind == 0 ? 1 + (int)(gen() % 32) : kind == 1 ? 256 : kind == 2 ? 1 + (int)(gen() % 256) : kind == 3 ? 33 + (int)(gen() % 32) : 1 + (int)(gen() % 64), m};
-          int e = check([&](int b, auto tile, auto f) { mp::short_row_blocks<32>(b, grid, 8, n, n_tiles_n, blocks, tile, f); }, grid,
+          int e = check([&](int b, auto tile, auto f) { mp::short_row_blocks<32>(b, grid, 8, n, n_tiles_n, blocks, tile, mask, f); }, grid,
                         n_tiles_n, tiles, kind == 0 || kind == 3, blocks);
           if (!e && kind == 2)
-            e = check([&](int b, auto tile, auto f) { mp::short_row_blocks<32>(b, grid, 8, n, n_tiles_n, 2, tile, f); }, grid,
+            e = check([&](int b, auto tile, auto f) { mp::short_row_blocks<32>(b, grid, 8, n, n_tiles_n, 2, tile, mask, f); }, grid,
                       n_tiles_n, tiles, false);
           if (!e)
             e = check([&](int b, auto tile, auto f) { mp::all_row_blocks<32, 8>(b, grid, 8, n, n_tiles_n, tile, f); }, grid,
