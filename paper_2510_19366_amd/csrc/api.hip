@@ -146,7 +146,7 @@ static int do_route(const moe_prism_shape* s, const Layout& L, const void* x, co
 static int do_dispatch_over(const Layout& L, const int32_t* ids, int32_t* cnt, int32_t* off,
                             int32_t* sorted_pair, int32_t* slot_of_pair, int32_t* chunk, int32_t* hdr,
                             MTile* tiles, int T, int E, int k_max, hipStream_t st) {
-  if (dispatch_is_small(T, E)) {
+  if (dispatch_is_small(T, E, k_max)) {
     MP_LAUNCH(MOE_PRISM_K_DISPATCH_PLACE, launch_dispatch_small(ids, cnt, off, hdr, sorted_pair, slot_of_pair,
                                                                 tiles, L.max_mtiles, T, E, k_max, st));
     return MOE_PRISM_OK;
@@ -265,7 +265,7 @@ static int do_route_proxy(const moe_prism_shape* s, const Layout& L, const void*
   MP_LAUNCH(MOE_PRISM_K_LOGITS,
             launch_logits(s->dtype, x, w_router0, bias0, logits0, hdr, s->T, s->d, N, st));
   const SmallDispatch small{q.cnt0, q.off0, q.sp0, q.sl0, tiles, L.max_mtiles};
-  const bool one = dispatch_is_small(s->T, N);
+  const bool one = dispatch_is_small(s->T, N, m);
   MP_LAUNCH(MOE_PRISM_K_TOPK, launch_topk(logits0, nullptr, q.ids0, q.w0, hdr, s->T, N, m,
                                           s->renormalize, s->routed_scale, one ? &small : nullptr, st));
   if (!one) {
@@ -430,7 +430,7 @@ static int layer_on(const moe_prism_shape* shape, const Layout& L, const void* x
   void* y = w8 + L.y;
   // a small batch is dispatched by the top-k kernel itself
   const SmallDispatch small{cnt, off, sp, sl, reinterpret_cast<MTile*>(w8 + L.tiles), L.max_mtiles};
-  const bool one = dispatch_is_small(shape->T, shape->n_experts * shape->n_sub);
+  const bool one = dispatch_is_small(shape->T, shape->n_experts * shape->n_sub, shape->k_max);
   int rc = do_route(shape, L, x, w_router, router_bias, k_tok, ids, w,
                     reinterpret_cast<float*>(w8 + L.logits), w8, st, one ? &small : nullptr);
   if (rc) return rc;

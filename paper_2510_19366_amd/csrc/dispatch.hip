@@ -140,7 +140,7 @@ hipError_t launch_dispatch_small(const int32_t* ids, int32_t* cnt, int32_t* off,
   return hipGetLastError();
 }
 
-bool dispatch_is_small(int T, int E) { return small_dispatch(T, E); }
+bool dispatch_is_small(int T, int E, int k_max) { return small_dispatch(T, E, k_max); }
 
 hipError_t launch_dispatch_count(const int32_t* ids, int32_t* chunk_cnt, int T, int E, int k_max,
                                  hipStream_t s) {

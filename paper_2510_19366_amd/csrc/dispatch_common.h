@@ -140,15 +140,22 @@ __device__ __forceinline__ void place_pairs(const int32_t* __restrict__ ids, con
 }
 
 // ---------------------------------------------------------------- a small batch in one workgroup
-// Up to 255 tokens (four 64-token words of mask) whose masks and prefixes fit the default 64 KiB of
-// LDS: the three launches of the general path cost more than their work there.
+// Up to 64 tokens, or more with few pairs, whose masks and prefixes fit the default 64 KiB of LDS: the three launches
+// of the general path cost more than their work there.  One workgroup places the pairs of all tokens by itself, and
+// from a second 64-token word of mask on the general path has a workgroup for each.  Calls of d = 64, Is = 32, 512
+// sub-experts from a captured graph, one workgroup | three launches: 40 tokens of 8 picks 26.2 | 30.3 us, 64 of 64
+// 50.8 | 59.2; 100 of 8 34.4 | 35.3, of 24 42.3 | 42.5, of 64 62.3 | 61.1; 160 of 4 32.7 | 31.6, of 32 54.4 | 46.1;
+// 255 of 32 67.1 | 47.8 (32 to 1024 sub-experts alike).  Budgets below k_max leave fewer pairs than T k_max: 79
+// tokens of up to 20, half of them on average, 36.5 | 39.2; 155 of up to 1, 39.5 | 40.7.
 struct SmallDispatch {
   int32_t *cnt, *off, *sorted_pair, *slot_of_pair;
   MTile* tiles;  // nullptr: no m-tile table
   int max_tiles;
 };
 __host__ __device__ inline size_t small_dispatch_lds(int T, int E) { return (size_t)E * ((T + 63) / 64) * 8 + 2 * ((size_t)E + 1) * 4; }
-inline bool small_dispatch(int T, int E) { return T > 0 && T < 256 && small_dispatch_lds(T, E) <= 60 * 1024; }
+inline bool small_dispatch(int T, int E, int k_max) {
+  return T > 0 && (T <= 64 || (T < 256 && T * k_max <= (T <= 128 ? 4096 : 320))) && small_dispatch_lds(T, E) <= 60 * 1024;
+}
 
 __device__ __forceinline__ void dispatch_one_workgroup(const int32_t* __restrict__ ids, const SmallDispatch& a,
                                                        int32_t* __restrict__ hdr, u64* lds,

@@ -46,7 +46,7 @@ hipError_t launch_proxy_select(int dtype, const void* act, int act_ld, const int
                                const int32_t* kappa, int32_t* ids, float* w, int32_t* hdr, int T,
                                int S, int r, int m, int k_max, hipStream_t s);
 hipError_t launch_dispatch_scan(int32_t* chunk_cnt, int32_t* cnt, int T, int E, hipStream_t s);
-bool dispatch_is_small(int T, int E);  // the whole stage in one workgroup (launch_dispatch_small)
+bool dispatch_is_small(int T, int E, int k_max);  // the whole stage in one workgroup (launch_dispatch_small)
 hipError_t launch_dispatch_small(const int32_t* ids, int32_t* cnt, int32_t* off, int32_t* hdr,
                                  int32_t* sorted_pair, int32_t* slot_of_pair, MTile* tiles,
                                  int max_tiles, int T, int E, int k_max, hipStream_t s);

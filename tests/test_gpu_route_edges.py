@@ -1,5 +1,5 @@
 """Top-k by threshold search and the one-workgroup dispatch of small batches, at the sizes where
-they change over: mask words of 64 tokens, the 256-token limit, the LDS limit, budgets around one
+they change over: mask words of 64 tokens, the token and pair limits, the LDS limit, budgets around one
 wave's 64 lanes, and logits with many equal values at the border of the budget."""
 import numpy as np
 import pytest
@@ -13,8 +13,9 @@ from gpu_util import max_rel, run_layer, run_stages, to_np
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T,E,k_max", [(1, 512, 32), (64, 40, 5), (65, 40, 5), (255, 64, 9), (256, 64, 9),
-                                       (255, 1500, 7), (255, 1530, 7), (130, 2100, 66)])
+@pytest.mark.parametrize("T,E,k_max", [(1, 512, 32), (64, 40, 5), (65, 40, 5), (128, 64, 32), (128, 64, 33), (129, 64, 2),
+                                       (129, 64, 3), (255, 64, 9),
+                                       (255, 1500, 1), (255, 1530, 1), (130, 2100, 66)])
 def test_small_batches_match_the_oracle(T, E, k_max):
     k = np.random.default_rng(T).integers(0, k_max + 1, size=T).astype(np.int32)
     wl = W.make_workload("small", dtype="bf16", d=64, n_experts=E // 2, n_sub=2, inter_sub=32,
