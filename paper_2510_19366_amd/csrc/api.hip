@@ -142,10 +142,26 @@ static int do_route(const moe_prism_shape* s, const Layout& L, const void* x, co
   return MOE_PRISM_OK;
 }
 
+// The fused gate-up/SwiGLU/down kernel serves bf16 layers with narrow sub-experts (but for a handful of
+// pairs, see ffn_few_pairs); the
+// environment variable MOE_PRISM_FFN=split forces the two-kernel path (for A/B measurements
+// and so that tests reach both paths on the same shapes).
+static bool use_fused_ffn(const moe_prism_shape* s) {
+  if (s->dtype != MOE_PRISM_BF16 || !ffn_fused_supported(s->T, s->d, s->inter_sub)) return false;
+  const char* e = getenv("MOE_PRISM_FFN");
+  return !(e != nullptr && strcmp(e, "split") == 0);
+}
+// the small tiles for a handful of pairs (bf16)
+static bool use_few(const moe_prism_shape* s) {
+  return s->dtype == MOE_PRISM_BF16 && ffn_few_pairs(s->T, s->k_max, s->n_experts * s->n_sub, s->inter_sub);
+}
+// m-tiles of even length (see mtile_rows) where the two-kernel path follows
+static bool even_tiles(const moe_prism_shape* s) { return use_few(s) || !use_fused_ffn(s); }
+
 // the dispatch of T tokens with up to k_max picks out of E groups
 static int do_dispatch_over(const Layout& L, const int32_t* ids, int32_t* cnt, int32_t* off,
                             int32_t* sorted_pair, int32_t* slot_of_pair, int32_t* chunk, int32_t* hdr,
-                            MTile* tiles, int T, int E, int k_max, hipStream_t st) {
+                            MTile* tiles, bool even, int T, int E, int k_max, hipStream_t st) {
   if (dispatch_is_small(T, E, k_max)) {
     MP_LAUNCH(MOE_PRISM_K_DISPATCH_PLACE, launch_dispatch_small(ids, cnt, off, hdr, sorted_pair, slot_of_pair,
                                                                 tiles, L.max_mtiles, T, E, k_max, st));
@@ -154,8 +170,8 @@ static int do_dispatch_over(const Layout& L, const int32_t* ids, int32_t* cnt, i
   MP_LAUNCH(MOE_PRISM_K_DISPATCH_COUNT, launch_dispatch_count(ids, chunk, T, E, k_max, st));
   MP_LAUNCH(MOE_PRISM_K_DISPATCH_SCAN, launch_dispatch_scan(chunk, cnt, T, E, st));
   MP_LAUNCH(MOE_PRISM_K_DISPATCH_PLACE,
-            launch_dispatch_place(ids, chunk, cnt, off, hdr, sorted_pair, slot_of_pair, tiles, L.max_mtiles, T, E,
-                                  k_max, st));
+            launch_dispatch_place(ids, chunk, cnt, off, hdr, sorted_pair, slot_of_pair, tiles, L.max_mtiles, even,
+                                  T, E, k_max, st));
   return MOE_PRISM_OK;
 }
 
@@ -168,17 +184,8 @@ static int do_dispatch(const moe_prism_shape* s, const Layout& L, const int32_t*
   int32_t* hdr = reinterpret_cast<int32_t*>(ws + L.hdr);
   int32_t* chunk = reinterpret_cast<int32_t*>(ws + L.chunk_cnt);
   MTile* tiles = with_tiles ? reinterpret_cast<MTile*>(ws + L.tiles) : nullptr;
-  return do_dispatch_over(L, ids, cnt, off, sorted_pair, slot_of_pair, chunk, hdr, tiles, s->T, E, s->k_max, st);
-}
-
-// The fused gate-up/SwiGLU/down kernel serves bf16 layers with narrow sub-experts (but for a handful of
-// pairs, see ffn_few_pairs); the
-// environment variable MOE_PRISM_FFN=split forces the two-kernel path (for A/B measurements
-// and so that tests reach both paths on the same shapes).
-static bool use_fused_ffn(const moe_prism_shape* s) {
-  if (s->dtype != MOE_PRISM_BF16 || !ffn_fused_supported(s->T, s->d, s->inter_sub)) return false;
-  const char* e = getenv("MOE_PRISM_FFN");
-  return !(e != nullptr && strcmp(e, "split") == 0);
+  return do_dispatch_over(L, ids, cnt, off, sorted_pair, slot_of_pair, chunk, hdr, tiles, even_tiles(s), s->T,
+                          E, s->k_max, st);
 }
 
 static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, const void* w_gu,
@@ -189,7 +196,8 @@ static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, cons
   MTile* tiles = reinterpret_cast<MTile*>(ws + L.tiles);
   void* h = ws + L.h;
   if (!tiles_built)
-    MP_LAUNCH(MOE_PRISM_K_FFN_TILES, launch_ffn_tiles(off, tiles, hdr, E, L.max_mtiles, s->T * s->k_max, st));
+    MP_LAUNCH(MOE_PRISM_K_FFN_TILES, launch_ffn_tiles(off, tiles, hdr, E, L.max_mtiles, !traffic_probe && even_tiles(s),
+                                                      s->T * s->k_max, st));
   if (s->T == 0) return MOE_PRISM_OK;
   if (traffic_probe) {
     MP_LAUNCH(MOE_PRISM_K_FFN_TRAFFIC,
@@ -199,7 +207,7 @@ static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, cons
                                             L.max_mtiles, st));
     return MOE_PRISM_OK;
   }
-  const bool few = s->dtype == MOE_PRISM_BF16 && ffn_few_pairs(s->T, s->k_max, E, s->inter_sub);
+  const bool few = use_few(s);
   if (use_fused_ffn(s) && !few) {
     MP_LAUNCH(MOE_PRISM_K_FFN_FUSED,
               launch_ffn_fused_bf16((const uint16_t*)x, (const uint16_t*)w_gu, (const uint16_t*)w_dn,
@@ -269,7 +277,8 @@ static int do_route_proxy(const moe_prism_shape* s, const Layout& L, const void*
   MP_LAUNCH(MOE_PRISM_K_TOPK, launch_topk(logits0, nullptr, q.ids0, q.w0, hdr, s->T, N, m,
                                           s->renormalize, s->routed_scale, one ? &small : nullptr, st));
   if (!one) {
-    const int rc = do_dispatch_over(L, q.ids0, q.cnt0, q.off0, q.sp0, q.sl0, chunk, hdr, tiles, s->T, N, m, st);
+    const int rc = do_dispatch_over(L, q.ids0, q.cnt0, q.off0, q.sp0, q.sl0, chunk, hdr, tiles, true, s->T,
+                                    N, m, st);
     if (rc) return rc;
   }
   if (s->T == 0) return MOE_PRISM_OK;

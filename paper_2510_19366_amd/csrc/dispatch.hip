@@ -107,7 +107,7 @@ __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_place_kernel(
     const int32_t* __restrict__ ids, const int32_t* __restrict__ chunk_base,
     const int32_t* __restrict__ cnt, int32_t* __restrict__ off, int32_t* __restrict__ hdr,
     int32_t* __restrict__ sorted_pair, int32_t* __restrict__ slot_of_pair,
-    MTile* __restrict__ tiles, int max_tiles, int T, int E, int W, int k_max) {
+    MTile* __restrict__ tiles, int max_tiles, int even, int T, int E, int W, int k_max) {
   extern __shared__ u64 masks[];  // E * W masks, then E + 1 offsets, then E + 1 first-tile indices
   __shared__ int32_t wave_tot[4][2];
   int32_t* off_lds = reinterpret_cast<int32_t*>(masks + (size_t)E * W);
@@ -117,7 +117,8 @@ __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_place_kernel(
   group_offsets([&](int g) { return cnt[g]; }, off_lds, first_lds, wave_tot, E);
   if (c == 0) write_offsets(off_lds, first_lds, off, hdr, tiles != nullptr, max_tiles, E);
   if (tiles != nullptr)
-    write_tiles(off_lds, first_lds, tiles, max_tiles, E, c * DISPATCH_THREADS + threadIdx.x, gridDim.x * DISPATCH_THREADS);
+    write_tiles(off_lds, first_lds, tiles, max_tiles, even != 0, E, c * DISPATCH_THREADS + threadIdx.x,
+                gridDim.x * DISPATCH_THREADS);
   build_masks(ids, masks, t0, ntok, E, W, k_max);
   place_pairs(ids, masks, [&](int g) { return off_lds[g] + chunk_base[(size_t)c * E + g]; }, sorted_pair,
               slot_of_pair, t0, ntok, off_lds[E], E, W, k_max);
@@ -160,8 +161,8 @@ hipError_t launch_dispatch_scan(int32_t* chunk_cnt, int32_t* cnt, int T, int E, 
 
 hipError_t launch_dispatch_place(const int32_t* ids, const int32_t* chunk_base, const int32_t* cnt,
                                  int32_t* off, int32_t* hdr, int32_t* sorted_pair,
-                                 int32_t* slot_of_pair, MTile* tiles, int max_tiles, int T, int E,
-                                 int k_max, hipStream_t s) {
+                                 int32_t* slot_of_pair, MTile* tiles, int max_tiles, bool even_tiles, int T,
+                                 int E, int k_max, hipStream_t s) {
   int W = dispatch_chunk_words(E, T);
   int nch = cdiv(T, 64 * W);
   if (nch < 1) nch = 1;  // T == 0: one workgroup still writes the (all-zero) offsets
@@ -170,7 +171,7 @@ hipError_t launch_dispatch_place(const int32_t* ids, const int32_t* chunk_base, 
   hipError_t e = raise_lds_limit<dispatch_place_kernel>(100 * 1024);
   if (e != hipSuccess) return e;
   dispatch_place_kernel<<<nch, DISPATCH_THREADS, lds, s>>>(ids, chunk_base, cnt, off, hdr, sorted_pair,
-                                              slot_of_pair, tiles, max_tiles, T, E, W, k_max);
+                                              slot_of_pair, tiles, max_tiles, even_tiles, T, E, W, k_max);
   return hipGetLastError();
 }
 

@@ -95,8 +95,8 @@ __device__ __forceinline__ void write_offsets(const int32_t* off_lds, const int3
 // one-tile groups costs one round and not one per group (512 groups and one workgroup: 43-67 -> 7 us
 // for the whole kernel).
 __device__ __forceinline__ void write_tiles(const int32_t* off_lds, const int32_t* first_lds,
-                                            MTile* __restrict__ tiles, int max_tiles, int E, int start,
-                                            int step) {
+                                            MTile* __restrict__ tiles, int max_tiles, bool even, int E,
+                                            int start, int step) {
   const int n_tiles = min(first_lds[E], max_tiles);
   for (int i = start; i < n_tiles; i += step) {
     int lo = 0, hi = E;  // first_lds[lo] <= i < first_lds[hi]
@@ -104,11 +104,12 @@ __device__ __forceinline__ void write_tiles(const int32_t* off_lds, const int32_
       const int m = (lo + hi) >> 1;
       if (first_lds[m] <= i) lo = m; else hi = m;
     }
-    const int first = first_lds[lo], row = (i - first) * FFN_BM;
+    const int n = off_lds[lo + 1] - off_lds[lo], per = mtile_rows(n, FFN_BM, even);
+    const int first = first_lds[lo], row = (i - first) * per;
     MTile t;
     t.g = lo;
     t.row0 = off_lds[lo] + row;
-    t.rows = min(FFN_BM, off_lds[lo + 1] - off_lds[lo] - row);
+    t.rows = min(per, n - row);
     t.first = first;
     t.count = min(first_lds[lo + 1] - first, max_tiles - first);
     t.pad[0] = t.pad[1] = t.pad[2] = 0;
@@ -173,7 +174,7 @@ __device__ __forceinline__ void dispatch_one_workgroup(const int32_t* __restrict
   group_offsets(count, off_lds, first_lds, wave_tot, E);
   for (int g = threadIdx.x; g < E; g += blockDim.x) a.cnt[g] = off_lds[g + 1] - off_lds[g];
   write_offsets(off_lds, first_lds, a.off, hdr, a.tiles != nullptr, a.max_tiles, E);
-  if (a.tiles != nullptr) write_tiles(off_lds, first_lds, a.tiles, a.max_tiles, E, threadIdx.x, blockDim.x);
+  if (a.tiles != nullptr) write_tiles(off_lds, first_lds, a.tiles, a.max_tiles, false, E, threadIdx.x, blockDim.x);
   place_pairs(ids, masks, [&](int g) { return off_lds[g]; }, a.sorted_pair, a.slot_of_pair, 0, T, off_lds[E], E,
               W, k_max);
 }

@@ -1,6 +1,6 @@
 // Grouped SwiGLU FFN over ragged per-sub-expert groups (Sec. 3.2.1, Eq. 1-3).
 //
-// The slot list is cut into m-tiles of FFN_BM rows that never straddle a
+// The slot list is cut into m-tiles of up to FFN_BM rows that never straddle a
 // group (ffn_tiles_kernel, on the device, from group_offset), and persistent
 // workgroups walk (m-tile, n-tile) work items round-robin.  Two GEMMs:
 //   gate-up : h[p, c] = SiLU(x[t_p,:] . Wg[g,c,:]) * (x[t_p,:] . Wu[g,c,:])
@@ -40,7 +40,7 @@ __device__ __forceinline__ int block_scan(int v, int32_t* wave_tot, int* total) 
 __global__ __launch_bounds__(TILES_THREADS) void ffn_tiles_kernel(const int32_t* __restrict__ off,
                                                                   MTile* __restrict__ tiles,
                                                                   int32_t* __restrict__ hdr, int E,
-                                                                  int max_tiles, int n_rows) {
+                                                                  int max_tiles, int even, int n_rows) {
   __shared__ int32_t wave_tot[TILES_THREADS / 64];
   const int tid = threadIdx.x;
   int carry = 0;  // tiles of the groups before this round (the same in every thread)
@@ -55,11 +55,12 @@ __global__ __launch_bounds__(TILES_THREADS) void ffn_tiles_kernel(const int32_t*
     const int nt = (n + FFN_BM - 1) / FFN_BM;
     int round_total = 0;
     const int first = carry + block_scan(nt, wave_tot, &round_total);
+    const int per = mtile_rows(n, FFN_BM, even != 0);
     for (int i = 0; i < nt; ++i) {
       MTile t;
       t.g = g;
-      t.row0 = lo + i * FFN_BM;
-      t.rows = min(FFN_BM, n - i * FFN_BM);
+      t.row0 = lo + i * per;
+      t.rows = min(per, n - i * per);
       t.first = first;
       t.count = min(nt, max_tiles - first);  // never points past the table
       t.pad[0] = t.pad[1] = t.pad[2] = 0;
@@ -80,8 +81,8 @@ __global__ __launch_bounds__(TILES_THREADS) void ffn_tiles_kernel(const int32_t*
 }
 
 hipError_t launch_ffn_tiles(const int32_t* off, MTile* tiles, int32_t* hdr, int E, int max_tiles,
-                            int n_rows, hipStream_t s) {
-  ffn_tiles_kernel<<<1, TILES_THREADS, 0, s>>>(off, tiles, hdr, E, max_tiles, n_rows);
+                            bool even_tiles, int n_rows, hipStream_t s) {
+  ffn_tiles_kernel<<<1, TILES_THREADS, 0, s>>>(off, tiles, hdr, E, max_tiles, even_tiles, n_rows);
   return hipGetLastError();
 }
 

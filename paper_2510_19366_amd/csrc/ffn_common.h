@@ -1,7 +1,6 @@
 // Shared by the grouped-FFN kernel files: persistent work distribution.
 #pragma once
 #include "kernels.h"
-#include "row_blocks.h"
 
 namespace mp {
 

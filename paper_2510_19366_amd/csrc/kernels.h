@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "row_blocks.h"
+
 namespace mp {
 
 // Workspace header: int32 words at the start of ws.
@@ -54,12 +56,12 @@ hipError_t launch_dispatch_small(const int32_t* ids, int32_t* cnt, int32_t* off,
 // FFN's m-tile table and its header words (what launch_ffn_tiles builds from off[])
 hipError_t launch_dispatch_place(const int32_t* ids, const int32_t* chunk_base, const int32_t* cnt,
                                  int32_t* off, int32_t* hdr, int32_t* sorted_pair,
-                                 int32_t* slot_of_pair, MTile* tiles, int max_tiles, int T, int E,
-                                 int k_max, hipStream_t s);
+                                 int32_t* slot_of_pair, MTile* tiles, int max_tiles, bool even_tiles, int T,
+                                 int E, int k_max, hipStream_t s);
 
 // grouped FFN
 hipError_t launch_ffn_tiles(const int32_t* off, MTile* tiles, int32_t* hdr, int E, int max_tiles,
-                            int n_rows, hipStream_t s);
+                            bool even_tiles, int n_rows, hipStream_t s);
 hipError_t launch_ffn_gate_up(int dtype, const void* x, const void* w_gu, const int32_t* sorted_pair,
                               const MTile* tiles, int32_t* hdr, void* h, int T, int d, int Is,
                               int k_max, bool few, int max_mtiles, hipStream_t s);

@@ -6,6 +6,17 @@
 
 namespace mp {
 
+// Rows of each m-tile that a group of n rows is cut into (the last one takes what is left); the number of tiles is
+// that of tiles of `most` rows.  `even`: about equal lengths, in steps of the 64 rows that the two-kernel FFN's time
+// goes in.  Its tiles share their sub-expert's weights through L2 only while they run in step: cut into 256 + 96 rows,
+// 256 sub-experts of 352 x 2048 with some 350 rows each fetched every weight twice (gate-up 1.81 GB), cut into
+// 192 + 160 once (1.27 GB; FFN 506 -> 485 us; 4500 tokens of 20 picks out of 256 x 256 364 -> 342, 2200 of 5 out of
+// 32 x 3584 1072 -> 1006, nothing slower).  The fused kernel's time goes in steps of 128 rows and keeps full tiles.
+MP_HD int mtile_rows(int n, int most, bool even) {
+  const int nt = (n + most - 1) / most;
+  return even && nt > 1 ? ((n + nt - 1) / nt + 63) / 64 * 64 : most;
+}
+
 // An m-tile of `rows` slot rows is cut into row blocks of ROWS, and each of those into n_tiles_n n-tiles.
 // f(m-tile, row block, n-tile) for the share of workgroup b out of `grid` (a multiple of n_xcd; b serves XCD
 // b % n_xcd, and an XCD a contiguous part of the list, in which a sub-expert's weights meet).

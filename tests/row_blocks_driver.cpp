@@ -45,8 +45,26 @@ int check(Deal&& deal, int grid, int n_tiles_n, const std::vector<Tile>& tiles, 
   return even && most > (share + per - 1) / per ? 5 : 0;
 }
 
+// the m-tiles of a group: as few as possible, none empty or too long, none left over; even ones differ by less
+// than a step of 64 rows per tile before the last
+static int check_rows(int n, int most) {
+  const int nt = (n + most - 1) / most;
+  for (bool even : {false, true}) {
+    const int per = mp::mtile_rows(n, most, even);
+    if (per > most || (nt > 1 && (per % 64 != 0 || (nt - 1) * per >= n)) || (long)nt * per < n) return 1;
+    if (even && nt > 1 && per - (n + nt - 1) / nt >= 64) return 2;
+    if (!even && per != most) return 3;
+  }
+  return 0;
+}
+
 int main() {
   std::mt19937 gen(3);
+  for (int n = 0; n < 5000; ++n)
+    if (const int e = check_rows(n, 256)) {
+      printf("m-tiles of %d rows: %d\n", n, e);
+      return e;
+    }
   for (int grid : {8, 64, 512})
     for (int n_tiles_n : {1, 2, 4, 6, 11, 22, 32})
       for (int n : {0, 1, 5, 20, 32, 250, 500})

@@ -10,6 +10,7 @@ from paper_2510_19366_amd import binding as B
 pytestmark = pytest.mark.gpu
 
 SIZES = [257, 1, 0, 31, 32, 33, 63, 64, 65, 0, 0, 127, 129, 191, 255, 256, 300, 2]
+LONG = [257, 320, 321, 352, 384, 385, 0, 448, 449, 511, 512, 513, 576, 577, 640, 769, 1025]
 FEW = [1, 0, 33, 0, 0, 30]
 
 
@@ -27,6 +28,7 @@ def ffn(dtype, x, w_gu, w_dn, group):
 
 @pytest.mark.parametrize("dtype,path,sizes,d,Is", [
     ("bf16", "auto", SIZES, 256, 256),    # two-kernel, shortest K of the ring driver
+    ("bf16", "auto", LONG, 256, 256),     # groups of several m-tiles, cut evenly
     ("bf16", "auto", SIZES, 448, 288),    # half K stage in the down GEMM; 32 neurons in the last gate-up tile
     ("bf16", "auto", SIZES, 576, 704),    # 64 columns in the last down tile, 64 neurons in the last gate-up tile
     ("bf16", "auto", SIZES, 192, 320),    # gate-up K too short for the ring
