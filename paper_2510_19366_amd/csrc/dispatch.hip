@@ -32,7 +32,8 @@ __global__ __launch_bounds__(256) void dispatch_count_kernel(const int32_t* __re
   extern __shared__ u64 masks[];
   const int c = blockIdx.x, t0 = c * 64 * W;
   const int ntok = min(64 * W, T - t0);
-  build_masks(ids, masks, t0, ntok, E, W, k_max);
+  Picks picks(ids + (size_t)t0 * k_max, ntok, k_max);
+  build_masks(picks, masks, E, W);
   for (int g = threadIdx.x; g < E; g += blockDim.x) {
     int n = 0;
     for (int w = 0; w < W; ++w) n += __popcll(masks[g * W + w]);
@@ -114,14 +115,16 @@ __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_place_kernel(
   int32_t* first_lds = off_lds + E + 1;
   const int c = blockIdx.x, t0 = c * 64 * W;
   const int ntok = max(min(64 * W, T - t0), 0);
+  Picks picks(ids + (size_t)t0 * k_max, ntok, k_max);
+  picks.load(0);  // on their way while the offsets are derived
   group_offsets([&](int g) { return cnt[g]; }, off_lds, first_lds, wave_tot, E);
   if (c == 0) write_offsets(off_lds, first_lds, off, hdr, tiles != nullptr, max_tiles, E);
   if (tiles != nullptr)
     write_tiles(off_lds, first_lds, tiles, max_tiles, even != 0, E, c * DISPATCH_THREADS + threadIdx.x,
                 gridDim.x * DISPATCH_THREADS);
-  build_masks(ids, masks, t0, ntok, E, W, k_max);
-  place_pairs(ids, masks, [&](int g) { return off_lds[g] + chunk_base[(size_t)c * E + g]; }, sorted_pair,
-              slot_of_pair, t0, ntok, off_lds[E], E, W, k_max);
+  build_masks(picks, masks, E, W);
+  place_pairs(picks, masks, [&](int g) { return off_lds[g] + chunk_base[(size_t)c * E + g]; }, sorted_pair,
+              slot_of_pair, (size_t)t0 * k_max, off_lds[E], E, W);
 }
 
 __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_small_kernel(const int32_t* __restrict__ ids,
@@ -129,7 +132,7 @@ __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_small_kernel(const 
                                                                           int32_t* __restrict__ hdr, int T,
                                                                           int E, int k_max) {
   extern __shared__ u64 masks[];
-  __shared__ int32_t wave_tot[4][2];
+  __shared__ int32_t wave_tot[DISPATCH_THREADS / 64];
   dispatch_one_workgroup(ids, a, hdr, masks, wave_tot, T, E, k_max);
 }
 

@@ -8,27 +8,73 @@ namespace mp {
 typedef unsigned long long u64;
 constexpr int DISPATCH_THREADS = 256;
 
-// masks[g * W + w]: which of tokens 64 w .. 64 w + 63 behind t0 picked g
-__device__ __forceinline__ void build_masks(const int32_t* __restrict__ ids, u64* masks, int t0,
-                                            int ntok, int E, int W, int k_max) {
-  for (int i = threadIdx.x; i < E * W; i += blockDim.x) masks[i] = 0ull;
-  __syncthreads();
-  const int n = ntok * k_max;
-  const int32_t* base = ids + (size_t)t0 * k_max;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    int g = base[i];
-    if (g >= 0 && g < E) {
-      int tl = i / k_max;
-      atomicOr(&masks[g * W + (tl >> 6)], 1ull << (tl & 63));
+// The picks of a run of tokens, PICKS per thread at a time, so that a memory latency is paid once per batch and not
+// once per pick; the last batch loaded stays in registers.
+constexpr int PICKS = 8;
+struct Picks {
+  const int32_t* ids;
+  int n, k_max;
+  uint32_t inv;  // i / k_max = umulhi(i, inv): i k_max < 2^32 (at most 65536 or 256 k_max picks of k_max <= 1024)
+  int at = -1, g[PICKS] = {};
+  __device__ __forceinline__ Picks(const int32_t* ids_, int ntok, int k) : ids(ids_), n(ntok * k), k_max(k), inv(0xffffffffu / (uint32_t)k + 1u) {}
+  __device__ __forceinline__ int token(int i) const { return k_max == 1 ? i : (int)__umulhi((uint32_t)i, inv); }
+  __device__ __forceinline__ void load(int first) {
+    if (at == first) return;
+    at = first;
+#pragma unroll
+    for (int u = 0; u < PICKS; ++u) {
+      const int i = first + u * DISPATCH_THREADS + (int)threadIdx.x;
+      if (first + u * DISPATCH_THREADS >= n) break;  // the same for all threads
+      g[u] = i < n ? ids[i] : -1;
     }
   }
+  // f(index, sub-expert) for every pick of this thread; last to first if `back`, so that a batch is used twice
+  template <class F>
+  __device__ __forceinline__ void each(bool back, F&& f) {
+    constexpr int STEP = PICKS * DISPATCH_THREADS;
+    const int batches = (n + STEP - 1) / STEP;
+    for (int b = 0; b < batches; ++b) {
+      const int first = (back ? batches - 1 - b : b) * STEP;
+      load(first);
+#pragma unroll
+      for (int u = 0; u < PICKS; ++u) {
+        const int i = first + u * DISPATCH_THREADS + (int)threadIdx.x;
+        if (first + u * DISPATCH_THREADS >= n) break;
+        if (i < n) f(i, g[u]);
+      }
+    }
+  }
+};
+
+// masks[g * W + w]: which of the run's tokens 64 w .. 64 w + 63 picked g
+__device__ __forceinline__ void build_masks(Picks& picks, u64* masks, int E, int W) {
+  picks.load(0);
+  for (int i = threadIdx.x; i < E * W; i += DISPATCH_THREADS) masks[i] = 0ull;
   __syncthreads();
+  picks.each(false, [&](int i, int g) {
+    if (g >= 0 && g < E) {
+      const int tl = picks.token(i);
+      atomicOr(&masks[g * W + (tl >> 6)], 1ull << (tl & 63));
+    }
+  });
+  __syncthreads();
+}
+
+// inclusive sum over the lanes of a wave: four steps inside the rows of 16 lanes, two across them
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15, into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31, into rows 2 and 3
+  return v;
 }
 
 // Exclusive prefixes over the groups by one workgroup of 256 threads, into LDS: off_lds[0..E]
 // of the row counts cnt(g) (off_lds[E] = P) and first_lds[0..E] of the m-tile counts
 // ceil(cnt(g) / FFN_BM) (first_lds[E] = number of m-tiles).  A thread sums a run of consecutive
-// groups, the 256 partial sums are scanned with shuffles, the run is walked again.
+// groups, the 256 partial sums are scanned, the run is walked again.
 template <class Cnt>
 __device__ __forceinline__ void group_offsets(Cnt cnt, int32_t* off_lds, int32_t* first_lds,
                                               int32_t (*wave_tot)[2], int E) {
@@ -40,15 +86,7 @@ __device__ __forceinline__ void group_offsets(Cnt cnt, int32_t* off_lds, int32_t
     mine += n;
     mine_t += (n + FFN_BM - 1) / FFN_BM;
   }
-  int incl = mine, incl_t = mine_t;
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) {
-    const int o = __shfl_up(incl, m, 64), ot = __shfl_up(incl_t, m, 64);
-    if (lane >= m) {
-      incl += o;
-      incl_t += ot;
-    }
-  }
+  const int incl = wave_scan(mine), incl_t = wave_scan(mine_t);
   if (lane == 63) {
     wave_tot[wv][0] = incl;
     wave_tot[wv][1] = incl_t;
@@ -73,21 +111,23 @@ __device__ __forceinline__ void group_offsets(Cnt cnt, int32_t* off_lds, int32_t
   __syncthreads();
 }
 
+// the header words that go with the offsets (one thread)
+__device__ __forceinline__ void write_counts(int32_t* __restrict__ hdr, int P, int n_tiles, bool with_tiles, int max_tiles) {
+  hdr[HDR_PAIRS] = P;
+  if (with_tiles) {
+    hdr[HDR_MTILES] = min(n_tiles, max_tiles);
+    hdr[HDR_DYN_GATE_UP] = 0;
+    hdr[HDR_DYN_DOWN] = 0;
+    for (int i = 0; i < 8; ++i) hdr[HDR_DYN_FUSED + i] = 0;
+    if (n_tiles > max_tiles) atomicOr(&hdr[HDR_FLAGS], 2);  // cannot happen: P <= T * k_max
+  }
+}
 // off[0..E] and the header words that go with them (one workgroup)
 __device__ __forceinline__ void write_offsets(const int32_t* off_lds, const int32_t* first_lds,
                                               int32_t* __restrict__ off, int32_t* __restrict__ hdr,
                                               bool with_tiles, int max_tiles, int E) {
   for (int g = threadIdx.x; g <= E; g += blockDim.x) off[g] = off_lds[g];
-  if (threadIdx.x == 0) {
-    hdr[HDR_PAIRS] = off_lds[E];
-    if (with_tiles) {
-      hdr[HDR_MTILES] = min(first_lds[E], max_tiles);
-      hdr[HDR_DYN_GATE_UP] = 0;
-      hdr[HDR_DYN_DOWN] = 0;
-      for (int i = 0; i < 8; ++i) hdr[HDR_DYN_FUSED + i] = 0;
-      if (first_lds[E] > max_tiles) atomicOr(&hdr[HDR_FLAGS], 2);  // cannot happen: P <= T * k_max
-    }
-  }
+  if (threadIdx.x == 0) write_counts(hdr, off_lds[E], first_lds[E], with_tiles, max_tiles);
 }
 
 // The m-tiles of all groups (a group's tiles are contiguous).  Tile i belongs to the last group
@@ -117,19 +157,14 @@ __device__ __forceinline__ void write_tiles(const int32_t* off_lds, const int32_
   }
 }
 
-// slots of the pairs of ntok tokens behind t0; base(g): the group's first slot plus its rows from earlier tokens
+// slots of a run's pairs, the first of which is pair0; base(g): the group's first slot plus its rows from earlier tokens
 template <class Base>
-__device__ __forceinline__ void place_pairs(const int32_t* __restrict__ ids, const u64* masks, Base base,
-                                            int32_t* __restrict__ sorted_pair,
-                                            int32_t* __restrict__ slot_of_pair, int t0, int ntok, int P,
-                                            int E, int W, int k_max) {
-  const int n = ntok * k_max;
-  const size_t pair0 = (size_t)t0 * k_max;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    int g = ids[pair0 + i];
+__device__ __forceinline__ void place_pairs(Picks& picks, const u64* masks, Base base, int32_t* __restrict__ sorted_pair,
+                                            int32_t* __restrict__ slot_of_pair, size_t pair0, int P, int E, int W) {
+  picks.each(true, [&](int i, int g) {
     int slot = -1;
     if (g >= 0 && g < E) {
-      int tl = i / k_max, wq = tl >> 6;
+      const int tl = picks.token(i), wq = tl >> 6;
       int rank = __popcll(masks[g * W + wq] & ((1ull << (tl & 63)) - 1ull));
       for (int w = 0; w < wq; ++w) rank += __popcll(masks[g * W + w]);
       slot = base(g) + rank;
@@ -137,46 +172,84 @@ __device__ __forceinline__ void place_pairs(const int32_t* __restrict__ ids, con
     }
     slot_of_pair[pair0 + i] = slot;
     if ((long)(pair0 + i) >= (long)P) sorted_pair[pair0 + i] = -1;  // tail beyond the P valid slots
-  }
+  });
 }
 
 // ---------------------------------------------------------------- a small batch in one workgroup
-// Up to 64 tokens, or more with few pairs, whose masks and prefixes fit the default 64 KiB of LDS: the three launches
-// of the general path cost more than their work there.  One workgroup places the pairs of all tokens by itself, and
-// from a second 64-token word of mask on the general path has a workgroup for each.  Calls of d = 64, Is = 32, 512
-// sub-experts from a captured graph, one workgroup | three launches: 40 tokens of 8 picks 26.2 | 30.3 us, 64 of 64
-// 50.8 | 59.2; 100 of 8 34.4 | 35.3, of 24 42.3 | 42.5, of 64 62.3 | 61.1; 160 of 4 32.7 | 31.6, of 32 54.4 | 46.1;
-// 255 of 32 67.1 | 47.8 (32 to 1024 sub-experts alike).  Budgets below k_max leave fewer pairs than T k_max: 79
-// tokens of up to 20, half of them on average, 36.5 | 39.2; 155 of up to 1, 39.5 | 40.7.
+// Up to 64 tokens, or more with few pairs, whose masks and offsets fit the default 64 KiB of LDS: the three launches
+// of the general path cost more than their work there.  What bounds it is a chain of latencies (picks, masks, scan,
+// offsets, slots); one workgroup places the pairs of all tokens by itself, and from a second 64-token word of mask on
+// the general path has a workgroup for each.  Calls of d = 64, Is = 32, 512 sub-experts from a captured graph, one
+// workgroup | three launches: 40 tokens of 8 picks 22.8 | 28.1 us, 64 of 64 42.7 | 51.8; 100 of 8 29.2 | 33.3, of 24 36.5 |
+// 38.7, of 64 52.3 | 55.2; 160 of 4 28.2 | 31.1, of 8 30.8 | 34.2, of 32 45.4 | 43.8; 255 of 8 33.4 | 33.8, of 32 54.2 |
+// 44.0 (32 to 1024 sub-experts alike).  Budgets below k_max leave fewer pairs than T k_max: 79 tokens of up to 20, half
+// of them on average, 32.7 | 37.1; 155 of up to 1, 22.1 | 25.8.  (With a loop over the picks that waits for each, a
+// bisection per m-tile and scans by shuffles, one workgroup took 26.2 us for 40 tokens of 8, 50.8 for 64 of 64.)
 struct SmallDispatch {
   int32_t *cnt, *off, *sorted_pair, *slot_of_pair;
   MTile* tiles;  // nullptr: no m-tile table
   int max_tiles;
 };
-__host__ __device__ inline size_t small_dispatch_lds(int T, int E) { return (size_t)E * ((T + 63) / 64) * 8 + 2 * ((size_t)E + 1) * 4; }
+__host__ __device__ inline size_t small_dispatch_lds(int T, int E) { return (size_t)E * ((T + 63) / 64) * 8 + (size_t)E * 4; }
 inline bool small_dispatch(int T, int E, int k_max) {
-  return T > 0 && (T <= 64 || (T < 256 && T * k_max <= (T <= 128 ? 4096 : 320))) && small_dispatch_lds(T, E) <= 60 * 1024;
+  return T > 0 && (T <= 64 || (T < 256 && T * k_max <= (T <= 128 ? 6400 : 2048))) && small_dispatch_lds(T, E) <= 60 * 1024;
 }
 
-__device__ __forceinline__ void dispatch_one_workgroup(const int32_t* __restrict__ ids, const SmallDispatch& a,
-                                                       int32_t* __restrict__ hdr, u64* lds,
-                                                       int32_t (*wave_tot)[2], int T, int E, int k_max) {
-  const int W = (T + 63) / 64;
-  u64* masks = lds;
-  int32_t* off_lds = reinterpret_cast<int32_t*>(masks + (size_t)E * W);
-  int32_t* first_lds = off_lds + E + 1;
-  build_masks(ids, masks, 0, T, E, W, k_max);
+// Offsets, counts and m-tiles of all groups from the masks, by one workgroup of `threads` threads; returns P.  A group
+// has fewer than 256 rows here: at most one m-tile, which the thread that places the group writes.  Ends in front of
+// a barrier that off_lds needs.
+__device__ __forceinline__ int small_groups(const SmallDispatch& a, int32_t* __restrict__ hdr, const u64* masks,
+                                            int32_t* off_lds, int32_t* wave_tot, int W, int E, int threads) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   auto count = [&](int g) {
     int n = 0;
     for (int w = 0; w < W; ++w) n += __popcll(masks[g * W + w]);
     return n;
   };
-  group_offsets(count, off_lds, first_lds, wave_tot, E);
-  for (int g = threadIdx.x; g < E; g += blockDim.x) a.cnt[g] = off_lds[g + 1] - off_lds[g];
-  write_offsets(off_lds, first_lds, a.off, hdr, a.tiles != nullptr, a.max_tiles, E);
-  if (a.tiles != nullptr) write_tiles(off_lds, first_lds, a.tiles, a.max_tiles, false, E, threadIdx.x, blockDim.x);
-  place_pairs(ids, masks, [&](int g) { return off_lds[g]; }, a.sorted_pair, a.slot_of_pair, 0, T, off_lds[E], E,
-              W, k_max);
+  // rows (at most 64 x 1024) in the low 18 bits of a word, m-tiles (at most 4096) above them: one scan for both
+  constexpr int TILE = 1 << 18;
+  const int per = (E + threads - 1) / threads, lo = min(tid * per, E), hi = min(lo + per, E);
+  int mine = 0;
+  for (int g = lo; g < hi; ++g) {
+    const int n = count(g);
+    mine += n + (n > 0 ? TILE : 0);
+  }
+  const int incl = wave_scan(mine);
+  if (lane == 63) wave_tot[wv] = incl;
+  __syncthreads();
+  int run = incl - mine, total = 0;
+  for (int i = 0; i < threads / 64; ++i) {
+    const int t = wave_tot[i];
+    run += i < wv ? t : 0;
+    total += t;
+  }
+  const int P = total & (TILE - 1);
+  for (int g = lo; g < hi; ++g) {
+    const int n = count(g), row0 = run & (TILE - 1), tile = run / TILE;
+    off_lds[g] = row0;
+    a.off[g] = row0;
+    a.cnt[g] = n;
+    if (a.tiles != nullptr && n > 0 && tile < a.max_tiles) a.tiles[tile] = MTile{g, row0, n, tile, 1, {0, 0, 0}};
+    run += n + (n > 0 ? TILE : 0);
+  }
+  if (tid == 0) {
+    a.off[E] = P;
+    write_counts(hdr, P, total / TILE, a.tiles != nullptr, a.max_tiles);
+  }
+  return P;
+}
+
+__device__ __forceinline__ void dispatch_one_workgroup(const int32_t* __restrict__ ids, const SmallDispatch& a,
+                                                       int32_t* __restrict__ hdr, u64* lds,
+                                                       int32_t* wave_tot, int T, int E, int k_max) {
+  const int W = (T + 63) / 64;
+  u64* masks = lds;
+  int32_t* off_lds = reinterpret_cast<int32_t*>(masks + (size_t)E * W);
+  Picks picks(ids, T, k_max);
+  build_masks(picks, masks, E, W);
+  const int P = small_groups(a, hdr, masks, off_lds, wave_tot, W, E, DISPATCH_THREADS);
+  __syncthreads();
+  place_pairs(picks, masks, [&](int g) { return off_lds[g]; }, a.sorted_pair, a.slot_of_pair, 0, P, E, W);
 }
 
 }  // namespace mp

@@ -136,7 +136,8 @@ template <int CTRL>
 __device__ __forceinline__ int dpp_i(int v) {
   return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
 }
-constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_XOR3 = 0x1B, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140,
+              DPP_ROR8 = 0x128;
 
 __device__ __forceinline__ float wave_max_f(float v) {
   v = fmaxf(v, __int_as_float(dpp_i<DPP_XOR1>(__float_as_int(v))));
@@ -158,9 +159,17 @@ __device__ __forceinline__ int wave_min_i(int v) {
   const int r2 = __builtin_amdgcn_readlane(v, 32), r3 = __builtin_amdgcn_readlane(v, 48);
   return min(min(r0, r1), min(r2, r3));
 }
+// the butterfly over lane ^ 32, 16, 8, 4, 2, 1 (every lane ends with the same sum)
 __device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m, 64);
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  const auto add = [](u32x2 v) { return __uint_as_float(v.x) + __uint_as_float(v.y); };
+  const auto bits = [](float f) { return __float_as_uint(f); };
+  x = add(__builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(bits(x), bits(x), false, false)));
+  x = add(__builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(bits(x), bits(x), false, false)));
+  x += __int_as_float(dpp_i<DPP_ROR8>(__float_as_int(x)));
+  x += __int_as_float(dpp_i<DPP_HALF_MIRROR>(dpp_i<DPP_XOR3>(__float_as_int(x))));  // 7 - l, then ^ 3
+  x += __int_as_float(dpp_i<DPP_XOR2>(__float_as_int(x)));
+  x += __int_as_float(dpp_i<DPP_XOR1>(__float_as_int(x)));
   return x;
 }
 
@@ -170,7 +179,7 @@ constexpr int TOPK_WAVES = 4;
 // 6 picks 20.5 | 20.4, 8 picks 23.7 | 21.3; 16 384 x 2048: 30.5 | 41.6, 44.6 | 47.2, 52.8 | 47.4.  With one element
 // per lane a maximum is cheaper: 4096 x 64, 8 picks 7.9 | 8.6, 12 picks 9.1 | 8.6 (16 384 x 64: 15.6 | 14.9).
 constexpr int topk_few(int elems) { return elems == 1 ? 8 : 6; }
-__host__ __device__ inline int topk_pad(int k_max) { return (k_max + 3) / 4 * 4; }
+__host__ __device__ inline int topk_pad(int k_max) { return (k_max + 7) / 8 * 8; }
 // a wave's own LDS writes are readable by all its lanes
 __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -188,23 +197,32 @@ __device__ __forceinline__ int wave_max_i(int v) {
   return max(max(r0, r1), max(r2, r3));
 }
 
-// DISPATCH: the last workgroup to finish also dispatches the picks of all T tokens (small batches).
-template <int ELEMS, bool DISPATCH>
-__global__ __launch_bounds__(64 * TOPK_WAVES) void topk_kernel(
+// What follows the picks of a small batch in the same launch.
+//   LAST: the last workgroup to finish dispatches the picks of all T tokens, which it reads back.
+//   SOLO: one workgroup of up to 16 waves has all tokens, and dispatches their picks from LDS.
+enum { TOPK_ONLY, TOPK_LAST, TOPK_SOLO };
+constexpr int SOLO_WAVES = 16;
+template <int ELEMS, int MODE>
+__global__ __launch_bounds__(64 * (MODE == TOPK_SOLO ? SOLO_WAVES : TOPK_WAVES)) void topk_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ k_tok, int32_t* __restrict__ ids,
     float* __restrict__ wout, int32_t* __restrict__ hdr, int T, int E, int k_max, int renorm,
     float scale, SmallDispatch small) {
   extern __shared__ __align__(16) unsigned char topk_smem[];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int t = blockIdx.x * TOPK_WAVES + wv;
+  const int t = MODE == TOPK_SOLO ? wv : blockIdx.x * TOPK_WAVES + wv;
+  // per wave: keys and ids of the picks in id order, then logits and ids in pick order
+  const int kp = topk_pad(k_max);
+  int* uk = reinterpret_cast<int*>(topk_smem) + (size_t)wv * 4 * kp;
+  int* uid = uk + kp;
+  float* se = reinterpret_cast<float*>(uid + kp);
+  int* sid = reinterpret_cast<int*>(se + kp);
+  u64* solo_masks = reinterpret_cast<u64*>(topk_smem + (size_t)(blockDim.x / 64) * 16 * kp);  // behind all waves' picks
+  if constexpr (MODE == TOPK_SOLO) {
+    for (int g = threadIdx.x; g < E; g += blockDim.x) solo_masks[g] = 0ull;
+    __syncthreads();
+  }
+  int picked = 0;
   if (t < T) {
-    // per wave: keys and ids of the picks in id order, then logits and ids in pick order
-    const int kp = topk_pad(k_max);
-    int* uk = reinterpret_cast<int*>(topk_smem) + (size_t)wv * 4 * kp;
-    int* uid = uk + kp;
-    float* se = reinterpret_cast<float*>(uid + kp);
-    int* sid = reinterpret_cast<int*>(se + kp);
-
     int kt = k_tok != nullptr ? k_tok[t] : k_max;  // null: every token takes k_max
     kt = __builtin_amdgcn_readfirstlane(kt);
     if (kt < 0 || kt > k_max) {
@@ -280,9 +298,18 @@ __global__ __launch_bounds__(64 * TOPK_WAVES) void topk_kernel(
       if (kt <= 2) low = max(low, dpp_i<DPP_MIRROR>(low));
       auto uniform = [](int m) { return __builtin_amdgcn_readfirstlane(m); };
       auto at_least = [&](int m) {
+        // eight ballots at a time into registers of their own: a bit count right behind its comparison waits for it
+        constexpr int G = ELEMS < 8 ? ELEMS : 8;
         int c = 0;
 #pragma unroll
-        for (int i = 0; i < ELEMS; ++i) c += __popcll(__ballot(key[i] >= m));
+        for (int i0 = 0; i0 < ELEMS; i0 += G) {
+          u64 b[G];
+#pragma unroll
+          for (int i = 0; i < G; ++i) b[i] = __ballot(key[i0 + i] >= m);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < G; ++i) c += __popcll(b[i]);
+        }
         return c;
       };
       const TopkCut cut = topk_cut(kt <= 64 ? wave_min_i(low) : GONE, wave_max_i(best) + 1, kt, uniform, at_least);
@@ -305,44 +332,68 @@ __global__ __launch_bounds__(64 * TOPK_WAVES) void topk_kernel(
         }
         base += __popcll(take);
       }
-      if (lane < 4 && kt + lane < kp) uk[kt + lane] = GONE;  // the ranking reads whole quadruples
+      if (lane < 8 && kt + lane < kp) uk[kt + lane] = GONE;  // the ranking reads eight at a time
       wave_lds_fence();
       // rank = number of larger keys plus equal keys of smaller ids (= earlier positions)
       for (int j = lane; j < kt; j += 64) {
         const int mine = uk[j];
         int rank = 0;
-        for (int q = 0; q < kt; q += 4) {
-          const int4 o = *reinterpret_cast<const int4*>(uk + q);
+        for (int q = 0; q < kt; q += 8) {
+          const int4 o = *reinterpret_cast<const int4*>(uk + q), p = *reinterpret_cast<const int4*>(uk + q + 4);
           rank += o.x > mine - (q < j ? 1 : 0);
           rank += o.y > mine - (q + 1 < j ? 1 : 0);
           rank += o.z > mine - (q + 2 < j ? 1 : 0);
           rank += o.w > mine - (q + 3 < j ? 1 : 0);
+          rank += p.x > mine - (q + 4 < j ? 1 : 0);
+          rank += p.y > mine - (q + 5 < j ? 1 : 0);
+          rank += p.z > mine - (q + 6 < j ? 1 : 0);
+          rank += p.w > mine - (q + 7 < j ? 1 : 0);
         }
         se[rank] = topk_unkey(mine);
         sid[rank] = uid[j];
       }
       wave_lds_fence();
     }
+    picked = kt;
     float dsel = 0.0f;
     for (int j = lane; j < kt; j += 64) dsel += expf(se[j] - mx);
     if (renorm) denom = wave_sum(dsel);
     for (int j = lane; j < k_max; j += 64) {
       bool on = j < kt;
       ids[(size_t)t * k_max + j] = on ? sid[j] : -1;
+      if (MODE == TOPK_SOLO && on) atomicOr(&solo_masks[sid[j]], 1ull << t);
       wout[(size_t)t * k_max + j] = on ? scale * expf(se[j] - mx) / denom : 0.0f;
     }
   }
-  if constexpr (DISPATCH) {
+  if constexpr (MODE == TOPK_SOLO) {
+    int32_t* off_lds = reinterpret_cast<int32_t*>(solo_masks + E);
+    __syncthreads();
+    const int P = small_groups(small, hdr, solo_masks, off_lds, off_lds + E, 1, E, blockDim.x);
+    __syncthreads();
+    if (t >= T) return;
+    for (int j = lane; j < k_max; j += 64) {
+      const int i = t * k_max + j;
+      int slot = -1;
+      if (j < picked) {
+        const int g = sid[j];
+        slot = off_lds[g] + __popcll(solo_masks[g] & ((1ull << t) - 1ull));
+        small.sorted_pair[slot] = i;
+      }
+      small.slot_of_pair[i] = slot;
+      if (i >= P) small.sorted_pair[i] = -1;  // tail beyond the P valid slots
+    }
+  }
+  if constexpr (MODE == TOPK_LAST) {
     // behind the dispatch's tables in the same dynamic LDS: the picks of the largest budget take all of
     // the default 64 KiB, so there is no room for static LDS beside them
     int32_t* is_last = reinterpret_cast<int32_t*>(topk_smem + small_dispatch_lds(T, E));
-    int32_t(*wave_tot)[2] = reinterpret_cast<int32_t(*)[2]>(is_last + 2);
-    __threadfence();  // this workgroup's picks are visible on the device before it counts itself done
+    int32_t* wave_tot = is_last + 1;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // this workgroup's picks are visible on the device before it counts itself done
     __syncthreads();
     if (threadIdx.x == 0) *is_last = atomicAdd(&hdr[HDR_TOPK_DONE], 1) == (int)gridDim.x - 1;
     __syncthreads();
     if (!*is_last) return;
-    __threadfence();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     dispatch_one_workgroup(ids, small, hdr, reinterpret_cast<u64*>(topk_smem), wave_tot, T, E, k_max);
   }
 }
@@ -353,17 +404,31 @@ hipError_t launch_topk(const float* logits, const int32_t* k_tok, int32_t* ids, 
   if (T == 0) return hipSuccess;
   static_assert(64 * TOPK_WAVES == DISPATCH_THREADS, "the same workgroup does both");
   dim3 grid(cdiv(T, TOPK_WAVES)), block(64 * TOPK_WAVES);
-  size_t sh = (size_t)TOPK_WAVES * 4 * topk_pad(k_max) * sizeof(float);
-  int elems = cdiv(E, 64);
-  const size_t sh_small = small_dispatch_lds(T, E) + 10 * sizeof(int32_t);  // the last flag and wave_tot
-  if (small != nullptr && sh_small > sh) sh = sh_small;
-#define MP_TOPK(N)                                                                                             \
-  do {                                                                                                         \
-    if (small != nullptr)                                                                                      \
-      topk_kernel<N, true><<<grid, block, sh, s>>>(logits, k_tok, ids, w, hdr, T, E, k_max, renorm, scale, *small); \
-    else                                                                                                       \
-      topk_kernel<N, false><<<grid, block, sh, s>>>(logits, k_tok, ids, w, hdr, T, E, k_max, renorm, scale,     \
-                                                    SmallDispatch{});                                          \
+  const size_t sh_wave = (size_t)4 * topk_pad(k_max) * sizeof(float);
+  size_t sh = TOPK_WAVES * sh_wave;
+  const int elems = cdiv(E, 64);
+  // One workgroup saves the fence, the count and the reading back of the picks; 16 waves have registers for 16
+  // logits per lane.  Layer calls of 1 | 4 | 8 | 16 tokens, 128 x 4 sub-experts: 42.1 | 50.6 | 57.2 | 118.3 us, with the last
+  // of several workgroups 43.4 | 52.4 | 58.0 | 119.0; 16 tokens in fp32, 8 x 4 of 128: 22.3, 23.4.
+  const int solo_waves = T < TOPK_WAVES ? TOPK_WAVES : T;
+  const size_t sh_solo = solo_waves * sh_wave + (size_t)E * 12 + SOLO_WAVES * sizeof(int32_t);
+  const bool solo = small != nullptr && T <= SOLO_WAVES && elems <= 16 && sh_solo <= 60 * 1024;
+  const size_t sh_small = small_dispatch_lds(T, E) + (1 + DISPATCH_THREADS / 64) * sizeof(int32_t);  // the last flag and wave_tot
+  if (solo) {
+    sh = sh_solo;
+    grid = dim3(1);
+    block = dim3(64 * solo_waves);
+  } else if (small != nullptr && sh_small > sh) {
+    sh = sh_small;
+  }
+  const SmallDispatch sd = small != nullptr ? *small : SmallDispatch{};
+#define MP_TOPK_MODE(N, MODE) \
+  topk_kernel<N, MODE><<<grid, block, sh, s>>>(logits, k_tok, ids, w, hdr, T, E, k_max, renorm, scale, sd)
+#define MP_TOPK(N)                                                           \
+  do {                                                                       \
+    if (small == nullptr) MP_TOPK_MODE(N, TOPK_ONLY);                        \
+    else if (solo && N <= 16) MP_TOPK_MODE((N <= 16 ? N : 16), TOPK_SOLO);   \
+    else MP_TOPK_MODE(N, TOPK_LAST);                                         \
   } while (0)
   if (elems <= 1) MP_TOPK(1);
   else if (elems <= 2) MP_TOPK(2);
@@ -373,6 +438,7 @@ hipError_t launch_topk(const float* logits, const int32_t* k_tok, int32_t* ids, 
   else if (elems <= 32) MP_TOPK(32);
   else MP_TOPK(64);
 #undef MP_TOPK
+#undef MP_TOPK_MODE
   return hipGetLastError();
 }
 

@@ -15,7 +15,12 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("T,E,k_max", [(1, 512, 32), (64, 40, 5), (65, 40, 5), (128, 64, 32), (128, 64, 33), (129, 64, 2),
                                        (129, 64, 3), (255, 64, 9),
-                                       (255, 1500, 1), (255, 1530, 1), (130, 2100, 66)])
+                                       (255, 1500, 1), (255, 1530, 1), (130, 2100, 66),
+                                       # the last of several workgroups or three launches
+                                       (128, 64, 50), (128, 64, 51), (129, 64, 15), (129, 64, 16), (255, 64, 8),
+                                       # one workgroup with all tokens: waves, elements per lane, LDS; just beyond
+                                       (3, 64, 64), (5, 512, 32), (16, 66, 1), (16, 1024, 40), (17, 64, 8),
+                                       (16, 1026, 8), (15, 1024, 200), (2, 1024, 512)])
 def test_small_batches_match_the_oracle(T, E, k_max):
     k = np.random.default_rng(T).integers(0, k_max + 1, size=T).astype(np.int32)
     wl = W.make_workload("small", dtype="bf16", d=64, n_experts=E // 2, n_sub=2, inter_sub=32,
