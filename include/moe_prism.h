@@ -129,8 +129,8 @@ MOE_PRISM_API int moe_prism_dispatch(const moe_prism_shape* shape, const int32_t
  * sub-expert g; w_down [E, d, Is].  y [T*k_max, d] in shape->dtype, rows >= P are
  * not written.  bf16: fp32 accumulation, h rounded to bf16 once, y rounded once.
  * Kernel choice (bf16): sub-experts with Is in {64, 128, 192} (and d >= 256) run one
- * fused kernel, all other shapes a gate-up and a down kernel; so few pairs that tiles of
- * 256 weight rows would leave the chip idle run both GEMMs on small tiles.  The environment
+ * fused kernel, all other shapes a gate-up and a down kernel, which few rows per
+ * sub-expert (decode batches, also of narrow ones) run on tiles of their own.  The environment
  * variable MOE_PRISM_FFN=split, read at every call, forces the gate-up and down kernels
  * (A/B measurements, tests).  Results agree within the rounding stated above.
  */

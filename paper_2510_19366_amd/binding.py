@@ -184,16 +184,17 @@ def moe_prism_layer(shape, x, w_router, router_bias, k_tok, w_gate_up, w_down, w
 
 
 def ffn_path(shape):
-    """Which grouped-FFN kernels moe_prism_grouped_ffn / _layer launch for this shape: "fused" (bf16,
-    inter_sub in {64, 128, 192}, d >= 256, unless MOE_PRISM_FFN=split), "few" (bf16, at most 64 tokens and
-    few sub-experts to touch: gate-up and down on small tiles) or "split" (gate-up and down)."""
-    pairs, groups = shape.T * shape.k_max, shape.E
-    cus = torch.cuda.get_device_properties(0).multi_processor_count if torch.cuda.is_available() else 256
-    tiles = min(pairs, groups) * -(-shape.inter_sub // 128)
-    if shape.dtype == 1 and shape.T <= 64 and 2 * tiles <= 3 * cus * (2 if shape.inter_sub <= 192 else 1):
+    """Which grouped-FFN kernels moe_prism_grouped_ffn / _layer launch for this shape: "few" (bf16, at most 64
+    tokens: gate-up and down on tiles for few rows per sub-expert), "fused" (bf16, inter_sub in {64, 128, 192},
+    d >= 256, unless MOE_PRISM_FFN=split or there are more sub-experts than CUs with 10 to 24 possible rows each) or
+    "split" (gate-up and down)."""
+    if shape.dtype == 1 and shape.T <= 64:
         return "few"
     ok = (shape.dtype == 1 and shape.inter_sub in (64, 128, 192) and shape.d % 64 == 0
           and shape.d >= 256 and shape.T * shape.d * 2 < 2 ** 32)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count if torch.cuda.is_available() else 256
+    if shape.E > cus and 10 * shape.E <= shape.T * shape.k_max <= 24 * shape.E:
+        ok = False
     return "fused" if ok and os.environ.get("MOE_PRISM_FFN") != "split" else "split"
 
 

@@ -142,8 +142,8 @@ static int do_route(const moe_prism_shape* s, const Layout& L, const void* x, co
   return MOE_PRISM_OK;
 }
 
-// The fused gate-up/SwiGLU/down kernel serves bf16 layers with narrow sub-experts (but for a handful of
-// pairs, see ffn_few_pairs); the
+// The fused gate-up/SwiGLU/down kernel serves bf16 layers with narrow sub-experts (but for few
+// rows per sub-expert, see ffn_few_blocks); the
 // environment variable MOE_PRISM_FFN=split forces the two-kernel path (for A/B measurements
 // and so that tests reach both paths on the same shapes).
 static bool use_fused_ffn(const moe_prism_shape* s) {
@@ -151,12 +151,12 @@ static bool use_fused_ffn(const moe_prism_shape* s) {
   const char* e = getenv("MOE_PRISM_FFN");
   return !(e != nullptr && strcmp(e, "split") == 0);
 }
-// the small tiles for a handful of pairs (bf16)
-static bool use_few(const moe_prism_shape* s) {
-  return s->dtype == MOE_PRISM_BF16 && ffn_few_pairs(s->T, s->k_max, s->n_experts * s->n_sub, s->inter_sub);
+// blocks of the tiles for few rows per sub-expert, or 0
+static int use_few(const moe_prism_shape* s) {
+  return s->dtype == MOE_PRISM_BF16 ? ffn_few_blocks(s->T, s->k_max, s->n_experts * s->n_sub, use_fused_ffn(s)) : 0;
 }
 // m-tiles of even length (see mtile_rows) where the two-kernel path follows
-static bool even_tiles(const moe_prism_shape* s) { return use_few(s) || !use_fused_ffn(s); }
+static bool even_tiles(const moe_prism_shape* s) { return use_few(s) != 0 || !use_fused_ffn(s); }
 
 // the dispatch of T tokens with up to k_max picks out of E groups
 static int do_dispatch_over(const Layout& L, const int32_t* ids, int32_t* cnt, int32_t* off,
@@ -207,8 +207,8 @@ static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, cons
                                             L.max_mtiles, st));
     return MOE_PRISM_OK;
   }
-  const bool few = use_few(s);
-  if (use_fused_ffn(s) && !few) {
+  const int few = use_few(s);
+  if (use_fused_ffn(s) && few == 0) {
     MP_LAUNCH(MOE_PRISM_K_FFN_FUSED,
               launch_ffn_fused_bf16((const uint16_t*)x, (const uint16_t*)w_gu, (const uint16_t*)w_dn,
                                     sorted_pair, tiles, hdr, (uint16_t*)y, s->T, s->d, s->inter_sub,
@@ -284,7 +284,7 @@ static int do_route_proxy(const moe_prism_shape* s, const Layout& L, const void*
   if (s->T == 0) return MOE_PRISM_OK;
   MP_LAUNCH(MOE_PRISM_K_FFN_GATE_UP,
             launch_ffn_gate_up(s->dtype, x, w_proxy, q.sp0, tiles, hdr, act, s->T, s->d, rows_half, m,
-                               s->dtype == MOE_PRISM_BF16 && ffn_few_pairs(s->T, m, N, rows_half), L.max_mtiles, st));
+                               s->dtype == MOE_PRISM_BF16 ? ffn_few_blocks(s->T, m, N, false) : 0, L.max_mtiles, st));
   MP_LAUNCH(MOE_PRISM_K_PROXY_SELECT,
             launch_proxy_select(s->dtype, act, rows_half, q.ids0, q.w0, q.sl0, k_tok, kappa, ids, w,
                                 hdr, s->T, s->n_sub, r, m, s->k_max, st));

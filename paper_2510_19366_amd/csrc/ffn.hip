@@ -196,7 +196,7 @@ static bool f32_short(int T) { return T <= 2 * F32_ROWS; }
 
 hipError_t launch_ffn_gate_up(int dtype, const void* x, const void* w_gu, const int32_t* sorted_pair,
                               const MTile* tiles, int32_t* hdr, void* h, int T, int d, int Is,
-                              int k_max, bool few, int max_mtiles, hipStream_t s) {
+                              int k_max, int few, int max_mtiles, hipStream_t s) {
   if (max_mtiles <= 0) return hipSuccess;
   if (dtype != 0)
     return launch_gate_up_bf16((const uint16_t*)x, (const uint16_t*)w_gu, sorted_pair, tiles, hdr,
@@ -211,7 +211,7 @@ hipError_t launch_ffn_gate_up(int dtype, const void* x, const void* w_gu, const 
 }
 
 hipError_t launch_ffn_down(int dtype, const void* h, const void* w_dn, const MTile* tiles,
-                           int32_t* hdr, void* y, int T, int d, int Is, bool few, int max_mtiles,
+                           int32_t* hdr, void* y, int T, int d, int Is, int few, int max_mtiles,
                            hipStream_t s) {
   if (max_mtiles <= 0) return hipSuccess;
   if (dtype != 0)

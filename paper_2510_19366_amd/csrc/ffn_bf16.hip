@@ -11,7 +11,7 @@
 //     into a double-buffered, XOR-swizzled LDS tile, one slab ahead of the MFMAs.  The weight block is the MFMA's first operand and its
 //     rows are fed in a permuted order, so that a lane ends up with 8 or 16 consecutive output
 //     columns of one slot row and stores them as 16-byte words (ffn_few_kernel likewise).
-// So few pairs that these tiles would leave CUs idle take ffn_few_kernel (tiles of 64 weight rows).
+// Few rows per sub-expert take ffn_few_kernel (tiles of 64 or 128 weight rows, see ffn_few_blocks).
 // Narrow sub-experts (Is in {64, 128, 192}) take the fused kernel in ffn_fused_bf16.hip
 // instead; these two kernels serve every other shape.
 #include <type_traits>
@@ -24,6 +24,7 @@ namespace mp {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 constexpr int BM = FFN_BM;   // slot rows per tile
 constexpr int BN = 256;      // weight rows per tile
@@ -144,6 +145,20 @@ struct GateUpOp {
           pack2(silu_mul(v[0], v[8]), silu_mul(v[1], v[9])), pack2(silu_mul(v[2], v[10]), silu_mul(v[3], v[11])),
           pack2(silu_mul(v[4], v[12]), silu_mul(v[5], v[13])), pack2(silu_mul(v[6], v[14]), silu_mul(v[7], v[15])));
   }
+  // ---- few rows: weight rows 0..7 of a wave are the gate rows of 8 neurons, 8..15 their up rows, so lanes 0..31 hold
+  // gates and lanes 32..63 the same neurons' ups
+  __device__ __forceinline__ int few_row(const Sc& it, int i) const { return it.n0 + (i & 7) + (i >> 3) * Is; }
+  __device__ __forceinline__ void few_store(const Sc& it, int row, int g, const f32x4& v) const {
+    float u[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t b = __float_as_uint(v[i]);
+      u[i] = __uint_as_float(__builtin_amdgcn_permlane32_swap(b, b, false, false)[1]);  // of lane + 32
+    }
+    if (g < 2 && row < it.rows)
+      *reinterpret_cast<uint2*>(h + (size_t)(it.row0 + row) * Is + it.n0 + 4 * g) =
+          make_uint2(pack2(silu_mul(v[0], u[0]), silu_mul(v[1], u[1])), pack2(silu_mul(v[2], u[2]), silu_mul(v[3], u[3])));
+  }
   __device__ __forceinline__ void epilogue(const Sc& it, f32x16 (&acc)[NB][MB], uint16_t*) const {  // short K
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int wm = wv >> 1, wn = wv & 1;
@@ -201,6 +216,12 @@ struct DownOp {
   __device__ __forceinline__ void put(const f32x16& a0, const f32x16& a1, int v, Store&& store) const {
     store(v, pack2(a0[v], a1[v]));
     store(v + 1, pack2(a0[v + 1], a1[v + 1]));
+  }
+  // ---- few rows
+  __device__ __forceinline__ int few_row(const Sc& it, int i) const { return it.n0 + i; }
+  __device__ __forceinline__ void few_store(const Sc& it, int row, int g, const f32x4& v) const {
+    if (row < it.rows)
+      *reinterpret_cast<uint2*>(y + (size_t)(it.row0 + row) * d + it.n0 + 4 * g) = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
   }
   // one lane's share of a 32-row weight block: 16 columns of one slot row
   __device__ __forceinline__ void store_block(const Sc& it, int row, int block, int hi, const f32x16& v) const {
@@ -856,105 +877,173 @@ __global__ __launch_bounds__(NT_) void ffn_short_kernel(Op op, const MTile* __re
   run_items<Op>(op, tiles, hdr, n_tiles_n);
 }
 
-// ---------------------------------------------------------------- few pairs
-// A handful of tokens touches a handful of sub-experts, and tiles of 256 weight rows are then fewer
-// than the CUs: one workgroup's copies (100 KB in flight, about 80 GB/s) set the time.  Here a
-// tile is 64 weight rows x 32 slot rows, with a ring of 6 stages of 64 K-elements and two workgroups
-// per CU.  Four waves copy, the first two multiply a block of 32 weight rows each: a sum over K is one
-// chain of MFMAs in ascending k, as in every other driver, so that which of them a batch takes does not
-// show in its results.
-// Bound by the latency of one chain: ring fill, K stages; a stage's fragments are read while the stage
-// before is multiplied.  Measured between HIP events, one token of the 128 x 4 layer (20 to 32 sub-experts of
-// 192, d = 2048): gate-up and down together 22.7 us, the fused kernel 85 (with the list of all row blocks, see
-// row_blocks.h, 28.9; with the two halves of every stage on two waves and added up at the end, which is another order
-// of the sum, 31.5).
-constexpr int FP_N = 64, FP_M = 32, FP_NS = 6, FP_THREADS = 256;
-constexpr int FP_STAGE = (FP_M + FP_N) * BK * 2, FP_LDS_BYTES = FP_NS * FP_STAGE;
-constexpr int FP_CP = (FP_M + FP_N) / 8 / (FP_THREADS / 64);  // copies per wave and stage
+// ---------------------------------------------------------------- few rows per sub-expert
+// A decode batch gives a sub-expert a row or a few, so the time is that of its weights' bytes, or with few of them that
+// of a tile's chain of latencies.  A wave has 16 weight rows and up to 64 slot rows
+// (v_mfma_f32_16x16x32_bf16: 16 cycles per 32 of K, and bit for bit what two v_mfma_f32_32x32x16_bf16 in a row give, so
+// that which driver a batch takes does not show in its results).  Weights go through a ring of 2 KiB stages that is the
+// wave's own: a stage is a wait, its LDS reads, two copies and its matrix instructions, no barrier.  Slot rows are shared
+// by the waves, in chunks of 4 to 8 stages of K, two of them, and one barrier per chunk.
+//   MOST = 1, 2 (blocks of 16 slot rows at a time): 4 waves, two workgroups per CU with 80 KB of weights in flight;
+//   MOST = 4: 8 waves, which halves what is copied of the slot rows per weight row.
+// Two tokens of 32 sub-experts each, 192 x 2048, both GEMMs between HIP events 17.6 us, with tiles that shared a stage of
+// weight and slot rows behind a barrier 24.4; 100 tokens of 4 to 12 on 128 of 704 231 -> 196 us (5.6 TB/s of weights)
+// against the ring driver.  (Weights straight into the registers of the matrix instruction: its lanes are rows, so that
+// every lane's 16 bytes are a cache access of their own, 330 cycles a step.)
+constexpr int FP_WAVE_N = 16;
+template <int MOST>
+struct Few {
+  static constexpr int WAVES = MOST == 4 ? 8 : 4, THREADS = 64 * WAVES, N = WAVES * FP_WAVE_N;
+  static constexpr int NS = MOST == 4 ? 5 : 6, STAGE = FP_WAVE_N * BK * 2, RING = WAVES * NS * STAGE;
+  static constexpr int CHUNK = WAVES * 4096, LDS_BYTES = RING + 2 * CHUNK, PER_CU = MOST == 4 ? 1 : 2;
+  static_assert(PER_CU * LDS_BYTES <= 160 * 1024);
+};
 
-template <class Op>
-__global__ __launch_bounds__(FP_THREADS) void ffn_few_kernel(Op op, const MTile* __restrict__ tiles,
-                                                             const int32_t* __restrict__ hdr, int n_tiles_n,
-                                                             int blocks) {
+template <class Op, int MOST>
+__global__ __launch_bounds__(Few<MOST>::THREADS) void ffn_few_kernel(Op op, const MTile* __restrict__ tiles,
+                                                                     const int32_t* __restrict__ hdr, int n_tiles_n) {
+  typedef Few<MOST> F;
   extern __shared__ __align__(16) unsigned char fp_smem[];
-  const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
-  const int wb = wv;  // weight block (waves 0 and 1)
-  const int fr = lane & 31, fh = lane >> 5, wrow = Op::wrow(fr);
+  constexpr int FP_NS = F::NS, FP_STAGE = F::STAGE, FP_CHUNK = F::CHUNK;
+  constexpr int CP = 2, XCP = FP_CHUNK / 1024 / F::WAVES;  // copies per wave: of a stage, of a chunk
+  constexpr int AHEAD = FP_NS - 1;                         // stages in flight
+  const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6), r = lane & 15, g = lane >> 4;
   const int K = op.K(), ns = (K + BK - 1) / BK;
-  const uint32_t lds0 = lds_offset(fp_smem), dst0 = lds0 + (uint32_t)(wv * FP_CP) * 1024u;
-  short_row_blocks<FP_M>(blockIdx.x, gridDim.x, N_XCD, hdr[HDR_MTILES], n_tiles_n, blocks,
-                         [&](int m) { return tiles[m]; }, [](auto&& pred) { return lane_mask(pred); },
-                         [&](const MTile& t, int blk, int nt) {
+  const uint32_t lds0 = lds_offset(fp_smem), ring = lds0 + (uint32_t)(wv * FP_NS * FP_STAGE), xs = lds0 + F::RING;
+  auto tile = [&](const Sc& sc, bool on, auto nb_c) {
+    constexpr int NB = decltype(nb_c)::value;  // blocks of 16 slot rows
+    constexpr int CPR = FP_CHUNK / 256 / NB, SPC = CPR / 8;  // 16-byte pieces of a row in a chunk, stages
+    const uint16_t *bx, *bw;
+    op.bases(sc, bx, bw);
+    const uint32_t row2 = (uint32_t)K * 2u;
+    uint32_t voff[CP], tail[CP], xrow[XCP], xcol[XCP];
+#pragma unroll
+    for (int j = 0; j < CP; ++j) {
+      const int row = j * 8 + (lane >> 3), piece = (lane & 7) ^ swz_f<SWZ_SEQ>(row);
+      voff[j] = (uint32_t)op.few_row(sc, row) * row2 + (uint32_t)piece * 16u;
+      tail[j] = piece & 4 ? 64u : 0u;
+    }
+    uint32_t p_slot = ring;
+    auto produce = [&](int stage) {  // one stage after the other
+      if (stage >= ns) return;
+      const bool cut = (stage + 1) * BK > K;  // K % 64 == 32: pieces 4..7 do not exist, fetch 0..3 (not used)
+#pragma unroll
+      for (int j = 0; j < CP; ++j)
+        copy_to_lds16(bw + (size_t)stage * BK, cut ? voff[j] - tail[j] : voff[j], p_slot + j * 1024u);
+      p_slot = p_slot == ring + (FP_NS - 1) * FP_STAGE ? ring : p_slot + FP_STAGE;
+    };
+    produce(0);  // on its way while the slot list is read
+    // piece p of row i sits at p ^ (i & 15): rows start in the same bank
+    constexpr int CROWS = CPR < 64 ? 64 / CPR : 1;  // rows of a copy
+    const int x_on = min(max((sc.rows + CROWS - 1) / CROWS - wv * XCP, 0), XCP);  // copies that have a row of the tile
+#pragma unroll
+    for (int j = 0; j < XCP; ++j) {
+      const int row = (wv * XCP + j) * CROWS + lane % 64 / CPR;
+      int pair = 0;
+      if constexpr (Op::GATHER) {
+        // a copy of one row: the same for all lanes, and a scalar load does not wait for the copies
+        typedef const __attribute__((address_space(4))) int32_t* Scalar;
+        const int32_t* src = op.idx_src(sc, row);
+        pair = CROWS == 1 ? *(Scalar)(uintptr_t)src : *src;
+      }
+      xrow[j] = (uint32_t)op.a_row(sc, row, pair) * row2;
+      xcol[j] = (uint32_t)((lane % CPR) ^ (row & 15)) * 16u;
+    }
+    auto produce_x = [&](int c) {
+#pragma unroll
+      for (int j = 0; j < XCP; ++j) {
+        if (j >= x_on) break;
+        const uint32_t col = (uint32_t)(c * CPR * 16) + xcol[j];
+        copy_to_lds16(bx, xrow[j] + (col < row2 ? col : 0u), xs + (uint32_t)((c & 1) * FP_CHUNK + (wv * XCP + j) * 1024));
+      }
+    };
+    produce_x(0);
+#pragma nounroll
+    for (int i = 1; i < AHEAD; ++i) produce(i);
+    f32x4 acc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    // fragment addresses of an even and an odd stage of a chunk
+    uint32_t rd_w[2], rd_x[2][2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      rd_w[ks] = ring + (uint32_t)(r * 128) + (uint32_t)((ks * 4 + g) ^ swz_f<SWZ_SEQ>(r)) * 16u;
+#pragma unroll
+      for (int set = 0; set < 2; ++set) rd_x[set][ks] = xs + (uint32_t)(r * CPR * 16) + (uint32_t)((set * 8 + ks * 4 + g) ^ r) * 16u;
+    }
+    bf16x8 fw[2][2] = {}, fx[2][2][NB] = {};
+    auto multiply = [&](auto set_c, int steps) {
+      constexpr int set = decltype(set_c)::value;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+        if (ks < steps)
+#pragma unroll
+          for (int b = 0; b < NB; ++b)
+            acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[set][ks], fx[set][ks][b], acc[b], 0, 0, 0);
+    };
+    const int nc = (ns + SPC - 1) / SPC;
+    uint32_t w_slot = 0;  // of the stage that is read next
+    for (int c = 0; c < nc; ++c) {
+      // chunk c has landed for this wave (behind it AHEAD - 1 stages of weights for the first, SPC for the others), and
+      // behind the barrier for all; nobody reads the chunk before any more
+      static_assert(SPC >= AHEAD - 1);
+      if (c * SPC + AHEAD - 1 < ns) wait_vmem<(AHEAD - 1) * CP>();
+      else wait_vmem<0>();
+      raw_barrier();
+      const bool more = c + 1 < nc;
+      if (more) produce_x(c + 1);
+      // stage q: its copies have landed, its fragments are read while those of stage q - 1 are multiplied
+      auto stage = [&](int s, auto set_c) {
+        constexpr int set = decltype(set_c)::value;
+        const int q = c * SPC + s;
+        if (q >= ns) return;
+        if (q + AHEAD - 1 >= ns) wait_vmem<0>();
+        else if (s < AHEAD && more && x_on == XCP) wait_vmem<(AHEAD - 1) * CP + XCP>();
+        else wait_vmem<(AHEAD - 1) * CP>();
+        const uint32_t x_at = (uint32_t)((c & 1) * FP_CHUNK + s / 2 * 256);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          read_lds16<0>(fw[set][ks], rd_w[ks] + w_slot);
+          read_lds16<0>(fx[set][ks][0], rd_x[set][ks] + x_at);
+          static_loop<1, NB>([&](auto b) {
+            read_lds16<decltype(b)::value * 16 * CPR * 16>(fx[set][ks][decltype(b)::value], rd_x[set][ks] + x_at);
+          });
+        }
+        w_slot = w_slot == (FP_NS - 1) * FP_STAGE ? 0u : w_slot + FP_STAGE;
+        produce(q + AHEAD);  // into the slot of stage q - 1, which has been read
+        if (q > 0) multiply(std::integral_constant<int, 1 - set>{}, 2);
+        wait_lds<0>(fw[set][0], fw[set][1], fx[set][0][0], fx[set][1][0]);
+        static_loop<1, NB>([&](auto b) { wait_lds<0>(fx[set][0][decltype(b)::value], fx[set][1][decltype(b)::value]); });
+      };
+#pragma nounroll
+      for (int s = 0; s < SPC; s += 2) {
+        stage(s, std::integral_constant<int, 0>{});
+        stage(s + 1, std::integral_constant<int, 1>{});
+      }
+    }
+    const int steps = (K - (ns - 1) * BK) / 32;
+    if (ns & 1) multiply(std::integral_constant<int, 0>{}, steps);
+    else multiply(std::integral_constant<int, 1>{}, steps);
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      if (on) op.few_store(sc, b * 16 + r, g, acc[b]);
+    raw_barrier();  // the first chunk is copied again
+  };
+  const ItemRange ir = xcd_items(hdr[HDR_MTILES] * n_tiles_n);
+  for (int item = ir.begin; item < ir.end; item += ir.step) {
+    const MTile t = tiles[item / n_tiles_n];
     Sc sc;
     sc.g = uni(t.g);
-    sc.row0 = uni(t.row0) + blk * FP_M;
-    sc.rows = min(FP_M, uni(t.rows) - blk * FP_M);
-    sc.n0 = nt * (FP_N / Op::N_PER_ROW);
-    const uint16_t *ba, *bb;
-    op.bases(sc, ba, bb);
-    const uint16_t* base[FP_CP];
-    uint32_t voff[FP_CP], tail[FP_CP];
-#pragma unroll
-    for (int j = 0; j < FP_CP; ++j) {
-      const int r0 = (wv * FP_CP + j) * 8, row = r0 + (lane >> 3);
-      const bool slot = r0 < FP_M;  // the same for the whole copy
-      const int br = row - FP_M;
-      const int rr = slot ? op.a_row(sc, row, Op::GATHER ? *op.idx_src(sc, row) : 0) : op.b_row(sc, br);
-      const int chunk = (lane & 7) ^ (slot ? swz_f<SWZ_SEQ>(row) : swz_f<Op::WSWZ>(br & 31));
-      base[j] = slot ? ba : bb;
-      voff[j] = (uint32_t)rr * (uint32_t)K * 2u + (uint32_t)chunk * 16u;
-      tail[j] = chunk & 4 ? 64u : 0u;
+    constexpr int PER_WAVE = FP_WAVE_N / Op::N_PER_ROW;
+    const int n0 = (item % n_tiles_n * F::WAVES + wv) * PER_WAVE;
+    sc.n0 = min(n0, op.n_cols() - PER_WAVE);  // of eight waves the last tile's second four may have none: again the last rows
+    for (int row = 0; row < uni(t.rows); row += 16 * MOST) {
+      sc.row0 = uni(t.row0) + row;
+      sc.rows = min(16 * MOST, uni(t.rows) - row);
+      if (MOST == 2 && sc.rows <= 16) tile(sc, n0 == sc.n0, std::integral_constant<int, 1>{});
+      else tile(sc, n0 == sc.n0, std::integral_constant<int, MOST>{});
     }
-    auto produce = [&](int stage) {
-      if (stage >= ns) return;
-      const bool cut = (stage + 1) * BK > K;  // K % 64 == 32: chunks 4..7 do not exist, fetch 0..3 (not used)
-#pragma unroll
-      for (int j = 0; j < FP_CP; ++j)
-        copy_to_lds16(base[j] + (size_t)stage * BK, cut ? voff[j] - tail[j] : voff[j],
-                      dst0 + (uint32_t)(stage % FP_NS * FP_STAGE + j * 1024));
-    };
-    for (int i = 0; i < FP_NS - 1; ++i) produce(i);
-    f32x16 acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-    bf16x8 f0[2][BK / 16], f1[2][BK / 16];
-    auto multiply = [&](const bf16x8 (&f)[2][BK / 16], int steps) {
-#pragma unroll
-      for (int ks = 0; ks < BK / 16; ++ks)
-        if (ks < steps) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[0][ks], f[1][ks], acc, 0, 0, 0);
-    };
-    auto stage = [&](int q, bf16x8 (&f)[2][BK / 16], const bf16x8 (&before)[2][BK / 16]) {
-      if (q + FP_NS - 2 < ns)
-        wait_vmem<(FP_NS - 2) * FP_CP>();  // stage q has landed
-      else
-        wait_vmem<0>();
-      raw_barrier();         // for every wave; and the slot of stage q - 1 has been read
-      produce(q + FP_NS - 1);
-      if (wb >= FP_N / 32) return;
-      const unsigned char* s = fp_smem + q % FP_NS * FP_STAGE;
-#pragma unroll
-      for (int ks = 0; ks < BK / 16; ++ks) {
-        const int c = 2 * ks + fh;
-        f[0][ks] = *reinterpret_cast<const bf16x8*>(s + (FP_M + wb * 32 + wrow) * 128 + ((c ^ swz_f<Op::WSWZ>(wrow)) * 16));
-        f[1][ks] = *reinterpret_cast<const bf16x8*>(s + fr * 128 + ((c ^ swz_f<SWZ_SEQ>(fr)) * 16));
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      if (q > 0) multiply(before, BK / 16);
-      __builtin_amdgcn_sched_barrier(0);
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this slot has been read
-    };
-    for (int q = 0; q < ns; q += 2) {
-      stage(q, f0, f1);
-      if (q + 1 < ns) stage(q + 1, f1, f0);
-    }
-    if (wb < FP_N / 32) {
-      const int steps = (K - (ns - 1) * BK) / 16;
-      if (ns & 1) multiply(f0, steps);
-      else multiply(f1, steps);
-    }
-    if (wb < FP_N / 32 && fr < sc.rows) op.store_block(sc, fr, wb, fh, acc);
-    __syncthreads();  // the ring is filled again
-  });
+  }
 }
 
 // ---------------------------------------------------------------- launchers
@@ -980,16 +1069,23 @@ static hipError_t launch_ring(const Op& op, int ntn, int grid, int dyn_word, con
   return launch_big<ffn_ring_kernel<Op, HALF, true>>(lds, grid, s, op, tiles, hdr, ntn, dyn_word);
 }
 
+template <class Op, int MOST>
+static hipError_t launch_few(const Op& op, int n_cols, int max_mtiles, const MTile* tiles, const int32_t* hdr, hipStream_t s) {
+  typedef Few<MOST> F;
+  hipError_t e = raise_lds_limit<ffn_few_kernel<Op, MOST>>(F::LDS_BYTES);
+  if (e != hipSuccess) return e;
+  const int ntn = cdiv(n_cols, F::N / Op::N_PER_ROW), grid = persistent_grid((long)max_mtiles * ntn, F::PER_CU);
+  ffn_few_kernel<Op, MOST><<<grid, F::THREADS, F::LDS_BYTES, s>>>(op, tiles, hdr, ntn);
+  return hipGetLastError();
+}
+
 template <class Op>
-static hipError_t launch_op(const Op& op, int T, int K, int n_cols, bool few, int dyn_word, int max_mtiles,
+static hipError_t launch_op(const Op& op, int T, int K, int n_cols, int few, int dyn_word, int max_mtiles,
                             const MTile* tiles, int32_t* hdr, hipStream_t s) {
-  if (few && op.offsets_fit()) {
-    const int ntn = cdiv(n_cols, FP_N / Op::N_PER_ROW);
-    const int blocks = cdiv(T, FP_M), grid = persistent_grid((long)max_mtiles * ntn * blocks, 2);
-    hipError_t e = raise_lds_limit<ffn_few_kernel<Op>>(FP_LDS_BYTES);
-    if (e != hipSuccess) return e;
-    ffn_few_kernel<Op><<<grid, FP_THREADS, FP_LDS_BYTES, s>>>(op, tiles, hdr, ntn, blocks);
-    return hipGetLastError();
+  if (op.offsets_fit()) {
+    if (few == 1) return launch_few<Op, 1>(op, n_cols, max_mtiles, tiles, hdr, s);
+    if (few == 2) return launch_few<Op, 2>(op, n_cols, max_mtiles, tiles, hdr, s);
+    if (few == 4) return launch_few<Op, 4>(op, n_cols, max_mtiles, tiles, hdr, s);
   }
   const int ntn = cdiv(n_cols, BN / Op::N_PER_ROW);
   const int grid = persistent_grid((long)max_mtiles * ntn, 1);
@@ -1000,27 +1096,36 @@ static hipError_t launch_op(const Op& op, int T, int K, int n_cols, bool few, in
   return launch_ring<Op, false>(op, ntn, grid, dyn_word, tiles, hdr, s);
 }
 
-// At most 64 tokens (a group is then one or two row blocks; more would read the weights again for
-// each), and the ring kernel's n-tiles of all sub-experts that they can touch are at most 1.5 per CU, or 3 where
-// Is <= 192.  Both GEMMs between HIP events, d = 2048, 64 tokens, one pair per touched sub-expert, small tiles | what
-// takes 65 tokens.  Is = 192 (fused): 20 sub-experts 25 | 79 us, 100 54 | 82, 200 100 | 113, 384 172 | 215.  Is = 32: 100
-// 28 | 45, 768 114 | 135; 96: 768 200 | 215; 160: 384 161 | 184; 352: 32 34 | 49, 128 112 | 140; 704: 16 33 | 50, 64 113 | 137.
-// All pairs on 8 sub-experts of 704, 32 rows each: 29 | 50; on 4 of 3584: 57 | 83.  So they are ahead as far as the
-// rule goes; beyond it the work is that of the weights' bytes, whichever tiles read them.
-bool ffn_few_pairs(int T, int k_max, int E, int Is) {
-  const long pairs = (long)T * k_max, groups = pairs < E ? pairs : E;
-  return T <= 64 && groups * cdiv(Is, BN / 2) * 2 <= 3L * num_cus() * (Is <= 192 ? 2 : 1);
+// T k_max pairs are what a batch can have, its pairs are that for one budget and about 0.6 of it for mixed ones.  Both
+// GEMMs, us between HIP events, d = 2048 unless said, against what the other rows take:
+//   up to 16 tokens, one block: no group has more rows;
+//   two blocks up to 24 (possible) rows per sub-expert, four up to 56 | the ring driver.  128 of 704, mixed: 100 tokens
+//     196 (four 210) | 230, 300 208 | 235, 512 (48 possible) 224 | 239, 1000 (94) 301 | 250; 256 of 256, mixed: 100 155 | 191,
+//     400 (50) 183 | 197, 700 (88) 207 | 200; 128 of 768, 8 picks each: 100 212 | 261, 400 (25) four 229, two 240 | 270, 700
+//     (44) 236 | 276, 900 (56) 273 | 280, 1000 (62) 299 | 282; 32 of 3584 x 4096, mixed: 64 481 | 515, 200 (50) 488 | 526, 400
+//     (100) 786 | 536; 256 of 32 x 512, mixed: 500 tokens 17.4 | 25.9;
+//   fused: the fused kernel gives a tile a workgroup, so it is good at about as many touched groups as CUs.  512 of
+//     192: up to 64 tokens few ones are touched, 30 tokens 73 | 96, 64 104 | 103 with skewed load, 203 | 242 with even.
+//     With 10 possible rows nearly all are, two rounds of tiles: skewed 200 tokens (12.5) 165 | 185, 140 (8.8) 147 | 122, even
+//     256 (16) 222 | 259, 400 (25) 228 | 263, 700 (44) 270 | 271.  256 of 64 or 128, one round of tiles: 150 tokens 31 | 33
+//     and 43 | 43, 600 37 | 34 and 50 | 44: the fused kernel.
+int ffn_few_blocks(int T, int k_max, int E, bool fused) {
+  const long pairs = (long)T * k_max;
+  if (T <= 16) return 1;
+  if (fused && T > 64 && (E <= num_cus() || pairs < 10L * E || pairs > 24L * E)) return 0;
+  if (pairs <= 24L * E) return 2;
+  return T <= 64 || pairs <= 56L * E ? 4 : 0;
 }
 
 hipError_t launch_gate_up_bf16(const uint16_t* x, const uint16_t* w_gu, const int32_t* sorted_pair,
                                const MTile* tiles, int32_t* hdr, uint16_t* h, int T, int d,
-                               int Is, int k_max, bool few, int max_mtiles, hipStream_t s) {
+                               int Is, int k_max, int few, int max_mtiles, hipStream_t s) {
   return launch_op(GateUpOp{x, w_gu, sorted_pair, h, T, d, Is, k_max}, T, d, Is, few, HDR_DYN_GATE_UP,
                    max_mtiles, tiles, hdr, s);
 }
 
 hipError_t launch_down_bf16(const uint16_t* h, const uint16_t* w_dn, const MTile* tiles,
-                            int32_t* hdr, uint16_t* y, int T, int d, int Is, bool few, int max_mtiles,
+                            int32_t* hdr, uint16_t* y, int T, int d, int Is, int few, int max_mtiles,
                             hipStream_t s) {
   return launch_op(DownOp{h, w_dn, y, d, Is}, T, Is, d, few, HDR_DYN_DOWN, max_mtiles, tiles, hdr, s);
 }

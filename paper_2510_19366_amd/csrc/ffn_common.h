@@ -48,12 +48,12 @@ inline int persistent_grid(long max_items, int per_cu) {  // a multiple of N_XCD
   return (int)((g + N_XCD - 1) / N_XCD * N_XCD);
 }
 
-// bf16 kernels (ffn_bf16.hip); few: tiles for a handful of pairs (see ffn_few_pairs)
+// bf16 kernels (ffn_bf16.hip); few: see ffn_few_blocks
 hipError_t launch_gate_up_bf16(const uint16_t* x, const uint16_t* w_gu, const int32_t* sorted_pair,
                                const MTile* tiles, int32_t* hdr, uint16_t* h, int T, int d,
-                               int Is, int k_max, bool few, int max_mtiles, hipStream_t s);
+                               int Is, int k_max, int few, int max_mtiles, hipStream_t s);
 hipError_t launch_down_bf16(const uint16_t* h, const uint16_t* w_dn, const MTile* tiles,
-                            int32_t* hdr, uint16_t* y, int T, int d, int Is, bool few, int max_mtiles,
+                            int32_t* hdr, uint16_t* y, int T, int d, int Is, int few, int max_mtiles,
                             hipStream_t s);
 
 }  // namespace mp

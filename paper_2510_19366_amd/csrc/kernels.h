@@ -64,13 +64,13 @@ hipError_t launch_ffn_tiles(const int32_t* off, MTile* tiles, int32_t* hdr, int 
                             bool even_tiles, int n_rows, hipStream_t s);
 hipError_t launch_ffn_gate_up(int dtype, const void* x, const void* w_gu, const int32_t* sorted_pair,
                               const MTile* tiles, int32_t* hdr, void* h, int T, int d, int Is,
-                              int k_max, bool few, int max_mtiles, hipStream_t s);
+                              int k_max, int few, int max_mtiles, hipStream_t s);
 hipError_t launch_ffn_down(int dtype, const void* h, const void* w_dn, const MTile* tiles,
-                           int32_t* hdr, void* y, int T, int d, int Is, bool few, int max_mtiles,
+                           int32_t* hdr, void* y, int T, int d, int Is, int few, int max_mtiles,
                            hipStream_t s);
-// bf16: so few pairs that the small tiles of ffn_few_kernel are the faster ones (also than the
-// fused kernel)
-bool ffn_few_pairs(int T, int k_max, int E, int Is);
+// bf16: so few rows per sub-expert that the tiles of ffn_few_kernel are the faster ones: their blocks of 16 slot rows, or
+// 0.  fused: the fused kernel would run instead
+int ffn_few_blocks(int T, int k_max, int E, bool fused);
 
 // fused gate-up -> SwiGLU -> down for narrow sub-experts (bf16); see ffn_fused_bf16.hip
 bool ffn_fused_supported(int T, int d, int Is);

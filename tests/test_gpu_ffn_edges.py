@@ -12,6 +12,9 @@ pytestmark = pytest.mark.gpu
 SIZES = [257, 1, 0, 31, 32, 33, 63, 64, 65, 0, 0, 127, 129, 191, 255, 256, 300, 2]
 LONG = [257, 320, 321, 352, 384, 385, 0, 448, 449, 511, 512, 513, 576, 577, 640, 769, 1025]
 FEW = [1, 0, 33, 0, 0, 30]
+ONE = [1, 0, 9, 2, 0, 3]
+TWO = [1, 0, 15, 16, 17, 31, 32, 33, 0, 47, 5, 64, 48]
+FOUR = [63, 64, 65, 48, 49, 15, 0, 1, 33, 128, 130, 16]
 
 
 def ffn(dtype, x, w_gu, w_dn, group):
@@ -43,6 +46,21 @@ def ffn(dtype, x, w_gu, w_dn, group):
     ("bf16", "auto", FEW, 64, 32),        # small tiles: one K stage; half a stage
     ("bf16", "auto", FEW, 448, 352),
     ("bf16", "auto", FEW, 2048, 192),
+    ("bf16", "auto", ONE, 64, 32),        # at most 16 tokens: one stage, half a stage, more stages than the ring has
+    ("bf16", "auto", ONE, 448, 352),
+    ("bf16", "auto", ONE, 2048, 192),
+    ("bf16", "auto", ONE, 4096, 96),
+    ("bf16", "auto", [16], 320, 1024),
+    ("bf16", "auto", [0, 17], 576, 160),  # one token more
+    # up to 24 rows per group: two blocks of 16 rows at a time, several times (bits at 64 x 32 are compared below; there the
+    # rounding of h, 2^-9 of its norm, reaches y times up to the condition number of 64 x 32 weights: 0.0041 in one row)
+    ("bf16", "auto", TWO, 128, 96),
+    ("bf16", "auto", TWO, 448, 352),
+    ("bf16", "auto", TWO, 1024, 160),
+    ("bf16", "auto", FOUR, 64, 32),       # up to 56: four; waves without weight rows in the last tiles
+    ("bf16", "auto", FOUR, 192, 96),
+    ("bf16", "auto", FOUR, 448, 352),
+    ("bf16", "auto", FOUR, 1024, 160),
     ("f32", "auto", SIZES, 64, 32),
     ("f32", "auto", SIZES, 320, 96),
     ("f32", "auto", FEW, 256, 128),
@@ -101,26 +119,30 @@ def test_a_rows_bits_do_not_depend_on_the_batch_it_is_in(d, Is):
     # a handful of tokens takes the small tiles, hundreds of them the other drivers; every sum over K
     # is one chain in ascending k in all of them
     g = torch.Generator().manual_seed(d + Is)
-    E, T, few = 6, 400, 24
+    E, T, few, one = 6, 400, 24, 13
     x = torch.randn(T, d, generator=g).bfloat16()
     w_gu = (torch.randn(E, 2 * Is, d, generator=g) * 0.05).bfloat16()
     w_dn = (torch.randn(E, d, Is, generator=g) * 0.05).bfloat16()
     group = torch.randint(0, E, (T,), generator=g)
-    assert torch.equal(ffn("bf16", x[:few], w_gu, w_dn, group[:few]), ffn("bf16", x, w_gu, w_dn, group)[:few])
+    whole = ffn("bf16", x, w_gu, w_dn, group)
+    assert torch.equal(ffn("bf16", x[:few], w_gu, w_dn, group[:few]), whole[:few])
+    assert torch.equal(ffn("bf16", x[:one], w_gu, w_dn, group[:one]), whole[:one])
+    for more in (100, 200):  # two and four blocks of 16 rows
+        assert torch.equal(ffn("bf16", x[:more], w_gu, w_dn, group[:more]), whole[:more])
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "f32"])
-def test_a_callers_own_tables_with_groups_of_more_rows_than_tokens(dtype):
+@pytest.mark.parametrize("dtype,T,k_max", [("bf16", 40, 8), ("f32", 40, 8), ("bf16", 10, 32)])
+def test_a_callers_own_tables_with_groups_of_more_rows_than_tokens(dtype, T, k_max):
     # all pairs of a few tokens in one group of 320 rows: a full m-tile and a second one, in the kernels whose
     # m-tiles otherwise have one or two row blocks
-    T, k_max, d, Is, E = 40, 8, 256, 96, 8
+    d, Is, E = 256, 96, 32
     g = torch.Generator().manual_seed(5)
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     x = torch.randn(T, d, generator=g).to(dt)
     w_gu = (torch.randn(E, 2 * Is, d, generator=g) * 0.05).to(dt)
     w_dn = (torch.randn(E, d, Is, generator=g) * 0.05).to(dt)
     pair = torch.randperm(T * k_max, generator=g).to(torch.int32)
-    off = torch.tensor([0, 0, 0, 320, 320, 320, 320, 320, 320], dtype=torch.int32)
+    off = torch.tensor([0] * 3 + [320] * (E - 2), dtype=torch.int32)
     shape = B.make_shape(T, d, E, 1, Is, k_max, dtype)
     y = B.moe_prism_grouped_ffn(shape, x.cuda(), w_gu.cuda(), w_dn.cuda(), off.cuda(), pair.cuda(), B.alloc_workspace(shape))
     v = x[(pair // k_max).long()].double() @ w_gu[2].double().T
