@@ -891,18 +891,24 @@ __global__ __launch_bounds__(NT_) void ffn_short_kernel(Op op, const MTile* __re
 // against the ring driver.  (Weights straight into the registers of the matrix instruction: its lanes are rows, so that
 // every lane's 16 bytes are a cache access of their own, 330 cycles a step.)
 constexpr int FP_WAVE_N = 16;
-template <int MOST>
+// SHORT: K of at most 3 stages (192), one chunk of slot rows; an item is then one chain of latencies, and three
+// workgroups per CU have more of them side by side.  Both GEMMs, us between HIP events, with two per CU and with three:
+// 1 token of the 128 x 4 layer 19.1 -> 18.1, 37 90.1 -> 88.6, 64 tokens on 256 of 64 x 1024 29.8 -> 26.0 (K = 256, 4 stages:
+// 180 tokens on 256 of 256 160 -> 163).
+template <int MOST, bool SHORT>
 struct Few {
+  static_assert(!SHORT || MOST <= 2);
   static constexpr int WAVES = MOST == 4 ? 8 : 4, THREADS = 64 * WAVES, N = WAVES * FP_WAVE_N;
-  static constexpr int NS = MOST == 4 ? 5 : 6, STAGE = FP_WAVE_N * BK * 2, RING = WAVES * NS * STAGE;
-  static constexpr int CHUNK = WAVES * 4096, LDS_BYTES = RING + 2 * CHUNK, PER_CU = MOST == 4 ? 1 : 2;
-  static_assert(PER_CU * LDS_BYTES <= 160 * 1024);
+  static constexpr int NS = SHORT ? 4 : MOST == 4 ? 5 : 6, STAGE = FP_WAVE_N * BK * 2, RING = WAVES * NS * STAGE;
+  static constexpr int CHUNK = WAVES * 4096, LDS_BYTES = RING + (SHORT ? 1 : 2) * CHUNK;
+  static constexpr int PER_CU = 160 * 1024 / LDS_BYTES;
 };
 
-template <class Op, int MOST>
-__global__ __launch_bounds__(Few<MOST>::THREADS) void ffn_few_kernel(Op op, const MTile* __restrict__ tiles,
-                                                                     const int32_t* __restrict__ hdr, int n_tiles_n) {
-  typedef Few<MOST> F;
+template <class Op, int MOST, bool SHORT>
+__global__ __launch_bounds__((Few<MOST, SHORT>::THREADS)) void ffn_few_kernel(Op op, const MTile* __restrict__ tiles,
+                                                                            const int32_t* __restrict__ hdr,
+                                                                            int n_tiles_n) {
+  typedef Few<MOST, SHORT> F;
   extern __shared__ __align__(16) unsigned char fp_smem[];
   constexpr int FP_NS = F::NS, FP_STAGE = F::STAGE, FP_CHUNK = F::CHUNK;
   constexpr int CP = 2, XCP = FP_CHUNK / 1024 / F::WAVES;  // copies per wave: of a stage, of a chunk
@@ -1069,13 +1075,13 @@ static hipError_t launch_ring(const Op& op, int ntn, int grid, int dyn_word, con
   return launch_big<ffn_ring_kernel<Op, HALF, true>>(lds, grid, s, op, tiles, hdr, ntn, dyn_word);
 }
 
-template <class Op, int MOST>
+template <class Op, int MOST, bool SHORT = false>
 static hipError_t launch_few(const Op& op, int n_cols, int max_mtiles, const MTile* tiles, const int32_t* hdr, hipStream_t s) {
-  typedef Few<MOST> F;
-  hipError_t e = raise_lds_limit<ffn_few_kernel<Op, MOST>>(F::LDS_BYTES);
+  typedef Few<MOST, SHORT> F;
+  hipError_t e = raise_lds_limit<ffn_few_kernel<Op, MOST, SHORT>>(F::LDS_BYTES);
   if (e != hipSuccess) return e;
   const int ntn = cdiv(n_cols, F::N / Op::N_PER_ROW), grid = persistent_grid((long)max_mtiles * ntn, F::PER_CU);
-  ffn_few_kernel<Op, MOST><<<grid, F::THREADS, F::LDS_BYTES, s>>>(op, tiles, hdr, ntn);
+  ffn_few_kernel<Op, MOST, SHORT><<<grid, F::THREADS, F::LDS_BYTES, s>>>(op, tiles, hdr, ntn);
   return hipGetLastError();
 }
 
@@ -1083,6 +1089,10 @@ template <class Op>
 static hipError_t launch_op(const Op& op, int T, int K, int n_cols, int few, int dyn_word, int max_mtiles,
                             const MTile* tiles, int32_t* hdr, hipStream_t s) {
   if (op.offsets_fit()) {
+    if constexpr (!Op::GATHER) {
+      if (few == 1 && K <= 3 * BK) return launch_few<Op, 1, true>(op, n_cols, max_mtiles, tiles, hdr, s);
+      if (few == 2 && K <= 3 * BK) return launch_few<Op, 2, true>(op, n_cols, max_mtiles, tiles, hdr, s);
+    }
     if (few == 1) return launch_few<Op, 1>(op, n_cols, max_mtiles, tiles, hdr, s);
     if (few == 2) return launch_few<Op, 2>(op, n_cols, max_mtiles, tiles, hdr, s);
     if (few == 4) return launch_few<Op, 4>(op, n_cols, max_mtiles, tiles, hdr, s);
