@@ -151,9 +151,11 @@ static bool use_fused_ffn(const moe_prism_shape* s) {
   const char* e = getenv("MOE_PRISM_FFN");
   return !(e != nullptr && strcmp(e, "split") == 0);
 }
-// blocks of the tiles for few rows per sub-expert, or 0
+// blocks of the tiles for few rows per sub-expert, or 0 (fp32: see ffn_f32_list)
 static int use_few(const moe_prism_shape* s) {
-  return s->dtype == MOE_PRISM_BF16 ? ffn_few_blocks(s->T, s->k_max, s->n_experts * s->n_sub, use_fused_ffn(s)) : 0;
+  const int E = s->n_experts * s->n_sub;
+  return s->dtype == MOE_PRISM_BF16 ? ffn_few_blocks(s->T, s->k_max, E, use_fused_ffn(s))
+                                    : ffn_f32_list(s->T, s->k_max, E, s->d, s->inter_sub);
 }
 // m-tiles of even length (see mtile_rows) where the two-kernel path follows
 static bool even_tiles(const moe_prism_shape* s) { return use_few(s) != 0 || !use_fused_ffn(s); }
@@ -284,7 +286,9 @@ static int do_route_proxy(const moe_prism_shape* s, const Layout& L, const void*
   if (s->T == 0) return MOE_PRISM_OK;
   MP_LAUNCH(MOE_PRISM_K_FFN_GATE_UP,
             launch_ffn_gate_up(s->dtype, x, w_proxy, q.sp0, tiles, hdr, act, s->T, s->d, rows_half, m,
-                               s->dtype == MOE_PRISM_BF16 ? ffn_few_blocks(s->T, m, N, false) : 0, L.max_mtiles, st));
+                               s->dtype == MOE_PRISM_BF16 ? ffn_few_blocks(s->T, m, N, false)
+                                                            : ffn_f32_list(s->T, m, N, s->d, rows_half),
+                               L.max_mtiles, st));
   MP_LAUNCH(MOE_PRISM_K_PROXY_SELECT,
             launch_proxy_select(s->dtype, act, rows_half, q.ids0, q.w0, q.sl0, k_tok, kappa, ids, w,
                                 hdr, s->T, s->n_sub, r, m, s->k_max, st));

@@ -93,15 +93,17 @@ hipError_t launch_ffn_tiles(const int32_t* off, MTile* tiles, int32_t* hdr, int 
 // eight such row blocks.  Between HIP events, against 128 x 128 tiles of v_fma_f32 (whose
 // workgroups left the chip idle): 64 tokens, d = 256, 32 sub-experts of 128, gate-up 66.3 -> 8.9 us, down 35.6 -> 6.4;
 // 4096 tokens, d = 1024, 32 of 256, 8 picks: both 1274 -> 576.
-constexpr int F32_ROWS = 32, F32_COLS = 64, F32_BLOCKS = FFN_BM / F32_ROWS;
-typedef ChainTile<float, 2, 2, 1, 2, 5> F32Tile;
+constexpr int F32_ROWS = 32, F32_BLOCKS = FFN_BM / F32_ROWS;
+template <int NT>
+using F32Tile = ChainTile<float, 2, 2, 1, NT, NT == 2 ? 5 : 6>;
 
 // Copies of one tile: row `row` of the stage starts at byte offset off(row) behind the base of its
 // operand (slot rows first).  WIDE: an operand of 4 GiB or more, offsets of 64 bits.
-template <bool WIDE, class Rows>
+template <bool WIDE, int NT, class Rows>
 __device__ __forceinline__ void f32_tile(const float* a_base, const float* b_base, int K, Rows&& off,
-                                         unsigned char* smem, f32x4_t (&acc)[1][2]) {
-  constexpr int CP = F32Tile::CP;
+                                         unsigned char* smem, f32x4_t (&acc)[1][NT]) {
+  typedef F32Tile<NT> Tile;
+  constexpr int CP = Tile::CP;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const unsigned char* base[CP];
   uint32_t voff[CP];
@@ -114,7 +116,7 @@ __device__ __forceinline__ void f32_tile(const float* a_base, const float* b_bas
     voff[j] = (uint32_t)o;
     addr[j] = reinterpret_cast<uint64_t>(base[j]) + o;
   }
-  chain_tile<F32Tile>(smem, K / F32Tile::KB, [&](int j, int stage, uint32_t lds) {
+  chain_tile<Tile>(smem, K / Tile::KB, [&](int j, int stage, uint32_t lds) {
     if constexpr (WIDE)
       copy_to_lds16_addr(addr[j] + (uint64_t)stage * 128, lds);
     else
@@ -133,32 +135,41 @@ __device__ __forceinline__ void f32_items(const MTile* __restrict__ tiles, const
   };
   if constexpr (SHORT)
     short_row_blocks<F32_ROWS>(blockIdx.x, gridDim.x, N_XCD, hdr[HDR_MTILES], n_tiles_n,
-                               (T + F32_ROWS - 1) / F32_ROWS, tile, [](auto&& pred) { return lane_mask(pred); },
+                               min((T + F32_ROWS - 1) / F32_ROWS, F32_BLOCKS), tile, [](auto&& pred) { return lane_mask(pred); },
                                each);
   else
     all_row_blocks<F32_ROWS, F32_BLOCKS>(blockIdx.x, gridDim.x, N_XCD, hdr[HDR_MTILES], n_tiles_n, tile, each);
 }
 
-// Weight rows of a tile: per wave column 16 neurons' gate rows, then their up rows.
-template <bool WIDE, bool SHORT>
+// NT = 2: a wave has 16 neurons' gate rows and the same neurons' up rows.  NT = 1: half of the chain per wave; the second
+// wave of a row has the up rows, and hands its sums over through LDS.
+template <bool WIDE, bool SHORT, int NT>
 __global__ __launch_bounds__(256) void ffn_gate_up_f32_kernel(
     const float* __restrict__ x, const float* __restrict__ w_gu,
     const int32_t* __restrict__ sorted_pair, const MTile* __restrict__ tiles,
     const int32_t* __restrict__ hdr, float* __restrict__ h, int d, int Is, int k_max, int T) {
   extern __shared__ __align__(16) unsigned char f_smem[];
+  __shared__ f32x4_t ups[NT == 1 ? 2 * 64 : 1];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, wm = wv >> 1, wn = wv & 1;
-  f32_items<SHORT>(tiles, hdr, Is / 32, T, [&](int g, int row0, int rows, int nt) {  // Is % 32 == 0
-    f32x4_t acc[1][2];
-    f32_tile<WIDE>(x, w_gu + (size_t)g * 2 * Is * d, d, [&](int row) -> size_t {
+  f32_items<SHORT>(tiles, hdr, Is / (16 * NT), T, [&](int g, int row0, int rows, int nt) {  // Is % 32 == 0
+    f32x4_t acc[1][NT];
+    f32_tile<WIDE, NT>(x, w_gu + (size_t)g * 2 * Is * d, d, [&](int row) -> size_t {
       if (row < F32_ROWS) return min(max(sorted_pair[row0 + min(row, rows - 1)] / k_max, 0), T - 1);
       const int b = row - F32_ROWS;
-      return ((b >> 4) & 1 ? Is : 0) + nt * 32 + (b >> 5) * 16 + (b & 15);
+      return ((b >> 4) & 1 ? Is : 0) + nt * (16 * NT) + (b >> 5) * 16 + (b & 15);
     }, f_smem, acc);
-    const int col = nt * 32 + wn * 16 + (lane & 15);
+    f32x4_t up = acc[0][NT - 1];
+    if constexpr (NT == 1) {
+      if (wn == 1) ups[wm * 64 + lane] = acc[0][0];
+      __syncthreads();
+      if (wn == 1) return;
+      up = ups[wm * 64 + lane];
+    }
+    const int col = nt * (16 * NT) + (NT == 2 ? wn * 16 : 0) + (lane & 15);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int row = wm * 16 + 4 * (lane >> 4) + v;
-      const float a = acc[0][0][v], u = acc[0][1][v];
+      const float a = acc[0][0][v], u = up[v];
       if (row < rows) h[(size_t)(row0 + row) * Is + col] = a / (1.0f + expf(-a)) * u;
     }
   });
@@ -171,28 +182,40 @@ __global__ __launch_bounds__(256) void ffn_down_f32_kernel(const float* __restri
                                                            const int32_t* __restrict__ hdr,
                                                            float* __restrict__ y, int T, int d, int Is) {
   extern __shared__ __align__(16) unsigned char f_smem[];
+  constexpr int NT = 2, COLS = F32Tile<NT>::BE;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, wm = wv >> 1, wn = wv & 1;
-  f32_items<SHORT>(tiles, hdr, d / F32_COLS, T, [&](int g, int row0, int rows, int nt) {  // d % 64 == 0
-    f32x4_t acc[1][2];
-    f32_tile<WIDE>(h + (size_t)row0 * Is, w_dn + (size_t)g * d * Is, Is, [&](int row) -> size_t {
-      return row < F32_ROWS ? min(row, rows - 1) : nt * F32_COLS + row - F32_ROWS;
+  f32_items<SHORT>(tiles, hdr, d / COLS, T, [&](int g, int row0, int rows, int nt) {  // d % 64 == 0
+    f32x4_t acc[1][NT];
+    f32_tile<WIDE, NT>(h + (size_t)row0 * Is, w_dn + (size_t)g * d * Is, Is, [&](int row) -> size_t {
+      return row < F32_ROWS ? min(row, rows - 1) : nt * COLS + row - F32_ROWS;
     }, f_smem, acc);
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NT; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int row = wm * 16 + 4 * (lane >> 4) + v, col = nt * F32_COLS + (wn * 2 + j) * 16 + (lane & 15);
+        const int row = wm * 16 + 4 * (lane >> 4) + v, col = nt * COLS + (wn * NT + j) * 16 + (lane & 15);
         if (row < rows) y[(size_t)(row0 + row) * d + col] = acc[0][j][v];
       }
   });
 }
 
 // ---------------------------------------------------------------- launchers
-// A token picks a sub-expert at most once, so a group of a dispatched batch has at most T rows: two row blocks (a
-// caller's own tables may hold more, which then take longer).  Both GEMMs between HIP events, 16 | 64 tokens, 32
-// sub-experts of 256, 8 picks, d = 1024: 30.5 | 30.6 us, with the list of all row blocks 77 | 77; 64 tokens of the
-// tiny layer 15.5 | 27.8.
-static bool f32_short(int T) { return T <= 2 * F32_ROWS; }
+// Which list of row blocks (row_blocks.h) and tile the fp32 kernels take: 0 the list of all row blocks, else the list of
+// first blocks, then second, with gate-up tiles of 1 or 2 column blocks per wave.
+// The list of all eight possible blocks of an m-tile is mostly empty where groups are short, and brings those that exist
+// to few workgroups; but what runs at the same time shares weights.  Both GEMMs between HIP events, us, all | first,
+// second: 64 tokens of 8 picks on 32 sub-experts of 128 x 256 15.5 | 15.3, 100 28 | 16, 300 29 | 18, 1024 32 | 31; 32 of 256 x
+// 1024: 100 79 | 32, 300 79 | 49, 1000 129 | 113; 128 of 256 x 1024 (400 MB): 100 293 | 99, 1000 (62 rows) 294 | 164; 32 of 704 x
+// 2048 (550 MB), 4 picks: 300 (37 possible rows) 161 | 157, 1000 (125) 362 | 382.  So up to 64 possible rows, or 256 where the
+// weights fit the memory-side cache of 256 MB.
+// One column block halves a wave's chain where there are CUs to spare: 64 tokens, 32 of 128 x 256, gate-up 8.1 | 9.4, 100
+// tokens on 32 of 256 x 1024 17.4 | 19.4; 300 tokens there (768 tiles) 29.9 | 28.3, 16 on 128 of them (640) 29.3 | 27.0.
+int ffn_f32_list(int T, int k_max, int E, int d, int Is) {
+  const long pairs = (long)T * k_max, groups = pairs < E ? pairs : E;
+  const bool cached = 12.0 * E * d * Is <= 256e6;
+  if (T > 2 * F32_ROWS && pairs > (cached ? 256L : 64L) * E) return 0;
+  return groups * (Is / 32) * cdiv(cdiv(pairs, E), F32_ROWS) <= 2L * num_cus() ? 1 : 2;
+}
 
 hipError_t launch_ffn_gate_up(int dtype, const void* x, const void* w_gu, const int32_t* sorted_pair,
                               const MTile* tiles, int32_t* hdr, void* h, int T, int d, int Is,
@@ -201,12 +224,22 @@ hipError_t launch_ffn_gate_up(int dtype, const void* x, const void* w_gu, const 
   if (dtype != 0)
     return launch_gate_up_bf16((const uint16_t*)x, (const uint16_t*)w_gu, sorted_pair, tiles, hdr,
                                (uint16_t*)h, T, d, Is, k_max, few, max_mtiles, s);
-  const int grid = persistent_grid((long)max_mtiles * F32_BLOCKS * (Is / 32), 2);
   const bool wide = (long)T * d >= (1L << 30) || (long)Is * d >= (1L << 29);
-  auto* kern = f32_short(T) ? (wide ? ffn_gate_up_f32_kernel<true, true> : ffn_gate_up_f32_kernel<false, true>)
-                            : (wide ? ffn_gate_up_f32_kernel<true, false> : ffn_gate_up_f32_kernel<false, false>);
-  kern<<<grid, 256, F32Tile::LDS_BYTES, s>>>((const float*)x, (const float*)w_gu, sorted_pair, tiles, hdr, (float*)h,
-                                             d, Is, k_max, T);
+  auto run = [&](auto* kern, int nt) {
+    const int grid = persistent_grid((long)max_mtiles * F32_BLOCKS * (Is / (16 * nt)), nt == 1 ? 4 : 2);
+    const int lds = nt == 1 ? F32Tile<1>::LDS_BYTES : F32Tile<2>::LDS_BYTES;
+    kern<<<grid, 256, lds, s>>>((const float*)x, (const float*)w_gu, sorted_pair, tiles, hdr, (float*)h, d, Is, k_max, T);
+  };
+  if (few == 1) {
+    if (wide) run(ffn_gate_up_f32_kernel<true, true, 1>, 1);
+    else run(ffn_gate_up_f32_kernel<false, true, 1>, 1);
+  } else if (few == 2) {
+    if (wide) run(ffn_gate_up_f32_kernel<true, true, 2>, 2);
+    else run(ffn_gate_up_f32_kernel<false, true, 2>, 2);
+  } else {
+    if (wide) run(ffn_gate_up_f32_kernel<true, false, 2>, 2);
+    else run(ffn_gate_up_f32_kernel<false, false, 2>, 2);
+  }
   return hipGetLastError();
 }
 
@@ -217,11 +250,11 @@ hipError_t launch_ffn_down(int dtype, const void* h, const void* w_dn, const MTi
   if (dtype != 0)
     return launch_down_bf16((const uint16_t*)h, (const uint16_t*)w_dn, tiles, hdr, (uint16_t*)y, T, d,
                             Is, few, max_mtiles, s);
-  const int grid = persistent_grid((long)max_mtiles * F32_BLOCKS * (d / F32_COLS), 2);
+  const int grid = persistent_grid((long)max_mtiles * F32_BLOCKS * (d / F32Tile<2>::BE), 2);
   const bool wide = (long)Is * d >= (1L << 30);
-  auto* kern = f32_short(T) ? (wide ? ffn_down_f32_kernel<true, true> : ffn_down_f32_kernel<false, true>)
+  auto* kern = few != 0 ? (wide ? ffn_down_f32_kernel<true, true> : ffn_down_f32_kernel<false, true>)
                             : (wide ? ffn_down_f32_kernel<true, false> : ffn_down_f32_kernel<false, false>);
-  kern<<<grid, 256, F32Tile::LDS_BYTES, s>>>((const float*)h, (const float*)w_dn, tiles, hdr, (float*)y, T, d, Is);
+  kern<<<grid, 256, F32Tile<2>::LDS_BYTES, s>>>((const float*)h, (const float*)w_dn, tiles, hdr, (float*)y, T, d, Is);
   return hipGetLastError();
 }
 

@@ -71,6 +71,8 @@ hipError_t launch_ffn_down(int dtype, const void* h, const void* w_dn, const MTi
 // bf16: so few rows per sub-expert that the tiles of ffn_few_kernel are the faster ones: their blocks of 16 slot rows, or
 // 0.  fused: the fused kernel would run instead
 int ffn_few_blocks(int T, int k_max, int E, bool fused);
+// fp32: the list of row blocks and the tile (`few` of the launchers)
+int ffn_f32_list(int T, int k_max, int E, int d, int Is);
 
 // fused gate-up -> SwiGLU -> down for narrow sub-experts (bf16); see ffn_fused_bf16.hip
 bool ffn_fused_supported(int T, int d, int Is);

@@ -64,6 +64,10 @@ def ffn(dtype, x, w_gu, w_dn, group):
     ("f32", "auto", SIZES, 64, 32),
     ("f32", "auto", SIZES, 320, 96),
     ("f32", "auto", FEW, 256, 128),
+    ("f32", "auto", TWO, 64, 32),         # several row blocks per group from the short list
+    ("f32", "auto", FOUR, 320, 96),
+    ("f32", "auto", [256, 3] * 30 + [40], 64, 640),  # two column blocks per wave
+    ("f32", "auto", [300, 600, 1], 64, 32),  # the list of all row blocks
 ])
 def test_group_sizes_at_the_edges_of_the_tiles(dtype, path, sizes, d, Is, monkeypatch):
     monkeypatch.setenv("MOE_PRISM_FFN", path)
