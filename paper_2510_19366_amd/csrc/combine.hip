@@ -1,6 +1,6 @@
 // Combine stage (Sec. 3.2.2): out[t,:] = sum_{j<k_t} w[t,j] * y[slot(t,j),:].
-// One workgroup per token, 16-byte column vectors per thread, picks visited in
-// ascending j (two batches of four row loads alternate in flight) with fp32 accumulation and a
+// One workgroup per token (few tokens: a wave per 64 column vectors), 16-byte column vectors per thread, picks
+// visited in ascending j (two batches of four row loads alternate in flight) with fp32 accumulation and a
 // single final rounding.  No atomics:
 // every output element has exactly one writer, so the result is reproducible.
 #include "kernels.h"
@@ -52,7 +52,7 @@ template <> struct Vec<1> {
 // The token's slots and weights are fetched once into LDS (one element per thread), padded to
 // a whole number of batches with slot-less picks, so the row loop below never waits for an
 // index before it can issue its row loads.
-constexpr int CB_RU = 4;        // rows per batch
+constexpr int CB_RU = 4;        // rows per batch (a token's picks are padded to a multiple)
 constexpr int CB_CHUNK = 1024;  // = the largest k_max the library accepts (a multiple of CB_RU)
 
 template <int DT>
@@ -119,9 +119,81 @@ __global__ __launch_bounds__(256) void combine_kernel(const void* __restrict__ y
   }
 }
 
+// Few tokens: the time is one chain of latencies.  Above, a row's slot comes out of LDS before its load can be issued, and
+// at most eight rows are in flight.  Here a wave has 64 of a token's column vectors and no LDS: lane l holds the slot and
+// weight of pick l, read as scalars, and up to 32 rows (fp32: 16, more end in scratch) are in flight.  The same additions in
+// the same order.
+template <int DT>
+__global__ __launch_bounds__(64) void combine_few_kernel(const void* __restrict__ y,
+                                                         const int32_t* __restrict__ slot_of_pair,
+                                                         const float* __restrict__ w,
+                                                         const int32_t* __restrict__ k_tok,
+                                                         void* __restrict__ out, int d, int k_max, int n_rows) {
+  constexpr int N = Vec<DT>::N, RU = DT == 0 ? 8 : 16;
+  const int t = blockIdx.x, lane = threadIdx.x;
+  const int col = (blockIdx.y * 64 + lane) * N, at = min(col, d - N);  // lanes beyond d keep their picks
+  int kt = k_tok[t];
+  kt = kt < 0 ? 0 : (kt > k_max ? k_max : kt);
+  const int ktp = (kt + CB_RU - 1) / CB_RU * CB_RU;  // as above
+  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  for (int c = 0; c < k_max; c += 64) {
+    const int j = c + lane;
+    const bool in = j < k_max;
+    const int slot = in ? slot_of_pair[(size_t)t * k_max + j] : -1;
+    const float wt = in ? w[(size_t)t * k_max + j] : 0.0f;
+    const bool ok = j < kt && slot >= 0 && slot < n_rows;
+    const int sl = ok ? slot : -1;
+    const int wj = __float_as_int(ok ? wt : 0.0f);
+    const int n = min(ktp - c, 64);
+    if (n <= 0) break;
+    auto issue = [&](int j0, u32x4_t (&r)[RU]) {
+#pragma unroll
+      for (int u = 0; u < RU; ++u) {
+        const int s = __builtin_amdgcn_readlane(sl, j0 + u);
+        u32x4_t v = {0u, 0u, 0u, 0u};
+        if (s >= 0) v = Vec<DT>::load(y, (size_t)s * d + at);
+        r[u] = v;
+      }
+    };
+    auto consume = [&](int j0, const u32x4_t (&r)[RU]) {
+#pragma unroll
+      for (int u = 0; u < RU; ++u)
+        if (j0 + u / CB_RU * CB_RU < n) {
+          const float ws = __int_as_float(__builtin_amdgcn_readlane(wj, j0 + u));
+          float v[8];
+          const u32x4_t raw = r[u];
+          Vec<DT>::widen(raw, v);
+#pragma unroll
+          for (int e = 0; e < N; ++e) acc[e] = fmaf(ws, v[e], acc[e]);
+        }
+    };
+    for (int j0 = 0; j0 < n; j0 += 2 * RU) {
+      u32x4_t ra[RU], rb[RU];
+      issue(j0, ra);
+      if (j0 + RU < n) issue(j0 + RU, rb);
+      consume(j0, ra);
+      if (j0 + RU < n) consume(j0 + RU, rb);
+    }
+  }
+  if (col < d) Vec<DT>::store(out, (size_t)t * d + col, acc);
+}
+
 hipError_t launch_combine(int dtype, const void* y, const int32_t* slot_of_pair, const float* w,
                           const int32_t* k_tok, void* out, int T, int d, int k_max, hipStream_t s) {
   if (T == 0) return hipSuccess;
+  const int waves = (d + 64 * (dtype == 0 ? 4 : 8) - 1) / (64 * (dtype == 0 ? 4 : 8));
+  // Calls back to back (which hides all below some 4.6 us), us, a workgroup per token | a wave per 64 column vectors, bf16, d =
+  // 2048, 8 to 32 picks (four waves per token): 4 tokens 6.0 | 4.9, 100 6.3 | 4.9, 256 7.3 | 5.3, 350 9.4 | 6.6, 512 10.2 | 8.4,
+  // 1024 14.9 | 17.2, 4096 63 | 82; fp32, 9 tokens of 60 to 130 picks 14.7 | 9.8.  So up to eight waves per CU.  Up to 8 picks
+  // all rows are in flight either way: 256 tokens of 2 to 8, d = 4096, 4.8 | 4.6, fp32 64 tokens, d = 256, 4.6 | 4.7.
+  if (k_max > 2 * CB_RU && (long)T * waves <= 8L * num_cus()) {
+    const dim3 grid(T, waves);
+    if (dtype == 0)
+      combine_few_kernel<0><<<grid, 64, 0, s>>>(y, slot_of_pair, w, k_tok, out, d, k_max, T * k_max);
+    else
+      combine_few_kernel<1><<<grid, 64, 0, s>>>(y, slot_of_pair, w, k_tok, out, d, k_max, T * k_max);
+    return hipGetLastError();
+  }
   if (dtype == 0)
     combine_kernel<0><<<T, 256, 0, s>>>(y, slot_of_pair, w, k_tok, out, d, k_max, T * k_max);
   else
