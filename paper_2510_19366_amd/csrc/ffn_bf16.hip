@@ -11,7 +11,8 @@
 //     into a double-buffered, XOR-swizzled LDS tile, one slab ahead of the MFMAs.  The weight block is the MFMA's first operand and its
 //     rows are fed in a permuted order, so that a lane ends up with 8 or 16 consecutive output
 //     columns of one slot row and stores them as 16-byte words (ffn_few_kernel likewise).
-// Few rows per sub-expert take ffn_few_kernel (tiles of 64 or 128 weight rows, see ffn_few_blocks).
+// Few rows per sub-expert take ffn_few_kernel (tiles of 64 or 128 weight rows, see ffn_few_blocks), and so does the
+// gate-up of up to 32 neurons.
 // Narrow sub-experts (Is in {64, 128, 192}) take the fused kernel in ffn_fused_bf16.hip
 // instead; these two kernels serve every other shape.
 #include <type_traits>
@@ -890,25 +891,34 @@ __global__ __launch_bounds__(NT_) void ffn_short_kernel(Op op, const MTile* __re
 // weight and slot rows behind a barrier 24.4; 100 tokens of 4 to 12 on 128 of 704 231 -> 196 us (5.6 TB/s of weights)
 // against the ring driver.  (Weights straight into the registers of the matrix instruction: its lanes are rows, so that
 // every lane's 16 bytes are a cache access of their own, 330 cycles a step.)
-constexpr int FP_WAVE_N = 16;
+constexpr int FP_WAVE_N = 16, NARROW_COLS = 32;
 // SHORT: K of at most 3 stages (192), one chunk of slot rows; an item is then one chain of latencies, and three
 // workgroups per CU have more of them side by side.  Both GEMMs, us between HIP events, with two per CU and with three:
 // 1 token of the 128 x 4 layer 19.1 -> 18.1, 37 90.1 -> 88.6, 64 tokens on 256 of 64 x 1024 29.8 -> 26.0 (K = 256, 4 stages:
 // 180 tokens on 256 of 256 160 -> 163).
-template <int MOST, bool SHORT>
+template <int MOST, bool SHORT, bool NARROW>
 struct Few {
-  static_assert(!SHORT || MOST <= 2);
-  static constexpr int WAVES = MOST == 4 ? 8 : 4, THREADS = 64 * WAVES, N = WAVES * FP_WAVE_N;
-  static constexpr int NS = SHORT ? 4 : MOST == 4 ? 5 : 6, STAGE = FP_WAVE_N * BK * 2, RING = WAVES * NS * STAGE;
+  static_assert((!SHORT || MOST <= 2) && (!NARROW || MOST == 4));
+  static constexpr int WAVES = MOST == 4 && !NARROW ? 8 : 4, THREADS = 64 * WAVES, N = WAVES * FP_WAVE_N;
+  static constexpr int NS = SHORT || NARROW ? 4 : MOST == 4 ? 5 : 6, STAGE = FP_WAVE_N * BK * 2, RING = WAVES * NS * STAGE;
   static constexpr int CHUNK = WAVES * 4096, LDS_BYTES = RING + (SHORT ? 1 : 2) * CHUNK;
-  static constexpr int PER_CU = 160 * 1024 / LDS_BYTES;
+  static constexpr int PER_CU = 160 * 1024 / LDS_BYTES, PARTS = NARROW ? BM / (16 * MOST) : 1;
 };
 
-template <class Op, int MOST, bool SHORT>
-__global__ __launch_bounds__((Few<MOST, SHORT>::THREADS)) void ffn_few_kernel(Op op, const MTile* __restrict__ tiles,
+// NARROW (gate-up of up to 32 neurons, any number of rows, K > 192): the ring driver's tile has 256 weight rows, of which only 64
+// exist, and one workgroup per m-tile, so that CUs without one are idle.  Here four waves have the 64 weight rows, and the
+// blocks of 64 slot rows of an m-tile are items of their own, PARTS of them one behind the other in the list, so that they
+// meet in an L2 with their weights; two workgroups per CU.  Bound by what the copies bring from L2 (twice the slot rows' bytes).
+// Gate-up between HIP events, us, ring driver | this: d = 2048, 256 sub-experts of 32, 8 picks, skewed: 2000 tokens 42.1 | 33.8,
+// 4096 69.6 | 44.6, 8192 81.1 | 67.9; even load on 128 of them: 1000 36.2 | 25.9, 4096 44.2 | 35.6, 16384 123 | 93; 64 of 32 x
+// 512: 1024 18.0 | 9.4, 8192 21.7 | 17.9; 128 of 32 x 4096: 4096 76.5 | 69.7.  (Blocks of 32 slot rows: 32.6, 42.2, 119 on the
+// 128.)  64 neurons are two such tiles, which read the slot rows twice, and half of a ring tile: 4096 tokens 45 | 56.  Where
+// few == 4 applies, it is ahead with even load (600 tokens on the 128 18.3 | 23.9).
+template <class Op, int MOST, bool SHORT, bool NARROW>
+__global__ __launch_bounds__((Few<MOST, SHORT, NARROW>::THREADS)) void ffn_few_kernel(Op op, const MTile* __restrict__ tiles,
                                                                             const int32_t* __restrict__ hdr,
                                                                             int n_tiles_n) {
-  typedef Few<MOST, SHORT> F;
+  typedef Few<MOST, SHORT, NARROW> F;
   extern __shared__ __align__(16) unsigned char fp_smem[];
   constexpr int FP_NS = F::NS, FP_STAGE = F::STAGE, FP_CHUNK = F::CHUNK;
   constexpr int CP = 2, XCP = FP_CHUNK / 1024 / F::WAVES;  // copies per wave: of a stage, of a chunk
@@ -1035,15 +1045,16 @@ __global__ __launch_bounds__((Few<MOST, SHORT>::THREADS)) void ffn_few_kernel(Op
       if (on) op.few_store(sc, b * 16 + r, g, acc[b]);
     raw_barrier();  // the first chunk is copied again
   };
-  const ItemRange ir = xcd_items(hdr[HDR_MTILES] * n_tiles_n);
-  for (int item = ir.begin; item < ir.end; item += ir.step) {
+  const ItemRange ir = xcd_items(hdr[HDR_MTILES] * n_tiles_n * F::PARTS);
+  for (int i = ir.begin; i < ir.end; i += ir.step) {
+    const int item = i / F::PARTS, part = i % F::PARTS;
     const MTile t = tiles[item / n_tiles_n];
     Sc sc;
     sc.g = uni(t.g);
     constexpr int PER_WAVE = FP_WAVE_N / Op::N_PER_ROW;
     const int n0 = (item % n_tiles_n * F::WAVES + wv) * PER_WAVE;
     sc.n0 = min(n0, op.n_cols() - PER_WAVE);  // of eight waves the last tile's second four may have none: again the last rows
-    for (int row = 0; row < uni(t.rows); row += 16 * MOST) {
+    for (int row = part * 16 * MOST; row < uni(t.rows); row += F::PARTS * 16 * MOST) {
       sc.row0 = uni(t.row0) + row;
       sc.rows = min(16 * MOST, uni(t.rows) - row);
       if (MOST == 2 && sc.rows <= 16) tile(sc, n0 == sc.n0, std::integral_constant<int, 1>{});
@@ -1075,13 +1086,14 @@ static hipError_t launch_ring(const Op& op, int ntn, int grid, int dyn_word, con
   return launch_big<ffn_ring_kernel<Op, HALF, true>>(lds, grid, s, op, tiles, hdr, ntn, dyn_word);
 }
 
-template <class Op, int MOST, bool SHORT = false>
+template <class Op, int MOST, bool SHORT = false, bool NARROW = false>
 static hipError_t launch_few(const Op& op, int n_cols, int max_mtiles, const MTile* tiles, const int32_t* hdr, hipStream_t s) {
-  typedef Few<MOST, SHORT> F;
-  hipError_t e = raise_lds_limit<ffn_few_kernel<Op, MOST, SHORT>>(F::LDS_BYTES);
+  typedef Few<MOST, SHORT, NARROW> F;
+  hipError_t e = raise_lds_limit<ffn_few_kernel<Op, MOST, SHORT, NARROW>>(F::LDS_BYTES);
   if (e != hipSuccess) return e;
-  const int ntn = cdiv(n_cols, F::N / Op::N_PER_ROW), grid = persistent_grid((long)max_mtiles * ntn, F::PER_CU);
-  ffn_few_kernel<Op, MOST, SHORT><<<grid, F::THREADS, F::LDS_BYTES, s>>>(op, tiles, hdr, ntn);
+  const int ntn = cdiv(n_cols, F::N / Op::N_PER_ROW);
+  const int grid = persistent_grid((long)max_mtiles * ntn * F::PARTS, F::PER_CU);
+  ffn_few_kernel<Op, MOST, SHORT, NARROW><<<grid, F::THREADS, F::LDS_BYTES, s>>>(op, tiles, hdr, ntn);
   return hipGetLastError();
 }
 
@@ -1096,6 +1108,9 @@ static hipError_t launch_op(const Op& op, int T, int K, int n_cols, int few, int
     if (few == 1) return launch_few<Op, 1>(op, n_cols, max_mtiles, tiles, hdr, s);
     if (few == 2) return launch_few<Op, 2>(op, n_cols, max_mtiles, tiles, hdr, s);
     if (few == 4) return launch_few<Op, 4>(op, n_cols, max_mtiles, tiles, hdr, s);
+    if constexpr (Op::GATHER) {
+      if (n_cols <= NARROW_COLS && K > 3 * BK) return launch_few<Op, 4, false, true>(op, n_cols, max_mtiles, tiles, hdr, s);
+    }
   }
   const int ntn = cdiv(n_cols, BN / Op::N_PER_ROW);
   const int grid = persistent_grid((long)max_mtiles * ntn, 1);

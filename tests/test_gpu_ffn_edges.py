@@ -61,6 +61,8 @@ def ffn(dtype, x, w_gu, w_dn, group):
     ("bf16", "auto", FOUR, 192, 96),
     ("bf16", "auto", FOUR, 448, 352),
     ("bf16", "auto", FOUR, 1024, 160),
+    ("bf16", "auto", LONG, 256, 32),      # gate-up of 32 neurons: row blocks of an m-tile as items of their own
+    ("bf16", "auto", LONG, 448, 32),
     ("f32", "auto", SIZES, 64, 32),
     ("f32", "auto", SIZES, 320, 96),
     ("f32", "auto", FEW, 256, 128),
@@ -118,7 +120,7 @@ def test_swiglu_of_huge_and_infinite_gates(path, T, d, Is, monkeypatch):
                                    msg=lambda m: f"gate {a[t]}: {m}")
 
 
-@pytest.mark.parametrize("d,Is", [(64, 32), (448, 192), (2048, 192), (320, 352), (1024, 704)])
+@pytest.mark.parametrize("d,Is", [(64, 32), (320, 32), (2048, 32), (448, 192), (2048, 192), (320, 352), (1024, 704)])
 def test_a_rows_bits_do_not_depend_on_the_batch_it_is_in(d, Is):
     # a handful of tokens takes the small tiles, hundreds of them the other drivers; every sum over K
     # is one chain in ascending k in all of them
