@@ -450,14 +450,41 @@ hipError_t launch_topk(const float* logits, const int32_t* k_tok, int32_t* ids, 
 // taken, score descending, equal scores to the smaller index.  Selected sub-experts are
 // appended in rank order with the expert's weight: rank j writes at the sum of the ranks'
 // allocations before it, the last rank also pads the tail.
-template <typename ActT>
-__device__ __forceinline__ float act_abs(const ActT* p);
-template <>
-__device__ __forceinline__ float act_abs<float>(const float* p) { return fabsf(*p); }
-template <>
-__device__ __forceinline__ float act_abs<uint16_t>(const uint16_t* p) { return fabsf(bf16_to_f32(*p)); }
+// A chain of latencies: budget, allocations, slot, activations.  What a step needs is requested at once: the allocations of
+// eight ranks, and of every sub-expert the next activation, or four where r % 4 == 0 (rows of act are whole multiples
+// of 32 elements, so that four are aligned).  MOST: 4 or 16, the largest S.  Between HIP events, one activation after the other
+// | this: 300 tokens of 8 experts, S = r = 4, 15.9 | 7.6 us, 4096 15.3 | 8.1, 16384 23.4 | 12.0.
+template <int N>
+__device__ __forceinline__ void act_abs(const float* p, float (&v)[N]) {
+  float f[N];
+  __builtin_memcpy(f, __builtin_assume_aligned(p, 4 * N), sizeof(f));
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = fabsf(f[i]);
+}
+template <int N>
+__device__ __forceinline__ void act_abs(const uint16_t* p, float (&v)[N]) {
+  uint16_t f[N];
+  __builtin_memcpy(f, __builtin_assume_aligned(p, 2 * N), sizeof(f));
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = fabsf(bf16_to_f32(f[i]));
+}
+// sums of |a[n r + c]| over ascending c
+template <int N, int MOST, typename ActT>
+__device__ __forceinline__ void proxy_sums(const ActT* a, int S, int r, float (&sum)[MOST]) {
+#pragma unroll
+  for (int n = 0; n < MOST; ++n) sum[n] = 0.0f;
+  for (int c = 0; c < r; c += N) {
+    float v[MOST][N];
+#pragma unroll
+    for (int n = 0; n < MOST; ++n) act_abs(a + min(n, S - 1) * r + c, v[n]);
+#pragma unroll
+    for (int n = 0; n < MOST; ++n)
+#pragma unroll
+      for (int i = 0; i < N; ++i) sum[n] += v[n][i];
+  }
+}
 
-template <typename ActT>
+template <typename ActT, int MOST>
 __global__ __launch_bounds__(256) void proxy_select_kernel(
     const ActT* __restrict__ act, int act_ld, const int32_t* __restrict__ ids0,
     const float* __restrict__ w0, const int32_t* __restrict__ slot0,
@@ -480,7 +507,13 @@ __global__ __launch_bounds__(256) void proxy_select_kernel(
     return (e < 0 || slot < 0) ? 0 : kap;
   };
   int pos = 0;
-  for (int jj = 0; jj < j; ++jj) pos += alloc(jj);
+  for (int j0 = 0; j0 < j; j0 += 8) {
+    int al[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) al[u] = alloc(min(j0 + u, j));
+#pragma unroll
+    for (int u = 0; u < 8; ++u) pos += j0 + u < j ? al[u] : 0;
+  }
   const int kap = alloc(j);
   int32_t* o = ids + (size_t)t * k_max;
   float* ow = w + (size_t)t * k_max;
@@ -488,22 +521,23 @@ __global__ __launch_bounds__(256) void proxy_select_kernel(
     const int e = ids0[idx];
     const ActT* a = act + (size_t)slot0[idx] * act_ld;
     const float inv_r = 1.0f / (float)r;
-    float sc[PROXY_MAX_SUB];
+    float sc[MOST];
+    if (r % 4 == 0) proxy_sums<4>(a, S, r, sc);
+    else proxy_sums<1>(a, S, r, sc);
 #pragma unroll
-    for (int n = 0; n < PROXY_MAX_SUB; ++n) {
-      float sum = 0.0f;
-      if (n < S)
-        for (int c = 0; c < r; ++c) sum += act_abs<ActT>(a + n * r + c);
-      sc[n] = n < S ? sum * inv_r : -1.0f;  // scores are >= 0: -1 marks taken or absent
-    }
+    for (int n = 0; n < MOST; ++n) sc[n] = n < S ? sc[n] * inv_r : -1.0f;  // scores are >= 0: -1 marks taken or absent
     const float wj = w0[idx];
     for (int i = 0; i < kap && pos < k_max; ++i) {
       int best = 0;
+      float most = sc[0];
 #pragma unroll
-      for (int n = 1; n < PROXY_MAX_SUB; ++n)
-        if (sc[n] > sc[best]) best = n;
+      for (int n = 1; n < MOST; ++n)
+        if (sc[n] > most) {
+          most = sc[n];
+          best = n;
+        }
 #pragma unroll
-      for (int n = 0; n < PROXY_MAX_SUB; ++n)
+      for (int n = 0; n < MOST; ++n)
         if (n == best) sc[n] = -1.0f;
       o[pos] = e * S + best;
       ow[pos] = wj;
@@ -522,13 +556,18 @@ hipError_t launch_proxy_select(int dtype, const void* act, int act_ld, const int
                                const int32_t* kappa, int32_t* ids, float* w, int32_t* hdr, int T,
                                int S, int r, int m, int k_max, hipStream_t s) {
   if (T == 0) return hipSuccess;
-  if (dtype == 0)
-    proxy_select_kernel<float><<<cdiv(T * m, 256), 256, 0, s>>>((const float*)act, act_ld, ids0, w0, slot0,
-                                                           k_tok, kappa, ids, w, hdr, T, S, r, m, k_max);
-  else
-    proxy_select_kernel<uint16_t><<<cdiv(T * m, 256), 256, 0, s>>>((const uint16_t*)act, act_ld, ids0, w0,
-                                                              slot0, k_tok, kappa, ids, w, hdr, T, S, r,
-                                                              m, k_max);
+  auto run = [&](auto* kern, auto* a) {
+    kern<<<cdiv(T * m, 256), 256, 0, s>>>(a, act_ld, ids0, w0, slot0, k_tok, kappa, ids, w, hdr, T, S, r, m, k_max);
+  };
+  if (dtype == 0) {
+    const float* a = (const float*)act;
+    if (S <= 4) run(proxy_select_kernel<float, 4>, a);
+    else run(proxy_select_kernel<float, PROXY_MAX_SUB>, a);
+  } else {
+    const uint16_t* a = (const uint16_t*)act;
+    if (S <= 4) run(proxy_select_kernel<uint16_t, 4>, a);
+    else run(proxy_select_kernel<uint16_t, PROXY_MAX_SUB>, a);
+  }
   return hipGetLastError();
 }
 
