@@ -151,55 +151,77 @@ static bool use_fused_ffn(const moe_prism_shape* s) {
   const char* e = getenv("MOE_PRISM_FFN");
   return !(e != nullptr && strcmp(e, "split") == 0);
 }
-// blocks of the tiles for few rows per sub-expert, or 0 (fp32: see ffn_f32_list)
-static int use_few(const moe_prism_shape* s) {
-  const int E = s->n_experts * s->n_sub;
-  return s->dtype == MOE_PRISM_BF16 ? ffn_few_blocks(s->T, s->k_max, E, use_fused_ffn(s))
-                                    : ffn_f32_list(s->T, s->k_max, E, s->d, s->inter_sub);
+// What follows a dispatch: blocks of the tiles for few rows per sub-expert, or 0 (fp32: see ffn_f32_list), and how the
+// groups are cut for it.  Few rows: into the tiles of ffn_few_kernel, which then are at most 2 E (16 rows and 16 tokens, 32
+// and 24 E pairs, 64 and 64 tokens or 56 E pairs: no more than E beside the last one of each group).  Else into
+// tiles of FFN_BM, of even length where the two-kernel path follows.
+// Made once per call: the table and the kernels that read it go by the same one, whatever becomes of the environment.
+struct FfnPlan {
+  bool fused;
+  int few;
+  TileCut cut;
+  int max_tiles;
+};
+static FfnPlan plan_ffn(const Layout& L, int dtype, int T, int k, int E, int d, int Is, bool fused) {
+  FfnPlan p{fused, 0, {8, true}, L.max_mtiles};
+  static_assert(FFN_BM == 1 << 8);
+  if (dtype != MOE_PRISM_BF16) {
+    p.few = ffn_f32_list(T, k, E, d, Is);
+    return p;
+  }
+  p.few = ffn_few_blocks(T, k, E, d, Is, fused);
+  if (p.few != 0) {
+    p.fused = false;
+    p.cut = {p.few == 4 ? 6 : p.few == 2 ? 5 : 4, false};
+    p.max_tiles = 2 * L.max_mtiles;
+  } else if (fused) {
+    p.cut.even = false;
+  }
+  return p;
 }
-// m-tiles of even length (see mtile_rows) where the two-kernel path follows
-static bool even_tiles(const moe_prism_shape* s) { return use_few(s) != 0 || !use_fused_ffn(s); }
+static FfnPlan plan_ffn(const Layout& L, const moe_prism_shape* s) {
+  return plan_ffn(L, s->dtype, s->T, s->k_max, s->n_experts * s->n_sub, s->d, s->inter_sub, use_fused_ffn(s));
+}
 
 // the dispatch of T tokens with up to k_max picks out of E groups
 static int do_dispatch_over(const Layout& L, const int32_t* ids, int32_t* cnt, int32_t* off,
                             int32_t* sorted_pair, int32_t* slot_of_pair, int32_t* chunk, int32_t* hdr,
-                            MTile* tiles, bool even, int T, int E, int k_max, hipStream_t st) {
+                            MTile* tiles, const FfnPlan& p, int T, int E, int k_max, hipStream_t st) {
   if (dispatch_is_small(T, E, k_max)) {
     MP_LAUNCH(MOE_PRISM_K_DISPATCH_PLACE, launch_dispatch_small(ids, cnt, off, hdr, sorted_pair, slot_of_pair,
-                                                                tiles, L.max_mtiles, T, E, k_max, st));
+                                                                tiles, p.max_tiles, p.cut, T, E, k_max, st));
     return MOE_PRISM_OK;
   }
   MP_LAUNCH(MOE_PRISM_K_DISPATCH_COUNT, launch_dispatch_count(ids, chunk, T, E, k_max, st));
   MP_LAUNCH(MOE_PRISM_K_DISPATCH_SCAN, launch_dispatch_scan(chunk, cnt, T, E, st));
   MP_LAUNCH(MOE_PRISM_K_DISPATCH_PLACE,
-            launch_dispatch_place(ids, chunk, cnt, off, hdr, sorted_pair, slot_of_pair, tiles, L.max_mtiles, even,
+            launch_dispatch_place(ids, chunk, cnt, off, hdr, sorted_pair, slot_of_pair, tiles, p.max_tiles, p.cut,
                                   T, E, k_max, st));
   return MOE_PRISM_OK;
 }
 
-// with_tiles: the place kernel also builds the grouped FFN's m-tile table (the layer entry
+// plan: the place kernel also builds that FFN's m-tile table (the layer entry
 // points, where the FFN follows on the same offsets; do_ffn is then told not to rebuild it)
 static int do_dispatch(const moe_prism_shape* s, const Layout& L, const int32_t* ids, int32_t* cnt,
                        int32_t* off, int32_t* sorted_pair, int32_t* slot_of_pair, char* ws,
-                       hipStream_t st, bool with_tiles = false) {
+                       hipStream_t st, const FfnPlan* plan = nullptr) {
   const int E = s->n_experts * s->n_sub;
   int32_t* hdr = reinterpret_cast<int32_t*>(ws + L.hdr);
   int32_t* chunk = reinterpret_cast<int32_t*>(ws + L.chunk_cnt);
-  MTile* tiles = with_tiles ? reinterpret_cast<MTile*>(ws + L.tiles) : nullptr;
-  return do_dispatch_over(L, ids, cnt, off, sorted_pair, slot_of_pair, chunk, hdr, tiles, even_tiles(s), s->T,
-                          E, s->k_max, st);
+  MTile* tiles = plan != nullptr ? reinterpret_cast<MTile*>(ws + L.tiles) : nullptr;
+  return do_dispatch_over(L, ids, cnt, off, sorted_pair, slot_of_pair, chunk, hdr, tiles,
+                          plan != nullptr ? *plan : FfnPlan{}, s->T, E, s->k_max, st);
 }
 
 static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, const void* w_gu,
                   const void* w_dn, const int32_t* off, const int32_t* sorted_pair, void* y,
-                  char* ws, hipStream_t st, bool traffic_probe = false, bool tiles_built = false) {
+                  char* ws, hipStream_t st, const FfnPlan& p, bool traffic_probe = false, bool tiles_built = false) {
   const int E = s->n_experts * s->n_sub;
   int32_t* hdr = reinterpret_cast<int32_t*>(ws + L.hdr);
   MTile* tiles = reinterpret_cast<MTile*>(ws + L.tiles);
   void* h = ws + L.h;
   if (!tiles_built)
-    MP_LAUNCH(MOE_PRISM_K_FFN_TILES, launch_ffn_tiles(off, tiles, hdr, E, L.max_mtiles, !traffic_probe && even_tiles(s),
-                                                      s->T * s->k_max, st));
+    MP_LAUNCH(MOE_PRISM_K_FFN_TILES, launch_ffn_tiles(off, tiles, hdr, E, p.max_tiles, p.cut, s->T * s->k_max, st));
   if (s->T == 0) return MOE_PRISM_OK;
   if (traffic_probe) {
     MP_LAUNCH(MOE_PRISM_K_FFN_TRAFFIC,
@@ -209,8 +231,7 @@ static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, cons
                                             L.max_mtiles, st));
     return MOE_PRISM_OK;
   }
-  const int few = use_few(s);
-  if (use_fused_ffn(s) && few == 0) {
+  if (p.fused) {
     MP_LAUNCH(MOE_PRISM_K_FFN_FUSED,
               launch_ffn_fused_bf16((const uint16_t*)x, (const uint16_t*)w_gu, (const uint16_t*)w_dn,
                                     sorted_pair, tiles, hdr, (uint16_t*)y, s->T, s->d, s->inter_sub,
@@ -219,9 +240,9 @@ static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, cons
   }
   MP_LAUNCH(MOE_PRISM_K_FFN_GATE_UP,
             launch_ffn_gate_up(s->dtype, x, w_gu, sorted_pair, tiles, hdr, h, s->T, s->d, s->inter_sub,
-                               s->k_max, few, L.max_mtiles, st));
+                               s->k_max, p.few, L.max_mtiles, st));
   MP_LAUNCH(MOE_PRISM_K_FFN_DOWN, launch_ffn_down(s->dtype, h, w_dn, tiles, hdr, y, s->T, s->d,
-                                                  s->inter_sub, few, L.max_mtiles, st));
+                                                  s->inter_sub, p.few, L.max_mtiles, st));
   return MOE_PRISM_OK;
 }
 
@@ -274,20 +295,19 @@ static int do_route_proxy(const moe_prism_shape* s, const Layout& L, const void*
   const ProxyScratch q = proxy_scratch(s, L, ws, m);
   MP_LAUNCH(MOE_PRISM_K_LOGITS,
             launch_logits(s->dtype, x, w_router0, bias0, logits0, hdr, s->T, s->d, N, st));
-  const SmallDispatch small{q.cnt0, q.off0, q.sp0, q.sl0, tiles, L.max_mtiles};
+  const FfnPlan p = plan_ffn(L, s->dtype, s->T, m, N, s->d, rows_half, false);
+  const SmallDispatch small{q.cnt0, q.off0, q.sp0, q.sl0, tiles, p.max_tiles, p.cut};
   const bool one = dispatch_is_small(s->T, N, m);
   MP_LAUNCH(MOE_PRISM_K_TOPK, launch_topk(logits0, nullptr, q.ids0, q.w0, hdr, s->T, N, m,
                                           s->renormalize, s->routed_scale, one ? &small : nullptr, st));
   if (!one) {
-    const int rc = do_dispatch_over(L, q.ids0, q.cnt0, q.off0, q.sp0, q.sl0, chunk, hdr, tiles, true, s->T,
+    const int rc = do_dispatch_over(L, q.ids0, q.cnt0, q.off0, q.sp0, q.sl0, chunk, hdr, tiles, p, s->T,
                                     N, m, st);
     if (rc) return rc;
   }
   if (s->T == 0) return MOE_PRISM_OK;
   MP_LAUNCH(MOE_PRISM_K_FFN_GATE_UP,
-            launch_ffn_gate_up(s->dtype, x, w_proxy, q.sp0, tiles, hdr, act, s->T, s->d, rows_half, m,
-                               s->dtype == MOE_PRISM_BF16 ? ffn_few_blocks(s->T, m, N, false)
-                                                            : ffn_f32_list(s->T, m, N, s->d, rows_half),
+            launch_ffn_gate_up(s->dtype, x, w_proxy, q.sp0, tiles, hdr, act, s->T, s->d, rows_half, m, p.few,
                                L.max_mtiles, st));
   MP_LAUNCH(MOE_PRISM_K_PROXY_SELECT,
             launch_proxy_select(s->dtype, act, rows_half, q.ids0, q.w0, q.sl0, k_tok, kappa, ids, w,
@@ -378,7 +398,7 @@ int moe_prism_grouped_ffn(const moe_prism_shape* shape, const void* x, const voi
     return MOE_PRISM_ERR_INVALID_ARG;
   MP_CHECK_WS(shape, L, ws, ws_bytes);
   return do_ffn(shape, L, x, w_gate_up, w_down, group_offset, sorted_pair, y,
-                static_cast<char*>(ws), (hipStream_t)stream);
+                static_cast<char*>(ws), (hipStream_t)stream, plan_ffn(L, shape));
 }
 
 int moe_prism_ffn_traffic_probe(const moe_prism_shape* shape, const void* x, const void* w_gate_up,
@@ -394,7 +414,7 @@ int moe_prism_ffn_traffic_probe(const moe_prism_shape* shape, const void* x, con
     return MOE_PRISM_ERR_UNSUPPORTED_SHAPE;
   MP_CHECK_WS(shape, L, ws, ws_bytes);
   return do_ffn(shape, L, x, w_gate_up, w_down, group_offset, sorted_pair, y,
-                static_cast<char*>(ws), (hipStream_t)stream, true);
+                static_cast<char*>(ws), (hipStream_t)stream, FfnPlan{true, 0, {8, false}, L.max_mtiles}, true);
 }
 
 int moe_prism_combine(const moe_prism_shape* shape, const void* y, const int32_t* slot_of_pair,
@@ -442,16 +462,17 @@ static int layer_on(const moe_prism_shape* shape, const Layout& L, const void* x
   int32_t* sl = reinterpret_cast<int32_t*>(w8 + L.slot_of_pair);
   void* y = w8 + L.y;
   // a small batch is dispatched by the top-k kernel itself
-  const SmallDispatch small{cnt, off, sp, sl, reinterpret_cast<MTile*>(w8 + L.tiles), L.max_mtiles};
+  const FfnPlan p = plan_ffn(L, shape);
+  const SmallDispatch small{cnt, off, sp, sl, reinterpret_cast<MTile*>(w8 + L.tiles), p.max_tiles, p.cut};
   const bool one = dispatch_is_small(shape->T, shape->n_experts * shape->n_sub, shape->k_max);
   int rc = do_route(shape, L, x, w_router, router_bias, k_tok, ids, w,
                     reinterpret_cast<float*>(w8 + L.logits), w8, st, one ? &small : nullptr);
   if (rc) return rc;
   if (!one) {
-    rc = do_dispatch(shape, L, ids, cnt, off, sp, sl, w8, st, true);
+    rc = do_dispatch(shape, L, ids, cnt, off, sp, sl, w8, st, &p);
     if (rc) return rc;
   }
-  rc = do_ffn(shape, L, x, w_gate_up, w_down, off, sp, y, w8, st, false, true);
+  rc = do_ffn(shape, L, x, w_gate_up, w_down, off, sp, y, w8, st, p, false, true);
   if (rc) return rc;
   if (shape->T == 0) return MOE_PRISM_OK;
   MP_LAUNCH(MOE_PRISM_K_COMBINE, launch_combine(shape->dtype, y, sl, w, k_tok, out, shape->T,
@@ -530,9 +551,10 @@ int moe_prism_layer_proxy(const moe_prism_shape* shape, const void* x, const voi
   rc = do_route_proxy(shape, L, x, w_router0, router_bias0, w_proxy, m, r, rows_half, kappa, k_tok,
                       ids, w, w8, st);
   if (rc) return rc;
-  rc = do_dispatch(shape, L, ids, cnt, off, sp, sl, w8, st, true);
+  const FfnPlan p = plan_ffn(L, shape);
+  rc = do_dispatch(shape, L, ids, cnt, off, sp, sl, w8, st, &p);
   if (rc) return rc;
-  rc = do_ffn(shape, L, x, w_gate_up, w_down, off, sp, y, w8, st, false, true);
+  rc = do_ffn(shape, L, x, w_gate_up, w_down, off, sp, y, w8, st, p, false, true);
   if (rc) return rc;
   if (shape->T == 0) return MOE_PRISM_OK;
   MP_LAUNCH(MOE_PRISM_K_COMBINE, launch_combine(shape->dtype, y, sl, w, k_tok, out, shape->T,

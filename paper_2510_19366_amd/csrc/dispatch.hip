@@ -108,7 +108,7 @@ __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_place_kernel(
     const int32_t* __restrict__ ids, const int32_t* __restrict__ chunk_base,
     const int32_t* __restrict__ cnt, int32_t* __restrict__ off, int32_t* __restrict__ hdr,
     int32_t* __restrict__ sorted_pair, int32_t* __restrict__ slot_of_pair,
-    MTile* __restrict__ tiles, int max_tiles, int even, int T, int E, int W, int k_max) {
+    MTile* __restrict__ tiles, int max_tiles, TileCut cut, int T, int E, int W, int k_max) {
   extern __shared__ u64 masks[];  // E * W masks, then E + 1 offsets, then E + 1 first-tile indices
   __shared__ int32_t wave_tot[4][2];
   int32_t* off_lds = reinterpret_cast<int32_t*>(masks + (size_t)E * W);
@@ -117,10 +117,10 @@ __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_place_kernel(
   const int ntok = max(min(64 * W, T - t0), 0);
   Picks picks(ids + (size_t)t0 * k_max, ntok, k_max);
   picks.load(0);  // on their way while the offsets are derived
-  group_offsets([&](int g) { return cnt[g]; }, off_lds, first_lds, wave_tot, E);
+  group_offsets([&](int g) { return cnt[g]; }, off_lds, first_lds, wave_tot, cut, E);
   if (c == 0) write_offsets(off_lds, first_lds, off, hdr, tiles != nullptr, max_tiles, E);
   if (tiles != nullptr)
-    write_tiles(off_lds, first_lds, tiles, max_tiles, even != 0, E, c * DISPATCH_THREADS + threadIdx.x,
+    write_tiles(off_lds, first_lds, tiles, max_tiles, cut, E, c * DISPATCH_THREADS + threadIdx.x,
                 gridDim.x * DISPATCH_THREADS);
   build_masks(picks, masks, E, W);
   place_pairs(picks, masks, [&](int g) { return off_lds[g] + chunk_base[(size_t)c * E + g]; }, sorted_pair,
@@ -138,9 +138,9 @@ __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_small_kernel(const 
 
 hipError_t launch_dispatch_small(const int32_t* ids, int32_t* cnt, int32_t* off, int32_t* hdr,
                                  int32_t* sorted_pair, int32_t* slot_of_pair, MTile* tiles,
-                                 int max_tiles, int T, int E, int k_max, hipStream_t s) {
+                                 int max_tiles, TileCut cut, int T, int E, int k_max, hipStream_t s) {
   dispatch_small_kernel<<<1, DISPATCH_THREADS, small_dispatch_lds(T, E), s>>>(
-      ids, SmallDispatch{cnt, off, sorted_pair, slot_of_pair, tiles, max_tiles}, hdr, T, E, k_max);
+      ids, SmallDispatch{cnt, off, sorted_pair, slot_of_pair, tiles, max_tiles, cut}, hdr, T, E, k_max);
   return hipGetLastError();
 }
 
@@ -164,7 +164,7 @@ hipError_t launch_dispatch_scan(int32_t* chunk_cnt, int32_t* cnt, int T, int E, 
 
 hipError_t launch_dispatch_place(const int32_t* ids, const int32_t* chunk_base, const int32_t* cnt,
                                  int32_t* off, int32_t* hdr, int32_t* sorted_pair,
-                                 int32_t* slot_of_pair, MTile* tiles, int max_tiles, bool even_tiles, int T,
+                                 int32_t* slot_of_pair, MTile* tiles, int max_tiles, TileCut cut, int T,
                                  int E, int k_max, hipStream_t s) {
   int W = dispatch_chunk_words(E, T);
   int nch = cdiv(T, 64 * W);
@@ -174,7 +174,7 @@ hipError_t launch_dispatch_place(const int32_t* ids, const int32_t* chunk_base, 
   hipError_t e = raise_lds_limit<dispatch_place_kernel>(100 * 1024);
   if (e != hipSuccess) return e;
   dispatch_place_kernel<<<nch, DISPATCH_THREADS, lds, s>>>(ids, chunk_base, cnt, off, hdr, sorted_pair,
-                                              slot_of_pair, tiles, max_tiles, even_tiles, T, E, W, k_max);
+                                              slot_of_pair, tiles, max_tiles, cut, T, E, W, k_max);
   return hipGetLastError();
 }
 

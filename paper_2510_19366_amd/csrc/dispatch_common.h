@@ -73,18 +73,18 @@ __device__ __forceinline__ int wave_scan(int v) {
 
 // Exclusive prefixes over the groups by one workgroup of 256 threads, into LDS: off_lds[0..E]
 // of the row counts cnt(g) (off_lds[E] = P) and first_lds[0..E] of the m-tile counts
-// ceil(cnt(g) / FFN_BM) (first_lds[E] = number of m-tiles).  A thread sums a run of consecutive
+// (first_lds[E] = number of m-tiles).  A thread sums a run of consecutive
 // groups, the 256 partial sums are scanned, the run is walked again.
 template <class Cnt>
 __device__ __forceinline__ void group_offsets(Cnt cnt, int32_t* off_lds, int32_t* first_lds,
-                                              int32_t (*wave_tot)[2], int E) {
+                                              int32_t (*wave_tot)[2], const TileCut& cut, int E) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int per = (E + 255) / 256, lo = min(tid * per, E), hi = min(lo + per, E);
   int mine = 0, mine_t = 0;
   for (int g = lo; g < hi; ++g) {
     const int n = cnt(g);
     mine += n;
-    mine_t += (n + FFN_BM - 1) / FFN_BM;
+    mine_t += cut.tiles(n);
   }
   const int incl = wave_scan(mine), incl_t = wave_scan(mine_t);
   if (lane == 63) {
@@ -102,7 +102,7 @@ __device__ __forceinline__ void group_offsets(Cnt cnt, int32_t* off_lds, int32_t
     off_lds[g] = run;
     first_lds[g] = run_t;
     run += n;
-    run_t += (n + FFN_BM - 1) / FFN_BM;
+    run_t += cut.tiles(n);
   }
   if (tid == 255) {  // lo == hi == E for the threads past the last group
     off_lds[E] = run;
@@ -135,7 +135,7 @@ __device__ __forceinline__ void write_offsets(const int32_t* off_lds, const int3
 // one-tile groups costs one round and not one per group (512 groups and one workgroup: 43-67 -> 7 us
 // for the whole kernel).
 __device__ __forceinline__ void write_tiles(const int32_t* off_lds, const int32_t* first_lds,
-                                            MTile* __restrict__ tiles, int max_tiles, bool even, int E,
+                                            MTile* __restrict__ tiles, int max_tiles, const TileCut& cut, int E,
                                             int start, int step) {
   const int n_tiles = min(first_lds[E], max_tiles);
   for (int i = start; i < n_tiles; i += step) {
@@ -144,16 +144,9 @@ __device__ __forceinline__ void write_tiles(const int32_t* off_lds, const int32_
       const int m = (lo + hi) >> 1;
       if (first_lds[m] <= i) lo = m; else hi = m;
     }
-    const int n = off_lds[lo + 1] - off_lds[lo], per = mtile_rows(n, FFN_BM, even);
+    const int n = off_lds[lo + 1] - off_lds[lo], per = cut.rows(n);
     const int first = first_lds[lo], row = (i - first) * per;
-    MTile t;
-    t.g = lo;
-    t.row0 = off_lds[lo] + row;
-    t.rows = min(per, n - row);
-    t.first = first;
-    t.count = min(first_lds[lo + 1] - first, max_tiles - first);
-    t.pad[0] = t.pad[1] = t.pad[2] = 0;
-    tiles[i] = t;
+    put_tile(tiles, cut, i, lo, off_lds[lo] + row, min(per, n - row), first, min(first_lds[lo + 1] - first, max_tiles - first));
   }
 }
 
@@ -189,6 +182,7 @@ struct SmallDispatch {
   int32_t *cnt, *off, *sorted_pair, *slot_of_pair;
   MTile* tiles;  // nullptr: no m-tile table
   int max_tiles;
+  TileCut cut;
 };
 __host__ __device__ inline size_t small_dispatch_lds(int T, int E) { return (size_t)E * ((T + 63) / 64) * 8 + (size_t)E * 4; }
 inline bool small_dispatch(int T, int E, int k_max) {
@@ -196,8 +190,8 @@ inline bool small_dispatch(int T, int E, int k_max) {
 }
 
 // Offsets, counts and m-tiles of all groups from the masks, by one workgroup of `threads` threads; returns P.  A group
-// has fewer than 256 rows here: at most one m-tile, which the thread that places the group writes.  Ends in front of
-// a barrier that off_lds needs.
+// has fewer than 256 rows here: one m-tile, or a few short ones, which the thread that places the group writes.  Ends in
+// front of a barrier that off_lds needs.
 __device__ __forceinline__ int small_groups(const SmallDispatch& a, int32_t* __restrict__ hdr, const u64* masks,
                                             int32_t* off_lds, int32_t* wave_tot, int W, int E, int threads) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -206,13 +200,14 @@ __device__ __forceinline__ int small_groups(const SmallDispatch& a, int32_t* __r
     for (int w = 0; w < W; ++w) n += __popcll(masks[g * W + w]);
     return n;
   };
-  // rows (at most 64 x 1024) in the low 18 bits of a word, m-tiles (at most 4096) above them: one scan for both
+  // rows (at most 64 x 1024) in the low 18 bits of a word, m-tiles (at most 4096 and one per 16 rows of 16 x 1024, or per 32 of
+  // 64 x 1024) above them: one scan for both
   constexpr int TILE = 1 << 18;
   const int per = (E + threads - 1) / threads, lo = min(tid * per, E), hi = min(lo + per, E);
   int mine = 0;
   for (int g = lo; g < hi; ++g) {
     const int n = count(g);
-    mine += n + (n > 0 ? TILE : 0);
+    mine += n + a.cut.tiles(n) * TILE;
   }
   const int incl = wave_scan(mine);
   if (lane == 63) wave_tot[wv] = incl;
@@ -225,12 +220,15 @@ __device__ __forceinline__ int small_groups(const SmallDispatch& a, int32_t* __r
   }
   const int P = total & (TILE - 1);
   for (int g = lo; g < hi; ++g) {
-    const int n = count(g), row0 = run & (TILE - 1), tile = run / TILE;
+    const int n = count(g), row0 = run & (TILE - 1), tile = run / TILE, nt = a.cut.tiles(n);
     off_lds[g] = row0;
     a.off[g] = row0;
     a.cnt[g] = n;
-    if (a.tiles != nullptr && n > 0 && tile < a.max_tiles) a.tiles[tile] = MTile{g, row0, n, tile, 1, {0, 0, 0}};
-    run += n + (n > 0 ? TILE : 0);
+    if (a.tiles != nullptr)
+      for (int i = 0; i < nt && tile + i < a.max_tiles; ++i)
+        put_tile(a.tiles, a.cut, tile + i, g, row0 + (i << a.cut.log2), min(n - (i << a.cut.log2), 1 << a.cut.log2), tile,
+                 min(nt, a.max_tiles - tile));
+    run += n + nt * TILE;
   }
   if (tid == 0) {
     a.off[E] = P;

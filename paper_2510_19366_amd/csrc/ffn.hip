@@ -40,7 +40,7 @@ __device__ __forceinline__ int block_scan(int v, int32_t* wave_tot, int* total) 
 __global__ __launch_bounds__(TILES_THREADS) void ffn_tiles_kernel(const int32_t* __restrict__ off,
                                                                   MTile* __restrict__ tiles,
                                                                   int32_t* __restrict__ hdr, int E,
-                                                                  int max_tiles, int even, int n_rows) {
+                                                                  int max_tiles, TileCut cut, int n_rows) {
   __shared__ int32_t wave_tot[TILES_THREADS / 64];
   const int tid = threadIdx.x;
   int carry = 0;  // tiles of the groups before this round (the same in every thread)
@@ -52,20 +52,12 @@ __global__ __launch_bounds__(TILES_THREADS) void ffn_tiles_kernel(const int32_t*
       n = off[g + 1] - lo;
       if (lo < 0 || n < 0 || lo > n_rows || n > n_rows - lo) n = 0;
     }
-    const int nt = (n + FFN_BM - 1) / FFN_BM;
+    const int nt = cut.tiles(n);
     int round_total = 0;
     const int first = carry + block_scan(nt, wave_tot, &round_total);
-    const int per = mtile_rows(n, FFN_BM, even != 0);
-    for (int i = 0; i < nt; ++i) {
-      MTile t;
-      t.g = g;
-      t.row0 = lo + i * per;
-      t.rows = min(per, n - i * per);
-      t.first = first;
-      t.count = min(nt, max_tiles - first);  // never points past the table
-      t.pad[0] = t.pad[1] = t.pad[2] = 0;
-      if (first + i < max_tiles) tiles[first + i] = t;
-    }
+    const int per = cut.rows(n);
+    for (int i = 0; i < nt && first + i < max_tiles; ++i)  // count: never points past the table
+      put_tile(tiles, cut, first + i, g, lo + i * per, min(per, n - i * per), first, min(nt, max_tiles - first));
     carry += round_total;
   }
   const int n_tiles = min(carry, max_tiles);
@@ -81,8 +73,8 @@ __global__ __launch_bounds__(TILES_THREADS) void ffn_tiles_kernel(const int32_t*
 }
 
 hipError_t launch_ffn_tiles(const int32_t* off, MTile* tiles, int32_t* hdr, int E, int max_tiles,
-                            bool even_tiles, int n_rows, hipStream_t s) {
-  ffn_tiles_kernel<<<1, TILES_THREADS, 0, s>>>(off, tiles, hdr, E, max_tiles, even_tiles, n_rows);
+                            TileCut cut, int n_rows, hipStream_t s) {
+  ffn_tiles_kernel<<<1, TILES_THREADS, 0, s>>>(off, tiles, hdr, E, max_tiles, cut, n_rows);
   return hipGetLastError();
 }
 

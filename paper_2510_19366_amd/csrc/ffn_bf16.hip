@@ -887,6 +887,14 @@ __global__ __launch_bounds__(NT_) void ffn_short_kernel(Op op, const MTile* __re
 // by the waves, in chunks of 4 to 8 stages of K, two of them, and one barrier per chunk.
 //   MOST = 1, 2 (blocks of 16 slot rows at a time): 4 waves, two workgroups per CU with 80 KB of weights in flight;
 //   MOST = 4: 8 waves, which halves what is copied of the slot rows per weight row.
+// The groups are cut into m-tiles of 16 MOST rows (FewTile), and those of a longer group with the same weight rows are
+// neighbours in the list (shared_item): they run side by side on an XCD, and its L2 serves the weights to all but the first.
+// Items are then of one length, whatever the load.  With m-tiles of 256 rows, which a workgroup went through 16 MOST at a
+// time, it fetched its weights again each time, and the XCD that had the long group finished last.  Both GEMMs, us, so |
+// now (| ring driver), router bias N(0, 1) per expert: 100 tokens on 32 of 3584 x 4096 (longest group 87) 610 | 405 | 410, 256
+// on 128 of 704 (170) 250 | 164 | 184, 192 on 256 of 256 (166) 195 | 132 | 156, 384 on 512 of 192 (213) 277 | 169, fused
+// kernel 247; even load: the same as before.  All tokens with the same picks, which nothing but the number of tokens bounds,
+// are better off with the ring driver from some four m-tiles per group on: 256 tokens on 12 of the 128 62 | 66, 590 97 | 71.
 // Two tokens of 32 sub-experts each, 192 x 2048, both GEMMs between HIP events 17.6 us, with tiles that shared a stage of
 // weight and slot rows behind a barrier 24.4; 100 tokens of 4 to 12 on 128 of 704 231 -> 196 us (5.6 TB/s of weights)
 // against the ring driver.  (Weights straight into the registers of the matrix instruction: its lanes are rows, so that
@@ -903,6 +911,8 @@ struct Few {
   static constexpr int NS = SHORT || NARROW ? 4 : MOST == 4 ? 5 : 6, STAGE = FP_WAVE_N * BK * 2, RING = WAVES * NS * STAGE;
   static constexpr int CHUNK = WAVES * 4096, LDS_BYTES = RING + (SHORT ? 1 : 2) * CHUNK;
   static constexpr int PER_CU = 160 * 1024 / LDS_BYTES, PARTS = NARROW ? BM / (16 * MOST) : 1;
+  static constexpr int CP = 2;           // copies of a wave per stage
+  static constexpr int AHEAD = NS - 1;   // stages in flight
 };
 
 // NARROW (gate-up of up to 32 neurons, any number of rows, K > 192): the ring driver's tile has 256 weight rows, of which only 64
@@ -921,8 +931,7 @@ __global__ __launch_bounds__((Few<MOST, SHORT, NARROW>::THREADS)) void ffn_few_k
   typedef Few<MOST, SHORT, NARROW> F;
   extern __shared__ __align__(16) unsigned char fp_smem[];
   constexpr int FP_NS = F::NS, FP_STAGE = F::STAGE, FP_CHUNK = F::CHUNK;
-  constexpr int CP = 2, XCP = FP_CHUNK / 1024 / F::WAVES;  // copies per wave: of a stage, of a chunk
-  constexpr int AHEAD = FP_NS - 1;                         // stages in flight
+  constexpr int CP = F::CP, AHEAD = F::AHEAD, XCP = FP_CHUNK / 1024 / F::WAVES;  // XCP: copies of a wave per chunk
   const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6), r = lane & 15, g = lane >> 4;
   const int K = op.K(), ns = (K + BK - 1) / BK;
   const uint32_t lds0 = lds_offset(fp_smem), ring = lds0 + (uint32_t)(wv * FP_NS * FP_STAGE), xs = lds0 + F::RING;
@@ -997,11 +1006,16 @@ __global__ __launch_bounds__((Few<MOST, SHORT, NARROW>::THREADS)) void ffn_few_k
           for (int b = 0; b < NB; ++b)
             acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[set][ks], fx[set][ks][b], acc[b], 0, 0, 0);
     };
+    // Copies land in the order of their issue, so a wait is a count of what may still be on its way behind what is needed:
+    //   stage 0, chunk 0, stages 1 .. AHEAD - 1 (above); then chunk by chunk: chunk c + 1, and in step q of it stage q + AHEAD.
+    // Stage q + AHEAD takes the slot of stage q - 1, which this wave has read; chunk c + 1 the place of chunk c - 1, which all
+    // have read at the barrier.  Stages that do not exist are not issued: near the end everything is waited for.
+    static_assert(FP_NS == AHEAD + 1 && (!SHORT || SPC >= 3));  // SHORT has one chunk
     const int nc = (ns + SPC - 1) / SPC;
     uint32_t w_slot = 0;  // of the stage that is read next
     for (int c = 0; c < nc; ++c) {
-      // chunk c has landed for this wave (behind it AHEAD - 1 stages of weights for the first, SPC for the others), and
-      // behind the barrier for all; nobody reads the chunk before any more
+      // Chunk c has landed for this wave, behind the barrier for all.  Issued after it: AHEAD - 1 stages for the first one, SPC
+      // for the others.
       static_assert(SPC >= AHEAD - 1);
       if (c * SPC + AHEAD - 1 < ns) wait_vmem<(AHEAD - 1) * CP>();
       else wait_vmem<0>();
@@ -1013,6 +1027,7 @@ __global__ __launch_bounds__((Few<MOST, SHORT, NARROW>::THREADS)) void ffn_few_k
         constexpr int set = decltype(set_c)::value;
         const int q = c * SPC + s;
         if (q >= ns) return;
+        // issued after stage q: AHEAD - 1 stages, and chunk c + 1 where stage q was issued before this chunk
         if (q + AHEAD - 1 >= ns) wait_vmem<0>();
         else if (s < AHEAD && more && x_on == XCP) wait_vmem<(AHEAD - 1) * CP + XCP>();
         else wait_vmem<(AHEAD - 1) * CP>();
@@ -1047,19 +1062,35 @@ __global__ __launch_bounds__((Few<MOST, SHORT, NARROW>::THREADS)) void ffn_few_k
   };
   const ItemRange ir = xcd_items(hdr[HDR_MTILES] * n_tiles_n * F::PARTS);
   for (int i = ir.begin; i < ir.end; i += ir.step) {
-    const int item = i / F::PARTS, part = i % F::PARTS;
-    const MTile t = tiles[item / n_tiles_n];
     Sc sc;
-    sc.g = uni(t.g);
-    constexpr int PER_WAVE = FP_WAVE_N / Op::N_PER_ROW;
-    const int n0 = (item % n_tiles_n * F::WAVES + wv) * PER_WAVE;
-    sc.n0 = min(n0, op.n_cols() - PER_WAVE);  // of eight waves the last tile's second four may have none: again the last rows
-    for (int row = part * 16 * MOST; row < uni(t.rows); row += F::PARTS * 16 * MOST) {
+    int nt;
+    if constexpr (NARROW) {
+      const int item = i / F::PARTS, row = i % F::PARTS * 16 * MOST;
+      const MTile t = tiles[item / n_tiles_n];
+      nt = item % n_tiles_n;
+      sc.g = uni(t.g);
       sc.row0 = uni(t.row0) + row;
       sc.rows = min(16 * MOST, uni(t.rows) - row);
-      if (MOST == 2 && sc.rows <= 16) tile(sc, n0 == sc.n0, std::integral_constant<int, 1>{});
-      else tile(sc, n0 == sc.n0, std::integral_constant<int, MOST>{});
+      if (sc.rows <= 0) continue;
+    } else {
+      const FewTile* few = reinterpret_cast<const FewTile*>(tiles);
+      FewTile t = few[i / n_tiles_n];
+      nt = i % n_tiles_n;
+      const int count = uni(t.rows_count) >> 8;
+      if (count > 1) {
+        int m;
+        shared_item(i, n_tiles_n, uni(t.first), count, m, nt);
+        t = few[m];
+      }
+      sc.g = uni(t.g);
+      sc.row0 = uni(t.row0);
+      sc.rows = uni(t.rows_count) & 255;
     }
+    constexpr int PER_WAVE = FP_WAVE_N / Op::N_PER_ROW;
+    const int n0 = (nt * F::WAVES + wv) * PER_WAVE;
+    sc.n0 = min(n0, op.n_cols() - PER_WAVE);  // of eight waves the last tile's second four may have none: again the last rows
+    if (MOST == 2 && sc.rows <= 16) tile(sc, n0 == sc.n0, std::integral_constant<int, 1>{});
+    else tile(sc, n0 == sc.n0, std::integral_constant<int, MOST>{});
   }
 }
 
@@ -1087,12 +1118,12 @@ static hipError_t launch_ring(const Op& op, int ntn, int grid, int dyn_word, con
 }
 
 template <class Op, int MOST, bool SHORT = false, bool NARROW = false>
-static hipError_t launch_few(const Op& op, int n_cols, int max_mtiles, const MTile* tiles, const int32_t* hdr, hipStream_t s) {
+static hipError_t launch_few(const Op& op, int n_cols, int max_tiles, const MTile* tiles, const int32_t* hdr, hipStream_t s) {
   typedef Few<MOST, SHORT, NARROW> F;
   hipError_t e = raise_lds_limit<ffn_few_kernel<Op, MOST, SHORT, NARROW>>(F::LDS_BYTES);
   if (e != hipSuccess) return e;
   const int ntn = cdiv(n_cols, F::N / Op::N_PER_ROW);
-  const int grid = persistent_grid((long)max_mtiles * ntn * F::PARTS, F::PER_CU);
+  const int grid = persistent_grid((long)max_tiles * ntn * F::PARTS, F::PER_CU);
   ffn_few_kernel<Op, MOST, SHORT, NARROW><<<grid, F::THREADS, F::LDS_BYTES, s>>>(op, tiles, hdr, ntn);
   return hipGetLastError();
 }
@@ -1100,17 +1131,16 @@ static hipError_t launch_few(const Op& op, int n_cols, int max_mtiles, const MTi
 template <class Op>
 static hipError_t launch_op(const Op& op, int T, int K, int n_cols, int few, int dyn_word, int max_mtiles,
                             const MTile* tiles, int32_t* hdr, hipStream_t s) {
-  if (op.offsets_fit()) {
-    if constexpr (!Op::GATHER) {
-      if (few == 1 && K <= 3 * BK) return launch_few<Op, 1, true>(op, n_cols, max_mtiles, tiles, hdr, s);
-      if (few == 2 && K <= 3 * BK) return launch_few<Op, 2, true>(op, n_cols, max_mtiles, tiles, hdr, s);
-    }
-    if (few == 1) return launch_few<Op, 1>(op, n_cols, max_mtiles, tiles, hdr, s);
-    if (few == 2) return launch_few<Op, 2>(op, n_cols, max_mtiles, tiles, hdr, s);
-    if (few == 4) return launch_few<Op, 4>(op, n_cols, max_mtiles, tiles, hdr, s);
-    if constexpr (Op::GATHER) {
-      if (n_cols <= NARROW_COLS && K > 3 * BK) return launch_few<Op, 4, false, true>(op, n_cols, max_mtiles, tiles, hdr, s);
-    }
+  if constexpr (!Op::GATHER) {
+    if (few == 1 && K <= 3 * BK) return launch_few<Op, 1, true>(op, n_cols, 2 * max_mtiles, tiles, hdr, s);
+    if (few == 2 && K <= 3 * BK) return launch_few<Op, 2, true>(op, n_cols, 2 * max_mtiles, tiles, hdr, s);
+  }
+  if (few == 1) return launch_few<Op, 1>(op, n_cols, 2 * max_mtiles, tiles, hdr, s);
+  if (few == 2) return launch_few<Op, 2>(op, n_cols, 2 * max_mtiles, tiles, hdr, s);
+  if (few == 4) return launch_few<Op, 4>(op, n_cols, 2 * max_mtiles, tiles, hdr, s);
+  if constexpr (Op::GATHER) {
+    if (n_cols <= NARROW_COLS && K > 3 * BK && op.offsets_fit())
+      return launch_few<Op, 4, false, true>(op, n_cols, max_mtiles, tiles, hdr, s);
   }
   const int ntn = cdiv(n_cols, BN / Op::N_PER_ROW);
   const int grid = persistent_grid((long)max_mtiles * ntn, 1);
@@ -1121,21 +1151,24 @@ static hipError_t launch_op(const Op& op, int T, int K, int n_cols, int few, int
   return launch_ring<Op, false>(op, ntn, grid, dyn_word, tiles, hdr, s);
 }
 
-// T k_max pairs are what a batch can have, its pairs are that for one budget and about 0.6 of it for mixed ones.  Both
-// GEMMs, us between HIP events, d = 2048 unless said, against what the other rows take:
+// T k_max pairs are what a batch can have, its pairs are that for one budget and about 0.6 of it for mixed ones.  Stage
+// calls back to back, us, two blocks, four | what else would run; mixed budgets and d = 2048 unless said; skewed: a router
+// bias N(0, 1) per expert.  By possible rows per sub-expert:
 //   up to 16 tokens, one block: no group has more rows;
-//   two blocks up to 24 (possible) rows per sub-expert, four up to 56 | the ring driver.  128 of 704, mixed: 100 tokens
-//     196 (four 210) | 230, 300 208 | 235, 512 (48 possible) 224 | 239, 1000 (94) 301 | 250; 256 of 256, mixed: 100 155 | 191,
-//     400 (50) 183 | 197, 700 (88) 207 | 200; 128 of 768, 8 picks each: 100 212 | 261, 400 (25) four 229, two 240 | 270, 700
-//     (44) 236 | 276, 900 (56) 273 | 280, 1000 (62) 299 | 282; 32 of 3584 x 4096, mixed: 64 481 | 515, 200 (50) 488 | 526, 400
-//     (100) 786 | 536; 256 of 32 x 512, mixed: 500 tokens 17.4 | 25.9;
-//   fused: the fused kernel gives a tile a workgroup, so it is good at about as many touched groups as CUs.  512 of
-//     192: up to 64 tokens few ones are touched, 30 tokens 73 | 96, 64 104 | 103 with skewed load, 203 | 242 with even.
-//     With 10 possible rows nearly all are, two rounds of tiles: skewed 200 tokens (12.5) 165 | 185, 140 (8.8) 147 | 122, even
-//     256 (16) 222 | 259, 400 (25) 228 | 263, 700 (44) 270 | 271.  256 of 64 or 128, one round of tiles: 150 tokens 31 | 33
-//     and 43 | 43, 600 37 | 34 and 50 | 44: the fused kernel.
-int ffn_few_blocks(int T, int k_max, int E, bool fused) {
+//   two blocks up to 24, then four | ring driver: 128 of 704: 18.8 201, 209 | 239, skewed 151, 152 | 179; 37.5 217, 218 | 244,
+//     skewed 190, 191 | 212; 256 of 256: 18.8 157, 176 | 191; 32 169, 179 | 196; 128 of 768, 8 picks each: 24 230, 227 | 269; 32
+//     257, 230 | 272, skewed 213, 179 | 196; 32 of 3584 x 4096: 40 511, 474 | 519;
+//   four up to 56 | ring driver: 128 of 704: 48 221 | 249, skewed 199 | 223; 60 228 | 251, 205 | 228; 256 of 352: 48 235 | 262, 226 |
+//     244; 60 242 | 265, 210 | 206; 75 262 | 270, 242 | 216; 128 of 768, 8 picks: 50 257 | 282, 231 | 224; 56 259 | 284, 248 | 245; 62
+//     278 | 287, 249 | 233; 32 of 3584 x 4096: 50 477 | 518, 502 | 491 (other tokens 506 | 514); 72 485 | 523, 526 | 499.  So with
+//     skewed load they meet at 50 to 60, with even load at 75 and beyond;
+//   fused, two blocks | fused kernel: it gives a tile a workgroup, so it is good at about as many touched groups as CUs.  More
+//     sub-experts than CUs, 512 of 192: 6.2 208 | 249, skewed 109 | 111; 10 217 | 255, 127 | 184; 24 237 | 264, 187 | 244; 37.5
+//     253 | 273, 214 | 255.  10 and 24 are where m-tiles of 256 rows were worth it (skewed: 8.8 147 | 122, 24 277 | 247); with
+//     the short ones two blocks are ahead beyond both, and with fewer sub-experts than CUs too (256 of 192: 12.5 114 | 124).
+int ffn_few_blocks(int T, int k_max, int E, int d, int Is, bool fused) {
   const long pairs = (long)T * k_max;
+  if (!GateUpOp{nullptr, nullptr, nullptr, nullptr, T, d, Is, k_max}.offsets_fit() || !DownOp{nullptr, nullptr, nullptr, d, Is}.offsets_fit()) return 0;
   if (T <= 16) return 1;
   if (fused && T > 64 && (E <= num_cus() || pairs < 10L * E || pairs > 24L * E)) return 0;
   if (pairs <= 24L * E) return 2;

@@ -22,6 +22,17 @@ struct MTile {  // one m-tile of a group: rows [row0, row0 + rows) of the slot l
   int32_t count;  // m-tiles of the group
   int32_t pad[3];
 };
+// ... and one of at most 64 rows (ffn_few_kernel): half of the bytes, so that the table of tiles of 256 rows,
+// rows / 256 + E entries, holds 2 E of them
+struct FewTile {
+  int32_t g, row0, rows_count, first;  // rows | m-tiles of the group << 8
+};
+static_assert(2 * sizeof(FewTile) == sizeof(MTile));
+// m-tile `i` into the table: FewTiles where the cut is below FFN_BM
+__device__ __forceinline__ void put_tile(MTile* tiles, const TileCut& cut, int i, int g, int row0, int rows, int first, int count) {
+  if ((1 << cut.log2) < FFN_BM) reinterpret_cast<FewTile*>(tiles)[i] = FewTile{g, row0, rows | count << 8, first};
+  else tiles[i] = MTile{g, row0, rows, first, count, {0, 0, 0}};
+}
 
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
@@ -51,17 +62,17 @@ hipError_t launch_dispatch_scan(int32_t* chunk_cnt, int32_t* cnt, int T, int E, 
 bool dispatch_is_small(int T, int E, int k_max);  // the whole stage in one workgroup (launch_dispatch_small)
 hipError_t launch_dispatch_small(const int32_t* ids, int32_t* cnt, int32_t* off, int32_t* hdr,
                                  int32_t* sorted_pair, int32_t* slot_of_pair, MTile* tiles,
-                                 int max_tiles, int T, int E, int k_max, hipStream_t s);
+                                 int max_tiles, TileCut cut, int T, int E, int k_max, hipStream_t s);
 // also writes off[0..E] and hdr[HDR_PAIRS] (from cnt[]) and, with tiles != nullptr, the grouped
 // FFN's m-tile table and its header words (what launch_ffn_tiles builds from off[])
 hipError_t launch_dispatch_place(const int32_t* ids, const int32_t* chunk_base, const int32_t* cnt,
                                  int32_t* off, int32_t* hdr, int32_t* sorted_pair,
-                                 int32_t* slot_of_pair, MTile* tiles, int max_tiles, bool even_tiles, int T,
+                                 int32_t* slot_of_pair, MTile* tiles, int max_tiles, TileCut cut, int T,
                                  int E, int k_max, hipStream_t s);
 
 // grouped FFN
 hipError_t launch_ffn_tiles(const int32_t* off, MTile* tiles, int32_t* hdr, int E, int max_tiles,
-                            bool even_tiles, int n_rows, hipStream_t s);
+                            TileCut cut, int n_rows, hipStream_t s);
 hipError_t launch_ffn_gate_up(int dtype, const void* x, const void* w_gu, const int32_t* sorted_pair,
                               const MTile* tiles, int32_t* hdr, void* h, int T, int d, int Is,
                               int k_max, int few, int max_mtiles, hipStream_t s);
@@ -70,7 +81,7 @@ hipError_t launch_ffn_down(int dtype, const void* h, const void* w_dn, const MTi
                            hipStream_t s);
 // bf16: so few rows per sub-expert that the tiles of ffn_few_kernel are the faster ones: their blocks of 16 slot rows, or
 // 0.  fused: the fused kernel would run instead
-int ffn_few_blocks(int T, int k_max, int E, bool fused);
+int ffn_few_blocks(int T, int k_max, int E, int d, int Is, bool fused);
 // fp32: the list of row blocks and the tile (`few` of the launchers)
 int ffn_f32_list(int T, int k_max, int E, int d, int Is);
 

@@ -17,6 +17,23 @@ MP_HD int mtile_rows(int n, int most, bool even) {
   return even && nt > 1 ? ((n + nt - 1) / nt + 63) / 64 * 64 : most;
 }
 
+// How the groups are cut into m-tiles: into tiles of at most 1 << log2 rows, `even` as above.
+struct TileCut {
+  int log2;
+  bool even;
+  MP_HD int tiles(int n) const { return (n + (1 << log2) - 1) >> log2; }
+  MP_HD int rows(int n) const { return mtile_rows(n, 1 << log2, even); }
+};
+
+// Item of a list of (m-tile, n-tile) pairs in which a group's m-tiles of the same n-tile are neighbours: they run at the
+// same time on one XCD, and its L2 serves their weights to all but the first.  first, count: the m-tiles of the
+// group that m-tile item / n_tiles_n belongs to.
+MP_HD void shared_item(int item, int n_tiles_n, int first, int count, int& m_tile, int& n_tile) {
+  const int i = item - first * n_tiles_n;
+  m_tile = first + i % count;
+  n_tile = i / count;
+}
+
 // An m-tile of `rows` slot rows is cut into row blocks of ROWS, and each of those into n_tiles_n n-tiles.
 // f(m-tile, row block, n-tile) for the share of workgroup b out of `grid` (a multiple of n_xcd; b serves XCD
 // b % n_xcd, and an XCD a contiguous part of the list, in which a sub-expert's weights meet).

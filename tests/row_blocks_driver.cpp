@@ -58,8 +58,53 @@ static int check_rows(int n, int most) {
   return 0;
 }
 
+// Groups cut into m-tiles of at most 1 << log2 rows: every row in one of them, and every (m-tile, n-tile) pair one item, the
+// m-tiles of a group with the same n-tile being neighbours, so that workgroups that run side by side share their weights.
+static int check_shared(const std::vector<int>& groups, int log2, int n_tiles_n) {
+  struct M {
+    int g, rows, first, count;
+  };
+  std::vector<M> tiles;
+  const mp::TileCut cut{log2, false};
+  for (int g = 0; g < (int)groups.size(); ++g) {
+    const int nt = cut.tiles(groups[g]), first = (int)tiles.size();
+    int rows = 0;
+    for (int i = 0; i < nt; ++i) {
+      tiles.push_back({g, std::min(cut.rows(groups[g]), groups[g] - rows), first, nt});
+      rows += tiles.back().rows;
+      if (tiles.back().rows < 1 || tiles.back().rows > 1 << log2) return 1;
+    }
+    if (rows != groups[g]) return 2;
+  }
+  const int total = (int)tiles.size() * n_tiles_n;
+  std::vector<int> seen(total, 0);
+  int last_g = -1, last_n = -1, changes = 0, exist = 0;
+  for (const int n : groups) exist += n > 0 ? n_tiles_n : 0;
+  for (int i = 0; i < total; ++i) {
+    const M& t0 = tiles[i / n_tiles_n];
+    int m, n;
+    mp::shared_item(i, n_tiles_n, t0.first, t0.count, m, n);
+    if (m < t0.first || m >= t0.first + t0.count || n < 0 || n >= n_tiles_n) return 3;
+    if (seen[m * n_tiles_n + n]++) return 4;
+    changes += tiles[m].g != last_g || n != last_n;
+    last_g = tiles[m].g;
+    last_n = n;
+  }
+  return changes != exist ? 5 : 0;  // each weight tile is one run of items
+}
+
 int main() {
   std::mt19937 gen(3);
+  for (int log2 : {4, 5, 6})
+    for (int n_tiles_n : {1, 2, 6, 11, 56})
+      for (int most : {1, 15, 16, 17, 64, 65, 300, 2000}) {
+        std::vector<int> groups(40);
+        for (int& n : groups) n = gen() % 3 == 0 ? 0 : 1 + (int)(gen() % most);
+        if (const int e = check_shared(groups, log2, n_tiles_n)) {
+          printf("groups of up to %d rows in tiles of %d, n-tiles %d: %d\n", most, 1 << log2, n_tiles_n, e);
+          return e;
+        }
+      }
   for (int n = 0; n < 5000; ++n)
     if (const int e = check_rows(n, 256)) {
       printf("m-tiles of %d rows: %d\n", n, e);

@@ -15,6 +15,8 @@ FEW = [1, 0, 33, 0, 0, 30]
 ONE = [1, 0, 9, 2, 0, 3]
 TWO = [1, 0, 15, 16, 17, 31, 32, 33, 0, 47, 5, 64, 48]
 FOUR = [63, 64, 65, 48, 49, 15, 0, 1, 33, 128, 130, 16]
+LONG_FOUR = [0, 0, 270, 1, 0, 0, 31, 0, 33, 0, 0, 96, 0, 0, 2, 0, 0, 0, 0, 128]  # 28 rows for each on average: four blocks
+LONG_TWO = [0] * 9 + [200] + [0] * 10 + [31, 1, 65] + [0] * 3
 
 
 def ffn(dtype, x, w_gu, w_dn, group):
@@ -61,6 +63,10 @@ def ffn(dtype, x, w_gu, w_dn, group):
     ("bf16", "auto", FOUR, 192, 96),
     ("bf16", "auto", FOUR, 448, 352),
     ("bf16", "auto", FOUR, 1024, 160),
+    ("bf16", "auto", LONG_FOUR, 448, 352),  # a group of several m-tiles beside empty ones, in tiles of 64 rows and of 32
+    ("bf16", "auto", LONG_FOUR, 128, 96),  # (not 64 x 32: as above)
+    ("bf16", "auto", LONG_TWO, 448, 352),
+    ("bf16", "auto", LONG_TWO, 128, 96),
     ("bf16", "auto", LONG, 256, 32),      # gate-up of 32 neurons: row blocks of an m-tile as items of their own
     ("bf16", "auto", LONG, 448, 32),
     ("f32", "auto", SIZES, 64, 32),

@@ -72,6 +72,7 @@ def check_route(split, pg, k_tok, ids, w, dtype):
     dict(T=64, d=64, N=4, I=256, S=8, m=2, r=3),
     dict(T=70, d=64, N=4, I=512, S=16, m=2, r=8),
     dict(T=90, d=64, N=16, I=128, S=4, m=10, r=4),
+    dict(T=150, d=64, N=48, I=128, S=4, m=4, r=4),   # experts of several tiles of 32 rows in the scoring pass
 ])
 def test_proxy_route_and_layer_against_oracle(dtype, case):
     whole, split, pg = make(dtype, seed=case["T"], bias_std=0.5, **case)

@@ -1,0 +1,40 @@
+"""Layers whose router prefers a few experts, at token counts that take the tiles for few rows per sub-expert: groups of
+several of their m-tiles beside groups without a row, with the m-tile table of each dispatch (one
+workgroup, the end of the top-k kernel, the place kernel, the stage call's own), against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2510_19366_amd import binding as B
+from paper_2510_19366_amd import workloads as W
+from gpu_util import max_rel, row_rel, run_layer, run_stages, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,N,S,k_max,d,Is,longest", [
+    (16, 16, 2, 4, 128, 96, 15),      # one workgroup for routing and dispatch; tiles of 16 rows, which all tokens fit
+    (40, 16, 4, 8, 128, 96, 33),      # the end of the top-k kernel; tiles of 32
+    (64, 4, 4, 8, 64, 32, 33),        # tiles of 64
+    (100, 16, 4, 8, 448, 352, 65),    # several tiles of 32 per group, two 64-token words
+    (200, 16, 4, 4, 256, 64, 97),     # the same; the fused kernel (a narrow width)
+    (200, 64, 8, 32, 256, 64, 97),    # as many rows as bring narrow sub-experts to the two-kernel path; place kernel
+    (300, 16, 4, 4, 128, 96, 129),    # place kernel, tiles of 32
+    (300, 16, 4, 8, 448, 352, 193),   # and of 64
+    (300, 16, 4, 8, 256, 32, 193),
+])
+def test_layer_with_a_skewed_load(T, N, S, k_max, d, Is, longest):
+    k = np.random.default_rng(T).integers(1, k_max + 1, size=T).astype(np.int32)
+    wl = W.make_workload("skewed", dtype="bf16", d=d, n_experts=N, n_sub=S, inter_sub=Is, req_tokens=[1] * T,
+                         req_k=k, k_max=k_max, seed=T, bias_std=4.0, w_std=0.05)
+    ref = O.layer_of(wl, return_all=True)
+    assert ref["cnt"].max() >= longest and (ref["cnt"] == 0).any()
+    r = run_stages(wl)
+    for name in ("ids", "cnt", "off", "sorted_pair", "slot_of_pair"):
+        assert np.array_equal(r[name], ref[name]), name
+    # bf16: h and y are rounded once each, as in the other layer tests
+    assert max_rel(r["y"], ref["y"]) <= 2e-2 and row_rel(r["y"], ref["y"]) <= 4e-2
+    assert max_rel(r["out"], ref["out"]) <= 2e-2
+    out, dev, ws = run_layer(wl, r["dev"], r["ws"])
+    assert np.array_equal(to_np(out), r["out"])
+    assert B.moe_prism_status(ws)[0] == 0
