@@ -35,3 +35,54 @@ def test_decisions_inside_and_outside_the_bounds_of_an_unordered_sum(t0, t1, equ
     ref = PO.anneal(A, g0, 4, 2, steps=400, t0=t0, t1=t1, seed=9)
     got = B.moe_prism_partition_anneal(A, g0, 4, 2, 400, t0, t1, 9)
     assert np.array_equal(got[0], ref[0]) and got[1] == ref[1]
+
+
+def plain_anneal(A, group_of, S, k_in, steps, t0, t1, seed):
+    """The solver's own arithmetic without bounds: group sums updated per kept swap, every loss its tokens' losses added
+    up in order."""
+    B_tok, C = A.shape
+    a = np.abs(A.astype(np.float64)).T
+    g, L = np.array(group_of, np.int32), np.zeros((S, B_tok))
+    for c in range(C):
+        L[g[c]] += a[c]
+
+    def loss_of(L):
+        tok = np.zeros(B_tok)
+        for v in np.sort(L, axis=0)[:S - k_in]:
+            tok = tok + v
+        return float(np.cumsum(tok)[-1])                     # one addition after the other
+
+    loss = loss_of(L)
+    for step in range(steps):
+        r = [PO.splitmix64((seed + 3 * step + n) & PO.MASK) for n in range(3)]
+        i, j = r[0] % C, r[1] % C
+        if g[i] == g[j]:
+            continue
+        new = L.copy()
+        new[g[i]] = L[g[i]] - a[i] + a[j]
+        new[g[j]] = L[g[j]] - a[j] + a[i]
+        new_loss = loss_of(new)
+        delta, temp = new_loss - loss, t0 * (t1 / t0) ** (step / (steps - 1))
+        if delta <= 0.0 or (r[2] >> 11) * 2.0 ** -53 < np.exp(-delta / temp):
+            g[i], g[j] = g[j], g[i]
+            L, loss = new, new_loss
+    return g, loss
+
+
+@pytest.mark.parametrize("t", [1e-300, 1e-9, 1.0])
+@pytest.mark.parametrize("columns", ["twice", "equal"])
+@pytest.mark.parametrize("S", [2, 3, 4, 8])
+def test_decisions_that_the_order_of_a_sum_makes(t, columns, S):
+    # activations of 2^-25 to 2^25, so that sums are rounded, with equal neurons, so that a loss changes by roundings only:
+    # the sum in another order says something else about many of these swaps
+    for seed in range(6):
+        rng = np.random.default_rng(seed)
+        A = rng.standard_normal((61, 24)) * 2.0 ** rng.integers(-25, 26, (61, 1))
+        A[:, 12:] = A[:, :12]
+        if columns == "equal":
+            A[:] = A[:, :1]
+        A = A.astype(np.float32)
+        g0 = PO.greedy(A, S)
+        ref = plain_anneal(A, g0, S, S // 2, 300, t, t, seed)
+        got = B.moe_prism_partition_anneal(A, g0, S, S // 2, 300, t, t, seed)
+        assert np.array_equal(got[0], ref[0]) and got[1] == ref[1]
