@@ -87,7 +87,12 @@ hipError_t launch_ffn_tiles(const int32_t* off, MTile* tiles, int32_t* hdr, int 
 // 4096 tokens, d = 1024, 32 of 256, 8 picks: both 1274 -> 576.
 constexpr int F32_ROWS = 32, F32_BLOCKS = FFN_BM / F32_ROWS;
 template <int NT>
-using F32Tile = ChainTile<float, 2, 2, 1, NT, NT == 2 ? 5 : 6>;
+using F32Tile = ChainTile<float, 2, 2, 1, NT, NT == 2 ? 5 : 4>;
+// Workgroups per CU: all resident, so that a batch of no more tiles than these is one round.
+template <int NT>
+constexpr int F32_PER_CU = NT == 1 ? 4 : 2;
+constexpr int F32_UPS_BYTES = 2 * 64 * sizeof(f32x4_t);  // the up rows' sums of NT = 1
+static_assert(F32_PER_CU<1> * (F32Tile<1>::LDS_BYTES + F32_UPS_BYTES) <= 160 * 1024 && F32_PER_CU<2> * F32Tile<2>::LDS_BYTES <= 160 * 1024);
 
 // Copies of one tile: row `row` of the stage starts at byte offset off(row) behind the base of its
 // operand (slot rows first).  WIDE: an operand of 4 GiB or more, offsets of 64 bits.
@@ -141,7 +146,7 @@ __global__ __launch_bounds__(256) void ffn_gate_up_f32_kernel(
     const int32_t* __restrict__ sorted_pair, const MTile* __restrict__ tiles,
     const int32_t* __restrict__ hdr, float* __restrict__ h, int d, int Is, int k_max, int T) {
   extern __shared__ __align__(16) unsigned char f_smem[];
-  __shared__ f32x4_t ups[NT == 1 ? 2 * 64 : 1];
+  __shared__ f32x4_t ups[NT == 1 ? F32_UPS_BYTES / sizeof(f32x4_t) : 1];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, wm = wv >> 1, wn = wv & 1;
   f32_items<SHORT>(tiles, hdr, Is / (16 * NT), T, [&](int g, int row0, int rows, int nt) {  // Is % 32 == 0
     f32x4_t acc[1][NT];
@@ -201,7 +206,10 @@ __global__ __launch_bounds__(256) void ffn_down_f32_kernel(const float* __restri
 // 2048 (550 MB), 4 picks: 300 (37 possible rows) 161 | 157, 1000 (125) 362 | 382.  So up to 64 possible rows, or 256 where the
 // weights fit the memory-side cache of 256 MB.
 // One column block halves a wave's chain where there are CUs to spare: 64 tokens, 32 of 128 x 256, gate-up 8.1 | 9.4, 100
-// tokens on 32 of 256 x 1024 17.4 | 19.4; 300 tokens there (768 tiles) 29.9 | 28.3, 16 on 128 of them (640) 29.3 | 27.0.
+// tokens on 32 of 256 x 1024 17.4 | 19.4; 300 tokens there (768 tiles) 29.9 | 28.3, 16 on 128 of them (640) 29.3 | 27.0.  Four
+// workgroups fit a CU, so two tiles of two column blocks per CU are one round.  Both GEMMs, 64 tokens on 32 of d = 256 | 1024 |
+// 2048, one column block, two: 320 tiles 18.6, 19.5 | 32.5, 38.2 | 54.9, 64.5; 512 23.3, 24.1 | 41.3, 43.1 | 96.9, 92.5, skewed
+// load 25.2, 26.8 | 56.0, 61.8 | 103, 109.  (With a ring of six stages three fit: 512 tiles 26.5 | 46.2 | 99.9.)
 int ffn_f32_list(int T, int k_max, int E, int d, int Is) {
   const long pairs = (long)T * k_max, groups = pairs < E ? pairs : E;
   const bool cached = 12.0 * E * d * Is <= 256e6;
@@ -218,7 +226,7 @@ hipError_t launch_ffn_gate_up(int dtype, const void* x, const void* w_gu, const 
                                (uint16_t*)h, T, d, Is, k_max, few, max_mtiles, s);
   const bool wide = (long)T * d >= (1L << 30) || (long)Is * d >= (1L << 29);
   auto run = [&](auto* kern, int nt) {
-    const int grid = persistent_grid((long)max_mtiles * F32_BLOCKS * (Is / (16 * nt)), nt == 1 ? 4 : 2);
+    const int grid = persistent_grid((long)max_mtiles * F32_BLOCKS * (Is / (16 * nt)), nt == 1 ? F32_PER_CU<1> : F32_PER_CU<2>);
     const int lds = nt == 1 ? F32Tile<1>::LDS_BYTES : F32Tile<2>::LDS_BYTES;
     kern<<<grid, 256, lds, s>>>((const float*)x, (const float*)w_gu, sorted_pair, tiles, hdr, (float*)h, d, Is, k_max, T);
   };
@@ -242,7 +250,7 @@ hipError_t launch_ffn_down(int dtype, const void* h, const void* w_dn, const MTi
   if (dtype != 0)
     return launch_down_bf16((const uint16_t*)h, (const uint16_t*)w_dn, tiles, hdr, (uint16_t*)y, T, d,
                             Is, few, max_mtiles, s);
-  const int grid = persistent_grid((long)max_mtiles * F32_BLOCKS * (d / F32Tile<2>::BE), 2);
+  const int grid = persistent_grid((long)max_mtiles * F32_BLOCKS * (d / F32Tile<2>::BE), F32_PER_CU<2>);
   const bool wide = (long)Is * d >= (1L << 30);
   auto* kern = few != 0 ? (wide ? ffn_down_f32_kernel<true, true> : ffn_down_f32_kernel<false, true>)
                             : (wide ? ffn_down_f32_kernel<true, false> : ffn_down_f32_kernel<false, false>);
