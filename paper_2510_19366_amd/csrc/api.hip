@@ -210,7 +210,7 @@ static int do_dispatch(const moe_prism_shape* s, const Layout& L, const int32_t*
   int32_t* chunk = reinterpret_cast<int32_t*>(ws + L.chunk_cnt);
   MTile* tiles = plan != nullptr ? reinterpret_cast<MTile*>(ws + L.tiles) : nullptr;
   return do_dispatch_over(L, ids, cnt, off, sorted_pair, slot_of_pair, chunk, hdr, tiles,
-                          plan != nullptr ? *plan : FfnPlan{}, s->T, E, s->k_max, st);
+                          plan != nullptr ? *plan : FfnPlan{false, 0, {8, true}, 0}, s->T, E, s->k_max, st);
 }
 
 static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, const void* w_gu,
