@@ -154,7 +154,7 @@ static bool use_fused_ffn(const moe_prism_shape* s) {
 // What follows a dispatch: blocks of the tiles for few rows per sub-expert, or 0 (fp32: see ffn_f32_list), and how the
 // groups are cut for it.  Few rows: into the tiles of ffn_few_kernel, which then are at most 2 E (16 rows and 16 tokens, 32
 // and 24 E pairs, 64 and 64 tokens or 56 E pairs: no more than E beside the last one of each group).  Else into
-// tiles of FFN_BM, of even length where the two-kernel path follows.
+// tiles of FFN_BM, of even length where the two-kernel path of bf16 or the short list of fp32 follows.
 // Made once per call: the table and the kernels that read it go by the same one, whatever becomes of the environment.
 struct FfnPlan {
   bool fused;
@@ -167,6 +167,7 @@ static FfnPlan plan_ffn(const Layout& L, int dtype, int T, int k, int E, int d, 
   static_assert(FFN_BM == 1 << 8);
   if (dtype != MOE_PRISM_BF16) {
     p.few = ffn_f32_list(T, k, E, d, Is);
+    p.cut.even = p.few != 0;  // see ffn_f32_list
     return p;
   }
   p.few = ffn_few_blocks(T, k, E, d, Is, fused);

@@ -200,11 +200,21 @@ __global__ __launch_bounds__(256) void ffn_down_f32_kernel(const float* __restri
 // Which list of row blocks (row_blocks.h) and tile the fp32 kernels take: 0 the list of all row blocks, else the list of
 // first blocks, then second, with gate-up tiles of 1 or 2 column blocks per wave.
 // The list of all eight possible blocks of an m-tile is mostly empty where groups are short, and brings those that exist
-// to few workgroups; but what runs at the same time shares weights.  Both GEMMs between HIP events, us, all | first,
-// second: 64 tokens of 8 picks on 32 sub-experts of 128 x 256 15.5 | 15.3, 100 28 | 16, 300 29 | 18, 1024 32 | 31; 32 of 256 x
-// 1024: 100 79 | 32, 300 79 | 49, 1000 129 | 113; 128 of 256 x 1024 (400 MB): 100 293 | 99, 1000 (62 rows) 294 | 164; 32 of 704 x
-// 2048 (550 MB), 4 picks: 300 (37 possible rows) 161 | 157, 1000 (125) 362 | 382.  So up to 64 possible rows, or 256 where the
-// weights fit the memory-side cache of 256 MB.
+// to few workgroups, the more so the fewer n-tiles a GEMM has; but what runs at the same time shares weights.  Both GEMMs
+// between HIP events, us, all | first, second: 64 tokens of 8 picks on 32 sub-experts of 128 x 256 15.5 | 15.3, 100 28 | 16, 300
+// 29 | 18, 1024 32 | 31; 32 of 256 x 1024: 100 79 | 32, 300 79 | 49, 1000 129 | 113.  Layer calls back to back, 4 picks, weights
+// beyond the memory-side cache of 256 MB, by possible rows, even load, then skewed (router bias N(0, 1) per expert):
+//   128 of 256 x 1024: 20 314 | 124, 207 | 179; 50 315 | 181, 268 | 277; 62 315 | 196, 267 | 287;  256 of them: 50 623 | 331, 405 |
+//     367; 62 623 | 386, 443 | 449;  32 of 256 x 4096: 62 291 | 206, 342 | 302;  128 of 704 x 512: 62 316 | 245, 247 | 254;
+//   64 of 512 x 1024: 40 202 | 139, 261 | 255; 62 203 | 187, 280 | 285;  128 of 704 x 1024: 40 386 | 295, 251 | 262; 50 428 | 397; 62 444 | 446,
+//     632 | 657;  32 of 1024 x 1024: 40 148 | 140, 191 | 201; 50 165 | 167; 62 172 | 182, 279 | 291;  32 of 704 x 2048: 37 189 | 174,
+//     222 | 236; 62 229 | 243, 554 | 567.
+// So up to 64 possible rows, 56 where the gate-up has more than 16 n-tiles and the down GEMM 16, 256 where the weights fit that cache (32 of 256 x
+// 1024, 8 picks: 250 rows 151 | 136, 182 | 183).
+// The list of all blocks wants full m-tiles: 2000 tokens on the last shape (two m-tiles a group) 228, with tiles of even
+// length 258; 4000 on 32 of 704 x 2048 975, 1005.  The other list is a little better off with even ones where the
+// load is skewed (256 of 256 x 1024, 50 and 62 rows 367 and 449, full 389 and 464; 32 of 256 x 4096 the other way round, 302
+// and 287).
 // One column block halves a wave's chain where there are CUs to spare: 64 tokens, 32 of 128 x 256, gate-up 8.1 | 9.4, 100
 // tokens on 32 of 256 x 1024 17.4 | 19.4; 300 tokens there (768 tiles) 29.9 | 28.3, 16 on 128 of them (640) 29.3 | 27.0.  Four
 // workgroups fit a CU, so two tiles of two column blocks per CU are one round.  Both GEMMs, 64 tokens on 32 of d = 256 | 1024 |
@@ -212,8 +222,8 @@ __global__ __launch_bounds__(256) void ffn_down_f32_kernel(const float* __restri
 // load 25.2, 26.8 | 56.0, 61.8 | 103, 109.  (With a ring of six stages three fit: 512 tiles 26.5 | 46.2 | 99.9.)
 int ffn_f32_list(int T, int k_max, int E, int d, int Is) {
   const long pairs = (long)T * k_max, groups = pairs < E ? pairs : E;
-  const bool cached = 12.0 * E * d * Is <= 256e6;
-  if (T > 2 * F32_ROWS && pairs > (cached ? 256L : 64L) * E) return 0;
+  const bool cached = 12.0 * E * d * Is <= 256e6, many_tiles = Is > 16 * 32 && d >= 16 * 64;
+  if (T > 2 * F32_ROWS && pairs > (cached ? 256L : many_tiles ? 56L : 64L) * E) return 0;
   return groups * (Is / 32) * cdiv(cdiv(pairs, E), F32_ROWS) <= 2L * num_cus() ? 1 : 2;
 }
 

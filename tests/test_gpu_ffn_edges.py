@@ -76,6 +76,9 @@ def ffn(dtype, x, w_gu, w_dn, group):
     ("f32", "auto", FOUR, 320, 96),
     ("f32", "auto", [256, 3] * 30 + [40], 64, 640),  # two column blocks per wave
     ("f32", "auto", [300, 600, 1], 64, 32),  # the list of all row blocks
+    # many weight tiles, 53 and 57 rows per group on average: on both sides of the border between the lists
+    ("f32", "auto", [0, 130, 31] * 13 + [33], 1024, 544),
+    ("f32", "auto", [0, 140, 33] * 13 + [34], 1024, 544),
 ])
 def test_group_sizes_at_the_edges_of_the_tiles(dtype, path, sizes, d, Is, monkeypatch):
     monkeypatch.setenv("MOE_PRISM_FFN", path)
