@@ -284,7 +284,7 @@ def main():
         "config": {"workload": wl.name, "T": wl.T, "d": d, "n_experts": wl.n_experts,
                    "n_sub": wl.n_sub, "inter_sub": Is, "k_max": wl.k_max, "pairs": P,
                    "requests": int(len(wl.req_k)), "k_mix": "per-request", "route": args.route,
-                   "ffn_path": "fused" if fused else "split"},
+                   "ffn_path": B.ffn_path(shape)},
         "ffn_mfma_util_pct": 100.0 * ffn_tflops / PEAK_BF16_TFLOPS,
         "ffn_mfma_util_pct_measured": {k: 100.0 * ffn_tflops / v for k, v in peaks.items()},
         "ffn_tflops": ffn_tflops,

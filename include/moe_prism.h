@@ -140,6 +140,16 @@ MOE_PRISM_API int moe_prism_grouped_ffn(const moe_prism_shape* shape, const void
                           void* stream);
 
 /*
+ * Which of the kernels above moe_prism_grouped_ffn and moe_prism_layer launch for `shape` with
+ * the present environment (host only): MOE_PRISM_FFN_SPLIT (gate-up and down), _FUSED (one
+ * kernel) or _FEW (gate-up and down on tiles for few rows per sub-expert; bf16 only).
+ */
+#define MOE_PRISM_FFN_SPLIT 0
+#define MOE_PRISM_FFN_FUSED 1
+#define MOE_PRISM_FFN_FEW 2
+MOE_PRISM_API int moe_prism_ffn_path(const moe_prism_shape* shape, int32_t* path);
+
+/*
  * Combine (Sec. 3.2.2, gate-weighted sum of the selected sub-expert outputs):
  *   out[t,:] = sum_{j < k_t} topk_w[t,j] * y[slot_of_pair[t*k_max+j], :]
  * j ascending, fp32 accumulation, one rounding to shape->dtype; k_t = 0 gives a

@@ -26,7 +26,7 @@ EXPORTS = ("moe_prism_workspace_bytes", "moe_prism_expand_k", "moe_prism_route",
            "moe_prism_partition_greedy", "moe_prism_partition_objective", "moe_prism_partition_anneal",
            "moe_prism_layer_offsets", "moe_prism_status", "moe_prism_timing_enable",
            "moe_prism_timing_select", "moe_prism_timing_read", "moe_prism_microbench",
-           "moe_prism_ffn_traffic_probe",
+           "moe_prism_ffn_path", "moe_prism_ffn_traffic_probe",
            "moe_prism_strerror")
 
 
@@ -184,18 +184,11 @@ def moe_prism_layer(shape, x, w_router, router_bias, k_tok, w_gate_up, w_down, w
 
 
 def ffn_path(shape):
-    """Which grouped-FFN kernels moe_prism_grouped_ffn / _layer launch for this shape: "few" (bf16, at most 64
-    tokens: gate-up and down on tiles for few rows per sub-expert), "fused" (bf16, inter_sub in {64, 128, 192},
-    d >= 256, unless MOE_PRISM_FFN=split or there are more sub-experts than CUs with 10 to 24 possible rows each) or
-    "split" (gate-up and down)."""
-    if shape.dtype == 1 and shape.T <= 64:
-        return "few"
-    ok = (shape.dtype == 1 and shape.inter_sub in (64, 128, 192) and shape.d % 64 == 0
-          and shape.d >= 256 and shape.T * shape.d * 2 < 2 ** 32)
-    cus = torch.cuda.get_device_properties(0).multi_processor_count if torch.cuda.is_available() else 256
-    if shape.E > cus and 10 * shape.E <= shape.T * shape.k_max <= 24 * shape.E:
-        ok = False
-    return "fused" if ok and os.environ.get("MOE_PRISM_FFN") != "split" else "split"
+    """Which grouped-FFN kernels moe_prism_grouped_ffn / _layer launch for this shape: "fused" (one kernel), "few"
+    (gate-up and down on tiles for few rows per sub-expert) or "split" (gate-up and down).  The library's own choice."""
+    path = C.c_int32(-1)
+    _check(lib().moe_prism_ffn_path(C.byref(shape), C.byref(path)))
+    return ("split", "fused", "few")[path.value]
 
 
 STATIC_WS_BYTES = 64 << 20  # MOE_PRISM_STATIC_WS_BYTES

@@ -402,6 +402,16 @@ int moe_prism_grouped_ffn(const moe_prism_shape* shape, const void* x, const voi
                 static_cast<char*>(ws), (hipStream_t)stream, plan_ffn(L, shape));
 }
 
+int moe_prism_ffn_path(const moe_prism_shape* shape, int32_t* path) {
+  const int rc = check_shape(shape);
+  if (rc) return rc;
+  if (path == nullptr) return MOE_PRISM_ERR_INVALID_ARG;
+  const FfnPlan p = plan_ffn(layout_of(shape), shape);
+  const bool few = shape->dtype == MOE_PRISM_BF16 && p.few != 0;
+  *path = p.fused ? MOE_PRISM_FFN_FUSED : few ? MOE_PRISM_FFN_FEW : MOE_PRISM_FFN_SPLIT;
+  return MOE_PRISM_OK;
+}
+
 int moe_prism_ffn_traffic_probe(const moe_prism_shape* shape, const void* x, const void* w_gate_up,
                                 const void* w_down, const int32_t* group_offset,
                                 const int32_t* sorted_pair, void* y, void* ws, size_t ws_bytes,

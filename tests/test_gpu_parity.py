@@ -103,7 +103,7 @@ def test_narrow_sub_experts_both_ffn_paths(case, path, monkeypatch):
     B.moe_prism_timing_enable(False)
     assert np.array_equal(to_np(out), r["out"])
     # the intended kernels ran
-    few = case["T"] <= 64
+    few = case["T"] <= 64 or (path == "split" and case["T"] == 65)  # a row or two per group, without the fused kernel
     assert (calls["ffn_fused"], calls["ffn_gate_up"], calls["ffn_down"]) == \
         ((1, 0, 0) if path == "fused" and not few else (0, 1, 1))
     assert B.ffn_path(r["shape"]) == ("few" if few else path)
@@ -115,18 +115,20 @@ def test_narrow_sub_experts_both_ffn_paths(case, path, monkeypatch):
     dict(T=700, d=1024, N=4, S=2, Is=704, k_max=5),     # 11 down stages
     dict(T=1100, d=448, N=3, S=4, Is=352, k_max=7),     # Is % 64 != 0: half a stage at the end of the down GEMM's K
     dict(T=1100, d=192, N=3, S=4, Is=160, k_max=7),     # K too short for the ring in both GEMMs
-    dict(T=65, d=320, N=16, S=4, Is=512, k_max=2),      # a row or two per group: most waves multiply nothing
+    dict(T=65, d=320, N=16, S=4, Is=512, k_max=2),      # a row or two per group: tiles for few rows
+    dict(T=1900, d=320, N=16, S=4, Is=512, k_max=2, some=65),  # the same in the ring driver: most waves multiply nothing
     dict(T=5, d=320, N=2, S=1, Is=512, k_max=2),        # a handful of tokens: small tiles
     dict(T=2600, d=384, N=2, S=1, Is=1024, k_max=2),    # groups of many m-tiles, several items per workgroup
 ])
 def test_wide_sub_experts(case):
     rng = np.random.default_rng(case["T"] + 1)
     k = rng.integers(0, case["k_max"] + 1, size=case["T"]).astype(np.int32)
+    k[case.get("some", case["T"]):] = 0  # the tokens that pick anything
     wl = W.make_workload("wide", dtype="bf16", d=case["d"], n_experts=case["N"], n_sub=case["S"],
                          inter_sub=case["Is"], req_tokens=[1] * case["T"], req_k=k,
                          k_max=case["k_max"], seed=case["T"], bias_std=1.0, w_std=0.05)
     r = run_stages(wl)
-    assert B.ffn_path(r["shape"]) == ("few" if case["T"] <= 64 else "split")
+    assert B.ffn_path(r["shape"]) == ("few" if case["T"] <= 65 else "split")
     ref = O.layer_of(wl, return_all=True)
     check_against_oracle(wl, r, ref)
     assert row_rel(r["y"], ref["y"]) <= 4e-2 and row_rel(r["out"], ref["out"]) <= 4e-2

@@ -49,6 +49,31 @@ def test_host_side_validation():
     assert all(v % 256 == 0 for v in offs.values()) and max(offs.values()) < n.value
 
 
+@pytest.mark.parametrize("T,E,k_max,d,Is,dtype,env,path", [
+    # narrow sub-experts: up to 64 tokens, and 10 to 24 possible rows for each of more sub-experts than CUs (256)
+    (64, 512, 32, 2048, 192, "bf16", "", "few"), (65, 512, 32, 2048, 192, "bf16", "", "fused"),
+    (159, 512, 32, 2048, 192, "bf16", "", "fused"), (160, 512, 32, 2048, 192, "bf16", "", "few"),
+    (384, 512, 32, 2048, 192, "bf16", "", "few"), (385, 512, 32, 2048, 192, "bf16", "", "fused"),
+    (65, 256, 32, 2048, 192, "bf16", "", "fused"), (65, 256, 32, 2048, 192, "bf16", "split", "few"),
+    (385, 256, 32, 2048, 192, "bf16", "split", "few"), (449, 256, 32, 2048, 192, "bf16", "split", "split"),
+    (385, 256, 32, 192, 192, "bf16", "", "few"),     # d below the fused kernel's
+    # others: up to 56 possible rows, any number for up to 64 tokens
+    (597, 128, 12, 2048, 704, "bf16", "", "few"), (598, 128, 12, 2048, 704, "bf16", "", "split"),
+    (64, 4, 4, 4096, 3584, "bf16", "", "few"), (65, 4, 4, 4096, 3584, "bf16", "", "split"),
+    (8, 2, 1, 65536, 16384, "bf16", "", "split"),    # weights of a sub-expert beyond 32-bit offsets
+    (8, 32, 8, 256, 128, "f32", "", "split")])
+def test_ffn_path_is_the_rule_of_the_library(T, E, k_max, d, Is, dtype, env, path, monkeypatch):
+    monkeypatch.setenv("MOE_PRISM_FFN", env)
+    assert B.ffn_path(B.make_shape(T, d, E, 1, Is, k_max, dtype)) == path
+
+
+def test_ffn_path_refuses_what_the_layer_refuses():
+    out = C.c_int32(7)
+    assert B.lib().moe_prism_ffn_path(C.byref(B.make_shape(64, 250, 8, 4, 128, 8, "bf16")), C.byref(out)) == -2
+    assert B.lib().moe_prism_ffn_path(C.byref(B.make_shape(64, 256, 8, 4, 128, 8, "bf16")), None) == -1
+    assert out.value == 7
+
+
 def test_proxy_stage_that_would_overflow_the_tile_table_is_refused():
     # the proxy-gate stage cuts T*m pairs over N groups into the layer's tile table of
     # T*k_max/256 + E entries; a shape where they do not fit is refused on the host
