@@ -38,3 +38,20 @@ def test_layer_with_a_skewed_load(T, N, S, k_max, d, Is, longest):
     out, dev, ws = run_layer(wl, r["dev"], r["ws"])
     assert np.array_equal(to_np(out), r["out"])
     assert B.moe_prism_status(ws)[0] == 0
+
+
+@pytest.mark.parametrize("T,path", [(159, "fused"), (160, "few"), (384, "few"), (385, "fused")])
+def test_narrow_sub_experts_on_both_sides_of_the_few_rows_rule(T, path):
+    # 512 sub-experts, 32 picks: 10 and 24 possible rows for each
+    k = np.random.default_rng(T).integers(0, 33, size=T).astype(np.int32)
+    wl = W.make_workload("border", dtype="bf16", d=256, n_experts=64, n_sub=8, inter_sub=64, req_tokens=[1] * T,
+                         req_k=k, k_max=32, seed=T, bias_std=1.0, w_std=0.05)
+    dev = B.to_device(wl)
+    assert B.ffn_path(dev["shape"]) == path
+    B.moe_prism_timing_enable(True)
+    B.moe_prism_timing_read()
+    out, _, _ = run_layer(wl, dev)
+    calls = {name: v[1] for name, v in B.moe_prism_timing_read().items()}
+    B.moe_prism_timing_enable(False)
+    assert (calls["ffn_fused"], calls["ffn_gate_up"], calls["ffn_down"]) == ((1, 0, 0) if path == "fused" else (0, 1, 1))
+    assert max_rel(to_np(out), O.layer_of(wl)) <= 2e-2
