@@ -55,9 +55,9 @@ __global__ __launch_bounds__(TILES_THREADS) void ffn_tiles_kernel(const int32_t*
     const int nt = cut.tiles(n);
     int round_total = 0;
     const int first = carry + block_scan(nt, wave_tot, &round_total);
-    const int per = cut.rows(n);
-    for (int i = 0; i < nt && first + i < max_tiles; ++i)  // count: never points past the table
-      put_tile(tiles, cut, first + i, g, lo + i * per, min(per, n - i * per), first, min(nt, max_tiles - first));
+    const int per = cut.rows(n), count = min(nt, max_tiles - first);  // never points past the table
+#pragma unroll 4
+    for (int i = 0; i < count; ++i) put_tile(tiles, cut, first + i, g, lo + i * per, min(per, n - i * per), first, count);
     carry += round_total;
   }
   const int n_tiles = min(carry, max_tiles);
