@@ -1161,7 +1161,10 @@ static hipError_t launch_op(const Op& op, int T, int K, int n_cols, int few, int
 //   four up to 56 | ring driver: 128 of 704: 48 221 | 249, skewed 199 | 223; 60 228 | 251, 205 | 228; 256 of 352: 48 235 | 262, 226 |
 //     244; 60 242 | 265, 210 | 206; 75 262 | 270, 242 | 216; 128 of 768, 8 picks: 50 257 | 282, 231 | 224; 56 259 | 284, 248 | 245; 62
 //     278 | 287, 249 | 233; 32 of 3584 x 4096: 50 477 | 518, 502 | 491 (other tokens 506 | 514); 72 485 | 523, 526 | 499.  So with
-//     skewed load they meet at 50 to 60, with even load at 75 and beyond;
+//     skewed load they meet at 50 to 60, with even load at 75 and beyond.  With a bias N(0, 3^2) nearly all tokens have the same
+//     picks, groups are as long as the batch and the ring driver is ahead where that is many tiles of 64.  Layer calls of 400 |
+//     200 tokens, four | ring driver: 128 of 704 130 | 124, 89 | 91; 256 of 352 145 | 131, 96 | 103; 256 of 256 127 | 123, 89 |
+//     106; the same 400 without a bias 254 | 267, 261 | 290, 215 | 237;
 //   fused, two blocks | fused kernel: it gives a tile a workgroup, so it is good at about as many touched groups as CUs.  More
 //     sub-experts than CUs, 512 of 192: 6.2 208 | 249, skewed 109 | 111; 10 217 | 255, 127 | 184; 24 237 | 264, 187 | 244; 37.5
 //     253 | 273, 214 | 255.  10 and 24 are where m-tiles of 256 rows were worth it (skewed: 8.8 147 | 122, 24 277 | 247); with
