@@ -224,10 +224,11 @@ __device__ __forceinline__ int small_groups(const SmallDispatch& a, int32_t* __r
     off_lds[g] = row0;
     a.off[g] = row0;
     a.cnt[g] = n;
-    if (a.tiles != nullptr)
-      for (int i = 0; i < nt && tile + i < a.max_tiles; ++i)
-        put_tile(a.tiles, a.cut, tile + i, g, row0 + (i << a.cut.log2), min(n - (i << a.cut.log2), 1 << a.cut.log2), tile,
-                 min(nt, a.max_tiles - tile));
+    if (a.tiles != nullptr) {
+      const int rows = 1 << a.cut.log2, end = min(nt, a.max_tiles - tile);
+      if (end > 0) put_tile(a.tiles, a.cut, tile, g, row0, min(n, rows), tile, end);  // mostly the only one
+      for (int i = 1; i < end; ++i) put_tile(a.tiles, a.cut, tile + i, g, row0 + i * rows, min(n - i * rows, rows), tile, end);
+    }
     run += n + nt * TILE;
   }
   if (tid == 0) {
