@@ -32,7 +32,7 @@ __global__ __launch_bounds__(256) void dispatch_count_kernel(const int32_t* __re
   extern __shared__ u64 masks[];
   const int c = blockIdx.x, t0 = c * 64 * W;
   const int ntok = min(64 * W, T - t0);
-  Picks picks(ids + (size_t)t0 * k_max, ntok, k_max);
+  Picks<false> picks(ids + (size_t)t0 * k_max, ntok, k_max);
   build_masks(picks, masks, E, W);
   for (int g = threadIdx.x; g < E; g += blockDim.x) {
     int n = 0;
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_place_kernel(
   int32_t* first_lds = off_lds + E + 1;
   const int c = blockIdx.x, t0 = c * 64 * W;
   const int ntok = max(min(64 * W, T - t0), 0);
-  Picks picks(ids + (size_t)t0 * k_max, ntok, k_max);
+  Picks<false> picks(ids + (size_t)t0 * k_max, ntok, k_max);
   picks.load(0);  // on their way while the offsets are derived
   group_offsets([&](int g) { return cnt[g]; }, off_lds, first_lds, wave_tot, cut, E);
   if (c == 0) write_offsets(off_lds, first_lds, off, hdr, tiles != nullptr, max_tiles, E);
@@ -133,7 +133,7 @@ __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_small_kernel(const 
                                                                           int E, int k_max) {
   extern __shared__ u64 masks[];
   __shared__ int32_t wave_tot[DISPATCH_THREADS / 64];
-  dispatch_one_workgroup(ids, a, hdr, masks, wave_tot, T, E, k_max);
+  dispatch_one_workgroup<false>(ids, a, hdr, masks, wave_tot, T, E, k_max);
 }
 
 hipError_t launch_dispatch_small(const int32_t* ids, int32_t* cnt, int32_t* off, int32_t* hdr,

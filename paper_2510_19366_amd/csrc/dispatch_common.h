@@ -10,7 +10,10 @@ constexpr int DISPATCH_THREADS = 256;
 
 // The picks of a run of tokens, PICKS per thread at a time, so that a memory latency is paid once per batch and not
 // once per pick; the last batch loaded stays in registers.
+// AGENT: the picks were stored at agent scope by other workgroups of this launch and are loaded likewise, past this CU's
+// and XCD's caches; else they are an earlier launch's.
 constexpr int PICKS = 8;
+template <bool AGENT>
 struct Picks {
   const int32_t* ids;
   int n, k_max;
@@ -25,7 +28,7 @@ struct Picks {
     for (int u = 0; u < PICKS; ++u) {
       const int i = first + u * DISPATCH_THREADS + (int)threadIdx.x;
       if (first + u * DISPATCH_THREADS >= n) break;  // the same for all threads
-      g[u] = i < n ? ids[i] : -1;
+      g[u] = i >= n ? -1 : AGENT ? __hip_atomic_load(ids + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ids[i];
     }
   }
   // f(index, sub-expert) for every pick of this thread; last to first if `back`, so that a batch is used twice
@@ -47,6 +50,7 @@ struct Picks {
 };
 
 // masks[g * W + w]: which of the run's tokens 64 w .. 64 w + 63 picked g
+template <class Picks>
 __device__ __forceinline__ void build_masks(Picks& picks, u64* masks, int E, int W) {
   picks.load(0);
   for (int i = threadIdx.x; i < E * W; i += DISPATCH_THREADS) masks[i] = 0ull;
@@ -151,7 +155,7 @@ __device__ __forceinline__ void write_tiles(const int32_t* off_lds, const int32_
 }
 
 // slots of a run's pairs, the first of which is pair0; base(g): the group's first slot plus its rows from earlier tokens
-template <class Base>
+template <class Picks, class Base>
 __device__ __forceinline__ void place_pairs(Picks& picks, const u64* masks, Base base, int32_t* __restrict__ sorted_pair,
                                             int32_t* __restrict__ slot_of_pair, size_t pair0, int P, int E, int W) {
   picks.each(true, [&](int i, int g) {
@@ -238,13 +242,14 @@ __device__ __forceinline__ int small_groups(const SmallDispatch& a, int32_t* __r
   return P;
 }
 
+template <bool AGENT>
 __device__ __forceinline__ void dispatch_one_workgroup(const int32_t* __restrict__ ids, const SmallDispatch& a,
                                                        int32_t* __restrict__ hdr, u64* lds,
                                                        int32_t* wave_tot, int T, int E, int k_max) {
   const int W = (T + 63) / 64;
   u64* masks = lds;
   int32_t* off_lds = reinterpret_cast<int32_t*>(masks + (size_t)E * W);
-  Picks picks(ids, T, k_max);
+  Picks<AGENT> picks(ids, T, k_max);
   build_masks(picks, masks, E, W);
   const int P = small_groups(a, hdr, masks, off_lds, wave_tot, W, E, DISPATCH_THREADS);
   __syncthreads();

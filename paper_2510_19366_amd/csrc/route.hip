@@ -360,7 +360,11 @@ __global__ __launch_bounds__(64 * (MODE == TOPK_SOLO ? SOLO_WAVES : TOPK_WAVES))
     if (renorm) denom = wave_sum(dsel);
     for (int j = lane; j < k_max; j += 64) {
       bool on = j < kt;
-      ids[(size_t)t * k_max + j] = on ? sid[j] : -1;
+      const int32_t id = on ? sid[j] : -1;
+      if constexpr (MODE == TOPK_LAST)
+        __hip_atomic_store(&ids[(size_t)t * k_max + j], id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else
+        ids[(size_t)t * k_max + j] = id;
       if (MODE == TOPK_SOLO && on) atomicOr(&solo_masks[sid[j]], 1ull << t);
       wout[(size_t)t * k_max + j] = on ? scale * expf(se[j] - mx) / denom : 0.0f;
     }
@@ -388,13 +392,15 @@ __global__ __launch_bounds__(64 * (MODE == TOPK_SOLO ? SOLO_WAVES : TOPK_WAVES))
     // the default 64 KiB, so there is no room for static LDS beside them
     int32_t* is_last = reinterpret_cast<int32_t*>(topk_smem + small_dispatch_lds(T, E));
     int32_t* wave_tot = is_last + 1;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // this workgroup's picks are visible on the device before it counts itself done
+    // The picks were stored at agent scope, i.e. through this XCD's L2, so once they are acknowledged every CU can read
+    // them: no release fence, which would have each workgroup write back all of its L2 (64 fp32 tokens of 8 x 4
+    // sub-experts, layer calls: 24.5 -> 23.6 us; 37 of 128 x 4: 107.4 -> 107.0)
+    wait_vmem<0>();
     __syncthreads();
     if (threadIdx.x == 0) *is_last = atomicAdd(&hdr[HDR_TOPK_DONE], 1) == (int)gridDim.x - 1;
     __syncthreads();
     if (!*is_last) return;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    dispatch_one_workgroup(ids, small, hdr, reinterpret_cast<u64*>(topk_smem), wave_tot, T, E, k_max);
+    dispatch_one_workgroup<true>(ids, small, hdr, reinterpret_cast<u64*>(topk_smem), wave_tot, T, E, k_max);
   }
 }
 
