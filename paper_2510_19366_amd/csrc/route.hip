@@ -223,13 +223,7 @@ __global__ __launch_bounds__(64 * (MODE == TOPK_SOLO ? SOLO_WAVES : TOPK_WAVES))
   }
   int picked = 0;
   if (t < T) {
-    int kt = k_tok != nullptr ? k_tok[t] : k_max;  // null: every token takes k_max
-    kt = __builtin_amdgcn_readfirstlane(kt);
-    if (kt < 0 || kt > k_max) {
-      if (lane == 0) atomicOr(&hdr[HDR_FLAGS], 1);
-      kt = kt < 0 ? 0 : k_max;
-    }
-
+    const int asked = k_tok != nullptr ? k_tok[t] : k_max;  // null: every token takes k_max
     const float NEG_INF = -__builtin_inff();
     constexpr int GONE = (int)0x80000000;  // key of an element beyond E
     float v[ELEMS];
@@ -238,6 +232,12 @@ __global__ __launch_bounds__(64 * (MODE == TOPK_SOLO ? SOLO_WAVES : TOPK_WAVES))
     for (int i = 0; i < ELEMS; ++i) {
       int g = i * 64 + lane;
       v[i] = g < E ? row[g] : NEG_INF;
+    }
+    // (behind the loads of the logits, so that one memory latency covers both)
+    int kt = __builtin_amdgcn_readfirstlane(asked);
+    if (kt < 0 || kt > k_max) {
+      if (lane == 0) atomicOr(&hdr[HDR_FLAGS], 1);
+      kt = kt < 0 ? 0 : k_max;
     }
     // full-softmax denominator (only needed when weights are not renormalised)
     float lmax = NEG_INF;
