@@ -31,7 +31,8 @@ inline uint64_t splitmix64(uint64_t x) {
 // tokens are one vector: a sorting network of vector minima and maxima replaces one sort per token.
 // Every token's arithmetic, and the order in which the tokens' losses are added up, is that of the
 // plain definition, so the decisions do not depend on the vector width.
-// Measured for 256 tokens, 768 neurons, S = 4: 4.1 us a proposal with one sort per token, 0.11 us now.
+// Measured for 256 tokens, 768 neurons, S = 4: 4.1 us a proposal with one sort per token, 0.11 us so, 0.07 us with most
+// proposals decided in binary32.
 constexpr int V = 8;
 typedef double vd __attribute__((vector_size(V * sizeof(double))));
 typedef float vf __attribute__((vector_size(V * sizeof(float))));
@@ -39,14 +40,15 @@ constexpr int MAX_SUB = 64;
 
 #define MP_INLINE inline __attribute__((always_inline))
 
-MP_INLINE void order(vd& a, vd& b) {
-  const vd lo = b < a ? b : a, hi = b < a ? a : b;
+template <class Vec>
+MP_INLINE void order(Vec& a, Vec& b) {
+  const Vec lo = b < a ? b : a, hi = b < a ? a : b;
   a = lo;
   b = hi;
 }
 // Batcher's odd-even merge sort of S vectors (S = 0: of n)
-template <int S>
-MP_INLINE void sort_vectors(vd* v, int n) {
+template <int S, class Vec>
+MP_INLINE void sort_vectors(Vec* v, int n) {
   auto merge = [&](int m, int p, int k, int j) {
     for (int i = 0; i < k; ++i)
       if (i + j + k < m && (i + j) / (2 * p) == (i + j + k) / (2 * p)) order(v[i + j], v[i + j + k]);
@@ -140,23 +142,102 @@ MP_INLINE double swap_losses_any(const double* L, int Bp, int S, int k, const Sw
     default: return swap_losses_t<0>(L, Bp, S, k, w, tok, plain);
   }
 }
-#define MP_SWAP_LOSSES(NAME, TARGET)                                                                                  \
-  TARGET double NAME(const double* L, int Bp, int S, int k, const Swap& w, double* tok, double* plain) {              \
-    return tok != nullptr ? swap_losses_any(L, Bp, S, k, w, tok, plain) : swap_losses_any(L, Bp, S, k, w, nullptr, plain); \
+// The same sum in binary32, sixteen tokens at a time, from the group sums rounded to it (Lf): a bound of it decides most
+// proposals.  At most RUN vectors are added up before a lane goes on in binary64.
+constexpr int VF = 16, RUN = 16;
+typedef float vf16 __attribute__((vector_size(VF * sizeof(float))));
+template <int S>
+MP_INLINE double screen_t(const float* Lf, int Bp, int n, int k, const Swap& w) {
+  const int m = S > 0 ? S : n;
+  const float* row[S > 0 ? S : MAX_SUB];
+  int kept = 0;
+  for (int g = 0; g < m; ++g)
+    if (g != w.gi && g != w.gj) row[kept++] = Lf + (size_t)g * Bp;
+  const float *li = Lf + (size_t)w.gi * Bp, *lj = Lf + (size_t)w.gj * Bp;
+  auto at = [](const float* p) { return *reinterpret_cast<const vf16*>(p); };
+  vd total = {};
+  for (int b0 = 0; b0 < Bp; b0 += RUN * VF) {
+    vf16 sum = {};
+    for (int b = b0; b < std::min(Bp, b0 + RUN * VF); b += VF) {
+      vf16 v[S > 0 ? S : MAX_SUB];
+      for (int g = 0; g < m - 2; ++g) v[g] = at(row[g] + b);
+      const vf16 ai = at(w.ci + b), aj = at(w.cj + b);
+      v[m - 2] = at(li + b) - ai + aj;
+      v[m - 1] = at(lj + b) - aj + ai;
+      sort_vectors<S>(v, n);
+      vf16 s = {};
+      if constexpr (S > 0) {
+#pragma unroll
+        for (int i = 0; i < S; ++i)
+          if (i < k) s += v[i];
+      } else {
+        for (int i = 0; i < k; ++i) s += v[i];
+      }
+      sum += s;
+    }
+    const vf* half = reinterpret_cast<const vf*>(&sum);
+    total += __builtin_convertvector(half[0], vd) + __builtin_convertvector(half[1], vd);
   }
-MP_SWAP_LOSSES(swap_losses_512, __attribute__((target("avx512f"))))
-MP_SWAP_LOSSES(swap_losses_256, __attribute__((target("avx2"))))
-MP_SWAP_LOSSES(swap_losses_128, )
-#undef MP_SWAP_LOSSES
-typedef double (*SwapLosses)(const double*, int, int, int, const Swap&, double*, double*);
-SwapLosses pick_swap_losses() {
-  __builtin_cpu_init();
-  if (__builtin_cpu_supports("avx512f")) return swap_losses_512;
-  if (__builtin_cpu_supports("avx2")) return swap_losses_256;
-  return swap_losses_128;
+  double r = 0.0;
+  for (int i = 0; i < V; ++i) r += total[i];
+  return r;
+}
+MP_INLINE double screen_any(const float* Lf, int Bp, int S, int k, const Swap& w) {
+  switch (S) {
+    case 2: return screen_t<2>(Lf, Bp, S, k, w);
+    case 4: return screen_t<4>(Lf, Bp, S, k, w);
+    case 8: return screen_t<8>(Lf, Bp, S, k, w);
+    default: return screen_t<0>(Lf, Bp, S, k, w);
+  }
+}
+// row += column
+MP_INLINE void add_column_t(double* row, const float* column, int Bp) {
+  for (int b = 0; b < Bp; b += V)
+    *reinterpret_cast<vd*>(row + b) += __builtin_convertvector(*reinterpret_cast<const vf*>(column + b), vd);
+}
+// the group sums after a swap that is taken, and what is kept of them in binary32 (Lf == nullptr: nothing)
+MP_INLINE void apply_t(double* L, float* Lf, int Bp, const Swap& w) {
+  double *li = L + (size_t)w.gi * Bp, *lj = L + (size_t)w.gj * Bp;
+  for (int b = 0; b < Bp; b += V) {
+    const vd ai = __builtin_convertvector(*reinterpret_cast<const vf*>(w.ci + b), vd);
+    const vd aj = __builtin_convertvector(*reinterpret_cast<const vf*>(w.cj + b), vd);
+    vd &ri = *reinterpret_cast<vd*>(li + b), &rj = *reinterpret_cast<vd*>(lj + b);
+    ri = ri - ai + aj;
+    rj = rj - aj + ai;
+    if (Lf != nullptr) {
+      *reinterpret_cast<vf*>(Lf + (size_t)w.gi * Bp + b) = __builtin_convertvector(ri, vf);
+      *reinterpret_cast<vf*>(Lf + (size_t)w.gj * Bp + b) = __builtin_convertvector(rj, vf);
+    }
+  }
 }
 
-// memory for vectors of 8 doubles
+// The loops over the tokens for the widest vectors of this CPU.
+struct Loops {
+  double (*losses)(const double* L, int Bp, int S, int k, const Swap& w, double* tok, double* plain);
+  double (*screen)(const float* Lf, int Bp, int S, int k, const Swap& w);
+  void (*add_column)(double* row, const float* column, int Bp);
+  void (*apply)(double* L, float* Lf, int Bp, const Swap& w);
+};
+#define MP_LOOPS(WIDTH, TARGET)                                                                                            \
+  TARGET double losses_##WIDTH(const double* L, int Bp, int S, int k, const Swap& w, double* tok, double* plain) {        \
+    return tok != nullptr ? swap_losses_any(L, Bp, S, k, w, tok, plain) : swap_losses_any(L, Bp, S, k, w, nullptr, plain); \
+  }                                                                                                                        \
+  TARGET double screen_##WIDTH(const float* Lf, int Bp, int S, int k, const Swap& w) { return screen_any(Lf, Bp, S, k, w); } \
+  TARGET void add_column_##WIDTH(double* row, const float* column, int Bp) { add_column_t(row, column, Bp); }              \
+  TARGET void apply_##WIDTH(double* L, float* Lf, int Bp, const Swap& w) { apply_t(L, Lf, Bp, w); }                         \
+  constexpr Loops loops_##WIDTH{losses_##WIDTH, screen_##WIDTH, add_column_##WIDTH, apply_##WIDTH};
+MP_LOOPS(512, __attribute__((target("avx512f"))))
+MP_LOOPS(256, __attribute__((target("avx2"))))
+MP_LOOPS(128, )
+#undef MP_LOOPS
+const Loops& pick_loops() {
+  __builtin_cpu_init();
+  if (__builtin_cpu_supports("avx512f")) return loops_512;
+  if (__builtin_cpu_supports("avx2")) return loops_256;
+  return loops_128;
+}
+
+// memory for vectors of 64 bytes
 template <class T>
 struct Aligned {
   T* p;
@@ -173,8 +254,9 @@ struct Problem {
   int B, C, S, Bp;
   Aligned<float> cols;   // [C][Bp]
   Aligned<double> L;     // [S][Bp]: neurons added in ascending index order
+  const Loops& loops = pick_loops();
   Problem(int B_, int C_, int S_, const float* A, const int32_t* g)
-      : B(B_), C(C_), S(S_), Bp((B_ + V - 1) / V * V), cols((size_t)C_ * Bp), L((size_t)S_ * Bp) {
+      : B(B_), C(C_), S(S_), Bp((B_ + VF - 1) / VF * VF), cols((size_t)C_ * Bp), L((size_t)S_ * Bp) {
     // |A| turned over in blocks of 4 x 4, 16 neurons (whole lines) of 4 tokens at a time
     const int B4 = B / 4 * 4, C4 = C / 4 * 4;
     const __m128 magnitude = _mm_castsi128_ps(_mm_set1_epi32(0x7fffffff));
@@ -188,11 +270,7 @@ struct Problem {
         }
     for (int c = 0; c < C; ++c)
       for (int b = c < C4 ? B4 : 0; b < B; ++b) cols.p[(size_t)c * Bp + b] = std::fabs(A[(size_t)b * C + c]);
-    for (int c = 0; c < C; ++c) {
-      const float* a = column(c);
-      double* l = L.p + (size_t)g[c] * Bp;
-      for (int b = 0; b < Bp; ++b) l[b] += (double)a[b];
-    }
+    for (int c = 0; c < C; ++c) loops.add_column(L.p + (size_t)g[c] * Bp, column(c), Bp);
   }
   const float* column(int c) const { return cols.p + (size_t)c * Bp; }
 };
@@ -248,7 +326,7 @@ extern "C" int moe_prism_partition_objective(int32_t B, int32_t C, int32_t S, in
   const Problem P(B, C, S, A, group_of);
   Aligned<double> tok(P.Bp);
   double unused;
-  pick_swap_losses()(P.L.p, P.Bp, S, S - k_in, Swap{nullptr, nullptr, 0, 0, nullptr, nullptr}, tok.p, &unused);
+  P.loops.losses(P.L.p, P.Bp, S, S - k_in, Swap{nullptr, nullptr, 0, 0, nullptr, nullptr}, tok.p, &unused);
   double total = 0.0;
   for (int b = 0; b < B; ++b) total += tok.p[b];
   *loss = total;
@@ -263,16 +341,17 @@ extern "C" int moe_prism_partition_anneal(int32_t B, int32_t C, int32_t S, int32
     return MOE_PRISM_ERR_INVALID_ARG;
   const int k_drop = S - k_in;
   Problem P(B, C, S, A, group_of);
-  const SwapLosses losses = pick_swap_losses();
+  const Loops& loops = P.loops;
   const int Bp = P.Bp;
   // A loss is its tokens' losses added up in order, one long chain of additions.  A decision rarely needs it: the sum in
   // any order (eight tokens at a time) is within a bound of it, and inside the bounds of a proposal's loss and the
   // current one nearly every decision is the same.  The others, and the final loss, are evaluated as the definition says.
-  // 256 tokens, 768 neurons in 4 groups, 3000 steps: 309 us, with the ordered sums of four proposals side by side 536.
+  // 256 tokens, 768 neurons in 4 groups, 3000 steps: 316 us, with the ordered sums of four proposals side by side 536; with
+  // the binary32 sums below in front (1 % of the proposals stay open behind them) 215.
   Aligned<double> tok(Bp), moved((size_t)2 * Bp);
   auto ordered = [&](const Swap& w) {
     double unused, sum = 0.0;
-    losses(P.L.p, Bp, S, k_drop, w, tok.p, &unused);
+    loops.losses(P.L.p, Bp, S, k_drop, w, tok.p, &unused);
     for (int b = 0; b < B; ++b) sum += tok.p[b];
     return sum;
   };
@@ -284,18 +363,26 @@ extern "C" int moe_prism_partition_anneal(int32_t B, int32_t C, int32_t S, int32
   const bool cooling = t1 <= t0;
   bool finite = true;  // (not: what a comparison makes of a NaN depends on the order of the groups)
   for (size_t b = 0; b < (size_t)S * Bp; ++b) finite = finite && std::isfinite(P.L.p[b]);
+  // Binary32 first.  With m the sum of all activations, which no swap changes and no group sum, partial or not, exceeds:
+  // the group sums are off by a rounding (together 2^-24 m), the two that change by two more each (of at most 2 m together,
+  // 4 2^-24 m), the k smallest of a token by no more than that in all, their sum by k - 1 roundings of it, and the sum of
+  // RUN vectors by RUN.  That is below (k + RUN + 5) 2^-24 m; a rounding below the normal numbers, also to zero, is off by
+  // 2^-126.  Everything stays finite where m does with room to spare.
+  double m = 0.0;
+  for (size_t b = 0; b < (size_t)S * Bp; ++b) m += std::fabs(P.L.p[b]);
+  bool screened = finite && m < 1e37 && k_drop > 0 && k_drop < S;  // (no sum or all of them: nothing to tell apart)
+  int credit = 64;  // where it leaves every other proposal open, it is given up
+  const double screen_err = (k_drop + RUN + 8.0) / 16777216.0 * m + (double)Bp * (4.0 * S + 4.0) * 1.2e-38;
+  Aligned<float> Lf((size_t)S * Bp);
+  if (screened)
+    for (size_t b = 0; b < (size_t)S * Bp; ++b) Lf.p[b] = (float)P.L.p[b];
   for (int64_t step = 0; step < steps; ++step) {
     const int i = (int)(splitmix64(seed + 3ull * (uint64_t)step) % (uint64_t)C);
     const int j = (int)(splitmix64(seed + 3ull * (uint64_t)step + 1ull) % (uint64_t)C);
     const int gi = group_of[i], gj = group_of[j];
     if (gi == gj) continue;
     const Swap w{P.column(i), P.column(j), gi, gj, moved.p, moved.p + Bp};
-    double sum = 0.0;
-    const double mass = finite ? losses(P.L.p, Bp, S, k_drop, w, nullptr, &sum) : 0.0;
-    // either order is within (B - 1) ULP of the sum of the |tok| of the real sum, to first order
-    double sum_err = (2.0 * B + 8.0) * ULP * mass;
-    const double slack = 1.001 * (sum_err + loss_err + 4.0 * ULP * (std::fabs(sum) + std::fabs(loss)));
-    const double least = sum - loss - slack, most = sum - loss + slack;  // bounds of the loss's increase
+    double sum = 0.0, sum_err = 0.0;
     double u = -1.0, temp = 0.0;
     auto draw = [&] {
       const uint64_t r2 = splitmix64(seed + 3ull * (uint64_t)step + 2ull);
@@ -305,14 +392,41 @@ extern "C" int moe_prism_partition_anneal(int32_t B, int32_t C, int32_t S, int32
       temp = steps > 1 ? t0 * std::pow(t1 / t0, (double)step / (double)(steps - 1)) : t0;
       if (cooling) temp_most = std::min(temp_most, temp * SLACK);
     };
-    bool take = finite && most <= 0.0, sure = take;
-    if (finite && least > 0.0) {
-      draw();
-      if (u > 0.0 && least > 40.0 * temp_most) continue;  // u is at least ULP > e^-37
-      heat();
-      if (u >= std::exp(-least / temp) * SLACK) continue;
-      take = sure = u * SLACK < std::exp(-most / temp);
+    // the proposal by bounds of the loss's increase
+    enum { REFUSED, TAKEN, OPEN };
+    auto decide = [&] {
+      const double slack = 1.001 * (sum_err + loss_err + 4.0 * ULP * (std::fabs(sum) + std::fabs(loss)));
+      const double least = sum - loss - slack, most = sum - loss + slack;
+      if (most <= 0.0) return TAKEN;
+      if (!(least > 0.0)) return OPEN;
+      if (u < 0.0) draw();
+      if (u > 0.0 && least > 40.0 * temp_most) return REFUSED;  // u is at least ULP > e^-37
+      if (temp == 0.0) heat();
+      if (u >= std::exp(-least / temp) * SLACK) return REFUSED;
+      return u * SLACK < std::exp(-most / temp) ? TAKEN : OPEN;
+    };
+    auto verdict = OPEN;
+    if (screened) {
+      sum = loops.screen(Lf.p, Bp, S, k_drop, w);
+      sum_err = screen_err;
+      verdict = decide();
+      credit = std::min(credit + (verdict == OPEN ? -1 : 1), 64);
+      screened = credit > 0;
+      if (verdict == OPEN && !exact) {  // the next bound is a narrow one: let the current loss not be what widens it
+        loss = ordered(none);
+        loss_err = 0.0;
+        exact = true;
+      }
     }
+    if (finite && verdict == OPEN) {
+      const double mass = loops.losses(P.L.p, Bp, S, k_drop, w, nullptr, &sum);
+      // either order is within (B - 1) ULP of the sum of the |tok| of the real sum, to first order
+      sum_err = (2.0 * B + 8.0) * ULP * mass;
+      verdict = decide();
+    }
+    if (verdict == REFUSED) continue;
+    const bool sure = verdict == TAKEN;
+    bool take = sure;
     if (!sure) {
       if (!exact) loss = ordered(none);
       exact = true;
@@ -328,12 +442,7 @@ extern "C" int moe_prism_partition_anneal(int32_t B, int32_t C, int32_t S, int32
       }
     }
     if (!take) continue;
-    double *li = P.L.p + (size_t)gi * Bp, *lj = P.L.p + (size_t)gj * Bp;
-    for (int b = 0; b < Bp; ++b) {
-      const double ai = (double)w.ci[b], aj = (double)w.cj[b];
-      li[b] = li[b] - ai + aj;
-      lj[b] = lj[b] - aj + ai;
-    }
+    loops.apply(P.L.p, screened ? Lf.p : nullptr, Bp, w);
     group_of[i] = gj;
     group_of[j] = gi;
     loss = sum;

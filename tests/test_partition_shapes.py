@@ -86,3 +86,17 @@ def test_decisions_that_the_order_of_a_sum_makes(t, columns, S):
         ref = plain_anneal(A, g0, S, S // 2, 300, t, t, seed)
         got = B.moe_prism_partition_anneal(A, g0, S, S // 2, 300, t, t, seed)
         assert np.array_equal(got[0], ref[0]) and got[1] == ref[1]
+
+
+@pytest.mark.parametrize("rows", [15, 16, 17, 256, 257])    # vectors of 16 tokens, 16 of them to a binary32 sum
+@pytest.mark.parametrize("scale", [1.0, 1e-42, 1e33, 1e36])  # subnormal; below and beyond what binary32 sums may reach
+@pytest.mark.parametrize("S,k_in", [(2, 1), (3, 1), (4, 2), (8, 5)])
+def test_decisions_behind_a_binary32_sum(rows, scale, S, k_in):
+    # hot enough to take swaps, then so cold that the binary32 bound leaves many open
+    A = np.random.default_rng(rows).standard_normal((rows, 24)) * scale
+    A = A.astype(np.float32)
+    g0 = PO.greedy(A, S)
+    for t0, t1 in ((scale, 1e-3 * scale), (1e-4 * scale, 1e-9 * scale)):
+        ref = plain_anneal(A, g0, S, k_in, 250, t0, t1, rows)
+        got = B.moe_prism_partition_anneal(A, g0, S, k_in, 250, t0, t1, rows)
+        assert np.array_equal(got[0], ref[0]) and got[1] == ref[1]
