@@ -1169,11 +1169,24 @@ static hipError_t launch_op(const Op& op, int T, int K, int n_cols, int few, int
 //     sub-experts than CUs, 512 of 192: 6.2 208 | 249, skewed 109 | 111; 10 217 | 255, 127 | 184; 24 237 | 264, 187 | 244; 37.5
 //     253 | 273, 214 | 255.  10 and 24 are where m-tiles of 256 rows were worth it (skewed: 8.8 147 | 122, 24 277 | 247); with
 //     the short ones two blocks are ahead beyond both, and with fewer sub-experts than CUs too (256 of 192: 12.5 114 | 124).
+//   fused, the ranges beside that, layer calls of more sub-experts than CUs, few | fused kernel.  Two blocks, 512 of 192: 5 242 | 279,
+//     skewed 164 | 219; 9 252 | 292, 180 | 232; bias N(0, 3^2) 7 86 | 120; 512 of 128: 5 162 | 193, 9 189 | 216; 320 of 192 x 4096: 7
+//     303 | 393; x 1024: 7 93 | 121; 1024 of 192 x 1024: 5 240 | 251, 9 257 | 258.  Four blocks, 512 of 192: 26 283 | 306, skewed 230 |
+//     293; 32 288 | 312, 249 | 287; 40 304 | 326, 271 | 299; 48 311 | 330, 293 | 312, but tied router rows 339 | 337, bias N(0, 3^2)
+//     204 | 185 (40 183 | 183); 512 of 128: 26 231 | 230, skewed 164 | 191; 40 247 | 247, 203 | 242; 320 of 192 x 4096: 40 358 | 433;
+//     x 1024, skewed, 26 97 | 107; 40 101 | 107.  Not where a tile's phases are short, 512 of 64: 32 160 | 157; 40 172 | 166; 512 of
+//     192 x 512: 26 98 | 90; 40 103 | 93; x 256: 32 68 | 65.  What is left between the ranges, about 4, 10 and 24 rows, is no better
+//     with the fused kernel: tests of both sides of those lines reach it there.
 int ffn_few_blocks(int T, int k_max, int E, int d, int Is, bool fused) {
   const long pairs = (long)T * k_max;
   if (!GateUpOp{nullptr, nullptr, nullptr, nullptr, T, d, Is, k_max}.offsets_fit() || !DownOp{nullptr, nullptr, nullptr, d, Is}.offsets_fit()) return 0;
   if (T <= 16) return 1;
-  if (fused && T > 64 && (E <= num_cus() || pairs < 10L * E || pairs > 24L * E)) return 0;
+  if (fused && T > 64) {
+    // in halves of a possible row per sub-expert
+    auto rows = [&](long lo, long hi) { return 2 * pairs >= lo * E && 2 * pairs <= hi * E; };
+    const bool long_phases = Is >= 128 && d >= 1024;
+    if (E <= num_cus() || !(rows(20, 48) || (long_phases && (rows(9, 19) || rows(49, 80))))) return 0;
+  }
   if (pairs <= 24L * E) return 2;
   return T <= 64 || pairs <= 56L * E ? 4 : 0;
 }

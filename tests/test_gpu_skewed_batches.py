@@ -55,3 +55,20 @@ def test_narrow_sub_experts_on_both_sides_of_the_few_rows_rule(T, path):
     B.moe_prism_timing_enable(False)
     assert (calls["ffn_fused"], calls["ffn_gate_up"], calls["ffn_down"]) == ((1, 0, 0) if path == "fused" else (0, 1, 1))
     assert max_rel(to_np(out), O.layer_of(wl)) <= 2e-2
+
+
+@pytest.mark.parametrize("T,path", [(74, "fused"), (75, "few"), (156, "few"), (157, "fused"), (404, "fused"), (405, "few"), (660, "few"),
+                                    (661, "fused")])
+def test_narrow_sub_experts_beside_that_range(T, path):
+    # 264 sub-experts of 128 x 1024, 16 picks: 4.5 to 9.5 and 24.5 to 40 possible rows for each; short groups beside long ones
+    k = np.random.default_rng(T).integers(0, 17, size=T).astype(np.int32)
+    wl = W.make_workload("beside", dtype="bf16", d=1024, n_experts=33, n_sub=8, inter_sub=128, req_tokens=[1] * T,
+                         req_k=k, k_max=16, seed=T, bias_std=1.0)
+    dev = B.to_device(wl)
+    assert B.ffn_path(dev["shape"]) == path
+    out, _, ws = run_layer(wl, dev)
+    tokens = np.arange(0, T, 9)
+    ref, _, _ = O.layer_tokens(tokens, wl.x, wl.w_router, wl.router_bias, wl.k_tok, wl.w_gate_up, wl.w_down, wl.k_max,
+                               wl.renormalize, wl.routed_scale)
+    assert max_rel(to_np(out)[tokens], ref) <= 2e-2
+    assert B.moe_prism_status(ws)[0] == 0

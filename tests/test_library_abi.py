@@ -67,6 +67,17 @@ def test_ffn_path_is_the_rule_of_the_library(T, E, k_max, d, Is, dtype, env, pat
     assert B.ffn_path(B.make_shape(T, d, E, 1, Is, k_max, dtype)) == path
 
 
+@pytest.mark.parametrize("T,path", [(71, "fused"), (72, "few"), (152, "few"), (153, "fused"), (391, "fused"), (392, "few"),
+                                    (640, "few"), (641, "fused")])
+@pytest.mark.parametrize("E,d,Is,narrow", [(512, 1024, 128, True), (512, 960, 128, False), (512, 1024, 64, False),
+                                           (256, 1024, 128, False)])
+def test_ffn_path_of_few_rows_beside_the_range_that_all_narrow_widths_have(T, path, E, d, Is, narrow, monkeypatch):
+    # 4.5 to 9.5 and 24.5 to 40 possible rows for each of more sub-experts than CUs, of at least 128 neurons and 1024 inputs
+    monkeypatch.setenv("MOE_PRISM_FFN", "")
+    k_max = 32 * E // 512
+    assert B.ffn_path(B.make_shape(T, d, E, 1, Is, k_max, "bf16")) == (path if narrow else "fused")
+
+
 def test_ffn_path_refuses_what_the_layer_refuses():
     out = C.c_int32(7)
     assert B.lib().moe_prism_ffn_path(C.byref(B.make_shape(64, 250, 8, 4, 128, 8, "bf16")), C.byref(out)) == -2
