@@ -7,8 +7,8 @@
 // atomic OR: commutative, so the result does not depend on timing).  The
 // chunk's count for g is the mask's popcount, and the rank of token t among the
 // chunk's pickers of g is the popcount of the mask bits below t.  A second
-// kernel turns the per-chunk counts into per-chunk bases and the groups' totals,
-// and the placing kernel derives the group offsets from the totals.
+// kernel turns the per-chunk counts into per-chunk bases and the groups' totals (few of them
+// the placing kernel itself), and the placing kernel derives the group offsets from the totals.
 // A batch of fewer than 256 tokens is dispatched by one workgroup instead (dispatch_common.h).
 // Because a token picks a sub-expert at most once, "token ascending" fixes the
 // order inside a group completely.
@@ -100,16 +100,62 @@ __global__ __launch_bounds__(SCAN_THREADS) void dispatch_scan_kernel(int32_t* __
   }
 }
 
+// Where the counts of all chunks are few, the place kernel adds them up itself, every workgroup for its own chunk: totals
+// and the counts of the chunks before it, four groups per load.  A launch less, which is a latency of 3 to 5 us, for
+// chunks x E counts read from L2 in each workgroup.  Layer calls, with the scan kernel | without: 500 tokens of 512 sub-experts
+// (4096 counts) 253.5 | 250.4 us, 2000 of 128 (4096) 318.7 | 315.8, 8192 of 128 (16 384) 702 | 699, 2000 of 512 (16 384) 378.8 |
+// 376.5; 6007 of 256 (24 064) 644.1 | 644.5, 4000 of 512 (32 256) 538.3 | 539.5.
+constexpr long SUM_COUNTS = 16384;
+static bool dispatch_sums(int T, int E) {
+  const int nch = cdiv(T, 64 * dispatch_chunk_words(E, T));
+  return T > 0 && E % 4 == 0 && E <= 4 * DISPATCH_THREADS && nch <= 256 && (long)nch * E <= SUM_COUNTS;
+}
+// tot[g], before[g] (LDS): rows of group g in all chunks and in those before c
+__device__ __forceinline__ void sum_counts(const int32_t* __restrict__ chunk_cnt, int32_t* tot, int32_t* before, int c,
+                                           int n_chunks, int E) {
+  for (int g = threadIdx.x; g < 2 * E; g += DISPATCH_THREADS) tot[g] = 0;  // before[] lies behind tot[]
+  __syncthreads();
+  const int quads = E / 4, parts = DISPATCH_THREADS / quads, part = threadIdx.x / quads, q = threadIdx.x % quads;
+  if (part < parts) {
+    const int4* rows = reinterpret_cast<const int4*>(chunk_cnt) + q;
+    int4 t = make_int4(0, 0, 0, 0), b = t;
+    constexpr int U = 8;
+    for (int i = part; i < n_chunks; i += U * parts) {
+      int4 v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = i + u * parts;
+        v[u] = rows[(size_t)min(j, n_chunks - 1) * quads];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = i + u * parts;
+        if (j < n_chunks) t.x += v[u].x, t.y += v[u].y, t.z += v[u].z, t.w += v[u].w;
+        if (j < c) b.x += v[u].x, b.y += v[u].y, b.z += v[u].z, b.w += v[u].w;
+      }
+    }
+    const int ts[4] = {t.x, t.y, t.z, t.w}, bs[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      atomicAdd(&tot[4 * q + e], ts[e]);
+      atomicAdd(&before[4 * q + e], bs[e]);
+    }
+  }
+  __syncthreads();
+}
+
 // Workgroup c places the pairs of chunk c.  Every workgroup derives the group offsets from
 // cnt[] (E additions); workgroup 0 also writes them out: off[0..E] and the pair count.
 // With tiles != nullptr the kernel also builds the grouped FFN's m-tile table (the table
 // ffn_tiles_kernel builds from off[]).
+// SUM: chunk_base and cnt are the chunks' counts, not yet added up, and where the groups' go (see dispatch_sums).
+template <bool SUM>
 __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_place_kernel(
     const int32_t* __restrict__ ids, const int32_t* __restrict__ chunk_base,
-    const int32_t* __restrict__ cnt, int32_t* __restrict__ off, int32_t* __restrict__ hdr,
+    int32_t* __restrict__ cnt, int32_t* __restrict__ off, int32_t* __restrict__ hdr,
     int32_t* __restrict__ sorted_pair, int32_t* __restrict__ slot_of_pair,
     MTile* __restrict__ tiles, int max_tiles, TileCut cut, int T, int E, int W, int k_max) {
-  extern __shared__ u64 masks[];  // E * W masks, then E + 1 offsets, then E + 1 first-tile indices
+  extern __shared__ u64 masks[];  // E * W masks, then E + 1 offsets, then E + 1 first-tile indices; SUM: then 2 E sums
   __shared__ int32_t wave_tot[4][2];
   int32_t* off_lds = reinterpret_cast<int32_t*>(masks + (size_t)E * W);
   int32_t* first_lds = off_lds + E + 1;
@@ -117,13 +163,19 @@ __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_place_kernel(
   const int ntok = max(min(64 * W, T - t0), 0);
   Picks<false> picks(ids + (size_t)t0 * k_max, ntok, k_max);
   picks.load(0);  // on their way while the offsets are derived
-  group_offsets([&](int g) { return cnt[g]; }, off_lds, first_lds, wave_tot, cut, E);
+  int32_t *tot_lds = first_lds + E + 1, *before_lds = tot_lds + E;
+  if constexpr (SUM) {
+    sum_counts(chunk_base, tot_lds, before_lds, c, gridDim.x, E);
+    if (c == 0)
+      for (int g = threadIdx.x; g < E; g += DISPATCH_THREADS) cnt[g] = tot_lds[g];
+  }
+  group_offsets([&](int g) { return SUM ? tot_lds[g] : cnt[g]; }, off_lds, first_lds, wave_tot, cut, E);
   if (c == 0) write_offsets(off_lds, first_lds, off, hdr, tiles != nullptr, max_tiles, E);
   if (tiles != nullptr)
     write_tiles(off_lds, first_lds, tiles, max_tiles, cut, E, c * DISPATCH_THREADS + threadIdx.x,
                 gridDim.x * DISPATCH_THREADS);
   build_masks(picks, masks, E, W);
-  place_pairs(picks, masks, [&](int g) { return off_lds[g] + chunk_base[(size_t)c * E + g]; }, sorted_pair,
+  place_pairs(picks, masks, [&](int g) { return off_lds[g] + (SUM ? before_lds[g] : chunk_base[(size_t)c * E + g]); }, sorted_pair,
               slot_of_pair, (size_t)t0 * k_max, off_lds[E], E, W);
 }
 
@@ -156,24 +208,27 @@ hipError_t launch_dispatch_count(const int32_t* ids, int32_t* chunk_cnt, int T, 
 }
 
 hipError_t launch_dispatch_scan(int32_t* chunk_cnt, int32_t* cnt, int T, int E, hipStream_t s) {
+  if (dispatch_sums(T, E)) return hipSuccess;
   int W = dispatch_chunk_words(E, T);
   int nch = cdiv(T, 64 * W);
   dispatch_scan_kernel<<<cdiv(E, SCAN_GROUPS), SCAN_THREADS, 0, s>>>(chunk_cnt, cnt, nch, E);
   return hipGetLastError();
 }
 
-hipError_t launch_dispatch_place(const int32_t* ids, const int32_t* chunk_base, const int32_t* cnt,
+hipError_t launch_dispatch_place(const int32_t* ids, const int32_t* chunk_base, int32_t* cnt,
                                  int32_t* off, int32_t* hdr, int32_t* sorted_pair,
                                  int32_t* slot_of_pair, MTile* tiles, int max_tiles, TileCut cut, int T,
                                  int E, int k_max, hipStream_t s) {
   int W = dispatch_chunk_words(E, T);
   int nch = cdiv(T, 64 * W);
   if (nch < 1) nch = 1;  // T == 0: one workgroup still writes the (all-zero) offsets
-  const size_t lds = (size_t)E * W * 8 + 2 * ((size_t)E + 1) * 4;
-  // up to 96 KiB + 8 bytes (E = 4096, W = 2): beyond the default limit for dynamic LDS
-  hipError_t e = raise_lds_limit<dispatch_place_kernel>(100 * 1024);
+  const bool sum = dispatch_sums(T, E);
+  const size_t lds = (size_t)E * W * 8 + 2 * ((size_t)E + 1) * 4 + (sum ? (size_t)E * 8 : 0);
+  // up to 96 KiB + 8 bytes (E = 4096, W = 2): beyond the default limit for dynamic LDS; with sums (E <= 1024, W <= 4) less
+  hipError_t e = sum ? raise_lds_limit<dispatch_place_kernel<true>>(100 * 1024) : raise_lds_limit<dispatch_place_kernel<false>>(100 * 1024);
   if (e != hipSuccess) return e;
-  dispatch_place_kernel<<<nch, DISPATCH_THREADS, lds, s>>>(ids, chunk_base, cnt, off, hdr, sorted_pair,
+  auto* kern = sum ? dispatch_place_kernel<true> : dispatch_place_kernel<false>;
+  kern<<<nch, DISPATCH_THREADS, lds, s>>>(ids, chunk_base, cnt, off, hdr, sorted_pair,
                                               slot_of_pair, tiles, max_tiles, cut, T, E, W, k_max);
   return hipGetLastError();
 }
