@@ -1165,27 +1165,32 @@ static hipError_t launch_op(const Op& op, int T, int K, int n_cols, int few, int
 //     picks, groups are as long as the batch and the ring driver is ahead where that is many tiles of 64.  Layer calls of 400 |
 //     200 tokens, four | ring driver: 128 of 704 130 | 124, 89 | 91; 256 of 352 145 | 131, 96 | 103; 256 of 256 127 | 123, 89 |
 //     106; the same 400 without a bias 254 | 267, 261 | 290, 215 | 237;
-//   fused, two blocks | fused kernel: it gives a tile a workgroup, so it is good at about as many touched groups as CUs.  More
-//     sub-experts than CUs, 512 of 192: 6.2 208 | 249, skewed 109 | 111; 10 217 | 255, 127 | 184; 24 237 | 264, 187 | 244; 37.5
-//     253 | 273, 214 | 255.  10 and 24 are where m-tiles of 256 rows were worth it (skewed: 8.8 147 | 122, 24 277 | 247); with
-//     the short ones two blocks are ahead beyond both, and with fewer sub-experts than CUs too (256 of 192: 12.5 114 | 124).
-//   fused, the ranges beside that, layer calls of more sub-experts than CUs, few | fused kernel.  Two blocks, 512 of 192: 5 242 | 279,
-//     skewed 164 | 219; 9 252 | 292, 180 | 232; bias N(0, 3^2) 7 86 | 120; 512 of 128: 5 162 | 193, 9 189 | 216; 320 of 192 x 4096: 7
-//     303 | 393; x 1024: 7 93 | 121; 1024 of 192 x 1024: 5 240 | 251, 9 257 | 258.  Four blocks, 512 of 192: 26 283 | 306, skewed 230 |
-//     293; 32 288 | 312, 249 | 287; 40 304 | 326, 271 | 299; 48 311 | 330, 293 | 312, but tied router rows 339 | 337, bias N(0, 3^2)
-//     204 | 185 (40 183 | 183); 512 of 128: 26 231 | 230, skewed 164 | 191; 40 247 | 247, 203 | 242; 320 of 192 x 4096: 40 358 | 433;
-//     x 1024, skewed, 26 97 | 107; 40 101 | 107.  Not where a tile's phases are short, 512 of 64: 32 160 | 157; 40 172 | 166; 512 of
-//     192 x 512: 26 98 | 90; 40 103 | 93; x 256: 32 68 | 65.  What is left between the ranges, about 4, 10 and 24 rows, is no better
-//     with the fused kernel: tests of both sides of those lines reach it there.
+//   where the fused kernel is what else would run: it gives a tile a workgroup, and draws tiles in runs of 32 per XCD, so it
+//     wants long groups and more of them than CUs.  Layer calls, four layers in turn so that weights come from HBM,
+//     these | fused kernel; budgets of a quarter of the most and up; skewed: a bias N(0, 1) per expert, N(0, 3^2).
+//     Up to 24 rows, any number of sub-experts, 8 of 192 x 2048: 24 35 | 552; 32: 12 39 | 493; 128: 12 86 | 169; 256: 5
+//     132 | 155, 24 151 | 165; 512: 1 130 | 155, 4 225 | 268, 10 249 | 288, 24 277 | 298, skewed 133 | 140, 168 | 229,
+//     219 | 273 and 75 | 112, 93 | 148, 134 | 164; 1024: 5 434 | 493, 24 525 | 564, but with N(0, 3^2) 219 | 193.  One pick
+//     each, groups of up to T rows: 512 at 9 335 | 370, 213 | 246, 154 | 220; 256 at 20 204 | 214, 149 | 197, 118 | 187.  Short
+//     phases too, 512 of 64 x 2048: 9 125 | 150, 24 134 | 154; 192 x 512: 4 77 | 85, 24 93 | 95; 64 x 256: 4 37 | 46, 24
+//     44 | 52.  They meet at 512 of 128 x 1024, 20 116 | 114, 24 119 | 115 (skewed 79 | 86, 64 | 85), and at 1024 of 192 x
+//     1024, 22 282 | 273.
+//     Beyond, four blocks: up to 3/4 as many sub-experts as CUs, 8 of 192 x 2048: 56 40 | 296; 128: 56 111 | 178; 192: 28
+//     144 | 193, 56 153 | 206; 192 of 128 x 1024: 56 73 | 96; of 64 x 512: 56 41 | 57; one pick each 50 230 | 288.  Not with
+//     224: 40 156 | 154, of 128 x 1024 75 | 71; 256 of 128 x 2048: 32 139 | 134.  With more than CUs, where the phases are long
+//     and no group can be: 512 of 192 x 2048, T = 400 25 278 | 300, T = 640 40 296 | 317, skewed 260 | 299, 175 | 181; x 4096:
+//     40 558 | 569, 524 | 561, 335 | 326; 320 of 192 x 2048: 40 213 | 252; 512 of 128 x 2048: 28 233 | 232, skewed 114 | 134, T
+//     = 640 40 245 | 246, tied router rows 263 | 256; x 4096: T = 448 28 386 | 422, skewed 217 | 233, T = 576 36 261 | 250.
+//     Not with longer groups, 1024 of 192 x 2048, T = 896 28 skewed 228 | 207, T = 1280 40 288 | 227 (even load 547 | 582,
+//     578 | 614); nor with short phases, 512 of 192 x 1536: 28 220 | 215; x 1024: 26 160 | 152, 40 170 | 159; 128 x 1024: 26
+//     128 | 116, 40 135 | 122; 64 x 2048, 256 of them: 28 96 | 94.
 int ffn_few_blocks(int T, int k_max, int E, int d, int Is, bool fused) {
   const long pairs = (long)T * k_max;
   if (!GateUpOp{nullptr, nullptr, nullptr, nullptr, T, d, Is, k_max}.offsets_fit() || !DownOp{nullptr, nullptr, nullptr, d, Is}.offsets_fit()) return 0;
   if (T <= 16) return 1;
-  if (fused && T > 64) {
-    // in halves of a possible row per sub-expert
-    auto rows = [&](long lo, long hi) { return 2 * pairs >= lo * E && 2 * pairs <= hi * E; };
-    const bool long_phases = Is >= 128 && d >= 1024;
-    if (E <= num_cus() || !(rows(20, 48) || (long_phases && (rows(9, 19) || rows(49, 80))))) return 0;
+  if (fused && T > 64 && pairs > 24L * E && 4 * E > 3 * num_cus()) {
+    const int longest = d < 2048 ? 0 : Is >= 192 ? 640 : Is >= 128 ? 448 : 0;  // rows of a group: at most T
+    if (E <= num_cus() || T > longest || pairs > 40L * E) return 0;
   }
   if (pairs <= 24L * E) return 2;
   return T <= 64 || pairs <= 56L * E ? 4 : 0;

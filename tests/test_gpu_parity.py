@@ -80,7 +80,8 @@ def test_small_cases_full_oracle(dtype, case):
     dict(T=1200, d=512, N=3, S=4, Is=128, k_max=5),
     dict(T=2000, d=320, N=6, S=4, Is=192, k_max=8),
     dict(T=3, d=256, N=2, S=2, Is=192, k_max=4),     # a handful of tokens: neither of the two, small tiles
-    dict(T=65, d=256, N=64, S=4, Is=192, k_max=4),   # a row or two per group: most waves multiply nothing
+    dict(T=65, d=256, N=64, S=4, Is=192, k_max=4),   # a row or two per group: tiles for few rows
+    dict(T=1600, d=256, N=64, S=4, Is=192, k_max=4, some=65),  # the same in the fused kernel: most waves multiply nothing
     dict(T=700, d=704, N=40, S=4, Is=192, k_max=20),
     dict(T=9000, d=256, N=64, S=4, Is=64, k_max=16),
 ])
@@ -89,6 +90,7 @@ def test_narrow_sub_experts_both_ffn_paths(case, path, monkeypatch):
     monkeypatch.setenv("MOE_PRISM_FFN", "split" if path == "split" else "auto")
     rng = np.random.default_rng(case["T"])
     k = rng.integers(0, case["k_max"] + 1, size=case["T"]).astype(np.int32)
+    k[case.get("some", case["T"]):] = 0  # the tokens that pick anything
     wl = W.make_workload("narrow", dtype="bf16", d=case["d"], n_experts=case["N"], n_sub=case["S"],
                          inter_sub=case["Is"], req_tokens=[1] * case["T"], req_k=k,
                          k_max=case["k_max"], seed=case["T"], bias_std=1.0, w_std=0.05)
@@ -103,7 +105,7 @@ def test_narrow_sub_experts_both_ffn_paths(case, path, monkeypatch):
     B.moe_prism_timing_enable(False)
     assert np.array_equal(to_np(out), r["out"])
     # the intended kernels ran
-    few = case["T"] <= 64 or (path == "split" and case["T"] == 65)  # a row or two per group, without the fused kernel
+    few = case["T"] <= 65 or (path == "split" and "some" in case)  # up to 24 possible rows per group, without the fused kernel 56
     assert (calls["ffn_fused"], calls["ffn_gate_up"], calls["ffn_down"]) == \
         ((1, 0, 0) if path == "fused" and not few else (0, 1, 1))
     assert B.ffn_path(r["shape"]) == ("few" if few else path)

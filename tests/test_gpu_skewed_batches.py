@@ -17,8 +17,11 @@ pytestmark = pytest.mark.gpu
     (40, 16, 4, 8, 128, 96, 33),      # the end of the top-k kernel; tiles of 32
     (64, 4, 4, 8, 64, 32, 33),        # tiles of 64
     (100, 16, 4, 8, 448, 352, 65),    # several tiles of 32 per group, two 64-token words
-    (200, 16, 4, 4, 256, 64, 97),     # the same; the fused kernel (a narrow width)
-    (200, 64, 8, 32, 256, 64, 97),    # as many rows as bring narrow sub-experts to the two-kernel path; place kernel
+    (200, 16, 4, 4, 256, 64, 97),     # the same; a narrow width
+    (200, 64, 8, 32, 256, 64, 97),    # the same; place kernel
+    (300, 32, 4, 16, 256, 128, 193),  # and tiles of 64, fewer sub-experts than CUs
+    (2000, 64, 8, 4, 256, 64, 385),   # groups of many tiles of 32
+    (900, 16, 4, 4, 256, 64, 257),    # the fused kernel
     (300, 16, 4, 4, 128, 96, 129),    # place kernel, tiles of 32
     (300, 16, 4, 8, 448, 352, 193),   # and of 64
     (300, 16, 4, 8, 256, 32, 193),
@@ -40,9 +43,9 @@ def test_layer_with_a_skewed_load(T, N, S, k_max, d, Is, longest):
     assert B.moe_prism_status(ws)[0] == 0
 
 
-@pytest.mark.parametrize("T,path", [(159, "fused"), (160, "few"), (384, "few"), (385, "fused")])
+@pytest.mark.parametrize("T,path", [(65, "few"), (159, "few"), (384, "few"), (385, "fused")])
 def test_narrow_sub_experts_on_both_sides_of_the_few_rows_rule(T, path):
-    # 512 sub-experts, 32 picks: 10 and 24 possible rows for each
+    # 512 sub-experts, 32 picks: up to 24 possible rows for each
     k = np.random.default_rng(T).integers(0, 33, size=T).astype(np.int32)
     wl = W.make_workload("border", dtype="bf16", d=256, n_experts=64, n_sub=8, inter_sub=64, req_tokens=[1] * T,
                          req_k=k, k_max=32, seed=T, bias_std=1.0, w_std=0.05)
@@ -57,12 +60,13 @@ def test_narrow_sub_experts_on_both_sides_of_the_few_rows_rule(T, path):
     assert max_rel(to_np(out), O.layer_of(wl)) <= 2e-2
 
 
-@pytest.mark.parametrize("T,path", [(74, "fused"), (75, "few"), (156, "few"), (157, "fused"), (404, "fused"), (405, "few"), (660, "few"),
-                                    (661, "fused")])
-def test_narrow_sub_experts_beside_that_range(T, path):
-    # 264 sub-experts of 128 x 1024, 16 picks: 4.5 to 9.5 and 24.5 to 40 possible rows for each; short groups beside long ones
+@pytest.mark.parametrize("T,d,Is,path", [(74, 1024, 128, "few"), (396, 1024, 128, "few"), (397, 1024, 128, "fused"),
+                                         (397, 2048, 128, "few"), (448, 2048, 128, "few"), (449, 2048, 128, "fused"),
+                                         (640, 2048, 192, "few"), (641, 2048, 192, "fused")])
+def test_narrow_sub_experts_beyond_that_range(T, d, Is, path):
+    # 264 sub-experts, 16 picks: 24 possible rows for each, or the tokens that long phases are worth; short groups beside long ones
     k = np.random.default_rng(T).integers(0, 17, size=T).astype(np.int32)
-    wl = W.make_workload("beside", dtype="bf16", d=1024, n_experts=33, n_sub=8, inter_sub=128, req_tokens=[1] * T,
+    wl = W.make_workload("beside", dtype="bf16", d=d, n_experts=33, n_sub=8, inter_sub=Is, req_tokens=[1] * T,
                          req_k=k, k_max=16, seed=T, bias_std=1.0)
     dev = B.to_device(wl)
     assert B.ffn_path(dev["shape"]) == path

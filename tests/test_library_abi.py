@@ -50,11 +50,13 @@ def test_host_side_validation():
 
 
 @pytest.mark.parametrize("T,E,k_max,d,Is,dtype,env,path", [
-    # narrow sub-experts: up to 64 tokens, and 10 to 24 possible rows for each of more sub-experts than CUs (256)
-    (64, 512, 32, 2048, 192, "bf16", "", "few"), (65, 512, 32, 2048, 192, "bf16", "", "fused"),
-    (159, 512, 32, 2048, 192, "bf16", "", "fused"), (160, 512, 32, 2048, 192, "bf16", "", "few"),
-    (384, 512, 32, 2048, 192, "bf16", "", "few"), (385, 512, 32, 2048, 192, "bf16", "", "fused"),
-    (65, 256, 32, 2048, 192, "bf16", "", "fused"), (65, 256, 32, 2048, 192, "bf16", "split", "few"),
+    # narrow sub-experts: up to 64 tokens, and up to 24 possible rows; beyond, see below
+    (64, 512, 32, 2048, 192, "bf16", "", "few"), (65, 512, 32, 2048, 192, "bf16", "", "few"),
+    (159, 512, 32, 2048, 192, "bf16", "", "few"), (160, 512, 32, 2048, 192, "bf16", "", "few"),
+    (384, 512, 32, 1024, 192, "bf16", "", "few"), (385, 512, 32, 1024, 192, "bf16", "", "fused"),
+    (64, 4, 4, 2048, 192, "bf16", "", "few"), (65, 4, 4, 2048, 192, "bf16", "", "fused"),
+    (192, 256, 32, 2048, 192, "bf16", "", "few"), (193, 256, 32, 2048, 192, "bf16", "", "fused"),
+    (65, 256, 32, 2048, 192, "bf16", "split", "few"),
     (385, 256, 32, 2048, 192, "bf16", "split", "few"), (449, 256, 32, 2048, 192, "bf16", "split", "split"),
     (385, 256, 32, 192, 192, "bf16", "", "few"),     # d below the fused kernel's
     # others: up to 56 possible rows, any number for up to 64 tokens
@@ -67,15 +69,20 @@ def test_ffn_path_is_the_rule_of_the_library(T, E, k_max, d, Is, dtype, env, pat
     assert B.ffn_path(B.make_shape(T, d, E, 1, Is, k_max, dtype)) == path
 
 
-@pytest.mark.parametrize("T,path", [(71, "fused"), (72, "few"), (152, "few"), (153, "fused"), (391, "fused"), (392, "few"),
-                                    (640, "few"), (641, "fused")])
-@pytest.mark.parametrize("E,d,Is,narrow", [(512, 1024, 128, True), (512, 960, 128, False), (512, 1024, 64, False),
-                                           (256, 1024, 128, False)])
-def test_ffn_path_of_few_rows_beside_the_range_that_all_narrow_widths_have(T, path, E, d, Is, narrow, monkeypatch):
-    # 4.5 to 9.5 and 24.5 to 40 possible rows for each of more sub-experts than CUs, of at least 128 neurons and 1024 inputs
+@pytest.mark.parametrize("E,k_max,d,Is,most", [
+    (512, 32, 2048, 192, 640), (512, 32, 4096, 192, 640),  # 40 possible rows for each, and 640 tokens
+    (288, 32, 2048, 192, 360), (1024, 32, 2048, 192, 768), (1024, 80, 2048, 192, 512),  # 40; 24, more than 640 tokens; 40
+    (512, 8, 2048, 192, 1536),                             # 24 possible rows are more than 640 tokens
+    (512, 32, 2048, 128, 448), (288, 32, 2048, 128, 360),  # 448 tokens; 40 possible rows
+    (512, 32, 1984, 192, 384), (512, 32, 2048, 64, 384), (512, 32, 256, 64, 384), (1024, 1, 1024, 128, 24576),  # 24
+    (256, 16, 2048, 64, 384), (193, 12, 1024, 192, 386),   # 24, no more sub-experts than CUs
+    (192, 12, 1024, 192, 896), (192, 12, 256, 64, 896), (8, 2, 2048, 128, 224)])  # 56, up to 3/4 as many as CUs
+def test_ffn_path_of_narrow_sub_experts_up_to_the_last_batch_of_few_rows(E, k_max, d, Is, most, monkeypatch):
+    # one range from the smallest batch on: nothing in between goes another way
     monkeypatch.setenv("MOE_PRISM_FFN", "")
-    k_max = 32 * E // 512
-    assert B.ffn_path(B.make_shape(T, d, E, 1, Is, k_max, "bf16")) == (path if narrow else "fused")
+    path = lambda T: B.ffn_path(B.make_shape(T, d, E, 1, Is, k_max, "bf16"))
+    assert all(path(T) == "few" for T in range(1, most + 1))
+    assert all(path(T) == "fused" for T in range(most + 1, most + 300))
 
 
 def test_ffn_path_refuses_what_the_layer_refuses():
