@@ -321,7 +321,7 @@ MOE_PRISM_API int moe_prism_status(const void* ws, int32_t* host_flags, int32_t*
 #define MOE_PRISM_K_LOGITS 0
 #define MOE_PRISM_K_TOPK 1
 #define MOE_PRISM_K_DISPATCH_COUNT 2
-#define MOE_PRISM_K_DISPATCH_SCAN 3 /* with few counts an empty bracket: the place kernel adds them up */
+#define MOE_PRISM_K_DISPATCH_SCAN 3 /* not launched with few counts: the place kernel adds them up */
 #define MOE_PRISM_K_DISPATCH_PLACE 4
 #define MOE_PRISM_K_FFN_TILES 5
 #define MOE_PRISM_K_FFN_GATE_UP 6

@@ -194,10 +194,11 @@ static int do_dispatch_over(const Layout& L, const int32_t* ids, int32_t* cnt, i
     return MOE_PRISM_OK;
   }
   MP_LAUNCH(MOE_PRISM_K_DISPATCH_COUNT, launch_dispatch_count(ids, chunk, T, E, k_max, st));
-  MP_LAUNCH(MOE_PRISM_K_DISPATCH_SCAN, launch_dispatch_scan(chunk, cnt, T, E, st));
+  const bool sum = dispatch_sums(T, E);
+  if (!sum) MP_LAUNCH(MOE_PRISM_K_DISPATCH_SCAN, launch_dispatch_scan(chunk, cnt, T, E, st));
   MP_LAUNCH(MOE_PRISM_K_DISPATCH_PLACE,
             launch_dispatch_place(ids, chunk, cnt, off, hdr, sorted_pair, slot_of_pair, tiles, p.max_tiles, p.cut,
-                                  T, E, k_max, st));
+                                  T, E, k_max, sum, st));
   return MOE_PRISM_OK;
 }
 

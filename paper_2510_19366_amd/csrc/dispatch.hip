@@ -101,12 +101,14 @@ __global__ __launch_bounds__(SCAN_THREADS) void dispatch_scan_kernel(int32_t* __
 }
 
 // Where the counts of all chunks are few, the place kernel adds them up itself, every workgroup for its own chunk: totals
-// and the counts of the chunks before it, four groups per load.  A launch less, which is a latency of 3 to 5 us, for
-// chunks x E counts read from L2 in each workgroup.  Layer calls, with the scan kernel | without: 500 tokens of 512 sub-experts
-// (4096 counts) 253.5 | 250.4 us, 2000 of 128 (4096) 318.7 | 315.8, 8192 of 128 (16 384) 702 | 699, 2000 of 512 (16 384) 378.8 |
-// 376.5; 6007 of 256 (24 064) 644.1 | 644.5, 4000 of 512 (32 256) 538.3 | 539.5.
+// and the counts of the chunks before it, four groups per load.  A launch and its latency less, for chunks x E counts read from
+// L2 in each workgroup.  Layer calls, with the scan kernel | without: 500 tokens of 512 sub-experts (4096 counts) 253.5 |
+// 250.4 us, 2000 of 128 (4096) 318.7 | 315.8, 8192 of 128 (16 384) 702 | 699, 2000 of 512 (16 384) 378.8 | 376.5; 6007 of 256
+// (24 064) 644.1 | 644.5, 4000 of 512 (32 256) 538.3 | 539.5.  Stage calls from a captured graph: 2048 of 4 7.3 | 6.6, 16 384 of 4
+// 7.9 | 7.6, of 64 9.2 | 7.8, 8192 of 128 10.7 | 7.9, 1024 of 1024 9.6 | 8.8; chunks of two and four words of tokens, 32 768 of 64
+// 10.9 | 9.5, 65 536 of 64 14.2 | 12.6, of 4 8.9 | 8.6.
 constexpr long SUM_COUNTS = 16384;
-static bool dispatch_sums(int T, int E) {
+bool dispatch_sums(int T, int E) {
   const int nch = cdiv(T, 64 * dispatch_chunk_words(E, T));
   return T > 0 && E % 4 == 0 && E <= 4 * DISPATCH_THREADS && nch <= 256 && (long)nch * E <= SUM_COUNTS;
 }
@@ -208,7 +210,6 @@ hipError_t launch_dispatch_count(const int32_t* ids, int32_t* chunk_cnt, int T, 
 }
 
 hipError_t launch_dispatch_scan(int32_t* chunk_cnt, int32_t* cnt, int T, int E, hipStream_t s) {
-  if (dispatch_sums(T, E)) return hipSuccess;
   int W = dispatch_chunk_words(E, T);
   int nch = cdiv(T, 64 * W);
   dispatch_scan_kernel<<<cdiv(E, SCAN_GROUPS), SCAN_THREADS, 0, s>>>(chunk_cnt, cnt, nch, E);
@@ -218,18 +219,21 @@ hipError_t launch_dispatch_scan(int32_t* chunk_cnt, int32_t* cnt, int T, int E, 
 hipError_t launch_dispatch_place(const int32_t* ids, const int32_t* chunk_base, int32_t* cnt,
                                  int32_t* off, int32_t* hdr, int32_t* sorted_pair,
                                  int32_t* slot_of_pair, MTile* tiles, int max_tiles, TileCut cut, int T,
-                                 int E, int k_max, hipStream_t s) {
+                                 int E, int k_max, bool sum, hipStream_t s) {
   int W = dispatch_chunk_words(E, T);
   int nch = cdiv(T, 64 * W);
   if (nch < 1) nch = 1;  // T == 0: one workgroup still writes the (all-zero) offsets
-  const bool sum = dispatch_sums(T, E);
-  const size_t lds = (size_t)E * W * 8 + 2 * ((size_t)E + 1) * 4 + (sum ? (size_t)E * 8 : 0);
-  // up to 96 KiB + 8 bytes (E = 4096, W = 2): beyond the default limit for dynamic LDS; with sums (E <= 1024, W <= 4) less
-  hipError_t e = sum ? raise_lds_limit<dispatch_place_kernel<true>>(100 * 1024) : raise_lds_limit<dispatch_place_kernel<false>>(100 * 1024);
+  const size_t lds = (size_t)E * W * 8 + 2 * ((size_t)E + 1) * 4;
+  if (sum) {  // E <= 1024 where W is 1, E <= 64 where it is more: 24 KiB and 8 bytes at most
+    dispatch_place_kernel<true><<<nch, DISPATCH_THREADS, lds + (size_t)E * 8, s>>>(
+        ids, chunk_base, cnt, off, hdr, sorted_pair, slot_of_pair, tiles, max_tiles, cut, T, E, W, k_max);
+    return hipGetLastError();
+  }
+  // up to 96 KiB + 8 bytes (E = 4096, W = 2): beyond the default limit for dynamic LDS
+  hipError_t e = raise_lds_limit<dispatch_place_kernel<false>>(100 * 1024);
   if (e != hipSuccess) return e;
-  auto* kern = sum ? dispatch_place_kernel<true> : dispatch_place_kernel<false>;
-  kern<<<nch, DISPATCH_THREADS, lds, s>>>(ids, chunk_base, cnt, off, hdr, sorted_pair,
-                                              slot_of_pair, tiles, max_tiles, cut, T, E, W, k_max);
+  dispatch_place_kernel<false><<<nch, DISPATCH_THREADS, lds, s>>>(
+      ids, chunk_base, cnt, off, hdr, sorted_pair, slot_of_pair, tiles, max_tiles, cut, T, E, W, k_max);
   return hipGetLastError();
 }
 

@@ -58,7 +58,8 @@ hipError_t launch_proxy_select(int dtype, const void* act, int act_ld, const int
                                const float* w0, const int32_t* slot0, const int32_t* k_tok,
                                const int32_t* kappa, int32_t* ids, float* w, int32_t* hdr, int T,
                                int S, int r, int m, int k_max, hipStream_t s);
-// (few counts: nothing is launched, the place kernel takes them as they are)
+// few counts: no scan, the place kernel adds them up (its `sum`)
+bool dispatch_sums(int T, int E);
 hipError_t launch_dispatch_scan(int32_t* chunk_cnt, int32_t* cnt, int T, int E, hipStream_t s);
 bool dispatch_is_small(int T, int E, int k_max);  // the whole stage in one workgroup (launch_dispatch_small)
 hipError_t launch_dispatch_small(const int32_t* ids, int32_t* cnt, int32_t* off, int32_t* hdr,
@@ -69,7 +70,7 @@ hipError_t launch_dispatch_small(const int32_t* ids, int32_t* cnt, int32_t* off,
 hipError_t launch_dispatch_place(const int32_t* ids, const int32_t* chunk_base, int32_t* cnt,
                                  int32_t* off, int32_t* hdr, int32_t* sorted_pair,
                                  int32_t* slot_of_pair, MTile* tiles, int max_tiles, TileCut cut, int T,
-                                 int E, int k_max, hipStream_t s);
+                                 int E, int k_max, bool sum, hipStream_t s);
 
 // grouped FFN
 hipError_t launch_ffn_tiles(const int32_t* off, MTile* tiles, int32_t* hdr, int E, int max_tiles,

@@ -279,22 +279,29 @@ def test_dispatch_alone_on_synthetic_picks(T, E, k_max):
     assert B.moe_prism_status(ws)[1] == int(ro[-1])   # the status word belongs to the route stage
 
 
-@pytest.mark.parametrize("T,E", [
-    (256, 4), (300, 4), (16384, 4), (16385, 4),    # one load of four counts holds all groups; 256 and 257 chunks
-    (8191, 128), (8192, 128), (8193, 128),         # 128 chunks of 128 counts, the most that the place kernel adds up itself
-    (1024, 1024), (1025, 1024), (1000, 1028),      # one load per thread and chunk; more groups than that
-    (700, 516), (1500, 500), (1500, 502)])         # threads without a load; counts that are no whole loads
-def test_dispatch_on_both_sides_of_the_rule_that_sums_counts_while_placing(T, E):
+@pytest.mark.parametrize("T,E,scan", [
+    (256, 4, 0), (300, 4, 0), (16384, 4, 0), (16385, 4, 1),    # one load of four counts holds all groups; 256 and 257 chunks
+    (8191, 128, 0), (8192, 128, 0), (8193, 128, 1),            # 128 chunks of 128 counts, the most that the place kernel adds up itself
+    (1024, 1024, 0), (1025, 1024, 1), (1000, 1028, 1),         # one load per thread and chunk; more groups than that
+    (700, 516, 0), (1500, 500, 0), (1500, 502, 1),             # threads without a load; counts that are no whole loads
+    (32768, 64, 0), (32768, 4, 0), (32769, 64, 1),             # 256 chunks of two words of tokens; one more
+    (49152, 64, 0), (65536, 64, 0), (65536, 4, 0), (65536, 68, 1)])  # of three and four
+def test_dispatch_on_both_sides_of_the_rule_that_sums_counts_while_placing(T, E, scan):
     rng = np.random.default_rng(T + E)
     k_max = 3
     ids = ((rng.integers(0, E, T)[:, None] + np.arange(k_max) * max(E // 4, 1)) % E).astype(np.int32)  # distinct per token
     ids[rng.random(T) < 0.3, 1:] = -1
     shape = B.make_shape(T, 64, E, 1, 32, k_max, "bf16")
     ws = B.alloc_workspace(shape)
+    B.moe_prism_timing_enable(True)
+    B.moe_prism_timing_read()
     for _ in range(2):     # a second call on what the first one left in the workspace
         tables = B.moe_prism_dispatch(shape, torch.from_numpy(ids).cuda(), ws)
         for got, ref in zip(tables, O.dispatch(ids, E)):
             assert np.array_equal(to_np(got), ref)
+    calls = {name: v[1] for name, v in B.moe_prism_timing_read().items()}
+    B.moe_prism_timing_enable(False)
+    assert (calls["dispatch_count"], calls["dispatch_scan"], calls["dispatch_place"]) == (2, 2 * scan, 2)
 
 
 def test_everything_routed_to_one_sub_expert():
