@@ -173,15 +173,16 @@ __device__ __forceinline__ void place_pairs(Picks& picks, const u64* masks, Base
 }
 
 // ---------------------------------------------------------------- a small batch in one workgroup
-// Up to 64 tokens, or more with few pairs, whose masks and offsets fit the default 64 KiB of LDS: the three launches
+// Up to 64 tokens, or more with few pairs, whose masks and offsets fit the default 64 KiB of LDS: the two or three launches
 // of the general path cost more than their work there.  What bounds it is a chain of latencies (picks, masks, scan,
 // offsets, slots); one workgroup places the pairs of all tokens by itself, and from a second 64-token word of mask on
-// the general path has a workgroup for each.  Calls of d = 64, Is = 32, 512 sub-experts from a captured graph, one
-// workgroup | three launches: 40 tokens of 8 picks 22.8 | 28.1 us, 64 of 64 42.7 | 51.8; 100 of 8 29.2 | 33.3, of 24 36.5 |
-// 38.7, of 64 52.3 | 55.2; 160 of 4 28.2 | 31.1, of 8 30.8 | 34.2, of 32 45.4 | 43.8; 255 of 8 33.4 | 33.8, of 32 54.2 |
-// 44.0 (32 to 1024 sub-experts alike).  Budgets below k_max leave fewer pairs than T k_max: 79 tokens of up to 20, half
-// of them on average, 32.7 | 37.1; 155 of up to 1, 22.1 | 25.8.  (With a loop over the picks that waits for each, a
-// bisection per m-tile and scans by shuffles, one workgroup took 26.2 us for 40 tokens of 8, 50.8 for 64 of 64.)
+// the general path has a workgroup for each: what counts is the pairs beyond those of 64 tokens.  Layer calls of d = 64,
+// Is = 32, 512 sub-experts from a captured graph, one workgroup | count and place kernels; stage calls alone, the same: 40 tokens
+// of 8 picks 21.1 | 25.4 us, 3.4 | 6.3; 64 of 64 33.9 | 41.0, 9.8 | 14.5; 65 of 200 86.3 | 96.5, 27.2 | 35.9; 80 of 160 74.2 | 77.2, 27.3 |
+// 29.4; 100 of 24 28.1 | 30.3, 7.7 | 8.9; of 71 45.5 | 46.0, 16.8 | 16.4; 110 of 56 39.2 | 38.7, 15.5 | 13.7; 128 of 16 26.4 | 29.2, 6.5 | 7.9; of
+// 40 35.8, 12.9; of 41 36.9 | 36.3, 13.3 | 12.2; of 50 39.7 | 38.2, 15.8 | 13.4; 160 of 8 24.4 | 27.2, 5.4 | 6.9; 192 of 10 25.2 | 27.5, 6.8 | 7.4; 200
+// of 11 27.7 | 28.0, 8.0 | 7.4; 255 of 4 22.5 | 24.4, 5.4 | 6.4; of 8 26.5 | 27.4, 7.4 | 7.0 (128 sub-experts alike; 1024: 128 of 41 41.4 | 42.0,
+// 255 of 8 32.4 | 32.2, 9.0 | 7.8).
 struct SmallDispatch {
   int32_t *cnt, *off, *sorted_pair, *slot_of_pair;
   MTile* tiles;  // nullptr: no m-tile table
@@ -190,7 +191,7 @@ struct SmallDispatch {
 };
 __host__ __device__ inline size_t small_dispatch_lds(int T, int E) { return (size_t)E * ((T + 63) / 64) * 8 + (size_t)E * 4; }
 inline bool small_dispatch(int T, int E, int k_max) {
-  return T > 0 && (T <= 64 || (T < 256 && T * k_max <= (T <= 128 ? 6400 : 2048))) && small_dispatch_lds(T, E) <= 60 * 1024;
+  return T > 0 && (T <= 64 || (T <= 128 ? (T - 64) * k_max <= 2560 : T < 256 && T * k_max <= 2048)) && small_dispatch_lds(T, E) <= 60 * 1024;
 }
 
 // Offsets, counts and m-tiles of all groups from the masks, by one workgroup of `threads` threads; returns P.  A group
@@ -204,8 +205,8 @@ __device__ __forceinline__ int small_groups(const SmallDispatch& a, int32_t* __r
     for (int w = 0; w < W; ++w) n += __popcll(masks[g * W + w]);
     return n;
   };
-  // rows (at most 64 x 1024) in the low 18 bits of a word, m-tiles (at most 4096 and one per 16 rows of 16 x 1024, or per 32 of
-  // 64 x 1024) above them: one scan for both
+  // rows (at most 66 x 1024) in the low 18 bits of a word, m-tiles (at most 4096 and one per 16 rows of 16 x 1024, or per 32 of
+  // 66 x 1024) above them: one scan for both
   constexpr int TILE = 1 << 18;
   const int per = (E + threads - 1) / threads, lo = min(tid * per, E), hi = min(lo + per, E);
   int mine = 0;

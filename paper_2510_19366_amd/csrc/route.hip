@@ -413,9 +413,11 @@ hipError_t launch_topk(const float* logits, const int32_t* k_tok, int32_t* ids, 
   const size_t sh_wave = (size_t)4 * topk_pad(k_max) * sizeof(float);
   size_t sh = TOPK_WAVES * sh_wave;
   const int elems = cdiv(E, 64);
-  // One workgroup saves the fence, the count and the reading back of the picks; 16 waves have registers for 16
-  // logits per lane.  Layer calls of 1 | 4 | 8 | 16 tokens, 128 x 4 sub-experts: 42.1 | 50.6 | 57.2 | 118.3 us, with the last
-  // of several workgroups 43.4 | 52.4 | 58.0 | 119.0; 16 tokens in fp32, 8 x 4 of 128: 22.3, 23.4.
+  // One workgroup saves the count and the reading back of the picks; 16 waves have registers for 16 logits per lane.
+  // Layer calls of 1 | 4 | 8 | 12 | 16 tokens from a captured graph, 128 x 4 sub-experts: 38.1 | 52.4 | 65.2 | 79.4 | 85.5 us, with
+  // the last of several workgroups 39.2 | 53.6 | 65.8 | 79.3 | 85.3; fp32, 8 x 4 of 128: 18.0 | 19.7 | 20.2 | 20.6 | 22.2, 19.0 |
+  // 20.7 | 21.4 | 21.3 | 21.9; d = 64, 256 x 4, 8 picks 18.6 | 19.6 | 20.7 | 21.5 | 23.0, 20.1 | 21.3 | 22.0 | 21.8 | 22.3.  From 12 to
+  // 16 tokens they are even.
   const int solo_waves = T < TOPK_WAVES ? TOPK_WAVES : T;
   const size_t sh_solo = solo_waves * sh_wave + (size_t)E * 12 + SOLO_WAVES * sizeof(int32_t);
   const bool solo = small != nullptr && T <= SOLO_WAVES && elems <= 16 && sh_solo <= 60 * 1024;

@@ -259,7 +259,7 @@ def test_largest_supported_router_and_budget():
 
 @pytest.mark.parametrize("T,E,k_max", [(33000, 4096, 3),   # two 64-token words per chunk: the largest LDS footprint
                                        (70000, 1000, 5),   # four words per chunk, E not a multiple of 4
-                                       (64, 1024, 1024),   # the most pairs of one workgroup
+                                       (64, 1024, 1024), (66, 1024, 1024),   # the most pairs of one workgroup
                                        (1, 7, 7), (257, 33, 2)])
 def test_dispatch_alone_on_synthetic_picks(T, E, k_max):
     # the dispatch stage by itself on picks that no router produced: distinct ids per token,

@@ -20,7 +20,8 @@ pytestmark = pytest.mark.gpu
                                        (128, 64, 50), (128, 64, 51), (129, 64, 15), (129, 64, 16), (255, 64, 8),
                                        # one workgroup with all tokens: waves, elements per lane, LDS; just beyond
                                        (3, 64, 64), (5, 512, 32), (16, 66, 1), (16, 1024, 40), (17, 64, 8),
-                                       (16, 1026, 8), (15, 1024, 200), (2, 1024, 512)])
+                                       (16, 1026, 8), (15, 1024, 200), (2, 1024, 512),
+                                       (66, 1040, 1024), (128, 64, 40), (128, 64, 41)])
 def test_small_batches_match_the_oracle(T, E, k_max):
     k = np.random.default_rng(T).integers(0, k_max + 1, size=T).astype(np.int32)
     wl = W.make_workload("small", dtype="bf16", d=64, n_experts=E // 2, n_sub=2, inter_sub=32,
@@ -37,6 +38,26 @@ def test_small_batches_match_the_oracle(T, E, k_max):
     for key, name in (("cnt", "group_count"), ("off", "group_offset"), ("sorted_pair", "sorted_pair"),
                       ("slot_of_pair", "slot_of_pair")):
         assert np.array_equal(to_np(im[name]), ref[key]), name
+
+
+@pytest.mark.parametrize("T,E,k_max,one", [
+    (64, 64, 64, 1), (65, 1024, 1024, 1), (66, 1024, 1024, 1), (67, 1024, 853, 1), (67, 1024, 854, 0),
+    (100, 128, 71, 1), (100, 128, 72, 0), (128, 64, 40, 1), (128, 64, 41, 0),  # 2560 pairs beyond those of 64 tokens
+    (129, 64, 15, 1), (129, 64, 16, 0), (255, 64, 8, 1), (255, 64, 9, 0), (256, 64, 1, 0)])  # 2048 pairs; 255 tokens
+def test_batches_that_one_workgroup_dispatches(T, E, k_max, one):
+    rng = np.random.default_rng(T + k_max)
+    ids = np.argsort(rng.random((T, E)), axis=1)[:, :k_max].astype(np.int32)
+    ids[np.arange(k_max) >= rng.integers(0, k_max + 1, T)[:, None]] = -1
+    shape = B.make_shape(T, 64, E, 1, 32, k_max, "bf16")
+    ws = B.alloc_workspace(shape)
+    B.moe_prism_timing_enable(True)
+    B.moe_prism_timing_read()
+    tables = B.moe_prism_dispatch(shape, torch.from_numpy(ids).cuda(), ws)
+    calls = {name: v[1] for name, v in B.moe_prism_timing_read().items()}
+    B.moe_prism_timing_enable(False)
+    assert (calls["dispatch_count"], calls["dispatch_place"]) == (1 - one, 1)
+    for got, ref in zip(tables, O.dispatch(ids, E)):
+        assert np.array_equal(to_np(got), ref)
 
 
 @pytest.mark.parametrize("values", [2, 9])
