@@ -394,7 +394,7 @@ __global__ __launch_bounds__(64 * (MODE == TOPK_SOLO ? SOLO_WAVES : TOPK_WAVES))
     int32_t* wave_tot = is_last + 1;
     // The picks were stored at agent scope, i.e. through this XCD's L2, so once they are acknowledged every CU can read
     // them: no release fence, which would have each workgroup write back all of its L2 (64 fp32 tokens of 8 x 4
-    // sub-experts, layer calls: 24.5 -> 23.6 us; 37 of 128 x 4: 107.4 -> 107.0)
+    // sub-experts, layer calls: 24.5 -> 23.6 us)
     wait_vmem<0>();
     __syncthreads();
     if (threadIdx.x == 0) *is_last = atomicAdd(&hdr[HDR_TOPK_DONE], 1) == (int)gridDim.x - 1;
