@@ -38,7 +38,6 @@ constexpr int BM = FFN_BM;
 constexpr int NSW = 4;    // weight ring slots
 constexpr int X_WAVE = 32 * 128;       // bytes of one wave's x slot: 32 rows x 64 K-elements
 constexpr int EPI_WAVE = 16 * 128;     // bytes of a wave's output staging: 16 rows x 64 columns
-constexpr int RUN = 32;   // consecutive tiles an XCD takes per turn
 constexpr int PD = 4;     // fragment reads in flight ahead of the MFMAs
 
 template <int IS>
@@ -53,7 +52,7 @@ struct Cfg {
   static constexpr int OFF_X = NSW * W_SLOT;
   static constexpr int OFF_PAIR = OFF_X + 8 * X_WAVE;
   static constexpr int OFF_EPI = OFF_PAIR + 2 * BM * 4;   // output transposition
-  static constexpr int OFF_DYN = OFF_EPI + 8 * EPI_WAVE;  // two words: tile numbers drawn by wave 0
+  static constexpr int OFF_DYN = OFF_EPI + 8 * EPI_WAVE;  // the tile number drawn by wave 0
   static constexpr int LDS_BYTES = OFF_DYN + 16;
   // steps of a stage (one MFMA each) behind which things happen
   static constexpr int STEPS = 2 * NBLK;
@@ -174,26 +173,39 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
   const int S1 = d / 32, S2 = d / 64, ST = S1 + S2;
 
-  // Tiles are drawn at run time, one tile ahead of the one being multiplied, in table order
-  // (group-major: ragged tails, which only stream weights, stay interleaved with full tiles;
-  // drawing the heavy tiles first measured slower).  The workgroups of an XCD (workgroup b runs
-  // on XCD b % 8) share a cursor: the i-th tile an XCD draws is (i / RUN) * 8 RUN + xcd * RUN +
-  // i % RUN, so runs of RUN consecutive tiles, which mostly belong to one group, meet in one L2.
-  const int n_tiles = hdr[HDR_MTILES];
-  const int xcd = blockIdx.x % N_XCD;
+  // Tiles are drawn at run time, in the order of TileLists (drawing the heavy tiles first measured slower): the first one
+  // of a workgroup is given, the next one is drawn near the end of the one before, just ahead of the first copies for it,
+  // from the list of its XCD (workgroup b runs on XCD b % 8) and, once that is empty, from the longest of the others.
+  // A list is always drained by its own workgroups, whatever the others take of it.  What this is about is the end of the
+  // kernel: a workgroup has a few tiles of 70 to 150 us.  With two tiles drawn ahead, lists that did not help each other and
+  // runs of 32 to the last tile, between HIP events, 128 x 4 sub-experts of 192 x 2048, budgets 8 to 32, router bias N(0, 1)
+  // per expert: 1200 | 3000 | 8000 | 16384 tokens 285 | 327 | 513 | 911 us, now 270 | 289 | 491 | 868.
+  const int xcd = blockIdx.x % N_XCD, slot = blockIdx.x / N_XCD;
   int32_t* dyn_lds = reinterpret_cast<int32_t*>(smem + C::OFF_DYN);
-  auto draw = [&]() {  // one lane of the workgroup
-    const int i = atomicAdd(&hdr[HDR_DYN_FUSED + xcd], 1);
-    return (i / RUN) * (RUN * N_XCD) + xcd * RUN + (i % RUN);
+  auto draw = [&]() {  // wave 0; -1: none is left
+    const TileLists lists(uni(__hip_atomic_load(&hdr[HDR_MTILES], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
+    const int slots = gridDim.x / N_XCD;
+    int from = xcd;
+#pragma nounroll
+    for (int tries = 0; tries <= N_XCD; ++tries) {
+      int i = 0;
+      if (lane == 0) i = atomicAdd(&hdr[HDR_DYN_FUSED + from], 1);
+      i = slots + uni(i);
+      if (i < lists.count(from)) return lists.tile(from, i);
+      // lane l looks at list l
+      const int l = lane % N_XCD;
+      const int left = lists.count(l) - slots - __hip_atomic_load(&hdr[HDR_DYN_FUSED + l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      int most = left * N_XCD + l;
+      most = max(most, __builtin_amdgcn_mov_dpp(most, 0xB1, 0xf, 0xf, true));   // lane ^ 1
+      most = max(most, __builtin_amdgcn_mov_dpp(most, 0x4E, 0xf, 0xf, true));   // lane ^ 2
+      most = uni(max(most, __builtin_amdgcn_mov_dpp(most, 0x141, 0xf, 0xf, true)));  // 7 - lane
+      if (most < N_XCD) break;
+      from = most % N_XCD;
+    }
+    return -1;
   };
-  if (threadIdx.x == 0) {
-    dyn_lds[0] = draw();
-    dyn_lds[1] = draw();
-  }
-  __syncthreads();
-  const int k0 = uni(dyn_lds[0]), k1 = uni(dyn_lds[1]);
-  if (k0 >= n_tiles) return;  // uniform over the workgroup
-  __syncthreads();            // dyn_lds is written again below
+  const TileLists lists(hdr[HDR_MTILES]);
+  if (slot >= lists.count(xcd)) return;  // uniform over the workgroup
 
   const uint32_t lds0 = lds_offset(smem);
   const int32_t* pair_lds = reinterpret_cast<const int32_t*>(smem + C::OFF_PAIR);
@@ -251,11 +263,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 
   // ---- prologue: tile 0's slot list
   TileHdr cur, nxt;
-  load_hdr(k0, cur);
+  load_hdr(lists.tile(xcd, slot), cur);
   nxt = cur;
-  bool has_next = k1 < n_tiles;
-  if (has_next) load_hdr(k1, nxt);
-  int k_after = n_tiles;  // the tile after `nxt` (>= n_tiles: none)
+  bool has_next = false;  // known from stage next_at + 2 on
   int par = 0;            // which half of the slot-list buffer holds the current tile's entries
   fetch_pairs(cur, 0);
   wait_vmem<0>();
@@ -263,7 +273,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 
   // ---- producer of weights, stage q + 3.  It keeps a running global pointer and LDS address and
   // counts the stages left in its phase; it runs ahead of the multiplying code across phase and
-  // tile borders (the next tile's header `nxt` is known a whole tile ahead).  Behind the last tile's
+  // tile borders (the next tile's header `nxt` is known by then).  Behind the last tile's
   // last stage that stage is copied again (nobody reads it), so that every stage issues the same
   // number of copies.
   const int half_w = IS / 2 * d;  // elements from a gate row of the first half to that of the second
@@ -336,29 +346,41 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   wait_vmem<WPW>();  // W(0), x, W(1) have landed
   raw_barrier();
 
-  // wave 0 draws the tile after `nxt` early in a tile (its wait for the returned number drains
-  // that wave's copies once per tile); every wave picks the number up two barriers later
-  auto sched_hook = [&](int s) {
-    if (!has_next) return;
-    if (s == 0 && threadIdx.x == 0) dyn_lds[0] = draw();
-    if (s == 1) fetch_pairs(nxt, par ^ 1);
-    if (s == 2) k_after = uni(dyn_lds[0]);
+  // The next tile: wave 0 draws its number ahead of stage next_at (the wait for the returned number drains that wave's
+  // copies once per tile), every wave picks it up two barriers later, then the slot list is fetched.  The offsets of the
+  // next tile's rows are computed at stage xo_at, before the first copy of them at ST - 4, which is also where the copies of
+  // its weights start.  That is as late as possible, so that a workgroup commits itself to little, unless phase 2 has few stages.
+  const bool early = S2 < 13;
+  const int next_at = early ? 0 : ST - 13, xo_at = early ? S1 : ST - 5;
+  auto next_tile = [&](int s) {  // at the start of stage next_at + s
+    if (s == 2) {
+      const int k = uni(dyn_lds[0]);
+      has_next = k >= 0;
+      if (has_next) load_hdr(k, nxt);
+    }
+    if (s == 4 && has_next) fetch_pairs(nxt, par ^ 1);
+  };
+  auto draw_next = [&]() {
+    if (wv != 0) return;
+    const int k = draw();
+    if (lane == 0) dyn_lds[0] = k;
   };
   uint32_t c_w = 0;  // byte offset of the weight slot of stage q
   auto next_w = [&](uint32_t c) { return c + C::W_SLOT == NSW * C::W_SLOT ? 0u : c + C::W_SLOT; };
   constexpr int STEPS = C::STEPS;          // MFMAs per wave and stage, both phases
 
   for (;;) {
+    if (early) draw_next();
     if (cur.rows <= wv * 32) {
       // a wave whose 32 rows lie beyond the tile's rows only takes part in the copies and barriers
 #pragma nounroll
       for (int s = 0; s < ST; ++s) {
+        next_tile(s - next_at);
         wait_vmem<WPW>();
         raw_barrier();
 #pragma unroll
         for (int j = 0; j < WPW; ++j) copy_w(j);
-        sched_hook(s);
-        if (s == S1) x_offsets(par ^ 1);
+        if (s == xo_at) x_offsets(par ^ 1);
         if (s == ST - 4 && has_next && nxt.rows > wv * 32) {
 #pragma unroll
           for (int j = 0; j < 4; ++j) copy_x(x, j);
@@ -418,7 +440,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             if constexpr (i == C::BAR) {
               if constexpr (half == 1) wait_one_of<WPW + 4, WPW>(x_go ? WPW + 4 : WPW);
               raw_barrier();
-              if (m <= 1) sched_hook(2 * m + half);
             }
             if constexpr (i >= C::W0 && i < C::W_END) copy_w(i - C::W0);
             static_loop<0, 4>([&](auto J) {
@@ -438,6 +459,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         };
 #pragma nounroll
         for (int m = 0; m < S1 / 2; ++m) {
+          if (early) next_tile(2 * m);
           stage(m, std::integral_constant<int, 0>{});
           stage(m, std::integral_constant<int, 1>{});
           x_src += 64;
@@ -507,13 +529,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
       uint32_t vo_w2[WPW];
 #pragma unroll
       for (int j = 0; j < WPW; ++j) vo_w2[j] = voff_w2(j);
-      x_offsets(par ^ 1);  // of the next tile, if there is one
       bf16x8 wd[PD];
 #pragma unroll
       for (int i = 0; i < PD; ++i) wd[i] = rd_w2f(c_w, i);
 #pragma nounroll
       for (int s2 = 0; s2 < S2; ++s2) {
         const uint32_t nw = next_w(c_w);
+        if (!early) {
+          if (S1 + s2 == next_at) draw_next();
+          next_tile(S1 + s2 - next_at);
+        }
+        if (S1 + s2 == xo_at) x_offsets(par ^ 1);  // of the next tile, if there is one
         const int x_go = s2 == S2 - 4 && has_next && nxt.rows > wv * 32;
         f32x16 acc2[2];
 #pragma unroll
@@ -578,9 +604,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     }
     cur = nxt;
     par ^= 1;
-    has_next = k_after < n_tiles;
-    if (has_next) load_hdr(k_after, nxt);
-    k_after = n_tiles;
+    has_next = false;
   }
 }
 

@@ -34,6 +34,21 @@ MP_HD void shared_item(int item, int n_tiles_n, int first, int count, int& m_til
   n_tile = i / count;
 }
 
+// Whose m-tiles are whose in the fused kernel.  An XCD's workgroups draw from a list of their own: turns of RUN
+// consecutive tiles, which mostly belong to one or a few groups and so meet in one L2 with their weights.  What is left
+// after the last whole turn is dealt out evenly, in consecutive tiles too: fewer tiles than workgroups give every XCD its share.
+struct TileLists {
+  static constexpr int RUN = 32, XCDS = 8, TURN = RUN * XCDS;
+  int turns, rest;  // whole turns, and the tiles behind them
+  MP_HD explicit TileLists(int n_tiles) : turns(n_tiles / TURN), rest(n_tiles % TURN) {}
+  MP_HD int count(int xcd) const { return turns * RUN + rest / XCDS + (xcd < rest % XCDS ? 1 : 0); }
+  MP_HD int tile(int xcd, int i) const {  // i < count(xcd)
+    if (i < turns * RUN) return i / RUN * TURN + xcd * RUN + i % RUN;
+    const int extra = rest % XCDS;
+    return turns * TURN + xcd * (rest / XCDS) + (xcd < extra ? xcd : extra) + i - turns * RUN;
+  }
+};
+
 // An m-tile of `rows` slot rows is cut into row blocks of ROWS, and each of those into n_tiles_n n-tiles.
 // f(m-tile, row block, n-tile) for the share of workgroup b out of `grid` (a multiple of n_xcd; b serves XCD
 // b % n_xcd, and an XCD a contiguous part of the list, in which a sub-expert's weights meet).

@@ -93,8 +93,32 @@ static int check_shared(const std::vector<int>& groups, int log2, int n_tiles_n)
   return changes != exist ? 5 : 0;  // each weight tile is one run of items
 }
 
+// The fused kernel's lists: every tile in one of them, lists of equal length but for one, whole turns in runs, and behind
+// them consecutive tiles as well.
+static int check_lists(int n) {
+  const mp::TileLists lists(n);
+  std::vector<int> seen(n, 0);
+  for (int x = 0; x < 8; ++x) {
+    const int c = lists.count(x);
+    if (c > lists.count(0) || c < lists.count(0) - 1) return 1;
+    for (int i = 0; i < c; ++i) {
+      const int t = lists.tile(x, i);
+      if (t < 0 || t >= n || seen[t]++) return 2;
+      if (i % 32 != 0 && t != lists.tile(x, i - 1) + 1) return 3;
+    }
+  }
+  for (int c : seen)
+    if (c != 1) return 4;
+  return 0;
+}
+
 int main() {
   std::mt19937 gen(3);
+  for (int n = 0; n < 1100; ++n)
+    if (const int e = check_lists(n)) {
+      printf("lists of %d tiles: %d\n", n, e);
+      return e;
+    }
   for (int log2 : {4, 5, 6})
     for (int n_tiles_n : {1, 2, 6, 11, 56})
       for (int most : {1, 15, 16, 17, 64, 65, 300, 2000}) {

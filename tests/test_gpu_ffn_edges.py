@@ -44,6 +44,9 @@ def ffn(dtype, x, w_gu, w_dn, group):
     ("bf16", "auto", SIZES, 256, 64),     # fused, each width
     ("bf16", "auto", SIZES, 576, 128),
     ("bf16", "auto", SIZES, 320, 192),
+    ("bf16", "auto", [34, 1, 64, 25] * 65, 320, 64),  # fused, more tiles than CUs: the next tile known from the start, near the end
+    ("bf16", "auto", [34, 1, 64, 25] * 65, 832, 64),
+    ("bf16", "auto", [300, 1, 64, 25, 0] * 65, 896, 192),
     ("bf16", "split", SIZES, 512, 192),   # weight tiles with and without a second half
     ("bf16", "auto", FEW, 64, 32),        # small tiles: one K stage; half a stage
     ("bf16", "auto", FEW, 448, 352),
