@@ -163,7 +163,7 @@ struct FfnPlan {
   int max_tiles;
 };
 static FfnPlan plan_ffn(const Layout& L, int dtype, int T, int k, int E, int d, int Is, bool fused) {
-  FfnPlan p{fused, 0, {8, true}, L.max_mtiles};
+  FfnPlan p{fused, 0, {8, true, 0}, L.max_mtiles};
   static_assert(FFN_BM == 1 << 8);
   if (dtype != MOE_PRISM_BF16) {
     p.few = ffn_f32_list(T, k, E, d, Is);
@@ -173,10 +173,17 @@ static FfnPlan plan_ffn(const Layout& L, int dtype, int T, int k, int E, int d, 
   p.few = ffn_few_blocks(T, k, E, d, Is, fused);
   if (p.few != 0) {
     p.fused = false;
-    p.cut = {p.few == 4 ? 6 : p.few == 2 ? 5 : 4, false};
+    p.cut = {p.few == 4 ? 6 : p.few == 2 ? 5 : 4, false, 0};
     p.max_tiles = 2 * L.max_mtiles;
   } else if (fused) {
     p.cut.even = false;
+    // Up to 1.8 tiles per CU, where some workgroups have one and others two, the long ones come first, so that short ones are
+    // what the second ones are.  With more tiles the short ones, which mostly stream weights, are better spread over the
+    // kernel.  128 x 4 sub-experts of 192 x 2048, budgets 8 to 32, router bias N(0, 1) per expert, fused kernel between HIP
+    // events, in the order of the groups | long ones first: 650 tokens 246 | 214 us, 1024 255 | 222, 1200 265 | 234, 1400 273 | 251,
+    // 1800 293 | 294, 2100 266 | 271, 3000 288 | 302, 8000 494 | 640 (sorting costs the place kernel 0.5).  More possible rows are
+    // more tiles: no counting there.
+    if ((long)T * k <= 96L * E) p.cut.sorted = num_cus() * 9 / 5;
   }
   return p;
 }
@@ -212,7 +219,7 @@ static int do_dispatch(const moe_prism_shape* s, const Layout& L, const int32_t*
   int32_t* chunk = reinterpret_cast<int32_t*>(ws + L.chunk_cnt);
   MTile* tiles = plan != nullptr ? reinterpret_cast<MTile*>(ws + L.tiles) : nullptr;
   return do_dispatch_over(L, ids, cnt, off, sorted_pair, slot_of_pair, chunk, hdr, tiles,
-                          plan != nullptr ? *plan : FfnPlan{false, 0, {8, true}, 0}, s->T, E, s->k_max, st);
+                          plan != nullptr ? *plan : FfnPlan{false, 0, {8, true, 0}, 0}, s->T, E, s->k_max, st);
 }
 
 static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, const void* w_gu,
@@ -426,7 +433,7 @@ int moe_prism_ffn_traffic_probe(const moe_prism_shape* shape, const void* x, con
     return MOE_PRISM_ERR_UNSUPPORTED_SHAPE;
   MP_CHECK_WS(shape, L, ws, ws_bytes);
   return do_ffn(shape, L, x, w_gate_up, w_down, group_offset, sorted_pair, y,
-                static_cast<char*>(ws), (hipStream_t)stream, FfnPlan{true, 0, {8, false}, L.max_mtiles}, true);
+                static_cast<char*>(ws), (hipStream_t)stream, FfnPlan{true, 0, {8, false, 0}, L.max_mtiles}, true);
 }
 
 int moe_prism_combine(const moe_prism_shape* shape, const void* y, const int32_t* slot_of_pair,

@@ -158,7 +158,7 @@ __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_place_kernel(
     int32_t* __restrict__ sorted_pair, int32_t* __restrict__ slot_of_pair,
     MTile* __restrict__ tiles, int max_tiles, TileCut cut, int T, int E, int W, int k_max) {
   extern __shared__ u64 masks[];  // E * W masks, then E + 1 offsets, then E + 1 first-tile indices; SUM: then 2 E sums
-  __shared__ int32_t wave_tot[4][2];
+  __shared__ GroupScan wave_tot[4];
   int32_t* off_lds = reinterpret_cast<int32_t*>(masks + (size_t)E * W);
   int32_t* first_lds = off_lds + E + 1;
   const int c = blockIdx.x, t0 = c * 64 * W;
@@ -171,8 +171,9 @@ __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_place_kernel(
     if (c == 0)
       for (int g = threadIdx.x; g < E; g += DISPATCH_THREADS) cnt[g] = tot_lds[g];
   }
-  group_offsets([&](int g) { return SUM ? tot_lds[g] : cnt[g]; }, off_lds, first_lds, wave_tot, cut, E);
-  if (c == 0) write_offsets(off_lds, first_lds, off, hdr, tiles != nullptr, max_tiles, E);
+  const int n_tiles = group_offsets([&](int g) { return SUM ? tot_lds[g] : cnt[g]; }, off_lds, first_lds, wave_tot, cut, E,
+                                    c == 0 ? tiles : nullptr, max_tiles);
+  if (c == 0) write_offsets(off_lds, n_tiles, off, hdr, tiles != nullptr, max_tiles, E);
   if (tiles != nullptr)
     write_tiles(off_lds, first_lds, tiles, max_tiles, cut, E, c * DISPATCH_THREADS + threadIdx.x,
                 gridDim.x * DISPATCH_THREADS);

@@ -76,43 +76,70 @@ __device__ __forceinline__ int wave_scan(int v) {
 }
 
 // Exclusive prefixes over the groups by one workgroup of 256 threads, into LDS: off_lds[0..E]
-// of the row counts cnt(g) (off_lds[E] = P) and first_lds[0..E] of the m-tile counts
-// (first_lds[E] = number of m-tiles).  A thread sums a run of consecutive
-// groups, the 256 partial sums are scanned, the run is walked again.
+// of the row counts cnt(g) (off_lds[E] = P) and first_lds[0..E] of the m-tile counts; in a table with the long tiles first
+// (cut.sorted) without the groups' last tiles, which are written to `last` (a table of max_tiles; null: by another
+// workgroup).  Returns the number of m-tiles.  A thread sums a run of consecutive groups, the 256 partial sums are scanned, the run is walked again.
+struct GroupScan {
+  int32_t rows, tiles;
+  LastTiles last;
+};
 template <class Cnt>
-__device__ __forceinline__ void group_offsets(Cnt cnt, int32_t* off_lds, int32_t* first_lds,
-                                              int32_t (*wave_tot)[2], const TileCut& cut, int E) {
+__device__ __forceinline__ int group_offsets(Cnt cnt, int32_t* off_lds, int32_t* first_lds, GroupScan* wave_tot,
+                                             const TileCut& cut, int E, MTile* last, int max_tiles) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int per = (E + 255) / 256, lo = min(tid * per, E), hi = min(lo + per, E);
-  int mine = 0, mine_t = 0;
+  GroupScan mine{0, 0, {}};
   for (int g = lo; g < hi; ++g) {
     const int n = cnt(g);
-    mine += n;
-    mine_t += cut.tiles(n);
+    mine.rows += n;
+    mine.tiles += cut.tiles(n);
+    if (cut.sorted != 0 && n > 0) mine.last.add(LastTiles::cls(n));
   }
-  const int incl = wave_scan(mine), incl_t = wave_scan(mine_t);
-  if (lane == 63) {
-    wave_tot[wv][0] = incl;
-    wave_tot[wv][1] = incl_t;
-  }
+  GroupScan run{wave_scan(mine.rows), wave_scan(mine.tiles), {}}, total{0, 0, {}};
+  if (cut.sorted != 0)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) run.last.n[i] = (uint32_t)wave_scan((int)mine.last.n[i]);
+  if (lane == 63) wave_tot[wv] = run;
+  run.rows -= mine.rows;
+  run.tiles -= mine.tiles;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) run.last.n[i] -= mine.last.n[i];
   __syncthreads();
-  int run = incl - mine, run_t = incl_t - mine_t;
-  for (int i = 0; i < wv; ++i) {
-    run += wave_tot[i][0];
-    run_t += wave_tot[i][1];
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const GroupScan t = wave_tot[w];
+    const bool before = w < wv;
+    run.rows += before ? t.rows : 0;
+    run.tiles += before ? t.tiles : 0;
+    total.tiles += t.tiles;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      run.last.n[i] += before ? t.last.n[i] : 0u;
+      total.last.n[i] += t.last.n[i];
+    }
   }
+  const bool sorted = total.tiles <= cut.sorted;
+  int first = run.tiles - (sorted ? run.last.from(0) : 0);
   for (int g = lo; g < hi; ++g) {
-    const int n = cnt(g);
-    off_lds[g] = run;
-    first_lds[g] = run_t;
-    run += n;
-    run_t += cut.tiles(n);
+    const int n = cnt(g), nt = cut.tiles(n);
+    off_lds[g] = run.rows;
+    first_lds[g] = first;
+    first += nt;
+    if (sorted && n > 0) {
+      const int k = LastTiles::cls(n), row = (nt - 1) << cut.log2;
+      const int at = total.tiles - total.last.from(0) + total.last.from(k + 1) + run.last.from(k) - run.last.from(k + 1);
+      if (last != nullptr && at < max_tiles) put_tile(last, cut, at, g, run.rows + row, n - row, at, 1);
+      run.last.add(k);
+      --first;
+    }
+    run.rows += n;
   }
   if (tid == 255) {  // lo == hi == E for the threads past the last group
-    off_lds[E] = run;
-    first_lds[E] = run_t;
+    off_lds[E] = run.rows;
+    first_lds[E] = first;
   }
   __syncthreads();
+  return total.tiles;
 }
 
 // the header words that go with the offsets (one thread)
@@ -127,14 +154,14 @@ __device__ __forceinline__ void write_counts(int32_t* __restrict__ hdr, int P, i
   }
 }
 // off[0..E] and the header words that go with them (one workgroup)
-__device__ __forceinline__ void write_offsets(const int32_t* off_lds, const int32_t* first_lds,
+__device__ __forceinline__ void write_offsets(const int32_t* off_lds, int n_tiles,
                                               int32_t* __restrict__ off, int32_t* __restrict__ hdr,
                                               bool with_tiles, int max_tiles, int E) {
   for (int g = threadIdx.x; g <= E; g += blockDim.x) off[g] = off_lds[g];
-  if (threadIdx.x == 0) write_counts(hdr, off_lds[E], first_lds[E], with_tiles, max_tiles);
+  if (threadIdx.x == 0) write_counts(hdr, off_lds[E], n_tiles, with_tiles, max_tiles);
 }
 
-// The m-tiles of all groups (a group's tiles are contiguous).  Tile i belongs to the last group
+// The m-tiles of all groups (a group's tiles are contiguous) that first_lds counts.  Tile i belongs to the last group
 // whose first tile is <= i: every thread finds its own by bisection, so a table of hundreds of
 // one-tile groups costs one round and not one per group (512 groups and one workgroup: 43-67 -> 7 us
 // for the whole kernel).

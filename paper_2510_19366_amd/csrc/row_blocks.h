@@ -21,6 +21,7 @@ MP_HD int mtile_rows(int n, int most, bool even) {
 struct TileCut {
   int log2;
   bool even;
+  int sorted = 0;  // not even: tables of up to so many tiles have the long ones first (LastTiles)
   MP_HD int tiles(int n) const { return (n + (1 << log2) - 1) >> log2; }
   MP_HD int rows(int n) const { return mtile_rows(n, 1 << log2, even); }
 };
@@ -33,6 +34,22 @@ MP_HD void shared_item(int item, int n_tiles_n, int first, int count, int& m_til
   m_tile = first + i % count;
   n_tile = i / count;
 }
+
+// The fused kernel's table with the long tiles first: the full tiles that are not their group's last in the order of the
+// groups, then the groups' last tiles in classes of 32 rows, longest first, in the order of the groups inside a class.
+// Groups per class, in 16 bits each (at most 4096 groups), so that four words are added up for all eight.
+struct LastTiles {
+  uint32_t n[4];
+  MP_HD static int cls(int rows) { return (rows - 1) % 256 >> 5; }  // of the last tile of a group of rows > 0
+  MP_HD void add(int k) {
+    for (int i = 0; i < 4; ++i) n[i] += k >> 1 == i ? 1u << 16 * (k & 1) : 0u;
+  }
+  MP_HD int from(int k) const {  // of class k and longer ones
+    int s = 0;
+    for (int j = 0; j < 8; ++j) s += j >= k ? (int)(n[j >> 1] >> 16 * (j & 1) & 0xffffu) : 0;
+    return s;
+  }
+};
 
 // Whose m-tiles are whose in the fused kernel.  An XCD's workgroups draw from a list of their own: turns of RUN
 // consecutive tiles, which mostly belong to one or a few groups and so meet in one L2 with their weights.  What is left

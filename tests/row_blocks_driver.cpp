@@ -112,8 +112,43 @@ static int check_lists(int n) {
   return 0;
 }
 
+// The groups' last tiles, longest class first: every place behind the other tiles taken once, by classes in falling order
+// and by groups inside a class.  The sums over the groups before one are built as a scan would.
+static int check_last(const std::vector<int>& groups) {
+  mp::LastTiles total{}, run{};
+  std::vector<int> at(groups.size(), -1), by(groups.size(), -1);
+  int n = 0;
+  for (int rows : groups)
+    if (rows > 0) {
+      total.add(mp::LastTiles::cls(rows));
+      ++n;
+    }
+  if (total.from(0) != n || total.from(8) != 0) return 1;
+  for (int g = 0; g < (int)groups.size(); ++g) {
+    if (groups[g] == 0) continue;
+    const int k = mp::LastTiles::cls(groups[g]), p = total.from(k + 1) + run.from(k) - run.from(k + 1);
+    if (k != ((groups[g] + 255) % 256) / 32 || p < 0 || p >= n || by[p] >= 0) return 2;
+    by[p] = g;
+    run.add(k);
+  }
+  for (int p = 1; p < n; ++p) {
+    const int a = mp::LastTiles::cls(groups[by[p - 1]]), b = mp::LastTiles::cls(groups[by[p]]);
+    if (a < b || (a == b && by[p - 1] >= by[p])) return 3;
+  }
+  return 0;
+}
+
 int main() {
   std::mt19937 gen(3);
+  for (int most : {1, 32, 33, 256, 257, 900})
+    for (int n_groups : {1, 7, 512, 4096}) {
+      std::vector<int> groups(n_groups);
+      for (int& n : groups) n = gen() % 4 == 0 ? 0 : 1 + (int)(gen() % most);
+      if (const int e = check_last(groups)) {
+        printf("last tiles of %d groups of up to %d rows: %d\n", n_groups, most, e);
+        return e;
+      }
+    }
   for (int n = 0; n < 1100; ++n)
     if (const int e = check_lists(n)) {
       printf("lists of %d tiles: %d\n", n, e);

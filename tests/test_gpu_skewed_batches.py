@@ -21,7 +21,8 @@ pytestmark = pytest.mark.gpu
     (200, 64, 8, 32, 256, 64, 97),    # the same; place kernel
     (300, 32, 4, 16, 256, 128, 193),  # and tiles of 64, fewer sub-experts than CUs
     (2000, 64, 8, 4, 256, 64, 385),   # groups of many tiles of 32
-    (900, 16, 4, 4, 256, 64, 257),    # the fused kernel
+    (900, 16, 4, 4, 256, 64, 257),    # the fused kernel, long tiles first
+    (1100, 64, 8, 32, 256, 64, 257),  # and more of them
     (300, 16, 4, 4, 128, 96, 129),    # place kernel, tiles of 32
     (300, 16, 4, 8, 448, 352, 193),   # and of 64
     (300, 16, 4, 8, 256, 32, 193),
