@@ -244,7 +244,7 @@ static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, cons
     MP_LAUNCH(MOE_PRISM_K_FFN_FUSED,
               launch_ffn_fused_bf16((const uint16_t*)x, (const uint16_t*)w_gu, (const uint16_t*)w_dn,
                                     sorted_pair, tiles, hdr, (uint16_t*)y, s->T, s->d, s->inter_sub,
-                                    s->k_max, L.max_mtiles, st));
+                                    s->k_max, L.max_mtiles, tiles_built ? p.cut.sorted : 0, st));
     return MOE_PRISM_OK;
   }
   MP_LAUNCH(MOE_PRISM_K_FFN_GATE_UP,

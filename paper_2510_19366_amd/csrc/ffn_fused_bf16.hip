@@ -39,6 +39,11 @@ constexpr int NSW = 4;    // weight ring slots
 constexpr int X_WAVE = 32 * 128;       // bytes of one wave's x slot: 32 rows x 64 K-elements
 constexpr int EPI_WAVE = 16 * 128;     // bytes of a wave's output staging: 16 rows x 64 columns
 constexpr int PD = 4;     // fragment reads in flight ahead of the MFMAs
+// Consecutive tiles of a list's turn; 1 where the long tiles come first, so that every list has its share of them (skewed, 700 |
+// 1024 tokens in runs of 32: 212 | 232 us, so 210 | 227).  With 32, one tile for each of an XCD's workgroups, | 64, 512
+// sub-experts of 192 x 2048, fused kernel between HIP events, three layers in turn: proxy gate, 2000 tokens 318 | 306 us, 4096
+// 368 | 355, 6000 434 | 436, 12000 666 | 667; skewed, 3000 tokens 313 | 304, 8000 497 | 501, 16384 885 | 890; 12000 of 32 picks 986 | 987.
+constexpr int RUN = 64;
 
 template <int IS>
 struct Cfg {
@@ -166,7 +171,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ w_gu,
     const uint16_t* __restrict__ w_dn, const int32_t* __restrict__ sorted_pair,
     const MTile* __restrict__ tiles, int32_t* __restrict__ hdr, uint16_t* __restrict__ y, int T,
-    int d, int k_max) {
+    int d, int k_max, int sorted) {
   using C = Cfg<IS>;
   constexpr int NBLK = C::NBLK, WPW = C::WPW;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -174,24 +179,23 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   const int S1 = d / 32, S2 = d / 64, ST = S1 + S2;
 
   // Tiles are drawn at run time, in the order of TileLists (drawing the heavy tiles first measured slower): the first one
-  // of a workgroup is given, the next one is drawn near the end of the one before, just ahead of the first copies for it,
-  // from the list of its XCD (workgroup b runs on XCD b % 8) and, once that is empty, from the longest of the others.
+  // of a workgroup is given, the next one is drawn at the end of phase 1 of the one before, from the list of its XCD
+  // (workgroup b runs on XCD b % 8) and, once that is empty, from the longest of the others.
   // A list is always drained by its own workgroups, whatever the others take of it.  What this is about is the end of the
   // kernel: a workgroup has a few tiles of 70 to 150 us.  With two tiles drawn ahead, lists that did not help each other and
-  // runs of 32 to the last tile, between HIP events, 128 x 4 sub-experts of 192 x 2048, budgets 8 to 32, router bias N(0, 1)
-  // per expert: 1200 | 3000 | 8000 | 16384 tokens 285 | 327 | 513 | 911 us, now 270 | 289 | 491 | 868.
+  // runs of 32 to the last tile | so, between HIP events, three layers in turn, 128 x 4 sub-experts of 192 x 2048, budgets 8 to
+  // 32, router bias N(0, 1) per expert: 3000 tokens 336 | 317 us, 8000 533 | 513, 16384 906 | 864; 12000 of 32 picks 980 | 950,
+  // 65536 5365 | 5300.
   const int xcd = blockIdx.x % N_XCD, slot = blockIdx.x / N_XCD;
   int32_t* dyn_lds = reinterpret_cast<int32_t*>(smem + C::OFF_DYN);
-  auto draw = [&]() {  // wave 0; -1: none is left
-    const TileLists lists(uni(__hip_atomic_load(&hdr[HDR_MTILES], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
+  auto lists_of = [&](int n) { return TileLists(n, n <= sorted ? 1 : RUN); };
+  auto ask = [&](int list) { return lane == 0 ? atomicAdd(&hdr[HDR_DYN_FUSED + list], 1) : 0; };
+  auto draw = [&](int asked) {  // wave 0, what ask(xcd) returned; -1: none is left
+    const TileLists lists = lists_of(uni(__hip_atomic_load(&hdr[HDR_MTILES], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
     const int slots = gridDim.x / N_XCD;
-    int from = xcd;
+    int from = xcd, i = slots + uni(asked);
 #pragma nounroll
-    for (int tries = 0; tries <= N_XCD; ++tries) {
-      int i = 0;
-      if (lane == 0) i = atomicAdd(&hdr[HDR_DYN_FUSED + from], 1);
-      i = slots + uni(i);
-      if (i < lists.count(from)) return lists.tile(from, i);
+    for (int tries = 0; i >= lists.count(from); ++tries) {
       // lane l looks at list l
       const int l = lane % N_XCD;
       const int left = lists.count(l) - slots - __hip_atomic_load(&hdr[HDR_DYN_FUSED + l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -199,12 +203,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
       most = max(most, __builtin_amdgcn_mov_dpp(most, 0xB1, 0xf, 0xf, true));   // lane ^ 1
       most = max(most, __builtin_amdgcn_mov_dpp(most, 0x4E, 0xf, 0xf, true));   // lane ^ 2
       most = uni(max(most, __builtin_amdgcn_mov_dpp(most, 0x141, 0xf, 0xf, true)));  // 7 - lane
-      if (most < N_XCD) break;
+      if (most < N_XCD || tries == N_XCD) return -1;
       from = most % N_XCD;
+      i = slots + uni(ask(from));
     }
-    return -1;
+    return lists.tile(from, i);
   };
-  const TileLists lists(hdr[HDR_MTILES]);
+  const TileLists lists = lists_of(hdr[HDR_MTILES]);
   if (slot >= lists.count(xcd)) return;  // uniform over the workgroup
 
   const uint32_t lds0 = lds_offset(smem);
@@ -265,7 +270,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   TileHdr cur, nxt;
   load_hdr(lists.tile(xcd, slot), cur);
   nxt = cur;
-  bool has_next = false;  // known from stage next_at + 2 on
+  bool has_next = false;  // known from stage next_at + 2 of a tile on
   int par = 0;            // which half of the slot-list buffer holds the current tile's entries
   fetch_pairs(cur, 0);
   wait_vmem<0>();
@@ -346,12 +351,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   wait_vmem<WPW>();  // W(0), x, W(1) have landed
   raw_barrier();
 
-  // The next tile: wave 0 draws its number ahead of stage next_at (the wait for the returned number drains that wave's
-  // copies once per tile), every wave picks it up two barriers later, then the slot list is fetched.  The offsets of the
-  // next tile's rows are computed at stage xo_at, before the first copy of them at ST - 4, which is also where the copies of
-  // its weights start.  That is as late as possible, so that a workgroup commits itself to little, unless phase 2 has few stages.
+  // The next tile: wave 0 asks for a number ahead of SwiGLU, behind which it is there (the wait for it is also one for that
+  // wave's copies: near the end of phase 2, 65 536 tokens of 32 picks took 5370 us instead of 5300), every wave picks it up two
+  // barriers later, then the slot list is fetched.  The offsets of the next tile's rows are computed at stage xo_at, before
+  // the first copy of them at ST - 4, which is also where the copies of its weights start.  Phases 2 of few stages have
+  // no time for that: the tile is drawn at the start of the one before.
   const bool early = S2 < 13;
-  const int next_at = early ? 0 : ST - 13, xo_at = early ? S1 : ST - 5;
+  const int next_at = early ? 0 : S1, xo_at = early ? S1 : ST - 5;
   auto next_tile = [&](int s) {  // at the start of stage next_at + s
     if (s == 2) {
       const int k = uni(dyn_lds[0]);
@@ -360,9 +366,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     }
     if (s == 4 && has_next) fetch_pairs(nxt, par ^ 1);
   };
-  auto draw_next = [&]() {
+  auto draw_next = [&](int asked) {
     if (wv != 0) return;
-    const int k = draw();
+    const int k = draw(asked);
     if (lane == 0) dyn_lds[0] = k;
   };
   uint32_t c_w = 0;  // byte offset of the weight slot of stage q
@@ -370,7 +376,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   constexpr int STEPS = C::STEPS;          // MFMAs per wave and stage, both phases
 
   for (;;) {
-    if (early) draw_next();
+    if (early) draw_next(wv == 0 ? ask(xcd) : 0);
     if (cur.rows <= wv * 32) {
       // a wave whose 32 rows lie beyond the tile's rows only takes part in the copies and barriers
 #pragma nounroll
@@ -465,6 +471,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
           x_src += 64;
         }
         static_loop<0, PD>([&](auto I) { wait_lds<0>(wf[decltype(I)::value], xa[decltype(I)::value]); });  // unused, but on their way
+        const int asked = !early && wv == 0 ? ask(xcd) : 0;  // on its way during what follows
         // ---- SwiGLU: gate/up accumulators -> the bf16 K-step fragments of phase 2, block by
         // block (16 accumulator registers become 4), before anything of phase 2 is read
         __builtin_amdgcn_sched_barrier(0);
@@ -478,6 +485,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
           hfrag[b] = __builtin_bit_cast(bf16x8, pk);
           __builtin_amdgcn_sched_barrier(0);
         }
+        if (!early) draw_next(asked);
       }
       // ---- phase 2: 64 output columns per stage (2 blocks of 32), K = Is (NBLK K steps) from
       // the register-resident h fragments; step i = K step i >> 1 of block i & 1
@@ -535,10 +543,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 #pragma nounroll
       for (int s2 = 0; s2 < S2; ++s2) {
         const uint32_t nw = next_w(c_w);
-        if (!early) {
-          if (S1 + s2 == next_at) draw_next();
-          next_tile(S1 + s2 - next_at);
-        }
+        if (!early) next_tile(s2);
         if (S1 + s2 == xo_at) x_offsets(par ^ 1);  // of the next tile, if there is one
         const int x_go = s2 == S2 - 4 && has_next && nxt.rows > wv * 32;
         f32x16 acc2[2];
@@ -611,12 +616,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 template <int IS, bool MATH>
 static hipError_t launch_is(const uint16_t* x, const uint16_t* w_gu, const uint16_t* w_dn,
                             const int32_t* sorted_pair, const MTile* tiles, int32_t* hdr,
-                            uint16_t* y, int T, int d, int k_max, int max_mtiles, hipStream_t s) {
+                            uint16_t* y, int T, int d, int k_max, int max_mtiles, int sorted, hipStream_t s) {
   hipError_t e = raise_lds_limit<ffn_fused_kernel<IS, MATH>>(Cfg<IS>::LDS_BYTES);
   if (e != hipSuccess) return e;
   const int grid = persistent_grid(max_mtiles, 1);
   ffn_fused_kernel<IS, MATH><<<grid, NT, Cfg<IS>::LDS_BYTES, s>>>(x, w_gu, w_dn, sorted_pair, tiles, hdr, y,
-                                                            T, d, k_max);
+                                                            T, d, k_max, sorted);
   return hipGetLastError();
 }
 
@@ -637,12 +642,12 @@ template <bool MATH>
 static hipError_t launch_fused(const uint16_t* x, const uint16_t* w_gu, const uint16_t* w_dn,
                                const int32_t* sorted_pair, const MTile* tiles, int32_t* hdr,
                                uint16_t* y, int T, int d, int Is, int k_max, int max_mtiles,
-                               hipStream_t s) {
+                               int sorted, hipStream_t s) {
   if (max_mtiles <= 0) return hipSuccess;
   switch (Is) {
-    case 64: return fused::launch_is<64, MATH>(x, w_gu, w_dn, sorted_pair, tiles, hdr, y, T, d, k_max, max_mtiles, s);
-    case 128: return fused::launch_is<128, MATH>(x, w_gu, w_dn, sorted_pair, tiles, hdr, y, T, d, k_max, max_mtiles, s);
-    case 192: return fused::launch_is<192, MATH>(x, w_gu, w_dn, sorted_pair, tiles, hdr, y, T, d, k_max, max_mtiles, s);
+    case 64: return fused::launch_is<64, MATH>(x, w_gu, w_dn, sorted_pair, tiles, hdr, y, T, d, k_max, max_mtiles, sorted, s);
+    case 128: return fused::launch_is<128, MATH>(x, w_gu, w_dn, sorted_pair, tiles, hdr, y, T, d, k_max, max_mtiles, sorted, s);
+    case 192: return fused::launch_is<192, MATH>(x, w_gu, w_dn, sorted_pair, tiles, hdr, y, T, d, k_max, max_mtiles, sorted, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -650,8 +655,8 @@ static hipError_t launch_fused(const uint16_t* x, const uint16_t* w_gu, const ui
 hipError_t launch_ffn_fused_bf16(const uint16_t* x, const uint16_t* w_gu, const uint16_t* w_dn,
                                  const int32_t* sorted_pair, const MTile* tiles, int32_t* hdr,
                                  uint16_t* y, int T, int d, int Is, int k_max, int max_mtiles,
-                                 hipStream_t s) {
-  return launch_fused<true>(x, w_gu, w_dn, sorted_pair, tiles, hdr, y, T, d, Is, k_max, max_mtiles, s);
+                                 int sorted, hipStream_t s) {
+  return launch_fused<true>(x, w_gu, w_dn, sorted_pair, tiles, hdr, y, T, d, Is, k_max, max_mtiles, sorted, s);
 }
 
 // The kernel's memory operations alone (see mma<false>): what y holds afterwards means nothing.
@@ -659,7 +664,7 @@ hipError_t launch_ffn_fused_traffic_bf16(const uint16_t* x, const uint16_t* w_gu
                                          const uint16_t* w_dn, const int32_t* sorted_pair,
                                          const MTile* tiles, int32_t* hdr, uint16_t* y, int T,
                                          int d, int Is, int k_max, int max_mtiles, hipStream_t s) {
-  return launch_fused<false>(x, w_gu, w_dn, sorted_pair, tiles, hdr, y, T, d, Is, k_max, max_mtiles, s);
+  return launch_fused<false>(x, w_gu, w_dn, sorted_pair, tiles, hdr, y, T, d, Is, k_max, max_mtiles, 0, s);
 }
 
 }  // namespace mp

@@ -89,10 +89,11 @@ int ffn_f32_list(int T, int k_max, int E, int d, int Is);
 
 // fused gate-up -> SwiGLU -> down for narrow sub-experts (bf16); see ffn_fused_bf16.hip
 bool ffn_fused_supported(int T, int d, int Is);
+// sorted: tables of up to so many tiles have the long ones first (TileCut)
 hipError_t launch_ffn_fused_bf16(const uint16_t* x, const uint16_t* w_gu, const uint16_t* w_dn,
                                  const int32_t* sorted_pair, const MTile* tiles, int32_t* hdr,
                                  uint16_t* y, int T, int d, int Is, int k_max, int max_mtiles,
-                                 hipStream_t s);
+                                 int sorted, hipStream_t s);
 // the same kernel without the matrix products (measurement: its memory traffic alone)
 hipError_t launch_ffn_fused_traffic_bf16(const uint16_t* x, const uint16_t* w_gu,
                                          const uint16_t* w_dn, const int32_t* sorted_pair,

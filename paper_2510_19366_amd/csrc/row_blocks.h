@@ -51,18 +51,20 @@ struct LastTiles {
   }
 };
 
-// Whose m-tiles are whose in the fused kernel.  An XCD's workgroups draw from a list of their own: turns of RUN
-// consecutive tiles, which mostly belong to one or a few groups and so meet in one L2 with their weights.  What is left
-// after the last whole turn is dealt out evenly, in consecutive tiles too: fewer tiles than workgroups give every XCD its share.
+// Whose m-tiles are whose in the fused kernel.  An XCD's workgroups draw from a list of their own: turns of `run`
+// consecutive tiles, which mostly belong to one or a few groups and so meet in one L2 with their weights and, with the other
+// sub-experts of their expert, with their slot rows.  What is left after the last whole turn is dealt out evenly, in
+// consecutive tiles too: fewer tiles than workgroups give every XCD its share.
 struct TileLists {
-  static constexpr int RUN = 32, XCDS = 8, TURN = RUN * XCDS;
-  int turns, rest;  // whole turns, and the tiles behind them
-  MP_HD explicit TileLists(int n_tiles) : turns(n_tiles / TURN), rest(n_tiles % TURN) {}
-  MP_HD int count(int xcd) const { return turns * RUN + rest / XCDS + (xcd < rest % XCDS ? 1 : 0); }
+  static constexpr int XCDS = 8;
+  int run, turns, rest;  // whole turns, and the tiles behind them
+  MP_HD TileLists(int n_tiles, int run_) : run(run_), turns(n_tiles / (run_ * XCDS)), rest(n_tiles % (run_ * XCDS)) {}
+  MP_HD int count(int xcd) const { return turns * run + rest / XCDS + (xcd < rest % XCDS ? 1 : 0); }
   MP_HD int tile(int xcd, int i) const {  // i < count(xcd)
-    if (i < turns * RUN) return i / RUN * TURN + xcd * RUN + i % RUN;
+    const int turn = i / run;
+    if (turn < turns) return (turn * XCDS + xcd) * run + i % run;
     const int extra = rest % XCDS;
-    return turns * TURN + xcd * (rest / XCDS) + (xcd < extra ? xcd : extra) + i - turns * RUN;
+    return turns * run * XCDS + xcd * (rest / XCDS) + (xcd < extra ? xcd : extra) + i - turns * run;
   }
 };
 

@@ -93,10 +93,10 @@ static int check_shared(const std::vector<int>& groups, int log2, int n_tiles_n)
   return changes != exist ? 5 : 0;  // each weight tile is one run of items
 }
 
-// The fused kernel's lists: every tile in one of them, lists of equal length but for one, whole turns in runs, and behind
-// them consecutive tiles as well.
-static int check_lists(int n) {
-  const mp::TileLists lists(n);
+// The fused kernel's lists: every tile in one of them, lists of equal length but for one, turns in runs, and behind the last
+// whole turn consecutive tiles as well.
+static int check_lists(int n, int run) {
+  const mp::TileLists lists(n, run);
   std::vector<int> seen(n, 0);
   for (int x = 0; x < 8; ++x) {
     const int c = lists.count(x);
@@ -104,7 +104,7 @@ static int check_lists(int n) {
     for (int i = 0; i < c; ++i) {
       const int t = lists.tile(x, i);
       if (t < 0 || t >= n || seen[t]++) return 2;
-      if (i % 32 != 0 && t != lists.tile(x, i - 1) + 1) return 3;
+      if (i % run != 0 && t != lists.tile(x, i - 1) + 1) return 3;
     }
   }
   for (int c : seen)
@@ -150,10 +150,11 @@ int main() {
       }
     }
   for (int n = 0; n < 1100; ++n)
-    if (const int e = check_lists(n)) {
-      printf("lists of %d tiles: %d\n", n, e);
-      return e;
-    }
+    for (int run : {1, 32, 64})
+      if (const int e = check_lists(n, run)) {
+        printf("lists of %d tiles in runs of %d: %d\n", n, run, e);
+        return e;
+      }
   for (int log2 : {4, 5, 6})
     for (int n_tiles_n : {1, 2, 6, 11, 56})
       for (int most : {1, 15, 16, 17, 64, 65, 300, 2000}) {
