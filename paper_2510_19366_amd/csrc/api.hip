@@ -136,7 +136,8 @@ static int do_route(const moe_prism_shape* s, const Layout& L, const void* x, co
   const int E = s->n_experts * s->n_sub;
   int32_t* hdr = reinterpret_cast<int32_t*>(ws + L.hdr);
   MP_LAUNCH(MOE_PRISM_K_LOGITS,
-            launch_logits(s->dtype, x, w_router, bias, logits, hdr, s->T, s->d, E, st));
+            launch_logits(s->dtype, x, w_router, bias, logits, hdr, s->T, s->d, E, s->n_sub,
+                          reinterpret_cast<int32_t*>(ws + L.chunk_cnt), st));
   MP_LAUNCH(MOE_PRISM_K_TOPK, launch_topk(logits, k_tok, ids, w, hdr, s->T, E, s->k_max,
                                           s->renormalize, s->routed_scale, small, st));
   return MOE_PRISM_OK;
@@ -303,7 +304,7 @@ static int do_route_proxy(const moe_prism_shape* s, const Layout& L, const void*
   void* act = ws + L.h;
   const ProxyScratch q = proxy_scratch(s, L, ws, m);
   MP_LAUNCH(MOE_PRISM_K_LOGITS,
-            launch_logits(s->dtype, x, w_router0, bias0, logits0, hdr, s->T, s->d, N, st));
+            launch_logits(s->dtype, x, w_router0, bias0, logits0, hdr, s->T, s->d, N, 1, nullptr, st));
   const FfnPlan p = plan_ffn(L, s->dtype, s->T, m, N, s->d, rows_half, false);
   const SmallDispatch small{q.cnt0, q.off0, q.sp0, q.sl0, tiles, p.max_tiles, p.cut};
   const bool one = dispatch_is_small(s->T, N, m);

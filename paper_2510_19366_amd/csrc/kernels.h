@@ -39,8 +39,9 @@ inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 hipError_t launch_expand_k(int R, int T, const int32_t* req_k, const int32_t* req_off,
                            int32_t* k_tok, hipStream_t s);
 
+// S: sub-experts of an expert, whose rows of w may be equal; differ: scratch of E / S words (not used with S = 1)
 hipError_t launch_logits(int dtype, const void* x, const void* w, const float* bias, float* logits,
-                         int32_t* hdr, int T, int d, int E, hipStream_t s);
+                         int32_t* hdr, int T, int d, int E, int S, int32_t* differ, hipStream_t s);
 // with `small` (only where dispatch_is_small): the kernel also dispatches its picks
 struct MTile;
 struct SmallDispatch;

@@ -23,17 +23,46 @@ hipError_t launch_expand_k(int R, int T, const int32_t* req_k, const int32_t* re
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------- equal router rows
+// An expanded gate that has not been trained yet repeats an expert's router row for each of its sub-experts (Sec. 3.2.2), and
+// equal rows have equal chains.  differ[e]: the rows of expert e's sub-experts are not all the same, bit for bit.
+__global__ __launch_bounds__(256) void rows_differ_kernel(const uint32_t* __restrict__ w, int32_t* __restrict__ differ,
+                                                          int words, int S) {
+  const uint32_t* row = w + (size_t)blockIdx.x * S * words;
+  int any = 0;
+  for (int i0 = 0; i0 < words && any == 0; i0 += 4 * 256) {
+    const int i = i0 + 4 * (int)threadIdx.x;
+    uint32_t diff = 0;
+    if (i < words) {  // words % 32 == 0
+      uint32_t first[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) first[q] = row[i + q];
+      for (int s0 = 1; s0 < S; s0 += 3)
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) diff |= first[q] ^ row[(size_t)min(s0 + u, S - 1) * words + i + q];
+    }
+    any = __syncthreads_or(diff != 0);
+  }
+  if (threadIdx.x == 0) differ[blockIdx.x] = any;
+}
+
 // ---------------------------------------------------------------- logits on the matrix cores
 // Every logit is ONE chain of d binary32 fused multiply-adds over the hidden index in
 // ascending order, then the fp32 bias add: the fixed summation order is what makes the
 // routing reproducible bit for bit.  The chains run on the matrix cores, see chain_tile.h.
+struct SharedRows {
+  const int32_t* differ;  // of the experts (rows_differ_kernel); null: rows are not compared
+  int S;
+};
 template <typename InT, int WM, int WN, int MT, int NT, int NS>
 __global__ __launch_bounds__(64 * WM * WN) void logits_kernel(const InT* __restrict__ x,
                                                               const InT* __restrict__ w,
                                                               const float* __restrict__ bias,
                                                               float* __restrict__ logits,
                                                               int32_t* __restrict__ hdr, int T, int d,
-                                                              int E) {
+                                                              int E, SharedRows shared) {
   using C = ChainTile<InT, WM, WN, MT, NT, NS>;
   constexpr int CP = C::CP;
   extern __shared__ __align__(16) unsigned char lg_smem[];
@@ -42,15 +71,28 @@ __global__ __launch_bounds__(64 * WM * WN) void logits_kernel(const InT* __restr
     hdr[HDR_FLAGS] = 0;
     hdr[HDR_TOPK_DONE] = 0;
   }
-  const int m0 = blockIdx.y * C::BT, n0 = blockIdx.x * C::BE;
+  int bx = blockIdx.x, by = blockIdx.y, cols = E, step = 1;  // columns of C are every step-th row of w
+  if (shared.differ != nullptr) {
+    bool same = true;
+    for (int e = lane; e < E / shared.S; e += 64) same = same && shared.differ[e] == 0;
+    if (__all(same)) {
+      step = shared.S;
+      cols = E / step;
+      const int nx = (cols + C::BE - 1) / C::BE, id = by * gridDim.x + bx;  // the first workgroups have all there is to do
+      by = id / nx;
+      bx = id % nx;
+      if (by * C::BT >= T) return;
+    }
+  }
+  const int m0 = by * C::BT, n0 = bx * C::BE;
   const unsigned char* base[CP];
   uint32_t voff[CP];
 #pragma unroll
   for (int j = 0; j < CP; ++j) {
     const int r0 = (wv * CP + j) * 8, row = r0 + (lane >> 3);
     const bool tok = r0 < C::BT;  // the same for the whole copy
-    base[j] = reinterpret_cast<const unsigned char*>(tok ? x + (size_t)m0 * d : w + (size_t)n0 * d);
-    const int rr = tok ? min(row, T - 1 - m0) : min(row - C::BT, E - 1 - n0);
+    base[j] = reinterpret_cast<const unsigned char*>(tok ? x + (size_t)m0 * d : w + (size_t)n0 * step * d);
+    const int rr = tok ? min(row, T - 1 - m0) : min(row - C::BT, cols - 1 - n0) * step;
     voff[j] = (uint32_t)rr * (uint32_t)(d * (int)sizeof(InT)) + (uint32_t)(chain_chunk(row) * 16);
   }
   f32x4_t acc[MT][NT];
@@ -62,6 +104,28 @@ __global__ __launch_bounds__(64 * WM * WN) void logits_kernel(const InT* __restr
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
     const int col = n0 + (wn * NT + j) * 16 + r;
+    if (step > 1) {
+      for (int c = col * step; c < (col + 1) * step && col < cols; c += step % 4 == 0 ? 4 : 1) {
+        float bv[4] = {};
+        if (bias != nullptr)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) bv[u] = u == 0 || step % 4 == 0 ? bias[c + u] : 0.0f;
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int row = m0 + (wm * MT + i) * 16 + 4 * g + v;
+            const float a = acc[i][j][v];
+            float o[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) o[u] = bias != nullptr ? a + bv[u] : a;
+            if (row >= T) continue;
+            if (step % 4 == 0) __builtin_memcpy(logits + (size_t)row * E + c, o, 16);
+            else logits[(size_t)row * E + c] = o[0];
+          }
+      }
+      continue;
+    }
     const float bv = bias != nullptr && col < E ? bias[col] : 0.0f;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -80,13 +144,13 @@ __global__ void clear_flags_kernel(int32_t* hdr) { hdr[HDR_FLAGS] = 0; }
 
 template <typename InT, int MT, int NT, int NS>
 static void launch_logits_cfg(const InT* x, const InT* w, const float* bias, float* logits,
-                              int32_t* hdr, int T, int d, int E, hipStream_t s) {
+                              int32_t* hdr, int T, int d, int E, SharedRows shared, hipStream_t s) {
   using C = ChainTile<InT, 2, 2, MT, NT, NS>;
   constexpr int MOST = 65535 * C::BT;  // tokens that the second dimension of a grid holds: 2.1 or 4.2 million
   for (long t0 = 0; t0 < T; t0 += MOST) {
     const int n = (int)(T - t0 < MOST ? T - t0 : MOST);
     logits_kernel<InT, 2, 2, MT, NT, NS><<<dim3(cdiv(E, C::BE), cdiv(n, C::BT)), 64 * C::NW, C::LDS_BYTES, s>>>(
-        x + t0 * d, w, bias, logits + t0 * E, hdr, n, d, E);
+        x + t0 * d, w, bias, logits + t0 * E, hdr, n, d, E, shared);
   }
 }
 
@@ -100,27 +164,39 @@ static void launch_logits_cfg(const InT* x, const InT* w, const float* bias, flo
 // 37 us (65), 2741 x 128 20 us (35), 1 x 512 11 us (25).
 template <typename InT>
 static void launch_logits_t(const InT* x, const InT* w, const float* bias, float* logits,
-                            int32_t* hdr, int T, int d, int E, hipStream_t s) {
+                            int32_t* hdr, int T, int d, int E, SharedRows shared, hipStream_t s) {
   auto cost = [&](int bt, int be, int sub) { return (long)cdiv((long)cdiv(T, bt) * cdiv(E, be), num_cus()) * sub; };
   const long c1 = cost(32, 32, 1), c2 = cost(32, 64, 2), c4 = cost(64, 64, 4);  // c1 <= c2 <= c4
   if (c4 > 4 && c4 * 20 <= c1 * 21)
-    launch_logits_cfg<InT, 2, 2, 3>(x, w, bias, logits, hdr, T, d, E, s);
+    launch_logits_cfg<InT, 2, 2, 3>(x, w, bias, logits, hdr, T, d, E, shared, s);
   else if (c2 == c1 && c1 > 2)
-    launch_logits_cfg<InT, 1, 2, 5>(x, w, bias, logits, hdr, T, d, E, s);
+    launch_logits_cfg<InT, 1, 2, 5>(x, w, bias, logits, hdr, T, d, E, shared, s);
   else
-    launch_logits_cfg<InT, 1, 1, 6>(x, w, bias, logits, hdr, T, d, E, s);
+    launch_logits_cfg<InT, 1, 1, 6>(x, w, bias, logits, hdr, T, d, E, shared, s);
 }
 
+// Rows are compared beyond 2^34 multiply-adds.  Logits between HIP events, d = 2048, 512 sub-experts, 4 to an expert, rows not
+// compared | compared, equal rows: 9000 tokens 173 | 71 us, 20 000 363 | 121, 65 536 1059 | 289 (layer calls 8030 | 7137); but
+// rows that differ: 8192 tokens 138 | 157, 16 384 (2^34) 272 | 280: a launch and in every workgroup the latency of its result,
+// 2 % of the logits and less from there on.
+static bool compare_rows(int dtype, int T, int d, int E, int S) {
+  return S > 1 && (double)T * E * d > 17179869184.0 && (long)E * d * (dtype == 0 ? 4 : 2) < (1L << 31);
+}
 hipError_t launch_logits(int dtype, const void* x, const void* w, const float* bias, float* logits,
-                         int32_t* hdr, int T, int d, int E, hipStream_t s) {
+                         int32_t* hdr, int T, int d, int E, int S, int32_t* differ, hipStream_t s) {
   if (T == 0) {
     clear_flags_kernel<<<1, 1, 0, s>>>(hdr);
     return hipGetLastError();
   }
+  SharedRows shared{nullptr, S};
+  if (compare_rows(dtype, T, d, E, S)) {
+    rows_differ_kernel<<<E / S, 256, 0, s>>>((const uint32_t*)w, differ, dtype == 0 ? d : d / 2, S);
+    shared.differ = differ;
+  }
   if (dtype == 0)
-    launch_logits_t((const float*)x, (const float*)w, bias, logits, hdr, T, d, E, s);
+    launch_logits_t((const float*)x, (const float*)w, bias, logits, hdr, T, d, E, shared, s);
   else
-    launch_logits_t((const uint16_t*)x, (const uint16_t*)w, bias, logits, hdr, T, d, E, s);
+    launch_logits_t((const uint16_t*)x, (const uint16_t*)w, bias, logits, hdr, T, d, E, shared, s);
   return hipGetLastError();
 }
 

@@ -145,3 +145,30 @@ def test_logits_of_more_tokens_than_a_grid_has_rows():
     assert torch.equal(ids[:, 0].long(), lg.argmax(dim=1))
     for t in (0, 2097100, 4194200, T - 300):
         assert all(torch.equal(a, b[t:t + 300]) for a, b in zip(route(x[t:t + 300].contiguous()), (ids, wt, lg)))
+
+
+@pytest.mark.parametrize("dtype,N,S,change", [("bf16", 128, 4, None), ("bf16", 85, 6, None), ("bf16", 64, 8, None),
+                                              ("bf16", 256, 2, None), ("f32", 128, 4, None), ("bf16", 128, 4, (511, 2047)),
+                                              ("bf16", 128, 4, (1, 0)), ("bf16", 85, 6, (505, 1030))])
+def test_equal_router_rows_are_computed_once_with_the_same_logits(dtype, N, S, change):
+    # beyond 2^34 multiply-adds the rows of an expert's sub-experts are compared; against the same rows as experts of their
+    # own, which are not: bit for bit, with a bias per sub-expert, and where one element of one row is another
+    T, d, E, k_max = 2 ** 23 // (N * S) + 67, 2048, N * S, 9
+    g = torch.Generator(device="cuda").manual_seed(N + S)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x = torch.empty(T, d, dtype=dt, device="cuda").normal_(generator=g)
+    w = torch.empty(N, d, dtype=dt, device="cuda").normal_(0.0, 0.02, generator=g).repeat_interleave(S, dim=0).contiguous()
+    if change is not None:
+        w[change] = w[change] + 0.5
+    bias = torch.empty(E, device="cuda").normal_(generator=g)
+    k = torch.full((T,), k_max, dtype=torch.int32, device="cuda")
+    for b in (None, bias):
+        shared, alone = (B.make_shape(T, d, n, s, 32, k_max, dtype, 1, 1.0) for n, s in ((N, S), (E, 1)))
+        got = B.moe_prism_route(shared, x, w, b, k, B.alloc_workspace(shared), want_logits=True)
+        ref = B.moe_prism_route(alone, x, w, b, k, B.alloc_workspace(alone), want_logits=True)
+        for a, r in zip(got, ref):
+            assert torch.equal(a, r)
+    tokens = torch.tensor([0, 63, 64, T // 2, T - 1])
+    exact = x[tokens].double() @ w.double().T
+    bound = 2.0 * d * 2.0 ** -24 * (x[tokens].double().abs() @ w.double().abs().T)  # d roundings of the running sum
+    assert ((ref[2][tokens].double() - bias.double() - exact).abs() <= bound + 1e-6).all()
