@@ -62,12 +62,16 @@ __device__ __forceinline__ int chain_chunk(int row) { return (threadIdx.x & 7) ^
 // acc[i][j] of wave (wm, wn), sub-tile rows (wm MT + i) 16 .., columns (wn NT + j) 16 ..: accumulator v
 // of lane l is row 4 (l >> 4) + v, column l & 15.  copy(j, stage, lds) issues copy j of `stage`.
 // All LDS reads of the tile have returned when it ends, but other waves may still be reading.
-template <class C, class Copy>
+// COPIES_APART: waves NW .. 2 NW - 1 of the workgroup copy, wave NW + w what else were the copies of wave w; their acc is not
+// set.  For short rows of sub-tiles on a SIMD: an LDS read behind a copy of the same wave waits until the copy's addresses are
+// out, some 45 cycles, and the multiply with it.  The tile alone, one token, 512 rows, K = 256 | 2048 | 4096: 2.0 | 9.8 | 18.8 us,
+// 10.5 cycles per k; apart 2.1 | 8.2 | 15.3, 8.3 per k.
+template <class C, bool COPIES_APART = false, class Copy>
 __device__ __forceinline__ void chain_tile(unsigned char* smem, int ns, Copy&& copy, f32x4_t (&acc)[C::M][C::N]) {
   typedef typename C::In InT;
   constexpr int CP = C::CP, PD = C::PD, R = C::R, NF = C::NF, NS = C::STAGES, MT = C::M, NT = C::N;
-  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = wv / C::WAVES_N, wn = wv % C::WAVES_N;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wv = COPIES_APART ? w % C::NW : w, wm = wv / C::WAVES_N, wn = wv % C::WAVES_N;
   const uint32_t lds0 = lds_offset(smem);
   const uint32_t dst0 = lds0 + (uint32_t)(wv * CP) * 1024u;
   auto produce = [&](int stage, int slot) {
@@ -76,8 +80,34 @@ __device__ __forceinline__ void chain_tile(unsigned char* smem, int ns, Copy&& c
       for (int j = 0; j < CP; ++j) copy(j, stage, dst0 + (uint32_t)(slot * C::STAGE + j * 1024));
     }
   };
+  auto landed_first = [&] {  // this wave's copies of stage 0
+    if (ns >= NS - 1)
+      wait_vmem<(NS - 2) * CP>();
+    else
+      wait_vmem<0>();
+  };
+  auto landed_after = [&](int q) {  // of stage q + 1
+    if (q + NS - 2 < ns)
+      wait_vmem<(NS - 3) * CP>();
+    else
+      wait_vmem<0>();
+  };
+  if (!COPIES_APART || w >= C::NW) {
 #pragma unroll
-  for (int i = 0; i < NS - 1; ++i) produce(i, i);
+    for (int i = 0; i < NS - 1; ++i) produce(i, i);
+  }
+  if (COPIES_APART && w >= C::NW) {
+    landed_first();
+    raw_barrier();
+    int slot = NS - 1;
+    for (int q = 0; q < ns; ++q) {
+      landed_after(q);
+      raw_barrier();
+      produce(q + NS - 1, slot);
+      slot = slot == NS - 1 ? 0 : slot + 1;
+    }
+    return;
+  }
 
   // consumer: addresses of this lane's element of chunk c, in token rows and in sub-expert rows
   const int r = lane & 15, g = lane >> 4;
@@ -108,10 +138,7 @@ __device__ __forceinline__ void chain_tile(unsigned char* smem, int ns, Copy&& c
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 
-  if (ns >= NS - 1)
-    wait_vmem<(NS - 2) * CP>();  // stage 0
-  else
-    wait_vmem<0>();
+  if (!COPIES_APART) landed_first();
   raw_barrier();
   static_loop<0, PD>([&](auto s) { read(std::integral_constant<int, 0>{}, s); });
   // Stage q: its successor's copies have landed for this wave (wait) and, behind the barrier,
@@ -122,12 +149,9 @@ __device__ __forceinline__ void chain_tile(unsigned char* smem, int ns, Copy&& c
       constexpr int SLOT = decltype(slot_c)::value, NSLOT = (SLOT + 1) % NS;
       const int q = q0 + SLOT;
       if (q >= ns) return;
-      if (q + NS - 2 < ns)
-        wait_vmem<(NS - 3) * CP>();
-      else
-        wait_vmem<0>();
+      if (!COPIES_APART) landed_after(q);
       raw_barrier();
-      produce(q + NS - 1, (SLOT + NS - 1) % NS);
+      if (!COPIES_APART) produce(q + NS - 1, (SLOT + NS - 1) % NS);
       __builtin_amdgcn_sched_barrier(0);
       static_loop<0, C::STEPS>([&](auto step_c) {
         constexpr int S = decltype(step_c)::value, A = S + PD;

@@ -56,17 +56,14 @@ struct SharedRows {
   const int32_t* differ;  // of the experts (rows_differ_kernel); null: rows are not compared
   int S;
 };
-template <typename InT, int WM, int WN, int MT, int NT, int NS>
-__global__ __launch_bounds__(64 * WM * WN) void logits_kernel(const InT* __restrict__ x,
-                                                              const InT* __restrict__ w,
-                                                              const float* __restrict__ bias,
-                                                              float* __restrict__ logits,
-                                                              int32_t* __restrict__ hdr, int T, int d,
-                                                              int E, SharedRows shared) {
+template <typename InT, int WM, int WN, int MT, int NT, int NS, bool APART>
+__global__ __launch_bounds__(64 * WM * WN * (APART ? 2 : 1)) void logits_kernel(
+    const InT* __restrict__ x, const InT* __restrict__ w, const float* __restrict__ bias,
+    float* __restrict__ logits, int32_t* __restrict__ hdr, int T, int d, int E, SharedRows shared) {
   using C = ChainTile<InT, WM, WN, MT, NT, NS>;
   constexpr int CP = C::CP;
   extern __shared__ __align__(16) unsigned char lg_smem[];
-  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, w0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wv = APART ? w0 % C::NW : w0;
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
     hdr[HDR_FLAGS] = 0;
     hdr[HDR_TOPK_DONE] = 0;
@@ -96,9 +93,10 @@ __global__ __launch_bounds__(64 * WM * WN) void logits_kernel(const InT* __restr
     voff[j] = (uint32_t)rr * (uint32_t)(d * (int)sizeof(InT)) + (uint32_t)(chain_chunk(row) * 16);
   }
   f32x4_t acc[MT][NT];
-  chain_tile<C>(lg_smem, d / C::KB, [&](int j, int stage, uint32_t lds) {  // d % 64 == 0
+  chain_tile<C, APART>(lg_smem, d / C::KB, [&](int j, int stage, uint32_t lds) {  // d % 64 == 0
     copy_to_lds16(base[j] + (size_t)stage * 128, voff[j], lds);
   }, acc);
+  if (APART && w0 >= C::NW) return;
 
   const int wm = wv / WN, wn = wv % WN, r = lane & 15, g = lane >> 4;
 #pragma unroll
@@ -142,14 +140,14 @@ __global__ __launch_bounds__(64 * WM * WN) void logits_kernel(const InT* __restr
 
 __global__ void clear_flags_kernel(int32_t* hdr) { hdr[HDR_FLAGS] = 0; }
 
-template <typename InT, int MT, int NT, int NS>
+template <typename InT, int MT, int NT, int NS, bool APART>
 static void launch_logits_cfg(const InT* x, const InT* w, const float* bias, float* logits,
                               int32_t* hdr, int T, int d, int E, SharedRows shared, hipStream_t s) {
   using C = ChainTile<InT, 2, 2, MT, NT, NS>;
   constexpr int MOST = 65535 * C::BT;  // tokens that the second dimension of a grid holds: 2.1 or 4.2 million
   for (long t0 = 0; t0 < T; t0 += MOST) {
     const int n = (int)(T - t0 < MOST ? T - t0 : MOST);
-    logits_kernel<InT, 2, 2, MT, NT, NS><<<dim3(cdiv(E, C::BE), cdiv(n, C::BT)), 64 * C::NW, C::LDS_BYTES, s>>>(
+    logits_kernel<InT, 2, 2, MT, NT, NS, APART><<<dim3(cdiv(E, C::BE), cdiv(n, C::BT)), 64 * C::NW * (APART ? 2 : 1), C::LDS_BYTES, s>>>(
         x + t0 * d, w, bias, logits + t0 * E, hdr, n, d, E, shared);
   }
 }
@@ -157,22 +155,25 @@ static void launch_logits_cfg(const InT* x, const InT* w, const float* bias, flo
 // Workgroups of 2 x 2 waves on tiles of 32 x 32, 32 x 64 or 64 x 64 logits: 1, 2 or 4 sub-tiles
 // per SIMD.  The time is the number of sub-tiles the busiest SIMD works through (workgroups per
 // CU, rounded up, times sub-tiles), so the tile with the smallest such number is taken; among
-// equals, and up to 5 % more, the widest, which re-reads less (65 536 x 512: 0.94 ms against 1.07 and 0.98;
-// 50 000 x 512, counts 100, 98 and 98: 0.735 against 0.82 and 0.76), but where one or two sub-tiles are all there
-// is its single workgroup per CU has nothing to overlap its start with (4096 x 128: 22.2 us on 32 x 32, 24.4 on
-// 32 x 64).  Measured, d = 2048, against the kernels this one replaced: 16 384 x 512 0.242 ms (0.308), 8192 x 128
-// 37 us (65), 2741 x 128 20 us (35), 1 x 512 11 us (25).
+// equals, and up to 5 % more, the widest, which re-reads less, but where one or two sub-tiles are all there
+// is its single workgroup per CU has nothing to overlap its start with (4096 x 128: 20.7 us on 32 x 32, 21.5 on
+// 32 x 64).  The narrow tiles have their copies done by waves of their own (APART).  The 64 x 64 tile does not: three of its
+// workgroups share a CU, and six waves per SIMD measured 152 us where three took 137 (8192 x 512).  A workgroup of it that is
+// left alone, the last of 4, 7, 10 .., takes a quarter longer.  Between HIP events, d = 2048, all in 32 x 64 | 64 x 64: 8192 x 512
+// 126.5 | 134.5, 16 384 x 256 126 | 140, 10 000 x 512 156.0 | 154.0, 12 000 185.6 | 182.3, 16 384 245 | 241, 65 536 955 | 947.
+// Copies by the same waves | apart: 1 x 512 13.6 | 11.8, 1024 22.1 | 20.6, 3000 56.4 | 50.2, 5000 89.5 | 79.6, 2741 x 128 21.9 |
+// 20.0, 8192 39.5 | 35.6, 6007 x 256 56.6 | 50.1; 100 x 32, d = 4096 23.1 | 19.4; fp32, 1024 x 32, d = 256 6.4 | 6.4.
 template <typename InT>
 static void launch_logits_t(const InT* x, const InT* w, const float* bias, float* logits,
                             int32_t* hdr, int T, int d, int E, SharedRows shared, hipStream_t s) {
   auto cost = [&](int bt, int be, int sub) { return (long)cdiv((long)cdiv(T, bt) * cdiv(E, be), num_cus()) * sub; };
   const long c1 = cost(32, 32, 1), c2 = cost(32, 64, 2), c4 = cost(64, 64, 4);  // c1 <= c2 <= c4
-  if (c4 > 4 && c4 * 20 <= c1 * 21)
-    launch_logits_cfg<InT, 2, 2, 3>(x, w, bias, logits, hdr, T, d, E, shared, s);
+  if (c4 > 4 && c4 * 20 + (c4 / 4 % 3 == 1 ? 22 : 0) <= c1 * 21)
+    launch_logits_cfg<InT, 2, 2, 3, false>(x, w, bias, logits, hdr, T, d, E, shared, s);
   else if (c2 == c1 && c1 > 2)
-    launch_logits_cfg<InT, 1, 2, 5>(x, w, bias, logits, hdr, T, d, E, shared, s);
+    launch_logits_cfg<InT, 1, 2, 5, true>(x, w, bias, logits, hdr, T, d, E, shared, s);
   else
-    launch_logits_cfg<InT, 1, 1, 6>(x, w, bias, logits, hdr, T, d, E, shared, s);
+    launch_logits_cfg<InT, 1, 1, 6, true>(x, w, bias, logits, hdr, T, d, E, shared, s);
 }
 
 // Rows are compared beyond 2^34 multiply-adds.  Logits between HIP events, d = 2048, 512 sub-experts, 4 to an expert, rows not

@@ -172,3 +172,21 @@ def test_equal_router_rows_are_computed_once_with_the_same_logits(dtype, N, S, c
     exact = x[tokens].double() @ w.double().T
     bound = 2.0 * d * 2.0 ** -24 * (x[tokens].double().abs() @ w.double().abs().T)  # d roundings of the running sum
     assert ((ref[2][tokens].double() - bias.double() - exact).abs() <= bound + 1e-6).all()
+
+
+@pytest.mark.parametrize("d", [64, 128, 192, 256, 320, 384, 448, 512])
+@pytest.mark.parametrize("T,E", [(1, 5), (33, 70), (3001, 510), (12001, 509)])  # tiles of 32 x 32, 32 x 64, 64 x 64
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_logits_of_every_tile_and_count_of_stages(T, E, d, dtype):
+    # fewer stages than the ring holds, and more, with the copies in the waves of the products or apart; small whole
+    # numbers, so that every order of the sum is exact
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x = torch.randint(-9, 10, (T, d), generator=g, device="cuda").to(dt)
+    w = torch.randint(-9, 10, (E, d), generator=g, device="cuda").to(dt)
+    k = torch.ones(T, dtype=torch.int32, device="cuda")
+    shape = B.make_shape(T, d, E, 1, 32, 1, dtype)
+    ids, _, lg = B.moe_prism_route(shape, x, w, None, k, B.alloc_workspace(shape), want_logits=True)
+    ref = x.double() @ w.double().T
+    assert torch.equal(lg.double(), ref)
+    assert torch.equal(lg.gather(1, ids[:, :1].long()), lg.max(dim=1, keepdim=True).values)
