@@ -326,7 +326,7 @@ MOE_PRISM_API int moe_prism_status(const void* ws, int32_t* host_flags, int32_t*
 #define MOE_PRISM_K_FFN_TILES 5
 #define MOE_PRISM_K_FFN_GATE_UP 6
 #define MOE_PRISM_K_FFN_DOWN 7
-#define MOE_PRISM_K_COMBINE 8
+#define MOE_PRISM_K_COMBINE 8 /* not launched by the layer calls where K_FFN_DOWN adds up the picks of a few tokens itself */
 #define MOE_PRISM_K_PROXY_SELECT 9
 #define MOE_PRISM_K_FFN_FUSED 10 /* gate-up + SwiGLU + down in one kernel (narrow sub-experts) */
 #define MOE_PRISM_K_FFN_TRAFFIC 11 /* moe_prism_ffn_traffic_probe */

@@ -223,9 +223,20 @@ static int do_dispatch(const moe_prism_shape* s, const Layout& L, const int32_t*
                           plan != nullptr ? *plan : FfnPlan{false, 0, {8, true, 0}, 0}, s->T, E, s->k_max, st);
 }
 
+// of the layer calls: a combine follows, which the down projection of a few tokens does itself
+struct CombineArgs {
+  const int32_t* slot_of_pair;
+  const float* w;
+  const int32_t* k_tok;
+  void* out;
+};
+static bool combines(const moe_prism_shape* s, const FfnPlan& p) {
+  return s->dtype == MOE_PRISM_BF16 && ffn_down_combines(p.few, s->T, s->k_max, s->n_experts * s->n_sub, s->d, s->inter_sub);
+}
 static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, const void* w_gu,
                   const void* w_dn, const int32_t* off, const int32_t* sorted_pair, void* y,
-                  char* ws, hipStream_t st, const FfnPlan& p, bool traffic_probe = false, bool tiles_built = false) {
+                  char* ws, hipStream_t st, const FfnPlan& p, bool traffic_probe = false, bool tiles_built = false,
+                  const CombineArgs* combine = nullptr) {
   const int E = s->n_experts * s->n_sub;
   int32_t* hdr = reinterpret_cast<int32_t*>(ws + L.hdr);
   MTile* tiles = reinterpret_cast<MTile*>(ws + L.tiles);
@@ -251,8 +262,25 @@ static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, cons
   MP_LAUNCH(MOE_PRISM_K_FFN_GATE_UP,
             launch_ffn_gate_up(s->dtype, x, w_gu, sorted_pair, tiles, hdr, h, s->T, s->d, s->inter_sub,
                                s->k_max, p.few, L.max_mtiles, st));
+  if (combine != nullptr && combines(s, p)) {
+    MP_LAUNCH(MOE_PRISM_K_FFN_DOWN,
+              launch_ffn_down_combine((const uint16_t*)h, (const uint16_t*)w_dn, tiles, hdr, p.max_tiles, combine->slot_of_pair,
+                                      combine->w, combine->k_tok, (uint16_t*)combine->out, p.few, s->T, s->d, s->inter_sub, E, s->k_max, st));
+    return MOE_PRISM_OK;
+  }
   MP_LAUNCH(MOE_PRISM_K_FFN_DOWN, launch_ffn_down(s->dtype, h, w_dn, tiles, hdr, y, s->T, s->d,
                                                   s->inter_sub, p.few, L.max_mtiles, st));
+  return MOE_PRISM_OK;
+}
+
+// the end of the layer calls
+static int ffn_and_combine(const moe_prism_shape* s, const Layout& L, const void* x, const void* w_gu, const void* w_dn,
+                           const int32_t* off, const int32_t* sorted_pair, char* ws, hipStream_t st, const FfnPlan& p,
+                           const CombineArgs& c) {
+  void* y = ws + L.y;
+  const int rc = do_ffn(s, L, x, w_gu, w_dn, off, sorted_pair, y, ws, st, p, false, true, &c);
+  if (rc || s->T == 0 || combines(s, p)) return rc;
+  MP_LAUNCH(MOE_PRISM_K_COMBINE, launch_combine(s->dtype, y, c.slot_of_pair, c.w, c.k_tok, c.out, s->T, s->d, s->k_max, st));
   return MOE_PRISM_OK;
 }
 
@@ -480,7 +508,6 @@ static int layer_on(const moe_prism_shape* shape, const Layout& L, const void* x
   int32_t* off = reinterpret_cast<int32_t*>(w8 + L.off);
   int32_t* sp = reinterpret_cast<int32_t*>(w8 + L.sorted_pair);
   int32_t* sl = reinterpret_cast<int32_t*>(w8 + L.slot_of_pair);
-  void* y = w8 + L.y;
   // a small batch is dispatched by the top-k kernel itself
   const FfnPlan p = plan_ffn(L, shape);
   const SmallDispatch small{cnt, off, sp, sl, reinterpret_cast<MTile*>(w8 + L.tiles), p.max_tiles, p.cut};
@@ -492,12 +519,7 @@ static int layer_on(const moe_prism_shape* shape, const Layout& L, const void* x
     rc = do_dispatch(shape, L, ids, cnt, off, sp, sl, w8, st, &p);
     if (rc) return rc;
   }
-  rc = do_ffn(shape, L, x, w_gate_up, w_down, off, sp, y, w8, st, p, false, true);
-  if (rc) return rc;
-  if (shape->T == 0) return MOE_PRISM_OK;
-  MP_LAUNCH(MOE_PRISM_K_COMBINE, launch_combine(shape->dtype, y, sl, w, k_tok, out, shape->T,
-                                                shape->d, shape->k_max, st));
-  return MOE_PRISM_OK;
+  return ffn_and_combine(shape, L, x, w_gate_up, w_down, off, sp, w8, st, p, CombineArgs{sl, w, k_tok, out});
 }
 
 int moe_prism_layer(const moe_prism_shape* shape, const void* x, const void* w_router,
@@ -567,19 +589,13 @@ int moe_prism_layer_proxy(const moe_prism_shape* shape, const void* x, const voi
   int32_t* off = reinterpret_cast<int32_t*>(w8 + L.off);
   int32_t* sp = reinterpret_cast<int32_t*>(w8 + L.sorted_pair);
   int32_t* sl = reinterpret_cast<int32_t*>(w8 + L.slot_of_pair);
-  void* y = w8 + L.y;
   rc = do_route_proxy(shape, L, x, w_router0, router_bias0, w_proxy, m, r, rows_half, kappa, k_tok,
                       ids, w, w8, st);
   if (rc) return rc;
   const FfnPlan p = plan_ffn(L, shape);
   rc = do_dispatch(shape, L, ids, cnt, off, sp, sl, w8, st, &p);
   if (rc) return rc;
-  rc = do_ffn(shape, L, x, w_gate_up, w_down, off, sp, y, w8, st, p, false, true);
-  if (rc) return rc;
-  if (shape->T == 0) return MOE_PRISM_OK;
-  MP_LAUNCH(MOE_PRISM_K_COMBINE, launch_combine(shape->dtype, y, sl, w, k_tok, out, shape->T,
-                                                shape->d, shape->k_max, st));
-  return MOE_PRISM_OK;
+  return ffn_and_combine(shape, L, x, w_gate_up, w_down, off, sp, w8, st, p, CombineArgs{sl, w, k_tok, out});
 }
 
 int moe_prism_status(const void* ws, int32_t* host_flags, int32_t* host_pairs, void* stream) {

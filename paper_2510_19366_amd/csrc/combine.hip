@@ -2,7 +2,8 @@
 // One workgroup per token (few tokens: a wave per 64 column vectors), 16-byte column vectors per thread, picks
 // visited in ascending j (two batches of four row loads alternate in flight) with fp32 accumulation and a
 // single final rounding.  No atomics:
-// every output element has exactly one writer, so the result is reproducible.
+// every output element has exactly one writer, so the result is reproducible.  (bf16 layer calls of a few tokens: see
+// ffn_down_combine_kernel.)
 #include "kernels.h"
 
 namespace mp {

@@ -1094,6 +1094,217 @@ __global__ __launch_bounds__((Few<MOST, SHORT, NARROW>::THREADS)) void ffn_few_k
   }
 }
 
+// ---------------------------------------------------------------- down projection and combine of a few tokens
+// A workgroup has 8 or 16 columns of the output and all slot rows: y of them stays in LDS, and the picks of a token are
+// added behind one barrier, in the combine's order.  The m-tiles are cut into blocks of 16 slot rows for 16 columns.  For 8
+// columns they are blocks of 8 rows, and a wave multiplies two of them at a time: weight rows 0 .. 7 of the matrix instruction
+// are the columns of one block's sub-expert, 8 .. 15 of the other's, and so are the slot rows; what it makes of one's weights
+// and the other's rows is dropped.  Weights and slot rows share the stages of a ring that is the wave's own.
+// Bound by the weights' bytes, as ffn_few_kernel is, and by one launch's latency; what it saves is the combine's launch, 3 us of
+// a call, and y's way through memory.  Layer calls that find their weights in HBM, us, two kernels | this one: 128 x 4
+// sub-experts of 192 x 2048, 8 to 32 picks, skewed: 1 token 32.9 | 30.8, 4 46.7 | 44.8, 16 78.2 | 75.5, 37 100.7 | 95.2; of 64 x 2048 20
+// tokens 82.2 | 73.6; 64 x 4 of 256 x 2048 20 tokens 149.3 | 140.4; 64 x 2 of 704 x 2048 40 tokens 207 | 205; 8 x 4 of 3584 x 4096 1 token
+// 104.8 | 99.8, 47 513 | 491; 32 x 4 of 256 x 3072 60 tokens 126.4 | 120.8.  (Pairs of m-tiles instead of blocks dealt to the waves:
+// 37 tokens 97.4, as a wave with a long group came last.)
+template <int COLUMNS>
+struct DownCombine {
+  static constexpr int COLS = COLUMNS, BLOCK = COLUMNS, PAIR = 16 / COLUMNS;  // columns, rows of a block, blocks at a time
+  static constexpr int WAVES = 8, THREADS = 64 * WAVES;
+  static constexpr int NS = 4, AHEAD = NS - 1, STAGE = 4096, RING = WAVES * NS * STAGE, CP = 4;
+  static constexpr int TOKENS = THREADS / (COLS / 2);  // a thread adds up two columns of a token
+  // behind the ring, of each possible slot row: y, a block (at most one per row, and one more), a pick's weight and slot
+  static constexpr int ROW = COLS * 2 + 4 + 4 + 2, LDS_BYTES = 160 * 1024 - 256, ROWS = (LDS_BYTES - RING - 16) / ROW;
+  static constexpr int PER_THREAD = (ROWS + THREADS - 1) / THREADS;
+  static_assert(ROWS < 1 << 11);  // dc_block
+  static size_t lds_bytes(int rows) { return RING + (size_t)rows * ROW + 16; }
+};
+// a block: sub-expert, first slot row, rows - 1
+__device__ __forceinline__ uint32_t dc_block(int g, int row0, int rows) { return (uint32_t)(g | row0 << 12 | (rows - 1) << 23); }
+__device__ __forceinline__ int dc_group(uint32_t b) { return b & 4095; }
+__device__ __forceinline__ int dc_row0(uint32_t b) { return b >> 12 & 2047; }
+__device__ __forceinline__ int dc_rows(uint32_t b) { return (int)(b >> 23) + 1; }
+
+template <int COLUMNS, int STAGES>  // STAGES: of K, or 0: any number
+__global__ __launch_bounds__(DownCombine<COLUMNS>::THREADS) void ffn_down_combine_kernel(
+    const uint16_t* __restrict__ h, const uint16_t* __restrict__ w_dn, const MTile* __restrict__ tiles,
+    const int32_t* __restrict__ hdr, int max_tiles, const int32_t* __restrict__ slot_of_pair, const float* __restrict__ w,
+    const int32_t* __restrict__ k_tok, uint16_t* __restrict__ out, int T, int d, int Is, int k_max) {
+  typedef DownCombine<COLUMNS> D;
+  extern __shared__ __align__(16) unsigned char dc_smem[];
+  __shared__ int sums[D::WAVES];
+  const int K = STAGES ? STAGES * BK : Is, ns = STAGES ? STAGES : (K + BK - 1) / BK;
+  const uint32_t row2 = (uint32_t)K * 2u;
+  const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6), r = lane & 15, g = lane >> 4;
+  // neighbouring columns on one XCD: a line of the output has eight or four writers
+  const int b = blockIdx.x, n0 = D::COLS * (gridDim.x % N_XCD != 0 ? b : b % N_XCD * (int)(gridDim.x / N_XCD) + b / N_XCD);
+  const int n_rows = T * k_max;
+  unsigned char* ys = dc_smem + D::RING;
+  uint32_t* blocks = reinterpret_cast<uint32_t*>(ys + n_rows * (D::COLS * 2));
+  float* pick_w = reinterpret_cast<float*>(blocks + (n_rows + 2));
+  int16_t* pick_slot = reinterpret_cast<int16_t*>(pick_w + n_rows);
+  // everything that is read before the ring starts, at once
+  const FewTile* few = reinterpret_cast<const FewTile*>(tiles);
+  FewTile tile = few[min((int)threadIdx.x, max_tiles - 1)];
+  const int token = threadIdx.x / (D::COLS / 2), budget = k_tok[min(token, T - 1)];
+  int slot[D::PER_THREAD];
+  float weight[D::PER_THREAD];
+#pragma unroll
+  for (int i = 0; i < D::PER_THREAD; ++i) {
+    const int at = min((int)threadIdx.x + i * D::THREADS, n_rows - 1);
+    slot[i] = slot_of_pair[at];
+    weight[i] = w[at];
+  }
+  const int n_tiles = uni(hdr[HDR_MTILES]);
+#pragma unroll
+  for (int i = 0; i < D::PER_THREAD; ++i) {
+    const int at = (int)threadIdx.x + i * D::THREADS;
+    asm volatile("" : "+v"(slot[i]), "+v"(weight[i]));  // the loads stay where they are
+    if (at < n_rows) {
+      pick_slot[at] = (int16_t)(slot[i] < n_rows ? slot[i] : -1);
+      pick_w[at] = weight[i];
+    }
+  }
+  int n_blocks = 0;
+  for (int base = 0; base < n_tiles; base += D::THREADS) {
+    if (base > 0) tile = few[min(base + (int)threadIdx.x, max_tiles - 1)];
+    const int rows = base + (int)threadIdx.x < n_tiles ? tile.rows_count & 255 : 0, n = (rows + D::BLOCK - 1) / D::BLOCK;
+    int at = base + threadIdx.x, total = min(n_tiles - base, D::THREADS);
+    if (T > D::BLOCK) {  // tiles of several blocks
+      int sum = n;
+#pragma unroll
+      for (int i = 1; i < 64; i *= 2) {
+        const int v = __shfl_up(sum, i);
+        if (lane >= i) sum += v;
+      }
+      if (base > 0) __syncthreads();
+      if (lane == 63) sums[wv] = sum;
+      __syncthreads();
+      at = n_blocks + sum - n;
+      total = 0;
+#pragma unroll
+      for (int i = 0; i < D::WAVES; ++i) {
+        if (i < wv) at += sums[i];
+        total += sums[i];
+      }
+    }
+    n_blocks += total;
+    for (int i = 0; i < n; ++i) {
+      const uint32_t bl = dc_block(tile.g, tile.row0 + i * D::BLOCK, min(rows - i * D::BLOCK, D::BLOCK));
+      blocks[at + i] = bl;
+      if (at + i == n_blocks - 1 && base + D::THREADS >= n_tiles) blocks[at + i + 1] = bl;  // of an odd number the last one twice
+    }
+  }
+  __syncthreads();
+  n_blocks = uni(n_blocks);
+
+  const uint32_t ring = lds_offset(dc_smem) + (uint32_t)(wv * D::NS * D::STAGE);
+  uint32_t piece[2], tail[2], rd[2], w_row[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int row = j * 8 + (lane >> 3);
+    piece[j] = (uint32_t)((lane & 7) ^ swz_f<SWZ_SEQ>(row)) * 16u;
+    tail[j] = piece[j] & 64u;
+    w_row[j] = (uint32_t)(row % D::COLS) * row2 + piece[j];
+    rd[j] = (uint32_t)(r * 128) + (uint32_t)((j * 4 + g) ^ swz_f<SWZ_SEQ>(r)) * 16u;
+  }
+  uint32_t p_slot = ring, c_slot = ring;
+  int ahead = 0, p_at = D::PAIR * wv, p_stage = 0;  // stages on their way; what is copied next
+  uint2 next = {0, 0};                              // ... and its blocks
+  auto look = [&] {
+    if (p_at >= n_blocks) return;
+    if constexpr (D::PAIR == 2) next = *reinterpret_cast<const uint2*>(blocks + p_at);
+    else next.x = next.y = blocks[p_at];
+  };
+  look();
+  const uint16_t* wp[2];
+  uint32_t h_off[2];
+  auto produce = [&](uint32_t b0, uint32_t b1) {
+    if (p_at >= n_blocks) return;
+    if (p_stage == 0) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const uint32_t bl = j == 0 ? b0 : b1;
+        wp[j] = w_dn + ((size_t)dc_group(bl) * d + n0) * K;
+        h_off[j] = (uint32_t)(dc_row0(bl) + min((j * 8 + (lane >> 3)) % D::BLOCK, dc_rows(bl) - 1)) * row2 + piece[j];
+      }
+    }
+    const bool cut = STAGES == 0 && (p_stage + 1) * BK > K;  // K % 64 == 32: pieces 4 .. 7 do not exist, fetch 0 .. 3 (not used)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const uint32_t back = cut ? tail[j] : 0u;
+      copy_to_lds16(wp[j] + p_stage * BK, w_row[j] - back, p_slot + j * 1024u);
+      copy_to_lds16(h + p_stage * BK, h_off[j] - back, p_slot + 2048u + j * 1024u);
+    }
+    p_slot = p_slot == ring + (D::NS - 1) * D::STAGE ? ring : p_slot + D::STAGE;
+    ++ahead;
+    if (++p_stage == ns) {
+      p_stage = 0;
+      p_at += D::PAIR * D::WAVES;
+      look();
+    }
+  };
+#pragma nounroll
+  for (int i = 0; i < D::AHEAD; ++i) produce(uni(next.x), uni(next.y));
+  for (int c_at = D::PAIR * wv; c_at < n_blocks; c_at += D::PAIR * D::WAVES) {
+    const uint32_t block = blocks[c_at + (D::PAIR == 2 ? g >> 1 : 0)];
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    auto stage = [&](int steps) {
+      const uint32_t b0 = uni(next.x), b1 = uni(next.y);  // here, where no LDS read is waited for with it
+      // the copies of this stage have landed; AHEAD - 1 stages were issued after it, or fewer near the end
+      if (ahead == D::AHEAD) wait_vmem<(D::AHEAD - 1) * D::CP>();
+      else wait_vmem<0>();
+      bf16x8 fw[2] = {}, fx[2] = {};
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        read_lds16<0>(fw[ks], rd[ks] + c_slot);
+        read_lds16<2048>(fx[ks], rd[ks] + c_slot);
+      }
+      c_slot = c_slot == ring + (D::NS - 1) * D::STAGE ? ring : c_slot + D::STAGE;
+      --ahead;
+      produce(b0, b1);  // into the slot of the stage before, which has been read
+      wait_lds<0>(fw[0], fw[1], fx[0], fx[1]);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+        if (ks < steps) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[ks], fx[ks], acc, 0, 0, 0);
+    };
+    if constexpr (STAGES > 0) {
+      static_loop<0, STAGES>([&](auto) { stage(2); });
+    } else {
+      for (int s = 1; s < ns; ++s) stage(2);
+      stage(K % BK != 0 ? 1 : 2);
+    }
+    const int row = r % D::BLOCK;
+    if ((D::PAIR == 1 || r >> 3 == g >> 1) && row < dc_rows(block))
+      *reinterpret_cast<uint2*>(ys + (dc_row0(block) + row) * (D::COLS * 2) + g % (D::COLS / 4) * 8) =
+          make_uint2(pack2(acc[0], acc[1]), pack2(acc[2], acc[3]));
+  }
+  __syncthreads();
+  if (token >= T) return;
+  const int c = threadIdx.x % (D::COLS / 2), kt = min(max(budget, 0), k_max);
+  float a0 = 0.0f, a1 = 0.0f;
+  for (int j0 = 0; j0 < kt; j0 += 8) {
+    int at[8];
+    float wt[8];
+    uint32_t v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int j = token * k_max + min(j0 + u, k_max - 1);
+      at[u] = j0 + u < kt ? pick_slot[j] : -1;
+      wt[u] = pick_w[j];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const uint32_t*>(ys + max(at[u], 0) * (D::COLS * 2) + c * 4);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const float wu = at[u] < 0 ? 0.0f : wt[u];  // a pick without a slot adds nothing
+      const uint32_t vu = at[u] < 0 ? 0u : v[u];
+      a0 = fmaf(wu, __uint_as_float(vu << 16), a0);
+      a1 = fmaf(wu, __uint_as_float(vu & 0xffff0000u), a1);
+    }
+  }
+  *reinterpret_cast<uint32_t*>(out + (size_t)token * d + n0 + 2 * c) = pack2(a0, a1);
+}
+
 // ---------------------------------------------------------------- launchers
 // The ring driver runs its producers two stages ahead, enters at most one new item per stage and
 // needs the next item's slot list one barrier before that: at least 4 stages per item.
@@ -1207,6 +1418,40 @@ hipError_t launch_down_bf16(const uint16_t* h, const uint16_t* w_dn, const MTile
                             int32_t* hdr, uint16_t* y, int T, int d, int Is, int few, int max_mtiles,
                             hipStream_t s) {
   return launch_op(DownOp{h, w_dn, y, d, Is}, T, Is, d, few, HDR_DYN_DOWN, max_mtiles, tiles, hdr, s);
+}
+
+// 8 or 16 columns, or 0: y in memory and a combine.
+//   As many workgroups as three quarters of the CUs, or they don't draw the weights' bytes: two kernels | one, us: 512 of 192 x
+//   1024 8 tokens 52.6 | 55.4, 30 99.7 | 108.5, x 512 37.8 | 42.5, 62 | 75; at d = 1536, 256 of 256, 10 tokens 63.0 | 61.0.  And no
+//   more than CUs, or some have two: in 8 columns, d = 4096, 32 of 3584, 1 token 110.7 | 118, 100 tokens 504 | 616.
+//   A sub-expert's weights are fetched again for each block of its rows: 8 of 704 x 2048, possible rows per sub-expert 12.5 33.1 | 32.1,
+//   30 38.6 | 40.3; 64 of 704 7.5 124.6 | 117.4, 12 126.5 | 125.4; 128 of 704 9.75 223 | 221.
+static int down_combine_columns(int few, int T, int k_max, int E, int d, int Is) {
+  const long rows = (long)T * k_max;
+  auto fits = [&](auto columns) {
+    typedef DownCombine<decltype(columns)::value> D;
+    return T <= D::TOKENS && rows <= D::ROWS && d <= D::COLS * num_cus() && 4 * d >= 3 * D::COLS * num_cus();
+  };
+  if (few == 0 || T < 1 || rows > 12L * E) return 0;
+  return fits(std::integral_constant<int, 8>{}) ? 8 : fits(std::integral_constant<int, 16>{}) ? 16 : 0;
+}
+bool ffn_down_combines(int few, int T, int k_max, int E, int d, int Is) { return down_combine_columns(few, T, k_max, E, d, Is) != 0; }
+
+hipError_t launch_ffn_down_combine(const uint16_t* h, const uint16_t* w_dn, const MTile* tiles, const int32_t* hdr,
+                                   int max_tiles, const int32_t* slot_of_pair, const float* w, const int32_t* k_tok,
+                                   uint16_t* out, int few, int T, int d, int Is, int E, int k_max, hipStream_t s) {
+  auto launch = [&](auto columns, auto stages) {
+    typedef DownCombine<decltype(columns)::value> D;
+    constexpr auto Kern = ffn_down_combine_kernel<D::COLS, decltype(stages)::value>;
+    hipError_t e = raise_lds_limit<Kern>(D::LDS_BYTES);
+    if (e != hipSuccess) return e;
+    Kern<<<d / D::COLS, D::THREADS, D::lds_bytes(T * k_max), s>>>(h, w_dn, tiles, hdr, max_tiles, slot_of_pair, w, k_tok, out, T, d, Is,
+                                                                  k_max);
+    return hipGetLastError();
+  };
+  if (down_combine_columns(few, T, k_max, E, d, Is) == 16) return launch(std::integral_constant<int, 16>{}, std::integral_constant<int, 0>{});
+  if (Is == 3 * BK) return launch(std::integral_constant<int, 8>{}, std::integral_constant<int, 3>{});
+  return launch(std::integral_constant<int, 8>{}, std::integral_constant<int, 0>{});
 }
 
 }  // namespace mp

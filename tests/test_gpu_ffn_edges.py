@@ -168,3 +168,44 @@ def test_a_callers_own_tables_with_groups_of_more_rows_than_tokens(dtype, T, k_m
     ref = (a / (1 + torch.exp(-a)) * u) @ w_dn[2].double().T
     err = (y.cpu().double() - ref).norm(dim=1) / ref.norm(dim=1)
     assert err.max() <= (2 * 2.0 ** -9 if dtype == "bf16" else 2 * d * 2.0 ** -24), int(err.argmax())
+
+
+@pytest.mark.parametrize("T,N,S,k_max,d,Is,combines", [
+    (1, 128, 4, 32, 2048, 192, 1),    # 8 columns: 256 workgroups; a block per tile
+    (1, 1, 1, 1, 2048, 64, 1),        # one block, of which a wave has two
+    (8, 16, 4, 4, 1536, 96, 1), (9, 16, 4, 4, 1600, 32, 1),  # up to 8 rows to a group, and more; half a stage; 200 workgroups
+    (17, 3, 1, 2, 1984, 352, 1),      # few groups, tiles of several blocks
+    (39, 128, 4, 32, 2048, 192, 1), (40, 128, 4, 32, 2048, 192, 0),  # 1250 possible rows
+    (128, 256, 4, 9, 2048, 64, 1), (129, 256, 4, 9, 2048, 64, 0),    # more tiles than threads; tokens
+    (64, 64, 2, 12, 2048, 704, 1), (50, 8, 1, 2, 2048, 192, 0),      # 12 possible rows to a group
+    (30, 16, 2, 4, 1472, 64, 0), (30, 16, 2, 4, 2112, 64, 0), (30, 16, 2, 4, 3008, 64, 0),  # 3/4 of the CUs; all of them
+    (5, 8, 4, 8, 4096, 608, 1), (24, 128, 4, 32, 3136, 192, 1), (25, 128, 4, 32, 3136, 192, 0),  # 16 columns: 196 workgroups; 779 rows
+    (64, 64, 4, 11, 3072, 64, 1), (65, 64, 4, 11, 3072, 64, 0), (30, 16, 2, 4, 4160, 64, 0)])
+def test_down_projection_and_combine_in_one_kernel(T, N, S, k_max, d, Is, combines):
+    # against the stage calls, which do them one after the other: the same sums in the same order, bit for bit.  Budgets of 0 to
+    # k_max; a router bias that gives some groups many tokens
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    E = N * S
+    shape = B.make_shape(T, d, N, S, Is, k_max, "bf16", 1, 1.5)
+
+    def normal(*size, std):
+        return torch.empty(size, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+    x, w_r, w_gu, w_dn = normal(T, d, std=1.0), normal(E, d, std=0.02), normal(E, 2 * Is, d, std=0.05), normal(E, d, Is, std=0.05)
+    bias = torch.empty(E, device="cuda").normal_(generator=g)
+    k = torch.randint(0, k_max + 1, (T,), generator=g, device="cuda", dtype=torch.int32)
+    k[0] = k_max
+    ws = B.alloc_workspace(shape)
+    B.moe_prism_timing_enable(True)
+    try:
+        out = B.moe_prism_layer(shape, x, w_r, bias, k, w_gu, w_dn, ws)
+        torch.cuda.synchronize()
+        assert (B.moe_prism_timing_read()["combine"][1] == 0) == bool(combines)
+    finally:
+        B.moe_prism_timing_enable(False)
+    out = out.clone()
+    ids, wt, _ = B.moe_prism_route(shape, x, w_r, bias, k, ws, want_logits=True)
+    _, off, sp, sl = B.moe_prism_dispatch(shape, ids, ws)
+    y = B.moe_prism_grouped_ffn(shape, x, w_gu, w_dn, off, sp, ws)
+    ref = B.moe_prism_combine(shape, y, sl, wt, k)
+    assert out[k > 0].abs().max() > 0
+    assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
