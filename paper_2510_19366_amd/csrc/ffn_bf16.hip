@@ -1102,34 +1102,34 @@ __global__ __launch_bounds__((Few<MOST, SHORT, NARROW>::THREADS)) void ffn_few_k
 // and the other's rows is dropped.  Weights and slot rows share the stages of a ring that is the wave's own.
 // Bound by the weights' bytes, as ffn_few_kernel is, and by one launch's latency; what it saves is the combine's launch, 3 us of
 // a call, and y's way through memory.  Layer calls that find their weights in HBM, us, two kernels | this one: 128 x 4
-// sub-experts of 192 x 2048, 8 to 32 picks, skewed: 1 token 32.9 | 30.8, 4 46.7 | 44.8, 16 78.2 | 75.5, 37 100.7 | 95.2; of 64 x 2048 20
-// tokens 82.2 | 73.6; 64 x 4 of 256 x 2048 20 tokens 149.3 | 140.4; 64 x 2 of 704 x 2048 40 tokens 207 | 205; 8 x 4 of 3584 x 4096 1 token
-// 104.8 | 99.8, 47 513 | 491; 32 x 4 of 256 x 3072 60 tokens 126.4 | 120.8.  (Pairs of m-tiles instead of blocks dealt to the waves:
-// 37 tokens 97.4, as a wave with a long group came last.)
-template <int COLUMNS>
+// sub-experts of 192 x 2048, 8 to 32 picks, skewed: 1 token 32.9 | 30.6, 4 46.7 | 44.8, 16 78.2 | 75.5, 37 100.9 | 96.9, 64 119 | 117; of 64 x
+// 2048 20 tokens 82.2 | 73.6, 60 111 | 97; 64 x 4 of 256 x 2048 20 tokens 149.3 | 140.4; 64 x 2 of 704 x 2048 40 tokens 207 | 205; 8 x 4 of 3584 x 4096 1 token
+// 104.8 | 99.8, 47 513 | 491; 32 x 4 of 256 x 3072 60 tokens 126.4 | 120.8.  (Pairs of m-tiles instead of blocks dealt to the waves: 37 tokens
+// 2 us more, as a wave with a long group came last.)
+template <int COLUMNS, int SLOTS>
 struct DownCombine {
   static constexpr int COLS = COLUMNS, BLOCK = COLUMNS, PAIR = 16 / COLUMNS;  // columns, rows of a block, blocks at a time
   static constexpr int WAVES = 8, THREADS = 64 * WAVES;
-  static constexpr int NS = 4, AHEAD = NS - 1, STAGE = 4096, RING = WAVES * NS * STAGE, CP = 4;
-  static constexpr int TOKENS = THREADS / (COLS / 2);  // a thread adds up two columns of a token
+  static constexpr int NS = SLOTS, AHEAD = NS - 1, STAGE = 4096, RING = WAVES * NS * STAGE, CP = 4;
+  static constexpr int TOKENS = THREADS / (COLS / 2);  // at a time: a thread adds up two columns of a token
   // behind the ring, of each possible slot row: y, a block (at most one per row, and one more), a pick's weight and slot
   static constexpr int ROW = COLS * 2 + 4 + 4 + 2, LDS_BYTES = 160 * 1024 - 256, ROWS = (LDS_BYTES - RING - 16) / ROW;
   static constexpr int PER_THREAD = (ROWS + THREADS - 1) / THREADS;
-  static_assert(ROWS < 1 << 11);  // dc_block
+  static_assert(ROWS < 1 << 12);  // dc_block
   static size_t lds_bytes(int rows) { return RING + (size_t)rows * ROW + 16; }
 };
 // a block: sub-expert, first slot row, rows - 1
-__device__ __forceinline__ uint32_t dc_block(int g, int row0, int rows) { return (uint32_t)(g | row0 << 12 | (rows - 1) << 23); }
+__device__ __forceinline__ uint32_t dc_block(int g, int row0, int rows) { return (uint32_t)(g | row0 << 12 | (rows - 1) << 24); }
 __device__ __forceinline__ int dc_group(uint32_t b) { return b & 4095; }
-__device__ __forceinline__ int dc_row0(uint32_t b) { return b >> 12 & 2047; }
-__device__ __forceinline__ int dc_rows(uint32_t b) { return (int)(b >> 23) + 1; }
+__device__ __forceinline__ int dc_row0(uint32_t b) { return b >> 12 & 4095; }
+__device__ __forceinline__ int dc_rows(uint32_t b) { return (int)(b >> 24) + 1; }
 
-template <int COLUMNS, int STAGES>  // STAGES: of K, or 0: any number
-__global__ __launch_bounds__(DownCombine<COLUMNS>::THREADS) void ffn_down_combine_kernel(
+template <int COLUMNS, int SLOTS, int STAGES>  // STAGES: of K, or 0: any number
+__global__ __launch_bounds__((DownCombine<COLUMNS, SLOTS>::THREADS)) void ffn_down_combine_kernel(
     const uint16_t* __restrict__ h, const uint16_t* __restrict__ w_dn, const MTile* __restrict__ tiles,
     const int32_t* __restrict__ hdr, int max_tiles, const int32_t* __restrict__ slot_of_pair, const float* __restrict__ w,
     const int32_t* __restrict__ k_tok, uint16_t* __restrict__ out, int T, int d, int Is, int k_max) {
-  typedef DownCombine<COLUMNS> D;
+  typedef DownCombine<COLUMNS, SLOTS> D;
   extern __shared__ __align__(16) unsigned char dc_smem[];
   __shared__ int sums[D::WAVES];
   const int K = STAGES ? STAGES * BK : Is, ns = STAGES ? STAGES : (K + BK - 1) / BK;
@@ -1145,7 +1145,8 @@ __global__ __launch_bounds__(DownCombine<COLUMNS>::THREADS) void ffn_down_combin
   // everything that is read before the ring starts, at once
   const FewTile* few = reinterpret_cast<const FewTile*>(tiles);
   FewTile tile = few[min((int)threadIdx.x, max_tiles - 1)];
-  const int token = threadIdx.x / (D::COLS / 2), budget = k_tok[min(token, T - 1)];
+  const int first = threadIdx.x / (D::COLS / 2);
+  const int first_budget = k_tok[min(first, T - 1)];
   int slot[D::PER_THREAD];
   float weight[D::PER_THREAD];
 #pragma unroll
@@ -1279,30 +1280,32 @@ __global__ __launch_bounds__(DownCombine<COLUMNS>::THREADS) void ffn_down_combin
           make_uint2(pack2(acc[0], acc[1]), pack2(acc[2], acc[3]));
   }
   __syncthreads();
-  if (token >= T) return;
-  const int c = threadIdx.x % (D::COLS / 2), kt = min(max(budget, 0), k_max);
-  float a0 = 0.0f, a1 = 0.0f;
-  for (int j0 = 0; j0 < kt; j0 += 8) {
-    int at[8];
-    float wt[8];
-    uint32_t v[8];
+  const int c = threadIdx.x % (D::COLS / 2);
+  for (int token = first; token < T; token += D::TOKENS) {
+    const int kt = min(max(token == first ? first_budget : k_tok[token], 0), k_max);
+    float a0 = 0.0f, a1 = 0.0f;
+    for (int j0 = 0; j0 < kt; j0 += 8) {
+      int at[8];
+      float wt[8];
+      uint32_t v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int j = token * k_max + min(j0 + u, k_max - 1);
-      at[u] = j0 + u < kt ? pick_slot[j] : -1;
-      wt[u] = pick_w[j];
+      for (int u = 0; u < 8; ++u) {
+        const int j = token * k_max + min(j0 + u, k_max - 1);
+        at[u] = j0 + u < kt ? pick_slot[j] : -1;
+        wt[u] = pick_w[j];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const uint32_t*>(ys + max(at[u], 0) * (D::COLS * 2) + c * 4);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const float wu = at[u] < 0 ? 0.0f : wt[u];  // a pick without a slot adds nothing
+        const uint32_t vu = at[u] < 0 ? 0u : v[u];
+        a0 = fmaf(wu, __uint_as_float(vu << 16), a0);
+        a1 = fmaf(wu, __uint_as_float(vu & 0xffff0000u), a1);
+      }
     }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const uint32_t*>(ys + max(at[u], 0) * (D::COLS * 2) + c * 4);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const float wu = at[u] < 0 ? 0.0f : wt[u];  // a pick without a slot adds nothing
-      const uint32_t vu = at[u] < 0 ? 0u : v[u];
-      a0 = fmaf(wu, __uint_as_float(vu << 16), a0);
-      a1 = fmaf(wu, __uint_as_float(vu & 0xffff0000u), a1);
-    }
+    *reinterpret_cast<uint32_t*>(out + (size_t)token * d + n0 + 2 * c) = pack2(a0, a1);
   }
-  *reinterpret_cast<uint32_t*>(out + (size_t)token * d + n0 + 2 * c) = pack2(a0, a1);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -1420,38 +1423,43 @@ hipError_t launch_down_bf16(const uint16_t* h, const uint16_t* w_dn, const MTile
   return launch_op(DownOp{h, w_dn, y, d, Is}, T, Is, d, few, HDR_DYN_DOWN, max_mtiles, tiles, hdr, s);
 }
 
-// 8 or 16 columns, or 0: y in memory and a combine.
-//   As many workgroups as three quarters of the CUs, or they don't draw the weights' bytes: two kernels | one, us: 512 of 192 x
-//   1024 8 tokens 52.6 | 55.4, 30 99.7 | 108.5, x 512 37.8 | 42.5, 62 | 75; at d = 1536, 256 of 256, 10 tokens 63.0 | 61.0.  And no
-//   more than CUs, or some have two: in 8 columns, d = 4096, 32 of 3584, 1 token 110.7 | 118, 100 tokens 504 | 616.
+// Three stages of ring leave room for twice the rows of four, and are as fast in 8 columns (37 tokens of 512 of 192 x 2048 96.9 us, four
+// 97.6).  In 16 four are the faster ones where they do: 32 of 3584 x 4096, 1 token 107.0 | 104.1, 5 307 | 304.
+typedef DownCombine<8, 3> Columns8;
+typedef DownCombine<16, 4> Columns16;
+typedef DownCombine<16, 3> Columns16Rows;
+// Two kernels | one, layer calls, us:
+//   As many workgroups as three quarters of the CUs, or they don't draw the weights' bytes: 512 of 192 x 1024 8 tokens 52.6 | 55.4, 30
+//   99.7 | 108.5, x 512 37.8 | 42.5, 62 | 75; at d = 1536, 256 of 256, 10 tokens 63.0 | 61.0.  And no more than CUs, or some have two: in
+//   8 columns, d = 4096, 32 of 3584, 1 token 110.7 | 118, 100 tokens 504 | 616.
 //   A sub-expert's weights are fetched again for each block of its rows: 8 of 704 x 2048, possible rows per sub-expert 12.5 33.1 | 32.1,
-//   30 38.6 | 40.3; 64 of 704 7.5 124.6 | 117.4, 12 126.5 | 125.4; 128 of 704 9.75 223 | 221.
-static int down_combine_columns(int few, int T, int k_max, int E, int d, int Is) {
-  const long rows = (long)T * k_max;
-  auto fits = [&](auto columns) {
-    typedef DownCombine<decltype(columns)::value> D;
-    return T <= D::TOKENS && rows <= D::ROWS && d <= D::COLS * num_cus() && 4 * d >= 3 * D::COLS * num_cus();
-  };
-  if (few == 0 || T < 1 || rows > 12L * E) return 0;
-  return fits(std::integral_constant<int, 8>{}) ? 8 : fits(std::integral_constant<int, 16>{}) ? 16 : 0;
+//   30 38.6 | 40.3; 64 of 704 7.5 124.6 | 117.4, 12 126.5 | 125.4; 128 of 704 9.75 223 | 221; 256 of 256 9.5 180.6 | 169.5.  Where rows of
+//   half a line straddle lines: 256 of 352 4.9 220 | 216, 5.6 224 | 219, 7.5 225 | 226, 9.4 236 | 238.
+template <class D>
+static bool down_combine_fits(int T, int k_max, int d) {
+  return (long)T * k_max <= D::ROWS && d <= D::COLS * num_cus() && 4 * d >= 3 * D::COLS * num_cus();
 }
-bool ffn_down_combines(int few, int T, int k_max, int E, int d, int Is) { return down_combine_columns(few, T, k_max, E, d, Is) != 0; }
+bool ffn_down_combines(int few, int T, int k_max, int E, int d, int Is) {
+  if (few == 0 || T < 1 || (long)T * k_max > (Is % BK != 0 ? 6L : 12L) * E) return false;
+  return down_combine_fits<Columns8>(T, k_max, d) || down_combine_fits<Columns16Rows>(T, k_max, d);
+}
 
 hipError_t launch_ffn_down_combine(const uint16_t* h, const uint16_t* w_dn, const MTile* tiles, const int32_t* hdr,
                                    int max_tiles, const int32_t* slot_of_pair, const float* w, const int32_t* k_tok,
                                    uint16_t* out, int few, int T, int d, int Is, int E, int k_max, hipStream_t s) {
-  auto launch = [&](auto columns, auto stages) {
-    typedef DownCombine<decltype(columns)::value> D;
-    constexpr auto Kern = ffn_down_combine_kernel<D::COLS, decltype(stages)::value>;
+  auto launch = [&](auto shape, auto stages) {
+    typedef decltype(shape) D;
+    constexpr auto Kern = ffn_down_combine_kernel<D::COLS, D::NS, decltype(stages)::value>;
     hipError_t e = raise_lds_limit<Kern>(D::LDS_BYTES);
     if (e != hipSuccess) return e;
     Kern<<<d / D::COLS, D::THREADS, D::lds_bytes(T * k_max), s>>>(h, w_dn, tiles, hdr, max_tiles, slot_of_pair, w, k_tok, out, T, d, Is,
                                                                   k_max);
     return hipGetLastError();
   };
-  if (down_combine_columns(few, T, k_max, E, d, Is) == 16) return launch(std::integral_constant<int, 16>{}, std::integral_constant<int, 0>{});
-  if (Is == 3 * BK) return launch(std::integral_constant<int, 8>{}, std::integral_constant<int, 3>{});
-  return launch(std::integral_constant<int, 8>{}, std::integral_constant<int, 0>{});
+  const std::integral_constant<int, 0> any;
+  const std::integral_constant<int, 3> three;
+  if (down_combine_fits<Columns8>(T, k_max, d)) return Is == 3 * BK ? launch(Columns8{}, three) : launch(Columns8{}, any);
+  return down_combine_fits<Columns16>(T, k_max, d) ? launch(Columns16{}, any) : launch(Columns16Rows{}, any);
 }
 
 }  // namespace mp

@@ -174,13 +174,15 @@ def test_a_callers_own_tables_with_groups_of_more_rows_than_tokens(dtype, T, k_m
     (1, 128, 4, 32, 2048, 192, 1),    # 8 columns: 256 workgroups; a block per tile
     (1, 1, 1, 1, 2048, 64, 1),        # one block, of which a wave has two
     (8, 16, 4, 4, 1536, 96, 1), (9, 16, 4, 4, 1600, 32, 1),  # up to 8 rows to a group, and more; half a stage; 200 workgroups
-    (17, 3, 1, 2, 1984, 352, 1),      # few groups, tiles of several blocks
-    (39, 128, 4, 32, 2048, 192, 1), (40, 128, 4, 32, 2048, 192, 0),  # 1250 possible rows
-    (128, 256, 4, 9, 2048, 64, 1), (129, 256, 4, 9, 2048, 64, 0),    # more tiles than threads; tokens
-    (64, 64, 2, 12, 2048, 704, 1), (50, 8, 1, 2, 2048, 192, 0),      # 12 possible rows to a group
+    (17, 3, 1, 2, 1984, 320, 1),      # few groups, tiles of several blocks
+    (37, 128, 4, 32, 2048, 192, 1), (78, 128, 4, 32, 2048, 192, 1), (79, 128, 4, 32, 2048, 192, 0),  # 2510 possible rows
+    (200, 256, 4, 12, 2048, 64, 1),   # more tiles than threads; the tokens in two turns
+    (64, 64, 2, 12, 2048, 704, 1), (129, 64, 2, 12, 2048, 704, 0),  # 12 possible rows to a group
+    (64, 64, 2, 12, 1536, 352, 1), (65, 64, 2, 12, 1536, 352, 0),  # 6, where K has half a stage
     (30, 16, 2, 4, 1472, 64, 0), (30, 16, 2, 4, 2112, 64, 0), (30, 16, 2, 4, 3008, 64, 0),  # 3/4 of the CUs; all of them
-    (5, 8, 4, 8, 4096, 608, 1), (24, 128, 4, 32, 3136, 192, 1), (25, 128, 4, 32, 3136, 192, 0),  # 16 columns: 196 workgroups; 779 rows
-    (64, 64, 4, 11, 3072, 64, 1), (65, 64, 4, 11, 3072, 64, 0), (30, 16, 2, 4, 4160, 64, 0)])
+    (5, 8, 4, 8, 4096, 608, 1), (24, 128, 4, 32, 3136, 192, 1), (25, 128, 4, 32, 3136, 192, 1),  # 16 columns: 196 workgroups; 773
+    (48, 128, 4, 32, 3136, 192, 1), (49, 128, 4, 32, 3136, 192, 0),  # and 1553 rows
+    (100, 64, 4, 11, 3072, 64, 1), (30, 16, 2, 4, 4160, 64, 0)])
 def test_down_projection_and_combine_in_one_kernel(T, N, S, k_max, d, Is, combines):
     # against the stage calls, which do them one after the other: the same sums in the same order, bit for bit.  Budgets of 0 to
     # k_max; a router bias that gives some groups many tokens
