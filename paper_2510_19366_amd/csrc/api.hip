@@ -132,14 +132,15 @@ struct Timed {  // brackets one kernel launch with events when timing is on
 // ------------------------------------------------------------ stages on a layout
 static int do_route(const moe_prism_shape* s, const Layout& L, const void* x, const void* w_router,
                     const float* bias, const int32_t* k_tok, int32_t* ids, float* w, float* logits,
-                    char* ws, hipStream_t st, const SmallDispatch* small = nullptr) {
+                    char* ws, hipStream_t st, const SmallDispatch* small = nullptr, bool picks = true) {
   const int E = s->n_experts * s->n_sub;
   int32_t* hdr = reinterpret_cast<int32_t*>(ws + L.hdr);
   MP_LAUNCH(MOE_PRISM_K_LOGITS,
             launch_logits(s->dtype, x, w_router, bias, logits, hdr, s->T, s->d, E, s->n_sub,
                           reinterpret_cast<int32_t*>(ws + L.chunk_cnt), st));
-  MP_LAUNCH(MOE_PRISM_K_TOPK, launch_topk(logits, k_tok, ids, w, hdr, s->T, E, s->k_max,
-                                          s->renormalize, s->routed_scale, small, st));
+  if (picks)
+    MP_LAUNCH(MOE_PRISM_K_TOPK, launch_topk(logits, k_tok, ids, w, hdr, s->T, E, s->k_max,
+                                            s->renormalize, s->routed_scale, small, st));
   return MOE_PRISM_OK;
 }
 
@@ -226,9 +227,13 @@ static int do_dispatch(const moe_prism_shape* s, const Layout& L, const int32_t*
 // of the layer calls: a combine follows, which the down projection of a few tokens does itself
 struct CombineArgs {
   const int32_t* slot_of_pair;
-  const float* w;
+  float* w;
   const int32_t* k_tok;
   void* out;
+  // the gate-up picks (ffn_picks) from these logits; or null
+  const SmallDispatch* picks = nullptr;
+  const float* logits = nullptr;
+  int32_t* ids = nullptr;
 };
 static bool combines(const moe_prism_shape* s, const FfnPlan& p) {
   return s->dtype == MOE_PRISM_BF16 && ffn_down_combines(p.few, s->T, s->k_max, s->n_experts * s->n_sub, s->d, s->inter_sub);
@@ -259,9 +264,15 @@ static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, cons
                                     s->k_max, L.max_mtiles, tiles_built ? p.cut.sorted : 0, st));
     return MOE_PRISM_OK;
   }
-  MP_LAUNCH(MOE_PRISM_K_FFN_GATE_UP,
-            launch_ffn_gate_up(s->dtype, x, w_gu, sorted_pair, tiles, hdr, h, s->T, s->d, s->inter_sub,
-                               s->k_max, p.few, L.max_mtiles, st));
+  if (combine != nullptr && combine->picks != nullptr)
+    MP_LAUNCH(MOE_PRISM_K_FFN_GATE_UP,
+              launch_ffn_pick_gate_up(combine->logits, combine->k_tok, combine->ids, combine->w, hdr, s->renormalize, s->routed_scale,
+                                      *combine->picks, (const uint16_t*)x, (const uint16_t*)w_gu, (uint16_t*)h, s->T, s->d, s->inter_sub, E,
+                                      s->k_max, st));
+  else
+    MP_LAUNCH(MOE_PRISM_K_FFN_GATE_UP,
+              launch_ffn_gate_up(s->dtype, x, w_gu, sorted_pair, tiles, hdr, h, s->T, s->d, s->inter_sub,
+                                 s->k_max, p.few, L.max_mtiles, st));
   if (combine != nullptr && combines(s, p)) {
     MP_LAUNCH(MOE_PRISM_K_FFN_DOWN,
               launch_ffn_down_combine((const uint16_t*)h, (const uint16_t*)w_dn, tiles, hdr, p.max_tiles, combine->slot_of_pair,
@@ -511,15 +522,17 @@ static int layer_on(const moe_prism_shape* shape, const Layout& L, const void* x
   // a small batch is dispatched by the top-k kernel itself
   const FfnPlan p = plan_ffn(L, shape);
   const SmallDispatch small{cnt, off, sp, sl, reinterpret_cast<MTile*>(w8 + L.tiles), p.max_tiles, p.cut};
-  const bool one = dispatch_is_small(shape->T, shape->n_experts * shape->n_sub, shape->k_max);
-  int rc = do_route(shape, L, x, w_router, router_bias, k_tok, ids, w,
-                    reinterpret_cast<float*>(w8 + L.logits), w8, st, one ? &small : nullptr);
+  const int E = shape->n_experts * shape->n_sub;
+  const bool one = dispatch_is_small(shape->T, E, shape->k_max);
+  const bool later = one && shape->dtype == MOE_PRISM_BF16 && ffn_picks(p.few, shape->T, shape->k_max, E);  // by the gate-up itself
+  float* logits = reinterpret_cast<float*>(w8 + L.logits);
+  int rc = do_route(shape, L, x, w_router, router_bias, k_tok, ids, w, logits, w8, st, one ? &small : nullptr, !later);
   if (rc) return rc;
   if (!one) {
     rc = do_dispatch(shape, L, ids, cnt, off, sp, sl, w8, st, &p);
     if (rc) return rc;
   }
-  return ffn_and_combine(shape, L, x, w_gate_up, w_down, off, sp, w8, st, p, CombineArgs{sl, w, k_tok, out});
+  return ffn_and_combine(shape, L, x, w_gate_up, w_down, off, sp, w8, st, p, CombineArgs{sl, w, k_tok, out, later ? &small : nullptr, logits, ids});
 }
 
 int moe_prism_layer(const moe_prism_shape* shape, const void* x, const void* w_router,

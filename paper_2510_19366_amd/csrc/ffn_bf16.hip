@@ -17,8 +17,10 @@
 // instead; these two kernels serve every other shape.
 #include <type_traits>
 
+#include "dispatch_common.h"
 #include "dma.h"
 #include "ffn_common.h"
+#include "topk_wave.h"
 
 namespace mp {
 
@@ -904,12 +906,17 @@ constexpr int FP_WAVE_N = 16, NARROW_COLS = 32;
 // workgroups per CU have more of them side by side.  Both GEMMs, us between HIP events, with two per CU and with three:
 // 1 token of the 128 x 4 layer 19.1 -> 18.1, 37 90.1 -> 88.6, 64 tokens on 256 of 64 x 1024 29.8 -> 26.0 (K = 256, 4 stages:
 // 180 tokens on 256 of 256 160 -> 163).
-template <int MOST, bool SHORT, bool NARROW>
+constexpr int PICK_K = 64;  // ELEMS: the largest k_max
+template <int MOST, bool SHORT, bool NARROW, int ELEMS = 0, int TOKENS = 0>
 struct Few {
-  static_assert((!SHORT || MOST <= 2) && (!NARROW || MOST == 4));
+  static_assert((!SHORT || MOST <= 2) && (!NARROW || MOST == 4) && (ELEMS == 0 || (MOST == 1 && !SHORT)));
   static constexpr int WAVES = MOST == 4 && !NARROW ? 8 : 4, THREADS = 64 * WAVES, N = WAVES * FP_WAVE_N;
-  static constexpr int NS = SHORT || NARROW ? 4 : MOST == 4 ? 5 : 6, STAGE = FP_WAVE_N * BK * 2, RING = WAVES * NS * STAGE;
-  static constexpr int CHUNK = WAVES * 4096, LDS_BYTES = RING + (SHORT ? 1 : 2) * CHUNK;
+  static constexpr int NS = SHORT || NARROW ? 4 : ELEMS > 0 ? 7 : MOST == 4 ? 5 : 6, STAGE = FP_WAVE_N * BK * 2, RING = WAVES * NS * STAGE;
+  static constexpr int CHUNK = WAVES * 4096;
+  // ELEMS: a row of a chunk is 1 KiB, and there are no more than TOKENS; what is read of the others is not used
+  static constexpr int CHUNK_STEP = ELEMS > 0 ? TOKENS * 1024 : CHUNK, GROUPS = RING + 2 * CHUNK_STEP;
+  static constexpr int LDS_BYTES = ELEMS > 0 ? RING + CHUNK_STEP + CHUNK : RING + (SHORT ? 1 : 2) * CHUNK;
+  static_assert(ELEMS == 0 || (GROUPS + TOKENS * PICK_K * 8 <= LDS_BYTES && 2 * LDS_BYTES <= 160 * 1024 && TOKENS <= WAVES));
   static constexpr int PER_CU = 160 * 1024 / LDS_BYTES, PARTS = NARROW ? BM / (16 * MOST) : 1;
   static constexpr int CP = 2;           // copies of a wave per stage
   static constexpr int AHEAD = NS - 1;   // stages in flight
@@ -924,17 +931,125 @@ struct Few {
 // 512: 1024 18.0 | 9.4, 8192 21.7 | 17.9; 128 of 32 x 4096: 4096 76.5 | 69.7.  (Blocks of 32 slot rows: 32.6, 42.2, 119 on the
 // 128.)  64 neurons are two such tiles, which read the slot rows twice, and half of a ring tile: 4096 tokens 45 | 56.  Where
 // few == 4 applies, it is ahead with even load (600 tokens on the 128 18.3 | 23.9).
-template <class Op, int MOST, bool SHORT, bool NARROW>
-__global__ __launch_bounds__((Few<MOST, SHORT, NARROW>::THREADS)) void ffn_few_kernel(Op op, const MTile* __restrict__ tiles,
+//
+// ELEMS, TOKENS (gate-up of up to TOKENS tokens, E <= 64 ELEMS): the route's picks and their dispatch belong to this launch.  Every
+// workgroup picks for itself, a wave per token, and lists the groups in LDS; the first one only writes what the route and the
+// dispatch leave in memory.  What it saves is the launch of the top-k kernel.  Layer calls that find their weights in HBM, us, top-k
+// kernel | this: 128 x 4 sub-experts of 192 x 2048, 1 token 30.7 | 27.1, 2 36.0 | 32.8, 4 44.5 | 41.4; 64 x 4 of 256 x 2048, 1 31.5 | 27.9, 4
+// 75.4 | 71.3; 64 x 2 of 704 x 2048, 1 31.1 | 27.9, 4 62.6 | 59.0; 8 x 4 of 3584 x 4096, 1 105.0 | 102.8; 512 of 128 x 256, 4 23.9 | 22.0.
+// With two tokens per wave 8 tokens of the first 61.0 | 59.8, but of the last 26.6 | 33.1: the first workgroup comes last.  (Where every
+// workgroup ranks its picks, which only the first one has to, one token 28.9.)
+struct PickArgs {
+  const float* logits;
+  const int32_t* k_tok;
+  int32_t* ids;
+  float* w;
+  int32_t* hdr;
+  int E, renorm;
+  float scale;
+  SmallDispatch small;
+};
+// The groups of the picks of T tokens, a bit per token and sub-expert in `takes` [token][element]: f(group, its place in the list, its
+// first row, its tokens as bits); returns the rows.  ALL: also the sub-experts that nobody took.
+template <int ELEMS, int TOKENS, bool ALL, class F>
+__device__ __forceinline__ int pick_groups(const u64* takes, int E, int& n_groups, F&& f) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  auto below = [](u64 m) { return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0)); };
+  int groups = 0, rows = 0;
+#pragma unroll
+  for (int i = 0; i < ELEMS; ++i) {
+    u64 take[TOKENS], any = 0;
+    int row0 = rows, bits = 0;
+#pragma unroll
+    for (int t = 0; t < TOKENS; ++t) {
+      take[t] = takes[t * ELEMS + i];
+      any |= take[t];
+      row0 += below(take[t]);
+      rows += __popcll(take[t]);
+      bits |= (int)(take[t] >> lane & 1) << t;
+    }
+    if (i % 4 == wv && (ALL ? i * 64 + lane < E : bits != 0)) f(i * 64 + lane, groups + below(any), row0, bits);
+    groups += __popcll(any);
+  }
+  n_groups = groups;
+  return rows;
+}
+
+template <class Op, int MOST, bool SHORT, bool NARROW, int ELEMS = 0, int TOKENS = 0, class... Pick>
+__global__ __launch_bounds__((Few<MOST, SHORT, NARROW, ELEMS, TOKENS>::THREADS)) void ffn_few_kernel(Op op, const MTile* __restrict__ tiles,
                                                                             const int32_t* __restrict__ hdr,
-                                                                            int n_tiles_n) {
-  typedef Few<MOST, SHORT, NARROW> F;
+                                                                            int n_tiles_n, Pick... pick) {
+  typedef Few<MOST, SHORT, NARROW, ELEMS, TOKENS> F;
   extern __shared__ __align__(16) unsigned char fp_smem[];
-  constexpr int FP_NS = F::NS, FP_STAGE = F::STAGE, FP_CHUNK = F::CHUNK;
+  constexpr int FP_NS = F::NS, FP_STAGE = F::STAGE, FP_CHUNK = F::CHUNK, STEP = F::CHUNK_STEP;
   constexpr int CP = F::CP, AHEAD = F::AHEAD, XCP = FP_CHUNK / 1024 / F::WAVES;  // XCP: copies of a wave per chunk
   const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6), r = lane & 15, g = lane >> 4;
   const int K = op.K(), ns = (K + BK - 1) / BK;
   const uint32_t lds0 = lds_offset(fp_smem), ring = lds0 + (uint32_t)(wv * FP_NS * FP_STAGE), xs = lds0 + F::RING;
+  int2* groups = reinterpret_cast<int2*>(fp_smem + F::GROUPS);  // ELEMS: sub-expert and tokens as bits << 16, first row
+  int n_m_tiles = 0, tokens = 0;  // m-tiles; ELEMS: tokens of the item's rows, as bits
+  if constexpr (ELEMS > 0) {
+    if (blockIdx.x > 0 && blockIdx.x < N_XCD) return;  // so that the items' workgroups keep their XCDs
+    const PickArgs& p = (pick, ...);
+    const int kp = topk_pad(op.k_max);
+    int* uk = reinterpret_cast<int*>(fp_smem) + wv * 4 * kp;  // as in the top-k kernel
+    int* uid = uk + kp;
+    float* se = reinterpret_cast<float*>(uid + kp);
+    int* sid = reinterpret_cast<int*>(se + kp);
+    u64* takes = reinterpret_cast<u64*>(fp_smem + F::WAVES * PICK_K * 16);
+    if (threadIdx.x < TOKENS * ELEMS) takes[threadIdx.x] = 0ull;
+    __syncthreads();
+    const bool first = blockIdx.x == 0;
+    TopkPicks picks{0, 0.0f, 1.0f};
+    if (wv < op.T) {
+      const float* row = p.logits + (size_t)wv * p.E;
+      const int asked = p.k_tok[wv];
+      u64* mine = takes + wv * ELEMS;
+      if (first) {
+        picks = topk_token<ELEMS>(row, asked, p.E, op.k_max, p.renorm, &p.hdr[HDR_FLAGS], uk, uid, se, sid);
+        for (int j = lane; j < picks.kt; j += 64) atomicOr(&mine[sid[j] >> 6], 1ull << (sid[j] & 63));
+      } else {
+        topk_token<ELEMS, true>(row, asked, p.E, op.k_max, p.renorm, nullptr, nullptr, nullptr, nullptr, nullptr, mine);
+      }
+    }
+    __syncthreads();
+    if (first) {
+      int* first_row = reinterpret_cast<int*>(takes + TOKENS * ELEMS);  // of a sub-expert's group; its tokens as bits << 16
+      const int rows = pick_groups<ELEMS, TOKENS, true>(takes, p.E, n_m_tiles, [&](int gr, int at, int row0, int bits) {
+        if (bits) {
+          put_tile(p.small.tiles, p.small.cut, at, gr, row0, __popc(bits), at, 1);
+          first_row[gr] = row0 | bits << 16;
+        }
+        p.small.off[gr] = row0;
+        p.small.cnt[gr] = __popc(bits);
+      });
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        p.small.off[p.E] = rows;
+        write_counts(p.hdr, rows, n_m_tiles, true, p.small.max_tiles);
+      }
+      if (wv >= op.T) return;
+      for (int j = lane; j < op.k_max; j += 64) {
+        const int i = wv * op.k_max + j;
+        const bool on = j < picks.kt;
+        const int gr = on ? sid[j] : -1;
+        int slot = -1;
+        if (on) {
+          const int f = first_row[gr];
+          slot = (f & 0xffff) + __popc((f >> 16) & ((1 << wv) - 1));
+          p.small.sorted_pair[slot] = i;
+        }
+        if (i >= rows) p.small.sorted_pair[i] = -1;  // tail beyond the valid slots
+        p.small.slot_of_pair[i] = slot;
+        p.ids[i] = gr;
+        p.w[i] = on ? p.scale * expf(se[j] - picks.most) / picks.denom : 0.0f;
+      }
+      return;
+    }
+    pick_groups<ELEMS, TOKENS, false>(takes, p.E, n_m_tiles, [&](int gr, int at, int row0, int bits) { groups[at] = int2{gr | bits << 16, row0}; });
+    n_m_tiles = uni(n_m_tiles);
+    __syncthreads();  // the ring takes the place of what was read
+  }
   auto tile = [&](const Sc& sc, bool on, auto nb_c) {
     constexpr int NB = decltype(nb_c)::value;  // blocks of 16 slot rows
     constexpr int CPR = FP_CHUNK / 256 / NB, SPC = CPR / 8;  // 16-byte pieces of a row in a chunk, stages
@@ -965,7 +1080,13 @@ __global__ __launch_bounds__((Few<MOST, SHORT, NARROW>::THREADS)) void ffn_few_k
     for (int j = 0; j < XCP; ++j) {
       const int row = (wv * XCP + j) * CROWS + lane % 64 / CPR;
       int pair = 0;
-      if constexpr (Op::GATHER) {
+      if constexpr (ELEMS > 0) {
+        int left = min(row, sc.rows - 1);  // the token of bit number `row`
+#pragma unroll
+        for (int t = 0; t < TOKENS; ++t)
+          if (tokens >> t & 1) pair = left-- == 0 ? t : pair;
+        pair *= op.k_max;
+      } else if constexpr (Op::GATHER) {
         // a copy of one row: the same for all lanes, and a scalar load does not wait for the copies
         typedef const __attribute__((address_space(4))) int32_t* Scalar;
         const int32_t* src = op.idx_src(sc, row);
@@ -979,7 +1100,7 @@ __global__ __launch_bounds__((Few<MOST, SHORT, NARROW>::THREADS)) void ffn_few_k
       for (int j = 0; j < XCP; ++j) {
         if (j >= x_on) break;
         const uint32_t col = (uint32_t)(c * CPR * 16) + xcol[j];
-        copy_to_lds16(bx, xrow[j] + (col < row2 ? col : 0u), xs + (uint32_t)((c & 1) * FP_CHUNK + (wv * XCP + j) * 1024));
+        copy_to_lds16(bx, xrow[j] + (col < row2 ? col : 0u), xs + (uint32_t)((c & 1) * STEP + (wv * XCP + j) * 1024));
       }
     };
     produce_x(0);
@@ -1031,7 +1152,7 @@ __global__ __launch_bounds__((Few<MOST, SHORT, NARROW>::THREADS)) void ffn_few_k
         if (q + AHEAD - 1 >= ns) wait_vmem<0>();
         else if (s < AHEAD && more && x_on == XCP) wait_vmem<(AHEAD - 1) * CP + XCP>();
         else wait_vmem<(AHEAD - 1) * CP>();
-        const uint32_t x_at = (uint32_t)((c & 1) * FP_CHUNK + s / 2 * 256);
+        const uint32_t x_at = (uint32_t)((c & 1) * STEP + s / 2 * 256);
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
           read_lds16<0>(fw[set][ks], rd_w[ks] + w_slot);
@@ -1060,11 +1181,20 @@ __global__ __launch_bounds__((Few<MOST, SHORT, NARROW>::THREADS)) void ffn_few_k
       if (on) op.few_store(sc, b * 16 + r, g, acc[b]);
     raw_barrier();  // the first chunk is copied again
   };
-  const ItemRange ir = xcd_items(hdr[HDR_MTILES] * n_tiles_n * F::PARTS);
+  ItemRange ir;
+  if constexpr (ELEMS > 0) ir = xcd_items(n_m_tiles * n_tiles_n, blockIdx.x - N_XCD, gridDim.x - N_XCD);
+  else ir = xcd_items(hdr[HDR_MTILES] * n_tiles_n * F::PARTS);
   for (int i = ir.begin; i < ir.end; i += ir.step) {
     Sc sc;
     int nt;
-    if constexpr (NARROW) {
+    if constexpr (ELEMS > 0) {
+      const int2 group = groups[i / n_tiles_n];
+      nt = i % n_tiles_n;
+      tokens = uni(group.x) >> 16;
+      sc.g = uni(group.x) & 0xffff;
+      sc.row0 = uni(group.y);
+      sc.rows = __popc(tokens);
+    } else if constexpr (NARROW) {
       const int item = i / F::PARTS, row = i % F::PARTS * 16 * MOST;
       const MTile t = tiles[item / n_tiles_n];
       nt = item % n_tiles_n;
@@ -1408,6 +1538,33 @@ int ffn_few_blocks(int T, int k_max, int E, int d, int Is, bool fused) {
   }
   if (pairs <= 24L * E) return 2;
   return T <= 64 || pairs <= 56L * E ? 4 : 0;
+}
+
+bool ffn_picks(int few, int T, int k_max, int E) { return few == 1 && T >= 1 && T <= 4 && k_max <= PICK_K && E <= 512; }
+
+hipError_t launch_ffn_pick_gate_up(const float* logits, const int32_t* k_tok, int32_t* ids, float* w, int32_t* hdr, int renorm, float scale,
+                                   const SmallDispatch& small, const uint16_t* x, const uint16_t* w_gu, uint16_t* h, int T, int d,
+                                   int Is, int E, int k_max, hipStream_t s) {
+  const GateUpOp op{x, w_gu, small.sorted_pair, h, T, d, Is, k_max};
+  const PickArgs p{logits, k_tok, ids, w, hdr, E, renorm, scale, small};
+  auto launch = [&](auto elems, auto tokens) {
+    typedef Few<1, false, false, decltype(elems)::value, decltype(tokens)::value> F;
+    constexpr auto Kern = ffn_few_kernel<GateUpOp, 1, false, false, decltype(elems)::value, decltype(tokens)::value, PickArgs>;
+    hipError_t e = raise_lds_limit<Kern>(F::LDS_BYTES);
+    if (e != hipSuccess) return e;
+    const int ntn = cdiv(Is, F::N / GateUpOp::N_PER_ROW);
+    const long most = (long)T * k_max < E ? (long)T * k_max : E;  // groups
+    const int grid = persistent_grid(most * ntn, F::PER_CU) + N_XCD;  // the first one writes, its neighbours have nothing to do
+    Kern<<<grid, F::THREADS, F::LDS_BYTES, s>>>(op, small.tiles, hdr, ntn, p);
+    return hipGetLastError();
+  };
+  auto of = [&](auto elems) {  // one token: a quarter of the looks at the picks, 0.6 us of 27.7
+    return T == 1 ? launch(elems, std::integral_constant<int, 1>{}) : launch(elems, std::integral_constant<int, 4>{});
+  };
+  if (E <= 64) return of(std::integral_constant<int, 1>{});
+  if (E <= 128) return of(std::integral_constant<int, 2>{});
+  if (E <= 256) return of(std::integral_constant<int, 4>{});
+  return of(std::integral_constant<int, 8>{});
 }
 
 hipError_t launch_gate_up_bf16(const uint16_t* x, const uint16_t* w_gu, const int32_t* sorted_pair,

@@ -13,9 +13,9 @@ constexpr int N_XCD = 8;
 struct ItemRange {
   int begin, end, step;
 };
-__device__ __forceinline__ ItemRange xcd_items(int total) {
-  const int xcd = blockIdx.x % N_XCD, slot = blockIdx.x / N_XCD;
-  const int per = gridDim.x / N_XCD;  // the grid is a multiple of N_XCD
+__device__ __forceinline__ ItemRange xcd_items(int total, int block, int grid) {
+  const int xcd = block % N_XCD, slot = block / N_XCD;
+  const int per = grid / N_XCD;  // the grid is a multiple of N_XCD
   const int chunk = (total + N_XCD - 1) / N_XCD;
   ItemRange r;
   r.begin = min(total, xcd * chunk) + slot;
@@ -23,6 +23,7 @@ __device__ __forceinline__ ItemRange xcd_items(int total) {
   r.step = per;
   return r;
 }
+__device__ __forceinline__ ItemRange xcd_items(int total) { return xcd_items(total, blockIdx.x, gridDim.x); }
 
 // SiLU(a) * u = a / (1 + e^-a) * u.  v_rcp_f32 and one correction of the quotient by its remainder,
 // in a third of the instructions of the IEEE division the compiler emits (which also scales its operands for

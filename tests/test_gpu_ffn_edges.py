@@ -211,3 +211,43 @@ def test_down_projection_and_combine_in_one_kernel(T, N, S, k_max, d, Is, combin
     ref = B.moe_prism_combine(shape, y, sl, wt, k)
     assert out[k > 0].abs().max() > 0
     assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
+
+
+@pytest.mark.parametrize("T,E,k_max,d,Is,picks", [
+    (1, 1, 1, 64, 32, 1), (1, 64, 6, 512, 64, 1), (2, 65, 7, 448, 96, 1), (3, 128, 64, 576, 32, 1), (4, 129, 40, 1088, 64, 1),
+    (1, 256, 64, 2048, 192, 1), (4, 257, 33, 64, 192, 1), (1, 512, 32, 2048, 192, 1), (4, 512, 64, 1024, 128, 1),
+    (4, 512, 8, 320, 352, 1), (2, 512, 2, 1536, 32, 1),
+    (5, 512, 8, 320, 192, 0), (1, 513, 8, 320, 192, 0), (4, 128, 65, 320, 64, 0)])
+@pytest.mark.parametrize("renorm,ties", [(1, False), (0, False), (1, True)])
+def test_gate_up_that_picks_for_itself(T, E, k_max, d, Is, picks, renorm, ties):
+    # against the stage calls: the same picks, and from them the same sums, bit for bit.  Budgets of 0 to k_max, and of
+    # outside of that, which the status reports; ties: logits of two values, so that the picks are the lowest ids
+    g = torch.Generator(device="cuda").manual_seed(T * E + d)
+    shape = B.make_shape(T, d, E, 1, Is, k_max, "bf16", renorm, 1.5)
+
+    def normal(*size, std):
+        return torch.empty(size, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+    x, w_r, w_gu, w_dn = normal(T, d, std=1.0), normal(E, d, std=0.02), normal(E, 2 * Is, d, std=0.05), normal(E, d, Is, std=0.05)
+    bias = torch.empty(E, device="cuda").normal_(generator=g)
+    if ties:
+        w_r.zero_()
+        bias = (bias > 0).float()
+    ws = B.alloc_workspace(shape)
+    for budgets in ([k_max] * T, [k_max // 2] * T, [0] * T, torch.randint(-2, k_max + 3, (T,), generator=g, device="cuda").tolist()):
+        k = torch.tensor(budgets, dtype=torch.int32, device="cuda")
+        ws.fill_(255)
+        B.moe_prism_timing_enable(True)
+        try:
+            out = B.moe_prism_layer(shape, x, w_r, bias, k, w_gu, w_dn, ws).clone()
+            torch.cuda.synchronize()
+            assert (B.moe_prism_timing_read()["topk"][1] == 0) == bool(picks)
+        finally:
+            B.moe_prism_timing_enable(False)
+        status = B.moe_prism_status(ws)
+        ids, wt, _ = B.moe_prism_route(shape, x, w_r, bias, k, ws, want_logits=True)
+        assert status[0] == B.moe_prism_status(ws)[0] == int(any(b < 0 or b > k_max for b in budgets))
+        _, off, sp, sl = B.moe_prism_dispatch(shape, ids, ws)
+        assert status[1] == B.moe_prism_status(ws)[1] == int(off[-1])
+        y = B.moe_prism_grouped_ffn(shape, x, w_gu, w_dn, off, sp, ws)
+        ref = B.moe_prism_combine(shape, y, sl, wt, k)
+        assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
