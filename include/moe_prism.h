@@ -319,7 +319,7 @@ MOE_PRISM_API int moe_prism_status(const void* ws, int32_t* host_flags, int32_t*
  * kernel inside a throughput measurement without event records around the rest.
  */
 #define MOE_PRISM_K_LOGITS 0
-#define MOE_PRISM_K_TOPK 1 /* not launched by the layer calls where K_FFN_GATE_UP picks for up to four tokens */
+#define MOE_PRISM_K_TOPK 1 /* not launched by the layer calls where K_FFN_GATE_UP picks for a few tokens */
 #define MOE_PRISM_K_DISPATCH_COUNT 2
 #define MOE_PRISM_K_DISPATCH_SCAN 3 /* not launched with few counts: the place kernel adds them up */
 #define MOE_PRISM_K_DISPATCH_PLACE 4

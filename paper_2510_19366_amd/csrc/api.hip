@@ -227,13 +227,10 @@ static int do_dispatch(const moe_prism_shape* s, const Layout& L, const int32_t*
 // of the layer calls: a combine follows, which the down projection of a few tokens does itself
 struct CombineArgs {
   const int32_t* slot_of_pair;
-  float* w;
+  const float* w;
   const int32_t* k_tok;
   void* out;
-  // the gate-up picks (ffn_picks) from these logits; or null
-  const SmallDispatch* picks = nullptr;
-  const float* logits = nullptr;
-  int32_t* ids = nullptr;
+  const PickArgs* picks = nullptr;  // the gate-up picks (ffn_picks)
 };
 static bool combines(const moe_prism_shape* s, const FfnPlan& p) {
   return s->dtype == MOE_PRISM_BF16 && ffn_down_combines(p.few, s->T, s->k_max, s->n_experts * s->n_sub, s->d, s->inter_sub);
@@ -266,9 +263,7 @@ static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, cons
   }
   if (combine != nullptr && combine->picks != nullptr)
     MP_LAUNCH(MOE_PRISM_K_FFN_GATE_UP,
-              launch_ffn_pick_gate_up(combine->logits, combine->k_tok, combine->ids, combine->w, hdr, s->renormalize, s->routed_scale,
-                                      *combine->picks, (const uint16_t*)x, (const uint16_t*)w_gu, (uint16_t*)h, s->T, s->d, s->inter_sub, E,
-                                      s->k_max, st));
+              launch_ffn_pick_gate_up(s->dtype, *combine->picks, x, w_gu, h, s->T, s->d, s->inter_sub, s->k_max, p.few, st));
   else
     MP_LAUNCH(MOE_PRISM_K_FFN_GATE_UP,
               launch_ffn_gate_up(s->dtype, x, w_gu, sorted_pair, tiles, hdr, h, s->T, s->d, s->inter_sub,
@@ -524,15 +519,16 @@ static int layer_on(const moe_prism_shape* shape, const Layout& L, const void* x
   const SmallDispatch small{cnt, off, sp, sl, reinterpret_cast<MTile*>(w8 + L.tiles), p.max_tiles, p.cut};
   const int E = shape->n_experts * shape->n_sub;
   const bool one = dispatch_is_small(shape->T, E, shape->k_max);
-  const bool later = one && shape->dtype == MOE_PRISM_BF16 && ffn_picks(p.few, shape->T, shape->k_max, E);  // by the gate-up itself
+  const bool later = one && ffn_picks(shape->dtype, p.few, shape->T, shape->k_max, E, shape->d, shape->inter_sub);  // by the gate-up itself
   float* logits = reinterpret_cast<float*>(w8 + L.logits);
+  const PickArgs picks{logits, k_tok, ids, w, reinterpret_cast<int32_t*>(w8 + L.hdr), E, shape->renormalize, shape->routed_scale, small};
   int rc = do_route(shape, L, x, w_router, router_bias, k_tok, ids, w, logits, w8, st, one ? &small : nullptr, !later);
   if (rc) return rc;
   if (!one) {
     rc = do_dispatch(shape, L, ids, cnt, off, sp, sl, w8, st, &p);
     if (rc) return rc;
   }
-  return ffn_and_combine(shape, L, x, w_gate_up, w_down, off, sp, w8, st, p, CombineArgs{sl, w, k_tok, out, later ? &small : nullptr, logits, ids});
+  return ffn_and_combine(shape, L, x, w_gate_up, w_down, off, sp, w8, st, p, CombineArgs{sl, w, k_tok, out, later ? &picks : nullptr});
 }
 
 int moe_prism_layer(const moe_prism_shape* shape, const void* x, const void* w_router,

@@ -216,6 +216,17 @@ struct SmallDispatch {
   int max_tiles;
   TileCut cut;
 };
+// where a kernel that picks for itself finds the logits, and what it leaves in place of the top-k kernel
+struct PickArgs {
+  const float* logits;
+  const int32_t* k_tok;
+  int32_t* ids;
+  float* w;
+  int32_t* hdr;
+  int E, renorm;
+  float scale;
+  SmallDispatch small;
+};
 __host__ __device__ inline size_t small_dispatch_lds(int T, int E) { return (size_t)E * ((T + 63) / 64) * 8 + (size_t)E * 4; }
 inline bool small_dispatch(int T, int E, int k_max) {
   return T > 0 && (T <= 64 || (T <= 128 ? (T - 64) * k_max <= 2560 : T < 256 && T * k_max <= 2048)) && small_dispatch_lds(T, E) <= 60 * 1024;

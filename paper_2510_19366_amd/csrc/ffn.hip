@@ -8,7 +8,9 @@
 // This file: the m-tile table and the fp32 path.  The bf16 kernels are in ffn_bf16.hip and
 // ffn_fused_bf16.hip.
 #include "chain_tile.h"
+#include "dispatch_common.h"
 #include "ffn_common.h"
+#include "topk_wave.h"
 
 namespace mp {
 
@@ -121,37 +123,160 @@ __device__ __forceinline__ void f32_tile(const float* a_base, const float* b_bas
   }, acc);
 }
 
-// SHORT: see row_blocks.h
-template <bool SHORT, class Body>
-__device__ __forceinline__ void f32_items(const MTile* __restrict__ tiles, const int32_t* __restrict__ hdr,
-                                          int n_tiles_n, int T, Body&& body) {
-  auto tile = [&](int m) { return tiles[m]; };
+// SHORT: see row_blocks.h.  tile: m-tile number m of n
+template <bool SHORT, class Tile, class Body>
+__device__ __forceinline__ void f32_items(Tile&& tile, int n, int block, int grid, int n_tiles_n, int T, Body&& body) {
   auto each = [&](const MTile& t, int blk, int nt) {
     body(t.g, t.row0 + blk * F32_ROWS, min(F32_ROWS, t.rows - blk * F32_ROWS), nt);
     __syncthreads();  // every wave has read the last stage before the ring is filled again
   };
   if constexpr (SHORT)
-    short_row_blocks<F32_ROWS>(blockIdx.x, gridDim.x, N_XCD, hdr[HDR_MTILES], n_tiles_n,
+    short_row_blocks<F32_ROWS>(block, grid, N_XCD, n, n_tiles_n,
                                min((T + F32_ROWS - 1) / F32_ROWS, F32_BLOCKS), tile, [](auto&& pred) { return lane_mask(pred); },
                                each);
   else
-    all_row_blocks<F32_ROWS, F32_BLOCKS>(blockIdx.x, gridDim.x, N_XCD, hdr[HDR_MTILES], n_tiles_n, tile, each);
+    all_row_blocks<F32_ROWS, F32_BLOCKS>(block, grid, N_XCD, n, n_tiles_n, tile, each);
+}
+
+// PICK (gate-up of up to 64 tokens, E <= 32, k_max picks): the route's picks and their dispatch belong to this launch.  Every
+// workgroup finds the picks of all tokens: a lane has a token, a wave eight sub-experts, and a sub-expert is picked if fewer
+// logits than the budget are larger, or equal with a lower id.  The first workgroups, a wave per token, only write what the
+// route and the dispatch leave in memory.  What it saves is the launch of the top-k kernel, which is longer than the 2 us of a
+// latency and 31 comparisons for each of eight sub-experts.  Layer calls of d = 256, 32 of 128, from a captured graph, top-k kernel |
+// this: 16 tokens 20.1 | 19.0 us, 32 21.9 | 19.7, 64 22.2 | 20.4; back to back, d = 1024, 32 of 256, 30 tokens 43.9 | 41.9, 60 43.9 | 42.4;
+// d = 2048, 32 of 704, 60 tokens 140.9 | 134.8.
+constexpr int PICK_T = 64, PICK_E = 32;
+struct F32Picks {
+  u64 masks[PICK_E];  // tokens that picked a sub-expert
+  int32_t row0[PICK_E];
+  MTile tiles[PICK_E];
+  uint8_t tokens[PICK_T * PICK_E];  // of the slot rows
+};
+// keys: PICK_T x (PICK_E + 1) words.  Returns the number of m-tiles; *rows: of slot rows.
+__device__ __forceinline__ int f32_find_picks(const PickArgs& a, F32Picks& s, int* keys, int T, int k_max, int* rows) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int EACH = PICK_E / 4, LD = PICK_T / 8;  // sub-experts of a wave; logits of a thread
+  const int asked = a.k_tok[min(lane, T - 1)];
+  auto token = [&](int q) { return wv * (PICK_T / 4) + q * 2 + (lane >> 5); };
+  float v[LD];
+#pragma unroll
+  for (int q = 0; q < LD; ++q) v[q] = a.logits[min(token(q), T - 1) * a.E + min(lane & 31, a.E - 1)];
+#pragma unroll
+  for (int q = 0; q < LD; ++q)  // absent ones are behind all others
+    keys[token(q) * (PICK_E + 1) + (lane & 31)] = (lane & 31) < a.E ? topk_key(v[q]) : INT32_MIN;
+  __syncthreads();
+  const int kt = lane < T ? min(max(asked, 0), k_max) : 0;
+  int key[PICK_E];  // of this lane's token, this wave's sub-experts first
+#pragma unroll
+  for (int j = 0; j < PICK_E; ++j) key[j] = keys[lane * (PICK_E + 1) + ((wv * EACH + j) & (PICK_E - 1))];
+#pragma unroll
+  for (int q = 0; q < EACH; ++q) {
+    int larger = 0;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int least = key[q] - (b > 0 && wv + b >= 4 ? 1 : 0);  // the ids of the blocks that wrap around are lower
+#pragma unroll
+      for (int j = b * EACH; j < (b + 1) * EACH; ++j) larger += b == 0 && j < q ? key[j] >= key[q] : key[j] > least;
+    }
+    const u64 m = __ballot(wv * EACH + q < a.E && larger < kt);
+    if (lane == 0) s.masks[wv * EACH + q] = m;
+  }
+  __syncthreads();
+  const int n = lane < PICK_E ? (int)__popcll(s.masks[lane]) : 0, incl = wave_scan(n), row0 = incl - n;
+  const u64 some = __ballot(n > 0);
+  if (wv == 0 && lane < PICK_E) s.row0[lane] = row0;
+  if (wv == 1 && n > 0) {
+    const int at = __builtin_amdgcn_mbcnt_hi((uint32_t)(some >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)some, 0));
+    s.tiles[at] = MTile{lane, row0, n, at, 1, {0, 0, 0}};
+  }
+#pragma unroll
+  for (int q = 0; q < EACH; ++q) {
+    const int e = wv * EACH + q;
+    const u64 m = s.masks[e];
+    const int at = __builtin_amdgcn_readlane(row0, e) +
+                   __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+    if (m >> lane & 1) s.tokens[at] = (uint8_t)lane;
+  }
+  __syncthreads();
+  *rows = __builtin_amdgcn_readlane(incl, 63);
+  return __popcll(some);
+}
+// workgroups that write: four tokens each, a whole number for each XCD
+__host__ __device__ constexpr int pick_writers(int T) { return ((T + 3) / 4 + N_XCD - 1) / N_XCD * N_XCD; }
+// what the top-k kernel leaves in memory: of token t, by a wave; the tables by the first workgroup
+__device__ __forceinline__ void f32_write_picks(const PickArgs& a, const F32Picks& s, int* scratch, int T, int k_max, int rows, int n_tiles) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, t = blockIdx.x * 4 + wv;
+  if (blockIdx.x == 0) {
+    if ((int)threadIdx.x < a.E) {
+      a.small.off[threadIdx.x] = s.row0[threadIdx.x];
+      a.small.cnt[threadIdx.x] = __popcll(s.masks[threadIdx.x]);
+    }
+    if ((int)threadIdx.x < n_tiles) a.small.tiles[threadIdx.x] = s.tiles[threadIdx.x];
+    if (threadIdx.x == 0) {
+      a.small.off[a.E] = rows;
+      write_counts(a.hdr, rows, n_tiles, true, a.small.max_tiles);
+    }
+  }
+  if (t >= T) return;
+  const int kp = topk_pad(k_max);
+  int* uk = scratch + wv * 4 * kp;  // as in the top-k kernel
+  float* se = reinterpret_cast<float*>(uk + 2 * kp);
+  int* sid = uk + 3 * kp;
+  const TopkPicks p = topk_token<1>(a.logits + (size_t)t * a.E, a.k_tok[t], a.E, k_max, a.renorm, &a.hdr[HDR_FLAGS], uk, uk + kp, se, sid);
+  for (int j = lane; j < k_max; j += 64) {
+    const int i = t * k_max + j;
+    const bool on = j < p.kt;
+    const int g = on ? sid[j] : -1;
+    int slot = -1;
+    if (on) {
+      slot = s.row0[g] + __popcll(s.masks[g] & ((1ull << t) - 1ull));
+      a.small.sorted_pair[slot] = i;
+    }
+    if (i >= rows) a.small.sorted_pair[i] = -1;  // tail beyond the valid slots
+    a.small.slot_of_pair[i] = slot;
+    a.ids[i] = g;
+    a.w[i] = on ? a.scale * expf(se[j] - p.most) / p.denom : 0.0f;
+  }
 }
 
 // NT = 2: a wave has 16 neurons' gate rows and the same neurons' up rows.  NT = 1: half of the chain per wave; the second
 // wave of a row has the up rows, and hands its sums over through LDS.
-template <bool WIDE, bool SHORT, int NT>
+template <bool WIDE, bool SHORT, int NT, class... Pick>
 __global__ __launch_bounds__(256) void ffn_gate_up_f32_kernel(
     const float* __restrict__ x, const float* __restrict__ w_gu,
     const int32_t* __restrict__ sorted_pair, const MTile* __restrict__ tiles,
-    const int32_t* __restrict__ hdr, float* __restrict__ h, int d, int Is, int k_max, int T) {
+    const int32_t* __restrict__ hdr, float* __restrict__ h, int d, int Is, int k_max, int T, Pick... pick) {
+  constexpr bool PICK = sizeof...(Pick) > 0;
+  static_assert(!PICK || (SHORT && !WIDE));
   extern __shared__ __align__(16) unsigned char f_smem[];
+  __shared__ std::conditional_t<PICK, F32Picks, int> picks;
   __shared__ f32x4_t ups[NT == 1 ? F32_UPS_BYTES / sizeof(f32x4_t) : 1];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, wm = wv >> 1, wn = wv & 1;
-  f32_items<SHORT>(tiles, hdr, Is / (16 * NT), T, [&](int g, int row0, int rows, int nt) {  // Is % 32 == 0
+  int n_m_tiles, first = 0;  // the first workgroup with items
+  if constexpr (PICK) {
+    const PickArgs& a = (pick, ...);
+    int n_rows;
+    n_m_tiles = f32_find_picks(a, picks, reinterpret_cast<int*>(f_smem), T, k_max, &n_rows);
+    first = pick_writers(T);
+    if ((int)blockIdx.x < first) {
+      f32_write_picks(a, picks, reinterpret_cast<int*>(f_smem), T, k_max, n_rows, n_m_tiles);
+      return;
+    }
+  } else {
+    n_m_tiles = hdr[HDR_MTILES];
+  }
+  auto tile = [&](int m) {
+    if constexpr (PICK) return picks.tiles[m];
+    else return tiles[m];
+  };
+  f32_items<SHORT>(tile, n_m_tiles, blockIdx.x - first, gridDim.x - first, Is / (16 * NT), T, [&](int g, int row0, int rows, int nt) {  // Is % 32 == 0
     f32x4_t acc[1][NT];
     f32_tile<WIDE, NT>(x, w_gu + (size_t)g * 2 * Is * d, d, [&](int row) -> size_t {
-      if (row < F32_ROWS) return min(max(sorted_pair[row0 + min(row, rows - 1)] / k_max, 0), T - 1);
+      if constexpr (PICK) {
+        if (row < F32_ROWS) return picks.tokens[row0 + min(row, rows - 1)];
+      } else {
+        if (row < F32_ROWS) return min(max(sorted_pair[row0 + min(row, rows - 1)] / k_max, 0), T - 1);
+      }
       const int b = row - F32_ROWS;
       return ((b >> 4) & 1 ? Is : 0) + nt * (16 * NT) + (b >> 5) * 16 + (b & 15);
     }, f_smem, acc);
@@ -181,7 +306,8 @@ __global__ __launch_bounds__(256) void ffn_down_f32_kernel(const float* __restri
   extern __shared__ __align__(16) unsigned char f_smem[];
   constexpr int NT = 2, COLS = F32Tile<NT>::BE;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, wm = wv >> 1, wn = wv & 1;
-  f32_items<SHORT>(tiles, hdr, d / COLS, T, [&](int g, int row0, int rows, int nt) {  // d % 64 == 0
+  auto tile = [&](int m) { return tiles[m]; };
+  f32_items<SHORT>(tile, hdr[HDR_MTILES], blockIdx.x, gridDim.x, d / COLS, T, [&](int g, int row0, int rows, int nt) {  // d % 64 == 0
     f32x4_t acc[1][NT];
     f32_tile<WIDE, NT>(h + (size_t)row0 * Is, w_dn + (size_t)g * d * Is, Is, [&](int row) -> size_t {
       return row < F32_ROWS ? min(row, rows - 1) : nt * COLS + row - F32_ROWS;
@@ -227,6 +353,8 @@ int ffn_f32_list(int T, int k_max, int E, int d, int Is) {
   return groups * (Is / 32) * cdiv(cdiv(pairs, E), F32_ROWS) <= 2L * num_cus() ? 1 : 2;
 }
 
+static bool f32_wide(int T, int d, int Is) { return (long)T * d >= (1L << 30) || (long)Is * d >= (1L << 29); }
+
 hipError_t launch_ffn_gate_up(int dtype, const void* x, const void* w_gu, const int32_t* sorted_pair,
                               const MTile* tiles, int32_t* hdr, void* h, int T, int d, int Is,
                               int k_max, int few, int max_mtiles, hipStream_t s) {
@@ -234,7 +362,7 @@ hipError_t launch_ffn_gate_up(int dtype, const void* x, const void* w_gu, const 
   if (dtype != 0)
     return launch_gate_up_bf16((const uint16_t*)x, (const uint16_t*)w_gu, sorted_pair, tiles, hdr,
                                (uint16_t*)h, T, d, Is, k_max, few, max_mtiles, s);
-  const bool wide = (long)T * d >= (1L << 30) || (long)Is * d >= (1L << 29);
+  const bool wide = f32_wide(T, d, Is);
   auto run = [&](auto* kern, int nt) {
     const int grid = persistent_grid((long)max_mtiles * F32_BLOCKS * (Is / (16 * nt)), nt == 1 ? F32_PER_CU<1> : F32_PER_CU<2>);
     const int lds = nt == 1 ? F32Tile<1>::LDS_BYTES : F32Tile<2>::LDS_BYTES;
@@ -265,6 +393,26 @@ hipError_t launch_ffn_down(int dtype, const void* h, const void* w_dn, const MTi
   auto* kern = few != 0 ? (wide ? ffn_down_f32_kernel<true, true> : ffn_down_f32_kernel<false, true>)
                             : (wide ? ffn_down_f32_kernel<true, false> : ffn_down_f32_kernel<false, false>);
   kern<<<grid, 256, F32Tile<2>::LDS_BYTES, s>>>((const float*)h, (const float*)w_dn, tiles, hdr, (float*)y, T, d, Is);
+  return hipGetLastError();
+}
+
+bool ffn_picks(int dtype, int few, int T, int k_max, int E, int d, int Is) {
+  if (dtype != 0) return picks_bf16(few, T, k_max, E);
+  return few != 0 && T >= 1 && T <= PICK_T && E <= PICK_E && !f32_wide(T, d, Is);
+}
+
+hipError_t launch_ffn_pick_gate_up(int dtype, const PickArgs& p, const void* x, const void* w_gu, void* h, int T, int d, int Is,
+                                   int k_max, int few, hipStream_t s) {
+  if (dtype != 0)
+    return launch_pick_gate_up_bf16(p, (const uint16_t*)x, (const uint16_t*)w_gu, (uint16_t*)h, T, d, Is, k_max, s);
+  auto run = [&](auto* kern, int nt) {
+    const long most = (long)T * k_max < p.E ? (long)T * k_max : p.E;  // groups
+    const int grid = persistent_grid(most * cdiv(T, F32_ROWS) * (Is / (16 * nt)), nt == 1 ? F32_PER_CU<1> : F32_PER_CU<2>);
+    const int lds = nt == 1 ? F32Tile<1>::LDS_BYTES : F32Tile<2>::LDS_BYTES;
+    kern<<<grid + pick_writers(T), 256, lds, s>>>((const float*)x, (const float*)w_gu, nullptr, nullptr, nullptr, (float*)h, d, Is, k_max, T, p);
+  };
+  if (few == 1) run(ffn_gate_up_f32_kernel<false, true, 1, PickArgs>, 1);
+  else run(ffn_gate_up_f32_kernel<false, true, 2, PickArgs>, 2);
   return hipGetLastError();
 }
 

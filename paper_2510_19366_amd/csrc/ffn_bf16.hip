@@ -939,16 +939,6 @@ struct Few {
 // 75.4 | 71.3; 64 x 2 of 704 x 2048, 1 31.1 | 27.9, 4 62.6 | 59.0; 8 x 4 of 3584 x 4096, 1 105.0 | 102.8; 512 of 128 x 256, 4 23.9 | 22.0.
 // With two tokens per wave 8 tokens of the first 61.0 | 59.8, but of the last 26.6 | 33.1: the first workgroup comes last.  (Where every
 // workgroup ranks its picks, which only the first one has to, one token 28.9.)
-struct PickArgs {
-  const float* logits;
-  const int32_t* k_tok;
-  int32_t* ids;
-  float* w;
-  int32_t* hdr;
-  int E, renorm;
-  float scale;
-  SmallDispatch small;
-};
 // The groups of the picks of T tokens, a bit per token and sub-expert in `takes` [token][element]: f(group, its place in the list, its
 // first row, its tokens as bits); returns the rows.  ALL: also the sub-experts that nobody took.
 template <int ELEMS, int TOKENS, bool ALL, class F>
@@ -1540,30 +1530,28 @@ int ffn_few_blocks(int T, int k_max, int E, int d, int Is, bool fused) {
   return T <= 64 || pairs <= 56L * E ? 4 : 0;
 }
 
-bool ffn_picks(int few, int T, int k_max, int E) { return few == 1 && T >= 1 && T <= 4 && k_max <= PICK_K && E <= 512; }
+bool picks_bf16(int few, int T, int k_max, int E) { return few == 1 && T >= 1 && T <= 4 && k_max <= PICK_K && E <= 512; }
 
-hipError_t launch_ffn_pick_gate_up(const float* logits, const int32_t* k_tok, int32_t* ids, float* w, int32_t* hdr, int renorm, float scale,
-                                   const SmallDispatch& small, const uint16_t* x, const uint16_t* w_gu, uint16_t* h, int T, int d,
-                                   int Is, int E, int k_max, hipStream_t s) {
-  const GateUpOp op{x, w_gu, small.sorted_pair, h, T, d, Is, k_max};
-  const PickArgs p{logits, k_tok, ids, w, hdr, E, renorm, scale, small};
+hipError_t launch_pick_gate_up_bf16(const PickArgs& p, const uint16_t* x, const uint16_t* w_gu, uint16_t* h, int T, int d, int Is, int k_max,
+                                    hipStream_t s) {
+  const GateUpOp op{x, w_gu, nullptr, h, T, d, Is, k_max};
   auto launch = [&](auto elems, auto tokens) {
     typedef Few<1, false, false, decltype(elems)::value, decltype(tokens)::value> F;
     constexpr auto Kern = ffn_few_kernel<GateUpOp, 1, false, false, decltype(elems)::value, decltype(tokens)::value, PickArgs>;
     hipError_t e = raise_lds_limit<Kern>(F::LDS_BYTES);
     if (e != hipSuccess) return e;
     const int ntn = cdiv(Is, F::N / GateUpOp::N_PER_ROW);
-    const long most = (long)T * k_max < E ? (long)T * k_max : E;  // groups
+    const long most = (long)T * k_max < p.E ? (long)T * k_max : p.E;  // groups
     const int grid = persistent_grid(most * ntn, F::PER_CU) + N_XCD;  // the first one writes, its neighbours have nothing to do
-    Kern<<<grid, F::THREADS, F::LDS_BYTES, s>>>(op, small.tiles, hdr, ntn, p);
+    Kern<<<grid, F::THREADS, F::LDS_BYTES, s>>>(op, nullptr, nullptr, ntn, p);
     return hipGetLastError();
   };
   auto of = [&](auto elems) {  // one token: a quarter of the looks at the picks, 0.6 us of 27.7
     return T == 1 ? launch(elems, std::integral_constant<int, 1>{}) : launch(elems, std::integral_constant<int, 4>{});
   };
-  if (E <= 64) return of(std::integral_constant<int, 1>{});
-  if (E <= 128) return of(std::integral_constant<int, 2>{});
-  if (E <= 256) return of(std::integral_constant<int, 4>{});
+  if (p.E <= 64) return of(std::integral_constant<int, 1>{});
+  if (p.E <= 128) return of(std::integral_constant<int, 2>{});
+  if (p.E <= 256) return of(std::integral_constant<int, 4>{});
   return of(std::integral_constant<int, 8>{});
 }
 

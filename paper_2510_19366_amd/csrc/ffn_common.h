@@ -57,4 +57,8 @@ hipError_t launch_down_bf16(const uint16_t* h, const uint16_t* w_dn, const MTile
                             int32_t* hdr, uint16_t* y, int T, int d, int Is, int few, int max_mtiles,
                             hipStream_t s);
 
+bool picks_bf16(int few, int T, int k_max, int E);
+hipError_t launch_pick_gate_up_bf16(const PickArgs& p, const uint16_t* x, const uint16_t* w_gu, uint16_t* h, int T, int d, int Is, int k_max,
+                                    hipStream_t s);
+
 }  // namespace mp

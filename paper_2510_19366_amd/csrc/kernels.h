@@ -85,11 +85,12 @@ hipError_t launch_ffn_down(int dtype, const void* h, const void* w_dn, const MTi
 // bf16: so few rows per sub-expert that the tiles of ffn_few_kernel are the faster ones: their blocks of 16 slot rows, or
 // 0.  fused: the fused kernel would run instead
 int ffn_few_blocks(int T, int k_max, int E, int d, int Is, bool fused);
-// the gate-up of up to four tokens that picks and dispatches for itself, in place of the top-k kernel (layer calls; few: of ffn_few_blocks)
-bool ffn_picks(int few, int T, int k_max, int E);
-hipError_t launch_ffn_pick_gate_up(const float* logits, const int32_t* k_tok, int32_t* ids, float* w, int32_t* hdr, int renorm, float scale,
-                                   const SmallDispatch& small, const uint16_t* x, const uint16_t* w_gu, uint16_t* h, int T, int d,
-                                   int Is, int E, int k_max, hipStream_t s);
+// the gate-up of a few tokens that picks and dispatches for itself, in place of the top-k kernel (layer calls; few: of ffn_few_blocks
+// or ffn_f32_list)
+struct PickArgs;
+bool ffn_picks(int dtype, int few, int T, int k_max, int E, int d, int Is);
+hipError_t launch_ffn_pick_gate_up(int dtype, const PickArgs& p, const void* x, const void* w_gu, void* h, int T, int d, int Is,
+                                   int k_max, int few, hipStream_t s);
 // the down projection of the few-rows tiles and the combine in one kernel, which leaves no y (layer calls; few: of ffn_few_blocks)
 bool ffn_down_combines(int few, int T, int k_max, int E, int d, int Is);
 hipError_t launch_ffn_down_combine(const uint16_t* h, const uint16_t* w_dn, const MTile* tiles, const int32_t* hdr,

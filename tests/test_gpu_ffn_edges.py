@@ -213,20 +213,24 @@ def test_down_projection_and_combine_in_one_kernel(T, N, S, k_max, d, Is, combin
     assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
 
 
-@pytest.mark.parametrize("T,E,k_max,d,Is,picks", [
-    (1, 1, 1, 64, 32, 1), (1, 64, 6, 512, 64, 1), (2, 65, 7, 448, 96, 1), (3, 128, 64, 576, 32, 1), (4, 129, 40, 1088, 64, 1),
-    (1, 256, 64, 2048, 192, 1), (4, 257, 33, 64, 192, 1), (1, 512, 32, 2048, 192, 1), (4, 512, 64, 1024, 128, 1),
-    (4, 512, 8, 320, 352, 1), (2, 512, 2, 1536, 32, 1),
-    (5, 512, 8, 320, 192, 0), (1, 513, 8, 320, 192, 0), (4, 128, 65, 320, 64, 0)])
+@pytest.mark.parametrize("dtype,T,E,k_max,d,Is,picks", [
+    ("bf16", 1, 1, 1, 64, 32, 1), ("bf16", 1, 64, 6, 512, 64, 1), ("bf16", 2, 65, 7, 448, 96, 1), ("bf16", 3, 128, 64, 576, 32, 1),
+    ("bf16", 4, 129, 40, 1088, 64, 1), ("bf16", 1, 256, 64, 2048, 192, 1), ("bf16", 4, 257, 33, 64, 192, 1),
+    ("bf16", 1, 512, 32, 2048, 192, 1), ("bf16", 4, 512, 64, 1024, 128, 1), ("bf16", 4, 512, 8, 320, 352, 1), ("bf16", 2, 512, 2, 1536, 32, 1),
+    ("bf16", 5, 512, 8, 320, 192, 0), ("bf16", 1, 513, 8, 320, 192, 0), ("bf16", 4, 128, 65, 320, 64, 0),
+    ("f32", 1, 1, 1, 64, 32, 1), ("f32", 2, 5, 5, 128, 96, 1), ("f32", 33, 31, 7, 192, 64, 1), ("f32", 64, 32, 8, 256, 128, 1),
+    ("f32", 64, 32, 32, 64, 32, 1), ("f32", 63, 9, 3, 320, 1184, 1),  # the last one: two column blocks per wave
+    ("f32", 65, 32, 8, 64, 32, 0), ("f32", 64, 33, 8, 64, 32, 0)])
 @pytest.mark.parametrize("renorm,ties", [(1, False), (0, False), (1, True)])
-def test_gate_up_that_picks_for_itself(T, E, k_max, d, Is, picks, renorm, ties):
+def test_gate_up_that_picks_for_itself(dtype, T, E, k_max, d, Is, picks, renorm, ties):
     # against the stage calls: the same picks, and from them the same sums, bit for bit.  Budgets of 0 to k_max, and of
     # outside of that, which the status reports; ties: logits of two values, so that the picks are the lowest ids
     g = torch.Generator(device="cuda").manual_seed(T * E + d)
-    shape = B.make_shape(T, d, E, 1, Is, k_max, "bf16", renorm, 1.5)
+    shape = B.make_shape(T, d, E, 1, Is, k_max, dtype, renorm, 1.5)
+    dt, bits = (torch.bfloat16, torch.int16) if dtype == "bf16" else (torch.float32, torch.int32)
 
     def normal(*size, std):
-        return torch.empty(size, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+        return torch.empty(size, dtype=dt, device="cuda").normal_(0.0, std, generator=g)
     x, w_r, w_gu, w_dn = normal(T, d, std=1.0), normal(E, d, std=0.02), normal(E, 2 * Is, d, std=0.05), normal(E, d, Is, std=0.05)
     bias = torch.empty(E, device="cuda").normal_(generator=g)
     if ties:
@@ -250,4 +254,4 @@ def test_gate_up_that_picks_for_itself(T, E, k_max, d, Is, picks, renorm, ties):
         assert status[1] == B.moe_prism_status(ws)[1] == int(off[-1])
         y = B.moe_prism_grouped_ffn(shape, x, w_gu, w_dn, off, sp, ws)
         ref = B.moe_prism_combine(shape, y, sl, wt, k)
-        assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
+        assert torch.equal(out.view(bits), ref.view(bits))
