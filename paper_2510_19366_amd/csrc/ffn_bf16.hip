@@ -1499,9 +1499,13 @@ static hipError_t launch_op(const Op& op, int T, int K, int n_cols, int few, int
 //     picks, groups are as long as the batch and the ring driver is ahead where that is many tiles of 64.  Layer calls of 400 |
 //     200 tokens, four | ring driver: 128 of 704 130 | 124, 89 | 91; 256 of 352 145 | 131, 96 | 103; 256 of 256 127 | 123, 89 |
 //     106; the same 400 without a bias 254 | 267, 261 | 290, 215 | 237;
-//   where the fused kernel is what else would run: it gives a tile a workgroup, and draws tiles in runs of 32 per XCD, so it
-//     wants long groups and more of them than CUs.  Layer calls, four layers in turn so that weights come from HBM,
-//     these | fused kernel; budgets of a quarter of the most and up; skewed: a bias N(0, 1) per expert, N(0, 3^2).
+//   where the fused kernel is what else would run: it gives a tile a workgroup, so it wants long groups and more of them than
+//     CUs.  Layer calls that find their weights in HBM, these | fused kernel, of 192 x 2048 unless said: 8 sub-experts, 4 picks, 100
+//     tokens 39 | 94; 32, 8 picks, 200 49 | 99; 128, 8 picks, 300 93 | 121, 880 114 | 127; 192, 8 picks, 1300 156 | 159; 256, 8 picks, 700 155 |
+//     176, of 128 120 | 141, of 64 85 | 100; 512, 32 picks, 200 262 | 291, 640 308 | 317, skewed 100 146 | 181, 300 195 | 244, 640 264 | 271, of 64 200
+//     101 | 152, of 192 x 1024 300 99 | 113, of 128 x 1024 81 | 93.
+//     The lines were drawn when its lists were runs of 32 tiles per XCD, the first XCDs before the others, which cost it most where
+//     tiles are few (up to 5 times, up to 192 sub-experts), and some per cent beyond.  Then, four layers in turn, these | fused kernel; budgets of a quarter of the most and up; skewed: a bias N(0, 1) per expert, N(0, 3^2).
 //     Up to 24 rows, any number of sub-experts, 8 of 192 x 2048: 24 35 | 552; 32: 12 39 | 493; 128: 12 86 | 169; 256: 5
 //     132 | 155, 24 151 | 165; 512: 1 130 | 155, 4 225 | 268, 10 249 | 288, 24 277 | 298, skewed 133 | 140, 168 | 229,
 //     219 | 273 and 75 | 112, 93 | 148, 134 | 164; 1024: 5 434 | 493, 24 525 | 564, but with N(0, 3^2) 219 | 193.  One pick
