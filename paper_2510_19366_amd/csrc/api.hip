@@ -341,7 +341,7 @@ static int do_route_proxy(const moe_prism_shape* s, const Layout& L, const void*
             launch_logits(s->dtype, x, w_router0, bias0, logits0, hdr, s->T, s->d, N, 1, nullptr, st));
   const FfnPlan p = plan_ffn(L, s->dtype, s->T, m, N, s->d, rows_half, false);
   const SmallDispatch small{q.cnt0, q.off0, q.sp0, q.sl0, tiles, p.max_tiles, p.cut};
-  const bool one = dispatch_is_small(s->T, N, m);
+  const bool one = topk_dispatches(s->T, N, m);
   MP_LAUNCH(MOE_PRISM_K_TOPK, launch_topk(logits0, nullptr, q.ids0, q.w0, hdr, s->T, N, m,
                                           s->renormalize, s->routed_scale, one ? &small : nullptr, st));
   if (!one) {
@@ -518,7 +518,7 @@ static int layer_on(const moe_prism_shape* shape, const Layout& L, const void* x
   const FfnPlan p = plan_ffn(L, shape);
   const SmallDispatch small{cnt, off, sp, sl, reinterpret_cast<MTile*>(w8 + L.tiles), p.max_tiles, p.cut};
   const int E = shape->n_experts * shape->n_sub;
-  const bool one = dispatch_is_small(shape->T, E, shape->k_max);
+  const bool one = topk_dispatches(shape->T, E, shape->k_max);
   const bool later = one && ffn_picks(shape->dtype, p.few, shape->T, shape->k_max, E, shape->d, shape->inter_sub);  // by the gate-up itself
   float* logits = reinterpret_cast<float*>(w8 + L.logits);
   const PickArgs picks{logits, k_tok, ids, w, reinterpret_cast<int32_t*>(w8 + L.hdr), E, shape->renormalize, shape->routed_scale, small};

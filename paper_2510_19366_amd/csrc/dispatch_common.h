@@ -1,5 +1,5 @@
 // The pieces of the dispatch stage (see dispatch.hip) that are also used where one workgroup does
-// all of it: for a small batch, at the end of the top-k kernel.  Workgroups of 256 threads.
+// all of it: for a small batch, at the end of the top-k kernel.  Workgroups of 256 threads, or more there.
 #pragma once
 #include "kernels.h"
 
@@ -13,8 +13,9 @@ constexpr int DISPATCH_THREADS = 256;
 // AGENT: the picks were stored at agent scope by other workgroups of this launch and are loaded likewise, past this CU's
 // and XCD's caches; else they are an earlier launch's.
 constexpr int PICKS = 8;
-template <bool AGENT>
+template <bool AGENT, int N_THREADS = DISPATCH_THREADS>
 struct Picks {
+  static constexpr int THREADS = N_THREADS;
   const int32_t* ids;
   int n, k_max;
   uint32_t inv;  // i / k_max = umulhi(i, inv): i k_max < 2^32 (at most 65536 or 256 k_max picks of k_max <= 1024)
@@ -26,23 +27,23 @@ struct Picks {
     at = first;
 #pragma unroll
     for (int u = 0; u < PICKS; ++u) {
-      const int i = first + u * DISPATCH_THREADS + (int)threadIdx.x;
-      if (first + u * DISPATCH_THREADS >= n) break;  // the same for all threads
+      const int i = first + u * THREADS + (int)threadIdx.x;
+      if (first + u * THREADS >= n) break;  // the same for all threads
       g[u] = i >= n ? -1 : AGENT ? __hip_atomic_load(ids + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ids[i];
     }
   }
   // f(index, sub-expert) for every pick of this thread; last to first if `back`, so that a batch is used twice
   template <class F>
   __device__ __forceinline__ void each(bool back, F&& f) {
-    constexpr int STEP = PICKS * DISPATCH_THREADS;
+    constexpr int STEP = PICKS * THREADS;
     const int batches = (n + STEP - 1) / STEP;
     for (int b = 0; b < batches; ++b) {
       const int first = (back ? batches - 1 - b : b) * STEP;
       load(first);
 #pragma unroll
       for (int u = 0; u < PICKS; ++u) {
-        const int i = first + u * DISPATCH_THREADS + (int)threadIdx.x;
-        if (first + u * DISPATCH_THREADS >= n) break;
+        const int i = first + u * THREADS + (int)threadIdx.x;
+        if (first + u * THREADS >= n) break;
         if (i < n) f(i, g[u]);
       }
     }
@@ -53,7 +54,7 @@ struct Picks {
 template <class Picks>
 __device__ __forceinline__ void build_masks(Picks& picks, u64* masks, int E, int W) {
   picks.load(0);
-  for (int i = threadIdx.x; i < E * W; i += DISPATCH_THREADS) masks[i] = 0ull;
+  for (int i = threadIdx.x; i < E * W; i += Picks::THREADS) masks[i] = 0ull;
   __syncthreads();
   picks.each(false, [&](int i, int g) {
     if (g >= 0 && g < E) {
@@ -281,16 +282,16 @@ __device__ __forceinline__ int small_groups(const SmallDispatch& a, int32_t* __r
   return P;
 }
 
-template <bool AGENT>
+template <bool AGENT, int THREADS = DISPATCH_THREADS>
 __device__ __forceinline__ void dispatch_one_workgroup(const int32_t* __restrict__ ids, const SmallDispatch& a,
                                                        int32_t* __restrict__ hdr, u64* lds,
                                                        int32_t* wave_tot, int T, int E, int k_max) {
   const int W = (T + 63) / 64;
   u64* masks = lds;
   int32_t* off_lds = reinterpret_cast<int32_t*>(masks + (size_t)E * W);
-  Picks<AGENT> picks(ids, T, k_max);
+  Picks<AGENT, THREADS> picks(ids, T, k_max);
   build_masks(picks, masks, E, W);
-  const int P = small_groups(a, hdr, masks, off_lds, wave_tot, W, E, DISPATCH_THREADS);
+  const int P = small_groups(a, hdr, masks, off_lds, wave_tot, W, E, THREADS);
   __syncthreads();
   place_pairs(picks, masks, [&](int g) { return off_lds[g]; }, a.sorted_pair, a.slot_of_pair, 0, P, E, W);
 }

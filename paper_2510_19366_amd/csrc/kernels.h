@@ -42,7 +42,8 @@ hipError_t launch_expand_k(int R, int T, const int32_t* req_k, const int32_t* re
 // S: sub-experts of an expert, whose rows of w may be equal; differ: scratch of E / S words (not used with S = 1)
 hipError_t launch_logits(int dtype, const void* x, const void* w, const float* bias, float* logits,
                          int32_t* hdr, int T, int d, int E, int S, int32_t* differ, hipStream_t s);
-// with `small` (only where dispatch_is_small): the kernel also dispatches its picks
+// with `small` (only where topk_dispatches): the kernel also dispatches its picks
+bool topk_dispatches(int T, int E, int k_max);
 struct MTile;
 struct SmallDispatch;
 hipError_t launch_topk(const float* logits, const int32_t* k_tok, int32_t* ids, float* w,

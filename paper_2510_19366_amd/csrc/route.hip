@@ -212,14 +212,14 @@ constexpr int TOPK_WAVES = 4;
 //   SOLO: one workgroup of up to 16 waves has all tokens, and dispatches their picks from LDS.
 enum { TOPK_ONLY, TOPK_LAST, TOPK_SOLO };
 constexpr int SOLO_WAVES = 16;
-template <int ELEMS, int MODE>
-__global__ __launch_bounds__(64 * (MODE == TOPK_SOLO ? SOLO_WAVES : TOPK_WAVES)) void topk_kernel(
+template <int ELEMS, int MODE, int WAVES = TOPK_WAVES>
+__global__ __launch_bounds__(64 * (MODE == TOPK_SOLO ? SOLO_WAVES : WAVES)) void topk_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ k_tok, int32_t* __restrict__ ids,
     float* __restrict__ wout, int32_t* __restrict__ hdr, int T, int E, int k_max, int renorm,
     float scale, SmallDispatch small) {
   extern __shared__ __align__(16) unsigned char topk_smem[];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int t = MODE == TOPK_SOLO ? wv : blockIdx.x * TOPK_WAVES + wv;
+  const int t = MODE == TOPK_SOLO ? wv : blockIdx.x * WAVES + wv;
   // per wave: keys and ids of the picks in id order, then logits and ids in pick order
   const int kp = topk_pad(k_max);
   int* uk = reinterpret_cast<int*>(topk_smem) + (size_t)wv * 4 * kp;
@@ -278,18 +278,33 @@ __global__ __launch_bounds__(64 * (MODE == TOPK_SOLO ? SOLO_WAVES : TOPK_WAVES))
     if (threadIdx.x == 0) *is_last = atomicAdd(&hdr[HDR_TOPK_DONE], 1) == (int)gridDim.x - 1;
     __syncthreads();
     if (!*is_last) return;
-    dispatch_one_workgroup<true>(ids, small, hdr, reinterpret_cast<u64*>(topk_smem), wave_tot, T, E, k_max);
+    dispatch_one_workgroup<true, 64 * WAVES>(ids, small, hdr, reinterpret_cast<u64*>(topk_smem), wave_tot, T, E, k_max);
   }
+}
+
+// TOPK_LAST has eight waves where their picks fit the default 64 KiB of LDS: four, which the general top-k has, take twice as long
+// to dispatch (masks, groups and places of 3200 pairs 7.7 of the kernel's 13.4 us), and sixteen get in each other's way at the
+// picks.  Layer calls back to back, us, four waves | eight | sixteen: 512 sub-experts of 32 picks, 37 tokens 105.3 | 104.5 | 106.1, 64 122.6 |
+// 121.7 | 123.1, 100 143.1 | 140.3 | 141.3; 256 of 24, 100 tokens 226.4 | 224.7 | 224.9; fp32, 32 of 8, 250 29.6 | 27.9 | 28.2; 2048 of 8, d = 256, 120
+// 37.6 | 34.5 | 34.5.
+constexpr int LAST_WAVES = 8;
+static bool wide_last(int k_max) { return (size_t)LAST_WAVES * 4 * topk_pad(k_max) * sizeof(float) <= 60 * 1024; }
+// So with eight waves the last workgroup is ahead of count and place kernels for more pairs than one of four (small_dispatch, which the
+// stage call goes by).  Layer calls, one workgroup | count and place kernels, by the pairs beyond those of 64 tokens: 512 of 32 picks 120
+// tokens (1792) 145.1 | 150.9, 160 (3072) 160.8 | 165.5, 200 (4352) 173.3 | 175.4, 255 (6112) 179.9 | 179.2; 256 of 32, 160 186.0 | 190.5, 220 (4992)
+// 207.1 | 207.7; 64 of 64, d = 256, 100 (2304) 40.0 | 46.3, 200 (8704) 50.4 | 48.9; 1024 of 24, 200 (3264) 50.8 | 52.7; 128 of 12, 130 216.7 | 222.5, 255
+// (2292) 223.1 | 227.2; fp32, 32 of 8, 140 25.6 | 29.4, 250 28.1 | 31.4.
+bool topk_dispatches(int T, int E, int k_max) {
+  return small_dispatch(T, E, k_max) ||
+         (T > 0 && T < 256 && (T - 64) * k_max <= 4608 && wide_last(k_max) && small_dispatch_lds(T, E) <= 60 * 1024);
 }
 
 hipError_t launch_topk(const float* logits, const int32_t* k_tok, int32_t* ids, float* w,
                        int32_t* hdr, int T, int E, int k_max, int renorm, float scale,
                        const SmallDispatch* small, hipStream_t s) {
   if (T == 0) return hipSuccess;
-  static_assert(64 * TOPK_WAVES == DISPATCH_THREADS, "the same workgroup does both");
-  dim3 grid(cdiv(T, TOPK_WAVES)), block(64 * TOPK_WAVES);
+  static_assert(64 * TOPK_WAVES == DISPATCH_THREADS, "what small_dispatch was drawn for");
   const size_t sh_wave = (size_t)4 * topk_pad(k_max) * sizeof(float);
-  size_t sh = TOPK_WAVES * sh_wave;
   const int elems = cdiv(E, 64);
   // One workgroup saves the count and the reading back of the picks; 16 waves have registers for 16 logits per lane.
   // Layer calls of 1 | 4 | 8 | 12 | 16 tokens from a captured graph, 128 x 4 sub-experts: 38.1 | 52.4 | 65.2 | 79.4 | 85.5 us, with
@@ -299,7 +314,10 @@ hipError_t launch_topk(const float* logits, const int32_t* k_tok, int32_t* ids, 
   const int solo_waves = T < TOPK_WAVES ? TOPK_WAVES : T;
   const size_t sh_solo = solo_waves * sh_wave + (size_t)E * 12 + SOLO_WAVES * sizeof(int32_t);
   const bool solo = small != nullptr && T <= SOLO_WAVES && elems <= 16 && sh_solo <= 60 * 1024;
-  const size_t sh_small = small_dispatch_lds(T, E) + (1 + DISPATCH_THREADS / 64) * sizeof(int32_t);  // the last flag and wave_tot
+  const int waves = !small || solo || !wide_last(k_max) ? TOPK_WAVES : LAST_WAVES;
+  const size_t sh_small = small_dispatch_lds(T, E) + (1 + waves) * sizeof(int32_t);  // the last flag and wave_tot
+  dim3 grid(cdiv(T, waves)), block(64 * waves);
+  size_t sh = waves * sh_wave;
   if (solo) {
     sh = sh_solo;
     grid = dim3(1);
@@ -308,12 +326,13 @@ hipError_t launch_topk(const float* logits, const int32_t* k_tok, int32_t* ids, 
     sh = sh_small;
   }
   const SmallDispatch sd = small != nullptr ? *small : SmallDispatch{};
-#define MP_TOPK_MODE(N, MODE) \
-  topk_kernel<N, MODE><<<grid, block, sh, s>>>(logits, k_tok, ids, w, hdr, T, E, k_max, renorm, scale, sd)
+#define MP_TOPK_MODE(N, ...) \
+  topk_kernel<N, __VA_ARGS__><<<grid, block, sh, s>>>(logits, k_tok, ids, w, hdr, T, E, k_max, renorm, scale, sd)
 #define MP_TOPK(N)                                                           \
   do {                                                                       \
     if (small == nullptr) MP_TOPK_MODE(N, TOPK_ONLY);                        \
     else if (solo && N <= 16) MP_TOPK_MODE((N <= 16 ? N : 16), TOPK_SOLO);   \
+    else if (waves == LAST_WAVES) MP_TOPK_MODE(N, TOPK_LAST, LAST_WAVES);    \
     else MP_TOPK_MODE(N, TOPK_LAST);                                         \
   } while (0)
   if (elems <= 1) MP_TOPK(1);

@@ -190,3 +190,33 @@ def test_logits_of_every_tile_and_count_of_stages(T, E, d, dtype):
     ref = x.double() @ w.double().T
     assert torch.equal(lg.double(), ref)
     assert torch.equal(lg.gather(1, ids[:, :1].long()), lg.max(dim=1, keepdim=True).values)
+
+
+@pytest.mark.parametrize("T,E,k_max,one", [
+    (128, 64, 64, 1), (136, 64, 64, 1), (137, 64, 64, 0), (255, 512, 24, 1), (255, 512, 25, 0), (256, 64, 1, 0),  # 4608 pairs, 255 tokens
+    (90, 1024, 177, 1), (90, 1024, 178, 0), (65, 1024, 480, 1), (73, 512, 480, 1), (66, 512, 512, 1), (80, 512, 481, 0),  # eight waves, four
+    (200, 1706, 3, 1), (200, 1707, 3, 0), (40, 4096, 8, 1)])  # 60 KiB of masks
+def test_layer_batches_that_the_top_k_kernel_dispatches(T, E, k_max, one):
+    # against the stage calls, whose own rules and kernels are others; skewed, budgets of 0 to k_max
+    d, Is = 64, 32
+    g = torch.Generator(device="cuda").manual_seed(T + E + k_max)
+    shape = B.make_shape(T, d, E, 1, Is, k_max, "f32", 1, 1.0)
+
+    def normal(*size, std):
+        return torch.empty(size, device="cuda").normal_(0.0, std, generator=g)
+    x, w_r, w_gu, w_dn = normal(T, d, std=1.0), normal(E, d, std=0.02), normal(E, 2 * Is, d, std=0.1), normal(E, d, Is, std=0.1)
+    bias = normal(E, std=1.0)
+    k = torch.randint(0, k_max + 1, (T,), generator=g, device="cuda", dtype=torch.int32)
+    ws = B.alloc_workspace(shape)
+    B.moe_prism_timing_enable(True)
+    try:
+        out = B.moe_prism_layer(shape, x, w_r, bias, k, w_gu, w_dn, ws).clone()
+        torch.cuda.synchronize()
+        calls = {name: v[1] for name, v in B.moe_prism_timing_read().items()}
+    finally:
+        B.moe_prism_timing_enable(False)
+    assert calls["dispatch_place"] == 1 - one
+    ids, wt, _ = B.moe_prism_route(shape, x, w_r, bias, k, ws, want_logits=True)
+    _, off, sp, sl = B.moe_prism_dispatch(shape, ids, ws)
+    y = B.moe_prism_grouped_ffn(shape, x, w_gu, w_dn, off, sp, ws)
+    assert torch.equal(out, B.moe_prism_combine(shape, y, sl, wt, k))
