@@ -209,9 +209,9 @@ hipError_t launch_logits(int dtype, const void* x, const void* w, const float* b
 constexpr int TOPK_WAVES = 4;
 // What follows the picks of a small batch in the same launch.
 //   LAST: the last workgroup to finish dispatches the picks of all T tokens, which it reads back.
-//   SOLO: one workgroup of up to 16 waves has all tokens, and dispatches their picks from LDS.
+//   SOLO: one workgroup of up to 8 waves has all tokens, and dispatches their picks from LDS.
 enum { TOPK_ONLY, TOPK_LAST, TOPK_SOLO };
-constexpr int SOLO_WAVES = 16;
+constexpr int SOLO_WAVES = 8;
 template <int ELEMS, int MODE, int WAVES = TOPK_WAVES>
 __global__ __launch_bounds__(64 * (MODE == TOPK_SOLO ? SOLO_WAVES : WAVES)) void topk_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ k_tok, int32_t* __restrict__ ids,
@@ -306,11 +306,10 @@ hipError_t launch_topk(const float* logits, const int32_t* k_tok, int32_t* ids, 
   static_assert(64 * TOPK_WAVES == DISPATCH_THREADS, "what small_dispatch was drawn for");
   const size_t sh_wave = (size_t)4 * topk_pad(k_max) * sizeof(float);
   const int elems = cdiv(E, 64);
-  // One workgroup saves the count and the reading back of the picks; 16 waves have registers for 16 logits per lane.
-  // Layer calls of 1 | 4 | 8 | 12 | 16 tokens from a captured graph, 128 x 4 sub-experts: 38.1 | 52.4 | 65.2 | 79.4 | 85.5 us, with
-  // the last of several workgroups 39.2 | 53.6 | 65.8 | 79.3 | 85.3; fp32, 8 x 4 of 128: 18.0 | 19.7 | 20.2 | 20.6 | 22.2, 19.0 |
-  // 20.7 | 21.4 | 21.3 | 21.9; d = 64, 256 x 4, 8 picks 18.6 | 19.6 | 20.7 | 21.5 | 23.0, 20.1 | 21.3 | 22.0 | 21.8 | 22.3.  From 12 to
-  // 16 tokens they are even.
+  // One workgroup saves the count and the reading back of the picks, but its waves are in each other's way.  Layer calls back to
+  // back, us, one workgroup | the last of several of eight waves: 512 sub-experts of 32 picks, 5 tokens 52.9 | 53.5, 8 60.9 | 61.7, 10 65.9 |
+  // 65.8, 12 74.7 | 74.3, 16 79.9 | 79.1; 256 of 32, 8 83.2 | 84.4, 12 106.2 | 105.8, 16 126.7 | 125.8; 128 of 12, 8 88.1 | 89.2, 12 124.1 | 124.2,
+  // 16 151.7 | 151.5; 1024 of 24, d = 256, 4 23.7 | 24.2, 8 23.9 | 24.8, 12 27.4 | 26.1, 16 29.4 | 27.7; fp32, 64 of 8, 8 21.7 | 22.0, 16 22.3 | 22.1.
   const int solo_waves = T < TOPK_WAVES ? TOPK_WAVES : T;
   const size_t sh_solo = solo_waves * sh_wave + (size_t)E * 12 + SOLO_WAVES * sizeof(int32_t);
   const bool solo = small != nullptr && T <= SOLO_WAVES && elems <= 16 && sh_solo <= 60 * 1024;
