@@ -26,7 +26,7 @@ int dispatch_chunk_words(int E, int T) {
   return w;
 }
 
-__global__ __launch_bounds__(256) void dispatch_count_kernel(const int32_t* __restrict__ ids,
+__global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_count_kernel(const int32_t* __restrict__ ids,
                                                              int32_t* __restrict__ chunk_cnt, int T,
                                                              int E, int W, int k_max) {
   extern __shared__ u64 masks[];
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void dispatch_scan_kernel(int32_t* __
 constexpr long SUM_COUNTS = 16384;
 bool dispatch_sums(int T, int E) {
   const int nch = cdiv(T, 64 * dispatch_chunk_words(E, T));
-  return T > 0 && E % 4 == 0 && E <= 4 * DISPATCH_THREADS && nch <= 256 && (long)nch * E <= SUM_COUNTS;
+  return T > 0 && E % 4 == 0 && E <= 1024 && nch <= 256 && (long)nch * E <= SUM_COUNTS;
 }
 // tot[g], before[g] (LDS): rows of group g in all chunks and in those before c
 __device__ __forceinline__ void sum_counts(const int32_t* __restrict__ chunk_cnt, int32_t* tot, int32_t* before, int c,
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_place_kernel(
     int32_t* __restrict__ sorted_pair, int32_t* __restrict__ slot_of_pair,
     MTile* __restrict__ tiles, int max_tiles, TileCut cut, int T, int E, int W, int k_max) {
   extern __shared__ u64 masks[];  // E * W masks, then E + 1 offsets, then E + 1 first-tile indices; SUM: then 2 E sums
-  __shared__ GroupScan wave_tot[4];
+  __shared__ GroupScan wave_tot[DISPATCH_THREADS / 64];
   int32_t* off_lds = reinterpret_cast<int32_t*>(masks + (size_t)E * W);
   int32_t* first_lds = off_lds + E + 1;
   const int c = blockIdx.x, t0 = c * 64 * W;
@@ -182,19 +182,21 @@ __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_place_kernel(
               slot_of_pair, (size_t)t0 * k_max, off_lds[E], E, W);
 }
 
-__global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_small_kernel(const int32_t* __restrict__ ids,
-                                                                          SmallDispatch a,
-                                                                          int32_t* __restrict__ hdr, int T,
-                                                                          int E, int k_max) {
+// Stage calls between HIP events, 256 threads | 512 | 1024, us: 4 tokens of 32 picks 6.6 | 6.5 | 6.3, 64 8.7 | 6.9 | 6.7, 64 of 64 12.9 | 8.9 | 8.4,
+// 100 of 71 19.6 | 12.4 | 10.3, 128 of 40 15.4 | 10.6 | 9.0, 255 of 8 10.0 | 7.8 | 7.4, 65 of 200 30.7 | 18.8 | 14.9; the gate-less layer of 100
+// tokens, whose picks it dispatches, 251 | 246.6.
+constexpr int SMALL_THREADS = 1024;
+__global__ __launch_bounds__(SMALL_THREADS) void dispatch_small_kernel(const int32_t* __restrict__ ids, SmallDispatch a,
+                                                                       int32_t* __restrict__ hdr, int T, int E, int k_max) {
   extern __shared__ u64 masks[];
-  __shared__ int32_t wave_tot[DISPATCH_THREADS / 64];
-  dispatch_one_workgroup<false>(ids, a, hdr, masks, wave_tot, T, E, k_max);
+  __shared__ int32_t wave_tot[SMALL_THREADS / 64];
+  dispatch_one_workgroup<false, SMALL_THREADS>(ids, a, hdr, masks, wave_tot, T, E, k_max);
 }
 
 hipError_t launch_dispatch_small(const int32_t* ids, int32_t* cnt, int32_t* off, int32_t* hdr,
                                  int32_t* sorted_pair, int32_t* slot_of_pair, MTile* tiles,
                                  int max_tiles, TileCut cut, int T, int E, int k_max, hipStream_t s) {
-  dispatch_small_kernel<<<1, DISPATCH_THREADS, small_dispatch_lds(T, E), s>>>(
+  dispatch_small_kernel<<<1, SMALL_THREADS, small_dispatch_lds(T, E), s>>>(
       ids, SmallDispatch{cnt, off, sorted_pair, slot_of_pair, tiles, max_tiles, cut}, hdr, T, E, k_max);
   return hipGetLastError();
 }
@@ -206,7 +208,7 @@ hipError_t launch_dispatch_count(const int32_t* ids, int32_t* chunk_cnt, int T, 
   if (T == 0) return hipSuccess;
   int W = dispatch_chunk_words(E, T);
   int nch = cdiv(T, 64 * W);
-  dispatch_count_kernel<<<nch, 256, (size_t)E * W * 8, s>>>(ids, chunk_cnt, T, E, W, k_max);
+  dispatch_count_kernel<<<nch, DISPATCH_THREADS, (size_t)E * W * 8, s>>>(ids, chunk_cnt, T, E, W, k_max);
   return hipGetLastError();
 }
 

@@ -1,12 +1,15 @@
 // The pieces of the dispatch stage (see dispatch.hip) that are also used where one workgroup does
-// all of it: for a small batch, at the end of the top-k kernel.  Workgroups of 256 threads, or more there.
+// all of it: for a small batch, at the end of the top-k kernel.
 #pragma once
 #include "kernels.h"
 
 namespace mp {
 
 typedef unsigned long long u64;
-constexpr int DISPATCH_THREADS = 256;
+// Of the count and place kernels: a chunk of 64 tokens has some 1300 picks, whose masks and places are chains of LDS latencies.
+// Place kernel between HIP events, 256 threads | 512 | 1024, us: 300 tokens of 32 picks out of 512 11.0 | 9.8 | 10.2, 3000 11.1 | 9.3 | 9.6, 6007 of 24
+// out of 256 9.9 | 8.8 | 9.3, 400 of 32 out of 256 10.4 | 9.4 | 9.7, 8192 of 12 out of 128 9.7 | 9.3 | 10.2, 1000 of 8 out of 32 7.5 | 7.5 | 8.6.
+constexpr int DISPATCH_THREADS = 512;
 
 // The picks of a run of tokens, PICKS per thread at a time, so that a memory latency is paid once per batch and not
 // once per pick; the last batch loaded stays in registers.
@@ -76,10 +79,10 @@ __device__ __forceinline__ int wave_scan(int v) {
   return v;
 }
 
-// Exclusive prefixes over the groups by one workgroup of 256 threads, into LDS: off_lds[0..E]
+// Exclusive prefixes over the groups by one workgroup, into LDS: off_lds[0..E]
 // of the row counts cnt(g) (off_lds[E] = P) and first_lds[0..E] of the m-tile counts; in a table with the long tiles first
 // (cut.sorted) without the groups' last tiles, which are written to `last` (a table of max_tiles; null: by another
-// workgroup).  Returns the number of m-tiles.  A thread sums a run of consecutive groups, the 256 partial sums are scanned, the run is walked again.
+// workgroup).  Returns the number of m-tiles.  A thread sums a run of consecutive groups, the partial sums are scanned, the run is walked again.
 struct GroupScan {
   int32_t rows, tiles;
   LastTiles last;
@@ -88,7 +91,7 @@ template <class Cnt>
 __device__ __forceinline__ int group_offsets(Cnt cnt, int32_t* off_lds, int32_t* first_lds, GroupScan* wave_tot,
                                              const TileCut& cut, int E, MTile* last, int max_tiles) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int per = (E + 255) / 256, lo = min(tid * per, E), hi = min(lo + per, E);
+  const int per = (E + DISPATCH_THREADS - 1) / DISPATCH_THREADS, lo = min(tid * per, E), hi = min(lo + per, E);
   GroupScan mine{0, 0, {}};
   for (int g = lo; g < hi; ++g) {
     const int n = cnt(g);
@@ -107,7 +110,7 @@ __device__ __forceinline__ int group_offsets(Cnt cnt, int32_t* off_lds, int32_t*
   for (int i = 0; i < 4; ++i) run.last.n[i] -= mine.last.n[i];
   __syncthreads();
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
+  for (int w = 0; w < DISPATCH_THREADS / 64; ++w) {
     const GroupScan t = wave_tot[w];
     const bool before = w < wv;
     run.rows += before ? t.rows : 0;
@@ -135,7 +138,7 @@ __device__ __forceinline__ int group_offsets(Cnt cnt, int32_t* off_lds, int32_t*
     }
     run.rows += n;
   }
-  if (tid == 255) {  // lo == hi == E for the threads past the last group
+  if (tid == DISPATCH_THREADS - 1) {  // lo == hi == E for the threads past the last group
     off_lds[E] = run.rows;
     first_lds[E] = first;
   }

@@ -303,7 +303,6 @@ hipError_t launch_topk(const float* logits, const int32_t* k_tok, int32_t* ids, 
                        int32_t* hdr, int T, int E, int k_max, int renorm, float scale,
                        const SmallDispatch* small, hipStream_t s) {
   if (T == 0) return hipSuccess;
-  static_assert(64 * TOPK_WAVES == DISPATCH_THREADS, "what small_dispatch was drawn for");
   const size_t sh_wave = (size_t)4 * topk_pad(k_max) * sizeof(float);
   const int elems = cdiv(E, 64);
   // One workgroup saves the count and the reading back of the picks, but its waves are in each other's way.  Layer calls back to
