@@ -271,7 +271,7 @@ static int do_ffn(const moe_prism_shape* s, const Layout& L, const void* x, cons
   if (combine != nullptr && combines(s, p)) {
     MP_LAUNCH(MOE_PRISM_K_FFN_DOWN,
               launch_ffn_down_combine((const uint16_t*)h, (const uint16_t*)w_dn, tiles, hdr, p.max_tiles, combine->slot_of_pair,
-                                      combine->w, combine->k_tok, (uint16_t*)combine->out, p.few, s->T, s->d, s->inter_sub, E, s->k_max, st));
+                                      combine->w, combine->k_tok, (uint16_t*)y, (uint16_t*)combine->out, s->T, s->d, s->inter_sub, s->k_max, st));
     return MOE_PRISM_OK;
   }
   MP_LAUNCH(MOE_PRISM_K_FFN_DOWN, launch_ffn_down(s->dtype, h, w_dn, tiles, hdr, y, s->T, s->d,

@@ -1215,13 +1215,13 @@ __global__ __launch_bounds__((Few<MOST, SHORT, NARROW, ELEMS, TOKENS>::THREADS))
 }
 
 // ---------------------------------------------------------------- down projection and combine of a few tokens
-// A workgroup has 8 or 16 columns of the output and all slot rows: y of them stays in LDS, and the picks of a token are
+// A workgroup has 8 or 16 columns of the output and all slot rows: y of them is kept in LDS, and the picks of a token are
 // added behind one barrier, in the combine's order.  The m-tiles are cut into blocks of 16 slot rows for 16 columns.  For 8
 // columns they are blocks of 8 rows, and a wave multiplies two of them at a time: weight rows 0 .. 7 of the matrix instruction
 // are the columns of one block's sub-expert, 8 .. 15 of the other's, and so are the slot rows; what it makes of one's weights
 // and the other's rows is dropped.  Weights and slot rows share the stages of a ring that is the wave's own.
 // Bound by the weights' bytes, as ffn_few_kernel is, and by one launch's latency; what it saves is the combine's launch, 3 us of
-// a call, and y's way through memory.  Layer calls that find their weights in HBM, us, two kernels | this one: 128 x 4
+// a call, and y's way back from memory.  Layer calls that find their weights in HBM, us, two kernels | this one: 128 x 4
 // sub-experts of 192 x 2048, 8 to 32 picks, skewed: 1 token 32.9 | 30.6, 4 46.7 | 44.8, 16 78.2 | 75.5, 37 100.9 | 96.9, 64 119 | 117; of 64 x
 // 2048 20 tokens 82.2 | 73.6, 60 111 | 97; 64 x 4 of 256 x 2048 20 tokens 149.3 | 140.4; 64 x 2 of 704 x 2048 40 tokens 207 | 205; 8 x 4 of 3584 x 4096 1 token
 // 104.8 | 99.8, 47 513 | 491; 32 x 4 of 256 x 3072 60 tokens 126.4 | 120.8.  (Pairs of m-tiles instead of blocks dealt to the waves: 37 tokens
@@ -1248,7 +1248,7 @@ template <int COLUMNS, int SLOTS, int STAGES>  // STAGES: of K, or 0: any number
 __global__ __launch_bounds__((DownCombine<COLUMNS, SLOTS>::THREADS)) void ffn_down_combine_kernel(
     const uint16_t* __restrict__ h, const uint16_t* __restrict__ w_dn, const MTile* __restrict__ tiles,
     const int32_t* __restrict__ hdr, int max_tiles, const int32_t* __restrict__ slot_of_pair, const float* __restrict__ w,
-    const int32_t* __restrict__ k_tok, uint16_t* __restrict__ out, int T, int d, int Is, int k_max) {
+    const int32_t* __restrict__ k_tok, uint16_t* __restrict__ y, uint16_t* __restrict__ out, int T, int d, int Is, int k_max) {
   typedef DownCombine<COLUMNS, SLOTS> D;
   extern __shared__ __align__(16) unsigned char dc_smem[];
   __shared__ int sums[D::WAVES];
@@ -1275,7 +1275,7 @@ __global__ __launch_bounds__((DownCombine<COLUMNS, SLOTS>::THREADS)) void ffn_do
     slot[i] = slot_of_pair[at];
     weight[i] = w[at];
   }
-  const int n_tiles = uni(hdr[HDR_MTILES]);
+  const int n_tiles = uni(hdr[HDR_MTILES]), n_slots = uni(hdr[HDR_PAIRS]);
 #pragma unroll
   for (int i = 0; i < D::PER_THREAD; ++i) {
     const int at = (int)threadIdx.x + i * D::THREADS;
@@ -1400,6 +1400,15 @@ __global__ __launch_bounds__((DownCombine<COLUMNS, SLOTS>::THREADS)) void ffn_do
           make_uint2(pack2(acc[0], acc[1]), pack2(acc[2], acc[3]));
   }
   __syncthreads();
+  // y is one of the layer's intermediates, so it is left in memory too.  These stores are on their way during the sums below; among
+  // the copies of the loop above they make its waits stricter.  Layer calls without y | with it | from the loop, 128 x 4 of 192 x 2048,
+  // 37 tokens 107.2 | 109.3 | 112.8 us, 64 tokens 121.4 | 124.3 | 129.1, 1 token 32.2 | 32.4 | 32.2.
+  for (int row = threadIdx.x; row < min(n_slots, n_rows); row += D::THREADS) {
+    const uint4* src = reinterpret_cast<const uint4*>(ys + row * (D::COLS * 2));
+    uint4* dst = reinterpret_cast<uint4*>(y + (size_t)row * d + n0);
+#pragma unroll
+    for (int q = 0; q < D::COLS / 8; ++q) dst[q] = src[q];
+  }
   const int c = threadIdx.x % (D::COLS / 2);
   for (int token = first; token < T; token += D::TOKENS) {
     const int kt = min(max(token == first ? first_budget : k_tok[token], 0), k_max);
@@ -1595,13 +1604,13 @@ bool ffn_down_combines(int few, int T, int k_max, int E, int d, int Is) {
 
 hipError_t launch_ffn_down_combine(const uint16_t* h, const uint16_t* w_dn, const MTile* tiles, const int32_t* hdr,
                                    int max_tiles, const int32_t* slot_of_pair, const float* w, const int32_t* k_tok,
-                                   uint16_t* out, int few, int T, int d, int Is, int E, int k_max, hipStream_t s) {
+                                   uint16_t* y, uint16_t* out, int T, int d, int Is, int k_max, hipStream_t s) {
   auto launch = [&](auto shape, auto stages) {
     typedef decltype(shape) D;
     constexpr auto Kern = ffn_down_combine_kernel<D::COLS, D::NS, decltype(stages)::value>;
     hipError_t e = raise_lds_limit<Kern>(D::LDS_BYTES);
     if (e != hipSuccess) return e;
-    Kern<<<d / D::COLS, D::THREADS, D::lds_bytes(T * k_max), s>>>(h, w_dn, tiles, hdr, max_tiles, slot_of_pair, w, k_tok, out, T, d, Is,
+    Kern<<<d / D::COLS, D::THREADS, D::lds_bytes(T * k_max), s>>>(h, w_dn, tiles, hdr, max_tiles, slot_of_pair, w, k_tok, y, out, T, d, Is,
                                                                   k_max);
     return hipGetLastError();
   };

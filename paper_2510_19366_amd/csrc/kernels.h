@@ -92,11 +92,11 @@ struct PickArgs;
 bool ffn_picks(int dtype, int few, int T, int k_max, int E, int d, int Is);
 hipError_t launch_ffn_pick_gate_up(int dtype, const PickArgs& p, const void* x, const void* w_gu, void* h, int T, int d, int Is,
                                    int k_max, int few, hipStream_t s);
-// the down projection of the few-rows tiles and the combine in one kernel, which leaves no y (layer calls; few: of ffn_few_blocks)
+// the down projection of the few-rows tiles and the combine in one kernel (layer calls; few: of ffn_few_blocks)
 bool ffn_down_combines(int few, int T, int k_max, int E, int d, int Is);
 hipError_t launch_ffn_down_combine(const uint16_t* h, const uint16_t* w_dn, const MTile* tiles, const int32_t* hdr,
                                    int max_tiles, const int32_t* slot_of_pair, const float* w, const int32_t* k_tok,
-                                   uint16_t* out, int few, int T, int d, int Is, int E, int k_max, hipStream_t s);
+                                   uint16_t* y, uint16_t* out, int T, int d, int Is, int k_max, hipStream_t s);
 // fp32: the list of row blocks and the tile (`few` of the launchers)
 int ffn_f32_list(int T, int k_max, int E, int d, int Is);
 

@@ -255,3 +255,33 @@ def test_gate_up_that_picks_for_itself(dtype, T, E, k_max, d, Is, picks, renorm,
         y = B.moe_prism_grouped_ffn(shape, x, w_gu, w_dn, off, sp, ws)
         ref = B.moe_prism_combine(shape, y, sl, wt, k)
         assert torch.equal(out.view(bits), ref.view(bits))
+
+
+@pytest.mark.parametrize("T,N,S,k_max,d,Is", [
+    (1, 128, 4, 32, 2048, 192), (37, 128, 4, 32, 2048, 192), (600, 128, 4, 4, 1600, 64),  # 8 columns; more rows than threads
+    (17, 3, 1, 2, 1984, 320), (5, 8, 4, 8, 4096, 608), (48, 128, 4, 32, 3136, 192),       # 16 columns, four stages and three
+    (80, 128, 4, 32, 2048, 192)])                                                         # the combine's own kernel
+def test_layer_leaves_y_where_its_offsets_say(T, N, S, k_max, d, Is):
+    # against the stage calls' y, bit for bit, whichever kernel adds up the picks; rows beyond the pairs are not written
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    E = N * S
+    shape = B.make_shape(T, d, N, S, Is, k_max, "bf16", 1, 1.0)
+
+    def normal(*size, std):
+        return torch.empty(size, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+    x, w_r, w_gu, w_dn = normal(T, d, std=1.0), normal(E, d, std=0.02), normal(E, 2 * Is, d, std=0.05), normal(E, d, Is, std=0.05)
+    k = torch.randint(0, k_max + 1, (T,), generator=g, device="cuda", dtype=torch.int32)
+    k[0] = k_max - 1 if k_max > 1 else 1
+    ws = B.alloc_workspace(shape)
+    ws.fill_(255)
+    B.moe_prism_layer(shape, x, w_r, None, k, w_gu, w_dn, ws)
+    at = B.moe_prism_layer_offsets(shape)["y"]
+    y = ws[at:at + T * k_max * d * 2].view(torch.int16).view(T * k_max, d).clone()
+    other = B.alloc_workspace(shape)
+    ids, _, _ = B.moe_prism_route(shape, x, w_r, None, k, other, want_logits=True)
+    _, off, sp, _ = B.moe_prism_dispatch(shape, ids, other)
+    ref = B.moe_prism_grouped_ffn(shape, x, w_gu, w_dn, off, sp, other)
+    P = int(off[-1])
+    assert 0 < P < T * k_max
+    assert torch.equal(y[:P], ref[:P].view(torch.int16))
+    assert (y[P:] == -1).all()
