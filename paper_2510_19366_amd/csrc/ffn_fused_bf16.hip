@@ -38,12 +38,12 @@ constexpr int BM = FFN_BM;
 constexpr int NSW = 4;    // weight ring slots
 constexpr int X_WAVE = 32 * 128;       // bytes of one wave's x slot: 32 rows x 64 K-elements
 constexpr int EPI_WAVE = 16 * 128;     // bytes of a wave's output staging: 16 rows x 64 columns
-constexpr int PD = 4;     // fragment reads in flight ahead of the MFMAs
 // Consecutive tiles of a list's turn; 1 where the long tiles come first, so that every list has its share of them (skewed, 700 |
 // 1024 tokens in runs of 32: 212 | 232 us, so 210 | 227).  With 32, one tile for each of an XCD's workgroups, | 64, 512
 // sub-experts of 192 x 2048, fused kernel between HIP events, three layers in turn: proxy gate, 2000 tokens 318 | 306 us, 4096
 // 368 | 355, 6000 434 | 436, 12000 666 | 667; skewed, 3000 tokens 313 | 304, 8000 497 | 501, 16384 885 | 890; 12000 of 32 picks 986 | 987.
 constexpr int RUN = 64;
+constexpr int PD = 4;     // fragment reads in flight ahead of the MFMAs
 
 template <int IS>
 struct Cfg {
@@ -57,7 +57,7 @@ struct Cfg {
   static constexpr int OFF_X = NSW * W_SLOT;
   static constexpr int OFF_PAIR = OFF_X + 8 * X_WAVE;
   static constexpr int OFF_EPI = OFF_PAIR + 2 * BM * 4;   // output transposition
-  static constexpr int OFF_DYN = OFF_EPI + 8 * EPI_WAVE;  // the tile number drawn by wave 0
+  static constexpr int OFF_DYN = OFF_EPI + 8 * EPI_WAVE;  // the tile number drawn by wave 0, and the number of tiles
   static constexpr int LDS_BYTES = OFF_DYN + 16;
   // steps of a stage (one MFMA each) behind which things happen
   static constexpr int STEPS = 2 * NBLK;
@@ -171,14 +171,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ w_gu,
     const uint16_t* __restrict__ w_dn, const int32_t* __restrict__ sorted_pair,
     const MTile* __restrict__ tiles, int32_t* __restrict__ hdr, uint16_t* __restrict__ y, int T,
-    int d, int k_max, int sorted) {
+    int d, int k_max, int sorted, int help) {
   using C = Cfg<IS>;
   constexpr int NBLK = C::NBLK, WPW = C::WPW;
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
   const int S1 = d / 32, S2 = d / 64, ST = S1 + S2;
 
-  // Tiles are drawn at run time, in the order of TileLists (drawing the heavy tiles first measured slower): the first one
+  // Tiles are drawn at run time, in the order of TileLists (long tables with the long tiles first measured slower): the first one
   // of a workgroup is given, the next one is drawn at the end of phase 1 of the one before, from the list of its XCD
   // (workgroup b runs on XCD b % 8) and, once that is empty, from the longest of the others.
   // A list is always drained by its own workgroups, whatever the others take of it.  What this is about is the end of the
@@ -186,14 +186,19 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   // runs of 32 to the last tile | so, between HIP events, three layers in turn, 128 x 4 sub-experts of 192 x 2048, budgets 8 to
   // 32, router bias N(0, 1) per expert: 3000 tokens 336 | 317 us, 8000 533 | 513, 16384 906 | 864; 12000 of 32 picks 980 | 950,
   // 65536 5365 | 5300.
+  // A draw is a latency that wave 0 stands still for, with its copies, and its line is one that all workgroups wait for: the
+  // number of tiles is kept in LDS, or short tiles take up to 40 % longer (see fused_help for the helping, which is one more).  Fused
+  // kernel, number of tiles read with each draw | kept: 512 sub-experts of 32 picks, 192 x 2048, 1500 tokens 279 | 273, 64 x 2048, 5000 217 |
+  // 195; 1024 of 16 picks, 64 x 512, 6772 116 | 95; 768 of 16 picks, 192 x 512, 1682 119 | 107; 64 of 64 picks, 128 x 256, 6535 95 | 82.
   const int xcd = blockIdx.x % N_XCD, slot = blockIdx.x / N_XCD;
   int32_t* dyn_lds = reinterpret_cast<int32_t*>(smem + C::OFF_DYN);
   auto lists_of = [&](int n) { return TileLists(n, n <= sorted ? 1 : RUN); };
   auto ask = [&](int list) { return lane == 0 ? atomicAdd(&hdr[HDR_DYN_FUSED + list], 1) : 0; };
   auto draw = [&](int asked) {  // wave 0, what ask(xcd) returned; -1: none is left
-    const TileLists lists = lists_of(uni(__hip_atomic_load(&hdr[HDR_MTILES], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
+    const TileLists lists = lists_of(uni(dyn_lds[1]));  // (from the header it is a line that all workgroups' draws are waiting for)
     const int slots = gridDim.x / N_XCD;
     int from = xcd, i = slots + uni(asked);
+    if (i >= lists.count(xcd) && !help) return -1;
 #pragma nounroll
     for (int tries = 0; i >= lists.count(from); ++tries) {
       // lane l looks at list l
@@ -209,7 +214,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     }
     return lists.tile(from, i);
   };
-  const TileLists lists = lists_of(hdr[HDR_MTILES]);
+  const int n_tiles = hdr[HDR_MTILES];
+  if (threadIdx.x == 0) dyn_lds[1] = n_tiles;  // (read behind the barriers of the first tile's start)
+  const TileLists lists = lists_of(n_tiles);
   if (slot >= lists.count(xcd)) return;  // uniform over the workgroup
 
   const uint32_t lds0 = lds_offset(smem);
@@ -613,6 +620,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   }
 }
 
+// Whether a workgroup whose list is empty draws from the others'.  It has to look at them first, and even load has the
+// workgroups do so all at once: 6 to 10 us, which long tiles get back with skewed load and short ones don't.  Fused kernel, us, not |
+// helping, even load (512 sub-experts, 2500 tokens of 32 picks) and skewed (256, 6000 of 16): 192 x 512 78 | 88, 78 | 79; 128 x 1024 98.5 | 107.0,
+// 103 | 96; 128 x 1536 151 | 158, 149 | 149; 128 x 2048 237 | 239, 201 | 199; 64 x 4096 281 | 287, 323 | 314; 192 x 1536 215.7 | 217.6, 186 | 179;
+// 128 x 2560 252 | 258, 248 | 248; 192 x 2048 317 | 317, 247 | 241; 128 x 4096 446 | 445, 393 | 380; skewed, 512 of 192 x 2048, 16 384 tokens 911 | 869.
+static bool fused_help(int d, int Is) { return (long)d * Is > 128L * 2048; }
+
 template <int IS, bool MATH>
 static hipError_t launch_is(const uint16_t* x, const uint16_t* w_gu, const uint16_t* w_dn,
                             const int32_t* sorted_pair, const MTile* tiles, int32_t* hdr,
@@ -620,8 +634,9 @@ static hipError_t launch_is(const uint16_t* x, const uint16_t* w_gu, const uint1
   hipError_t e = raise_lds_limit<ffn_fused_kernel<IS, MATH>>(Cfg<IS>::LDS_BYTES);
   if (e != hipSuccess) return e;
   const int grid = persistent_grid(max_mtiles, 1);
+  const int help = fused_help(d, IS);
   ffn_fused_kernel<IS, MATH><<<grid, NT, Cfg<IS>::LDS_BYTES, s>>>(x, w_gu, w_dn, sorted_pair, tiles, hdr, y,
-                                                            T, d, k_max, sorted);
+                                                            T, d, k_max, sorted, help);
   return hipGetLastError();
 }
 

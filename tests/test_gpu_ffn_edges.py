@@ -47,6 +47,7 @@ def ffn(dtype, x, w_gu, w_dn, group):
     ("bf16", "auto", [34, 1, 64, 25] * 65, 320, 64),  # fused, more tiles than CUs: the next tile known from the start, near the end
     ("bf16", "auto", [34, 1, 64, 25] * 65, 832, 64),
     ("bf16", "auto", [300, 1, 64, 25, 0] * 65, 896, 192),
+    ("bf16", "auto", [300, 1, 64, 25, 0] * 65, 1408, 192),  # long enough that empty lists draw from the others
     ("bf16", "split", SIZES, 512, 192),   # weight tiles with and without a second half
     ("bf16", "auto", FEW, 64, 32),        # small tiles: one K stage; half a stage
     ("bf16", "auto", FEW, 448, 352),
