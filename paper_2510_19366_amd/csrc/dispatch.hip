@@ -112,16 +112,20 @@ bool dispatch_sums(int T, int E) {
   const int nch = cdiv(T, 64 * dispatch_chunk_words(E, T));
   return T > 0 && E % 4 == 0 && E <= 1024 && nch <= 256 && (long)nch * E <= SUM_COUNTS;
 }
-// tot[g], before[g] (LDS): rows of group g in all chunks and in those before c
+// tot[g], before[g] (LDS): rows of group g in all chunks and in those before c.  No more threads than have U loads each: every one
+// adds to the same LDS words in the end, which with all threads on four groups takes longer than the loads.  Layer calls of 4 picks,
+// d = 64, Is = 32, all threads | so: 4 groups, 300 tokens 28.5 | 25.9 us, 2000 30.1 | 27.6, 16 384 46.0 | 43.6; 8, 300 27.2 | 26.0; 32, 2000
+// 27.8 | 27.7.
 __device__ __forceinline__ void sum_counts(const int32_t* __restrict__ chunk_cnt, int32_t* tot, int32_t* before, int c,
                                            int n_chunks, int E) {
   for (int g = threadIdx.x; g < 2 * E; g += DISPATCH_THREADS) tot[g] = 0;  // before[] lies behind tot[]
   __syncthreads();
-  const int quads = E / 4, parts = DISPATCH_THREADS / quads, part = threadIdx.x / quads, q = threadIdx.x % quads;
+  constexpr int U = 8;
+  const int quads = E / 4, part = threadIdx.x / quads, q = threadIdx.x % quads;
+  const int parts = min(DISPATCH_THREADS / quads, (n_chunks + U - 1) / U);
   if (part < parts) {
     const int4* rows = reinterpret_cast<const int4*>(chunk_cnt) + q;
     int4 t = make_int4(0, 0, 0, 0), b = t;
-    constexpr int U = 8;
     for (int i = part; i < n_chunks; i += U * parts) {
       int4 v[U];
 #pragma unroll

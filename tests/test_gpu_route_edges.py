@@ -221,3 +221,26 @@ def test_layer_batches_that_the_top_k_kernel_dispatches(T, E, k_max, one):
     _, off, sp, sl = B.moe_prism_dispatch(shape, ids, ws)
     y = B.moe_prism_grouped_ffn(shape, x, w_gu, w_dn, off, sp, ws)
     assert torch.equal(out, B.moe_prism_combine(shape, y, sl, wt, k))
+
+
+@pytest.mark.parametrize("T,E,k_max", [
+    (300, 4, 4), (8000, 4, 3), (16384, 4, 4), (16320, 4, 1), (300, 8, 2), (513, 16, 16), (2000, 32, 4),  # few groups: counts added up by few threads
+])
+def test_dispatch_of_random_picks(T, E, k_max):
+    # against a stable sort of the pairs by sub-expert; budgets of 0 to k_max
+    g = torch.Generator(device="cuda").manual_seed(T + E + k_max)
+    budget = torch.randint(0, k_max + 1, (T, 1), generator=g, device="cuda")
+    load = torch.rand(E, generator=g, device="cuda")
+    ids = (torch.rand(T, E, generator=g, device="cuda") + load).topk(k_max, dim=1).indices.int()
+    ids[torch.arange(k_max, device="cuda")[None, :] >= budget] = -1
+    shape = B.make_shape(T, 64, E, 1, 32, k_max, "bf16")
+    cnt, off, sp, sl = B.moe_prism_dispatch(shape, ids, B.alloc_workspace(shape))
+    flat = ids.flatten().long()
+    count = torch.bincount(flat[flat >= 0], minlength=E)
+    P = int(count.sum())
+    order = torch.where(flat >= 0, flat, E).sort(stable=True).indices
+    assert torch.equal(cnt.long(), count) and torch.equal(off[1:].long(), count.cumsum(0)) and off[0] == 0
+    assert torch.equal(sp[:P].long(), order[:P]) and (sp[P:] == -1).all()
+    slots = torch.full_like(flat, -1)
+    slots[order[:P]] = torch.arange(P, device="cuda")
+    assert torch.equal(sl.long(), slots)
