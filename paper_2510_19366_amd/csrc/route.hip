@@ -209,11 +209,11 @@ hipError_t launch_logits(int dtype, const void* x, const void* w, const float* b
 constexpr int TOPK_WAVES = 4;
 // What follows the picks of a small batch in the same launch.
 //   LAST: the last workgroup to finish dispatches the picks of all T tokens, which it reads back.
-//   SOLO: one workgroup of up to 8 waves has all tokens, and dispatches their picks from LDS.
+//   SOLO: one workgroup of up to WAVES waves has all tokens, and dispatches their picks from LDS.
 enum { TOPK_ONLY, TOPK_LAST, TOPK_SOLO };
-constexpr int SOLO_WAVES = 8;
+constexpr int SOLO_WAVES = 16;
 template <int ELEMS, int MODE, int WAVES = TOPK_WAVES>
-__global__ __launch_bounds__(64 * (MODE == TOPK_SOLO ? SOLO_WAVES : WAVES)) void topk_kernel(
+__global__ __launch_bounds__(64 * WAVES) void topk_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ k_tok, int32_t* __restrict__ ids,
     float* __restrict__ wout, int32_t* __restrict__ hdr, int T, int E, int k_max, int renorm,
     float scale, SmallDispatch small) {
@@ -305,13 +305,15 @@ hipError_t launch_topk(const float* logits, const int32_t* k_tok, int32_t* ids, 
   if (T == 0) return hipSuccess;
   const size_t sh_wave = (size_t)4 * topk_pad(k_max) * sizeof(float);
   const int elems = cdiv(E, 64);
-  // One workgroup saves the count and the reading back of the picks, but its waves are in each other's way.  Layer calls back to
-  // back, us, one workgroup | the last of several of eight waves: 512 sub-experts of 32 picks, 5 tokens 52.9 | 53.5, 8 60.9 | 61.7, 10 65.9 |
-  // 65.8, 12 74.7 | 74.3, 16 79.9 | 79.1; 256 of 32, 8 83.2 | 84.4, 12 106.2 | 105.8, 16 126.7 | 125.8; 128 of 12, 8 88.1 | 89.2, 12 124.1 | 124.2,
-  // 16 151.7 | 151.5; 1024 of 24, d = 256, 4 23.7 | 24.2, 8 23.9 | 24.8, 12 27.4 | 26.1, 16 29.4 | 27.7; fp32, 64 of 8, 8 21.7 | 22.0, 16 22.3 | 22.1.
+  // One workgroup saves the count and the reading back of the picks, but its waves are in each other's way.  Layer calls from a
+  // captured graph, us, one workgroup | the last of several of eight waves, d = 128, Is = 64: 9 tokens of 2 picks out of 32 sub-experts 15.7 |
+  // 16.7, of 32 out of 32 19.6 | 20.4, out of 512 21.5 | 22.0, out of 1024 24.6 | 25.7; 12 tokens of 2 out of 16 15.9 | 16.7, of 24 out of 512
+  // 21.4 | 21.7, of 32 21.6 | 21.9, out of 1024 24.0 | 23.4; 16 tokens of 2 out of 16 16.7 | 17.7, of 16 out of 128 18.6 | 19.0, of 20 out of
+  // 128 20.4 | 20.4, of 32 out of 128 21.0 | 21.2; of 2 out of 256 17.1 | 17.5, of 8 19.2 | 19.0, of 32 22.2 | 21.8; of 12 out of 512 20.5 | 20.0, out of
+  // 1024 23.1 | 22.0.
   const int solo_waves = T < TOPK_WAVES ? TOPK_WAVES : T;
   const size_t sh_solo = solo_waves * sh_wave + (size_t)E * 12 + SOLO_WAVES * sizeof(int32_t);
-  const bool solo = small != nullptr && T <= SOLO_WAVES && elems <= 16 && sh_solo <= 60 * 1024;
+  const bool solo = small != nullptr && ((T <= 12 && T * E <= 10 * 1024) || (T <= SOLO_WAVES && E <= 128)) && elems <= 16 && sh_solo <= 60 * 1024;
   const int waves = !small || solo || !wide_last(k_max) ? TOPK_WAVES : LAST_WAVES;
   const size_t sh_small = small_dispatch_lds(T, E) + (1 + waves) * sizeof(int32_t);  // the last flag and wave_tot
   dim3 grid(cdiv(T, waves)), block(64 * waves);
@@ -329,7 +331,8 @@ hipError_t launch_topk(const float* logits, const int32_t* k_tok, int32_t* ids, 
 #define MP_TOPK(N)                                                           \
   do {                                                                       \
     if (small == nullptr) MP_TOPK_MODE(N, TOPK_ONLY);                        \
-    else if (solo && N <= 16) MP_TOPK_MODE((N <= 16 ? N : 16), TOPK_SOLO);   \
+    else if (solo && T <= 8) MP_TOPK_MODE((N <= 16 ? N : 16), TOPK_SOLO, 8); \
+    else if (solo) MP_TOPK_MODE((N <= 16 ? N : 16), TOPK_SOLO, SOLO_WAVES);  \
     else if (waves == LAST_WAVES) MP_TOPK_MODE(N, TOPK_LAST, LAST_WAVES);    \
     else MP_TOPK_MODE(N, TOPK_LAST);                                         \
   } while (0)
