@@ -186,10 +186,12 @@ __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_place_kernel(
               slot_of_pair, (size_t)t0 * k_max, off_lds[E], E, W);
 }
 
-// Stage calls between HIP events, 256 threads | 512 | 1024, us: 4 tokens of 32 picks 6.6 | 6.5 | 6.3, 64 8.7 | 6.9 | 6.7, 64 of 64 12.9 | 8.9 | 8.4,
-// 100 of 71 19.6 | 12.4 | 10.3, 128 of 40 15.4 | 10.6 | 9.0, 255 of 8 10.0 | 7.8 | 7.4, 65 of 200 30.7 | 18.8 | 14.9; the gate-less layer of 100
-// tokens, whose picks it dispatches, 251 | 246.6.
-constexpr int SMALL_THREADS = 1024;
+// A thread per pick, and per two groups, as long as 256 threads are enough, else 1024, which more picks keep busy.  Stage calls from a captured graph, us, 256
+// threads | 512 | 1024, 32 sub-experts unless said: 1 token of 8 picks 2.3 | 2.6 | 2.8, 64 of 4 2.4 | 2.6 | 2.8, 64 of 8 2.8 | 2.7 | 2.9, of 12 3.2 | 3.1 |
+// 3.0, of 16 3.6 | 3.1 | 3.1, of 32 5.3 | 4.0 | 3.6, 200 of 8 5.6 | 4.4 | 3.9; 512 sub-experts: 4 of 32 2.8 | 2.8 | 3.0, 32 of 16 3.3 | 2.9 | 3.1, 64 of 32
+// 5.7 | 4.2 | 3.8; 1024: 4 of 8 3.4 | | 3.2.  Between HIP events: 64 of 64 12.9 | 8.9 | 8.4, 100 of 71 19.6 | 12.4 | 10.3, 128 of 40 15.4 | 10.6 | 9.0, 65 of 200 30.7 | 18.8 | 14.9;
+// the gate-less layer of 100 tokens, whose picks it dispatches, 251 | | 246.6.
+template <int SMALL_THREADS>
 __global__ __launch_bounds__(SMALL_THREADS) void dispatch_small_kernel(const int32_t* __restrict__ ids, SmallDispatch a,
                                                                        int32_t* __restrict__ hdr, int T, int E, int k_max) {
   extern __shared__ u64 masks[];
@@ -200,7 +202,8 @@ __global__ __launch_bounds__(SMALL_THREADS) void dispatch_small_kernel(const int
 hipError_t launch_dispatch_small(const int32_t* ids, int32_t* cnt, int32_t* off, int32_t* hdr,
                                  int32_t* sorted_pair, int32_t* slot_of_pair, MTile* tiles,
                                  int max_tiles, TileCut cut, int T, int E, int k_max, hipStream_t s) {
-  dispatch_small_kernel<<<1, SMALL_THREADS, small_dispatch_lds(T, E), s>>>(
+  const bool few = T * k_max <= 256 && E <= 512;
+  (few ? dispatch_small_kernel<256> : dispatch_small_kernel<1024>)<<<1, few ? 256 : 1024, small_dispatch_lds(T, E), s>>>(
       ids, SmallDispatch{cnt, off, sorted_pair, slot_of_pair, tiles, max_tiles, cut}, hdr, T, E, k_max);
   return hipGetLastError();
 }

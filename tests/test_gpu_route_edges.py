@@ -226,6 +226,7 @@ def test_layer_batches_that_the_top_k_kernel_dispatches(T, E, k_max, one):
 
 @pytest.mark.parametrize("T,E,k_max", [
     (300, 4, 4), (8000, 4, 3), (16384, 4, 4), (16320, 4, 1), (300, 8, 2), (513, 16, 16), (2000, 32, 4),  # few groups: counts added up by few threads
+    (1, 1, 1), (64, 16, 4), (65, 4, 4), (32, 1100, 8), (33, 512, 8), (1, 1024, 257), (8, 4096, 32),  # one workgroup, of 256 threads and of 1024
 ])
 def test_dispatch_of_random_picks(T, E, k_max):
     # against a stable sort of the pairs by sub-expert; budgets of 0 to k_max
