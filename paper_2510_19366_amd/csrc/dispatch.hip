@@ -175,8 +175,10 @@ __global__ __launch_bounds__(DISPATCH_THREADS) void dispatch_place_kernel(
     if (c == 0)
       for (int g = threadIdx.x; g < E; g += DISPATCH_THREADS) cnt[g] = tot_lds[g];
   }
-  const int n_tiles = group_offsets([&](int g) { return SUM ? tot_lds[g] : cnt[g]; }, off_lds, first_lds, wave_tot, cut, E,
-                                    c == 0 ? tiles : nullptr, max_tiles);
+  auto count = [&](int g) { return SUM ? tot_lds[g] : cnt[g]; };
+  MTile* last = c == 0 ? tiles : nullptr;
+  const int n_tiles = cut.sorted != 0 ? group_offsets<true>(count, off_lds, first_lds, wave_tot, cut, E, last, max_tiles)
+                                      : group_offsets<false>(count, off_lds, first_lds, wave_tot, cut, E, last, max_tiles);
   if (c == 0) write_offsets(off_lds, n_tiles, off, hdr, tiles != nullptr, max_tiles, E);
   if (tiles != nullptr)
     write_tiles(off_lds, first_lds, tiles, max_tiles, cut, E, c * DISPATCH_THREADS + threadIdx.x,

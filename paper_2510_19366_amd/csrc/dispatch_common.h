@@ -83,11 +83,13 @@ __device__ __forceinline__ int wave_scan(int v) {
 // of the row counts cnt(g) (off_lds[E] = P) and first_lds[0..E] of the m-tile counts; in a table with the long tiles first
 // (cut.sorted) without the groups' last tiles, which are written to `last` (a table of max_tiles; null: by another
 // workgroup).  Returns the number of m-tiles.  A thread sums a run of consecutive groups, the partial sums are scanned, the run is walked again.
+// SORTED: cut.sorted is not 0.  (Last tiles that are counted whatever it is cost every call half a microsecond, stage calls of 4 picks,
+// counted | not: 1000 tokens, 32 sub-experts 6.1 | 5.8 us, 512 6.9 | 6.3; 12 000, 128 11.9 | 11.5.)
 struct GroupScan {
   int32_t rows, tiles;
   LastTiles last;
 };
-template <class Cnt>
+template <bool SORTED, class Cnt>
 __device__ __forceinline__ int group_offsets(Cnt cnt, int32_t* off_lds, int32_t* first_lds, GroupScan* wave_tot,
                                              const TileCut& cut, int E, MTile* last, int max_tiles) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -97,32 +99,40 @@ __device__ __forceinline__ int group_offsets(Cnt cnt, int32_t* off_lds, int32_t*
     const int n = cnt(g);
     mine.rows += n;
     mine.tiles += cut.tiles(n);
-    if (cut.sorted != 0 && n > 0) mine.last.add(LastTiles::cls(n));
+    if (SORTED && n > 0) mine.last.add(LastTiles::cls(n));
   }
   GroupScan run{wave_scan(mine.rows), wave_scan(mine.tiles), {}}, total{0, 0, {}};
-  if (cut.sorted != 0)
+  if constexpr (SORTED) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) run.last.n[i] = (uint32_t)wave_scan((int)mine.last.n[i]);
-  if (lane == 63) wave_tot[wv] = run;
+    if (lane == 63) wave_tot[wv].last = run.last;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) run.last.n[i] -= mine.last.n[i];
+  }
+  if (lane == 63) {
+    wave_tot[wv].rows = run.rows;
+    wave_tot[wv].tiles = run.tiles;
+  }
   run.rows -= mine.rows;
   run.tiles -= mine.tiles;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) run.last.n[i] -= mine.last.n[i];
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < DISPATCH_THREADS / 64; ++w) {
-    const GroupScan t = wave_tot[w];
+    const int rows = wave_tot[w].rows, tiles = wave_tot[w].tiles;
     const bool before = w < wv;
-    run.rows += before ? t.rows : 0;
-    run.tiles += before ? t.tiles : 0;
-    total.tiles += t.tiles;
+    run.rows += before ? rows : 0;
+    run.tiles += before ? tiles : 0;
+    total.tiles += tiles;
+    if constexpr (SORTED) {
+      const LastTiles t = wave_tot[w].last;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      run.last.n[i] += before ? t.last.n[i] : 0u;
-      total.last.n[i] += t.last.n[i];
+      for (int i = 0; i < 4; ++i) {
+        run.last.n[i] += before ? t.n[i] : 0u;
+        total.last.n[i] += t.n[i];
+      }
     }
   }
-  const bool sorted = total.tiles <= cut.sorted;
+  const bool sorted = SORTED && total.tiles <= cut.sorted;
   int first = run.tiles - (sorted ? run.last.from(0) : 0);
   for (int g = lo; g < hi; ++g) {
     const int n = cnt(g), nt = cut.tiles(n);
