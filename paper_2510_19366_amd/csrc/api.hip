@@ -189,8 +189,13 @@ static FfnPlan plan_ffn(const Layout& L, int dtype, int T, int k, int E, int d, 
   }
   return p;
 }
-static FfnPlan plan_ffn(const Layout& L, const moe_prism_shape* s) {
-  return plan_ffn(L, s->dtype, s->T, s->k_max, s->n_experts * s->n_sub, s->d, s->inter_sub, use_fused_ffn(s));
+// one: a single workgroup dispatches, and leaves the tiles in the order of the groups.  So the fused kernel deals them in runs: layer
+// calls of 193 to 256 sub-experts and up to 255 tokens, tile by tile | so, 192 x 4096, 200 tokens of 32 picks out of 256 286.7 | 274.1 us, skewed
+// 275.7 | 268.5; 192 x 2048 158.5 | 154.9, 120 of 60 out of 224 157.6 | 150.3; narrower or shorter ones alike.
+static FfnPlan plan_ffn(const Layout& L, const moe_prism_shape* s, bool one = false) {
+  FfnPlan p = plan_ffn(L, s->dtype, s->T, s->k_max, s->n_experts * s->n_sub, s->d, s->inter_sub, use_fused_ffn(s));
+  if (one) p.cut.sorted = 0;
+  return p;
 }
 
 // the dispatch of T tokens with up to k_max picks out of E groups
@@ -515,10 +520,10 @@ static int layer_on(const moe_prism_shape* shape, const Layout& L, const void* x
   int32_t* sp = reinterpret_cast<int32_t*>(w8 + L.sorted_pair);
   int32_t* sl = reinterpret_cast<int32_t*>(w8 + L.slot_of_pair);
   // a small batch is dispatched by the top-k kernel itself
-  const FfnPlan p = plan_ffn(L, shape);
-  const SmallDispatch small{cnt, off, sp, sl, reinterpret_cast<MTile*>(w8 + L.tiles), p.max_tiles, p.cut};
   const int E = shape->n_experts * shape->n_sub;
   const bool one = topk_dispatches(shape->T, E, shape->k_max);
+  const FfnPlan p = plan_ffn(L, shape, one);
+  const SmallDispatch small{cnt, off, sp, sl, reinterpret_cast<MTile*>(w8 + L.tiles), p.max_tiles, p.cut};
   const bool later = one && ffn_picks(shape->dtype, p.few, shape->T, shape->k_max, E, shape->d, shape->inter_sub);  // by the gate-up itself
   float* logits = reinterpret_cast<float*>(w8 + L.logits);
   const PickArgs picks{logits, k_tok, ids, w, reinterpret_cast<int32_t*>(w8 + L.hdr), E, shape->renormalize, shape->routed_scale, small};
@@ -601,7 +606,7 @@ int moe_prism_layer_proxy(const moe_prism_shape* shape, const void* x, const voi
   rc = do_route_proxy(shape, L, x, w_router0, router_bias0, w_proxy, m, r, rows_half, kappa, k_tok,
                       ids, w, w8, st);
   if (rc) return rc;
-  const FfnPlan p = plan_ffn(L, shape);
+  const FfnPlan p = plan_ffn(L, shape, dispatch_is_small(shape->T, shape->n_experts * shape->n_sub, shape->k_max));
   rc = do_dispatch(shape, L, ids, cnt, off, sp, sl, w8, st, &p);
   if (rc) return rc;
   return ffn_and_combine(shape, L, x, w_gate_up, w_down, off, sp, w8, st, p, CombineArgs{sl, w, k_tok, out});

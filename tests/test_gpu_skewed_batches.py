@@ -23,6 +23,8 @@ pytestmark = pytest.mark.gpu
     (2000, 64, 8, 4, 256, 64, 385),   # groups of many tiles of 32
     (900, 16, 4, 4, 256, 64, 257),    # the fused kernel, long tiles first
     (1100, 64, 8, 32, 256, 64, 257),  # and more of them
+    (160, 50, 4, 32, 256, 64, 65),    # the fused kernel behind one workgroup's table, in the order of the groups
+    (120, 50, 4, 60, 832, 192, 65),
     (300, 16, 4, 4, 128, 96, 129),    # place kernel, tiles of 32
     (300, 16, 4, 8, 448, 352, 193),   # and of 64
     (300, 16, 4, 8, 256, 32, 193),
