@@ -286,3 +286,33 @@ def test_layer_leaves_y_where_its_offsets_say(T, N, S, k_max, d, Is):
     assert 0 < P < T * k_max
     assert torch.equal(y[:P], ref[:P].view(torch.int16))
     assert (y[P:] == -1).all()
+
+
+@pytest.mark.parametrize("dtype,T,E,k_max,d,Is", [
+    ("bf16", 1, 1, 1, 64, 32), ("bf16", 2, 65, 7, 448, 96), ("bf16", 4, 129, 40, 1088, 64), ("bf16", 1, 512, 32, 2048, 192), ("bf16", 4, 512, 64, 1024, 128),
+    ("f32", 1, 1, 1, 64, 32), ("f32", 2, 5, 5, 128, 96), ("f32", 33, 31, 7, 192, 64), ("f32", 64, 32, 8, 256, 128), ("f32", 64, 32, 32, 64, 32)])
+def test_gate_up_that_picks_leaves_the_tables_of_route_and_dispatch(dtype, T, E, k_max, d, Is):
+    # every table of the layer's workspace against the stage calls', behind a workspace of 0xff; budgets of 0 to k_max
+    g = torch.Generator(device="cuda").manual_seed(T + E + d)
+    shape = B.make_shape(T, d, E, 1, Is, k_max, dtype, 1, 1.5)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+
+    def normal(*size, std):
+        return torch.empty(size, dtype=dt, device="cuda").normal_(0.0, std, generator=g)
+    x, w_r, w_gu, w_dn = normal(T, d, std=1.0), normal(E, d, std=0.02), normal(E, 2 * Is, d, std=0.05), normal(E, d, Is, std=0.05)
+    k = torch.randint(0, k_max + 1, (T,), generator=g, device="cuda", dtype=torch.int32)
+    k[0] = k_max
+    ws, other = B.alloc_workspace(shape), B.alloc_workspace(shape)
+    ws.fill_(255)
+    B.moe_prism_timing_enable(True)
+    try:
+        B.moe_prism_layer(shape, x, w_r, None, k, w_gu, w_dn, ws)
+        torch.cuda.synchronize()
+        assert B.moe_prism_timing_read()["topk"][1] == 0
+    finally:
+        B.moe_prism_timing_enable(False)
+    ids, wt, lg = B.moe_prism_route(shape, x, w_r, None, k, other, want_logits=True)
+    cnt, off, sp, sl = B.moe_prism_dispatch(shape, ids, other)
+    ref = dict(topk_ids=ids, topk_w=wt, group_count=cnt, group_offset=off, sorted_pair=sp, slot_of_pair=sl, logits=lg)
+    for name, table in B.layer_intermediates(shape, ws).items():
+        assert torch.equal(table.view(torch.int32), ref[name].view(torch.int32)), name

@@ -94,3 +94,44 @@ def test_timing_select_brackets_only_the_named_kernels():
     finally:
         B.moe_prism_timing_select(None)
         B.moe_prism_timing_enable(False)
+
+
+@pytest.mark.parametrize("dtype,T,N,S,k_max,d,Is,idle", [
+    ("bf16", 3, 16, 4, 8, 2048, 64, ("topk", "combine")),   # the gate-up picks, the down projection adds up the picks
+    ("bf16", 30, 16, 4, 16, 1600, 64, ("combine",)),
+    ("f32", 40, 8, 4, 8, 128, 64, ("topk",)),
+    ("bf16", 300, 64, 8, 32, 256, 192, ())])                # the fused kernel, whose workgroups draw their tiles
+def test_replays_of_the_small_calls_kernels(dtype, T, N, S, k_max, d, Is, idle):
+    # every replay against an eager call, bit for bit, with eager work and synchronisations between
+    g = torch.Generator(device="cuda").manual_seed(T)
+    dt, bits = (torch.bfloat16, torch.int16) if dtype == "bf16" else (torch.float32, torch.int32)
+    E = N * S
+    shape = B.make_shape(T, d, N, S, Is, k_max, dtype, 1, 1.0)
+
+    def normal(*size, std):
+        return torch.empty(size, dtype=dt, device="cuda").normal_(0.0, std, generator=g)
+    x, w_r, w_gu, w_dn = normal(T, d, std=1.0), normal(E, d, std=0.02), normal(E, 2 * Is, d, std=0.05), normal(E, d, Is, std=0.05)
+    k = torch.full((T,), k_max, dtype=torch.int32, device="cuda")
+    ws, ws_eager = B.alloc_workspace(shape), B.alloc_workspace(shape)
+    out, ref = torch.empty((T, d), dtype=dt, device="cuda"), torch.empty((T, d), dtype=dt, device="cuda")
+    B.moe_prism_timing_enable(True)
+    try:
+        B.moe_prism_layer(shape, x, w_r, None, k, w_gu, w_dn, ws, out=out)
+        torch.cuda.synchronize()
+        calls = {name: v[1] for name, v in B.moe_prism_timing_read().items()}
+    finally:
+        B.moe_prism_timing_enable(False)
+    assert tuple(name for name in ("topk", "combine") if calls[name] == 0) == idle
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.moe_prism_layer(shape, x, w_r, None, k, w_gu, w_dn, ws, out=out)
+    for budgets in ([k_max] * T, [0] * T, torch.randint(0, k_max + 1, (T,), generator=g, device="cuda").tolist(), [1] * T):
+        x.normal_(generator=g)
+        k.copy_(torch.tensor(budgets, dtype=torch.int32))
+        B.moe_prism_layer(shape, x, w_r, None, k, w_gu, w_dn, ws_eager, out=ref)
+        torch.cuda.synchronize()
+        out.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert B.moe_prism_status(ws) == (0, sum(budgets))
+        assert torch.equal(out.view(bits), ref.view(bits))

@@ -146,3 +146,44 @@ def test_proxy_argument_errors_and_clamping():
         bad[key] = val
         with pytest.raises(B.MoePrismError):
             B.moe_prism_route_proxy(shape, dev["x"], bad, k_bad, ws)
+
+
+@pytest.mark.parametrize("T,combines", [(24, 1), (25, 0)])  # 12 possible rows per sub-expert, and more
+@pytest.mark.parametrize("short", [False, True])
+def test_down_projection_that_adds_up_the_proxy_gates_picks(T, combines, short):
+    # against the stage calls, bit for bit; short: allocations of less than the budget, which leave picks without a sub-expert
+    m, S, N, d, I, r = 8, 4, 16, 2048, 256, 4
+    g = torch.Generator(device="cuda").manual_seed(T)
+    E, Is, k_max = N * S, I // S, m * S
+    shape = B.make_shape(T, d, N, S, Is, k_max, "bf16", 1, 1.0)
+
+    def normal(*size, std):
+        return torch.empty(size, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+    x, w_gu, w_dn = normal(T, d, std=1.0), normal(E, 2 * Is, d, std=0.05), normal(E, d, Is, std=0.05)
+    kappa = W.default_kappa_table(m, S)
+    if short:
+        kappa[:, 2] -= np.minimum(kappa[:, 2], 1 + np.arange(len(kappa)) % 2)
+    rows_half = 32
+    w_proxy = torch.zeros((N, 2 * rows_half, d), dtype=torch.bfloat16, device="cuda")
+    w_proxy[:, :S * r] = normal(N, S * r, d, std=0.05)
+    w_proxy[:, rows_half:rows_half + S * r] = normal(N, S * r, d, std=0.05)
+    pdev = dict(w_router0=normal(N, d, std=0.02), bias0=None, w_proxy=w_proxy, rows_half=rows_half, m=m, r=r,
+                kappa=torch.from_numpy(np.ascontiguousarray(kappa, np.int32)).cuda())
+    k = torch.randint(0, k_max + 1, (T,), generator=g, device="cuda", dtype=torch.int32)
+    k[0] = k_max
+    ws = B.alloc_workspace(shape)
+    B.moe_prism_timing_enable(True)
+    try:
+        out = B.moe_prism_layer_proxy(shape, x, pdev, k, w_gu, w_dn, ws).clone()
+        torch.cuda.synchronize()
+        assert (B.moe_prism_timing_read()["combine"][1] == 0) == bool(combines)
+    finally:
+        B.moe_prism_timing_enable(False)
+    ids, wt = B.moe_prism_route_proxy(shape, x, pdev, k, ws)
+    below = torch.arange(k_max, device="cuda")[None, :] < k[:, None]
+    assert bool(((ids < 0) & below).any()) == short
+    _, off, sp, sl = B.moe_prism_dispatch(shape, ids, ws)
+    y = B.moe_prism_grouped_ffn(shape, x, w_gu, w_dn, off, sp, ws)
+    ref = B.moe_prism_combine(shape, y, sl, wt, k)
+    assert out.abs().max() > 0
+    assert torch.equal(out.view(torch.int16), ref.view(torch.int16))

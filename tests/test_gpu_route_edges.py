@@ -196,8 +196,7 @@ def test_logits_of_every_tile_and_count_of_stages(T, E, d, dtype):
     (128, 64, 64, 1), (136, 64, 64, 1), (137, 64, 64, 0), (255, 512, 24, 1), (255, 512, 25, 0), (256, 64, 1, 0),  # 4608 pairs, 255 tokens
     (90, 1024, 177, 1), (90, 1024, 178, 0), (65, 1024, 480, 1), (73, 512, 480, 1), (66, 512, 512, 1), (80, 512, 481, 0),  # eight waves, four
     (200, 1706, 3, 1), (200, 1707, 3, 0), (40, 4096, 8, 1),  # 60 KiB of masks
-    (8, 64, 9, 1), (9, 64, 9, 1), (8, 1100, 70, 1), (9, 1000, 70, 1),  # one workgroup for all tokens, the last of two
-    (10, 1024, 33, 1), (11, 1024, 33, 1), (12, 853, 9, 1), (13, 512, 9, 1), (12, 512, 512, 1), (16, 128, 128, 1), (16, 129, 20, 1), (17, 128, 20, 1), (13, 17, 17, 1)])  # of 12, of 16 and more waves
+    (8, 64, 9, 1), (9, 64, 9, 1), (8, 1100, 70, 1), (9, 1000, 70, 1)])  # one workgroup for all tokens, the last of two
 def test_layer_batches_that_the_top_k_kernel_dispatches(T, E, k_max, one):
     # against the stage calls, whose own rules and kernels are others; skewed, budgets of 0 to k_max
     d, Is = 64, 32
@@ -246,3 +245,9 @@ def test_dispatch_of_random_picks(T, E, k_max):
     slots = torch.full_like(flat, -1)
     slots[order[:P]] = torch.arange(P, device="cuda")
     assert torch.equal(sl.long(), slots)
+
+
+@pytest.mark.parametrize("T,E,k_max", [
+    (9, 64, 9), (10, 1024, 33), (11, 1024, 33), (12, 853, 9), (13, 512, 9), (12, 512, 512), (16, 128, 128), (16, 129, 20), (17, 128, 20), (13, 17, 17)])
+def test_layer_batches_around_one_workgroup_for_all_tokens(T, E, k_max):
+    test_layer_batches_that_the_top_k_kernel_dispatches(T, E, k_max, 1)
