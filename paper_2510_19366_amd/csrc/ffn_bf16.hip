@@ -1615,8 +1615,14 @@ hipError_t launch_ffn_down_combine(const uint16_t* h, const uint16_t* w_dn, cons
     return hipGetLastError();
   };
   const std::integral_constant<int, 0> any;
-  const std::integral_constant<int, 3> three;
-  if (down_combine_fits<Columns8>(T, k_max, d)) return Is == 3 * BK ? launch(Columns8{}, three) : launch(Columns8{}, any);
+  // Up to three whole stages unrolled.  Layer calls, us, any number | so, d = 2048, 256 sub-experts of 24 picks: Is = 64, 1 token 24.3 | 24.1, 16
+  // 35.4 | 34.9, 64 53.6 | 51.6; 128, 1 26.1 | 25.9, 64 75.0 | 74.3; 192, 1 29.3 | 29.0, 64 82.2 | 82.1; but 256 29.8 | 29.6, 32 tokens 87.4 | 88.3.
+  if (down_combine_fits<Columns8>(T, k_max, d)) {
+    if (Is == BK) return launch(Columns8{}, std::integral_constant<int, 1>{});
+    if (Is == 2 * BK) return launch(Columns8{}, std::integral_constant<int, 2>{});
+    if (Is == 3 * BK) return launch(Columns8{}, std::integral_constant<int, 3>{});
+    return launch(Columns8{}, any);
+  }
   return down_combine_fits<Columns16>(T, k_max, d) ? launch(Columns16{}, any) : launch(Columns16Rows{}, any);
 }
 

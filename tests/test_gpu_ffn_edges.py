@@ -316,3 +316,9 @@ def test_gate_up_that_picks_leaves_the_tables_of_route_and_dispatch(dtype, T, E,
     ref = dict(topk_ids=ids, topk_w=wt, group_count=cnt, group_offset=off, sorted_pair=sp, slot_of_pair=sl, logits=lg)
     for name, table in B.layer_intermediates(shape, ws).items():
         assert torch.equal(table.view(torch.int32), ref[name].view(torch.int32)), name
+
+
+@pytest.mark.parametrize("Is", [32, 64, 96, 128, 160, 192, 224, 256])
+@pytest.mark.parametrize("T", [1, 9, 50])
+def test_down_projection_and_combine_of_every_count_of_stages(T, Is):
+    test_down_projection_and_combine_in_one_kernel(T, 32, 4, 9, 1728, Is, 1)
