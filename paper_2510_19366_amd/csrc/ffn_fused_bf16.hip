@@ -625,7 +625,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 // helping, even load (512 sub-experts, 2500 tokens of 32 picks) and skewed (256, 6000 of 16): 192 x 512 78 | 88, 78 | 79; 128 x 1024 98.5 | 107.0,
 // 103 | 96; 128 x 1536 151 | 158, 149 | 149; 128 x 2048 237 | 239, 201 | 199; 64 x 4096 281 | 287, 323 | 314; 192 x 1536 215.7 | 217.6, 186 | 179;
 // 128 x 2560 252 | 258, 248 | 248; 192 x 2048 317 | 317, 247 | 241; 128 x 4096 446 | 445, 393 | 380; skewed, 512 of 192 x 2048, 16 384 tokens 911 | 869.
-static bool fused_help(int d, int Is) { return (long)d * Is > 128L * 2048; }
+// Layer calls, helping over not, on average over 9 calls of 256 to 560 sub-experts, even load, skewed: 128 x 1792 1.007, 0.980; 64 x 3840 1.008, 0.981;
+// 192 x 1280 1.015, 0.977; 64 x 4096 1.005, 0.990; 128 x 2048 0.996, 0.992; 192 x 1536 1.012, 0.975.
+static bool fused_help(int d, int Is) { return (long)d * Is >= 128L * 2048; }
 
 template <int IS, bool MATH>
 static hipError_t launch_is(const uint16_t* x, const uint16_t* w_gu, const uint16_t* w_dn,
