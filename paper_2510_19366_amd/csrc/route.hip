@@ -52,11 +52,13 @@ __global__ __launch_bounds__(256) void rows_differ_kernel(const uint32_t* __rest
 // Every logit is ONE chain of d binary32 fused multiply-adds over the hidden index in
 // ascending order, then the fp32 bias add: the fixed summation order is what makes the
 // routing reproducible bit for bit.  The chains run on the matrix cores, see chain_tile.h.
+// SHARE: the rows were compared.  (An instance of its own: with the branch and its epilogue in one kernel the 64 x 64 tile took 53 registers
+// instead of 37, and its stores waited for one bias after the other; route calls, one kernel | two, d = 384: 14 000 x 512 63.5 | 58.9 us, 20 200 x 512 83.2 | 80.7.)
 struct SharedRows {
-  const int32_t* differ;  // of the experts (rows_differ_kernel); null: rows are not compared
+  const int32_t* differ;  // of the experts (rows_differ_kernel)
   int S;
 };
-template <typename InT, int WM, int WN, int MT, int NT, int NS, bool APART>
+template <typename InT, int WM, int WN, int MT, int NT, int NS, bool APART, bool SHARE>
 __global__ __launch_bounds__(64 * WM * WN * (APART ? 2 : 1)) void logits_kernel(
     const InT* __restrict__ x, const InT* __restrict__ w, const float* __restrict__ bias,
     float* __restrict__ logits, int32_t* __restrict__ hdr, int T, int d, int E, SharedRows shared) {
@@ -69,7 +71,7 @@ __global__ __launch_bounds__(64 * WM * WN * (APART ? 2 : 1)) void logits_kernel(
     hdr[HDR_TOPK_DONE] = 0;
   }
   int bx = blockIdx.x, by = blockIdx.y, cols = E, step = 1;  // columns of C are every step-th row of w
-  if (shared.differ != nullptr) {
+  if constexpr (SHARE) {
     bool same = true;
     for (int e = lane; e < E / shared.S; e += 64) same = same && shared.differ[e] == 0;
     if (__all(same)) {
@@ -99,10 +101,10 @@ __global__ __launch_bounds__(64 * WM * WN * (APART ? 2 : 1)) void logits_kernel(
   if (APART && w0 >= C::NW) return;
 
   const int wm = wv / WN, wn = wv % WN, r = lane & 15, g = lane >> 4;
+  if (SHARE && step > 1) {
 #pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    const int col = n0 + (wn * NT + j) * 16 + r;
-    if (step > 1) {
+    for (int j = 0; j < NT; ++j) {
+      const int col = n0 + (wn * NT + j) * 16 + r;
       for (int c = col * step; c < (col + 1) * step && col < cols; c += step % 4 == 0 ? 4 : 1) {
         float bv[4] = {};
         if (bias != nullptr)
@@ -122,8 +124,12 @@ __global__ __launch_bounds__(64 * WM * WN * (APART ? 2 : 1)) void logits_kernel(
             else logits[(size_t)row * E + c] = o[0];
           }
       }
-      continue;
     }
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const int col = n0 + (wn * NT + j) * 16 + r;
     const float bv = bias != nullptr && col < E ? bias[col] : 0.0f;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -140,14 +146,14 @@ __global__ __launch_bounds__(64 * WM * WN * (APART ? 2 : 1)) void logits_kernel(
 
 __global__ void clear_flags_kernel(int32_t* hdr) { hdr[HDR_FLAGS] = 0; }
 
-template <typename InT, int MT, int NT, int NS, bool APART>
+template <typename InT, bool SHARE, int MT, int NT, int NS, bool APART>
 static void launch_logits_cfg(const InT* x, const InT* w, const float* bias, float* logits,
                               int32_t* hdr, int T, int d, int E, SharedRows shared, hipStream_t s) {
   using C = ChainTile<InT, 2, 2, MT, NT, NS>;
   constexpr int MOST = 65535 * C::BT;  // tokens that the second dimension of a grid holds: 2.1 or 4.2 million
   for (long t0 = 0; t0 < T; t0 += MOST) {
     const int n = (int)(T - t0 < MOST ? T - t0 : MOST);
-    logits_kernel<InT, 2, 2, MT, NT, NS, APART><<<dim3(cdiv(E, C::BE), cdiv(n, C::BT)), 64 * C::NW * (APART ? 2 : 1), C::LDS_BYTES, s>>>(
+    logits_kernel<InT, 2, 2, MT, NT, NS, APART, SHARE><<<dim3(cdiv(E, C::BE), cdiv(n, C::BT)), 64 * C::NW * (APART ? 2 : 1), C::LDS_BYTES, s>>>(
         x + t0 * d, w, bias, logits + t0 * E, hdr, n, d, E, shared);
   }
 }
@@ -163,17 +169,17 @@ static void launch_logits_cfg(const InT* x, const InT* w, const float* bias, flo
 // 126.5 | 134.5, 16 384 x 256 126 | 140, 10 000 x 512 156.0 | 154.0, 12 000 185.6 | 182.3, 16 384 245 | 241, 65 536 955 | 947.
 // Copies by the same waves | apart: 1 x 512 13.6 | 11.8, 1024 22.1 | 20.6, 3000 56.4 | 50.2, 5000 89.5 | 79.6, 2741 x 128 21.9 |
 // 20.0, 8192 39.5 | 35.6, 6007 x 256 56.6 | 50.1; 100 x 32, d = 4096 23.1 | 19.4; fp32, 1024 x 32, d = 256 6.4 | 6.4.
-template <typename InT>
+template <typename InT, bool SHARE = false>
 static void launch_logits_t(const InT* x, const InT* w, const float* bias, float* logits,
                             int32_t* hdr, int T, int d, int E, SharedRows shared, hipStream_t s) {
   auto cost = [&](int bt, int be, int sub) { return (long)cdiv((long)cdiv(T, bt) * cdiv(E, be), num_cus()) * sub; };
   const long c1 = cost(32, 32, 1), c2 = cost(32, 64, 2), c4 = cost(64, 64, 4);  // c1 <= c2 <= c4
   if (c4 > 4 && c4 * 20 + (c4 / 4 % 3 == 1 ? 22 : 0) <= c1 * 21)
-    launch_logits_cfg<InT, 2, 2, 3, false>(x, w, bias, logits, hdr, T, d, E, shared, s);
+    launch_logits_cfg<InT, SHARE, 2, 2, 3, false>(x, w, bias, logits, hdr, T, d, E, shared, s);
   else if (c2 == c1 && c1 > 2)
-    launch_logits_cfg<InT, 1, 2, 5, true>(x, w, bias, logits, hdr, T, d, E, shared, s);
+    launch_logits_cfg<InT, SHARE, 1, 2, 5, true>(x, w, bias, logits, hdr, T, d, E, shared, s);
   else
-    launch_logits_cfg<InT, 1, 1, 6, true>(x, w, bias, logits, hdr, T, d, E, shared, s);
+    launch_logits_cfg<InT, SHARE, 1, 1, 6, true>(x, w, bias, logits, hdr, T, d, E, shared, s);
 }
 
 // Rows are compared beyond 2^34 multiply-adds.  Logits between HIP events, d = 2048, 512 sub-experts, 4 to an expert, rows not
@@ -189,15 +195,18 @@ hipError_t launch_logits(int dtype, const void* x, const void* w, const float* b
     clear_flags_kernel<<<1, 1, 0, s>>>(hdr);
     return hipGetLastError();
   }
-  SharedRows shared{nullptr, S};
+  const SharedRows shared{differ, S};
   if (compare_rows(dtype, T, d, E, S)) {
     rows_differ_kernel<<<E / S, 256, 0, s>>>((const uint32_t*)w, differ, dtype == 0 ? d : d / 2, S);
-    shared.differ = differ;
-  }
-  if (dtype == 0)
+    if (dtype == 0)
+      launch_logits_t<float, true>((const float*)x, (const float*)w, bias, logits, hdr, T, d, E, shared, s);
+    else
+      launch_logits_t<uint16_t, true>((const uint16_t*)x, (const uint16_t*)w, bias, logits, hdr, T, d, E, shared, s);
+  } else if (dtype == 0) {
     launch_logits_t((const float*)x, (const float*)w, bias, logits, hdr, T, d, E, shared, s);
-  else
+  } else {
     launch_logits_t((const uint16_t*)x, (const uint16_t*)w, bias, logits, hdr, T, d, E, shared, s);
+  }
   return hipGetLastError();
 }
 
