@@ -163,7 +163,10 @@ static void launch_logits_cfg(const InT* x, const InT* w, const float* bias, flo
 // CU, rounded up, times sub-tiles), so the tile with the smallest such number is taken; among
 // equals, and up to 5 % more, the widest, which re-reads less, but where one or two sub-tiles are all there
 // is its single workgroup per CU has nothing to overlap its start with (4096 x 128: 20.7 us on 32 x 32, 21.5 on
-// 32 x 64).  The narrow tiles have their copies done by waves of their own (APART).  The 64 x 64 tile does not: three of its
+// 32 x 64).  The narrow tiles have their copies done by waves of their own (APART); not 32 x 32 for short rows on CUs with many
+// tiles, where other workgroups' products hide the copies and what is left is twice the waves at a barrier.  Route calls, copies by the
+// same waves | apart: 41 000 x 256, d = 256 73.0 | 78.3, d = 384 89.6 | 93.9; 17 293 x 256, d = 256 37.5 | 38.9; but d = 512 54.2 | 53.5, d = 1024 90.9 | 87.8; and
+// with few tiles, 1024 x 512, d = 256 9.5 | 9.4.  The 64 x 64 tile does not: three of its
 // workgroups share a CU, and six waves per SIMD measured 152 us where three took 137 (8192 x 512).  A workgroup of it that is
 // left alone, the last of 4, 7, 10 .., takes a quarter longer.  Between HIP events, d = 2048, all in 32 x 64 | 64 x 64: 8192 x 512
 // 126.5 | 134.5, 16 384 x 256 126 | 140, 10 000 x 512 156.0 | 154.0, 12 000 185.6 | 182.3, 16 384 245 | 241, 65 536 955 | 947.
@@ -178,8 +181,10 @@ static void launch_logits_t(const InT* x, const InT* w, const float* bias, float
     launch_logits_cfg<InT, SHARE, 2, 2, 3, false>(x, w, bias, logits, hdr, T, d, E, shared, s);
   else if (c2 == c1 && c1 > 2)
     launch_logits_cfg<InT, SHARE, 1, 2, 5, true>(x, w, bias, logits, hdr, T, d, E, shared, s);
-  else
+  else if (SHARE || d * sizeof(InT) >= 1024 || c1 <= 8)
     launch_logits_cfg<InT, SHARE, 1, 1, 6, true>(x, w, bias, logits, hdr, T, d, E, shared, s);
+  else
+    launch_logits_cfg<InT, SHARE, 1, 1, 6, false>(x, w, bias, logits, hdr, T, d, E, shared, s);
 }
 
 // Rows are compared beyond 2^34 multiply-adds.  Logits between HIP events, d = 2048, 512 sub-experts, 4 to an expert, rows not
