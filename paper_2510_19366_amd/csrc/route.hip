@@ -168,7 +168,10 @@ static void launch_logits_cfg(const InT* x, const InT* w, const float* bias, flo
 // same waves | apart: 41 000 x 256, d = 256 73.0 | 78.3, d = 384 89.6 | 93.9; 17 293 x 256, d = 256 37.5 | 38.9; but d = 512 54.2 | 53.5, d = 1024 90.9 | 87.8; and
 // with few tiles, 1024 x 512, d = 256 9.5 | 9.4.  The 64 x 64 tile does not: three of its
 // workgroups share a CU, and six waves per SIMD measured 152 us where three took 137 (8192 x 512).  A workgroup of it that is
-// left alone, the last of 4, 7, 10 .., takes a quarter longer.  Between HIP events, d = 2048, all in 32 x 64 | 64 x 64: 8192 x 512
+// left alone, the last of 4, 7, 10 .., takes a quarter longer, which narrow tiles are worth where rows are long, or with 4 and as many
+// in 32 x 64.  Route calls, 64 x 64 | narrow: 8192 x 512, d = 128 25.4 | 26.4, d = 256 35.8 | 34.2, d = 1024 86.1 | 73.1; 25 200 x 512, d = 256 78.8 | 88.8, d = 512 122.1 |
+// 128.7, 1024 212.7 | 212.6; 27 340 x 256, d = 512 72.6 | 75.0, d = 2048 219.5 | 211.5; fp32, 27 340 x 256, d = 512 75.6 | 80.8, 2048 231 | 261, 8192 x 512, d = 256 35.6 | 34.1, d =
+// 1024 78.6 | 80.7.  Between HIP events, d = 2048, all in 32 x 64 | 64 x 64: 8192 x 512
 // 126.5 | 134.5, 16 384 x 256 126 | 140, 10 000 x 512 156.0 | 154.0, 12 000 185.6 | 182.3, 16 384 245 | 241, 65 536 955 | 947.
 // Copies by the same waves | apart: 1 x 512 13.6 | 11.8, 1024 22.1 | 20.6, 3000 56.4 | 50.2, 5000 89.5 | 79.6, 2741 x 128 21.9 |
 // 20.0, 8192 39.5 | 35.6, 6007 x 256 56.6 | 50.1; 100 x 32, d = 4096 23.1 | 19.4; fp32, 1024 x 32, d = 256 6.4 | 6.4.
@@ -177,7 +180,8 @@ static void launch_logits_t(const InT* x, const InT* w, const float* bias, float
                             int32_t* hdr, int T, int d, int E, SharedRows shared, hipStream_t s) {
   auto cost = [&](int bt, int be, int sub) { return (long)cdiv((long)cdiv(T, bt) * cdiv(E, be), num_cus()) * sub; };
   const long c1 = cost(32, 32, 1), c2 = cost(32, 64, 2), c4 = cost(64, 64, 4);  // c1 <= c2 <= c4
-  if (c4 > 4 && c4 * 20 + (c4 / 4 % 3 == 1 ? 22 : 0) <= c1 * 21)
+  const bool alone = sizeof(InT) == 2 && c4 / 4 % 3 == 1 && (d >= 2048 || (d >= 256 && c4 == 16 && c2 == 16));
+  if (c4 > 4 && c4 * 20 + (alone ? 22 : 0) <= c1 * 21)
     launch_logits_cfg<InT, SHARE, 2, 2, 3, false>(x, w, bias, logits, hdr, T, d, E, shared, s);
   else if (c2 == c1 && c1 > 2)
     launch_logits_cfg<InT, SHARE, 1, 2, 5, true>(x, w, bias, logits, hdr, T, d, E, shared, s);

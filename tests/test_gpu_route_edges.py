@@ -251,3 +251,10 @@ def test_dispatch_of_random_picks(T, E, k_max):
     (9, 64, 9), (10, 1024, 33), (11, 1024, 33), (12, 853, 9), (13, 512, 9), (12, 512, 512), (16, 128, 128), (16, 129, 20), (17, 128, 20), (13, 17, 17)])
 def test_layer_batches_around_one_workgroup_for_all_tokens(T, E, k_max):
     test_layer_batches_that_the_top_k_kernel_dispatches(T, E, k_max, 1)
+
+
+@pytest.mark.parametrize("dtype,T,E,d", [
+    (dtype, T, E, d) for dtype in ("bf16", "f32") for T, E in ((17293, 250), (8100, 510), (25200, 512)) for d in (64, 192, 256, 448, 512)])
+def test_logits_where_the_tile_goes_by_the_length_of_a_row(dtype, T, E, d):
+    # 32 x 32 with copies by the same waves and apart; the fourth workgroup of 64 x 64 on a CU or 32 x 64; the thirteenth
+    test_logits_of_every_tile_and_count_of_stages(T=T, E=E, d=d, dtype=dtype)
