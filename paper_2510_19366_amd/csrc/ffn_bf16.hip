@@ -1593,13 +1593,29 @@ typedef DownCombine<16, 3> Columns16Rows;
 //   A sub-expert's weights are fetched again for each block of its rows: 8 of 704 x 2048, possible rows per sub-expert 12.5 33.1 | 32.1,
 //   30 38.6 | 40.3; 64 of 704 7.5 124.6 | 117.4, 12 126.5 | 125.4; 128 of 704 9.75 223 | 221; 256 of 256 9.5 180.6 | 169.5.  Where rows of
 //   half a line straddle lines: 256 of 352 4.9 220 | 216, 5.6 224 | 219, 7.5 225 | 226, 9.4 236 | 238.
+//   Every workgroup reads h of all slot rows, and a sub-expert's weights again for each block, 64 bytes a clock: a time that goes with
+//   pairs x Is, hides behind the weights' bytes as long as it is shorter, and is longer where some CUs have no columns or the load is skewed.
+//   Layer calls of 256 sub-experts unless said, bias N(0, 1) per expert, N(0, 3^2); pairs x Is in thousands.  d = 2048: 192, 20 tokens of 12 picks (46)
+//   49 | 48, 38 | 37; 37 of 32 (227) 75 | 74, 51 | 52; 64 of 24 (295) 77 | 80, 53 | 55; 704, 20 of 12 (169) 106 | 103, 62 | 62, 64 of 12 (541) 165 | 167, 63 | 71, 64 of
+//   24 (1081) 227 | 231, 123 | 136; 832, 64 of 24 (1278) 244 | 248, 109 | 124.  d = 1536: 128, 64 of 12 (98) 42 | 42, 34 | 35; 192, 64 of 12 (147) 47 | 49, 34 | 36; 704, 37 of 32
+//   (834) 170 | 181, 102 | 118.  In 16 columns d = 3072: 448, 64 of 12 (344) 170 | 171, 86 | 92; 704, 37 of 32 376 | 384, 189 | 200; d = 4096: 704, 64 of 24 517 | 504, 244 | 243.
+//   Half a stage of K at d = 1536: 352, 4 of 16 (23) 36 | 34, 40 of 12 (169) 58 | 60; 608, 4 of 16 (39) 45 | 44, 20 of 12 (146) 76 | 81; 864, 64 of 12 (664) 133 | 156; d = 2048: 480, 20 of
+//   12 (115) 85 | 83; 608 (146) 108 | 111; 864, 64 of 12 203 | 218.  (Up to 352, where six possible rows per sub-expert are the line, 128 sub-experts of
+//   352 x 1536, 64 tokens of 12 picks (270) 58 | 65.)
 template <class D>
 static bool down_combine_fits(int T, int k_max, int d) {
   return (long)T * k_max <= D::ROWS && d <= D::COLS * num_cus() && 4 * d >= 3 * D::COLS * num_cus();
 }
+template <class D>
+static bool down_combine_pays(int T, int k_max, int d, int Is) {
+  if (!down_combine_fits<D>(T, k_max, d)) return false;
+  const double work = (double)T * k_max * Is, share = 4.0 * d / (D::COLS * num_cus()) - 3.0;  // 0 .. 1: of the CUs beyond three quarters
+  if (Is % BK != 0) return Is <= 352 || work <= 50e3 + 70e3 * share;
+  return work <= (D::COLS == 8 ? 100e3 + 460e3 * share : 300e3 + 1000e3 * share);
+}
 bool ffn_down_combines(int few, int T, int k_max, int E, int d, int Is) {
   if (few == 0 || T < 1 || (long)T * k_max > (Is % BK != 0 ? 6L : 12L) * E) return false;
-  return down_combine_fits<Columns8>(T, k_max, d) || down_combine_fits<Columns16Rows>(T, k_max, d);
+  return down_combine_pays<Columns8>(T, k_max, d, Is) || down_combine_pays<Columns16Rows>(T, k_max, d, Is);
 }
 
 hipError_t launch_ffn_down_combine(const uint16_t* h, const uint16_t* w_dn, const MTile* tiles, const int32_t* hdr,

@@ -322,3 +322,13 @@ def test_gate_up_that_picks_leaves_the_tables_of_route_and_dispatch(dtype, T, E,
 @pytest.mark.parametrize("T", [1, 9, 50])
 def test_down_projection_and_combine_of_every_count_of_stages(T, Is):
     test_down_projection_and_combine_in_one_kernel(T, 32, 4, 9, 1728, Is, 1)
+
+
+@pytest.mark.parametrize("T,N,S,k_max,d,Is,combines", [
+    (65, 64, 4, 12, 2048, 704, 1), (67, 64, 4, 12, 2048, 704, 0),    # 560 000 elements of h with columns for every CU
+    (43, 64, 4, 12, 1536, 192, 1), (44, 64, 4, 12, 1536, 192, 0),    # 100 000 with columns for three quarters
+    (83, 64, 4, 12, 3072, 320, 0), (78, 64, 4, 12, 3072, 320, 1),    # 300 000 in 16 columns
+    (16, 64, 4, 12, 2048, 608, 1), (17, 64, 4, 12, 2048, 608, 0),    # half a stage
+    (6, 64, 4, 12, 1536, 608, 1), (7, 64, 4, 12, 1536, 608, 0), (64, 64, 4, 12, 1536, 224, 1)])
+def test_down_projection_and_combine_on_both_sides_of_what_it_reads(T, N, S, k_max, d, Is, combines):
+    test_down_projection_and_combine_in_one_kernel(T, N, S, k_max, d, Is, combines)
