@@ -326,12 +326,12 @@ hipError_t launch_topk(const float* logits, const int32_t* k_tok, int32_t* ids, 
   // One workgroup saves the count and the reading back of the picks, but its waves are in each other's way.  Layer calls from a
   // captured graph, us, one workgroup | the last of several of eight waves, d = 128, Is = 64: 9 tokens of 2 picks out of 32 sub-experts 15.7 |
   // 16.7, of 32 out of 32 19.6 | 20.4, out of 512 21.5 | 22.0, out of 1024 24.6 | 25.7; 12 tokens of 2 out of 16 15.9 | 16.7, of 24 out of 512
-  // 21.4 | 21.7, of 32 21.6 | 21.9, out of 1024 24.0 | 23.4; 16 tokens of 2 out of 16 16.7 | 17.7, of 16 out of 128 18.6 | 19.0, of 20 out of
-  // 128 20.4 | 20.4, of 32 out of 128 21.0 | 21.2; of 2 out of 256 17.1 | 17.5, of 8 19.2 | 19.0, of 32 22.2 | 21.8; of 12 out of 512 20.5 | 20.0, out of
-  // 1024 23.1 | 22.0.
+  // 21.4 | 21.7, of 32 21.6 | 21.9, out of 1024 24.0 | 23.4; 16 tokens of 2 out of 16 16.7 | 17.7, of 12 out of 128 0.3 less, of 20 20.4 |
+  // 20.4, equal logits among them (long searches) 2 more; of 2 out of 256 17.1 | 17.5, of 8 19.2 | 19.0, of 32 22.2 | 21.8; of 12 out of 512 20.5 | 20.0, out
+  // of 1024 23.1 | 22.0.  Equal logits cost one workgroup of 12 tokens 1, too.
   const int solo_waves = T < TOPK_WAVES ? TOPK_WAVES : T;
   const size_t sh_solo = solo_waves * sh_wave + (size_t)E * 12 + SOLO_WAVES * sizeof(int32_t);
-  const bool solo = small != nullptr && ((T <= 12 && T * E <= 10 * 1024) || (T <= SOLO_WAVES && E <= 128)) && elems <= 16 && sh_solo <= 60 * 1024;
+  const bool solo = small != nullptr && ((T <= 12 && T * E <= 10 * 1024) || (T <= SOLO_WAVES && E <= 128 && k_max <= 12)) && elems <= 16 && sh_solo <= 60 * 1024;
   const int waves = !small || solo || !wide_last(k_max) ? TOPK_WAVES : LAST_WAVES;
   const size_t sh_small = small_dispatch_lds(T, E) + (1 + waves) * sizeof(int32_t);  // the last flag and wave_tot
   dim3 grid(cdiv(T, waves)), block(64 * waves);

@@ -248,7 +248,7 @@ def test_dispatch_of_random_picks(T, E, k_max):
 
 
 @pytest.mark.parametrize("T,E,k_max", [
-    (9, 64, 9), (10, 1024, 33), (11, 1024, 33), (12, 853, 9), (13, 512, 9), (12, 512, 512), (16, 128, 128), (16, 129, 20), (17, 128, 20), (13, 17, 17)])
+    (9, 64, 9), (10, 1024, 33), (11, 1024, 33), (12, 853, 9), (13, 512, 9), (12, 512, 512), (16, 128, 128), (16, 128, 12), (16, 128, 13), (16, 129, 12), (17, 128, 20), (13, 17, 17)])
 def test_layer_batches_around_one_workgroup_for_all_tokens(T, E, k_max):
     test_layer_batches_that_the_top_k_kernel_dispatches(T, E, k_max, 1)
 
