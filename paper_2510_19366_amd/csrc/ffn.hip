@@ -396,18 +396,33 @@ hipError_t launch_ffn_down(int dtype, const void* h, const void* w_dn, const MTi
   return hipGetLastError();
 }
 
+// The gate-up's tiles of 16 nt columns: an XCD's share of them (groups x n-tiles) rounded up, as short_row_blocks deals them, for one row block
+struct F32PickGrid {
+  int nt, cap;  // cap: resident workgroups
+  long tiles;
+  F32PickGrid(int few, int T, int k_max, int E, int Is) : nt(few == 1 ? 1 : 2), cap(num_cus() * (nt == 1 ? F32_PER_CU<1> : F32_PER_CU<2>)) {
+    const long groups = (long)T * k_max < E ? (long)T * k_max : E;
+    tiles = (groups * (Is / (16 * nt)) + N_XCD - 1) / N_XCD * N_XCD;
+  }
+};
+// Not where the workgroups that write would push tiles into one more round: layer calls, us, top-k kernel | picking for itself, 8 sub-experts of 1024 x
+// 64, 64 tokens of 6 picks 31.9 | 35.5, 16 of them, 40 of 2 28.7 | 31.2.
 bool ffn_picks(int dtype, int few, int T, int k_max, int E, int d, int Is) {
   if (dtype != 0) return picks_bf16(few, T, k_max, E);
-  return few != 0 && T >= 1 && T <= PICK_T && E <= PICK_E && !f32_wide(T, d, Is);
+  if (few == 0 || T < 1 || T > PICK_T || E > PICK_E || f32_wide(T, d, Is)) return false;
+  const F32PickGrid g(few, T, k_max, E, Is);
+  const long items = g.tiles * cdiv(cdiv((long)T * k_max, E), F32_ROWS);  // of groups of the same length
+  return cdiv(items + pick_writers(T), g.cap) == cdiv(items, g.cap);
 }
 
 hipError_t launch_ffn_pick_gate_up(int dtype, const PickArgs& p, const void* x, const void* w_gu, void* h, int T, int d, int Is,
                                    int k_max, int few, hipStream_t s) {
   if (dtype != 0)
     return launch_pick_gate_up_bf16(p, (const uint16_t*)x, (const uint16_t*)w_gu, (uint16_t*)h, T, d, Is, k_max, s);
+  const F32PickGrid g(few, T, k_max, p.E, Is);
   auto run = [&](auto* kern, int nt) {
-    const long most = (long)T * k_max < p.E ? (long)T * k_max : p.E;  // groups
-    const int grid = persistent_grid(most * cdiv(T, F32_ROWS) * (Is / (16 * nt)), nt == 1 ? F32_PER_CU<1> : F32_PER_CU<2>);
+    const long all = g.tiles * cdiv(T, F32_ROWS), room = (g.cap - pick_writers(T)) / N_XCD * N_XCD;  // beside those that write
+    const int grid = (int)(all < room ? all : room);
     const int lds = nt == 1 ? F32Tile<1>::LDS_BYTES : F32Tile<2>::LDS_BYTES;
     kern<<<grid + pick_writers(T), 256, lds, s>>>((const float*)x, (const float*)w_gu, nullptr, nullptr, nullptr, (float*)h, d, Is, k_max, T, p);
   };

@@ -332,3 +332,11 @@ def test_down_projection_and_combine_of_every_count_of_stages(T, Is):
     (6, 64, 4, 12, 1536, 608, 1), (7, 64, 4, 12, 1536, 608, 0), (64, 64, 4, 12, 1536, 224, 1)])
 def test_down_projection_and_combine_on_both_sides_of_what_it_reads(T, N, S, k_max, d, Is, combines):
     test_down_projection_and_combine_in_one_kernel(T, N, S, k_max, d, Is, combines)
+
+
+@pytest.mark.parametrize("T,E,k_max,d,Is,picks", [
+    (64, 2, 2, 128, 32, 1), (64, 1, 1, 64, 64, 1), (50, 3, 2, 192, 96, 1),  # fewer tiles than XCDs
+    (64, 8, 4, 64, 992, 1), (64, 8, 4, 64, 1024, 1), (64, 8, 5, 64, 992, 1), (64, 8, 5, 64, 1024, 0), (64, 32, 32, 64, 256, 0), (33, 16, 2, 64, 1024, 0)])
+def test_gate_up_that_picks_and_the_workgroups_that_write(T, E, k_max, d, Is, picks):
+    # fp32: as many tiles as workgroups fit, and room for those that write
+    test_gate_up_that_picks_for_itself("f32", T, E, k_max, d, Is, picks, 1, False)
