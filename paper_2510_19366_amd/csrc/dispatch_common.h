@@ -217,13 +217,12 @@ __device__ __forceinline__ void place_pairs(Picks& picks, const u64* masks, Base
 // Up to 64 tokens, or more with few pairs, whose masks and offsets fit the default 64 KiB of LDS: the two or three launches
 // of the general path cost more than their work there.  What bounds it is a chain of latencies (picks, masks, scan,
 // offsets, slots); one workgroup places the pairs of all tokens by itself, and from a second 64-token word of mask on
-// the general path has a workgroup for each: what counts is the pairs beyond those of 64 tokens.  Layer calls of d = 64,
-// Is = 32, 512 sub-experts from a captured graph, one workgroup | count and place kernels; stage calls alone, the same: 40 tokens
-// of 8 picks 21.1 | 25.4 us, 3.4 | 6.3; 64 of 64 33.9 | 41.0, 9.8 | 14.5; 65 of 200 86.3 | 96.5, 27.2 | 35.9; 80 of 160 74.2 | 77.2, 27.3 |
-// 29.4; 100 of 24 28.1 | 30.3, 7.7 | 8.9; of 71 45.5 | 46.0, 16.8 | 16.4; 110 of 56 39.2 | 38.7, 15.5 | 13.7; 128 of 16 26.4 | 29.2, 6.5 | 7.9; of
-// 40 35.8, 12.9; of 41 36.9 | 36.3, 13.3 | 12.2; of 50 39.7 | 38.2, 15.8 | 13.4; 160 of 8 24.4 | 27.2, 5.4 | 6.9; 192 of 10 25.2 | 27.5, 6.8 | 7.4; 200
-// of 11 27.7 | 28.0, 8.0 | 7.4; 255 of 4 22.5 | 24.4, 5.4 | 6.4; of 8 26.5 | 27.4, 7.4 | 7.0 (128 sub-experts alike; 1024: 128 of 41 41.4 | 42.0,
-// 255 of 8 32.4 | 32.2, 9.0 | 7.8).
+// the general path has a workgroup for each: what counts is the pairs beyond those of 64 tokens.  The lines lie where the two met with
+// workgroups of 256 threads for both, and stayed: stage calls from a captured graph, one workgroup | count and place kernels with the
+// present ones, 512 sub-experts: 64 tokens of 32 picks 3.8 | 7.2 us, of 160 8.6 | 17.3, 100 of 24 4.2 | 7.1, 128 of 32 5.1 | 7.8, 160 of 12 4.1 | 6.5, 255 of
+// 8 4.3 | 6.2; beyond the lines 100 of 100 8.7 | 12.8, 128 of 64 7.2 | 10.1, 80 of 256 15.3 | 25.4, 160 of 24 5.1 | 7.3, 255 of 12 4.9 | 6.6, of 24 7.0 | 7.3, of 32 8.0 |
+// 7.9, of 64 13.3 | 10.3.  So they meet at about 6000 pairs beyond those of 64 tokens, and up to 128 tokens nowhere; 32, 128 and 1024
+// sub-experts alike.  (Layer calls, whose workgroup is the top-k kernel's: topk_dispatches.)
 struct SmallDispatch {
   int32_t *cnt, *off, *sorted_pair, *slot_of_pair;
   MTile* tiles;  // nullptr: no m-tile table

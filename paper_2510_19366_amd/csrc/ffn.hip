@@ -145,6 +145,7 @@ __device__ __forceinline__ void f32_items(Tile&& tile, int n, int block, int gri
 // latency and 31 comparisons for each of eight sub-experts.  Layer calls of d = 256, 32 of 128, from a captured graph, top-k kernel |
 // this: 16 tokens 20.1 | 19.0 us, 32 21.9 | 19.7, 64 22.2 | 20.4; back to back, d = 1024, 32 of 256, 30 tokens 43.9 | 41.9, 60 43.9 | 42.4;
 // d = 2048, 32 of 704, 60 tokens 140.9 | 134.8.
+// (A lane has a token and its logits in registers, so 64 tokens, and 32 sub-experts, whose comparisons go with the square.)
 constexpr int PICK_T = 64, PICK_E = 32;
 struct F32Picks {
   u64 masks[PICK_E];  // tokens that picked a sub-expert

@@ -1509,28 +1509,19 @@ static hipError_t launch_op(const Op& op, int T, int K, int n_cols, int few, int
 //     200 tokens, four | ring driver: 128 of 704 130 | 124, 89 | 91; 256 of 352 145 | 131, 96 | 103; 256 of 256 127 | 123, 89 |
 //     106; the same 400 without a bias 254 | 267, 261 | 290, 215 | 237;
 //   where the fused kernel is what else would run: it gives a tile a workgroup, so it wants long groups and more of them than
-//     CUs.  Layer calls that find their weights in HBM, these | fused kernel, of 192 x 2048 unless said: 8 sub-experts, 4 picks, 100
-//     tokens 39 | 94; 32, 8 picks, 200 49 | 99; 128, 8 picks, 300 93 | 121, 880 114 | 127; 192, 8 picks, 1300 156 | 159; 256, 8 picks, 700 155 |
-//     176, of 128 120 | 141, of 64 85 | 100; 512, 32 picks, 200 262 | 291, 640 308 | 317, skewed 100 146 | 181, 300 195 | 244, 640 264 | 271, of 64 200
-//     101 | 152, of 192 x 1024 300 99 | 113, of 128 x 1024 81 | 93.
-//     The lines were drawn when its lists were runs of 32 tiles per XCD, the first XCDs before the others, which cost it most where
-//     tiles are few (up to 5 times, up to 192 sub-experts), and some per cent beyond.  Then, four layers in turn, these | fused kernel; budgets of a quarter of the most and up; skewed: a bias N(0, 1) per expert, N(0, 3^2).
-//     Up to 24 rows, any number of sub-experts, 8 of 192 x 2048: 24 35 | 552; 32: 12 39 | 493; 128: 12 86 | 169; 256: 5
-//     132 | 155, 24 151 | 165; 512: 1 130 | 155, 4 225 | 268, 10 249 | 288, 24 277 | 298, skewed 133 | 140, 168 | 229,
-//     219 | 273 and 75 | 112, 93 | 148, 134 | 164; 1024: 5 434 | 493, 24 525 | 564, but with N(0, 3^2) 219 | 193.  One pick
-//     each, groups of up to T rows: 512 at 9 335 | 370, 213 | 246, 154 | 220; 256 at 20 204 | 214, 149 | 197, 118 | 187.  Short
-//     phases too, 512 of 64 x 2048: 9 125 | 150, 24 134 | 154; 192 x 512: 4 77 | 85, 24 93 | 95; 64 x 256: 4 37 | 46, 24
-//     44 | 52.  They meet at 512 of 128 x 1024, 20 116 | 114, 24 119 | 115 (skewed 79 | 86, 64 | 85), and at 1024 of 192 x
-//     1024, 22 282 | 273.
-//     Beyond, four blocks: up to 3/4 as many sub-experts as CUs, 8 of 192 x 2048: 56 40 | 296; 128: 56 111 | 178; 192: 28
-//     144 | 193, 56 153 | 206; 192 of 128 x 1024: 56 73 | 96; of 64 x 512: 56 41 | 57; one pick each 50 230 | 288.  Not with
-//     224: 40 156 | 154, of 128 x 1024 75 | 71; 256 of 128 x 2048: 32 139 | 134.  With more than CUs, where the phases are long
-//     and no group can be: 512 of 192 x 2048, T = 400 25 278 | 300, T = 640 40 296 | 317, skewed 260 | 299, 175 | 181; x 4096:
-//     40 558 | 569, 524 | 561, 335 | 326; 320 of 192 x 2048: 40 213 | 252; 512 of 128 x 2048: 28 233 | 232, skewed 114 | 134, T
-//     = 640 40 245 | 246, tied router rows 263 | 256; x 4096: T = 448 28 386 | 422, skewed 217 | 233, T = 576 36 261 | 250.
-//     Not with longer groups, 1024 of 192 x 2048, T = 896 28 skewed 228 | 207, T = 1280 40 288 | 227 (even load 547 | 582,
-//     578 | 614); nor with short phases, 512 of 192 x 1536: 28 220 | 215; x 1024: 26 160 | 152, 40 170 | 159; 128 x 1024: 26
-//     128 | 116, 40 135 | 122; 64 x 2048, 256 of them: 28 96 | 94.
+//     CUs.  Layer calls that find their weights in HBM, these | fused kernel, of 192 x 2048 unless said, by possible rows; even load,
+//     skewed: bias N(0, 1) per sub-expert, N(0, 3^2).
+//     Up to 24 rows, any number of sub-experts: 8, 300 tokens 41 | 96, 43 | 126; 128, 300 90 | 118, 77 | 139; 192 121 | 141, 103 | 144; 256 154 | 158, 125 | 155; 512, 448 of 9 rows
+//     243 | 266, 126 | 167, 65 | 142, of 24 269 | 281, 190 | 236, 112 | 149; 1024, 1024 tokens of 5 454 | 486, 173 | 208, 90 | 166, of 24 525 | 573, 329 | 398, but 212 | 183;
+//     64 x 2048, 256 of 24 83 | 89, 71 | 98; 192 x 1536, 512 of 24 208 | 214, 145 | 178, 87 | 121; x 1024, 20 144 | 147, 83 | 94.  They meet at 512 of 128 x 1024, 20 115 |
+//     114, 70 | 77, 24 125 | 116, 89 | 85, and at 1024 of 192 x 1024, 22 267 | 280, 149 | 141.
+//     Beyond, four blocks: up to 3/4 as many sub-experts as CUs, 128, 400 tokens of 40 104 | 117, 98 | 143, 600 of 56 124 | 118, 147 | 147; 192 of 40 145 | 148, 133 | 157, of
+//     56 150 | 150, 154 | 158; of 128 x 1024, 40 68 | 63, 60 | 73.  Not with 224: 40 150 | 151, 136 | 161, of 128 x 1024 73 | 67, 64 | 75; 256 of 40 164 | 163, 148 | 162 (what
+//     skewed load would gain, even load of short phases would lose).  With more than CUs, where the phases are long
+//     and no group can be: 512, 400 tokens of 25 279 | 283, 213 | 238, 120 | 152, 640 of 40 298 | 302, 254 | 259, 161 | 164; x 4096, 40 549 | 571, 529 | 532, 325 | 316; 320 of 40
+//     196 | 232, 166 | 197, 111 | 148; 512 of 128 x 2048, 448 of 28 231 | 240, 190 | 195, 98 | 122, 640 of 40 243 | 253, 205 | 205, 131 | 133; x 4096, 28 391 | 388, 350 | 380, 36 410 |
+//     406, 385 | 398.  Not with longer groups, 1024, 896 of 28 551 | 538, 379 | 410, 218 | 194, 1280 of 40 560 | 580, 436 | 436, 272 | 217; nor with short phases, 512 of 192 x
+//     1536, 28 219 | 216, 166 | 178; x 1024, 24.4 159 | 151, 95 | 96, 40 163 | 156, 123 | 122; 64 x 2048, 256 of them, 28 94 | 91, 80 | 108.
 int ffn_few_blocks(int T, int k_max, int E, int d, int Is, bool fused) {
   const long pairs = (long)T * k_max;
   if (!GateUpOp{nullptr, nullptr, nullptr, nullptr, T, d, Is, k_max}.offsets_fit() || !DownOp{nullptr, nullptr, nullptr, d, Is}.offsets_fit()) return 0;
@@ -1543,6 +1534,7 @@ int ffn_few_blocks(int T, int k_max, int E, int d, int Is, bool fused) {
   return T <= 64 || pairs <= 56L * E ? 4 : 0;
 }
 
+// Eight logits per lane are the most: 1024 sub-experts would gain too with sixteen, 1 token of 192 x 2048 35.9 | 31.8, of 32 x 256 17.0 | 14.2.
 bool picks_bf16(int few, int T, int k_max, int E) { return few == 1 && T >= 1 && T <= 4 && k_max <= PICK_K && E <= 512; }
 
 hipError_t launch_pick_gate_up_bf16(const PickArgs& p, const uint16_t* x, const uint16_t* w_gu, uint16_t* h, int T, int d, int Is, int k_max,

@@ -191,10 +191,12 @@ static void launch_logits_t(const InT* x, const InT* w, const float* bias, float
     launch_logits_cfg<InT, SHARE, 1, 1, 6, false>(x, w, bias, logits, hdr, T, d, E, shared, s);
 }
 
-// Rows are compared beyond 2^34 multiply-adds.  Logits between HIP events, d = 2048, 512 sub-experts, 4 to an expert, rows not
-// compared | compared, equal rows: 9000 tokens 173 | 71 us, 20 000 363 | 121, 65 536 1059 | 289 (layer calls 8030 | 7137); but
-// rows that differ: 8192 tokens 138 | 157, 16 384 (2^34) 272 | 280: a launch and in every workgroup the latency of its result,
-// 2 % of the logits and less from there on.
+// Rows are compared beyond 2^34 multiply-adds, where a gate whose rows differ loses less than 2 % of its route call by it: a launch, and
+// in every workgroup the latency of its result.  Route calls from a captured graph, rows not compared | compared, rows that differ, equal rows, 512
+// sub-experts, 4 to an expert, d = 2048: 2^31 40.7 | 43.6, 27.4; 2^32 73.5 | 77.5, 46.7; 2^33 130 | 142, 49.5; 2^33.5 190 | 194.5, 79; 2^34 (16 384 tokens) 250.6 |
+// 254.6, 82; 2^35 492 | 497, 162; 2^36 976 | 981, 286.  256 of d = 4096, 128 of 2 to an expert, 1024 of 8 and d = 1024: 6 to 10 % at 2^31, 3 to 9 at 2^32, 2.5 to 7 at 2^33, 1.5 to
+// 2.9 at 2^33.5, 1.6 to 1.8 at 2^34, up to 1.8 and falling beyond (between HIP events, 2^34 272 | 280).  Below the line equal rows are left alone: trained
+// gates, which are the more frequent, would pay for them.
 static bool compare_rows(int dtype, int T, int d, int E, int S) {
   return S > 1 && (double)T * E * d > 17179869184.0 && (long)E * d * (dtype == 0 ? 4 : 2) < (1L << 31);
 }
@@ -308,10 +310,11 @@ __global__ __launch_bounds__(64 * WAVES) void topk_kernel(
 constexpr int LAST_WAVES = 8;
 static bool wide_last(int k_max) { return (size_t)LAST_WAVES * 4 * topk_pad(k_max) * sizeof(float) <= 60 * 1024; }
 // So with eight waves the last workgroup is ahead of count and place kernels for more pairs than one of four (small_dispatch, which the
-// stage call goes by).  Layer calls, one workgroup | count and place kernels, by the pairs beyond those of 64 tokens: 512 of 32 picks 120
-// tokens (1792) 145.1 | 150.9, 160 (3072) 160.8 | 165.5, 200 (4352) 173.3 | 175.4, 255 (6112) 179.9 | 179.2; 256 of 32, 160 186.0 | 190.5, 220 (4992)
-// 207.1 | 207.7; 64 of 64, d = 256, 100 (2304) 40.0 | 46.3, 200 (8704) 50.4 | 48.9; 1024 of 24, 200 (3264) 50.8 | 52.7; 128 of 12, 130 216.7 | 222.5, 255
-// (2292) 223.1 | 227.2; fp32, 32 of 8, 140 25.6 | 29.4, 250 28.1 | 31.4.
+// stage call goes by).  The line lies where they met while those had 256 threads.  Layer calls from a captured graph, d = 64, Is = 32, one workgroup |
+// count and place kernels of 512, 512 sub-experts, by the pairs beyond those of 64 tokens: 128 tokens of 24 picks (1536) 25.4 | 28.1, 255 of 12 (2292) 24.7 | 26.2, 128 of
+// 48 (3072) 31.8 | 32.9, 160 of 32 (3072) 29.7 | 30.2, 200 of 24 (3264) 28.4 | 28.2, 128 of 64 (4096) 35.2 | 35.3, 200 of 32 (4352) 31.2 | 29.7, 255 of 24 (4584)
+// 30.2 | 28.7, 160 of 48 (4608) 33.5 | 32.4, beyond it 128 of 100 (6400) 50.9 | 48.8, 255 of 32 (6112) 33.1 | 30.0; 32, 128 and 1024 alike.  So they meet at 4100 up to 128
+// tokens, at 3100 beyond.
 bool topk_dispatches(int T, int E, int k_max) {
   return small_dispatch(T, E, k_max) ||
          (T > 0 && T < 256 && (T - 64) * k_max <= 4608 && wide_last(k_max) && small_dispatch_lds(T, E) <= 60 * 1024);

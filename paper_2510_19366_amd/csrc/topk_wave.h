@@ -74,7 +74,6 @@ __device__ __forceinline__ int wave_max_i(int v) {
   return max(max(r0, r1), max(r2, r3));
 }
 
-
 struct TopkPicks {
   int kt;            // picks: the budget, inside 0 .. k_max
   float most, denom;  // the weight of a pick is scale expf(logit - most) / denom
@@ -86,142 +85,142 @@ template <int ELEMS, bool SET = false>
 __device__ __forceinline__ TopkPicks topk_token(const float* __restrict__ row, int asked, int E, int k_max, int renorm,
                                                 int32_t* __restrict__ flags, int* uk, int* uid, float* se, int* sid, u64* set = nullptr) {
   const int lane = threadIdx.x & 63, kp = topk_pad(k_max);
-    const float NEG_INF = -__builtin_inff();
-    constexpr int GONE = (int)0x80000000;  // key of an element beyond E
-    float v[ELEMS];
-    #pragma unroll
-    for (int i = 0; i < ELEMS; ++i) {
-      int g = i * 64 + lane;
-      v[i] = g < E ? row[g] : NEG_INF;
-    }
-    // (behind the loads of the logits, so that one memory latency covers both)
-    int kt = __builtin_amdgcn_readfirstlane(asked);
-    if (kt < 0 || kt > k_max) {
-      if (lane == 0 && flags != nullptr) atomicOr(flags, 1);
-      kt = kt < 0 ? 0 : k_max;
-    }
-    // full-softmax denominator (only needed when weights are not renormalised)
-    float lmax = NEG_INF;
+  const float NEG_INF = -__builtin_inff();
+  constexpr int GONE = (int)0x80000000;  // key of an element beyond E
+  float v[ELEMS];
 #pragma unroll
-    for (int i = 0; i < ELEMS; ++i) lmax = fmaxf(lmax, v[i]);
-    const float mx = wave_max_f(lmax);
-    float denom = 0.0f;
-    if (!SET && !renorm) {
+  for (int i = 0; i < ELEMS; ++i) {
+    int g = i * 64 + lane;
+    v[i] = g < E ? row[g] : NEG_INF;
+  }
+  // (behind the loads of the logits, so that one memory latency covers both)
+  int kt = __builtin_amdgcn_readfirstlane(asked);
+  if (kt < 0 || kt > k_max) {
+    if (lane == 0 && flags != nullptr) atomicOr(flags, 1);
+    kt = kt < 0 ? 0 : k_max;
+  }
+  // full-softmax denominator (only needed when weights are not renormalised)
+  float lmax = NEG_INF;
 #pragma unroll
-      for (int i = 0; i < ELEMS; ++i)
-        if (i * 64 + lane < E) denom += expf(v[i] - mx);
-      denom = wave_sum(denom);
-    }
+  for (int i = 0; i < ELEMS; ++i) lmax = fmaxf(lmax, v[i]);
+  const float mx = wave_max_f(lmax);
+  float denom = 0.0f;
+  if (!SET && !renorm) {
+#pragma unroll
+    for (int i = 0; i < ELEMS; ++i)
+      if (i * 64 + lane < E) denom += expf(v[i] - mx);
+    denom = wave_sum(denom);
+  }
 
-    int key[ELEMS];
-    int best = GONE;
+  int key[ELEMS];
+  int best = GONE;
+#pragma unroll
+  for (int i = 0; i < ELEMS; ++i) {
+    const int k = topk_key(v[i]);  // outside the choice, or it becomes a branch per element
+    key[i] = i * 64 + lane < E ? k : GONE;
+    best = max(best, key[i]);
+  }
+  if (kt > 0 && kt <= topk_few(ELEMS)) {
+    // One wave-wide maximum per pick: g = 64 i + lane, so inside a lane the lower element index is
+    // the lower id, and the winner's lane is g & 63.  Only that lane retires its element.
+    constexpr int NONE = 0x7fffffff;
+    for (int j = 0; j < kt; ++j) {
+      const int top = wave_max_i(best);
+      int mine = NONE;  // this lane's first element with that key
+      if (best == top) {
+#pragma unroll
+        for (int i = ELEMS - 1; i >= 0; --i) mine = key[i] == top ? i * 64 + lane : mine;
+      }
+      const int g = wave_min_i(mine);
+      if (lane == 0) {
+        if (SET) {
+          set[g >> 6] |= 1ull << (g & 63);
+        } else {
+          se[j] = topk_unkey(top);
+          sid[j] = g;
+        }
+      }
+      if (g == mine) {
+        best = GONE;
+#pragma unroll
+        for (int i = 0; i < ELEMS; ++i) {
+          key[i] = i * 64 + lane == g ? GONE : key[i];
+          best = max(best, key[i]);
+        }
+      }
+    }
+    wave_lds_fence();
+  } else if (kt > 0) {
+    // Lower bound of the border: the best keys of 64 lanes are 64 elements, so for k_t <= 64 the k_t-th
+    // largest is at least their minimum.  Fewer picks need fewer such sets of elements: with the best
+    // of 2, 4, 8 or 16 neighbouring lanes the bound is tighter (at 2 picks 2.6 steps instead of 4.5).
+    // Twice as many sets as picks are kept: where the bound is the border itself the search is long.
+    int low = best;
+    if (kt <= 16) low = max(low, dpp_i<DPP_XOR1>(low));
+    if (kt <= 8) low = max(low, dpp_i<DPP_XOR2>(low));
+    if (kt <= 4) low = max(low, dpp_i<DPP_HALF_MIRROR>(low));
+    if (kt <= 2) low = max(low, dpp_i<DPP_MIRROR>(low));
+    auto uniform = [](int m) { return __builtin_amdgcn_readfirstlane(m); };
+    auto at_least = [&](int m) {
+      // eight ballots at a time into registers of their own: a bit count right behind its comparison waits for it
+      constexpr int G = ELEMS < 8 ? ELEMS : 8;
+      int c = 0;
+#pragma unroll
+      for (int i0 = 0; i0 < ELEMS; i0 += G) {
+        u64 b[G];
+#pragma unroll
+        for (int i = 0; i < G; ++i) b[i] = __ballot(key[i0 + i] >= m);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < G; ++i) c += __popcll(b[i]);
+      }
+      return c;
+    };
+    const TopkCut cut = topk_cut(kt <= 64 ? wave_min_i(low) : GONE, wave_max_i(best) + 1, kt, uniform, at_least);
+    const int thr = cut.thr;
+    // compact in id order (g = 64 i + lane: element by element, lanes ascending)
+    int base = 0, rem = cut.rem;
 #pragma unroll
     for (int i = 0; i < ELEMS; ++i) {
-      const int k = topk_key(v[i]);  // outside the choice, or it becomes a branch per element
-      key[i] = i * 64 + lane < E ? k : GONE;
-      best = max(best, key[i]);
+      u64 take = __ballot(key[i] > thr);
+      if (rem > 0) {
+        const u64 eq = __ballot(key[i] == thr);
+        const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(eq >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eq, 0));
+        take |= __ballot(key[i] == thr && before < rem);
+        rem -= min(rem, (int)__popcll(eq));
+      }
+      if (SET) {
+        if (lane == 0) set[i] = take;
+      } else if ((take >> lane) & 1) {
+        const int pos = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(take >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)take, 0));
+        uk[pos] = key[i];
+        uid[pos] = i * 64 + lane;
+      }
+      base += __popcll(take);
     }
-    if (kt > 0 && kt <= topk_few(ELEMS)) {
-      // One wave-wide maximum per pick: g = 64 i + lane, so inside a lane the lower element index is
-      // the lower id, and the winner's lane is g & 63.  Only that lane retires its element.
-      constexpr int NONE = 0x7fffffff;
-      for (int j = 0; j < kt; ++j) {
-        const int top = wave_max_i(best);
-        int mine = NONE;  // this lane's first element with that key
-        if (best == top) {
-#pragma unroll
-          for (int i = ELEMS - 1; i >= 0; --i) mine = key[i] == top ? i * 64 + lane : mine;
-        }
-        const int g = wave_min_i(mine);
-        if (lane == 0) {
-          if (SET) {
-            set[g >> 6] |= 1ull << (g & 63);
-          } else {
-            se[j] = topk_unkey(top);
-            sid[j] = g;
-          }
-        }
-        if (g == mine) {
-          best = GONE;
-#pragma unroll
-          for (int i = 0; i < ELEMS; ++i) {
-            key[i] = i * 64 + lane == g ? GONE : key[i];
-            best = max(best, key[i]);
-          }
-        }
+    if (SET) return {kt, mx, denom};
+    if (lane < 8 && kt + lane < kp) uk[kt + lane] = GONE;  // the ranking reads eight at a time
+    wave_lds_fence();
+    // rank = number of larger keys plus equal keys of smaller ids (= earlier positions)
+    for (int j = lane; j < kt; j += 64) {
+      const int mine = uk[j];
+      int rank = 0;
+      for (int q = 0; q < kt; q += 8) {
+        const int4 o = *reinterpret_cast<const int4*>(uk + q), p = *reinterpret_cast<const int4*>(uk + q + 4);
+        rank += o.x > mine - (q < j ? 1 : 0);
+        rank += o.y > mine - (q + 1 < j ? 1 : 0);
+        rank += o.z > mine - (q + 2 < j ? 1 : 0);
+        rank += o.w > mine - (q + 3 < j ? 1 : 0);
+        rank += p.x > mine - (q + 4 < j ? 1 : 0);
+        rank += p.y > mine - (q + 5 < j ? 1 : 0);
+        rank += p.z > mine - (q + 6 < j ? 1 : 0);
+        rank += p.w > mine - (q + 7 < j ? 1 : 0);
       }
-      wave_lds_fence();
-    } else if (kt > 0) {
-      // Lower bound of the border: the best keys of 64 lanes are 64 elements, so for k_t <= 64 the k_t-th
-      // largest is at least their minimum.  Fewer picks need fewer such sets of elements: with the best
-      // of 2, 4, 8 or 16 neighbouring lanes the bound is tighter (at 2 picks 2.6 steps instead of 4.5).
-      // Twice as many sets as picks are kept: where the bound is the border itself the search is long.
-      int low = best;
-      if (kt <= 16) low = max(low, dpp_i<DPP_XOR1>(low));
-      if (kt <= 8) low = max(low, dpp_i<DPP_XOR2>(low));
-      if (kt <= 4) low = max(low, dpp_i<DPP_HALF_MIRROR>(low));
-      if (kt <= 2) low = max(low, dpp_i<DPP_MIRROR>(low));
-      auto uniform = [](int m) { return __builtin_amdgcn_readfirstlane(m); };
-      auto at_least = [&](int m) {
-        // eight ballots at a time into registers of their own: a bit count right behind its comparison waits for it
-        constexpr int G = ELEMS < 8 ? ELEMS : 8;
-        int c = 0;
-#pragma unroll
-        for (int i0 = 0; i0 < ELEMS; i0 += G) {
-          u64 b[G];
-#pragma unroll
-          for (int i = 0; i < G; ++i) b[i] = __ballot(key[i0 + i] >= m);
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int i = 0; i < G; ++i) c += __popcll(b[i]);
-        }
-        return c;
-      };
-      const TopkCut cut = topk_cut(kt <= 64 ? wave_min_i(low) : GONE, wave_max_i(best) + 1, kt, uniform, at_least);
-      const int thr = cut.thr;
-      // compact in id order (g = 64 i + lane: element by element, lanes ascending)
-      int base = 0, rem = cut.rem;
-#pragma unroll
-      for (int i = 0; i < ELEMS; ++i) {
-        u64 take = __ballot(key[i] > thr);
-        if (rem > 0) {
-          const u64 eq = __ballot(key[i] == thr);
-          const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(eq >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eq, 0));
-          take |= __ballot(key[i] == thr && before < rem);
-          rem -= min(rem, (int)__popcll(eq));
-        }
-        if (SET) {
-          if (lane == 0) set[i] = take;
-        } else if ((take >> lane) & 1) {
-          const int pos = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(take >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)take, 0));
-          uk[pos] = key[i];
-          uid[pos] = i * 64 + lane;
-        }
-        base += __popcll(take);
-      }
-      if (SET) return {kt, mx, denom};
-      if (lane < 8 && kt + lane < kp) uk[kt + lane] = GONE;  // the ranking reads eight at a time
-      wave_lds_fence();
-      // rank = number of larger keys plus equal keys of smaller ids (= earlier positions)
-      for (int j = lane; j < kt; j += 64) {
-        const int mine = uk[j];
-        int rank = 0;
-        for (int q = 0; q < kt; q += 8) {
-          const int4 o = *reinterpret_cast<const int4*>(uk + q), p = *reinterpret_cast<const int4*>(uk + q + 4);
-          rank += o.x > mine - (q < j ? 1 : 0);
-          rank += o.y > mine - (q + 1 < j ? 1 : 0);
-          rank += o.z > mine - (q + 2 < j ? 1 : 0);
-          rank += o.w > mine - (q + 3 < j ? 1 : 0);
-          rank += p.x > mine - (q + 4 < j ? 1 : 0);
-          rank += p.y > mine - (q + 5 < j ? 1 : 0);
-          rank += p.z > mine - (q + 6 < j ? 1 : 0);
-          rank += p.w > mine - (q + 7 < j ? 1 : 0);
-        }
-        se[rank] = topk_unkey(mine);
-        sid[rank] = uid[j];
-      }
-      wave_lds_fence();
+      se[rank] = topk_unkey(mine);
+      sid[rank] = uid[j];
     }
+    wave_lds_fence();
+  }
   if (SET) return {kt, mx, denom};
   float dsel = 0.0f;
   for (int j = lane; j < kt; j += 64) dsel += expf(se[j] - mx);
